@@ -273,15 +273,46 @@ struct Streamer {
   }
 };
 
+// The two products on (a block of) A.  Wide fp32 panels go to the split kernels; their packed right panel lives in the work
+// area of the TSQR route (8 bytes per panel element, of which 6 are used), which is only in use inside an orthonormalisation.
+template <typename T>
+bool uses_split(brsvd_handle h, int64_t out, int64_t K, int64_t lda) {
+  return sizeof(T) == 4 && split_fits(out, K, h->Lp, lda, h->lay.tsqr_bytes);
+}
+
+template <typename T>
+int product_an(brsvd_handle h, const T* A, int64_t lda, int64_t rows, const T* X, T* Y, const KernelEvents* ke) {
+  const int Lp = h->Lp;
+  void* scr = h->arena + h->lay.gemm_scratch;
+  if constexpr (sizeof(T) == 4) {
+    if (uses_split<T>(h, rows, h->prm.n, lda))
+      return split_gemm_an(A, lda, rows, h->prm.n, X, Lp, Lp, Lp, Y, Lp, Lp, scr, h->lay.gemm_scratch_bytes,
+                           h->arena + h->lay.tsqr, h->lay.tsqr_bytes, h->compute, ke);
+  }
+  return gemm_an(A, lda, rows, h->prm.n, X, Lp, Y, Lp, Lp, scr, h->lay.gemm_scratch_bytes, h->compute, ke);
+}
+
+template <typename T>
+int product_at(brsvd_handle h, const T* A, int64_t lda, int64_t rows, const T* Q, T* Z, bool accumulate,
+               const KernelEvents* ke) {
+  const int Lp = h->Lp;
+  void* scr = h->arena + h->lay.gemm_scratch;
+  if constexpr (sizeof(T) == 4) {
+    if (uses_split<T>(h, h->prm.n, rows, lda))
+      return split_gemm_at(A, lda, rows, h->prm.n, Q, Lp, Lp, Lp, Z, Lp, Lp, accumulate, scr, h->lay.gemm_scratch_bytes,
+                           h->arena + h->lay.tsqr, h->lay.tsqr_bytes, h->compute, ke);
+  }
+  return gemm_at(A, lda, rows, h->prm.n, Q, Lp, Z, accumulate, rows, scr, h->lay.gemm_scratch_bytes, h->compute, ke);
+}
+
 template <typename T>
 int pass_an(brsvd_handle h, const T* A, int64_t lda, const T* X, T* Y) {
   const int Lp = h->Lp;
   const int64_t m = h->prm.m, n = h->prm.n;
-  void* scr = h->arena + h->lay.gemm_scratch;
   if (!h->host_a) {
     KernelEvents ke;
     bool t = kernel_events(h, CAT_AN, m, &ke);
-    return gemm_an(A, lda, m, n, X, Lp, Y, Lp, Lp, scr, h->lay.gemm_scratch_bytes, h->compute, t ? &ke : nullptr);
+    return product_an<T>(h, A, lda, m, X, Y, t ? &ke : nullptr);
   }
   Streamer st(h, A, lda);
   for (int i = 0; i < h->nblocks; ++i) {
@@ -289,8 +320,7 @@ int pass_an(brsvd_handle h, const T* A, int64_t lda, const T* X, T* Y) {
     BRSVD_TRY(st.acquire(i, &blk));
     KernelEvents ke;
     bool t = kernel_events(h, CAT_AN, st.rows_of(i), &ke);
-    BRSVD_TRY(gemm_an(blk, n, st.rows_of(i), n, X, Lp, Y + (int64_t)i * h->b * Lp, Lp, Lp, scr,
-                      h->lay.gemm_scratch_bytes, h->compute, t ? &ke : nullptr));
+    BRSVD_TRY(product_an<T>(h, blk, n, st.rows_of(i), X, Y + (int64_t)i * h->b * Lp, t ? &ke : nullptr));
     BRSVD_TRY(st.release(i));
   }
   return BRSVD_OK;
@@ -300,14 +330,12 @@ template <typename T>
 int pass_at(brsvd_handle h, const T* A, int64_t lda, const T* Q, T* Z) {
   const int Lp = h->Lp;
   const int64_t m = h->prm.m, n = h->prm.n;
-  void* scr = h->arena + h->lay.gemm_scratch;
   if (!h->host_a) {
     KernelEvents ke;
     bool t = kernel_events(h, CAT_AT, m, &ke);
     // device-resident A: one launch over all rows; the row range is cut into equal sub-ranges whose partial
     // panels are added in row order (the row blocks matter only when A is streamed block by block)
-    return gemm_at(A, lda, m, n, Q, Lp, Z, false, m, scr, h->lay.gemm_scratch_bytes, h->compute,
-                   t ? &ke : nullptr);
+    return product_at<T>(h, A, lda, m, Q, Z, false, t ? &ke : nullptr);
   }
   Streamer st(h, A, lda);
   for (int i = 0; i < h->nblocks; ++i) {
@@ -315,8 +343,7 @@ int pass_at(brsvd_handle h, const T* A, int64_t lda, const T* Q, T* Z) {
     BRSVD_TRY(st.acquire(i, &blk));
     KernelEvents ke;
     bool t = kernel_events(h, CAT_AT, st.rows_of(i), &ke);
-    BRSVD_TRY(gemm_at(blk, n, st.rows_of(i), n, Q + (int64_t)i * h->b * Lp, Lp, Z, i > 0, st.rows_of(i), scr,
-                      h->lay.gemm_scratch_bytes, h->compute, t ? &ke : nullptr));
+    BRSVD_TRY(product_at<T>(h, blk, n, st.rows_of(i), Q + (int64_t)i * h->b * Lp, Z, i > 0, t ? &ke : nullptr));
     BRSVD_TRY(st.release(i));
   }
   return BRSVD_OK;
@@ -328,7 +355,6 @@ template <typename T>
 int pass_fused(brsvd_handle h, const T* A, int64_t lda, const T* X, T* Tm_, T* Z) {
   const int Lp = h->Lp;
   const int64_t n = h->prm.n;
-  void* scr = h->arena + h->lay.gemm_scratch;
   if (!h->host_a) {
     BRSVD_TRY(pass_an<T>(h, A, lda, X, Tm_));
     return pass_at<T>(h, A, lda, Tm_, Z);
@@ -340,11 +366,9 @@ int pass_fused(brsvd_handle h, const T* A, int64_t lda, const T* X, T* Tm_, T* Z
     T* Ti = Tm_ + (int64_t)i * h->b * Lp;
     KernelEvents ke;
     bool t = kernel_events(h, CAT_AN, st.rows_of(i), &ke);
-    BRSVD_TRY(gemm_an(blk, n, st.rows_of(i), n, X, Lp, Ti, Lp, Lp, scr, h->lay.gemm_scratch_bytes, h->compute,
-                      t ? &ke : nullptr));
+    BRSVD_TRY(product_an<T>(h, blk, n, st.rows_of(i), X, Ti, t ? &ke : nullptr));
     t = kernel_events(h, CAT_AT, st.rows_of(i), &ke);
-    BRSVD_TRY(gemm_at(blk, n, st.rows_of(i), n, Ti, Lp, Z, i > 0, st.rows_of(i), scr, h->lay.gemm_scratch_bytes,
-                      h->compute, t ? &ke : nullptr));
+    BRSVD_TRY(product_at<T>(h, blk, n, st.rows_of(i), Ti, Z, i > 0, t ? &ke : nullptr));
     BRSVD_TRY(st.release(i));
   }
   return BRSVD_OK;
@@ -481,7 +505,7 @@ int enqueue_alg2(brsvd_handle h, const T* A, int64_t lda, uint64_t seed, const T
     auto at = [&](const T* Qp, T* Z, bool accumulate) {
       KernelEvents ke;
       bool t = kernel_events(h, CAT_AT, rows, &ke);
-      return gemm_at(blk, ldb, rows, n, Qp, Lp, Z, accumulate, rows, scr, scr_bytes, cs, t ? &ke : nullptr);
+      return product_at<T>(h, blk, ldb, rows, Qp, Z, accumulate, t ? &ke : nullptr);
     };
     if (q == 0) {
       BRSVD_TRY(at(OmI, Yn, i > 0));
@@ -490,7 +514,7 @@ int enqueue_alg2(brsvd_handle h, const T* A, int64_t lda, uint64_t seed, const T
       for (int t = 0; t < q; ++t) {
         KernelEvents ke;
         bool tm = kernel_events(h, CAT_AN, rows, &ke);
-        BRSVD_TRY(gemm_an(blk, ldb, rows, n, Pn1, Lp, TI, Lp, Lp, scr, scr_bytes, cs, tm ? &ke : nullptr));
+        BRSVD_TRY(product_an<T>(h, blk, ldb, rows, Pn1, TI, tm ? &ke : nullptr));
         const bool last = t == q - 1;
         BRSVD_TRY(at(TI, last ? Yn : Pn1, last && i > 0));
       }
@@ -856,6 +880,10 @@ int step_gemm_an(const T* A, int64_t lda, int64_t rows, int64_t n, const T* X, i
   T* Xp = (T*)scratch;
   char* part = (char*)scratch + 2 * panel;
   hipStream_t s = (hipStream_t)stream;
+  if constexpr (sizeof(T) == 4) {      // the packed right panel takes the place of the two padded panels
+    if (split_fits(rows, n, Lp, lda, 2 * panel))
+      return split_gemm_an(A, lda, rows, n, X, l, l, Lp, Y, l, l, part, scratch_bytes - 2 * panel, scratch, 2 * panel, s);
+  }
   BRSVD_TRY(pad_panel(X, n, l, Xp, Lp, s));
   return gemm_an(A, lda, rows, n, Xp, Lp, Y, l, l, part, scratch_bytes - 2 * panel, s);
 }
@@ -871,6 +899,11 @@ int step_gemm_at(const T* A, int64_t lda, int64_t rows, int64_t n, const T* Q, i
   T* Zp = (T*)((char*)scratch + panel);
   char* part = (char*)scratch + 2 * panel;
   hipStream_t s = (hipStream_t)stream;
+  if constexpr (sizeof(T) == 4) {
+    if (split_fits(n, rows, Lp, lda, 2 * panel))
+      return split_gemm_at(A, lda, rows, n, Q, l, l, Lp, Z, l, l, accumulate != 0, part, scratch_bytes - 2 * panel, scratch,
+                           2 * panel, s);
+  }
   BRSVD_TRY(pad_panel(Q, rows, l, Qp, Lp, s));
   BRSVD_TRY(gemm_at(A, lda, rows, n, Qp, Lp, Zp, false, rows, part, scratch_bytes - 2 * panel, s));
   return unpad_panel(Zp, n, Lp, l, Z, accumulate != 0, s);

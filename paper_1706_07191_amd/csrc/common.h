@@ -59,6 +59,75 @@ int gemm_at(const double* A, int64_t lda, int64_t rows, int64_t n, const double*
             double* Z, bool accumulate, int64_t block_rows, void* scratch, uint64_t scratch_bytes,
             hipStream_t stream, const KernelEvents* ev = nullptr);
 
+// Work partition of Y = A X (described at k_gemm_an): C chunks per tile, whole and leftover row tiles, f main splits,
+// tail strips of x chunks, j of them per workgroup.
+struct AnShape {
+  int C, whole, lt, f, x, j;
+};
+// The part of workgroup b: chunks [c0, c1) of nseg row tiles from first_tile on, into Y or into partial panel `slot`.
+struct AnWork {
+  int first_tile, nseg, c0, c1, slot;
+  bool partial;
+};
+__host__ __device__ inline AnWork an_work(const AnShape& sh, int b) {
+  AnWork w;
+  w.nseg = 1;
+  w.slot = 0;
+  w.partial = true;
+  const int C = sh.C;
+  if (b < sh.whole) {
+    w.first_tile = b; w.c0 = 0; w.c1 = C; w.partial = false;
+  } else if (b < sh.whole + sh.lt * sh.f) {
+    const int idx = b - sh.whole, s = idx % sh.f;
+    w.first_tile = sh.whole + idx / sh.f;
+    w.c0 = (int)((int64_t)s * (C - sh.x) / sh.f);
+    w.c1 = (int)((int64_t)(s + 1) * (C - sh.x) / sh.f);
+    w.slot = s;
+  } else {
+    const int i = b - sh.whole - sh.lt * sh.f, left = sh.whole + sh.lt;
+    w.first_tile = sh.whole + i * sh.j;
+    w.nseg = sh.j < left - w.first_tile ? sh.j : left - w.first_tile;
+    w.c0 = C - sh.x; w.c1 = C; w.slot = sh.f;
+  }
+  return w;
+}
+AnShape an_shape(int T, int C, int S, int min_piece, int min_strip);
+
+// ---- pieces of the planners and the split sum, shared by gemm_thin.hip and gemm_split.hip ----
+struct NGroups {
+  int groups, nt;   // column groups per launch sequence, n-tiles per group
+};
+NGroups column_groups(int Lp, int esz);
+double traffic_weight(int nt);
+int pick_splits(int64_t tiles, int slots, int64_t units, double out_over_in, double traffic_weight, int max_splits);
+int reduce_splits_f32(float* part, int nsplit, int64_t split_stride, int64_t rows, int ncols, int64_t ldi, float* out,
+                      int64_t ldo, bool accumulate, hipStream_t stream);
+
+// ---- the same two products for wide fp32 panels on the bf16 matrix cores (gemm_split.hip) ----
+// out x K (an) or K x out (at) is the part of A multiplied; pack is device memory for the split right panel.
+// Taken for contractions of at least 512, 48 padded columns and 2^22 elements of A.  Measured, plain fp32 kernel and this one
+// (us, A X / A^T Q): 100000x50000 l=272 20944 / 21274 and 12640 / 13114; 20000x20000 l=110 877 / 791 and 514 / 514; 89083x2783
+// l=97 583 / 748 and 336 / 343; 76800x2000 l=40 189 / 197 and 165 / 148; 4000x4000 l=48 36.8 / 30.9 and 31.9 / 25.6; below the
+// bound the extra launches cost what the product saves: 2000x1000 l=60 21.2 / 23.6 and 24.2 / 18.0, 1024x1024 l=300
+// 79 / 35.6 and 73 / 36.8.
+constexpr int64_t kSplitMinK = 512, kSplitMinOut = 64, kSplitMinLp = 48, kSplitMinA = 1 << 22;
+struct SplitPlan {
+  int tile, groups, nt, nsplit, wgs;           // rows (columns of A) per workgroup, column groups, tiles per group, partial panels
+  AnShape sh;                                  // an
+  int64_t partial_rows;                        // an: rows of the partial panels
+  int col_tiles, blocks, blocks_per_sub;       // at: column tiles, blocks of 32 rows in all and per sub-range
+};
+SplitPlan split_an_plan(int64_t rows, int64_t K, int Lp, uint64_t scratch_bytes);
+SplitPlan split_at_plan(int64_t rows, int64_t n, int Lp, uint64_t scratch_bytes);
+bool split_fits(int64_t out, int64_t K, int Lp, int64_t lda, uint64_t pack_bytes);
+// X (K x xcols, leading dimension ldx) and Q (rows x qcols, ldq) need no padding; Lp = padded width of the partial panels.
+int split_gemm_an(const float* A, int64_t lda, int64_t rows, int64_t K, const float* X, int64_t ldx, int xcols, int Lp,
+                  float* Y, int64_t ldy, int ncols, void* scratch, uint64_t scratch_bytes, void* pack,
+                  uint64_t pack_bytes, hipStream_t stream, const KernelEvents* ev = nullptr);
+int split_gemm_at(const float* A, int64_t lda, int64_t rows, int64_t n, const float* Q, int64_t ldq, int qcols, int Lp,
+                  float* Z, int64_t ldz, int ncols, bool accumulate, void* scratch, uint64_t scratch_bytes, void* pack,
+                  uint64_t pack_bytes, hipStream_t stream, const KernelEvents* ev = nullptr);
+
 // Launch plans as numbers (see brsvd_gemm_plan in the C ABI).
 void gemm_an_plan_describe(int64_t rows, int64_t K, int Lp, int esz, int32_t out[12]);
 void gemm_at_plan_describe(int64_t rows, int64_t n, int Lp, int64_t block_rows, int esz, int32_t out[12]);

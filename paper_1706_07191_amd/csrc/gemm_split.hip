@@ -1,0 +1,533 @@
+// The two thin products of gemm_thin.hip for wide fp32 panels (more than 32 columns) on the bf16 matrix cores, with
+// every fp32 operand split exactly into three bf16 numbers:
+//
+//   a = h + m + l,   h = the upper 16 bits of a (8 significant bits), m = bf16(a - h), l = a - h - m
+//
+// (24 significant bits = 8 + 8 + 8, so nothing of a is lost, at any exponent).  Of the nine products of two such
+// sums the six above 2^-24 are taken, l*h + h*l + m*m + m*h + h*m + h*h: six v_mfma_f32_16x16x32_bf16 do the work of
+// eight v_mfma_f32_16x16x4_f32 in 96 cycles instead of 256.  The dropped products are below 2^-22 of |a||x| at most and
+// 2^-26 on average, and random in sign.
+//
+// Accuracy.  The bf16 instruction truncates its sum to fp32 instead of rounding it, which over a long contraction
+// would add up to a bias (K = 20000, entries N(0.5, 1): 5e-6, against 2.2e-6 for the fp32 instruction).  So the six
+// products of one block of 32 contraction indices are added into a register tile that starts from zero, smallest
+// products first -- only the last one can truncate anything that matters -- and that tile is added to the
+// running sum by rounded fp32 additions.  That makes K/32 additions where the fp32 instruction makes K/4 or more:
+// measured error against fp64, this kernel and the fp32 instruction: K = 112 6.1e-8 and 1.9e-7, K = 1000 1.2e-7
+// and 5.5e-7, K = 20000 4.7e-7 and 2.5e-6 (N(0,1) entries); K = 20000, N(0.5,1): 3.8e-7 and 2.2e-6.
+//
+// Both products are one kernel.  The contraction runs over blocks of 32 (columns of A for Y = A X, rows of A for
+// Z = A^T Q); the right panel is split once per call into the operand layout of the instruction (k_split_pack), A is
+// split in registers on its way into the matrix cores:
+//   operands: lane = 16*g + r holds eight contraction indices 4*g + {0..3}, 16 + 4*g + {0..3} of the block (any
+//   assignment is allowed as long as both operands share it), for row / column r; D: component v of lane (r, g) is
+//   entry [4*g + v][r].
+#include <algorithm>
+
+#include "common.h"
+
+namespace brsvd {
+
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+
+constexpr int kSplitB = 32;          // contraction indices per block
+constexpr int kFragU = 64;           // 16-byte units of one operand fragment (16 x 32 bf16)
+
+struct Frag3 { uintx4 p[3]; };       // h, m, l of eight contraction indices
+
+__device__ __forceinline__ floatx4 mfma_bf16(uintx4 a, uintx4 b, floatx4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ unsigned pack_bf16(float a, float b) {
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{a, b}, bf16x2));
+}
+// Pair q (elements 2q, 2q + 1) of a fragment.
+__device__ __forceinline__ void split_pair(float a, float b, Frag3& f, int q) {
+  const unsigned ua = __float_as_uint(a), ub = __float_as_uint(b);
+  f.p[0][q] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);              // the two upper halves
+  float ra = a - __uint_as_float(ua & 0xffff0000u), rb = b - __uint_as_float(ub & 0xffff0000u);
+  const unsigned m = pack_bf16(ra, rb);
+  f.p[1][q] = m;
+  ra -= __uint_as_float(m << 16);
+  rb -= __uint_as_float(m & 0xffff0000u);
+  f.p[2][q] = pack_bf16(ra, rb);
+}
+
+// First contraction index of block `blk`: the last blocks are moved back so that they end with the range, and the
+// indices the block before has already covered are zero in the packed panel.  Neither operand is then ever read
+// outside its range, and A needs no masks.  K >= kSplitB.
+__device__ __forceinline__ int64_t block_start(int64_t blk, int64_t K) { return min(blk * kSplitB, K - kSplitB); }
+
+// Packed panel: [block][column tile][h, m, l][lane][8 bf16], i.e. 3 KiB per block and tile of 16 columns; an even number of
+// blocks.  src: K x cols, leading dimension ld; columns cols.. are zero.  Also clears the flag of the products.
+__global__ void __launch_bounds__(256)
+k_split_pack(const float* __restrict__ src, int64_t K, int64_t ld, int cols, int nt_total, int64_t blocks,
+             uintx4* __restrict__ out, int* __restrict__ flag) {
+  const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (id == 0) *flag = 0;
+  const int lane = (int)(id & 63), r = lane & 15, g = lane >> 4;
+  const int64_t tile = id >> 6, blk = tile / nt_total;
+  if (blk >= blocks) return;
+  const int nt = (int)(tile - blk * nt_total), col = 16 * nt + r;
+  const int64_t k0 = block_start(blk, K);
+  float v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int64_t k = k0 + (e >> 2) * 16 + 4 * g + (e & 3);
+    v[e] = k >= blk * kSplitB && col < cols ? src[k * ld + col] : 0.f;
+  }
+  Frag3 f;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) split_pair(v[2 * q], v[2 * q + 1], f, q);
+  uintx4* o = out + tile * (3 * kFragU) + lane;
+#pragma unroll
+  for (int p = 0; p < 3; ++p) o[p * kFragU] = f.p[p];
+}
+
+template <int I, int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<I + 1, N>(f);
+  }
+}
+
+// What one workgroup multiplies: `blocks` blocks (even) of the contraction from block `b0` on, and where its result goes.
+struct SplitTile {
+  const float* A;        // Y = A X: first row of the tile;  Z = A^T Q: first row of A
+  int64_t lda;
+  int64_t K;             // length of the contraction
+  int64_t b0;
+  int blocks;
+  int first, count;      // first row (column) of the tile and how many rows (columns) the output has in all
+  float* out;            // row `first` of the output is out + first * ldo
+  int64_t ldo;
+  int ncols;
+};
+
+// Workgroup: WR x WC waves; wave (wr, wc) owns MT tiles of 16 rows (AT: columns of A) and NTW tiles of the panel's
+// columns.  Wave column 0 owns the first NTW tiles, wave column 1 the rest; the waves of one SIMD are one of each.
+//
+// What bounds it: the matrix cores and the power they may draw (16 cycles per instruction, 204 of them per
+// 32 x 32 x 272 block step; the clock falls to 1.7-1.9 GHz under full load), so everything else is spread over the
+// stream of matrix instructions in small portions between scheduling barriers: the reads of the next tile's panel
+// fragments from LDS, the addition of the previous tile's block sum, the split of the next block's part of A with
+// the loads of the block after that, and the hand-over of the next block's packed panel from registers to LDS.  One barrier
+// per block.  A first version that did these things between the blocks ran at 75-85 % of this one.
+template <bool AT, int NT, int NTW, int MT, int WR, int WC>
+__device__ __forceinline__ bool split_tile(const SplitTile& s, const uintx4* __restrict__ XP, int64_t xstride, uintx4* lds,
+                                           int wr, int nt0) {
+  constexpr int NTH = WR * WC * 64;
+  constexpr int BUF = NT * 3 * kFragU;                 // 16-byte units of one staged block
+  constexpr int XPT = (BUF + NTH - 1) / NTH;
+  constexpr int SL = NTW * 6;                          // slots of matrix instructions per block
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+  const int w0 = s.first + wr * (MT * 16);             // first row (column) of this wave
+
+  // Byte offsets of this lane's loads from a uniform base (below 2^32: see split_fits).  Rows past the end repeat the last one, columns past the end the
+  // last MT; their results are not stored, or stored twice with the same value.
+  unsigned off[AT ? 1 : MT];
+  int c0 = 0;
+  if constexpr (AT) {
+    c0 = max(0, min(w0 + MT * r, s.count - MT));
+    off[0] = (unsigned)((4 * g * s.lda + c0) * 4);
+  } else {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) off[mt] = (unsigned)(((min(w0 + mt * 16 + r, s.count - 1) - s.first) * s.lda + 4 * g) * 4);
+  }
+  typedef float vecM __attribute__((ext_vector_type(MT)));
+  typedef vecM vecMu __attribute__((aligned(4)));
+  typedef floatx4 floatx4u __attribute__((aligned(4)));
+
+  floatx4 acc[MT][NTW], t[2][MT], tl[MT];
+  floatx4 ra[MT][2];                                   // Y = A X: [tile][half block] four indices of one row
+  vecM rq[8];                                          // Z = A^T Q: [index] MT columns of one row of A
+  Frag3 fa[MT], fb[MT];
+  uintx4 xr[XPT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    tl[mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int nt = 0; nt < NTW; ++nt) acc[mt][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+  }
+  const int last = s.blocks - 1;
+  auto xid = [&](int x) { return min(tid + x * NTH, BUF - 1); };
+  auto load_x = [&](int x, const uintx4* src) { xr[x] = src[xid(x)]; };
+  // base of block c: A + k0 (row part of the address is in off) or A + k0 * lda
+  auto block_base = [&](int c) {
+    const int64_t k0 = block_start(s.b0 + c, s.K);
+    return (const char*)(s.A + (AT ? k0 * s.lda : k0));
+  };
+  // the loads that become possible once pairs 0..p of the block have been split
+  auto load_a = [&](int p, const char* base) {
+    if constexpr (AT) {
+      if (p % MT == MT - 1) {
+        const int q = p / MT;                          // pair q of every tile is done: rows 2q, 2q + 1 are free
+#pragma unroll
+        for (int e = 2 * q; e < 2 * q + 2; ++e)
+          rq[e] = *(const vecMu*)(base + (int64_t)((e >> 2) * 16 + (e & 3)) * s.lda * 4 + off[0]);
+      }
+    } else {
+      if (p & 1) ra[p >> 2][(p >> 1) & 1] = *(const floatx4u*)(base + ((p >> 1) & 1) * 64 + off[p >> 2]);
+    }
+  };
+  auto split_a = [&](int p, Frag3 (&f)[MT]) {
+    if constexpr (AT) {
+      const int q = p / MT, mt = p % MT;
+      split_pair(rq[2 * q][mt], rq[2 * q + 1][mt], f[mt], q);
+    } else {
+      const int mt = p >> 2, q = p & 3;
+      split_pair(ra[mt][q >> 1][2 * (q & 1)], ra[mt][q >> 1][2 * (q & 1) + 1], f[mt], q);
+    }
+  };
+
+  const uintx4* xb = XP + s.b0 * xstride;
+  {
+    const char* base = block_base(0);
+    static_for<0, XPT>([&](auto x) { load_x(x, xb); });
+    static_for<0, 4 * MT>([&](auto p) { load_a(p, base); });
+    const uintx4* xb1 = xb + xstride;
+    static_for<0, XPT>([&](auto x) { lds[xid(x)] = xr[x]; load_x(x, xb1); });
+    base = block_base(1);
+    static_for<0, 4 * MT>([&](auto p) { split_a(p, fa); load_a(p, base); });
+  }
+  __syncthreads();
+
+  auto block = [&](int c, const Frag3 (&cf)[MT], Frag3 (&nf)[MT]) __attribute__((always_inline)) {
+    const uintx4* bb = lds + (c & 1) * BUF + nt0 * (3 * kFragU) + lane;
+    uintx4* nxt = lds + ((c & 1) ^ 1) * BUF;
+    const int c2 = min(c + 2, last);
+    const uintx4* x2 = xb + c2 * xstride;
+    const char* base2 = block_base(c2);
+    uintx4 b[2][3];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) b[0][p] = bb[p * kFragU];
+    static_for<0, SL>([&](auto slot) __attribute__((always_inline)) {
+      constexpr int sl = decltype(slot)::value, nt = sl / 6, i = sl % 6;
+      constexpr int pa = i == 0 ? 2 : (i == 2 || i == 3 ? 1 : 0);        // l m h of A: l*h, h*l, m*m, m*h, h*m, h*h
+      constexpr int pb = i == 1 ? 2 : (i == 2 || i == 4 ? 1 : 0);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+        t[nt & 1][mt] = mfma_bf16(cf[mt].p[pa], b[nt & 1][pb], i == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : t[nt & 1][mt]);
+      // split of the next block's part of A, and the loads of the block after it into the freed registers
+#pragma unroll
+      for (int p = sl * (4 * MT) / SL; p < (sl + 1) * (4 * MT) / SL; ++p) { split_a(p, nf); load_a(p, base2); }
+      // the next block's packed panel goes to LDS, the one after it is requested
+#pragma unroll
+      for (int x = sl * XPT / SL; x < (sl + 1) * XPT / SL; ++x) { nxt[xid(x)] = xr[x]; load_x(x, x2); }
+      // the previous tile's block sum
+      constexpr int pv = (nt + NTW - 1) % NTW;
+#pragma unroll
+      for (int e = i * (4 * MT) / 6; e < (i + 1) * (4 * MT) / 6; ++e)
+        acc[e >> 2][pv][e & 3] += nt == 0 ? tl[e >> 2][e & 3] : t[(nt + 1) & 1][e >> 2][e & 3];
+      if constexpr (nt + 1 < NTW && i < 3) b[(nt + 1) & 1][i] = bb[((nt + 1) * 3 + i) * kFragU];
+    });
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) tl[mt] = t[(NTW - 1) & 1][mt];
+    __syncthreads();
+  };
+#pragma nounroll
+  for (int c = 0; c < s.blocks; c += 2) {
+    block(c, fa, fb);
+    block(c + 1, fb, fa);
+  }
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) acc[mt][NTW - 1] += tl[mt];
+
+  float worst = 0.f;                                   // NaN as soon as one result is not finite
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = 4 * g + v;
+      // row i of tile mt is the mt-th of the MT columns lane i loaded (AT), or row 16 * mt + i
+      const int row = AT ? max(0, min(w0 + MT * i, s.count - MT)) + mt : w0 + mt * 16 + i;
+      const bool valid = AT ? w0 + MT * i < s.count : row < s.count;
+      if (valid) {
+        float* o = s.out + (int64_t)row * s.ldo;
+#pragma unroll
+        for (int nt = 0; nt < NTW; ++nt) {
+          const int col = (nt0 + nt) * 16 + r;
+          const float y = acc[mt][nt][v];
+          if (col < s.ncols) { o[col] = y; worst += y * 0.f; }
+        }
+      }
+    }
+  return !(worst == 0.f);
+}
+
+template <bool AT, int NT, int MT, int WR, int WC>
+__device__ __forceinline__ void split_tile_waves(const SplitTile& s, const uintx4* XP, int64_t xstride, uintx4* lds, int* flag) {
+  constexpr int NTW = (NT + WC - 1) / WC;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wr = wave % WR, wc = wave / WR;
+  bool bad;
+  if constexpr (NT % WC == 0) {
+    bad = split_tile<AT, NT, NTW, MT, WR, WC>(s, XP, xstride, lds, wr, wc * NTW);
+  } else {
+    if (wc == 0) bad = split_tile<AT, NT, NTW, MT, WR, WC>(s, XP, xstride, lds, wr, 0);
+    else bad = split_tile<AT, NT, NTW - 1, MT, WR, WC>(s, XP, xstride, lds, wr, NTW);
+  }
+  if (bad) *flag = 1;
+}
+
+// Y = A X.  Work partition and partial panels as in k_gemm_an (AnShape), in chunks of two blocks.
+template <int NT, int MT, int WR, int WC>
+__global__ void __launch_bounds__(WR * WC * 64)
+k_split_an(const float* __restrict__ A, int64_t lda, int rows, int K, const uintx4* __restrict__ XP, int64_t xstride,
+           float* __restrict__ Y, int64_t ldy, int ncols, float* __restrict__ Part, int64_t ldp, int64_t split_stride,
+           AnShape sh, int* __restrict__ flag) {
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  constexpr int TR = WR * MT * 16;
+  const AnWork w = an_work(sh, blockIdx.x);
+  for (int seg = 0; seg < w.nseg; ++seg) {
+    SplitTile s;
+    s.first = (w.first_tile + seg) * TR;
+    s.A = A + (int64_t)s.first * lda;
+    s.lda = lda;
+    s.K = K;
+    s.b0 = 2 * (int64_t)w.c0;
+    s.blocks = 2 * (w.c1 - w.c0);
+    s.count = rows;
+    s.out = w.partial ? Part + (int64_t)w.slot * split_stride - (int64_t)sh.whole * TR * ldp : Y;
+    s.ldo = w.partial ? ldp : ldy;
+    s.ncols = w.partial ? NT * 16 : ncols;
+    split_tile_waves<false, NT, MT, WR, WC>(s, XP, xstride, (uintx4*)lds_raw, flag);
+    __syncthreads();                                   // before the next strip reuses the staging buffers
+  }
+}
+
+// Partial panel blockIdx.y of Z = A^T Q: blocks [y * blocks_per_sub, ...) of the rows.
+template <int NT, int MT, int WR, int WC>
+__global__ void __launch_bounds__(WR * WC * 64)
+k_split_at(const float* __restrict__ A, int64_t lda, int64_t rows, int n, const uintx4* __restrict__ QP, int64_t xstride,
+           float* __restrict__ Zpart, int64_t ldz, int64_t split_stride, int blocks, int blocks_per_sub,
+           int* __restrict__ flag) {
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  SplitTile s;
+  s.A = A;
+  s.lda = lda;
+  s.K = rows;
+  s.b0 = (int64_t)blockIdx.y * blocks_per_sub;
+  s.blocks = min(blocks_per_sub, blocks - (int)s.b0);
+  s.first = blockIdx.x * (WR * MT * 16);
+  s.count = n;
+  s.out = Zpart + (int64_t)blockIdx.y * split_stride;
+  s.ldo = ldz;
+  s.ncols = NT * 16;
+  split_tile_waves<true, NT, MT, WR, WC>(s, QP, xstride, (uintx4*)lds_raw, flag);
+}
+
+// Products with infinities, NaN or overflow: a split infinity is inf + NaN + NaN, and inf times the zero low parts
+// of a short number is NaN, so such a product is taken once more with plain fp32 multiplications when a result of the
+// kernels above is not finite.  One wave per 16 x 16 tile of the output, grid stride; every workgroup leaves at once when the
+// flag is clear (about 3 us).  The whole product goes to `out` (rows from `part_row0` on: to the first partial panel, and the
+// other partial panels are cleared).
+template <bool AT>
+__global__ void __launch_bounds__(256)
+k_split_repair(const float* __restrict__ A, int64_t lda, int64_t rows, int64_t K, const float* __restrict__ X, int64_t ldx,
+               int xcols, float* __restrict__ Y, int64_t ldy, int ncols, float* __restrict__ part, int64_t ldp,
+               int64_t split_stride, int nsplit, int64_t part_row0, const int* __restrict__ flag) {
+  if (*flag == 0) return;
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int64_t ctiles = (ldp + 15) / 16, rtiles = (rows + 15) / 16, waves = (int64_t)gridDim.x * 4;
+  for (int64_t tile = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); tile < rtiles * ctiles; tile += waves) {
+    const int64_t row0 = tile / ctiles * 16;
+    const int col = (int)(tile % ctiles) * 16 + r;
+    const int64_t row = min(row0 + r, rows - 1);
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int64_t k = 0; k < K; k += 4) {
+      const int64_t kk = min(k + g, K - 1);
+      const float a = AT ? A[kk * lda + row] : A[row * lda + kk];
+      const float x = k + g < K && col < xcols ? X[kk * ldx + col] : 0.f;
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(k + g < K ? a : 0.f, x, acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int64_t i = row0 + 4 * g + v;
+      if (i >= rows) continue;
+      if (i < part_row0) {
+        if (col < ncols) Y[i * ldy + col] = acc[v];
+      } else if (col < ldp) {
+        float* p = part + (i - part_row0) * ldp + col;
+        p[0] = acc[v];
+        for (int s = 1; s < nsplit; ++s) p[(int64_t)s * split_stride] = 0.f;
+      }
+    }
+  }
+}
+
+// ---- host side --------------------------------------------------------------------------------------------------
+struct SplitCfg { int wr, wc, tile; };
+constexpr int kSplitMT = 2;
+// Up to ten column tiles one wave holds them all (accumulators of 2 x 10 tiles: 234 registers of 256); wider panels take
+// two columns of waves, i.e. half as many rows per workgroup.
+static SplitCfg split_cfg(int nt) {
+  return nt <= 10 ? SplitCfg{8, 1, 8 * kSplitMT * 16} : SplitCfg{4, 2, 4 * kSplitMT * 16};
+}
+constexpr int kSplitSlots = 256;                        // one workgroup of eight waves per CU
+static int64_t split_chunks(int64_t K) { return ceil_div(K, 2 * kSplitB); }
+static uint64_t pack_panel_bytes(int64_t K, int Lp) { return (uint64_t)split_chunks(K) * 2 * (Lp / 16) * 3 * kFragU * 16; }
+
+bool split_fits(int64_t out, int64_t K, int Lp, int64_t lda, uint64_t pack_bytes) {
+  // byte offsets of a lane's loads: at most 255 rows and a row length, in 32 bits
+  if (K < kSplitMinK || out < kSplitMinOut || Lp < kSplitMinLp || out * K < kSplitMinA || lda > (1 << 21)) return false;
+  if (out > INT32_MAX || K > INT32_MAX) return false;
+  return pack_bytes >= pack_panel_bytes(K, Lp) + 64;
+}
+
+SplitPlan split_an_plan(int64_t rows, int64_t K, int Lp, uint64_t scratch_bytes) {
+  const NGroups ng = column_groups(Lp, 4);
+  SplitPlan p;
+  p.nt = ng.nt;
+  p.groups = ng.groups;
+  p.tile = split_cfg(ng.nt).tile;
+  const int T = (int)ceil_div(rows, p.tile), C = (int)split_chunks(K);
+  // as many splits as the scratch has room for
+  for (int S = kSplitSlots;; S = S * 3 / 4) {
+    p.sh = an_shape(T, C, S, 8, 4);
+    p.nsplit = p.sh.lt > 0 ? p.sh.f + (p.sh.x > 0 ? 1 : 0) : 0;
+    p.partial_rows = p.nsplit > 0 ? rows - (int64_t)p.sh.whole * p.tile : 0;
+    if ((uint64_t)p.nsplit * p.partial_rows * Lp * 4 <= scratch_bytes) break;
+    if (S <= 1) { p.sh = AnShape{C, T, 0, 1, 0, 0}; p.nsplit = 0; p.partial_rows = 0; break; }
+  }
+  p.wgs = p.sh.whole + p.sh.lt * p.sh.f + (p.sh.x > 0 ? (int)ceil_div(p.sh.lt, p.sh.j) : 0);
+  return p;
+}
+
+SplitPlan split_at_plan(int64_t rows, int64_t n, int Lp, uint64_t scratch_bytes) {
+  const NGroups ng = column_groups(Lp, 4);
+  SplitPlan p;
+  p.nt = ng.nt;
+  p.groups = ng.groups;
+  p.tile = split_cfg(ng.nt).tile;
+  p.col_tiles = (int)ceil_div(n, p.tile);
+  const int64_t chunks = split_chunks(rows);
+  const int64_t room = (int64_t)(scratch_bytes / ((uint64_t)n * Lp * 4));
+  const int want = pick_splits(p.col_tiles, kSplitSlots, chunks, (double)Lp / (double)rows, traffic_weight(ng.nt), (int)std::min<int64_t>(room, 4096));
+  const int64_t per = ceil_div(chunks, want);
+  p.blocks = (int)(2 * chunks);
+  p.blocks_per_sub = (int)(2 * per);
+  p.nsplit = room < 1 ? 0 : (int)ceil_div(chunks, per);
+  return p;
+}
+
+// (ten tiles in two columns of waves: the second group of a panel of 21 tiles, whose first group has eleven)
+#define BRSVD_SPLIT_SWITCH(nt, tile, CALL)                                                                       \
+  if (nt == 10 && tile == 4 * kSplitMT * 16) { CALL(10, 4, 2); } else                                            \
+  switch (nt) {                                                                                                  \
+    case 3: CALL(3, 8, 1); break; case 4: CALL(4, 8, 1); break; case 5: CALL(5, 8, 1); break;                    \
+    case 6: CALL(6, 8, 1); break; case 7: CALL(7, 8, 1); break; case 8: CALL(8, 8, 1); break;                    \
+    case 9: CALL(9, 8, 1); break; case 10: CALL(10, 8, 1); break; case 11: CALL(11, 4, 2); break;                \
+    case 12: CALL(12, 4, 2); break; case 13: CALL(13, 4, 2); break; case 14: CALL(14, 4, 2); break;              \
+    case 15: CALL(15, 4, 2); break; case 16: CALL(16, 4, 2); break; case 17: CALL(17, 4, 2); break;              \
+    default: return BRSVD_ERR_ARG;                                                                               \
+  }
+
+template <typename K>
+static int split_lds(K kern, int nt, bool* done) {
+  if (!*done) {
+    BRSVD_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * nt * 3 * kFragU * 16));
+    *done = true;
+  }
+  return BRSVD_OK;
+}
+
+static int split_pack(const float* X, int64_t K, int64_t ldx, int xcols, int Lp, void* pack, int** flag, hipStream_t stream) {
+  const int64_t blocks = 2 * split_chunks(K), units = blocks * (Lp / 16) * kFragU;
+  *flag = (int*)((char*)pack + pack_panel_bytes(K, Lp));
+  hipLaunchKernelGGL(k_split_pack, dim3((unsigned)ceil_div(units, 256)), dim3(256), 0, stream, X, K, ldx, xcols, Lp / 16,
+                     blocks, (uintx4*)pack, *flag);
+  BRSVD_HIP_TRY(hipGetLastError());
+  return BRSVD_OK;
+}
+
+int split_gemm_an(const float* A, int64_t lda, int64_t rows, int64_t K, const float* X, int64_t ldx, int xcols, int Lp,
+                  float* Y, int64_t ldy, int ncols, void* scratch, uint64_t scratch_bytes, void* pack,
+                  uint64_t pack_bytes, hipStream_t stream, const KernelEvents* ev) {
+  if (!split_fits(rows, K, Lp, lda, pack_bytes) || ncols > Lp) return BRSVD_ERR_ARG;
+  const SplitPlan p = split_an_plan(rows, K, Lp, scratch_bytes);
+  float* part = (float*)scratch;
+  const int64_t stride = p.partial_rows * Lp, xstride = (Lp / 16) * 3 * kFragU;
+  int* flag;
+  if (ev) BRSVD_HIP_TRY(hipEventRecord(ev->start, stream));
+  BRSVD_TRY(split_pack(X, K, ldx, xcols, Lp, pack, &flag, stream));
+  for (int gi = 0; gi < p.groups; ++gi) {
+    const int c0 = gi * p.nt * 16, nt = std::min(p.nt, (Lp - c0) / 16);
+    if (nt <= 0) break;
+    const uintx4* xp = (const uintx4*)pack + (c0 / 16) * 3 * kFragU;
+#define CALL(N, WR, WC)                                                                                              \
+  {                                                                                                                  \
+    if (p.tile != WR * kSplitMT * 16) return BRSVD_ERR_ARG;                                                          \
+    auto kern = k_split_an<N, kSplitMT, WR, WC>;                                                                     \
+    static bool done = false;                                                                                        \
+    BRSVD_TRY(split_lds(kern, N, &done));                                                                            \
+    hipLaunchKernelGGL(kern, dim3(p.wgs), dim3(WR * WC * 64), 2 * N * 3 * kFragU * 16, stream, A, lda, (int)rows, (int)K, \
+                       xp, xstride, Y + c0, ldy, std::min(ncols - c0, N * 16), part ? part + c0 : nullptr, (int64_t)Lp, stride, p.sh, flag); \
+  }
+    BRSVD_SPLIT_SWITCH(nt, p.tile, CALL)
+#undef CALL
+    BRSVD_HIP_TRY(hipGetLastError());
+  }
+  hipLaunchKernelGGL(k_split_repair<false>, dim3(kSplitSlots), dim3(256), 0, stream, A, lda, rows, K, X, ldx, xcols, Y, ldy,
+                     ncols, part, (int64_t)Lp, stride, p.nsplit, rows - p.partial_rows, flag);
+  BRSVD_HIP_TRY(hipGetLastError());
+  if (ev) {
+    BRSVD_HIP_TRY(hipEventRecord(ev->stop, stream));
+    BRSVD_HIP_TRY(hipEventRecord(ev->sum_start, stream));
+  }
+  if (p.nsplit > 0) {
+    const int64_t r0 = rows - p.partial_rows;
+    BRSVD_TRY(reduce_splits_f32(part, p.nsplit, stride, p.partial_rows, ncols, Lp, Y + r0 * ldy, ldy, false, stream));
+  }
+  if (ev) BRSVD_HIP_TRY(hipEventRecord(ev->sum_stop, stream));
+  return BRSVD_OK;
+}
+
+int split_gemm_at(const float* A, int64_t lda, int64_t rows, int64_t n, const float* Q, int64_t ldq, int qcols, int Lp,
+                  float* Z, int64_t ldz, int ncols, bool accumulate, void* scratch, uint64_t scratch_bytes, void* pack,
+                  uint64_t pack_bytes, hipStream_t stream, const KernelEvents* ev) {
+  if (!split_fits(n, rows, Lp, lda, pack_bytes) || ncols > Lp) return BRSVD_ERR_ARG;
+  const SplitPlan p = split_at_plan(rows, n, Lp, scratch_bytes);
+  if (p.nsplit < 1) return BRSVD_ERR_BUDGET;
+  if (p.nsplit > 65535) return BRSVD_ERR_ARG;
+  float* part = (float*)scratch;
+  const int64_t stride = n * Lp, xstride = (Lp / 16) * 3 * kFragU;
+  int* flag;
+  if (ev) BRSVD_HIP_TRY(hipEventRecord(ev->start, stream));
+  BRSVD_TRY(split_pack(Q, rows, ldq, qcols, Lp, pack, &flag, stream));
+  for (int gi = 0; gi < p.groups; ++gi) {
+    const int c0 = gi * p.nt * 16, nt = std::min(p.nt, (Lp - c0) / 16);
+    if (nt <= 0) break;
+    const uintx4* qp = (const uintx4*)pack + (c0 / 16) * 3 * kFragU;
+#define CALL(N, WR, WC)                                                                                              \
+  {                                                                                                                  \
+    if (p.tile != WR * kSplitMT * 16) return BRSVD_ERR_ARG;                                                          \
+    auto kern = k_split_at<N, kSplitMT, WR, WC>;                                                                     \
+    static bool done = false;                                                                                        \
+    BRSVD_TRY(split_lds(kern, N, &done));                                                                            \
+    hipLaunchKernelGGL(kern, dim3(p.col_tiles, p.nsplit), dim3(WR * WC * 64), 2 * N * 3 * kFragU * 16, stream, A, lda, rows, \
+                       (int)n, qp, xstride, part + c0, (int64_t)Lp, stride, p.blocks, p.blocks_per_sub, flag);       \
+  }
+    BRSVD_SPLIT_SWITCH(nt, p.tile, CALL)
+#undef CALL
+    BRSVD_HIP_TRY(hipGetLastError());
+  }
+  hipLaunchKernelGGL(k_split_repair<true>, dim3(kSplitSlots), dim3(256), 0, stream, A, lda, n, rows, Q, ldq, qcols, nullptr,
+                     (int64_t)0, 0, part, (int64_t)Lp, stride, p.nsplit, (int64_t)0, flag);
+  BRSVD_HIP_TRY(hipGetLastError());
+  if (ev) {
+    BRSVD_HIP_TRY(hipEventRecord(ev->stop, stream));
+    BRSVD_HIP_TRY(hipEventRecord(ev->sum_start, stream));
+  }
+  BRSVD_TRY(reduce_splits_f32(part, p.nsplit, stride, n, ncols, Lp, Z, ldz, accumulate, stream));
+  if (ev) BRSVD_HIP_TRY(hipEventRecord(ev->sum_stop, stream));
+  return BRSVD_OK;
+}
+
+}  // namespace brsvd

@@ -84,10 +84,6 @@ constexpr int kMaxNT = 17;   // n-tiles (of 16 columns) one launch keeps in regi
 //     workgroup, with x chosen so that j strips weigh as much as one main split.
 // Workgroups of one kind walk the contraction in lockstep, so the panel chunks they share stay in L2.
 // The partial panels of a leftover tile (slots 0..f-1, then the tail) are added in that order.
-struct AnShape {
-  int C, whole, lt, f, x, j;
-};
-
 template <typename T, int NT, int MT, int WAVES, int KC, bool RAGGED>
 __global__ void __launch_bounds__(WAVES * 64)
 k_gemm_an(const T* __restrict__ A, int64_t lda, int rows, int K,
@@ -112,25 +108,9 @@ k_gemm_an(const T* __restrict__ A, int64_t lda, int rows, int K,
   T* buf0 = lds;
   T* buf1 = lds + KC * LD;
 
-  int first_tile, nseg = 1, c0, c1, slot = 0;
-  bool partial = true;
-  {
-    const int b = blockIdx.x, C = sh.C;
-    if (b < sh.whole) {
-      first_tile = b; c0 = 0; c1 = C; partial = false;
-    } else if (b < sh.whole + sh.lt * sh.f) {
-      const int idx = b - sh.whole, s = idx % sh.f;
-      first_tile = sh.whole + idx / sh.f;
-      c0 = (int)((int64_t)s * (C - sh.x) / sh.f);
-      c1 = (int)((int64_t)(s + 1) * (C - sh.x) / sh.f);
-      slot = s;
-    } else {
-      const int i = b - sh.whole - sh.lt * sh.f;
-      first_tile = sh.whole + i * sh.j;
-      nseg = min(sh.j, sh.whole + sh.lt - first_tile);
-      c0 = C - sh.x; c1 = C; slot = sh.f;
-    }
-  }
+  const AnWork work = an_work(sh, blockIdx.x);
+  const int first_tile = work.first_tile, nseg = work.nseg, c0 = work.c0, c1 = work.c1, slot = work.slot;
+  const bool partial = work.partial;
   const int nchunks = c1 - c0;
   const int kbeg = c0 * KC;
   const int kend = min(K, c1 * KC);
@@ -316,25 +296,9 @@ k_gemm_an_narrow(const float* __restrict__ A, int64_t lda, int rows, int K,
   float* abuf = lds;
   float* xbuf = lds + ROWS * LDA;
 
-  int first_tile, nseg = 1, c0, c1, slot = 0;
-  bool partial = true;
-  {
-    const int b = blockIdx.x, C = sh.C;
-    if (b < sh.whole) {
-      first_tile = b; c0 = 0; c1 = C; partial = false;
-    } else if (b < sh.whole + sh.lt * sh.f) {
-      const int idx = b - sh.whole, sp = idx % sh.f;
-      first_tile = sh.whole + idx / sh.f;
-      c0 = (int)((int64_t)sp * (C - sh.x) / sh.f);
-      c1 = (int)((int64_t)(sp + 1) * (C - sh.x) / sh.f);
-      slot = sp;
-    } else {
-      const int i = b - sh.whole - sh.lt * sh.f;
-      first_tile = sh.whole + i * sh.j;
-      nseg = min(sh.j, sh.whole + sh.lt - first_tile);
-      c0 = C - sh.x; c1 = C; slot = sh.f;
-    }
-  }
+  const AnWork work = an_work(sh, blockIdx.x);
+  const int first_tile = work.first_tile, nseg = work.nseg, c0 = work.c0, c1 = work.c1, slot = work.slot;
+  const bool partial = work.partial;
   const int nchunks = c1 - c0;
   const int kbeg = c0 * KC;
   const int kend = min(K, c1 * KC);
@@ -721,10 +685,10 @@ static int wg_slots(int lds_bytes, int wg_per_cu_regs) {
 // partial output panel (written and re-read) relative to the bytes of A the launch reads;
 // units = indivisible pieces of the contraction range; traffic_weight in (0, 1] discounts that
 // traffic when the launch is bound by MFMA rather than by HBM.
-static int pick_splits(int64_t tiles, int slots, int64_t units, double out_over_in, double traffic_weight) {
+int pick_splits(int64_t tiles, int slots, int64_t units, double out_over_in, double traffic_weight, int max_splits) {
   int best = 1;
   double best_score = -1.0;
-  const int smax = (int)std::min<int64_t>(units, 4096);   // long split sums are reduced in two levels
+  const int smax = (int)std::min<int64_t>(units, max_splits);
   for (int sp = 1; sp <= smax; ++sp) {
     const int64_t per = ceil_div(units, sp);
     const int64_t eff_sp = ceil_div(units, per);          // splits actually produced
@@ -740,12 +704,9 @@ static int pick_splits(int64_t tiles, int slots, int64_t units, double out_over_
   return best;
 }
 
-struct NGroups {
-  int groups, nt;   // column groups per launch sequence, n-tiles per group
-};
 // esz = element size: fp64 accumulators take twice the registers, so a launch keeps 8 n-tiles at most.
 static int max_nt(int esz) { return esz == 8 ? 8 : kMaxNT; }
-static NGroups column_groups(int Lp, int esz) {
+NGroups column_groups(int Lp, int esz) {
   int nt_total = Lp / 16;
   int groups = (nt_total + max_nt(esz) - 1) / max_nt(esz);
   int nt = (nt_total + groups - 1) / groups;
@@ -771,7 +732,7 @@ static AnCfg an_cfg(int nt, int esz, int64_t K) {
   return cfg(nt > 14 ? 1 : 2, 8, 32);
 }
 // Discount of partial-panel traffic: 1 for HBM-bound widths, smaller once 2*Lp/8 flop/B is past the ridge.
-static double traffic_weight(int nt) { return nt <= 2 ? 1.0 : (nt <= 4 ? 0.6 : 0.3); }
+double traffic_weight(int nt) { return nt <= 2 ? 1.0 : (nt <= 4 ? 0.6 : 0.3); }
 // Workgroups per CU assumed when a launch is cut to fill the chip.  The registers alone would allow more of
 // the narrowest kernels (four-wave k_gemm_an with one or two column tiles: 112-128 registers, four workgroups per
 // CU; eight-wave k_gemm_at with one or two column tiles: 104-124 registers, two), but plans made for those counts
@@ -787,20 +748,10 @@ struct AnPlan {
   int row_tiles, tile_rows, nsplit, wgs;      // nsplit = partial panels per leftover tile (0: none)
   AnShape sh;
 };
-// See AnShape.  Short contractions (the R^-1 applies and lifts: fewer than 16 chunks) and launches
-// with very many tiles keep one whole tile per workgroup.
-static AnPlan an_plan(int64_t rows, int64_t K, int nt, int esz) {
-  AnCfg c = an_cfg(nt, esz, K);
-  AnPlan p;
-  p.tile_rows = c.tile_rows;
-  p.row_tiles = (int)ceil_div(rows, p.tile_rows);
-  const int T = p.row_tiles, C = (int)ceil_div(K, c.kc);
-  const bool narrow = esz == 4 && nt <= kAnNarrowMaxNT && K >= kAnNarrowMinK;
-  const int lds_bytes = narrow ? an_narrow_lds_bytes(nt) : 2 * c.kc * (nt * 16 + 4) * esz;
-  const int S = wg_slots(lds_bytes, an_wg_per_cu_regs(esz, c.waves));
+// T row tiles of C chunks for S workgroup slots (see AnShape).  Short contractions (the R^-1 applies and lifts: fewer
+// than two pieces of min_piece chunks) and launches with very many tiles keep one whole tile per workgroup.
+AnShape an_shape(int T, int C, int S, int min_piece, int min_strip) {
   AnShape sh = {C, T, 0, 1, 0, 0};
-  // a split or a strip is worth its partial panel from about 512 columns on: 8 chunks of 64, 2 of 256
-  const int min_piece = c.kc >= 256 ? 2 : 8, min_strip = c.kc >= 256 ? 1 : 4;
   if (C >= 2 * min_piece && T < 8 * S) {
     sh.whole = T / S * S;
     sh.lt = T - sh.whole;
@@ -815,6 +766,19 @@ static AnPlan an_plan(int64_t rows, int64_t K, int nt, int esz) {
       if (sh.f == 1 && sh.x == 0) { sh.whole = T; sh.lt = 0; }
     }
   }
+  return sh;
+}
+static AnPlan an_plan(int64_t rows, int64_t K, int nt, int esz) {
+  AnCfg c = an_cfg(nt, esz, K);
+  AnPlan p;
+  p.tile_rows = c.tile_rows;
+  p.row_tiles = (int)ceil_div(rows, p.tile_rows);
+  const int T = p.row_tiles, C = (int)ceil_div(K, c.kc);
+  const bool narrow = esz == 4 && nt <= kAnNarrowMaxNT && K >= kAnNarrowMinK;
+  const int lds_bytes = narrow ? an_narrow_lds_bytes(nt) : 2 * c.kc * (nt * 16 + 4) * esz;
+  const int S = wg_slots(lds_bytes, an_wg_per_cu_regs(esz, c.waves));
+  // a split or a strip is worth its partial panel from about 512 columns on: 8 chunks of 64, 2 of 256
+  const AnShape sh = an_shape(T, C, S, c.kc >= 256 ? 2 : 8, c.kc >= 256 ? 1 : 4);
   p.sh = sh;
   p.nsplit = sh.lt > 0 ? sh.f + (sh.x > 0 ? 1 : 0) : 0;
   p.wgs = sh.whole + sh.lt * sh.f + (sh.x > 0 ? (int)ceil_div(sh.lt, sh.j) : 0);
@@ -978,6 +942,11 @@ static int reduce_splits(T* part, int nsplit, int64_t split_stride, int64_t rows
   return BRSVD_OK;
 }
 
+int reduce_splits_f32(float* part, int nsplit, int64_t split_stride, int64_t rows, int ncols, int64_t ldi, float* out,
+                      int64_t ldo, bool accumulate, hipStream_t stream) {
+  return reduce_splits<float>(part, nsplit, split_stride, rows, ncols, ldi, out, ldo, accumulate, stream);
+}
+
 template <typename T>
 static int gemm_an_t(const T* A, int64_t lda, int64_t rows, int64_t K, const T* X, int Lp, T* Y, int64_t ldy,
                      int ncols, void* scratch, uint64_t scratch_bytes, hipStream_t stream, const KernelEvents* ev) {
@@ -1055,7 +1024,7 @@ static AtPlan at_plan(int64_t rows, int64_t n, int nt, int64_t block_rows, int e
   const int lds_bytes = 2 * kAtKC * at_ld(nt, esz) * esz;
   // one partial panel (n x Lp) per split, against block_rows x n of A read per block
   const int want = pick_splits((int64_t)p.col_tiles * p.nblocks, wg_slots(lds_bytes, at_wg_per_cu_regs(nt, p.waves)), max_sub,
-                               (double)(nt * 16) / (double)block_rows, traffic_weight(nt));
+                               (double)(nt * 16) / (double)block_rows, traffic_weight(nt), 4096);   // long split sums take two levels
   int64_t rps = ceil_div(block_rows, want);
   rps = ceil_div(rps, kAtKC) * kAtKC;
   p.rows_per_sub = (int)rps;

@@ -10,8 +10,11 @@
 #include <cstdlib>
 #include <cstring>
 
+#include <vector>
+
 #include "brsvd.h"
 #include "brsvd_steps.h"
+#include "common.h"
 
 static int g_checks = 0, g_failed = 0;
 #define CHECK(cond)                                                             \
@@ -134,6 +137,39 @@ int main() {
     CHECK(brsvd_gemm_scratch_bytes(0, 10, 4) == 0 && brsvd_gemm_scratch_bytes(512, 1000, 30) > 0);
     CHECK(brsvd_orth_scratch_bytes(100, 600) == 0 && brsvd_small_svd_scratch_bytes(0) == 0);
     CHECK(brsvd_small_svd_scratch_bytes(512) >= 2ull * 512 * 512 * 8);
+  }
+
+  // ---- plans of the split products: every unit of work covered once, partial panels inside whatever scratch there is ----
+  for (int it = 0; it < 400; ++it) {
+    const int64_t rows = uniform(1, 3) == 1 ? uniform(64, 3000) : uniform(64, 700000);
+    const int64_t n = uniform(1, 3) == 1 ? uniform(64, 3000) : uniform(64, 100000);
+    const int Lp = 16 * (int)uniform(3, 32);
+    const uint64_t an = brsvd::gemm_an_scratch_bytes(rows, n, Lp), at = brsvd::gemm_at_scratch_bytes(rows, n, Lp, rows);
+    const uint64_t scratch = uniform(1, 4) == 1 ? (uint64_t)uniform(0, 1 << 24) : (an > at ? an : at);
+    const brsvd::SplitPlan p = brsvd::split_an_plan(rows, n, Lp, scratch);
+    CHECK((uint64_t)p.nsplit * p.partial_rows * Lp * 4 <= scratch && p.groups * p.nt * 16 >= Lp && p.nt <= 17);
+    CHECK((int64_t)(p.sh.whole + p.sh.lt) * p.tile >= rows && (int64_t)(p.sh.whole + p.sh.lt - 1) * p.tile < rows);
+    CHECK((int64_t)p.sh.C * 64 >= n && p.partial_rows == (p.nsplit ? rows - (int64_t)p.sh.whole * p.tile : 0));
+    std::vector<int> chunks(p.sh.whole + p.sh.lt, 0);
+    for (int b = 0; b < p.wgs; ++b) {
+      const brsvd::AnWork w = brsvd::an_work(p.sh, b);
+      CHECK(w.c0 < w.c1 && w.c1 <= p.sh.C && w.partial == (w.first_tile >= p.sh.whole) && (!w.partial || w.slot < p.nsplit));
+      for (int t = 0; t < w.nseg; ++t) chunks[w.first_tile + t] += w.c1 - w.c0;
+    }
+    for (int c : chunks) CHECK(c == p.sh.C);
+    const brsvd::SplitPlan q = brsvd::split_at_plan(rows, n, Lp, scratch);
+    CHECK((uint64_t)q.nsplit * n * Lp * 4 <= scratch);
+    if (q.nsplit > 0) {
+      CHECK(q.blocks % 2 == 0 && q.blocks_per_sub % 2 == 0 && q.blocks_per_sub >= 2 && (int64_t)q.blocks * 32 >= rows);
+      CHECK((int64_t)q.nsplit * q.blocks_per_sub >= q.blocks && (int64_t)(q.nsplit - 1) * q.blocks_per_sub < q.blocks);
+      CHECK((int64_t)q.col_tiles * q.tile >= n && (int64_t)(q.col_tiles - 1) * q.tile < n);
+    }
+    // the packed panel fits where the driver and the step calls put it: the TSQR work area, two padded fp32 panels
+    if (rows * n >= brsvd::kSplitMinA && n >= brsvd::kSplitMinK) {
+      const int64_t most = rows > n ? rows : n;
+      CHECK(brsvd::split_fits(rows, n, Lp, n, brsvd::tsqr_work_bytes(n, Lp)));
+      CHECK(brsvd::split_fits(rows, n, Lp, n, 2ull * most * Lp * 4));
+    }
   }
 
   // ---- step calls: scratch that is missing, misaligned or too short is refused before any device call ----

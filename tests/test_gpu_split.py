@@ -1,0 +1,91 @@
+"""The products of wide fp32 panels, whose operands are split into three bf16 numbers: elementwise error against fp64 at the
+edges of their tiles and of the rule that selects them, and the values a split cannot carry."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1706_07191_amd as B
+from paper_1706_07191_amd import synth
+from tests.gpu_util import EPS32, need_gpu
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [  # rows, n, l, elements between A's rows beyond n, offset of A's base in elements
+    (8200, 512, 33, 0, 0),       # shortest contraction, narrowest panel of A X; 32 columns + 1
+    (513, 8200, 48, 0, 0),       # shortest contraction of A^T Q, not a multiple of its blocks
+    (4097, 1031, 97, 0, 0),      # odd row length, one row more than whole tiles
+    (2049, 2050, 160, 6, 1),     # ten column tiles (one column of waves), padded rows, odd base
+    (2049, 2050, 161, 0, 3),     # eleven column tiles (two columns of waves)
+    (1300, 3300, 272, 0, 0),     # seventeen column tiles: 9 + 8 per wave column
+    (1300, 3300, 273, 0, 0),     # two column groups
+    (1100, 4000, 336, 0, 0),     # 21 column tiles: groups of 11 and 10
+    (1025, 4100, 512, 0, 0),     # the largest sketch width
+    (70000, 600, 110, 0, 0),     # more row tiles than workgroups: whole tiles and a cut leftover round
+]
+
+
+def _inputs(rows, n, l, pad, off, dev, mean=0.0):
+    flat = torch.zeros(rows * (n + pad) + 8, device=dev)
+    A = flat[off:off + rows * (n + pad)].view(rows, n + pad)[:, :n]
+    A.copy_(synth.gaussian(rows, n, 401, device=dev) + mean)
+    X = synth.gaussian(n, l, 402, device=dev) + mean
+    Q = synth.gaussian(rows, l, 403, device=dev) + mean
+    return A, X, Q
+
+
+def _bound(K, A, X):
+    # A sum of K products in blocks of 32: the block sum is truncated once (2^-23 of it) and added to the running
+    # sum with one rounding (K / 32 of them, each of eps/2 of a partial sum that is at most sum |a||x|; as a random
+    # walk sqrt(K/32)), and the products left out of a split are below 2^-22 each.  Less than the 8 sqrt(K) eps that
+    # the plain fp32 products are held to.
+    return (4.0 + np.sqrt(K / 32.0)) * EPS32 * (A.abs().double() @ X.abs().double())
+
+
+@pytest.mark.parametrize("rows,n,l,pad,off", SHAPES)
+@pytest.mark.parametrize("mean", [0.0, 0.5])
+def test_split_products(rows, n, l, pad, off, mean):
+    dev = need_gpu()
+    print(f"[case] split rows={rows} n={n} l={l} pad={pad} off={off} mean={mean}", flush=True)
+    A, X, Q = _inputs(rows, n, l, pad, off, dev, mean)
+    Ad = A.double()
+    Y = B.brsvd_gemm_an(A, X)
+    assert bool(((Y.double() - Ad @ X.double()).abs() <= _bound(n, A, X)).all())
+    Z = B.brsvd_gemm_at(A, Q)
+    ref = Ad.T.contiguous() @ Q.double()
+    bound = _bound(rows, A.T.contiguous(), Q)
+    assert bool(((Z.double() - ref).abs() <= bound).all())
+    Z2 = B.brsvd_gemm_at(A, Q, Z=Z.clone(), accumulate=True)
+    assert bool(((Z2.double() - 2 * ref).abs() <= 2 * bound + 2 * EPS32 * ref.abs()).all())
+
+
+@pytest.mark.parametrize("scale_a,scale_x", [(1e-30, 1e25), (1e30, 1e-25), (1e-18, 1e-10)])
+def test_split_products_at_any_exponent(scale_a, scale_x):
+    dev = need_gpu()
+    A, X, Q = _inputs(2049, 2050, 64, 0, 0, dev)
+    A, X, Q = A * scale_a, X * scale_x, Q * scale_x
+    assert bool(((B.brsvd_gemm_an(A, X).double() - A.double() @ X.double()).abs() <= _bound(2050, A, X)).all())
+    At = A.T.contiguous()
+    assert bool(((B.brsvd_gemm_at(A, Q).double() - At.double() @ Q.double()).abs() <= _bound(2049, At, Q)).all())
+
+
+def test_split_products_not_finite():
+    """An infinity, a NaN and values near the largest one come out as with plain fp32 products: the split of an
+    infinity has NaN parts, and its upper part times the zero low parts of a short number would be NaN."""
+    dev = need_gpu()
+    A, X, Q = _inputs(2049, 2050, 64, 0, 0, dev)
+    X[5:9] = 1.0
+    Q[11:13] = 1.0
+    A[3, 7] = float("inf")
+    A[11, 1000] = float("-inf")
+    A[40, 9] = float("nan")
+    A[100, 20] = 3.4028e38
+    X[20] = 0.25
+    Y, Z = B.brsvd_gemm_an(A, X), B.brsvd_gemm_at(A, Q)
+    Yr, Zr = (A.cpu() @ X.cpu()).to(dev), (A.cpu().T.contiguous() @ Q.cpu()).to(dev)
+    for got, ref in ((Y, Yr), (Z, Zr)):
+        assert torch.equal(got.isnan(), ref.isnan()) and torch.equal(got.isinf(), ref.isinf())
+        fin = ref.isfinite()
+        assert torch.equal(torch.sign(got[got.isinf()]), torch.sign(ref[ref.isinf()]))
+        assert bool(((got - ref)[fin].abs() <= 1e-5 * ref[fin].abs().clamp(min=100.0)).all())
+    Z2 = B.brsvd_gemm_at(A, Q, Z=torch.ones_like(Z), accumulate=True)
+    assert torch.equal(Z2.isfinite(), Zr.isfinite())
