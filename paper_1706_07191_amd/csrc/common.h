@@ -181,7 +181,7 @@ template <typename T>
 int cholqr_sweeps(T* P, T* tmp, int64_t rows, int l, int Lp, int nsweeps, OrthWorkT<T>& w, double* Rtot,
                   T** result, hipStream_t stream, bool strict_last, bool publish_R = false);
 template <typename T>
-int chol_inv_factored(double* G, int l, int Lp, double* Rout, double* Xtmp, T* Rinv, int* flags, hipStream_t stream);
+int chol_inv_factored(double* G, int l, int Lp, double* Rout, T* Rinv, int* flags, hipStream_t stream);
 template <typename T>
 int tsqr_panel(T* P, T* tmp, int64_t rows, int l, int Lp, OrthWorkT<T>& w, double* Rtot, T** result,
                hipStream_t stream);

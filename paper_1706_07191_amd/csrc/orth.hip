@@ -98,15 +98,33 @@ k_gram(const T* __restrict__ P, int64_t rows, int Lp, int64_t rows_per_chunk, do
 }
 
 // ---- Cholesky factor and its inverse ---------------------------------------------------------
-// One workgroup of 1024 threads; blocked right-looking factorisation G = R^T R with 16 x 16
-// blocks, then R^-1 by recursive doubling (invert the diagonal blocks, then merge neighbouring
-// blocks: inv([R11 R12; 0 R22]) = [X11, -X11 R12 X22; 0, X22]).  Everything is fp64.  For
-// Lp <= kCholLdsMaxLp the matrix lives in LDS for the whole kernel; above that it stays in global
-// memory (L2) and only the current 16-row panel is mirrored in LDS.
+// One workgroup; everything is fp64, in 16 x 16 tiles on v_mfma_f64_16x16x4_f64.  G = R^T R is eliminated with the
+// identity beside it: the row operations that turn G into R turn the identity into E = R^-T, so the inverse needs no
+// pass of its own.  With E_kk = R_kk^-T, step k is
+//   pan_c   = E_kk M_kc for every column tile c: R_kc for c > k, E_kc for c < k  (pan_k = E_kk)
+//   M_ic   -= R_ki^T pan_c for the rows i > k, columns c <= k (E) and c >= i (what is left of G)
+// where M holds G in its upper tiles and E in its lower ones (zero before step c).  Row k is final after its panel:
+// R and R^-1 = E^T are written out from there.  The diagonal tile of the next step is updated and
+// factored by wave 0 while the other waves finish the update of step k, which takes the chain of 16 pivots
+// off the path of everything else: a step is the longer of the two plus the panel and two barriers.
+//
+// What bounds it: the chain of pivots (375 cycles each: a matrix instruction, two lane reads, a reciprocal with two
+// Newton steps, the scale of the row) up to l of 128, where M is in LDS; above that M stays in global memory (L2) and the
+// tile updates, 2 l^3 / 3 flops on one CU, take over.  Measured (us with the launch; before: the factorisation with
+// row-wise panel solves, then a recursive inversion): l = 20 19.8 -> 11.3, 60 38.0 -> 20.2, 110 73.7 -> 33.1,
+// 128 87.4 -> 38.9, 160 151 -> 65, 272 383 -> 208, 400 895 -> 562.
 // A pivot <= tol * its original diagonal entry is clamped to that value (lenient) or sets
-// flag[0] = 1 + column and ends the kernel.
+// flag[0] = 1 + column of its tile and ends the kernel.
 constexpr int kNB = 16;
-constexpr int kCholLdsMaxLp = 128;    // largest padded size whose (Lp x (Lp+1)) fp64 matrix fits the LDS
+constexpr int kCholLdsMaxLp = 128;    // largest padded size whose fp64 matrix fits the LDS
+
+// Row strides (in doubles): 16 modulo 32 puts the four rows a wave reads at once on distinct banks; the matrix of
+// the largest sizes has no room for that and takes two doubles of padding.
+static constexpr int chol_ldp(int Lp) { return Lp % 32 == 0 ? Lp + 16 : Lp; }
+static constexpr int chol_ldm(int Lp) { return Lp % 32 == 0 ? (Lp < 128 ? Lp + 16 : Lp + 2) : Lp; }
+static constexpr size_t chol_lds_bytes(int Lp, bool in_lds) {
+  return sizeof(double) * ((size_t)kNB * (kNB + 1) + Lp + (size_t)kNB * chol_ldp(Lp) + (in_lds ? (size_t)Lp * chol_ldm(Lp) : 0));
+}
 
 // Broadcast of lane `src` (a compile-time constant after unrolling): two scalar lane reads.
 __device__ __forceinline__ double shfl_d(double v, int src) {
@@ -129,282 +147,198 @@ __device__ __forceinline__ double rcp_fast(double x) {
   return y;
 }
 
-// Wave-level Cholesky of the 16 x 16 diagonal block at (kb, kb).  The tile sits in the MFMA
-// accumulator layout (lane (r, g), component v = entry [g + 4 v][r]), so that the four rows 4p .. 4p+3 of
-// a panel are one register across the wave.  Per panel: the four rows are gathered into every lane
-// (lane r keeps column r of them), factored in four pivot steps with lane broadcasts, and the rest of
-// the tile receives their rank-4 update as a single v_mfma_f64_16x16x4_f64 with the panel as both
-// operands.  Pivots at or below tol * (original diagonal) are clamped (see k_chol_inv); returns false
-// if that happened.  Writes R_kk into M (upper part) and into Rkk (16 x 17, spare column = 1/diagonal).
-__device__ bool chol_diag_wave(double* M, int64_t ld, int kb, int nb, const double* d0, double tol,
-                               double* Rkk, int lane) {
-  (void)nb;
+// One wave: factors the diagonal tile D (upper triangle) and inverts the factor, both in the accumulator layout of the
+// matrix instruction (component v of lane (r, g) is entry [g + 4 v][r]).  The elimination is D = L d L^T without square
+// roots: row j of D sits in component j >> 2 of the lanes of group j & 3, which is where the instruction expects
+// contraction index j & 3 of both operands, so a pivot step is one instruction for D and one for the identity E,
+//   D -= (row_j / d_j)^T row_j,  E -= (row_j / d_j)^T E_j   (first operand masked to the rows below j),
+// with no value moved between lanes.  The next pivot is taken from the old tile, d_(j+1) = D_(j+1,j+1) -
+// D_(j,j+1)^2 / d_j, so its reciprocal is worked out while the instruction runs.  Rows are scaled by 1/sqrt(d)
+// at the end: D = R_kk, E = R_kk^-T.  FACTORED: D is already R_kk.  d0: original diagonal of the tile.  Returns false if
+// a pivot had to be clamped.
+template <bool FACTORED>
+__device__ __forceinline__ bool chol_diag_wave(doublex4& D, doublex4& E, const double* d0, double tol, int lane) {
   const int r = lane & 15, g = lane >> 4;
-  doublex4 t;
+  const double floors = tol * d0[r];
+  doublex4 ds;
 #pragma unroll
-  for (int v = 0; v < 4; ++v) t[v] = M[(int64_t)(kb + g + 4 * v) * ld + kb + r];
-  bool ok = true;
+  for (int v = 0; v < 4; ++v) { E[v] = g + 4 * v == r ? 1.0 : 0.0; ds[v] = 1.0; }
+  int clamped = 0;
+  auto pivot = [&](int j, double d) {
+    if (FACTORED) return d;
+    const double floor_ = shfl_d(floors, j);
+    const bool low = !(d > floor_);
+    clamped |= low;
+    return low ? (floor_ > 0.0 ? floor_ : 1.0) : d;            // an all-zero column keeps R_jj = 1
+  };
+  double d = pivot(0, shfl_d(D[0], 0)), inv = rcp_fast(d);
 #pragma unroll
-  for (int p4 = 0; p4 < 4; ++p4) {
-    const int jb = 4 * p4;
-    double pr[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const double x = __shfl(t[p4], 16 * i + r, 64);           // entry [jb + i][r]
-      pr[i] = r >= jb + i ? x : 0.0;
+  for (int j = 0; j < kNB; ++j) {
+    const bool mine = g == (j & 3);
+    ds[j >> 2] = mine ? d : ds[j >> 2];
+    if (j + 1 < kNB) {
+      const double x = shfl_d(D[j >> 2], 16 * (j & 3) + j + 1), dn = shfl_d(D[(j + 1) >> 2], 16 * ((j + 1) & 3) + j + 1);
+      const double a = mine && r > j ? D[j >> 2] * -inv : 0.0;
+      if (!FACTORED) D = mfma_f64(a, D[j >> 2], D);
+      // the chain of the next pivot between the two matrix instructions: the second would wait for the first otherwise,
+      // and everything behind it
+      __builtin_amdgcn_sched_barrier(0);
+      d = pivot(j + 1, FACTORED ? dn : fma(-x * inv, x, dn));
+      inv = rcp_fast(d);
+      __builtin_amdgcn_sched_barrier(0);
+      E = mfma_f64(a, E[j >> 2], E);
     }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int j = jb + i;
-      double d = shfl_d(pr[i], j);
-      const double floor_ = tol * d0[kb + j];
-      if (!(d > floor_)) { ok = false; d = floor_ > 0.0 ? floor_ : 1.0; }   // an all-zero column keeps R_jj = 1
-      const double inv = rsqrt_fast(d);
-      const double ri = r > j ? pr[i] * inv : (r == j ? d * inv : 0.0);
-      pr[i] = ri;
-#pragma unroll
-      for (int i2 = i + 1; i2 < 4; ++i2) {
-        const double s = shfl_d(ri, jb + i2);
-        if (r >= jb + i2) pr[i2] -= s * ri;
-      }
-    }
-    const double rowv = g == 0 ? pr[0] : (g == 1 ? pr[1] : (g == 2 ? pr[2] : pr[3]));   // row jb + g, column r
-    if (r >= jb + g) M[(int64_t)(kb + jb + g) * ld + kb + r] = rowv;
-    Rkk[(jb + g) * 17 + r] = rowv;
-    if (r == jb + g) Rkk[(jb + g) * 17 + 16] = rcp_fast(rowv);    // 1 / R[j][j] in the spare column, for the panel solve
-    if (p4 < 3) t = mfma_f64(-rowv, rowv, t);
   }
-  return ok;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int i = g + 4 * v;
+    const double sc = FACTORED ? rcp_fast(ds[v]) : rsqrt_fast(ds[v]);
+    E[v] *= sc;
+    if (!FACTORED) D[v] = i == r ? ds[v] * sc : D[v] * sc;
+    D[v] = i <= r ? D[v] : 0.0;
+  }
+  return clamped == 0;
 }
 
-// In-place inverse of the nb x nb upper-triangular diagonal block at (kb, kb), one wave.
-__device__ void inv_diag_wave(double* M, int ld, int kb, int nb, int lane) {
-  const int c = lane & 15;
-  double rc[kNB], x[kNB];
-#pragma unroll
-  for (int i = 0; i < kNB; ++i) {
-    rc[i] = (i < nb && c < nb) ? (i <= c ? M[(int64_t)(kb + i) * ld + kb + c] : 0.0) : (i == c ? 1.0 : 0.0);
-    x[i] = 0.0;
-  }
-  // x = column c of the inverse: x[c] = 1/r[c][c]; x[i] = -(sum_{t=i+1..c} r[i][t] x[t]) / r[i][i]
-#pragma unroll
-  for (int i = kNB - 1; i >= 0; --i) {
-    double s = 0.0;
-#pragma unroll
-    for (int t = i + 1; t < kNB; ++t) {
-      const double rit = shfl_d(rc[i], t);      // r[i][t] lives in lane t
-      if (t <= c) s = fma(rit, x[t], s);
-    }
-    const double inv_rii = rcp_fast(shfl_d(rc[i], i));
-    if (i == c) x[i] = inv_rii;
-    else if (i < c) x[i] = -s * inv_rii;
-  }
-  if (lane < kNB && c < nb) {
-#pragma unroll
-    for (int i = 0; i < kNB; ++i)
-      if (i <= c) M[(int64_t)(kb + i) * ld + kb + c] = x[i];
-  }
-}
-
-// Trailing update of one 16 x 16 tile on the fp64 matrix cores: M[r0.., c0..] -= P[:, r0..]^T P[:, c0..],
-// P = the 16 freshly solved rows of R (row stride ldp).  Lane (r, g) holds P[4*kk + g][. + r] as A and
-// B operand of step kk; accumulator component v of lane (r, g) is entry [g + 4*v][r].
-__device__ __forceinline__ void trailing_tile(double* M, int64_t ld, const double* P, int ldp, int r0, int c0,
-                                              int lane) {
-  const int r = lane & 15, g = lane >> 4;
-  double* mt = M + (int64_t)(r0 + g) * ld + c0 + r;
-  doublex4 acc;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) acc[v] = mt[(int64_t)4 * v * ld];
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const double* prow = P + (4 * kk + g) * ldp;
-    acc = mfma_f64(-prow[r0 + r], prow[c0 + r], acc);
-  }
-#pragma unroll
-  for (int v = 0; v < 4; ++v) mt[(int64_t)4 * v * ld] = acc[v];
-}
-
-// The working matrix is padded to Lp x Lp with an identity block, so that every block is a full
-// 16 x 16 tile.  Schedule of the factorisation: wave 0 factors the diagonal block of step k+1 (after
-// updating that one tile) while the other waves finish the trailing update of step k, which takes
-// the 16-step pivot chain off the critical path of all but the first block.
-template <bool IN_LDS, typename TO>
+template <bool IN_LDS, bool FACTORED, typename TO>
 __global__ void __launch_bounds__(1024)
-k_chol_inv(double* __restrict__ G, int l, int Lp, double* __restrict__ Rout, double* __restrict__ Xtmp,
-           TO* __restrict__ Rinv_out, int* __restrict__ flag, double tol, int factored, int lenient) {
+k_chol_inv(double* __restrict__ G, int l, int Lp, double* __restrict__ Rout, TO* __restrict__ Rinv_out,
+           int* __restrict__ flag, double tol, int lenient) {
   extern __shared__ double smem[];
   __shared__ int bad;
-  double* Rkk = smem;                 // 16 x 17
-  double* d0 = smem + 16 * 17;        // kMaxL
-  double* rest = d0 + kMaxL;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int ldp = chol_ldp(Lp), ld = IN_LDS ? chol_ldm(Lp) : Lp;
+  double* e = smem;                                // 16 x 17: E_kk
+  double* d0 = e + kNB * (kNB + 1);                // Lp: original diagonal
+  double* pan = d0 + Lp;                           // 16 x ldp
+  double* M = IN_LDS ? pan + kNB * ldp : G;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
+  const int r = lane & 15, g = lane >> 4, nb = Lp / kNB;
   if (flag[0] != 0) return;           // an earlier panel already broke down: results are void anyway
-  double* M;
-  int ld;
-  double* pan;                        // current 16-row panel R[kb:kb+16, :] (row stride ldp)
-  int ldp;
-  if (IN_LDS) {
-    M = rest; ld = Lp + 1;
-    for (int idx = tid; idx < Lp * Lp; idx += 1024) {
-      const int i = idx / Lp, c = idx - i * Lp;
-      M[i * ld + c] = (i < l && c < l) ? (c >= i ? G[(int64_t)i * Lp + c] : 0.0) : (i == c ? 1.0 : 0.0);
-    }
-    pan = nullptr; ldp = ld;
-  } else {
-    M = G; ld = Lp;
-    for (int idx = tid; idx < Lp * Lp; idx += 1024) {
-      const int i = idx / Lp, c = idx - i * Lp;
-      if (i >= l || c >= l) M[(int64_t)i * ld + c] = i == c ? 1.0 : 0.0;
-    }
-    pan = rest; ldp = kMaxL;
-  }
   if (tid == 0) bad = 0;
-  __syncthreads();
-  for (int i = tid; i < Lp; i += 1024) d0[i] = M[(int64_t)i * ld + i];
-  __syncthreads();
 
-  // ---- factorisation (skipped when G already holds an upper-triangular factor) ----
-  if (!factored) {
-    if (wave == 0) {
-      const bool ok = chol_diag_wave(M, ld, 0, kNB, d0, tol, Rkk, lane);
-      if (!ok && !lenient && lane == 0) bad = 1;
+  // The matrix is padded to Lp x Lp with an identity block; R^-1 is zero below its diagonal tiles and in the padding.
+  for (int idx = tid; idx < Lp * Lp; idx += blockDim.x) Rinv_out[idx] = TO(0);
+  for (int t = wave; t < nb * (nb + 1) / 2; t += nw) {
+    int ti = 0, rem = t;
+    while (rem >= nb - ti) { rem -= nb - ti; ++ti; }
+    const int tj = ti + rem, col = kNB * tj + r;
+    double v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int row = kNB * ti + g + 4 * q;
+      const bool in = row < l && col < l;
+      v[q] = G[(int64_t)(in ? row : 0) * Lp + (in ? col : 0)];
+      if (!in) v[q] = row == col ? 1.0 : 0.0;
     }
-    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int row = kNB * ti + g + 4 * q;
+      if (IN_LDS || row >= l || col >= l) M[(int64_t)row * ld + col] = v[q];
+      if (row == col) d0[row] = v[q];
+    }
+  }
+  // the diagonal tile of step k (wave 0), its factor stored, E_kk left for the panel
+  auto diagonal = [&](int k, doublex4 D) {
+    doublex4 E;
+    const bool ok = chol_diag_wave<FACTORED>(D, E, d0 + kNB * k, tol, lane);
+    if (!ok && !lenient && lane == 0) bad = kNB * k + 1;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = g + 4 * v, row = kNB * k + i, col = kNB * k + r;
+      e[i * (kNB + 1) + r] = E[v];
+      if (Rout && row < l && col < l) Rout[(int64_t)row * Lp + col] = D[v];
+    }
+  };
+
+  // Step k = -1 only factors the first diagonal tile (one copy of that long code serves every step).
+  for (int k = -1; k < nb; ++k) {
+    __syncthreads();                  // E_kk is in place, the update of step k - 1 is complete
     if (bad) {
       if (tid == 0) flag[0] = bad;
       return;
     }
-  }
-  for (int kb = factored ? Lp : 0; kb < Lp; kb += kNB) {
-    const int t0 = kb + kNB;          // first trailing column
-    // row panel: R[kb:kb+16, c] = R_kk^-T G[kb:kb+16, c], one column per thread
-    for (int c = t0 + tid; c < Lp; c += 1024) {
-      double x[kNB];
+    // ---- panel: row k of R and of E, and their stores ----
+    const int row0 = kNB * k;
+    for (int c = k < 0 ? nb : wave; c < nb; c += nw) {
+      const int c0 = kNB * c;
+      doublex4 acc = {0.0, 0.0, 0.0, 0.0};
+      if (c == k) {
 #pragma unroll
-      for (int i = 0; i < kNB; ++i) {
-        double sacc = M[(int64_t)(kb + i) * ld + c];
+        for (int v = 0; v < 4; ++v) acc[v] = e[(g + 4 * v) * (kNB + 1) + r];
+      } else if (FACTORED && c > k) {
 #pragma unroll
-        for (int t = 0; t < kNB; ++t)
-          if (t < i) sacc = fma(-Rkk[t * 17 + i], x[t], sacc);
-        x[i] = sacc * Rkk[i * 17 + 16];
-        M[(int64_t)(kb + i) * ld + c] = x[i];
-        if (!IN_LDS) pan[i * ldp + c] = x[i];
+        for (int v = 0; v < 4; ++v) acc[v] = M[(int64_t)(row0 + g + 4 * v) * ld + c0 + r];
+      } else {
+        double b[4];
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) b[kk] = M[(int64_t)(row0 + 4 * kk + g) * ld + c0 + r];
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) acc = mfma_f64(e[r * (kNB + 1) + 4 * kk + g], b[kk], acc);
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int i = row0 + g + 4 * v, j = c0 + r;
+        pan[(g + 4 * v) * ldp + j] = acc[v];
+        if (i < l && j < l) {
+          if (c > k) { if (Rout) { Rout[(int64_t)i * Lp + j] = acc[v]; Rout[(int64_t)j * Lp + i] = 0.0; } }
+          else Rinv_out[(int64_t)j * Lp + i] = (TO)acc[v];
+        }
       }
     }
     __syncthreads();
-    // trailing update, upper tiles (ti <= tj) of the (Lp - t0)^2 block; tile 0 = (0, 0) is the next
-    // diagonal block: wave 0 updates it and factors it at once, waves 1..15 share the other tiles
-    const double* P = IN_LDS ? (M + (int64_t)kb * ld) : pan;
-    const int T16 = (Lp - t0) / kNB;
-    const int ntile = T16 * (T16 + 1) / 2;
+    // ---- update of the rows below, a few tiles at a time so that their loads overlap ----
+    const int a = nb - 1 - k;                       // rows left
+    auto update = [&](int i, int c, doublex4 acc) {
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        const double* p = pan + (4 * kk + g) * ldp + r;
+        acc = mfma_f64(-p[kNB * i], p[kNB * c], acc);
+      }
+      return acc;
+    };
+    auto load = [&](int i, int c) {
+      doublex4 t = {0.0, 0.0, 0.0, 0.0};
+      if (c != k) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) t[v] = M[(int64_t)(kNB * i + g + 4 * v) * ld + kNB * c + r];
+      }
+      return t;
+    };
     if (wave == 0) {
-      if (ntile > 0) {
-        trailing_tile(M, ld, P, ldp, t0, t0, lane);
-        const bool ok = chol_diag_wave(M, ld, t0, kNB, d0, tol, Rkk, lane);
-        if (!ok && !lenient && lane == 0) bad = t0 + 1;
+      if (a > 0) {
+        doublex4 t = load(k + 1, k + 1);
+        if (!FACTORED && k >= 0) t = update(k + 1, k + 1, t);
+        __builtin_amdgcn_s_setprio(3);
+        diagonal(k + 1, t);
+        __builtin_amdgcn_s_setprio(0);
       }
-    } else {
-      for (int idx = wave; idx < ntile; idx += 15) {
-        int ti = 0, rem = idx;
-        while (rem >= T16 - ti) { rem -= T16 - ti; ++ti; }
-        trailing_tile(M, ld, P, ldp, t0 + kNB * ti, t0 + kNB * (ti + rem), lane);
-      }
-    }
-    __syncthreads();
-    if (bad) {
-      if (tid == 0) flag[0] = bad;
-      return;
-    }
-  }
-
-  // ---- publish R ----
-  if (Rout) {
-    for (int idx = tid; idx < l * l; idx += 1024) {
-      int i = idx / l, c = idx - i * l;
-      Rout[(int64_t)i * Lp + c] = c >= i ? M[(int64_t)i * ld + c] : 0.0;
-    }
-  }
-  __syncthreads();
-
-  // ---- inverse, level 0: diagonal blocks, one wave each (the padding block is an identity) ----
-  const int nblk = Lp / kNB;
-  for (int bi = wave; bi < nblk; bi += 16) inv_diag_wave(M, ld, bi * kNB, kNB, lane);
-  __syncthreads();
-  // ---- merge levels on the fp64 matrix cores: X12 = -X11 (R12 X22), tile by tile.  A pair at level B
-  // (in tiles) joins the inverted blocks [a0, a0+B) and [a0+B, a0+B+w).  Phase 0 forms T = R12 X22
-  // (X22 upper triangular: tiles tk <= tj), phase 1 forms X12 = -X11 T (tiles tk >= ti).  Diagonal tiles
-  // of X11 / X22 are masked to their upper triangle (their lower part holds leftovers of the trailing
-  // updates).  LDS variant: at most 16 tiles per phase, one per wave, held in registers until every
-  // wave has finished reading, then written in place.  Global variant: T goes to the scratch Xtmp. ----
-  {
-    const int r = lane & 15, g = lane >> 4;
-    for (int B = 1; B < nblk; B *= 2) {
-      const int npair = (nblk + 2 * B - 1) / (2 * B);
-      for (int phase = 0; phase < 2; ++phase) {
-        doublex4 keep = {0.0, 0.0, 0.0, 0.0};
-        int kr0 = -1, kc0 = 0;
-        int tile = 0;                                   // running tile index over all pairs of this level
-        for (int p = 0; p < npair; ++p) {
-          const int a0 = 2 * B * p;                     // in tiles
-          const int w = min(a0 + 2 * B, nblk) - (a0 + B);
-          if (w <= 0) continue;
-          for (int t = 0; t < B * w; ++t, ++tile) {
-            if ((tile & 15) != wave) continue;
-            const int ti = t / w, tj = t - ti * w;      // tile row within the left block, tile column within the right
-            const int r0 = (a0 + ti) * kNB, c0 = (a0 + B + tj) * kNB;
-            doublex4 acc = {0.0, 0.0, 0.0, 0.0};
-            if (phase == 0) {
-              for (int tk = 0; tk <= tj; ++tk) {
-                const int k0 = (a0 + B + tk) * kNB;
+    } else if (k >= 0 && (!IN_LDS || (wave & 3) != 0)) {
+      // small matrices: the pivot chain has its SIMD (every fourth wave) to itself
+      // row i = k + 1 + q: k + 1 tiles of E, then the tiles i..nb - 1 of G (not the first one of all: wave 0 has it)
+      const int helpers = IN_LDS ? nw - nw / 4 : nw - 1;
+      int q = 0, pos = IN_LDS ? wave - 1 - (wave >> 2) : wave - 1, width = k + 1 + (FACTORED ? 0 : a - 1);
+      constexpr int BATCH = 4;
+      while (q < a) {
+        int ti[BATCH], tc[BATCH];
+        doublex4 t[BATCH];
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk) {
-                  const int k = 4 * kk + g;
-                  const double av = M[(int64_t)(r0 + r) * ld + k0 + k];                       // R12[i = r][k]
-                  double bv = M[(int64_t)(k0 + k) * ld + c0 + r];                             // X22[k][j = r]
-                  if (tk == tj && k > r) bv = 0.0;
-                  acc = mfma_f64(av, bv, acc);
-                }
-              }
-            } else {
-              const double* Tm = IN_LDS ? M : Xtmp;
-              const int64_t ldt = IN_LDS ? ld : Lp;
-              for (int tk = ti; tk < B; ++tk) {
-                const int k0 = (a0 + tk) * kNB;
-#pragma unroll
-                for (int kk = 0; kk < 4; ++kk) {
-                  const int k = 4 * kk + g;
-                  double av = M[(int64_t)(r0 + r) * ld + k0 + k];                             // X11[i = r][k]
-                  if (tk == ti && r > k) av = 0.0;
-                  const double bv = Tm[(int64_t)(k0 + k) * ldt + c0 + r];                     // T[k][j = r]
-                  acc = mfma_f64(-av, bv, acc);
-                }
-              }
-            }
-            // accumulator component v of lane (r, g) is entry [g + 4 v][r] of the tile
-            if (IN_LDS) {
-              keep = acc; kr0 = r0; kc0 = c0;
-            } else {
-              double* dst = phase == 0 ? Xtmp : M;
-              const int64_t ldd = phase == 0 ? Lp : ld;
-#pragma unroll
-              for (int v = 0; v < 4; ++v) dst[(int64_t)(r0 + g + 4 * v) * ldd + c0 + r] = acc[v];
-            }
-          }
+        for (int b = 0; b < BATCH; ++b) {
+          while (q < a && pos >= width) { pos -= width; ++q; width = k + 1 + (FACTORED ? 0 : a - q); }
+          const int i = k + 1 + q;
+          ti[b] = q < a ? i : -1;
+          tc[b] = pos <= k ? pos : i + (pos - (k + 1)) + (q == 0 ? 1 : 0);
+          if (ti[b] >= 0) t[b] = load(ti[b], tc[b]);
+          pos += helpers;
         }
-        __syncthreads();
-        if (IN_LDS && kr0 >= 0) {
 #pragma unroll
-          for (int v = 0; v < 4; ++v) M[(int64_t)(kr0 + g + 4 * v) * ld + kc0 + r] = keep[v];
+        for (int b = 0; b < BATCH; ++b) {
+          if (ti[b] < 0) continue;
+          t[b] = update(ti[b], tc[b], t[b]);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) M[(int64_t)(kNB * ti[b] + g + 4 * v) * ld + kNB * tc[b] + r] = t[b][v];
         }
-        __syncthreads();
       }
     }
-  }
-  // R^-1 in the panels' type, zero below the diagonal and in the padding
-  for (int idx = tid; idx < Lp * Lp; idx += 1024) {
-    const int i = idx / Lp, c = idx - i * Lp;
-    Rinv_out[idx] = (i < l && c < l && c >= i) ? (TO)M[(int64_t)i * ld + c] : TO(0);
   }
 }
 
@@ -488,32 +422,32 @@ static int gram(const T* P, int64_t rows, int Lp, OrthWorkT<T>& w, hipStream_t s
 // lenient != 0: pivots below tol * (original diagonal) are clamped and the factorisation goes on;
 // otherwise such a pivot raises the breakdown flag and ends the kernel.
 template <typename TO>
-static int chol_inv(double* G, int l, int Lp, double* Rout, double* Xtmp, TO* Rinv, int* flags, double tol,
-                    hipStream_t stream, int factored = 0, int lenient = 0) {
+static int chol_inv(double* G, int l, int Lp, double* Rout, TO* Rinv, int* flags, double tol, hipStream_t stream,
+                    int factored = 0, int lenient = 0) {
   const bool in_lds = Lp <= kCholLdsMaxLp;
-  const size_t lds = (16 * 17 + kMaxL + (in_lds ? (size_t)Lp * (Lp + 1) : (size_t)kNB * kMaxL)) * sizeof(double);
-  static bool attr_set = false;
-  if (!attr_set) {
-    const int max_lds = (16 * 17 + kMaxL + kCholLdsMaxLp * (kCholLdsMaxLp + 1)) * (int)sizeof(double);
-    BRSVD_HIP_TRY(hipFuncSetAttribute((const void*)k_chol_inv<true, TO>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      max_lds));
-    BRSVD_HIP_TRY(hipFuncSetAttribute((const void*)k_chol_inv<false, TO>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      (16 * 17 + kMaxL + kNB * kMaxL) * (int)sizeof(double)));
-    attr_set = true;
-  }
-  if (in_lds)
-    hipLaunchKernelGGL((k_chol_inv<true, TO>), dim3(1), dim3(1024), lds, stream, G, l, Lp, Rout, Xtmp, Rinv, flags, tol,
-                       factored, lenient);
-  else
-    hipLaunchKernelGGL((k_chol_inv<false, TO>), dim3(1), dim3(1024), lds, stream, G, l, Lp, Rout, Xtmp, Rinv, flags,
-                       tol, factored, lenient);
-  BRSVD_HIP_TRY(hipGetLastError());
-  return BRSVD_OK;
+  const size_t lds = chol_lds_bytes(Lp, in_lds);
+  // a step has at most one panel tile per wave up to 16 column tiles; two tiles leave work for four waves only
+  const int threads = Lp <= 32 ? 256 : (Lp <= 64 ? 512 : 1024);
+  auto launch = [&](auto kern, size_t max_lds, bool* attr_set) -> int {
+    if (!*attr_set) {
+      BRSVD_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds));
+      *attr_set = true;
+    }
+    hipLaunchKernelGGL(kern, dim3(1), dim3(threads), lds, stream, G, l, Lp, Rout, Rinv, flags, tol, lenient);
+    BRSVD_HIP_TRY(hipGetLastError());
+    return BRSVD_OK;
+  };
+  static bool attr_set[4] = {false, false, false, false};
+  const size_t most_lds = chol_lds_bytes(kCholLdsMaxLp, true), most = chol_lds_bytes(kMaxL, false);
+  if (factored)
+    return in_lds ? launch(k_chol_inv<true, true, TO>, most_lds, attr_set) : launch(k_chol_inv<false, true, TO>, most, attr_set + 1);
+  return in_lds ? launch(k_chol_inv<true, false, TO>, most_lds, attr_set + 2)
+                : launch(k_chol_inv<false, false, TO>, most, attr_set + 3);
 }
 
 template <typename T>
-int chol_inv_factored(double* G, int l, int Lp, double* Rout, double* Xtmp, T* Rinv, int* flags, hipStream_t stream) {
-  return chol_inv<T>(G, l, Lp, Rout, Xtmp, Rinv, flags, 0.0, stream, 1);
+int chol_inv_factored(double* G, int l, int Lp, double* Rout, T* Rinv, int* flags, hipStream_t stream) {
+  return chol_inv<T>(G, l, Lp, Rout, Rinv, flags, 0.0, stream, 1);
 }
 
 template <typename T>
@@ -572,7 +506,7 @@ int cholqr_sweeps(T* P, T* tmp, int64_t rows, int l, int Lp, int nsweeps, OrthWo
     BRSVD_TRY(gram<T>(src, rows, Lp, w, stream));
     const int lenient = (sweep + 1 < nsweeps || !strict_last) ? 1 : 0;
     double* Rs = (Rtot || publish_R) ? w.R[sweep] : nullptr;      // the factor is only written out when someone reads it
-    BRSVD_TRY(chol_inv<T>(w.G, l, Lp, Rs, w.Xinv, w.Rinv, w.flags, tol, stream, 0, lenient));
+    BRSVD_TRY(chol_inv<T>(w.G, l, Lp, Rs, w.Rinv, w.flags, tol, stream, 0, lenient));
     BRSVD_TRY(gemm_an(src, Lp, rows, Lp, w.Rinv, Lp, dst, Lp, Lp, w.gemm_scratch, w.gemm_scratch_bytes, stream));
     BRSVD_TRY(apply_to_companion<T>(w, Lp, stream));
     T* t = src; src = dst; dst = t;
@@ -600,7 +534,7 @@ int orth_panel(T* P, T* tmp, int64_t rows, int l, int Lp, int method, bool final
 }
 
 #define BRSVD_ORTH_INSTANTIATE(T)                                                                               \
-  template int chol_inv_factored<T>(double*, int, int, double*, double*, T*, int*, hipStream_t);                \
+  template int chol_inv_factored<T>(double*, int, int, double*, T*, int*, hipStream_t);                         \
   template int apply_to_companion<T>(OrthWorkT<T>&, int, hipStream_t);                                          \
   template int cholqr_sweeps<T>(T*, T*, int64_t, int, int, int, OrthWorkT<T>&, double*, T**, hipStream_t, bool, \
                                 bool);                                                                          \
