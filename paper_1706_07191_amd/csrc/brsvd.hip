@@ -51,16 +51,22 @@ struct brsvd_handle_s {
   hipStream_t compute, copy;
   bool own_copy;
   hipEvent_t filled[2], drained[2];
-  int* host_flags;                 // pinned: [0] breakdown, [1] sweeps, [2] converged
-  double* host_scal;               // pinned scalars for the robust-PCA loop
-  std::vector<hipEvent_t> ev;      // timing event pool
-  std::vector<std::pair<int, int>> regions[CAT_COUNT];
-  size_t ev_used;
+  int* host_flags;                 // pinned copy of the flags: [0] breakdown, [4] sweeps, [5] converged
+  double* host_scal;               // and of the scalars (same allocation: both arrive with one copy)
+  std::vector<hipEvent_t> ev;      // timing event pool, one half per timeline
   bool timing;
   bool own_arena;                  // false: the arena is the caller's workspace
-  int64_t launches[CAT_COUNT];
-  int64_t bytes_A_kernels;         // bytes of A (or of its staged blocks) read by the pass kernels
-  int64_t bytes_A_copied;          // bytes of A copied host -> device
+  // What one call, or one iteration of the robust-PCA loop, has recorded.  The loop alternates between the two, so that the
+  // host reads one iteration's events while the next one runs.
+  struct Timeline {
+    std::vector<std::pair<int, int>> regions[CAT_COUNT];
+    size_t ev_used, ev_end;
+    int last;                      // the last event recorded on the compute stream, -1 if work may have followed it
+    int64_t launches[CAT_COUNT];
+    int64_t bytes_A_kernels;       // bytes of A (or of its staged blocks) read by the pass kernels
+    int64_t bytes_A_copied;        // bytes of A copied host -> device
+  } tl[2];
+  int cur;                         // the timeline being recorded
 
   int esz() const { return prm.dtype == BRSVD_DTYPE_F64 ? 8 : 4; }
   template <typename T = float> T* Pm(int i) { return (T*)(arena + lay.Pm[i]); }
@@ -127,7 +133,7 @@ Layout make_layout(const brsvd_params& p, int64_t b) {
   L.sig = take((uint64_t)3 * Lp * 8);
   L.S32 = take((uint64_t)Lp * esz);
   L.flags = take(64);
-  L.scal = take(64);
+  L.scal = take(64);         // directly behind the flags (run_sync_with copies both at once)
   if (!host) {   // results of the inner SVDs of the robust-PCA loop, and its reduction scratch
     L.rpcaU = take((uint64_t)m * l * esz);
     L.rpcaVt = take((uint64_t)l * n * esz);
@@ -175,40 +181,61 @@ int resolve_block(const brsvd_params& p, int64_t* b_out) {
   return BRSVD_OK;
 }
 
+// Records an event of the running timeline on s; -1 when the pool is used up.
+int mark(brsvd_handle h, hipStream_t s) {
+  auto& t = h->tl[h->cur];
+  if (!h->timing || t.ev_used + 1 > t.ev_end) return -1;
+  const int i = (int)t.ev_used++;
+  (void)hipEventRecord(h->ev[i], s);
+  return i;
+}
+
+// A timed phase.  Phases that follow each other with nothing enqueued in between (`follows`) share the event: each one costs
+// a stop of the queue.
 struct Region {
   brsvd_handle h;
   int cat;
   hipStream_t s;
   int i0;
-  Region(brsvd_handle h_, int cat_, hipStream_t s_) : h(h_), cat(cat_), s(s_), i0(-1) {
-    if (!h->timing || h->ev_used + 2 > h->ev.size()) return;
+  Region(brsvd_handle h_, int cat_, hipStream_t s_, bool follows = false) : h(h_), cat(cat_), s(s_), i0(-1) {
     // timing_level 1: only the pass kernels, the copies and the whole call are timed
-    if (h->prm.timing_level == 1 && cat != CAT_TOTAL && cat != CAT_COPY && cat != CAT_UPD) return;
-    i0 = (int)h->ev_used;
-    h->ev_used += 2;
-    (void)hipEventRecord(h->ev[i0], s);
+    auto& t = h->tl[h->cur];
+    if (!h->timing || (h->prm.timing_level == 1 && cat != CAT_TOTAL && cat != CAT_COPY && cat != CAT_UPD)) {
+      t.last = -1;                 // work that is not timed follows
+      return;
+    }
+    i0 = follows && t.last >= 0 ? t.last : mark(h, s);
   }
   ~Region() {
-    if (i0 < 0) return;
-    (void)hipEventRecord(h->ev[i0 + 1], s);
-    h->regions[cat].push_back({i0, i0 + 1});
+    const int i1 = i0 < 0 ? -1 : mark(h, s);
+    if (i1 < 0) {
+      h->tl[h->cur].last = -1;
+      return;
+    }
+    h->tl[h->cur].regions[cat].push_back({i0, i1});
+    if (s == h->compute) h->tl[h->cur].last = i1;
   }
 };
 
-// Accounts for one pass-kernel launch that reads `rows` rows of A, and hands out events from the pool
-// for tight per-kernel timing: one pair registered under `cat`, one under CAT_SUM for the split sums.
-bool kernel_events(brsvd_handle h, int cat, int64_t rows, KernelEvents* ke) {
-  h->launches[cat]++;
-  h->bytes_A_kernels += rows * h->prm.n * h->esz();
-  if (!h->timing || h->ev_used + 4 > h->ev.size()) return false;
-  int i0 = (int)h->ev_used;
-  h->ev_used += 4;
-  ke->start = h->ev[i0];
-  ke->stop = h->ev[i0 + 1];
-  ke->sum_start = h->ev[i0 + 2];
-  ke->sum_stop = h->ev[i0 + 3];
-  h->regions[cat].push_back({i0, i0 + 1});
-  h->regions[CAT_SUM].push_back({i0 + 2, i0 + 3});
+// Accounts for one pass-kernel launch that reads `rows` rows of A, and hands out events for tight per-kernel timing:
+// start and stop of the product kernels, registered under `cat`, and the end of the split sums (CAT_SUM).
+// follows: nothing has been enqueued since the last phase ended.
+bool kernel_events(brsvd_handle h, int cat, int64_t rows, KernelEvents* ke, bool follows = false) {
+  auto& t = h->tl[h->cur];
+  t.launches[cat]++;
+  t.bytes_A_kernels += rows * h->prm.n * h->esz();
+  if (!h->timing || t.ev_used + 3 > t.ev_end) {
+    t.last = -1;
+    return false;
+  }
+  const int i0 = follows && t.last >= 0 ? t.last : mark(h, h->compute);
+  const int i1 = (int)t.ev_used;
+  t.ev_used += 2;
+  ke->stop = h->ev[i1];
+  ke->sum_stop = h->ev[i1 + 1];
+  t.regions[cat].push_back({i0, i1});
+  t.regions[CAT_SUM].push_back({i1, i1 + 1});
+  t.last = i1 + 1;
   return true;
 }
 
@@ -247,7 +274,7 @@ struct Streamer {
     const size_t esz = (size_t)h->esz();
     const char* src = A + (int64_t)i * h->b * lda * esz;
     const int64_t rows = rows_of(i), n = h->prm.n;
-    h->bytes_A_copied += rows * n * (int64_t)esz;
+    h->tl[h->cur].bytes_A_copied += rows * n * (int64_t)esz;
     Region r(h, CAT_COPY, h->copy);
     if (lda == n) {
       BRSVD_HIP_TRY(hipMemcpyAsync(dst, src, (size_t)rows * n * esz, hipMemcpyHostToDevice, h->copy));
@@ -306,12 +333,12 @@ int product_at(brsvd_handle h, const T* A, int64_t lda, int64_t rows, const T* Q
 }
 
 template <typename T>
-int pass_an(brsvd_handle h, const T* A, int64_t lda, const T* X, T* Y) {
+int pass_an(brsvd_handle h, const T* A, int64_t lda, const T* X, T* Y, bool follows = false) {
   const int Lp = h->Lp;
   const int64_t m = h->prm.m, n = h->prm.n;
   if (!h->host_a) {
     KernelEvents ke;
-    bool t = kernel_events(h, CAT_AN, m, &ke);
+    bool t = kernel_events(h, CAT_AN, m, &ke, follows);
     return product_an<T>(h, A, lda, m, X, Y, t ? &ke : nullptr);
   }
   Streamer st(h, A, lda);
@@ -327,12 +354,12 @@ int pass_an(brsvd_handle h, const T* A, int64_t lda, const T* X, T* Y) {
 }
 
 template <typename T>
-int pass_at(brsvd_handle h, const T* A, int64_t lda, const T* Q, T* Z) {
+int pass_at(brsvd_handle h, const T* A, int64_t lda, const T* Q, T* Z, bool follows = false) {
   const int Lp = h->Lp;
   const int64_t m = h->prm.m, n = h->prm.n;
   if (!h->host_a) {
     KernelEvents ke;
-    bool t = kernel_events(h, CAT_AT, m, &ke);
+    bool t = kernel_events(h, CAT_AT, m, &ke, follows);
     // device-resident A: one launch over all rows; the row range is cut into equal sub-ranges whose partial
     // panels are added in row order (the row blocks matter only when A is streamed block by block)
     return product_at<T>(h, A, lda, m, Q, Z, false, t ? &ke : nullptr);
@@ -357,7 +384,7 @@ int pass_fused(brsvd_handle h, const T* A, int64_t lda, const T* X, T* Tm_, T* Z
   const int64_t n = h->prm.n;
   if (!h->host_a) {
     BRSVD_TRY(pass_an<T>(h, A, lda, X, Tm_));
-    return pass_at<T>(h, A, lda, Tm_, Z);
+    return pass_at<T>(h, A, lda, Tm_, Z, true);
   }
   Streamer st(h, A, lda);
   for (int i = 0; i < h->nblocks; ++i) {
@@ -422,32 +449,32 @@ int enqueue_brsvd(brsvd_handle h, const T* A, int64_t lda, const T* Omega, T* U,
   } else {
     BRSVD_TRY(pass_an<T>(h, A, lda, Xn, Ym));
     {
-      Region r(h, CAT_ORTH, cs);
+      Region r(h, CAT_ORTH, cs, !h->host_a);
       BRSVD_TRY(orth_panel<T>(Ym, Tm, m, l, Lp, method, q == 0, ow, nullptr, &res, cs));
       if (res != Ym) std::swap(Ym, Tm);
     }
     for (int it = 0; it < q; ++it) {
-      BRSVD_TRY(pass_at<T>(h, A, lda, Ym, Xn));
+      BRSVD_TRY(pass_at<T>(h, A, lda, Ym, Xn, true));
       {
-        Region r(h, CAT_ORTH, cs);
+        Region r(h, CAT_ORTH, cs, !h->host_a);
         BRSVD_TRY(orth_panel<T>(Xn, Tn, n, l, Lp, method, false, ow, nullptr, &res, cs));
         if (res != Xn) std::swap(Xn, Tn);
       }
-      BRSVD_TRY(pass_an<T>(h, A, lda, Xn, Tm));
+      BRSVD_TRY(pass_an<T>(h, A, lda, Xn, Tm, true));
       std::swap(Ym, Tm);
       {
-        Region r(h, CAT_ORTH, cs);
+        Region r(h, CAT_ORTH, cs, !h->host_a);
         BRSVD_TRY(orth_panel<T>(Ym, Tm, m, l, Lp, method, it == q - 1, ow, nullptr, &res, cs));
         if (res != Ym) std::swap(Ym, Tm);
       }
     }
     // projection B^T = A^T Q
-    BRSVD_TRY(pass_at<T>(h, A, lda, Ym, Xn));
+    BRSVD_TRY(pass_at<T>(h, A, lda, Ym, Xn, true));
   }
   // thin QR of B^T, the small SVD, the lifts
   double* Rtot = h->at<double>(h->lay.Rtot);
   {
-    Region r(h, CAT_ORTH, cs);
+    Region r(h, CAT_ORTH, cs, !h->host_a);
     BRSVD_TRY(orth_panel<T>(Xn, Tn, n, l, Lp, method, true, ow, Rtot, &res, cs));
     if (res != Xn) std::swap(Xn, Tn);
   }
@@ -459,11 +486,11 @@ int enqueue_brsvd(brsvd_handle h, const T* A, int64_t lda, const T* Omega, T* U,
   T* XV = h->at<T>(h->lay.XV);
   T* XU = h->at<T>(h->lay.XU);
   {
-    Region r(h, CAT_SVD, cs);
+    Region r(h, CAT_SVD, cs, true);
     BRSVD_TRY(small_svd<T>(Rtot, Lp, l, Lp, sw, ow.flags, nullptr, S, XV, XU, nullptr, nullptr, cs));
   }
   {
-    Region r(h, CAT_LIFT, cs);
+    Region r(h, CAT_LIFT, cs, true);
     BRSVD_TRY(gemm_an(Ym, Lp, m, Lp, XV, Lp, U, l, l, scr, scr_bytes, cs));          // U = Q * Vr
     BRSVD_TRY(gemm_an(Xn, Lp, n, Lp, XU, Lp, Tn, Lp, Lp, scr, scr_bytes, cs));       // V = W_B * Ur
     BRSVD_TRY(transpose_panel(Tn, n, Lp, l, Vt, cs));
@@ -555,16 +582,22 @@ int enqueue_alg2(brsvd_handle h, const T* A, int64_t lda, uint64_t seed, const T
   return BRSVD_OK;
 }
 
-void reset_timing(brsvd_handle h, bool on) {
+// Starts recording into timeline k.
+void reset_timing(brsvd_handle h, bool on, int k = 0) {
   h->timing = on;
-  h->ev_used = 0;
-  h->bytes_A_kernels = h->bytes_A_copied = 0;
-  for (int c = 0; c < CAT_COUNT; ++c) { h->regions[c].clear(); h->launches[c] = 0; }
+  h->cur = k;
+  auto& t = h->tl[k];
+  const size_t half = h->ev.size() / 2;
+  t.ev_used = k * half;
+  t.ev_end = t.ev_used + half;
+  t.last = -1;
+  t.bytes_A_kernels = t.bytes_A_copied = 0;
+  for (int c = 0; c < CAT_COUNT; ++c) { t.regions[c].clear(); t.launches[c] = 0; }
 }
 
-double sum_regions(brsvd_handle h, int cat) {
+double sum_regions(brsvd_handle h, int k, int cat) {
   double s = 0.0;
-  for (auto& pr : h->regions[cat]) {
+  for (auto& pr : h->tl[k].regions[cat]) {
     float ms = 0.f;
     if (hipEventElapsedTime(&ms, h->ev[pr.first], h->ev[pr.second]) == hipSuccess) s += ms * 1e-3;
   }
@@ -573,27 +606,28 @@ double sum_regions(brsvd_handle h, int cat) {
 
 // Reads of A are counted where they happen: a host-resident A is read over the host link by the block
 // copies (the kernels then read the staged blocks), a device-resident A by the pass kernels themselves.
-void fill_stats(brsvd_handle h, brsvd_stats* st, int fallbacks, int fused_fallbacks) {
+void fill_stats(brsvd_handle h, brsvd_stats* st, int fallbacks, int fused_fallbacks, int k = 0) {
+  const auto& t = h->tl[k];
   std::memset(st, 0, sizeof(*st));
-  st->total_seconds = sum_regions(h, CAT_TOTAL);
-  st->gemm_an_seconds = sum_regions(h, CAT_AN);
-  st->gemm_at_seconds = sum_regions(h, CAT_AT);
-  st->orth_seconds = sum_regions(h, CAT_ORTH);
-  st->svd_seconds = sum_regions(h, CAT_SVD);
-  st->lift_seconds = sum_regions(h, CAT_LIFT);
-  st->copy_seconds = sum_regions(h, CAT_COPY);
-  st->elementwise_seconds = sum_regions(h, CAT_ELEM);
-  st->gemm_an_launches = h->launches[CAT_AN];
-  st->gemm_at_launches = h->launches[CAT_AT];
-  st->split_sum_seconds = sum_regions(h, CAT_SUM);
-  st->rpca_update_seconds = sum_regions(h, CAT_UPD);
-  st->rpca_update_launches = h->launches[CAT_UPD];
-  st->bytes_A_streamed = h->host_a ? h->bytes_A_copied : h->bytes_A_kernels;
-  st->bytes_A_read_by_kernels = h->bytes_A_kernels;
+  st->total_seconds = sum_regions(h, k, CAT_TOTAL);
+  st->gemm_an_seconds = sum_regions(h, k, CAT_AN);
+  st->gemm_at_seconds = sum_regions(h, k, CAT_AT);
+  st->orth_seconds = sum_regions(h, k, CAT_ORTH);
+  st->svd_seconds = sum_regions(h, k, CAT_SVD);
+  st->lift_seconds = sum_regions(h, k, CAT_LIFT);
+  st->copy_seconds = sum_regions(h, k, CAT_COPY);
+  st->elementwise_seconds = sum_regions(h, k, CAT_ELEM);
+  st->gemm_an_launches = t.launches[CAT_AN];
+  st->gemm_at_launches = t.launches[CAT_AT];
+  st->split_sum_seconds = sum_regions(h, k, CAT_SUM);
+  st->rpca_update_seconds = sum_regions(h, k, CAT_UPD);
+  st->rpca_update_launches = t.launches[CAT_UPD];
+  st->bytes_A_streamed = h->host_a ? t.bytes_A_copied : t.bytes_A_kernels;
+  st->bytes_A_read_by_kernels = t.bytes_A_kernels;
   st->passes_over_A = st->bytes_A_streamed / ((int64_t)h->esz() * h->prm.m * h->prm.n);
   st->orth_fallbacks = fallbacks;
   st->fused_fallbacks = fused_fallbacks;
-  st->jacobi_sweeps = h->host_flags[1];
+  st->jacobi_sweeps = h->host_flags[4];
   st->row_block = (int32_t)h->b;
   st->n_blocks = h->nblocks;
 }
@@ -639,7 +673,6 @@ int run_sync_with(brsvd_handle h, bool fused_possible, int* fallbacks, int* fuse
   int method = h->prm.orth_method;
   bool fused = fused_possible;
   int* dflags = h->at<int>(h->lay.flags);
-  double* dratio = h->at<double>(h->lay.scal) + kScalFusedRatio;
   for (int attempt = 0; attempt < 3; ++attempt) {
     BRSVD_HIP_TRY(hipMemsetAsync(dflags, 0, 64, h->compute));
     if (h->host_a) {
@@ -656,12 +689,8 @@ int run_sync_with(brsvd_handle h, bool fused_possible, int* fallbacks, int* fuse
         return st;
       }
     }
-    BRSVD_HIP_TRY(hipMemcpyAsync(h->host_flags, dflags, sizeof(int), hipMemcpyDeviceToHost, h->compute));
-    BRSVD_HIP_TRY(hipMemcpyAsync(h->host_flags + 1, dflags + 4, 2 * sizeof(int), hipMemcpyDeviceToHost,
-                                 h->compute));
-    if (fused)
-      BRSVD_HIP_TRY(hipMemcpyAsync(h->host_scal + kScalFusedRatio, dratio, sizeof(double), hipMemcpyDeviceToHost,
-                                   h->compute));
+    // flags and scalars lie next to each other, on the device and in the pinned block: one copy
+    BRSVD_HIP_TRY(hipMemcpyAsync(h->host_flags, dflags, kAlign + 64, hipMemcpyDeviceToHost, h->compute));
     BRSVD_HIP_TRY(hipStreamSynchronize(h->compute));
     if (h->host_a) BRSVD_HIP_TRY(hipStreamSynchronize(h->copy));
     if (h->host_flags[0] != 0) {
@@ -675,7 +704,7 @@ int run_sync_with(brsvd_handle h, bool fused_possible, int* fallbacks, int* fuse
       if (fused_fallbacks) ++*fused_fallbacks;
       continue;
     }
-    if (h->host_flags[2] == 0) return BRSVD_ERR_SVD_NOCONV;
+    if (h->host_flags[5] == 0) return BRSVD_ERR_SVD_NOCONV;
     return BRSVD_OK;
   }
   return BRSVD_ERR_ORTH_BREAKDOWN;
@@ -772,7 +801,10 @@ int rpca_loop(brsvd_handle h, const T* M, const T* Omegas, int32_t max_iters, do
   // so the multiplier an iteration read is still there when the loop stops and L and S are formed from it.
   T* Ycur = work;
   T* Yalt = L;
+  // The matrix handed to the SVD alternates between the second half of `work` and S, so that the update can be enqueued before
+  // the host knows whether the SVD succeeded: a repeated attempt finds everything it reads in place.
   T* X = work + count;
+  T* Xalt = S;
   T* Uw = h->at<T>(h->lay.rpcaU);
   T* Vtw = h->at<T>(h->lay.rpcaVt);
   T* Sw = h->at<T>(h->lay.S32);
@@ -780,13 +812,13 @@ int rpca_loop(brsvd_handle h, const T* M, const T* Omegas, int32_t max_iters, do
   double* scal = h->at<double>(h->lay.scal);
   brsvd_stats acc;
   std::memset(&acc, 0, sizeof(acc));
-  auto flush_stats = [&](int fallbacks, int fused_fallbacks) {
+  // adds timeline k to the statistics, once its last event has been reached
+  auto add_timeline = [&](int k, int fallbacks, int fused_fallbacks) {
     if (!stats) return;
-    (void)hipStreamSynchronize(cs);
+    if (h->tl[k].last >= 0) (void)hipEventSynchronize(h->ev[h->tl[k].last]);
     brsvd_stats one;
-    fill_stats(h, &one, fallbacks, fused_fallbacks);
+    fill_stats(h, &one, fallbacks, fused_fallbacks, k);
     add_stats(&acc, one);
-    reset_timing(h, true);
   };
   reset_timing(h, stats != nullptr);
 
@@ -808,53 +840,66 @@ int rpca_loop(brsvd_handle h, const T* M, const T* Omegas, int32_t max_iters, do
     T s0 = T(0);
     BRSVD_HIP_TRY(hipMemcpy(&s0, Sw, sizeof(T), hipMemcpyDeviceToHost));
     norm2_M = (double)s0;
-    flush_stats(fb, ffb);
+    add_timeline(0, fb, ffb);
+    reset_timing(h, stats != nullptr);
     if (!(norm2_M > 0.0)) return BRSVD_ERR_ARG;
   }
   const double J = std::max(norm2_M, max_abs / (double)lambda);
   double mu = mu0;
   {
     Region r(h, CAT_ELEM, cs);
-    BRSVD_TRY(rpca_init<T>(M, count, (T)(1.0 / J), (T)(1.0 / mu), Ycur, S, X, cs));
+    BRSVD_TRY(rpca_init<T>(M, count, (T)(1.0 / J), (T)(1.0 / mu), Ycur, X, cs));
   }
-  int it = 0;
+  int it = 0, pending = 0, fb_p = 0, ffb_p = 0;      // timeline whose events have not been read yet, with its fallbacks
   double mu_last = mu;
   while (it < max_iters) {
     int fb = 0, ffb = 0;
     const double mu_next = mu * (double)rho;
     mu_last = mu;
+    reset_timing(h, stats != nullptr, pending ^ 1);
+    bool read = false;
     {
       Region total(h, CAT_TOTAL, cs);
-      BRSVD_TRY(run_sync<T>(h, X, n, Omegas + (int64_t)it * n * l, Uw, Sw, Vtw, &fb, &ffb));
-      {
-        Region r(h, CAT_ELEM, cs);
-        int nparts = 0;
+      const int st = run_sync_with(h, h->prm.pass_mode == BRSVD_PASSES_FUSED, &fb, &ffb, [&](int method, bool fused) -> int {
+        BRSVD_TRY(enqueue_brsvd<T>(h, X, n, Omegas + (int64_t)it * n * l, Uw, Sw, Vtw, method, fused));
         {
-          Region u(h, CAT_UPD, cs);
-          h->launches[CAT_UPD]++;
-          BRSVD_TRY(rpca_update<T>(M, Uw, Sw, Vtw, m, n, l, (T)mu, (T)lambda, (T)mu_next, Ycur, Yalt, X, part, &nparts,
-                                   cs));
-          std::swap(Ycur, Yalt);                       // Yalt: what this iteration read
+          Region r(h, CAT_ELEM, cs, true);
+          int nparts = 0;
+          {
+            Region u(h, CAT_UPD, cs, true);
+            BRSVD_TRY(rpca_update<T>(M, Uw, Sw, Vtw, m, n, l, (T)mu, (T)lambda, (T)mu_next, Ycur, Yalt, Xalt, part,
+                                     &nparts, cs));
+          }
+          BRSVD_TRY(rpca_residual_sum(part, nparts, scal + 2, cs));
         }
-        BRSVD_TRY(rpca_residual_sum(part, nparts, scal + 2, cs));
-      }
-      BRSVD_HIP_TRY(hipMemcpyAsync(h->host_scal + 2, scal + 2, sizeof(double), hipMemcpyDeviceToHost, cs));
-      BRSVD_HIP_TRY(hipStreamSynchronize(cs));
+        // the previous iteration's events, while this one runs
+        if (!read) { add_timeline(pending, fb_p, ffb_p); read = true; }
+        return BRSVD_OK;
+      });
+      BRSVD_TRY(st);
+      h->tl[h->cur].launches[CAT_UPD]++;
+      std::swap(Ycur, Yalt);                       // Yalt: what this iteration read
+      std::swap(X, Xalt);
     }
+    pending ^= 1;
+    fb_p = fb;
+    ffb_p = ffb;
     const double res = std::sqrt(h->host_scal[2]) / normF;
     if (residuals) residuals[it] = res;
-    flush_stats(fb, ffb);
     ++it;
     if (res < tol) break;       // the stopping rule of Alg. 3: mu is not advanced any more
     mu = mu_next;
   }
+  BRSVD_HIP_TRY(hipStreamSynchronize(cs));           // the end event of the last iteration
+  add_timeline(pending, fb_p, ffb_p);
+  reset_timing(h, stats != nullptr);
   // L and S of the last iteration run: its triplets, its mu and the multiplier it read are still in place
   {
     Region r(h, CAT_ELEM, cs);
     BRSVD_TRY(rpca_finalize<T>(M, Uw, Sw, Vtw, m, n, l, (T)mu_last, (T)lambda, Yalt, L, S, cs));
   }
   BRSVD_HIP_TRY(hipStreamSynchronize(cs));
-  flush_stats(0, 0);
+  add_timeline(0, 0, 0);
   if (iters_done) *iters_done = it;
   if (stats) *stats = acc;
   return BRSVD_OK;
@@ -1008,8 +1053,8 @@ static int create_impl(const brsvd_params* params, brsvd_handle* handle_out) {
   h->own_copy = false;
   h->host_flags = nullptr;
   h->host_scal = nullptr;
-  h->ev_used = 0;
   h->timing = false;
+  h->cur = 0;
   h->own_arena = params->workspace == nullptr;
   for (int i = 0; i < 2; ++i) { h->filled[i] = nullptr; h->drained[i] = nullptr; }
   int status = BRSVD_OK;
@@ -1022,9 +1067,9 @@ static int create_impl(const brsvd_params* params, brsvd_handle* handle_out) {
     if (hipMemset(h->arena + h->lay.gram_part, 0, (size_t)h->lay.gram_chunks * h->Lp * h->Lp * 8) != hipSuccess) {
       status = BRSVD_ERR_HIP; break;
     }
-    if (hipHostMalloc((void**)&h->host_flags, 64, hipHostMallocDefault) != hipSuccess) { status = BRSVD_ERR_ALLOC; break; }
-    if (hipHostMalloc((void**)&h->host_scal, 64, hipHostMallocDefault) != hipSuccess) { status = BRSVD_ERR_ALLOC; break; }
-    std::memset(h->host_flags, 0, 64);
+    if (hipHostMalloc((void**)&h->host_flags, kAlign + 64, hipHostMallocDefault) != hipSuccess) { status = BRSVD_ERR_ALLOC; break; }
+    h->host_scal = (double*)((char*)h->host_flags + kAlign);
+    std::memset(h->host_flags, 0, kAlign + 64);
     if (h->host_a) {
       if (!h->copy) {
         if (hipStreamCreateWithFlags(&h->copy, hipStreamNonBlocking) != hipSuccess) { status = BRSVD_ERR_HIP; break; }
@@ -1037,15 +1082,19 @@ static int create_impl(const brsvd_params* params, brsvd_handle* handle_out) {
       }
       if (!ok) { status = BRSVD_ERR_HIP; break; }
     }
-    // per block and pass at most two products (4 events each) and one copy (2 events)
-    const size_t pool = 64 + (size_t)h->nblocks * 12 * (2 * params->q + 2);
+    // per block and pass at most two products (3 events each) and one copy (2 events)
+    const size_t pool = 64 + (size_t)h->nblocks * 8 * (2 * params->q + 2);
     try {
-      h->ev.resize(pool, nullptr);
-      for (int c = 0; c < CAT_COUNT; ++c) h->regions[c].reserve(pool / 2);   // no growth while a run records
+      h->ev.resize(2 * pool, nullptr);
+      for (auto& t : h->tl)
+        for (int c = 0; c < CAT_COUNT; ++c) t.regions[c].reserve(pool);   // no growth while a run records
     } catch (...) { status = BRSVD_ERR_ALLOC; break; }
     bool ok = true;
-    for (size_t i = 0; i < pool && ok; ++i) ok = hipEventCreate(&h->ev[i]) == hipSuccess;
+    // the events only time kernels of one stream: their records need not write the caches back to the system
+    for (size_t i = 0; i < h->ev.size() && ok; ++i)
+      ok = hipEventCreateWithFlags(&h->ev[i], hipEventDisableSystemFence) == hipSuccess;
     if (!ok) { status = BRSVD_ERR_HIP; break; }
+    reset_timing(h, false);
   } while (0);
   if (status != BRSVD_OK) {
     brsvd_destroy(h);
@@ -1075,7 +1124,6 @@ int brsvd_destroy(brsvd_handle h) {
   }
   if (h->own_copy && h->copy) (void)hipStreamDestroy(h->copy);
   if (h->host_flags) (void)hipHostFree(h->host_flags);
-  if (h->host_scal) (void)hipHostFree(h->host_scal);
   if (h->arena && h->own_arena) (void)hipFree(h->arena);
   delete h;
   return BRSVD_OK;

@@ -31,11 +31,10 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
   } while (0)
 
 // ---- thin-panel GEMMs (gemm_thin.hip) ------------------------------------------------------
-// Optional events for per-kernel timing of one call: start/stop immediately around the MFMA kernel
-// launch(es), sum_start/sum_stop around the split-sum kernels that follow (recorded even when there is
-// nothing to sum).
+// Optional events for per-kernel timing of one call: stop directly behind the MFMA kernel launch(es), sum_stop behind the
+// split-sum kernels that follow (recorded even when there is nothing to sum).  The caller records the start.
 struct KernelEvents {
-  hipEvent_t start, stop, sum_start, sum_stop;
+  hipEvent_t stop, sum_stop;
 };
 
 // Y (rows x ncols, ldy) = A (rows x K, lda) * X (K x Lp padded panel, ldx = Lp).
@@ -208,9 +207,9 @@ int small_svd(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* br
 uint64_t rpca_part_doubles(int64_t m, int64_t n);
 // scal[0] = max |M_ij|, scal[1] = ||M||_F^2 (device doubles).  T = float or double throughout.
 template <typename T> int rpca_norms(const T* M, int64_t count, double* part, double* scal, hipStream_t stream);
-// Y0 = M * inv_J, S0 = 0, X0 = M - S0 + Y0 * inv_mu
+// Y0 = M * inv_J, X0 = M - S0 + Y0 * inv_mu with S0 = 0
 template <typename T>
-int rpca_init(const T* M, int64_t count, T inv_J, T inv_mu, T* Y, T* S, T* X, hipStream_t stream);
+int rpca_init(const T* M, int64_t count, T inv_J, T inv_mu, T* Y, T* X, hipStream_t stream);
 // Fused update after the SVD of X_i: with L = U diag(shrink(sig, 1/mu)) Vt (contraction over l) and
 // S = shrink(M - L + Yin/mu, lambda/mu) formed in registers, writes Yout = Yin + mu (M - L - S), the next SVD input
 // X = M - S + Yout/mu_next and per-workgroup partial sums of ||M-L-S||_F^2 into `part` (*nparts_out of them); L and

@@ -455,7 +455,6 @@ int split_gemm_an(const float* A, int64_t lda, int64_t rows, int64_t K, const fl
   float* part = (float*)scratch;
   const int64_t stride = p.partial_rows * Lp, xstride = (Lp / 16) * 3 * kFragU;
   int* flag;
-  if (ev) BRSVD_HIP_TRY(hipEventRecord(ev->start, stream));
   BRSVD_TRY(split_pack(X, K, ldx, xcols, Lp, pack, &flag, stream));
   for (int gi = 0; gi < p.groups; ++gi) {
     const int c0 = gi * p.nt * 16, nt = std::min(p.nt, (Lp - c0) / 16);
@@ -477,10 +476,7 @@ int split_gemm_an(const float* A, int64_t lda, int64_t rows, int64_t K, const fl
   hipLaunchKernelGGL(k_split_repair<false>, dim3(kSplitSlots), dim3(256), 0, stream, A, lda, rows, K, X, ldx, xcols, Y, ldy,
                      ncols, part, (int64_t)Lp, stride, p.nsplit, rows - p.partial_rows, flag);
   BRSVD_HIP_TRY(hipGetLastError());
-  if (ev) {
-    BRSVD_HIP_TRY(hipEventRecord(ev->stop, stream));
-    BRSVD_HIP_TRY(hipEventRecord(ev->sum_start, stream));
-  }
+  if (ev) BRSVD_HIP_TRY(hipEventRecord(ev->stop, stream));
   if (p.nsplit > 0) {
     const int64_t r0 = rows - p.partial_rows;
     BRSVD_TRY(reduce_splits_f32(part, p.nsplit, stride, p.partial_rows, ncols, Lp, Y + r0 * ldy, ldy, false, stream));
@@ -499,7 +495,6 @@ int split_gemm_at(const float* A, int64_t lda, int64_t rows, int64_t n, const fl
   float* part = (float*)scratch;
   const int64_t stride = n * Lp, xstride = (Lp / 16) * 3 * kFragU;
   int* flag;
-  if (ev) BRSVD_HIP_TRY(hipEventRecord(ev->start, stream));
   BRSVD_TRY(split_pack(Q, rows, ldq, qcols, Lp, pack, &flag, stream));
   for (int gi = 0; gi < p.groups; ++gi) {
     const int c0 = gi * p.nt * 16, nt = std::min(p.nt, (Lp - c0) / 16);
@@ -521,10 +516,7 @@ int split_gemm_at(const float* A, int64_t lda, int64_t rows, int64_t n, const fl
   hipLaunchKernelGGL(k_split_repair<true>, dim3(kSplitSlots), dim3(256), 0, stream, A, lda, n, rows, Q, ldq, qcols, nullptr,
                      (int64_t)0, 0, part, (int64_t)Lp, stride, p.nsplit, (int64_t)0, flag);
   BRSVD_HIP_TRY(hipGetLastError());
-  if (ev) {
-    BRSVD_HIP_TRY(hipEventRecord(ev->stop, stream));
-    BRSVD_HIP_TRY(hipEventRecord(ev->sum_start, stream));
-  }
+  if (ev) BRSVD_HIP_TRY(hipEventRecord(ev->stop, stream));
   BRSVD_TRY(reduce_splits_f32(part, p.nsplit, stride, n, ncols, Lp, Z, ldz, accumulate, stream));
   if (ev) BRSVD_HIP_TRY(hipEventRecord(ev->sum_stop, stream));
   return BRSVD_OK;

@@ -962,7 +962,6 @@ static int gemm_an_t(const T* A, int64_t lda, int64_t rows, int64_t K, const T* 
             "chunks (%d per workgroup), %d chunks per tile, %d workgroups\n", esz * 8, (long)rows, (long)K, Lp,
             p.sh.whole, p.sh.lt, p.sh.f, p.sh.x, p.sh.j, p.sh.C, p.wgs);
   T* part = (T*)scratch;
-  if (ev) BRSVD_HIP_TRY(hipEventRecord(ev->start, stream));
   for (int gi = 0; gi < ng.groups; ++gi) {
     int c0 = gi * ng.nt * 16;
     int nt = (Lp - c0) / 16 < ng.nt ? (Lp - c0) / 16 : ng.nt;
@@ -971,10 +970,7 @@ static int gemm_an_t(const T* A, int64_t lda, int64_t rows, int64_t K, const T* 
     BRSVD_TRY(launch_an<T>(nt, A, lda, (int)rows, (int)K, X + c0, Lp, Y + c0, ldy, nc, part ? part + c0 : nullptr,
                            Lp, prows * Lp, p, stream));
   }
-  if (ev) {
-    BRSVD_HIP_TRY(hipEventRecord(ev->stop, stream));
-    BRSVD_HIP_TRY(hipEventRecord(ev->sum_start, stream));
-  }
+  if (ev) BRSVD_HIP_TRY(hipEventRecord(ev->stop, stream));
   if (p.nsplit > 0) {
     // rows of the leftover tiles: their partial panels, in split order
     const int64_t r0 = rows - prows;
@@ -1122,17 +1118,13 @@ static int gemm_at_t(const T* A, int64_t lda, int64_t rows, int64_t n, const T* 
   if (verbose())
     fprintf(stderr, "[brsvd] gemm_at f%d rows=%ld n=%ld Lp=%d: %d col tiles (%d waves) x %d blocks x %d sub-ranges of %d rows\n",
             esz * 8, (long)rows, (long)n, Lp, p.col_tiles, p.waves, p.nblocks, p.sub, p.rows_per_sub);
-  if (ev) BRSVD_HIP_TRY(hipEventRecord(ev->start, stream));
   for (int gi = 0; gi < ng.groups; ++gi) {
     int c0 = gi * ng.nt * 16;
     int nt = (Lp - c0) / 16 < ng.nt ? (Lp - c0) / 16 : ng.nt;
     if (nt <= 0) break;
     BRSVD_TRY(launch_at<T>(nt, A, lda, rows, (int)n, Q + c0, Lp, part + c0, Lp, n * Lp, block_rows, p, stream));
   }
-  if (ev) {
-    BRSVD_HIP_TRY(hipEventRecord(ev->stop, stream));
-    BRSVD_HIP_TRY(hipEventRecord(ev->sum_start, stream));
-  }
+  if (ev) BRSVD_HIP_TRY(hipEventRecord(ev->stop, stream));
   BRSVD_TRY(reduce_splits<T>(part, p.nsplit, n * Lp, n, Lp, Lp, Z, Lp, accumulate, stream));
   if (ev) BRSVD_HIP_TRY(hipEventRecord(ev->sum_stop, stream));
   return BRSVD_OK;

@@ -78,17 +78,16 @@ k_sum_partials(const double* __restrict__ part, int nblocks, int per, double* __
   if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
-// Multiplier initialisation of Alg. 3: Y0 = M / J, S0 = 0, and the first SVD input
+// Multiplier initialisation of Alg. 3: Y0 = M / J, S0 = 0 (not stored), and the first SVD input
 // X0 = M - S0 + Y0 / mu0.
 template <typename T>
 __global__ void k_rpca_init(const T* __restrict__ M, int64_t count, T inv_J, T inv_mu,
-                            T* __restrict__ Y, T* __restrict__ S, T* __restrict__ X) {
+                            T* __restrict__ Y, T* __restrict__ X) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= count) return;
   const T mv = M[i];
   const T y = mv * inv_J;
   Y[i] = y;
-  S[i] = T(0);
   X[i] = fma(y, inv_mu, mv);
 }
 
@@ -302,9 +301,9 @@ int rpca_norms(const T* M, int64_t count, double* part, double* scal, hipStream_
 }
 
 template <typename T>
-int rpca_init(const T* M, int64_t count, T inv_J, T inv_mu, T* Y, T* S, T* X, hipStream_t stream) {
+int rpca_init(const T* M, int64_t count, T inv_J, T inv_mu, T* Y, T* X, hipStream_t stream) {
   hipLaunchKernelGGL(k_rpca_init<T>, dim3((unsigned)ceil_div(count, 256)), dim3(256), 0, stream, M, count, inv_J,
-                     inv_mu, Y, S, X);
+                     inv_mu, Y, X);
   BRSVD_HIP_TRY(hipGetLastError());
   return BRSVD_OK;
 }
@@ -385,7 +384,7 @@ int scale_rsqrt(T* P, int64_t count, const double* s2, hipStream_t stream) {
 
 #define BRSVD_RPCA_INSTANTIATE(T)                                                                                   \
   template int rpca_norms<T>(const T*, int64_t, double*, double*, hipStream_t);                                     \
-  template int rpca_init<T>(const T*, int64_t, T, T, T*, T*, T*, hipStream_t);                                      \
+  template int rpca_init<T>(const T*, int64_t, T, T, T*, T*, hipStream_t);                                          \
   template int rpca_update<T>(const T*, const T*, const T*, const T*, int64_t, int64_t, int, T, T, T, const T*, T*, \
                               T*, double*, int*, hipStream_t);                                                      \
   template int rpca_finalize<T>(const T*, const T*, const T*, const T*, int64_t, int64_t, int, T, T, const T*, T*,  \
