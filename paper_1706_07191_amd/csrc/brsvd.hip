@@ -303,8 +303,8 @@ struct Streamer {
 // The two products on (a block of) A.  Wide fp32 panels go to the split kernels; their packed right panel lives in the work
 // area of the TSQR route (8 bytes per panel element, of which 6 are used), which is only in use inside an orthonormalisation.
 template <typename T>
-bool uses_split(brsvd_handle h, int64_t out, int64_t K, int64_t lda) {
-  return sizeof(T) == 4 && split_fits(out, K, h->Lp, lda, h->lay.tsqr_bytes);
+bool uses_split(brsvd_handle h, bool at, const T* A, int64_t out, int64_t K, int64_t lda) {
+  return split_fits(at, A, out, K, h->Lp, lda, h->lay.tsqr_bytes);
 }
 
 template <typename T>
@@ -312,7 +312,7 @@ int product_an(brsvd_handle h, const T* A, int64_t lda, int64_t rows, const T* X
   const int Lp = h->Lp;
   void* scr = h->arena + h->lay.gemm_scratch;
   if constexpr (sizeof(T) == 4) {
-    if (uses_split<T>(h, rows, h->prm.n, lda))
+    if (uses_split<T>(h, false, A, rows, h->prm.n, lda))
       return split_gemm_an(A, lda, rows, h->prm.n, X, Lp, Lp, Lp, Y, Lp, Lp, scr, h->lay.gemm_scratch_bytes,
                            h->arena + h->lay.tsqr, h->lay.tsqr_bytes, h->compute, ke);
   }
@@ -325,7 +325,7 @@ int product_at(brsvd_handle h, const T* A, int64_t lda, int64_t rows, const T* Q
   const int Lp = h->Lp;
   void* scr = h->arena + h->lay.gemm_scratch;
   if constexpr (sizeof(T) == 4) {
-    if (uses_split<T>(h, h->prm.n, rows, lda))
+    if (uses_split<T>(h, true, A, h->prm.n, rows, lda))
       return split_gemm_at(A, lda, rows, h->prm.n, Q, Lp, Lp, Lp, Z, Lp, Lp, accumulate, scr, h->lay.gemm_scratch_bytes,
                            h->arena + h->lay.tsqr, h->lay.tsqr_bytes, h->compute, ke);
   }
@@ -926,7 +926,7 @@ int step_gemm_an(const T* A, int64_t lda, int64_t rows, int64_t n, const T* X, i
   char* part = (char*)scratch + 2 * panel;
   hipStream_t s = (hipStream_t)stream;
   if constexpr (sizeof(T) == 4) {      // the packed right panel takes the place of the two padded panels
-    if (split_fits(rows, n, Lp, lda, 2 * panel))
+    if (split_fits(false, A, rows, n, Lp, lda, 2 * panel))
       return split_gemm_an(A, lda, rows, n, X, l, l, Lp, Y, l, l, part, scratch_bytes - 2 * panel, scratch, 2 * panel, s);
   }
   BRSVD_TRY(pad_panel(X, n, l, Xp, Lp, s));
@@ -945,7 +945,7 @@ int step_gemm_at(const T* A, int64_t lda, int64_t rows, int64_t n, const T* Q, i
   char* part = (char*)scratch + 2 * panel;
   hipStream_t s = (hipStream_t)stream;
   if constexpr (sizeof(T) == 4) {
-    if (split_fits(n, rows, Lp, lda, 2 * panel))
+    if (split_fits(true, A, n, rows, Lp, lda, 2 * panel))
       return split_gemm_at(A, lda, rows, n, Q, l, l, Lp, Z, l, l, accumulate != 0, part, scratch_bytes - 2 * panel, scratch,
                            2 * panel, s);
   }

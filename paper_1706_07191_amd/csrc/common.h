@@ -104,12 +104,15 @@ int reduce_splits_f32(float* part, int nsplit, int64_t split_stride, int64_t row
 
 // ---- the same two products for wide fp32 panels on the bf16 matrix cores (gemm_split.hip) ----
 // out x K (an) or K x out (at) is the part of A multiplied; pack is device memory for the split right panel.
-// Taken for contractions of at least 512, 48 padded columns and 2^22 elements of A.  Measured, plain fp32 kernel and this one
-// (us, A X / A^T Q): 100000x50000 l=272 20944 / 21274 and 12640 / 13114; 20000x20000 l=110 877 / 791 and 514 / 514; 89083x2783
-// l=97 583 / 748 and 336 / 343; 76800x2000 l=40 189 / 197 and 165 / 148; 4000x4000 l=48 36.8 / 30.9 and 31.9 / 25.6; below the
-// bound the extra launches cost what the product saves: 2000x1000 l=60 21.2 / 23.6 and 24.2 / 18.0, 1024x1024 l=300
-// 79 / 35.6 and 73 / 36.8.
-constexpr int64_t kSplitMinK = 512, kSplitMinOut = 64, kSplitMinLp = 48, kSplitMinA = 1 << 22;
+// Taken for contractions of at least 512 and 2^22 elements of A, from 48 padded columns on, and at 32 for rows of at least 8000 or
+// (Z = A^T Q) rows that do not start on 16-byte boundaries.  Measured, plain fp32 kernel and this one (us, A X / A^T Q):
+// 100000x50000 l=272 20944 / 21274 and 12640 / 13114; 20000x20000 l=110 877 / 791 and 514 / 514; 89083x2783 l=97 583 / 748 and
+// 336 / 343; 76800x2000 l=40 189 / 197 and 165 / 148; 4000x4000 l=48 36.8 / 30.9 and 31.9 / 25.6; 60000x20000 l=24 1035 / 834 and
+// 879 / 789; 8000x8000 l=30 54.7 / 57.9 and 51.4 / 50.5; 32256x2383 l=20 77.3 / 111.5 and 85.5 / 73.1.  Below, the extra launches
+// cost what the product saves, or the read of A bounds both: 2000x1000 l=60 21.2 / 23.6 and 24.2 / 18.0, 1024x1024 l=300 79 /
+// 35.6 and 73 / 36.8, 100000x50000 l=16 3287 / 3266 and 3911 / 3373, 76800x2000 l=20 (inside the robust-PCA loop) 129 / 115
+// and 139 / 126.
+constexpr int64_t kSplitMinK = 512, kSplitMinOut = 64, kSplitMinLp = 32, kSplitMinA = 1 << 22, kSplitLongRow = 8000;
 struct SplitPlan {
   int tile, groups, nt, nsplit, wgs;           // rows (columns of A) per workgroup, column groups, tiles per group, partial panels
   AnShape sh;                                  // an
@@ -118,7 +121,7 @@ struct SplitPlan {
 };
 SplitPlan split_an_plan(int64_t rows, int64_t K, int Lp, uint64_t scratch_bytes);
 SplitPlan split_at_plan(int64_t rows, int64_t n, int Lp, uint64_t scratch_bytes);
-bool split_fits(int64_t out, int64_t K, int Lp, int64_t lda, uint64_t pack_bytes);
+bool split_fits(bool at, const float* A, int64_t out, int64_t K, int Lp, int64_t lda, uint64_t pack_bytes);
 // X (K x xcols, leading dimension ldx) and Q (rows x qcols, ldq) need no padding; Lp = padded width of the partial panels.
 int split_gemm_an(const float* A, int64_t lda, int64_t rows, int64_t K, const float* X, int64_t ldx, int xcols, int Lp,
                   float* Y, int64_t ldy, int ncols, void* scratch, uint64_t scratch_bytes, void* pack,

@@ -1,4 +1,4 @@
-// The two thin products of gemm_thin.hip for wide fp32 panels (more than 32 columns) on the bf16 matrix cores, with
+// The two thin products of gemm_thin.hip for wide fp32 panels (more than 16 columns) on the bf16 matrix cores, with
 // every fp32 operand split exactly into three bf16 numbers:
 //
 //   a = h + m + l,   h = the upper 16 bits of a (8 significant bits), m = bf16(a - h), l = a - h - m
@@ -374,10 +374,12 @@ constexpr int kSplitSlots = 256;                        // one workgroup of eigh
 static int64_t split_chunks(int64_t K) { return ceil_div(K, 2 * kSplitB); }
 static uint64_t pack_panel_bytes(int64_t K, int Lp) { return (uint64_t)split_chunks(K) * 2 * (Lp / 16) * 3 * kFragU * 16; }
 
-bool split_fits(int64_t out, int64_t K, int Lp, int64_t lda, uint64_t pack_bytes) {
+bool split_fits(bool at, const float* A, int64_t out, int64_t K, int Lp, int64_t lda, uint64_t pack_bytes) {
   // byte offsets of a lane's loads: at most 255 rows and a row length, in 32 bits
   if (K < kSplitMinK || out < kSplitMinOut || Lp < kSplitMinLp || out * K < kSplitMinA || lda > (1 << 21)) return false;
   if (out > INT32_MAX || K > INT32_MAX) return false;
+  const bool aligned = lda % 4 == 0 && (uintptr_t)A % 16 == 0;
+  if (Lp < 48 && (at ? out : K) < kSplitLongRow && (!at || aligned)) return false;
   return pack_bytes >= pack_panel_bytes(K, Lp) + 64;
 }
 
@@ -421,7 +423,7 @@ SplitPlan split_at_plan(int64_t rows, int64_t n, int Lp, uint64_t scratch_bytes)
 #define BRSVD_SPLIT_SWITCH(nt, tile, CALL)                                                                       \
   if (nt == 10 && tile == 4 * kSplitMT * 16) { CALL(10, 4, 2); } else                                            \
   switch (nt) {                                                                                                  \
-    case 3: CALL(3, 8, 1); break; case 4: CALL(4, 8, 1); break; case 5: CALL(5, 8, 1); break;                    \
+    case 2: CALL(2, 8, 1); break; case 3: CALL(3, 8, 1); break; case 4: CALL(4, 8, 1); break; case 5: CALL(5, 8, 1); break;                    \
     case 6: CALL(6, 8, 1); break; case 7: CALL(7, 8, 1); break; case 8: CALL(8, 8, 1); break;                    \
     case 9: CALL(9, 8, 1); break; case 10: CALL(10, 8, 1); break; case 11: CALL(11, 4, 2); break;                \
     case 12: CALL(12, 4, 2); break; case 13: CALL(13, 4, 2); break; case 14: CALL(14, 4, 2); break;              \
@@ -450,7 +452,7 @@ static int split_pack(const float* X, int64_t K, int64_t ldx, int xcols, int Lp,
 int split_gemm_an(const float* A, int64_t lda, int64_t rows, int64_t K, const float* X, int64_t ldx, int xcols, int Lp,
                   float* Y, int64_t ldy, int ncols, void* scratch, uint64_t scratch_bytes, void* pack,
                   uint64_t pack_bytes, hipStream_t stream, const KernelEvents* ev) {
-  if (!split_fits(rows, K, Lp, lda, pack_bytes) || ncols > Lp) return BRSVD_ERR_ARG;
+  if (!split_fits(false, A, rows, K, Lp, lda, pack_bytes) || ncols > Lp) return BRSVD_ERR_ARG;
   const SplitPlan p = split_an_plan(rows, K, Lp, scratch_bytes);
   float* part = (float*)scratch;
   const int64_t stride = p.partial_rows * Lp, xstride = (Lp / 16) * 3 * kFragU;
@@ -488,7 +490,7 @@ int split_gemm_an(const float* A, int64_t lda, int64_t rows, int64_t K, const fl
 int split_gemm_at(const float* A, int64_t lda, int64_t rows, int64_t n, const float* Q, int64_t ldq, int qcols, int Lp,
                   float* Z, int64_t ldz, int ncols, bool accumulate, void* scratch, uint64_t scratch_bytes, void* pack,
                   uint64_t pack_bytes, hipStream_t stream, const KernelEvents* ev) {
-  if (!split_fits(n, rows, Lp, lda, pack_bytes) || ncols > Lp) return BRSVD_ERR_ARG;
+  if (!split_fits(true, A, n, rows, Lp, lda, pack_bytes) || ncols > Lp) return BRSVD_ERR_ARG;
   const SplitPlan p = split_at_plan(rows, n, Lp, scratch_bytes);
   if (p.nsplit < 1) return BRSVD_ERR_BUDGET;
   if (p.nsplit > 65535) return BRSVD_ERR_ARG;

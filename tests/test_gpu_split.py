@@ -11,7 +11,9 @@ from tests.gpu_util import EPS32, need_gpu
 pytestmark = pytest.mark.gpu
 
 SHAPES = [  # rows, n, l, elements between A's rows beyond n, offset of A's base in elements
-    (8200, 512, 33, 0, 0),       # shortest contraction, narrowest panel of A X; 32 columns + 1
+    (8200, 512, 33, 0, 0),       # shortest contraction of A X, 32 columns + 1
+    (530, 8001, 17, 0, 0),       # narrowest panel: both products from rows of 8000 on
+    (5003, 1001, 32, 0, 0),      # narrowest panel, short rows: A^T Q only
     (513, 8200, 48, 0, 0),       # shortest contraction of A^T Q, not a multiple of its blocks
     (4097, 1031, 97, 0, 0),      # odd row length, one row more than whole tiles
     (2049, 2050, 160, 6, 1),     # ten column tiles (one column of waves), padded rows, odd base
