@@ -5,17 +5,14 @@
 // The rows of a working copy W of R are rotated in pairs (round-robin schedule) until they are
 // mutually orthogonal: then W = diag(s) Vr^T, so s_i is the norm of row i and Vr's column i the
 // normalised row i; Ur = R Vr diag(1/s) follows from one small product.  Everything is fp64.
-//   l <= kJacobiLdsMaxL : one workgroup of 1024 threads, W resident in LDS for all sweeps.
-//   larger l            : block Jacobi, one launch per round of block pairs, W in L2, block pairs in LDS.
 #include <cstdlib>
 
 #include "common.h"
 
 namespace brsvd {
 
-constexpr int kSvdThreads = 1024;
 constexpr int kMaxSweeps = 40;
-constexpr int kJacobiLdsMaxL = 128;
+constexpr int kJacobiRowsMaxL = 128;   // largest l whose rows fit the LDS of one CU for row rotations
 
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
@@ -49,19 +46,22 @@ __device__ __forceinline__ double rcp_nr(double x) {
   return y;
 }
 
-// Rotation (c, s) that makes two rows with squared norms al, be and inner product ga orthogonal:
-// with zeta = (be - al) / (2 ga), t = sign(zeta) / (|zeta| + sqrt(1 + zeta^2)), c = 1/sqrt(1+t^2),
-// s = c t, written so that it needs one reciprocal and two reciprocal square roots.
-// Returns false (identity) when |ga| <= tol * sqrt(al * be).
 // Sweeps end when a whole sweep met no pair with |cos| above kSettled: all cosines are then of the order
 // l * kSettled^2 after that sweep's rotations (quadratic convergence), below the rotation threshold, so
 // a further sweep that would only confirm it is not run.
 // With results delivered in single precision the bar is lower: a last sweep whose largest cosine was below
 // kSettledF32 leaves cosines of the order l * kSettledF32^2 = 1e-8, an order of magnitude below what the fp32
 // lifts U = Q V_R and V = W_B U_R can show, and that saves one sweep of the seven to eight an l of 100 to 300 takes.
+// Row rotations skip pairs whose cosine is below kTolRows (a skipped rotation saves its traffic); on the 32 x 32 Gram matrix a
+// rotation costs the same whether it turns or not, so everything above rounding is rotated.
+constexpr double kTolRows = 1e-13, kTolBlocks = 1e-16;
 constexpr double kSettled = 1e-8;
 constexpr double kSettledF32 = 1e-5;
-__device__ __forceinline__ bool rotation(double al, double be, double ga, double tol2, double settled2, double& c,
+// Rotation (c, s) that makes two rows with squared norms al, be and inner product ga orthogonal:
+// with zeta = (be - al) / (2 ga), t = sign(zeta) / (|zeta| + sqrt(1 + zeta^2)), c = 1/sqrt(1+t^2),
+// s = c t, written so that it needs one reciprocal and two reciprocal square roots.
+// Returns false (identity) when |ga| <= tol * sqrt(al * be); big: above the settled bar.
+__device__ __forceinline__ bool rotation_exact(double al, double be, double ga, double tol2, double settled2, double& c,
                                          double& s, bool& big) {
   c = 1.0; s = 0.0;
   big = ga * ga > settled2 * al * be;
@@ -75,7 +75,7 @@ __device__ __forceinline__ bool rotation(double al, double be, double ga, double
   return true;
 }
 
-// Sum over the 16 lanes of a DPP row, result in every lane of the row.
+// A value from another lane of the row of 16 (CTRL: the lane pattern).
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v) {
   int lo = __double2loint(v), hi = __double2hiint(v);
@@ -83,6 +83,7 @@ __device__ __forceinline__ double dpp_f64(double v) {
   hi = __builtin_amdgcn_update_dpp(0, hi, CTRL, 0xf, 0xf, true);
   return __hiloint2double(hi, lo);
 }
+// Sum over the 16 lanes of a DPP row, result in every lane of the row.
 __device__ __forceinline__ double row16_sum(double v) {
   v += dpp_f64<0x128>(v);   // row_ror:8
   v += dpp_f64<0x124>(v);   // row_ror:4
@@ -124,17 +125,6 @@ __device__ void publish(const double* W, int ld, int l, int Lp, double* Wg, doub
     }
 }
 
-// Sum over the 64 lanes of a wave, result in every lane: the four row sums are read as scalars and added.
-__device__ __forceinline__ double lane_value(double v, int src) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(v), src);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src);
-  return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double wave64_sum(double v) {
-  v = row16_sum(v);
-  return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
-}
-
 // Sum over groups of 8 lanes (half a DPP row), result in every lane of the group.
 __device__ __forceinline__ double row8_sum(double v) {
   v += dpp_f64<0xB1>(v);    // quad_perm [1,0,3,2]
@@ -143,7 +133,8 @@ __device__ __forceinline__ double row8_sum(double v) {
   return v;
 }
 
-// LDS-resident Jacobi: each group of LPP lanes (16) owns one row pair per step, so a wave handles
+// ---- 33 to 128 rows: row rotations in LDS -------------------------------------------------------------------------
+// Each group of LPP lanes (16) owns one row pair per step, so a wave handles
 // 64/LPP pairs with one instruction stream and up to 64 pairs (l <= 128) take 1024 threads.
 // EPL = elements of a row per lane = ceil(l / LPP).
 // Pair schedule of a sweep (every pair of rows met exactly once): the index range is halved
@@ -156,7 +147,7 @@ constexpr int kJLev = 7;      // levels for l <= 128
 
 template <int EPL, int LPP>
 __global__ void __launch_bounds__(64 * LPP)
-k_jacobi_lds(const double* __restrict__ R, int ldr, int l, int Lp, double* __restrict__ Wg,
+k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __restrict__ Wg,
              double* __restrict__ sig, int* __restrict__ info, const int* __restrict__ breakdown_flag,
              double tol, double settled) {
   extern __shared__ double W[];
@@ -244,7 +235,7 @@ k_jacobi_lds(const double* __restrict__ R, int ldr, int l, int Lp, double* __res
         else { al = row8_sum(al); be = row8_sum(be); ga = row8_sum(ga); }
         double c, s;
         bool big;
-        const bool rot = rotation(al, be, ga, tol2, settled2, c, s, big) && valid;
+        const bool rot = rotation_exact(al, be, ga, tol2, settled2, c, s, big) && valid;
         any |= big && valid;
         if (rot) {
           double* wbw = W + (bb + j) * ld;
@@ -277,143 +268,341 @@ k_jacobi_lds(const double* __restrict__ R, int ldr, int l, int Lp, double* __res
   if (tid == 0) { info[0] = sweeps; info[1] = converged; }
 }
 
-// ---- large l: block Jacobi, rows in global memory (L2), blocks of kJB rows ---------------------
-// The rows are cut into blocks of kJB = 16.  One sweep = one "diagonal" launch, in which every
-// workgroup orthogonalises the pairs inside two blocks (round robin within a block), followed by a
-// round robin over block pairs, one launch per round: workgroup p loads blocks (I, J) into LDS and
-// rotates all kJB x kJB cross pairs in kJB steps (step s pairs row i of I with row (i + s) mod kJB of
-// J; the row of I stays in registers, the rows of J travel through LDS), then writes both blocks
-// back.  Every pair of rows is met exactly once per sweep; launches replace grid-wide barriers.
+// ---- Jacobi by blocks of rows -------------------------------------------------------------------------------------
+// The rows are cut into blocks of kJB = 16 and pairs of blocks are orthogonalised at a time: the Gram matrix of the 32
+// rows (fp64 matrix cores), one sweep of rotations on that 32 x 32 matrix alone, accumulated in an orthogonal J, and
+// the rows replaced by J^T times the rows (matrix cores again).  A rotation then touches 32 numbers of the Gram
+// matrix and of J instead of two whole rows, and needs no inner products: its step is a read of four matrix entries
+// per thread, the rotation, and a write.  The Gram matrix is formed afresh from the rows for every pair of blocks, so
+// what the two-sided updates lose never accumulates; singular values keep the relative accuracy of plain row rotations
+// (simulated at condition 1e6, 1e10, 1e14: 8e-15, 9e-15, 8e-13, plain rotations 9e-15, 1.3e-14, 8e-13).
+// A sweep is a round robin over the block pairs.  Its first round rotates all 496 pairs of the 32 rows (31 steps of
+// 16 disjoint pairs), the others the 256 pairs across the two blocks (16 steps).
+//   l <= 32: one block pair, rows in LDS for all sweeps (k_jacobi_small);
+//   l > kJacobiRowsMaxL = 128: one launch per round, one workgroup per block pair, rows in L2 (k_jacobi_pair);
+//   in between two to four block pairs share one CU, or seven launches make a sweep, and row rotations stay ahead (l = 33 382
+//   against 243 us, 60 440 / 413, 96 891 / 823, 110 1273 / 1062; 128 1290 / 1452).
+// What bounds it: the latency of a step, 800 to 900 cycles from barrier to barrier, half of it the rotation; the matrix products
+// take 5 to 9 thousand cycles of a round's 14 + 10 thousand (l = 160, 272).  Measured (us per call of the small SVD, row
+// rotations before and this): l = 20 143 -> 134, 30 181 -> 151, 160 2867 -> 1980, 272 6140 -> 4280, 512 13900 -> 9850.  Two
+// accumulator chains per product: four gain 2 % at l <= 32 and lose 6 % above 128.
 constexpr int kJB = 16;
+constexpr int kJN = 2 * kJB;                      // rows of a block pair
+// Place of entry (x, y) of the Gram matrix and of J: odd rows have their halves exchanged, so that the two rows of 16
+// consecutive columns that half a wave touches, and 16 consecutive diagonal entries, lie on distinct banks.
+__device__ __forceinline__ int jat(int x, int y) { return x * kJN + (y ^ ((x & 1) << 4)); }
+constexpr int kJThreads = 256;                    // threads per block pair: (i, j) = pairs of rows
+constexpr int kJWork = 3 * kJN * kJN + 128;       // doubles of LDS per block pair: two Gram buffers, J, rotations
 
-__global__ void k_jacobi_init(const double* __restrict__ R, int ldr, int l, int Lp, double* __restrict__ W) {
-  int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= l * l) return;
-  int i = idx / l, c = idx - i * l;
-  W[(int64_t)i * Lp + c] = R[(int64_t)i * ldr + c];
+__device__ __forceinline__ doublex4 mfma_f64(double a, double b, doublex4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// outer < 0: diagonal launch (workgroup p owns blocks 2p and 2p+1); otherwise round `outer` of the
-// round robin over nblk2 (even) blocks.  1024 threads = 16 row pairs, one wave per pair (a wave of 64 lanes per
-// pair keeps four waves on every SIMD of the CU, which hides the LDS and cross-lane latencies that a quarter wave per
-// pair left exposed: 5.3 -> about 1 us per step at l = 272); EPL = ceil(l / 64).
-constexpr int kJBLanes = 64;
-constexpr int kJBThreads = kJB * kJBLanes;
-template <int EPL>
-__global__ void __launch_bounds__(kJBThreads)
-k_jacobi_block(double* __restrict__ W, int l, int Lp, int nblk2, int outer, double tol, double settled,
-               int* __restrict__ rotated) {
-  extern __shared__ double sh[];               // 2 * kJB rows of l doubles: block I, then block J
-  const int tid = threadIdx.x, pi = tid / kJBLanes, rl = tid % kJBLanes;
-  int I, J;
-  if (outer < 0) { I = 2 * blockIdx.x; J = I + 1; }
-  else rr_pair(blockIdx.x, outer, nblk2, I, J);
-  const int rI = I * kJB, rJ = J * kJB;
-  if (rI >= l) return;                                  // uniform over the workgroup
-  const int nI = min(kJB, l - rI), nJ = max(0, min(kJB, l - rJ));
-  if (outer >= 0 && nJ == 0) return;                    // the padding block of an odd block count
-  for (int idx = tid; idx < 2 * kJB * l; idx += kJBThreads) {
-    const int rr = idx / l, c = idx - rr * l;
-    const bool live = rr < kJB ? rr < nI : rr - kJB < nJ;
-    const int grow = rr < kJB ? rI + rr : rJ + rr - kJB;
-    sh[idx] = live ? W[(int64_t)grow * Lp + c] : 0.0;
+// Rotation (c, s) that makes two rows with squared norms al, be and inner product ga orthogonal: tan of the smaller
+// angle, t = 2 ga / (tau +- sqrt(tau^2 + 4 ga^2)), tau = be - al.  t itself is worked out in single precision: that only
+// leaves 1e-7 of the inner product, while c and s, which have to be orthogonal, follow from it in double.
+// Identity when |ga| <= tol * sqrt(al * be); big: above the settled bar.  Returns t.
+__device__ __forceinline__ double rotation(double al, double be, double ga, double tol2, double settled2, double& c,
+                                           double& s, bool& big) {
+  const double gg = ga * ga, ab = al * be;
+  big = gg > settled2 * ab;
+  const bool rot = gg > tol2 * ab;
+  const double tau = be - al, g2 = 2.0 * ga;
+  const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(tau), fabs(g2)));
+  const float tf = (float)__builtin_amdgcn_ldexp(tau, ex), gf = (float)__builtin_amdgcn_ldexp(g2, ex);
+  const float den = fabsf(tf) + __builtin_amdgcn_sqrtf(fmaf(tf, tf, gf * gf));
+  const float t32 = copysignf(gf, gf * tf >= 0.f ? 1.f : -1.f) * __builtin_amdgcn_rcpf(den);
+  // c = 1 / sqrt(1 + t^2) from a single-precision seed by one step of third order (2^-22 -> below 2^-64)
+  const float ts = rot ? t32 : 0.f;
+  const double t = (double)ts, x = fma(t, t, 1.0), y = (double)__builtin_amdgcn_rsqf(fmaf(ts, ts, 1.f));
+  const double e = fma(-x * y, y, 1.0);
+  c = fma(y, e * fma(e, 0.375, 0.5), y);
+  s = c * t;
+  return t;
+}
+
+// Value of the next lane, cyclically among each H lanes.
+template <int H>
+__device__ __forceinline__ double next_lane(double v, int lane) {
+  if constexpr (H == 16) return dpp_f64<0x12F>(v);           // row_ror:15
+  else if constexpr (H == 8) {
+    const double up = dpp_f64<0x101>(v), back = dpp_f64<0x117>(v);     // row_shl:1, row_shr:7
+    return (lane & 7) == 7 ? back : up;
   }
-  __syncthreads();
-  const double tol2 = tol * tol, settled2 = settled * settled;
-  bool any = false;
-  if (outer < 0) {
-    const int blk = pi >> 3, q = pi & 7, nrows = blk == 0 ? nI : nJ;
-    for (int step = 0; step < kJB - 1; ++step) {
-      int a, b;
-      rr_pair(q, step, kJB, a, b);
-      const bool valid = b < nrows;                     // a < b
-      double* wa = sh + (blk * kJB + a) * l;
-      double* wb = sh + (blk * kJB + b) * l;
-      double x[EPL], y[EPL], al = 0.0, be = 0.0, ga = 0.0;
+  else if constexpr (H == 4) return dpp_f64<0x39>(v);        // quad_perm [1,2,3,0]
+  else if constexpr (H == 2) return dpp_f64<0xB1>(v);        // quad_perm [1,0,3,2]
+  else return v;
+}
+
+// The four waves of a block pair form the Gram matrix of its rows in G; row(x) is the LDS address of row x, cols (a multiple of
+// 16) its length.
+template <typename Row>
+__device__ __forceinline__ void gram_32(Row row, int cols, double* G, int t) {
+  const int lane = t & 63, w = t >> 6, r = lane & 15, g = lane >> 4;
+  if (w == 3) return;                                    // three tiles: the matrix is symmetric
+  const double *lo = row((w == 2 ? kJB : 0) + r), *hi = row((w == 0 ? 0 : kJB) + r);
+  doublex4 acc[2];
+  acc[0] = acc[1] = doublex4{0.0, 0.0, 0.0, 0.0};
+  // the operands of the next 16 columns are read while the products of these 16 run
+  double x[4], y[4];
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) {
-        const int col = rl + kJBLanes * e;
-        const bool in = valid && col < l;
-        x[e] = in ? wa[col] : 0.0;
-        y[e] = in ? wb[col] : 0.0;
-        al = fma(x[e], x[e], al); be = fma(y[e], y[e], be); ga = fma(x[e], y[e], ga);
-      }
-      al = wave64_sum(al); be = wave64_sum(be); ga = wave64_sum(ga);
-      double c, s;
-      bool big;
-      const bool rot = rotation(al, be, ga, tol2, settled2, c, s, big) && valid;
-      any |= big && valid;
-      if (rot) {
+  for (int q = 0; q < 4; ++q) { x[q] = lo[4 * q + g]; y[q] = hi[4 * q + g]; }
+  for (int k = 0; k < cols; k += 16) {
+    const int kn = k + 16 < cols ? k + 16 : k;
+    double xn[4], yn[4];
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) {
-          const int col = rl + kJBLanes * e;
-          if (col < l) { wa[col] = c * x[e] - s * y[e]; wb[col] = s * x[e] + c * y[e]; }
-        }
-      }
-      __syncthreads();
-    }
+    for (int q = 0; q < 4; ++q) { xn[q] = lo[kn + 4 * q + g]; yn[q] = hi[kn + 4 * q + g]; }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[q & 1] = mfma_f64(x[q], y[q], acc[q & 1]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) { x[q] = xn[q]; y[q] = yn[q]; }
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int x = (w == 2 ? kJB : 0) + g + 4 * v, y = (w == 0 ? 0 : kJB) + r;
+    const double s = acc[0][v] + acc[1][v];
+    G[jat(x, y)] = s;
+    if (w == 1) G[jat(y, x)] = s;
+  }
+}
+
+// The 32 rows in groups of 2 H: rotates all pairs of a row of the first half of a group with a row of its second half, in H steps
+// (row x of the one with row (x + step) mod H of the other), on the Gram matrix in buffer 0 of work, and updates J (fresh: J is
+// the identity so far).  Everything but the rotations lives in registers: thread (i, j) holds the 2 x 2 block of the pairs
+// i and j and two rows of J.  From one step to the next the rows of the second halves move up by one pair, i.e. columns come
+// from the next lane and rows through LDS from the thread of the next pair.  The thread (i, i) works out the next rotation of
+// pair i as soon as it has the new inner product: the squared norms follow from those before, al - t ga and be + t ga, so
+// a step is one read, four multiply-adds, the rotation and one write between two barriers.  store: the Gram matrix is left in
+// buffer 0.  Every thread of the workgroup calls it; the caller's barriers separate it from what is around it.
+// Returns whether a rotation was above the settled bar.
+template <int H>
+__device__ __forceinline__ bool cross_pairs(double* work, int t, bool fresh, bool store, double tol2, double settled2) {
+  const int i = t >> 4, j = t & 15, up = (i & ~(H - 1)) | ((i + 1) & (H - 1));
+  auto top = [](int k) { return (k & ~(H - 1)) + k; };       // 2 H (k / H) + k mod H; the partner at step 0 is H rows below
+  double* G = work;
+  double2* T = (double2*)(work + kJN * kJN);                 // two buffers of 256
+  double* J = work + 2 * kJN * kJN;
+  double* S = J + kJN * kJN;                                 // two buffers of 16 x {c, s, be, unused}
+  const int e0 = jat(top(i), top(j)), e1 = jat(top(i), top(j) + H);
+  const int e2 = jat(top(i) + H, top(j)), e3 = jat(top(i) + H, top(j) + H);
+  const int f0 = jat(i, top(j)), f1 = jat(i, top(j) + H), h0 = f0 + kJB * kJN, h1 = f1 + kJB * kJN;   // rows i, 16 + i
+  double a = G[e0], b = G[e1], bt = G[e2], cc = G[e3];
+  double p0, p1, q0, q1;
+  if (fresh) {
+    p0 = top(j) == i; p1 = top(j) + H == i; q0 = top(j) == kJB + i; q1 = top(j) + H == kJB + i;
   } else {
-    double x[EPL];
-    double* wa = sh + pi * l;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-      const int col = rl + kJBLanes * e;
-      x[e] = (pi < nI && col < l) ? wa[col] : 0.0;
+    p0 = J[f0]; p1 = J[f1]; q0 = J[h0]; q1 = J[h1];
+  }
+  const bool diag = i == j;
+  bool any = false;
+  double al = a;
+  auto next_rotation = [&](double be, double ga, double* Sn) {
+    double c, s;
+    bool big;
+    const double tg = rotation(al, be, ga, tol2, settled2, c, s, big) * ga;
+    any |= big && diag;
+    al -= tg;
+    if (diag) {
+      *(double2*)(Sn + 4 * i) = double2{c, s};
+      Sn[4 * i + 2] = be + tg;
     }
-    for (int step = 0; step < kJB; ++step) {
-      const int j = (pi + step) & (kJB - 1);
-      const bool valid = pi < nI && j < nJ;
-      double* wb = sh + (kJB + j) * l;
-      double y[EPL], al = 0.0, be = 0.0, ga = 0.0;
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) {
-        const int col = rl + kJBLanes * e;
-        y[e] = (valid && col < l) ? wb[col] : 0.0;
-        al = fma(x[e], x[e], al); be = fma(y[e], y[e], be); ga = fma(x[e], y[e], ga);
-      }
-      al = wave64_sum(al); be = wave64_sum(be); ga = wave64_sum(ga);
-      double c, s;
-      bool big;
-      const bool rot = rotation(al, be, ga, tol2, settled2, c, s, big) && valid;
-      any |= big && valid;
-      if (rot) {
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) {
-          const int col = rl + kJBLanes * e;
-          const double xn = c * x[e] - s * y[e];
-          if (col < l) wb[col] = s * x[e] + c * y[e];
-          x[e] = xn;
-        }
-      }
-      __syncthreads();
+  };
+  next_rotation(cc, b, S);
+  __syncthreads();
+#pragma unroll 1
+  for (int step = 0; step < H; ++step) {
+    const double* Sc = S + (step & 1) * 64;
+    const double2 rj = *(const double2*)(Sc + 4 * j), ri = *(const double2*)(Sc + 4 * i);
+    const double be = Sc[4 * up + 2];
+    if (step > 0) {
+      const double2 v = T[(step & 1) * 256 + 16 * up + j];
+      bt = v.x;
+      cc = v.y;
     }
-    if (pi < nI) {
+    const double x0 = rj.x * a - rj.y * b, x1 = rj.y * a + rj.x * b;
+    const double y0 = rj.x * bt - rj.y * cc, y1 = rj.y * bt + rj.x * cc;
+    b = next_lane<H>(ri.x * x1 - ri.y * y1, j);
+    if (step + 1 < H) next_rotation(be, b, S + ((step & 1) ^ 1) * 64);
+    a = ri.x * x0 - ri.y * y0;
+    T[((step & 1) ^ 1) * 256 + t] = double2{ri.y * x0 + ri.x * y0, next_lane<H>(ri.y * x1 + ri.x * y1, j)};
+    const double u = rj.y * p0 + rj.x * p1, v = rj.y * q0 + rj.x * q1;
+    p0 = rj.x * p0 - rj.y * p1;
+    q0 = rj.x * q0 - rj.y * q1;
+    p1 = next_lane<H>(u, j);
+    q1 = next_lane<H>(v, j);
+    __syncthreads();
+  }
+  // H moves have brought every row and column home
+  J[f0] = p0;
+  J[f1] = p1;
+  J[h0] = q0;
+  J[h1] = q1;
+  if (store) {
+    const double2 v = T[(H & 1) * 256 + 16 * up + j];
+    G[e0] = a;
+    G[e1] = b;
+    G[e2] = v.x;
+    G[e3] = v.y;
+  }
+  return any;
+}
+
+// One sweep of rotations on the Gram matrix in buffer 0 of work: all pairs of the 32 rows, or those across the two blocks.
+__device__ __forceinline__ bool sweep_32(double* work, int t, bool all, double tol2, double settled2) {
+  bool any = false;
+  __syncthreads();
+  if (all) {
+    any |= cross_pairs<8>(work, t, true, true, tol2, settled2);
+    __syncthreads();
+    any |= cross_pairs<4>(work, t, false, true, tol2, settled2);
+    __syncthreads();
+    any |= cross_pairs<2>(work, t, false, true, tol2, settled2);
+    __syncthreads();
+    any |= cross_pairs<1>(work, t, false, true, tol2, settled2);
+    __syncthreads();
+  }
+  any |= cross_pairs<16>(work, t, !all, false, tol2, settled2);
+  __syncthreads();
+  return any;
+}
+
+// The 16 columns from c0 on of J^T times the rows of a block pair (one wave): out(x, col, value) for the 32 x 16 entries.
+template <typename Row, typename Out>
+__device__ __forceinline__ void apply_32(Row row, const double* J, int c0, int lane, Out out) {
+  const int r = lane & 15, g = lane >> 4;
+  doublex4 acc[2];
+  acc[0] = acc[1] = doublex4{0.0, 0.0, 0.0, 0.0};
+  double b[kJN / 4];
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) {
-        const int col = rl + kJBLanes * e;
-        if (col < l) wa[col] = x[e];
-      }
+  for (int k = 0; k < kJN / 4; ++k) b[k] = row(4 * k + g)[c0 + r];
+#pragma unroll
+  for (int k = 0; k < kJN; k += 4) {
+    acc[0] = mfma_f64(J[jat(k + g, r)], b[k / 4], acc[0]);
+    acc[1] = mfma_f64(J[jat(k + g, kJB + r)], b[k / 4], acc[1]);
+  }
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) out(kJB * m + g + 4 * v, c0 + r, acc[m][v]);
+}
+
+// Bytes of LDS of a block pair: its rows have Lp columns (padding zero) and a stride of Lp + 2 doubles, which spreads the 16
+// rows a wave reads over the banks.
+static constexpr size_t jacobi_lds_bytes(int Lp) { return sizeof(double) * ((size_t)kJN * (Lp + 2) + kJWork); }
+
+// Up to 32 rows: one workgroup, one block pair.
+__global__ void __launch_bounds__(kJThreads)
+k_jacobi_small(const double* __restrict__ R, int ldr, int l, int Lp, double* __restrict__ Wg, double* __restrict__ sig,
+               int* __restrict__ info, const int* __restrict__ breakdown_flag, double tol, double settled) {
+  extern __shared__ __align__(16) double W[];
+  __shared__ int rotated;
+  __shared__ int order_sh[kJN];
+  const int t = threadIdx.x, ld = Lp + 2;
+  if (breakdown_flag && breakdown_flag[0] != 0) {
+    if (t == 0) { info[0] = 0; info[1] = 0; }
+    return;
+  }
+  for (int i = t >> 5; i < kJN; i += kJThreads / 32)
+    for (int c = t & 31; c < Lp; c += 32) W[i * ld + c] = i < l && c < l ? R[(int64_t)i * ldr + c] : 0.0;
+  double* work = W + kJN * ld;
+  int sweeps = 0, converged = (l < 2);
+  auto row = [&](int x) { return W + x * ld; };
+  while (!converged && sweeps < kMaxSweeps) {
+    if (t == 0) rotated = 0;
+    __syncthreads();
+    gram_32(row, Lp, work, t);
+    if (sweep_32(work, t, true, tol * tol, settled * settled)) rotated = 1;
+    for (int c0 = kJB * (t >> 6); c0 < Lp; c0 += 4 * kJB)
+      apply_32(row, work + 2 * kJN * kJN, c0, t & 63, [&](int x, int c, double v) { row(x)[c] = v; });
+    __syncthreads();
+    ++sweeps;
+    converged = rotated == 0;
+    __syncthreads();
+  }
+  publish<kJThreads>(W, ld, l, Lp, Wg, sig, order_sh, t, t & 63, t >> 6);
+  if (t == 0) { info[0] = sweeps; info[1] = converged; }
+}
+
+// ---- rows in global memory, one launch per round ----------------------------------------------------------------------
+// info: [0] sweeps done, [1] converged, [2] a rotation of the running sweep was above the bar, [3] nothing left to do.
+__global__ void k_jacobi_init(const double* __restrict__ R, int ldr, int l, int Lp, double* __restrict__ W,
+                              int* __restrict__ info, const int* __restrict__ breakdown_flag) {
+  const int c = threadIdx.x, i = blockIdx.x;
+  if (i == 0 && c == 0) {
+    info[0] = info[1] = info[2] = 0;
+    info[3] = breakdown_flag && breakdown_flag[0] != 0;
+  }
+  for (int cc = c; cc < Lp; cc += blockDim.x) W[(int64_t)i * Lp + cc] = i < l && cc < l ? R[(int64_t)i * ldr + cc] : 0.0;
+}
+
+__global__ void __launch_bounds__(kJThreads)
+k_jacobi_pair(double* __restrict__ W, int l, int Lp, int nblk2, int outer, double tol, double settled, int* __restrict__ info) {
+  extern __shared__ __align__(16) double sh[];
+  const int t = threadIdx.x, ld = Lp + 2, done = info[3];
+  int I, J;
+  rr_pair(blockIdx.x, outer, nblk2, I, J);
+  const int rI = I * kJB, rJ = J * kJB;                 // I < J; the last block of an odd count is all padding
+  if (rI >= l || (outer > 0 && rJ >= l)) return;        // uniform over the workgroup
+  if (done) return;
+  double* work = sh + kJN * ld;
+  auto grow = [&](int x) { return x < kJB ? rI + x : rJ + x - kJB; };
+  for (int x = t >> 5; x < kJN; x += kJThreads / 32) {
+    const double* src = W + (int64_t)min(grow(x), Lp - 1) * Lp;
+    const bool live = grow(x) < l;
+#pragma unroll 4
+    for (int c = 2 * (t & 31); c < Lp; c += 64) {
+      const double2 v = *(const double2*)(src + c);
+      *(double2*)(sh + x * ld + c) = live ? v : double2{0.0, 0.0};
     }
   }
   __syncthreads();
-  for (int idx = tid; idx < 2 * kJB * l; idx += kJBThreads) {
-    const int rr = idx / l, c = idx - rr * l;
-    const bool live = rr < kJB ? rr < nI : rr - kJB < nJ;
-    const int grow = rr < kJB ? rI + rr : rJ + rr - kJB;
-    if (live) W[(int64_t)grow * Lp + c] = sh[idx];
-  }
-  if (any && rl == 0) *rotated = 1;
+  auto row = [&](int x) { return sh + x * ld; };
+  gram_32(row, Lp, work, t);
+  const bool any = sweep_32(work, t, outer == 0, tol * tol, settled * settled);
+  for (int c0 = kJB * (t >> 6); c0 < Lp; c0 += 4 * kJB)
+    apply_32(row, work + 2 * kJN * kJN, c0, t & 63, [&](int x, int c, double v) {
+      if (grow(x) < l) W[(int64_t)grow(x) * Lp + c] = v;
+    });
+  if (any) info[2] = 1;
 }
 
-__global__ void k_set_int(int* p, int v) { *p = v; }
+// End of a sweep.
+__global__ void k_jacobi_check(int* __restrict__ info) {
+  if (info[3]) return;
+  info[0] += 1;
+  if (info[2] == 0) info[1] = info[3] = 1;
+  info[2] = 0;
+}
 
-__global__ void __launch_bounds__(kSvdThreads)
-k_jacobi_publish(double* __restrict__ W, int l, int Lp, double* __restrict__ sig, int* __restrict__ info,
-                 int sweeps, int converged) {
+// Row norms, one wave per row.
+__global__ void __launch_bounds__(256)
+k_jacobi_norms(const double* __restrict__ W, int l, int Lp, double* __restrict__ sig, const int* __restrict__ breakdown_flag) {
+  const int lane = threadIdx.x & 63, i = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (i >= l || (breakdown_flag && breakdown_flag[0] != 0)) return;
+  double s2 = 0.0;
+  for (int e = lane; e < l; e += 64) { const double x = W[(int64_t)i * Lp + e]; s2 = fma(x, x, s2); }
+  s2 = wave_sum(s2);
+  if (lane == 0) sig[Lp + i] = sqrt(s2);
+}
+
+// Their descending order.
+__global__ void __launch_bounds__(kMaxL)
+k_jacobi_order(int l, int Lp, double* __restrict__ sig, const int* __restrict__ breakdown_flag) {
+  __shared__ double s[kMaxL];
   __shared__ int order_sh[kMaxL];
-  const int tid = threadIdx.x;
-  publish<kSvdThreads>(W, Lp, l, Lp, W, sig, order_sh, tid, tid & 63, tid >> 6);
-  if (tid == 0) { info[0] = sweeps; info[1] = converged; }
+  if (breakdown_flag && breakdown_flag[0] != 0) return;
+  const int i = threadIdx.x;
+  if (i < l) { s[i] = sig[Lp + i]; order_sh[i] = 0; }
+  __syncthreads();
+  if (i < l) {
+    const double si = s[i];
+    int rank = 0;
+    for (int j = 0; j < l; ++j) rank += (s[j] > si) || (s[j] == si && j < i);
+    order_sh[rank] = i;
+  }
+  __syncthreads();
+  if (i < l) { sig[i] = s[order_sh[i]]; sig[2 * Lp + i] = (double)order_sh[i]; }
 }
 
 // Sorted factors.  Vr[t][i] = W[o_i][t] / s_i;  Ur[kk][i] = sum_t R[kk][t] Vr[t][i] / s_i.
@@ -455,14 +644,14 @@ __global__ void k_svd_outputs(const double* __restrict__ R, int ldr, const doubl
 }
 
 template <int EPL, int LPP>
-static int launch_jacobi_lds(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* breakdown_flag,
+static int launch_jacobi_rows(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* breakdown_flag,
                              double tol, double settled, hipStream_t stream) {
-  auto kern = k_jacobi_lds<EPL, LPP>;
+  auto kern = k_jacobi_rows<EPL, LPP>;
   const size_t lds = (size_t)l * l * sizeof(double);
   static bool attr_set = false;
   if (!attr_set) {
     BRSVD_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      kJacobiLdsMaxL * kJacobiLdsMaxL * (int)sizeof(double)));
+                                      kJacobiRowsMaxL * kJacobiRowsMaxL * (int)sizeof(double)));
     attr_set = true;
   }
   hipLaunchKernelGGL(kern, dim3(1), dim3(64 * LPP), lds, stream, R, ldr, l, Lp, w.W, w.sig, w.info,
@@ -471,71 +660,58 @@ static int launch_jacobi_lds(const double* R, int ldr, int l, int Lp, SvdWork& w
   return BRSVD_OK;
 }
 
-template <int EPL>
-static int launch_jacobi_block_inst(double* W, int l, int Lp, int nblk2, int outer, double tol, double settled,
-                                    int* rotated, hipStream_t stream) {
-  auto kern = k_jacobi_block<EPL>;
+// Sweeps that are enqueued before the host looks at the convergence flag: fewer have not been seen to do for more than
+// 128 rows, and the launches of a sweep that is not needed any more return at once (about 3 us each).
+constexpr int kJacobiBlindSweeps = 5;
+
+static int jacobi_global(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* breakdown_flag, double tol,
+                         double settled, hipStream_t stream) {
   static bool attr_set = false;
   if (!attr_set) {
-    BRSVD_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      2 * kJB * kMaxL * (int)sizeof(double)));
+    BRSVD_HIP_TRY(hipFuncSetAttribute((const void*)k_jacobi_pair, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                      (int)jacobi_lds_bytes(kMaxL)));
     attr_set = true;
   }
-  hipLaunchKernelGGL(kern, dim3(nblk2 / 2), dim3(kJBThreads), (size_t)2 * kJB * l * sizeof(double), stream, W, l, Lp, nblk2,
-                     outer, tol, settled, rotated);
+  hipLaunchKernelGGL(k_jacobi_init, dim3(Lp), dim3(128), 0, stream, R, ldr, l, Lp, w.W, w.info, breakdown_flag);
+  const int nblk = (int)ceil_div(l, kJB), nblk2 = (nblk + 1) & ~1;
+  for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
+    for (int outer = 0; outer < nblk2 - 1; ++outer)
+      hipLaunchKernelGGL(k_jacobi_pair, dim3(nblk2 / 2), dim3(kJThreads), jacobi_lds_bytes(Lp), stream, w.W, l, Lp,
+                         nblk2, outer, tol, settled, w.info);
+    hipLaunchKernelGGL(k_jacobi_check, dim3(1), dim3(1), 0, stream, w.info);
+    BRSVD_HIP_TRY(hipGetLastError());
+    if (sweep + 1 < kJacobiBlindSweeps) continue;
+    int done = 0;
+    BRSVD_HIP_TRY(hipMemcpyAsync(&done, w.info + 3, sizeof(int), hipMemcpyDeviceToHost, stream));
+    BRSVD_HIP_TRY(hipStreamSynchronize(stream));
+    if (done) break;
+  }
+  hipLaunchKernelGGL(k_jacobi_norms, dim3((unsigned)ceil_div(l, 4)), dim3(256), 0, stream, w.W, l, Lp, w.sig, breakdown_flag);
+  hipLaunchKernelGGL(k_jacobi_order, dim3(1), dim3(kMaxL), 0, stream, l, Lp, w.sig, breakdown_flag);
+  BRSVD_HIP_TRY(hipGetLastError());
   return BRSVD_OK;
-}
-static int launch_jacobi_block(double* W, int l, int Lp, int nblk2, int outer, double tol, double settled, int* rotated,
-                               hipStream_t stream) {
-  if (l <= 192) return launch_jacobi_block_inst<3>(W, l, Lp, nblk2, outer, tol, settled, rotated, stream);
-  if (l <= 320) return launch_jacobi_block_inst<5>(W, l, Lp, nblk2, outer, tol, settled, rotated, stream);
-  return launch_jacobi_block_inst<8>(W, l, Lp, nblk2, outer, tol, settled, rotated, stream);
 }
 
 template <typename TO>
 int small_svd(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* breakdown_flag, double* S,
               TO* S32, TO* XV, TO* XU, double* Ur, double* Vr, hipStream_t stream) {
   if (l < 1 || l > kMaxL) return BRSVD_ERR_ARG;
-  const double tol = 1e-13;
+  const double tol = kTolRows;
   // fp64 factors or singular values asked for: the strict bar; single-precision results only: the relaxed one
   const double settled = (sizeof(TO) == 4 && !S && !Ur && !Vr) ? kSettledF32 : kSettled;
-  if (l <= kJacobiLdsMaxL) {
+  if (l <= kJN) {
+    hipLaunchKernelGGL(k_jacobi_small, dim3(1), dim3(kJThreads), jacobi_lds_bytes(Lp), stream, R, ldr, l, Lp, w.W, w.sig, w.info,
+                       breakdown_flag, kTolBlocks, settled);
+    BRSVD_HIP_TRY(hipGetLastError());
+  } else if (l <= kJacobiRowsMaxL) {
     // Lanes per pair: 16 for l <= 96; above that 8 (fewer, longer instruction streams: the per-pair
     // rotation arithmetic and reductions are issued half as often; 0.88 against 0.92 ms at l = 110).
-    if (l <= 32) BRSVD_TRY((launch_jacobi_lds<2, 16>(R, ldr, l, Lp, w, breakdown_flag, tol, settled, stream)));
-    else if (l <= 64) BRSVD_TRY((launch_jacobi_lds<4, 16>(R, ldr, l, Lp, w, breakdown_flag, tol, settled, stream)));
-    else if (l <= 96) BRSVD_TRY((launch_jacobi_lds<6, 16>(R, ldr, l, Lp, w, breakdown_flag, tol, settled, stream)));
-    else if (l <= 112) BRSVD_TRY((launch_jacobi_lds<14, 8>(R, ldr, l, Lp, w, breakdown_flag, tol, settled, stream)));
-    else BRSVD_TRY((launch_jacobi_lds<16, 8>(R, ldr, l, Lp, w, breakdown_flag, tol, settled, stream)));
+    if (l <= 64) BRSVD_TRY((launch_jacobi_rows<4, 16>(R, ldr, l, Lp, w, breakdown_flag, tol, settled, stream)));
+    else if (l <= 96) BRSVD_TRY((launch_jacobi_rows<6, 16>(R, ldr, l, Lp, w, breakdown_flag, tol, settled, stream)));
+    else if (l <= 112) BRSVD_TRY((launch_jacobi_rows<14, 8>(R, ldr, l, Lp, w, breakdown_flag, tol, settled, stream)));
+    else BRSVD_TRY((launch_jacobi_rows<16, 8>(R, ldr, l, Lp, w, breakdown_flag, tol, settled, stream)));
   } else {
-    // Host-driven sweeps: the convergence flag is read back once per sweep.
-    int* rotated = w.info + 2;
-    int host_flag = 0;
-    if (breakdown_flag) {
-      BRSVD_HIP_TRY(hipMemcpyAsync(&host_flag, breakdown_flag, sizeof(int), hipMemcpyDeviceToHost, stream));
-      BRSVD_HIP_TRY(hipStreamSynchronize(stream));
-    }
-    int sweeps = 0, converged = 0;
-    if (host_flag == 0) {
-      hipLaunchKernelGGL(k_jacobi_init, dim3((unsigned)ceil_div((int64_t)l * l, 256)), dim3(256), 0, stream, R,
-                         ldr, l, Lp, w.W);
-      const int nblk = (int)ceil_div(l, kJB), nblk2 = (nblk + 1) & ~1;
-      while (!converged && sweeps < kMaxSweeps) {
-        hipLaunchKernelGGL(k_set_int, dim3(1), dim3(1), 0, stream, rotated, 0);
-        for (int outer = -1; outer < nblk2 - 1; ++outer)
-          BRSVD_TRY(launch_jacobi_block(w.W, l, Lp, nblk2, outer, tol, settled, rotated, stream));
-        BRSVD_HIP_TRY(hipGetLastError());
-        int rot = 1;
-        BRSVD_HIP_TRY(hipMemcpyAsync(&rot, rotated, sizeof(int), hipMemcpyDeviceToHost, stream));
-        BRSVD_HIP_TRY(hipStreamSynchronize(stream));
-        ++sweeps;
-        converged = (rot == 0);
-      }
-    }
-    if (host_flag == 0)
-      hipLaunchKernelGGL(k_jacobi_publish, dim3(1), dim3(kSvdThreads), 0, stream, w.W, l, Lp, w.sig, w.info,
-                         sweeps, converged);
-    BRSVD_HIP_TRY(hipGetLastError());
+    BRSVD_TRY(jacobi_global(R, ldr, l, Lp, w, breakdown_flag, kTolBlocks, settled, stream));
   }
   hipLaunchKernelGGL(k_svd_outputs<TO>, dim3((unsigned)ceil_div((int64_t)Lp * Lp, 256)), dim3(256), 0, stream, R, ldr,
                      w.W, w.sig, l, Lp, S, S32, XV, XU, Ur, Vr, breakdown_flag);

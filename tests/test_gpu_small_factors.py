@@ -1,0 +1,89 @@
+"""The l x l factors at the edges of their tiles and of the kernels' ranges: Cholesky factor and inverse behind the
+orthonormalisation (16 x 16 tiles, in LDS up to 128, in global memory above), and the Jacobi SVD (row blocks of 16; one
+workgroup up to 32 rows, row rotations up to 128, block pairs in global memory above)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1706_07191_amd as B
+from tests.gpu_util import EPS32, need_gpu
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [1, 15, 16, 17, 32, 33, 64, 65, 112, 113, 127, 128, 129, 144, 161, 272, 512]
+
+
+def _panel(rows, l, decay, seed):
+    g = torch.Generator().manual_seed(seed)
+    s = torch.exp(-torch.arange(l, dtype=torch.float64) * (np.log(decay) / max(l, 2)))
+    mix = torch.linalg.qr(torch.randn(l, l, generator=g, dtype=torch.float64))[0]
+    return ((torch.randn(rows, l, generator=g, dtype=torch.float64) * s) @ mix).float()
+
+
+@pytest.mark.parametrize("l", EDGES)
+@pytest.mark.parametrize("method", [B.BRSVD_ORTH_AUTO, B.BRSVD_ORTH_TSQR])
+def test_orthonormalisation_and_its_factor(l, method):
+    dev = need_gpu()
+    print(f"[case] orth l={l} method={method}", flush=True)
+    rows = 3 * l + 70
+    P = _panel(rows, l, 30.0, l)
+    Q, R, _ = B.brsvd_orth(P.to(dev), method=method, want_R=True)
+    Q, R = Q.double().cpu(), R.cpu()
+    eye = torch.eye(l, dtype=torch.float64)
+    # Q is stored in fp32: each entry of Q^T Q carries the rounding of rows products of entries around rows^-1/2 (random
+    # signs), and the product P R^-1 that of l terms; P = Q R holds to the same, times the size of R's columns
+    assert float((Q.T @ Q - eye).abs().max()) <= 8 * EPS32 * np.sqrt(l)
+    assert float((Q @ R - P.double()).abs().max()) <= 16 * EPS32 * np.sqrt(l) * float(P.double().norm(dim=0).max() / np.sqrt(rows) * 4)
+    assert bool((torch.tril(R, -1) == 0).all())
+    if method == B.BRSVD_ORTH_AUTO:
+        assert bool((torch.diagonal(R) > 0).all())
+
+
+def test_zero_columns_are_clamped():
+    """Columns of zeros: their pivots are clamped in the first sweep and refused in the last one, the fallback takes over or
+    the call says so; nothing is left undefined."""
+    dev = need_gpu()
+    P = _panel(500, 40, 10.0, 5)
+    P[:, 17] = 0
+    try:
+        Q, R, fb = B.brsvd_orth(P.to(dev), want_R=True)
+        assert bool(torch.isfinite(Q).all()) and bool(torch.isfinite(R).all())
+    except B.BrsvdError as e:
+        assert e.status == B.BRSVD_ERR_ORTH_BREAKDOWN
+
+
+@pytest.mark.parametrize("l", EDGES)
+@pytest.mark.parametrize("cond", [1e2, 1e8])
+def test_small_svd(l, cond):
+    dev = need_gpu()
+    print(f"[case] small_svd l={l} cond={cond}", flush=True)
+    g = torch.Generator().manual_seed(1000 + l)
+    s = torch.logspace(0, -np.log10(cond), l, dtype=torch.float64)
+    q = [torch.linalg.qr(torch.randn(l, l, generator=g, dtype=torch.float64))[0] for _ in range(2)]
+    R = torch.linalg.qr((q[0] * s) @ q[1])[1]
+    S, U, V, sweeps = (x.cpu() if isinstance(x, torch.Tensor) else x for x in B.brsvd_small_svd(R.to(dev).contiguous()))
+    ref = torch.linalg.svdvals(R)
+    eye = torch.eye(l, dtype=torch.float64)
+    eps = 2.0 ** -52
+    assert sweeps <= 20 and bool((S[:-1] >= S[1:]).all())
+    # LAPACK's values are good to a few eps of the largest one; rotations act on rows of l entries
+    assert float((S - ref).abs().max()) <= 40 * eps * np.sqrt(l)
+    # cosines up to 1e-13 are left where rows are rotated; U = R V / s carries them times s_1 / s_i
+    assert float((V.T @ V - eye).abs().max()) <= 4e-13
+    assert float((U.T @ U - eye).abs().max()) <= 4e-13 * cond * 10
+    assert float(((U * S) @ V.T - R).abs().max()) <= 1e-12
+
+
+def test_small_svd_of_equal_and_zero_values():
+    dev = need_gpu()
+    for l in (16, 30, 40, 160):
+        g = torch.Generator().manual_seed(l)
+        Q = torch.linalg.qr(torch.randn(l, l, generator=g, dtype=torch.float64))[0]
+        S, U, V, _ = B.brsvd_small_svd(Q.to(dev).contiguous())             # all singular values equal
+        assert float((S.cpu() - 1).abs().max()) <= 1e-13
+        R = torch.linalg.qr(torch.randn(l, l, generator=g, dtype=torch.float64))[1]
+        R[l // 2:] = 0                                                     # rank l / 2
+        S = B.brsvd_small_svd(R.to(dev).contiguous())[0].cpu()
+        ref = torch.linalg.svdvals(R)
+        assert float((S - ref).abs().max()) <= 1e-13 * float(ref[0])
+        assert bool((B.brsvd_small_svd(torch.zeros(l, l, dtype=torch.float64, device=dev))[0] == 0).all())
