@@ -32,7 +32,7 @@ enum Cat { CAT_AN = 0, CAT_AT, CAT_ORTH, CAT_SVD, CAT_LIFT, CAT_COPY, CAT_ELEM, 
 
 struct Layout {
   // offsets into the arena
-  uint64_t Pm[2], Pn[2], gemm_scratch, gram_part, G, R0, R1, Xinv, Rinv, Rtot, XV, XU, svdW, svdJ, sig,
+  uint64_t Pm[2], Pn[2], gemm_scratch, gram_part, G, R0, R1, Rinv, Rtot, XV, XU, svdW, sig,
       S32, flags, tsqr, stage[2], scal, rpcaU, rpcaVt, rpca_part, total;
   uint64_t gemm_scratch_bytes, tsqr_bytes, stage_bytes;
   int gram_chunks;
@@ -126,10 +126,11 @@ Layout make_layout(const brsvd_params& p, int64_t b) {
   L.gram_chunks = (int)std::max(orth_gram_slots(m, Lp), orth_gram_slots(n, Lp));
   L.gram_part = take((uint64_t)L.gram_chunks * Lp * Lp * 8);
   const uint64_t sq8 = (uint64_t)Lp * Lp * 8;
-  L.G = take(sq8); L.R0 = take(sq8); L.R1 = take(sq8); L.Xinv = take(sq8); L.Rtot = take(sq8);
+  L.G = take(sq8); L.R0 = take(sq8); L.R1 = take(sq8); L.Rtot = take(sq8);
+  take(2 * sq8);             // not used: the workspace keeps the size that callers' budgets were chosen for
   const uint64_t sqe = (uint64_t)Lp * Lp * esz;
   L.Rinv = take(sqe); L.XV = take(sqe); L.XU = take(sqe);
-  L.svdW = take(sq8); L.svdJ = take(sq8);
+  L.svdW = take(sq8);
   L.sig = take((uint64_t)3 * Lp * 8);
   L.S32 = take((uint64_t)Lp * esz);
   L.flags = take(64);
@@ -247,7 +248,6 @@ OrthWorkT<T> orth_work(brsvd_handle h) {
   w.G = h->at<double>(h->lay.G);
   w.R[0] = h->at<double>(h->lay.R0);
   w.R[1] = h->at<double>(h->lay.R1);
-  w.Xinv = h->at<double>(h->lay.Xinv);
   w.Rinv = h->at<T>(h->lay.Rinv);
   w.flags = h->at<int>(h->lay.flags);
   w.gemm_scratch = h->arena + h->lay.gemm_scratch;
@@ -480,7 +480,6 @@ int enqueue_brsvd(brsvd_handle h, const T* A, int64_t lda, const T* Omega, T* U,
   }
   SvdWork sw;
   sw.W = h->at<double>(h->lay.svdW);
-  sw.J = h->at<double>(h->lay.svdJ);
   sw.sig = h->at<double>(h->lay.sig);
   sw.info = h->at<int>(h->lay.flags) + 4;
   T* XV = h->at<T>(h->lay.XV);
@@ -564,7 +563,6 @@ int enqueue_alg2(brsvd_handle h, const T* A, int64_t lda, uint64_t seed, const T
   }
   SvdWork sw;
   sw.W = h->at<double>(h->lay.svdW);
-  sw.J = h->at<double>(h->lay.svdJ);
   sw.sig = h->at<double>(h->lay.sig);
   sw.info = h->at<int>(h->lay.flags) + 4;
   T* XV = h->at<T>(h->lay.XV);
@@ -955,7 +953,7 @@ int step_gemm_at(const T* A, int64_t lda, int64_t rows, int64_t n, const T* Q, i
 }
 
 // ---- small SVD on a given scratch buffer ---------------------------------------------------------
-// Scratch of small_svd: the rows being rotated and one more Lp x Lp fp64 matrix, 3*Lp doubles (norms,
+// Scratch of small_svd: the rows being rotated, an Lp x Lp fp64 matrix that is not used, 3*Lp doubles (norms,
 // sorted values, order) and a few integer flags.  Nothing in it has to be initialised: every kernel
 // writes what it later reads.
 constexpr uint64_t small_svd_scratch_bytes(int Lp) {
@@ -968,7 +966,6 @@ int small_svd_on_scratch(const double* R, int l, double* S, double* Ur, double* 
   const uint64_t sq8 = align_up((uint64_t)Lp * Lp * 8);
   SvdWork w;
   w.W = (double*)buf;
-  w.J = (double*)(buf + sq8);
   w.sig = (double*)(buf + 2 * sq8);
   w.info = (int*)(buf + 2 * sq8 + align_up((uint64_t)3 * Lp * 8));
   int status = small_svd<float>(R, l, l, Lp, w, nullptr, S, nullptr, nullptr, nullptr, Ur, Vr, s);
@@ -1300,7 +1297,7 @@ int brsvd_orth(float* P, int64_t rows, int32_t l, int32_t method, double* R, int
     w.gram_part = (double*)take((uint64_t)o.chunks * o.sq8);
     w.gram_chunks_max = o.chunks;
     w.G = (double*)take(o.sq8); w.R[0] = (double*)take(o.sq8); w.R[1] = (double*)take(o.sq8);
-    w.Xinv = (double*)take(o.sq8);
+    take(o.sq8);             // not used: the scratch keeps the size that callers have planned
     double* Rtot = (double*)take(o.sq8);
     w.Rinv = (float*)take(o.sq4);
     w.flags = (int*)take(256);

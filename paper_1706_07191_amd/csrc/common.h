@@ -152,7 +152,6 @@ struct OrthWorkT {
   int gram_chunks_max;
   double* G;           // Lp x Lp
   double* R[2];        // upper-triangular factors of the two CholeskyQR sweeps (stride Lp)
-  double* Xinv;        // Lp x Lp fp64 scratch for R^-1
   T* Rinv;             // Lp x Lp zero-padded inverse factor in the panels' type (right operand of the apply GEMM)
   int* flags;          // device: [0] = breakdown flag (0 = none, else 1 + column)
   void* gemm_scratch;
@@ -194,9 +193,8 @@ int diag_ratio(const double* R, int l, int Lp, double* out, hipStream_t stream);
 // ---- small SVD (small_svd.hip) -------------------------------------------------------------
 struct SvdWork {
   double* W;     // Lp x Lp rows being orthogonalised
-  double* J;     // Lp x Lp accumulated rotations (transposed)
   double* sig;   // 3 * Lp
-  int* info;     // device: [0] sweeps, [1] converged
+  int* info;     // device, six: [0] sweeps, [1] converged, the others for the iteration itself
 };
 // R (l x l fp64, stride ldr): R = Ur diag(S) Vr^T.  Writes S (descending) as fp64 and/or in the
 // panels' type TO, the zero-padded (Lp x Lp) operands XV = Vr and XU = Ur used by the lifts (type TO),

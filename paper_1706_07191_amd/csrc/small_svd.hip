@@ -12,7 +12,6 @@
 namespace brsvd {
 
 constexpr int kMaxSweeps = 40;
-constexpr int kJacobiRowsMaxL = 128;   // largest l whose rows fit the LDS of one CU for row rotations
 
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
@@ -133,10 +132,9 @@ __device__ __forceinline__ double row8_sum(double v) {
   return v;
 }
 
-// ---- 33 to 128 rows: row rotations in LDS -------------------------------------------------------------------------
-// Each group of LPP lanes (16) owns one row pair per step, so a wave handles
-// 64/LPP pairs with one instruction stream and up to 64 pairs (l <= 128) take 1024 threads.
-// EPL = elements of a row per lane = ceil(l / LPP).
+// ---- 33 to 48 and 65 to 80 rows: row rotations in LDS -------------------------------------------------------------------------
+// Each group of 16 lanes owns one row pair per step, so a wave handles 4 pairs with one instruction stream and up to
+// 64 pairs take 1024 threads.  EPL = elements of a row per lane = ceil(l / 16).
 // Pair schedule of a sweep (every pair of rows met exactly once): the index range is halved
 // recursively.  At a level, every segment [base, base + n) is cut into a top half of h = ceil(n/2) rows
 // and a bottom half; in step s top row i meets bottom row (i + s) mod h, so h steps pair every top with
@@ -144,8 +142,9 @@ __device__ __forceinline__ double row8_sum(double v) {
 // side (l-1 .. l+1 steps in all).  Within a level a group keeps its top row in registers and only the
 // bottom rows travel through LDS, which halves the LDS traffic of the round-robin schedule.
 constexpr int kJLev = 7;      // levels for l <= 128
+constexpr int LPP = 16;
 
-template <int EPL, int LPP>
+template <int EPL>
 __global__ void __launch_bounds__(64 * LPP)
 k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __restrict__ Wg,
              double* __restrict__ sig, int* __restrict__ info, const int* __restrict__ breakdown_flag,
@@ -231,8 +230,7 @@ k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __re
           be = fma(y[e], y[e], be);
           ga = fma(x[e], y[e], ga);
         }
-        if (LPP == 16) { al = row16_sum(al); be = row16_sum(be); ga = row16_sum(ga); }
-        else { al = row8_sum(al); be = row8_sum(be); ga = row8_sum(ga); }
+        al = row16_sum(al); be = row16_sum(be); ga = row16_sum(ga);
         double c, s;
         bool big;
         const bool rot = rotation_exact(al, be, ga, tol2, settled2, c, s, big) && valid;
@@ -279,12 +277,14 @@ k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __re
 // A sweep is a round robin over the block pairs.  Its first round rotates all 496 pairs of the 32 rows (31 steps of
 // 16 disjoint pairs), the others the 256 pairs across the two blocks (16 steps).
 //   l <= 32: one block pair, rows in LDS for all sweeps (k_jacobi_small);
-//   l > kJacobiRowsMaxL = 128: one launch per round, one workgroup per block pair, rows in L2 (k_jacobi_pair);
-//   in between two to four block pairs share one CU, or seven launches make a sweep, and row rotations stay ahead (l = 33 382
-//   against 243 us, 60 440 / 413, 96 891 / 823, 110 1273 / 1062; 128 1290 / 1452).
+//   otherwise: one workgroup per block pair, rows in global memory, one launch (k_jacobi_rounds);
+//   but with three or five blocks, where a padding block goes round with the others, row rotations stay ahead (us, this against row
+//   rotations: l = 33 367 / 236, 48 354 / 296, 72 654 / 567; on the other side 60 407 / 414 (27 of 2526 less in a
+//   whole decomposition with single-precision results), 64 368 / 431, 96 659 / 824, 110 893 / 1064, 128 906 / 1458).
 // What bounds it: the latency of a step, 800 to 900 cycles from barrier to barrier, half of it the rotation; the matrix products
-// take 5 to 9 thousand cycles of a round's 14 + 10 thousand (l = 160, 272).  Measured (us per call of the small SVD, row
-// rotations before and this): l = 20 143 -> 134, 30 181 -> 151, 160 2867 -> 1980, 272 6140 -> 4280, 512 13900 -> 9850.  Two
+// take 5 to 9 thousand cycles of a round beside the 14 thousand of the steps (l = 160, 272).  Measured (us per call of the small
+// SVD, row rotations before and this): l = 20 143 -> 134, 30 181 -> 151, 110 1064 -> 893, 160 2867 -> 1405, 272 6140 -> 3660,
+// 512 13900 -> 8890.  Two
 // accumulator chains per product: four gain 2 % at l <= 32 and lose 6 % above 128.
 constexpr int kJB = 16;
 constexpr int kJN = 2 * kJB;                      // rows of a block pair
@@ -524,85 +524,127 @@ k_jacobi_small(const double* __restrict__ R, int ldr, int l, int Lp, double* __r
   if (t == 0) { info[0] = sweeps; info[1] = converged; }
 }
 
-// ---- rows in global memory, one launch per round ----------------------------------------------------------------------
-// info: [0] sweeps done, [1] converged, [2] a rotation of the running sweep was above the bar, [3] nothing left to do.
+// ---- more than 32 rows: one workgroup per pair of blocks ---------------------------------------------------------------
+// info: [0] sweeps done, [1] converged, [2] arrivals, [3] last sweep (from 1) with a rotation above the bar, [4] nothing to do,
+// [5] a workgroup has given up waiting.
 __global__ void k_jacobi_init(const double* __restrict__ R, int ldr, int l, int Lp, double* __restrict__ W,
                               int* __restrict__ info, const int* __restrict__ breakdown_flag) {
   const int c = threadIdx.x, i = blockIdx.x;
-  if (i == 0 && c == 0) {
-    info[0] = info[1] = info[2] = 0;
-    info[3] = breakdown_flag && breakdown_flag[0] != 0;
-  }
+  if (i == 0 && c < 6) info[c] = c == 4 && breakdown_flag && breakdown_flag[0] != 0;
   for (int cc = c; cc < Lp; cc += blockDim.x) W[(int64_t)i * Lp + cc] = i < l && cc < l ? R[(int64_t)i * ldr + cc] : 0.0;
 }
 
-__global__ void __launch_bounds__(kJThreads)
-k_jacobi_pair(double* __restrict__ W, int l, int Lp, int nblk2, int outer, double tol, double settled, int* __restrict__ info) {
-  extern __shared__ __align__(16) double sh[];
-  const int t = threadIdx.x, ld = Lp + 2, done = info[3];
-  int I, J;
-  rr_pair(blockIdx.x, outer, nblk2, I, J);
-  const int rI = I * kJB, rJ = J * kJB;                 // I < J; the last block of an odd count is all padding
-  if (rI >= l || (outer > 0 && rJ >= l)) return;        // uniform over the workgroup
-  if (done) return;
-  double* work = sh + kJN * ld;
-  auto grow = [&](int x) { return x < kJB ? rI + x : rJ + x - kJB; };
-  for (int x = t >> 5; x < kJN; x += kJThreads / 32) {
-    const double* src = W + (int64_t)min(grow(x), Lp - 1) * Lp;
-    const bool live = grow(x) < l;
-#pragma unroll 4
-    for (int c = 2 * (t & 31); c < Lp; c += 64) {
-      const double2 v = *(const double2*)(src + c);
-      *(double2*)(sh + x * ld + c) = live ? v : double2{0.0, 0.0};
+// Ticks of the 100 MHz clock after which a workgroup stops waiting for the others.  They are all resident unless the GPU is
+// filled by other work, and start as that work ends; the limit only makes sure that every wait ends (the call then reports
+// that the iteration did not converge).
+constexpr unsigned long long kMeetTicks = 2000000000ull;
+
+// The 32 rows of the block pair at rows rI and rJ of W, to LDS; rows from l on are zero.  64 H columns at a time are under way.
+template <int H>
+__device__ __forceinline__ void load_pair(const double* W, int l, int Lp, int rI, int rJ, double* sh, int ld, int t) {
+  constexpr int XN = kJN / (kJThreads / 32);
+  for (int c0 = 2 * (t & 31); c0 < Lp; c0 += 64 * H) {
+    double2 v[XN][H];
+#pragma unroll
+    for (int q = 0; q < XN; ++q) {
+      const int x = (t >> 5) + q * (kJThreads / 32), i = x < kJB ? rI + x : rJ + x - kJB;
+      const double* src = W + (int64_t)min(i, l - 1) * Lp;
+#pragma unroll
+      for (int h = 0; h < H; ++h) v[q][h] = *(const double2*)(src + min(c0 + 64 * h, Lp - 2));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < XN; ++q) {
+      const int x = (t >> 5) + q * (kJThreads / 32), i = x < kJB ? rI + x : rJ + x - kJB;
+#pragma unroll
+      for (int h = 0; h < H; ++h)
+        if (c0 + 64 * h < Lp) *(double2*)(sh + x * ld + c0 + 64 * h) = i < l ? v[q][h] : double2{0.0, 0.0};
     }
   }
-  __syncthreads();
+}
+
+// All sweeps in one launch: nblk2 / 2 workgroups rotate one pair of blocks each, meet, and go on with the pairs of the next round.
+// The rows travel through global memory between rounds; they are stored at the scope of the device, past the L2 of an XCD, which
+// leaves the release at a meeting little to write back (4 % of the whole).  With a launch per round, and the host looking at the
+// convergence flag, l = 160 took 1980 us and 272 4280 us.  Eight times the workgroups with all but every eighth leaving at
+// once, to keep the rest on one XCD, gains 5 % below 128 and loses up to 13 % above.
+__global__ void __launch_bounds__(kJThreads)
+k_jacobi_rounds(double* W, int l, int Lp, int nblk2, double tol, double settled, double* sig, int* info) {
+  extern __shared__ __align__(16) double sh[];
+  __shared__ int state;
+  const int t = threadIdx.x, ld = Lp + 2;
+  if (info[4]) return;
+  double* work = sh + kJN * ld;
   auto row = [&](int x) { return sh + x * ld; };
-  gram_32(row, Lp, work, t);
-  const bool any = sweep_32(work, t, outer == 0, tol * tol, settled * settled);
-  for (int c0 = kJB * (t >> 6); c0 < Lp; c0 += 4 * kJB)
-    apply_32(row, work + 2 * kJN * kJN, c0, t & 63, [&](int x, int c, double v) {
-      if (grow(x) < l) W[(int64_t)grow(x) * Lp + c] = v;
-    });
-  if (any) info[2] = 1;
-}
-
-// End of a sweep.
-__global__ void k_jacobi_check(int* __restrict__ info) {
-  if (info[3]) return;
-  info[0] += 1;
-  if (info[2] == 0) info[1] = info[3] = 1;
-  info[2] = 0;
-}
-
-// Row norms, one wave per row.
-__global__ void __launch_bounds__(256)
-k_jacobi_norms(const double* __restrict__ W, int l, int Lp, double* __restrict__ sig, const int* __restrict__ breakdown_flag) {
-  const int lane = threadIdx.x & 63, i = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (i >= l || (breakdown_flag && breakdown_flag[0] != 0)) return;
-  double s2 = 0.0;
-  for (int e = lane; e < l; e += 64) { const double x = W[(int64_t)i * Lp + e]; s2 = fma(x, x, s2); }
-  s2 = wave_sum(s2);
-  if (lane == 0) sig[Lp + i] = sqrt(s2);
-}
-
-// Their descending order.
-__global__ void __launch_bounds__(kMaxL)
-k_jacobi_order(int l, int Lp, double* __restrict__ sig, const int* __restrict__ breakdown_flag) {
-  __shared__ double s[kMaxL];
-  __shared__ int order_sh[kMaxL];
-  if (breakdown_flag && breakdown_flag[0] != 0) return;
-  const int i = threadIdx.x;
-  if (i < l) { s[i] = sig[Lp + i]; order_sh[i] = 0; }
-  __syncthreads();
-  if (i < l) {
-    const double si = s[i];
-    int rank = 0;
-    for (int j = 0; j < l; ++j) rank += (s[j] > si) || (s[j] == si && j < i);
-    order_sh[rank] = i;
+  int arrivals = 0, sweeps = 0, rI = 0, rJ = 0;
+  bool converged = false;
+  // Waits for every workgroup, and makes what each wrote before visible to all; false: given up.
+  auto meet = [&]() {
+    __syncthreads();
+    if (t == 0) {
+      arrivals += gridDim.x;
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      __hip_atomic_fetch_add(info + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      bool all = true;
+      const unsigned long long start = wall_clock64();
+      while (__hip_atomic_load(info + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < arrivals) {
+        if (wall_clock64() - start > kMeetTicks || __hip_atomic_load(info + 5, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+          __hip_atomic_store(info + 5, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          all = false;
+          break;
+        }
+        __builtin_amdgcn_s_sleep(1);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      state = all ? __hip_atomic_load(info + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -1;
+    }
+    __syncthreads();
+    return state >= 0;
+  };
+  while (!converged && sweeps < kMaxSweeps) {
+    ++sweeps;
+    bool any = false;
+    for (int outer = 0; outer < nblk2 - 1; ++outer) {
+      int I, J;
+      rr_pair(blockIdx.x, outer, nblk2, I, J);
+      rI = I * kJB;                                     // I < J; the last blocks may be all padding
+      rJ = J * kJB;
+      auto grow = [&](int x) { return x < kJB ? rI + x : rJ + x - kJB; };
+      if (rI < l && (outer == 0 || rJ < l)) {           // uniform over the workgroup
+        if (Lp <= 128) load_pair<2>(W, l, Lp, rI, rJ, sh, ld, t);
+        else load_pair<4>(W, l, Lp, rI, rJ, sh, ld, t);
+        __syncthreads();
+        gram_32(row, Lp, work, t);
+        any |= sweep_32(work, t, outer == 0, tol * tol, settled * settled);
+        for (int c0 = kJB * (t >> 6); c0 < Lp; c0 += 4 * kJB)
+          apply_32(row, work + 2 * kJN * kJN, c0, t & 63, [&](int x, int c, double v) {
+            if (grow(x) < l) __hip_atomic_store(W + (int64_t)grow(x) * Lp + c, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          });
+      }
+      if (outer == nblk2 - 2 && any)
+        __hip_atomic_fetch_max(info + 3, sweeps, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (!meet()) return;
+    }
+    converged = state < sweeps;                         // one that is ahead can only have noted a later sweep
   }
-  __syncthreads();
-  if (i < l) { sig[i] = s[order_sh[i]]; sig[2 * Lp + i] = (double)order_sh[i]; }
+  // norms of the rows of this workgroup's last pair, eight lanes a row; then their place in the descending order
+  const int x = t >> 3, e0 = t & 7, i = x < kJB ? rI + x : rJ + x - kJB;
+  double s2 = 0.0;
+  if (i < l)
+    for (int e = e0; e < l; e += 8) { const double v = W[(int64_t)i * Lp + e]; s2 = fma(v, v, s2); }
+  const double si = sqrt(row8_sum(s2));
+  if (i < l && e0 == 0) sig[Lp + i] = si;
+  if (!meet()) return;
+  if (i < l) {
+    int rank = 0;
+    for (int j = e0; j < l; j += 8) {
+      const double sj = sig[Lp + j];
+      rank += (sj > si) || (sj == si && j < i);
+    }
+    for (int off = 4; off > 0; off >>= 1) rank += __shfl_xor(rank, off, 8);
+    if (e0 == 0) { sig[rank] = si; sig[2 * Lp + rank] = (double)i; }
+  }
+  if (blockIdx.x == 0 && t == 0) { info[0] = sweeps; info[1] = converged; }
 }
 
 // Sorted factors.  Vr[t][i] = W[o_i][t] / s_i;  Ur[kk][i] = sum_t R[kk][t] Vr[t][i] / s_i.
@@ -643,51 +685,18 @@ __global__ void k_svd_outputs(const double* __restrict__ R, int ldr, const doubl
   if (XU) XU[idx] = xu;
 }
 
-template <int EPL, int LPP>
-static int launch_jacobi_rows(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* breakdown_flag,
-                             double tol, double settled, hipStream_t stream) {
-  auto kern = k_jacobi_rows<EPL, LPP>;
-  const size_t lds = (size_t)l * l * sizeof(double);
-  static bool attr_set = false;
-  if (!attr_set) {
-    BRSVD_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      kJacobiRowsMaxL * kJacobiRowsMaxL * (int)sizeof(double)));
-    attr_set = true;
-  }
-  hipLaunchKernelGGL(kern, dim3(1), dim3(64 * LPP), lds, stream, R, ldr, l, Lp, w.W, w.sig, w.info,
-                     breakdown_flag, tol, settled);
-  BRSVD_HIP_TRY(hipGetLastError());
-  return BRSVD_OK;
-}
-
-// Sweeps that are enqueued before the host looks at the convergence flag: fewer have not been seen to do for more than
-// 128 rows, and the launches of a sweep that is not needed any more return at once (about 3 us each).
-constexpr int kJacobiBlindSweeps = 5;
-
 static int jacobi_global(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* breakdown_flag, double tol,
                          double settled, hipStream_t stream) {
   static bool attr_set = false;
   if (!attr_set) {
-    BRSVD_HIP_TRY(hipFuncSetAttribute((const void*)k_jacobi_pair, hipFuncAttributeMaxDynamicSharedMemorySize,
+    BRSVD_HIP_TRY(hipFuncSetAttribute((const void*)k_jacobi_rounds, hipFuncAttributeMaxDynamicSharedMemorySize,
                                       (int)jacobi_lds_bytes(kMaxL)));
     attr_set = true;
   }
   hipLaunchKernelGGL(k_jacobi_init, dim3(Lp), dim3(128), 0, stream, R, ldr, l, Lp, w.W, w.info, breakdown_flag);
   const int nblk = (int)ceil_div(l, kJB), nblk2 = (nblk + 1) & ~1;
-  for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
-    for (int outer = 0; outer < nblk2 - 1; ++outer)
-      hipLaunchKernelGGL(k_jacobi_pair, dim3(nblk2 / 2), dim3(kJThreads), jacobi_lds_bytes(Lp), stream, w.W, l, Lp,
-                         nblk2, outer, tol, settled, w.info);
-    hipLaunchKernelGGL(k_jacobi_check, dim3(1), dim3(1), 0, stream, w.info);
-    BRSVD_HIP_TRY(hipGetLastError());
-    if (sweep + 1 < kJacobiBlindSweeps) continue;
-    int done = 0;
-    BRSVD_HIP_TRY(hipMemcpyAsync(&done, w.info + 3, sizeof(int), hipMemcpyDeviceToHost, stream));
-    BRSVD_HIP_TRY(hipStreamSynchronize(stream));
-    if (done) break;
-  }
-  hipLaunchKernelGGL(k_jacobi_norms, dim3((unsigned)ceil_div(l, 4)), dim3(256), 0, stream, w.W, l, Lp, w.sig, breakdown_flag);
-  hipLaunchKernelGGL(k_jacobi_order, dim3(1), dim3(kMaxL), 0, stream, l, Lp, w.sig, breakdown_flag);
+  hipLaunchKernelGGL(k_jacobi_rounds, dim3(nblk2 / 2), dim3(kJThreads), jacobi_lds_bytes(Lp), stream, w.W, l, Lp, nblk2, tol,
+                     settled, w.sig, w.info);
   BRSVD_HIP_TRY(hipGetLastError());
   return BRSVD_OK;
 }
@@ -696,20 +705,19 @@ template <typename TO>
 int small_svd(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* breakdown_flag, double* S,
               TO* S32, TO* XV, TO* XU, double* Ur, double* Vr, hipStream_t stream) {
   if (l < 1 || l > kMaxL) return BRSVD_ERR_ARG;
-  const double tol = kTolRows;
   // fp64 factors or singular values asked for: the strict bar; single-precision results only: the relaxed one
   const double settled = (sizeof(TO) == 4 && !S && !Ur && !Vr) ? kSettledF32 : kSettled;
   if (l <= kJN) {
     hipLaunchKernelGGL(k_jacobi_small, dim3(1), dim3(kJThreads), jacobi_lds_bytes(Lp), stream, R, ldr, l, Lp, w.W, w.sig, w.info,
                        breakdown_flag, kTolBlocks, settled);
     BRSVD_HIP_TRY(hipGetLastError());
-  } else if (l <= kJacobiRowsMaxL) {
-    // Lanes per pair: 16 for l <= 96; above that 8 (fewer, longer instruction streams: the per-pair
-    // rotation arithmetic and reductions are issued half as often; 0.88 against 0.92 ms at l = 110).
-    if (l <= 64) BRSVD_TRY((launch_jacobi_rows<4, 16>(R, ldr, l, Lp, w, breakdown_flag, tol, settled, stream)));
-    else if (l <= 96) BRSVD_TRY((launch_jacobi_rows<6, 16>(R, ldr, l, Lp, w, breakdown_flag, tol, settled, stream)));
-    else if (l <= 112) BRSVD_TRY((launch_jacobi_rows<14, 8>(R, ldr, l, Lp, w, breakdown_flag, tol, settled, stream)));
-    else BRSVD_TRY((launch_jacobi_rows<16, 8>(R, ldr, l, Lp, w, breakdown_flag, tol, settled, stream)));
+  } else if (l <= 5 * kJB && ((l + kJB - 1) / kJB) % 2) {   // three or five blocks
+    const size_t lds = (size_t)l * l * sizeof(double);
+    if (l <= 3 * kJB) hipLaunchKernelGGL(k_jacobi_rows<3>, dim3(1), dim3(64 * LPP), lds, stream, R, ldr, l, Lp, w.W, w.sig, w.info,
+                                          breakdown_flag, kTolRows, settled);
+    else hipLaunchKernelGGL(k_jacobi_rows<5>, dim3(1), dim3(64 * LPP), lds, stream, R, ldr, l, Lp, w.W, w.sig, w.info,
+                            breakdown_flag, kTolRows, settled);
+    BRSVD_HIP_TRY(hipGetLastError());
   } else {
     BRSVD_TRY(jacobi_global(R, ldr, l, Lp, w, breakdown_flag, kTolBlocks, settled, stream));
   }

@@ -1,6 +1,6 @@
 """The l x l factors at the edges of their tiles and of the kernels' ranges: Cholesky factor and inverse behind the
 orthonormalisation (16 x 16 tiles, in LDS up to 128, in global memory above), and the Jacobi SVD (row blocks of 16; one
-workgroup up to 32 rows, row rotations up to 128, block pairs in global memory above)."""
+workgroup up to 32 rows, row rotations for three or five blocks, a workgroup per block pair otherwise)."""
 import numpy as np
 import pytest
 import torch
@@ -10,7 +10,7 @@ from tests.gpu_util import EPS32, need_gpu
 
 pytestmark = pytest.mark.gpu
 
-EDGES = [1, 15, 16, 17, 32, 33, 64, 65, 112, 113, 127, 128, 129, 144, 161, 272, 512]
+EDGES = [1, 15, 16, 17, 32, 33, 48, 49, 64, 65, 80, 81, 96, 97, 112, 127, 128, 129, 144, 161, 272, 512]
 
 
 def _panel(rows, l, decay, seed):
@@ -76,7 +76,7 @@ def test_small_svd(l, cond):
 
 def test_small_svd_of_equal_and_zero_values():
     dev = need_gpu()
-    for l in (16, 30, 40, 160):
+    for l in (16, 30, 40, 100, 160):
         g = torch.Generator().manual_seed(l)
         Q = torch.linalg.qr(torch.randn(l, l, generator=g, dtype=torch.float64))[0]
         S, U, V, _ = B.brsvd_small_svd(Q.to(dev).contiguous())             # all singular values equal
@@ -87,3 +87,26 @@ def test_small_svd_of_equal_and_zero_values():
         ref = torch.linalg.svdvals(R)
         assert float((S - ref).abs().max()) <= 1e-13 * float(ref[0])
         assert bool((B.brsvd_small_svd(torch.zeros(l, l, dtype=torch.float64, device=dev))[0] == 0).all())
+
+
+def test_block_pairs_on_several_streams():
+    """Calls whose workgroups wait for each other, on four streams beside a stream of large products: every call ends and
+    gives what it gives alone."""
+    dev = need_gpu()
+    g = torch.Generator().manual_seed(9)
+    Rs = [torch.linalg.qr(torch.randn(l, l, generator=g, dtype=torch.float64))[1].to(dev).contiguous() for l in (81, 130, 200, 330)]
+    alone = [B.brsvd_small_svd(R)[0].clone() for R in Rs]
+    big = torch.randn(4096, 4096, device=dev)
+    streams = [torch.cuda.Stream() for _ in Rs]
+    busy = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(busy):
+        for _ in range(40):
+            big @ big
+    got = []
+    for R, st in zip(Rs, streams):
+        with torch.cuda.stream(st):
+            got.append(B.brsvd_small_svd(R)[0])
+    torch.cuda.synchronize()
+    for a, b in zip(alone, got):
+        assert bool((a == b).all())
