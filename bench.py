@@ -33,6 +33,9 @@ sys.path.insert(0, ROOT)
 PEAK_HBM_GBS = 8000.0        # MI355X HBM3E
 PEAK_MFMA_F32_TFLOPS = 157.3  # dense fp32 MFMA
 PEAK_MFMA_F64_TFLOPS = 78.6   # dense fp64 MFMA
+# Wide fp32 panels over large A are multiplied on the bf16 matrix cores, six bf16 products of exactly split operands for each
+# fp32 one: a sixth of the dense bf16 peak of 2500 TFLOP/s.
+PEAK_SPLIT_F32_TFLOPS = 2500.0 / 6.0
 C4_ROWS = 160000              # the GPU machine pins at most about 64 GB of host memory: 160000 of the 200000 rows
 
 # HBM bytes per launch of the pass kernels from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this script, each
@@ -108,7 +111,8 @@ def run_in_core(B, torch, cfg, steps, warmup, fused=False, f64=False, copy_calib
     sec = (t1 - t0) / steps
     passes = acc["passes_over_A"] // steps
     bytes_a = float(acc["bytes_A_streamed"]) / steps
-    peak_mfma = PEAK_MFMA_F64_TFLOPS if f64 else PEAK_MFMA_F32_TFLOPS
+    split = not f64 and l > 32 and m * n >= 1 << 22
+    peak_mfma = PEAK_MFMA_F64_TFLOPS if f64 else PEAK_SPLIT_F32_TFLOPS if split else PEAK_MFMA_F32_TFLOPS
     kern = {"gemm_an": kernel_figures(m, n, l, esz, acc["gemm_an_seconds"], acc["gemm_an_launches"], peak_mfma),
             "gemm_at": kernel_figures(m, n, l, esz, acc["gemm_at_seconds"], acc["gemm_at_launches"], peak_mfma)}
     kname = "gemm_an" if acc["gemm_an_seconds"] >= acc["gemm_at_seconds"] else "gemm_at"

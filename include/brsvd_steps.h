@@ -68,8 +68,9 @@ uint64_t brsvd_small_svd_scratch_bytes(int32_t l);
 int brsvd_small_svd_static(const double* R, int32_t l, double* S, double* Ur, double* Vr,
                            int32_t* sweeps, void* stream);
 
-/* How the two thin products would be cut into workgroups (host-only, no GPU call): for checking the
- * plans' invariants and for reading profiles.  which = 0: Y = A X with A rows x n, out12 = {rows per
+/* How the plain kernels of the two thin products would cut them into workgroups (host-only, no GPU call): for checking the
+ * plans' invariants and for reading profiles.  Wide fp32 panels over large A take other kernels with plans of their own
+ * (csrc/gemm_split.hip) when the scratch allows it.  which = 0: Y = A X with A rows x n, out12 = {rows per
  * tile, row tiles, chunks per tile C, whole tiles, leftover tiles, main splits f, tail chunks x, tail
  * strips per workgroup j, partial panels per leftover tile, workgroups, column groups, column tiles per
  * group}.  which = 1: Z += A^T Q, out12 = {m-tiles per wave, waves, column tiles, row blocks,
