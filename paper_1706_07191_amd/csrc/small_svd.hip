@@ -280,11 +280,11 @@ k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __re
 //   otherwise: one workgroup per block pair, rows in global memory, one launch (k_jacobi_rounds);
 //   but with three or five blocks, where a padding block goes round with the others, row rotations stay ahead (us, this against row
 //   rotations: l = 33 367 / 236, 48 354 / 296, 72 654 / 567; on the other side 60 407 / 414 (27 of 2526 less in a
-//   whole decomposition with single-precision results), 64 368 / 431, 96 659 / 824, 110 893 / 1064, 128 906 / 1458).
+//   whole decomposition with single-precision results), 64 368 / 431, 96 673 / 824, 110 918 / 1064, 128 938 / 1458).
 // What bounds it: the latency of a step, 800 to 900 cycles from barrier to barrier, half of it the rotation; the matrix products
 // take 5 to 9 thousand cycles of a round beside the 14 thousand of the steps (l = 160, 272).  Measured (us per call of the small
-// SVD, row rotations before and this): l = 20 143 -> 134, 30 181 -> 151, 110 1064 -> 893, 160 2867 -> 1405, 272 6140 -> 3660,
-// 512 13900 -> 8890.  Two
+// SVD, row rotations before and this): l = 20 143 -> 134, 30 181 -> 151, 110 1064 -> 918, 160 2867 -> 1440, 272 6140 -> 3690,
+// 512 13900 -> 9110.  Two
 // accumulator chains per product: four gain 2 % at l <= 32 and lose 6 % above 128.
 constexpr int kJB = 16;
 constexpr int kJN = 2 * kJB;                      // rows of a block pair
@@ -565,7 +565,7 @@ __device__ __forceinline__ void load_pair(const double* W, int l, int Lp, int rI
 
 // All sweeps in one launch: nblk2 / 2 workgroups rotate one pair of blocks each, meet, and go on with the pairs of the next round.
 // The rows travel through global memory between rounds; they are stored at the scope of the device, past the L2 of an XCD, which
-// leaves the release at a meeting little to write back (4 % of the whole).  With a launch per round, and the host looking at the
+// leaves the releases at a meeting little to write back (2 to 4 % of the whole).  With a launch per round, and the host looking at the
 // convergence flag, l = 160 took 1980 us and 272 4280 us.  Eight times the workgroups with all but every eighth leaving at
 // once, to keep the rest on one XCD, gains 5 % below 128 and loses up to 13 % above.
 __global__ void __launch_bounds__(kJThreads)
@@ -579,11 +579,13 @@ k_jacobi_rounds(double* W, int l, int Lp, int nblk2, double tol, double settled,
   int arrivals = 0, sweeps = 0, rI = 0, rJ = 0;
   bool converged = false;
   // Waits for every workgroup, and makes what each wrote before visible to all; false: given up.
+  // Each wave releases what it wrote itself before the barrier: the barrier does not wait for stores that are under way, and a
+  // release by one wave waits for that wave's stores only.
   auto meet = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __syncthreads();
     if (t == 0) {
       arrivals += gridDim.x;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
       __hip_atomic_fetch_add(info + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       bool all = true;
       const unsigned long long start = wall_clock64();
@@ -595,10 +597,10 @@ k_jacobi_rounds(double* W, int l, int Lp, int nblk2, double tol, double settled,
         }
         __builtin_amdgcn_s_sleep(1);
       }
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
       state = all ? __hip_atomic_load(info + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -1;
     }
     __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     return state >= 0;
   };
   while (!converged && sweeps < kMaxSweeps) {

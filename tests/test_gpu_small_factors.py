@@ -110,3 +110,20 @@ def test_block_pairs_on_several_streams():
     torch.cuda.synchronize()
     for a, b in zip(alone, got):
         assert bool((a == b).all())
+
+
+@pytest.mark.parametrize("l", [49, 81, 112, 134, 161, 257, 512])
+def test_workgroups_see_each_others_rows(l):
+    """The rows travel between workgroups through global memory: a fixed order of operations, so every call gives the same
+    bits and a row read too early shows at once.  Full rank and rank l - 10 (rows of rounding noise)."""
+    dev = need_gpu()
+    g = torch.Generator().manual_seed(l)
+    A = torch.randn(2 * l, l, generator=g, dtype=torch.float64)
+    B10 = torch.randn(2 * l, l - 10, generator=g, dtype=torch.float64) @ torch.randn(l - 10, l, generator=g, dtype=torch.float64)
+    for M in (A, B10):
+        R = torch.linalg.qr(M)[1].to(dev).contiguous()
+        first = [x.clone() for x in B.brsvd_small_svd(R)[:3]]
+        assert float(((first[1] * first[0]) @ first[2].T - R).abs().max()) <= 1e-12 * float(first[0][0])
+        for _ in range(60):
+            again = B.brsvd_small_svd(R)
+            assert all(bool(torch.equal(a.nan_to_num(), b.nan_to_num())) for a, b in zip(first, again))
