@@ -966,6 +966,10 @@ static int gemm_an_t(const T* A, int64_t lda, int64_t rows, int64_t K, const T* 
     int c0 = gi * ng.nt * 16;
     int nt = (Lp - c0) / 16 < ng.nt ? (Lp - c0) / 16 : ng.nt;
     if (nt <= 0) break;
+    // The plan is one for all groups: where a narrower last group would take an instance with another tile of rows (9 or 25
+    // tiles in fp64, 29 in fp32), it starts earlier instead and computes a few columns again, to the same values.
+    const bool one_row_tile = (esz == 8 && nt >= 5) || nt > 14, plan_one = (esz == 8 && ng.nt >= 5) || ng.nt > 14;
+    if (one_row_tile != plan_one) { nt = ng.nt; c0 = Lp - nt * 16; }
     int nc = ncols - c0 < nt * 16 ? ncols - c0 : nt * 16;   // valid output columns in this group (may be <= 0)
     BRSVD_TRY(launch_an<T>(nt, A, lda, (int)rows, (int)K, X + c0, Lp, Y + c0, ldy, nc, part ? part + c0 : nullptr,
                            Lp, prows * Lp, p, stream));

@@ -218,3 +218,18 @@ def test_f64_norm2_power_matches_oracle():
             assert abs(got - want) <= 1e-12 * want
     finally:
         B.brsvd_destroy(h)
+
+
+@pytest.mark.parametrize("l,f64", [(134, True), (395, True), (460, False)])
+def test_gemm_an_when_the_last_column_group_is_narrower(l, f64):
+    """Column groups of unequal width share one plan of row tiles: leftover tiles included, every row is right."""
+    dev = need_gpu()
+    dt = torch.float64 if f64 else torch.float32
+    g = torch.Generator().manual_seed(l)
+    for rows, K in ((20011, 100), (4000, 700)):
+        A = torch.randn(rows, K, generator=g, dtype=torch.float64).to(dt)
+        X = torch.randn(K, l, generator=g, dtype=torch.float64).to(dt)
+        Y = B.brsvd_gemm_an(A.to(dev), X.to(dev)).double().cpu()
+        eps = 2.0 ** -52 if f64 else 2.0 ** -23
+        bound = 8 * np.sqrt(K) * eps * (A.double().abs() @ X.double().abs())
+        assert bool(((Y - A.double() @ X.double()).abs() <= bound).all())
