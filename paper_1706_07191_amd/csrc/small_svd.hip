@@ -91,6 +91,13 @@ __device__ __forceinline__ double row16_sum(double v) {
   return v;
 }
 
+// Whether row j comes before row i in the descending order of their norms: NaN first, equal ones by index, so that the ranks are a
+// permutation whatever the norms are.
+__device__ __forceinline__ bool ranks_before(double sj, int j, double si, int i) {
+  if (sj != sj || si != si) return sj != sj && (si == si || j < i);
+  return sj > si || (sj == si && j < i);
+}
+
 // Singular values (row norms), their descending order, and the final rows, written to global.
 template <int NTHREADS>
 __device__ void publish(const double* W, int ld, int l, int Lp, double* Wg, double* sig, int* order_sh,
@@ -101,15 +108,11 @@ __device__ void publish(const double* W, int ld, int l, int Lp, double* Wg, doub
     s2 = wave_sum(s2);
     if (lane == 0) sig[Lp + i] = sqrt(s2);
   }
-  for (int i = tid; i < l; i += NTHREADS) order_sh[i] = 0;
   __syncthreads();
   for (int i = tid; i < l; i += NTHREADS) {
     const double si = sig[Lp + i];
     int rank = 0;
-    for (int j = 0; j < l; ++j) {
-      const double sj = sig[Lp + j];
-      rank += (sj > si) || (sj == si && j < i);
-    }
+    for (int j = 0; j < l; ++j) rank += ranks_before(sig[Lp + j], j, si, i);
     order_sh[rank] = i;
   }
   __syncthreads();
@@ -274,6 +277,8 @@ k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __re
 // per thread, the rotation, and a write.  The Gram matrix is formed afresh from the rows for every pair of blocks, so
 // what the two-sided updates lose never accumulates; singular values keep the relative accuracy of plain row rotations
 // (simulated at condition 1e6, 1e10, 1e14: 8e-15, 9e-15, 8e-13, plain rotations 9e-15, 1.3e-14, 8e-13).
+// A row whose squared norm is not finite is set aside: it is zero while the others are rotated (one of its products with them would make
+// the whole block NaN) and comes back at the end with its own norm, as when rows are rotated, where no comparison with it holds.
 // A sweep is a round robin over the block pairs.  Its first round rotates all 496 pairs of the 32 rows (31 steps of
 // 16 disjoint pairs), the others the 256 pairs across the two blocks (16 steps).
 //   l <= 32: one block pair, rows in LDS for all sweeps (k_jacobi_small);
@@ -503,8 +508,17 @@ k_jacobi_small(const double* __restrict__ R, int ldr, int l, int Lp, double* __r
     if (t == 0) { info[0] = 0; info[1] = 0; }
     return;
   }
-  for (int i = t >> 5; i < kJN; i += kJThreads / 32)
-    for (int c = t & 31; c < Lp; c += 32) W[i * ld + c] = i < l && c < l ? R[(int64_t)i * ldr + c] : 0.0;
+  unsigned aside = 0;                                  // bit q: row (t >> 5) + q (kJThreads / 32) is set aside
+#pragma unroll
+  for (int q = 0; q < kJN / (kJThreads / 32); ++q) {
+    const int i = (t >> 5) + q * (kJThreads / 32), c = t & 31;      // Lp <= 32: a lane has one entry of a row
+    double v = i < l && c < l ? R[(int64_t)i * ldr + c] : 0.0;
+    double s2 = v * v;
+#pragma unroll
+    for (int off = 16; off > 0; off >>= 1) s2 += __shfl_xor(s2, off, 32);
+    if (!isfinite(s2)) { aside |= 1u << q; v = 0.0; }
+    if (c < Lp) W[i * ld + c] = v;
+  }
   double* work = W + kJN * ld;
   int sweeps = 0, converged = (l < 2);
   auto row = [&](int x) { return W + x * ld; };
@@ -520,6 +534,12 @@ k_jacobi_small(const double* __restrict__ R, int ldr, int l, int Lp, double* __r
     converged = rotated == 0;
     __syncthreads();
   }
+#pragma unroll
+  for (int q = 0; q < kJN / (kJThreads / 32); ++q) {
+    const int i = (t >> 5) + q * (kJThreads / 32), c = t & 31;
+    if ((aside >> q & 1) && i < l && c < l) W[i * ld + c] = R[(int64_t)i * ldr + c];
+  }
+  __syncthreads();
   publish<kJThreads>(W, ld, l, Lp, Wg, sig, order_sh, t, t & 63, t >> 6);
   if (t == 0) { info[0] = sweeps; info[1] = converged; }
 }
@@ -527,11 +547,31 @@ k_jacobi_small(const double* __restrict__ R, int ldr, int l, int Lp, double* __r
 // ---- more than 32 rows: one workgroup per pair of blocks ---------------------------------------------------------------
 // info: [0] sweeps done, [1] converged, [2] arrivals, [3] last sweep (from 1) with a rotation above the bar, [4] nothing to do,
 // [5] a workgroup has given up waiting.
-__global__ void k_jacobi_init(const double* __restrict__ R, int ldr, int l, int Lp, double* __restrict__ W,
-                              int* __restrict__ info, const int* __restrict__ breakdown_flag) {
+// One workgroup of 128 threads per row; sig[Lp + i]: the squared norm of a row that is set aside, otherwise 0.
+__global__ void __launch_bounds__(128)
+k_jacobi_init(const double* __restrict__ R, int ldr, int l, int Lp, double* __restrict__ W, double* __restrict__ sig,
+              int* __restrict__ info, const int* __restrict__ breakdown_flag) {
+  __shared__ double part[2];
   const int c = threadIdx.x, i = blockIdx.x;
   if (i == 0 && c < 6) info[c] = c == 4 && breakdown_flag && breakdown_flag[0] != 0;
-  for (int cc = c; cc < Lp; cc += blockDim.x) W[(int64_t)i * Lp + cc] = i < l && cc < l ? R[(int64_t)i * ldr + cc] : 0.0;
+  double v[kMaxL / 128], s2 = 0.0;
+#pragma unroll
+  for (int q = 0; q < kMaxL / 128; ++q) {
+    const int cc = c + 128 * q;
+    v[q] = i < l && cc < l ? R[(int64_t)i * ldr + cc] : 0.0;
+    s2 = fma(v[q], v[q], s2);
+  }
+  s2 = wave_sum(s2);
+  if ((c & 63) == 0) part[c >> 6] = s2;
+  __syncthreads();
+  s2 = part[0] + part[1];
+  const bool aside = !isfinite(s2);
+  if (c == 0) sig[Lp + i] = aside ? s2 : 0.0;
+#pragma unroll
+  for (int q = 0; q < kMaxL / 128; ++q) {
+    const int cc = c + 128 * q;
+    if (cc < Lp) W[(int64_t)i * Lp + cc] = aside ? 0.0 : v[q];
+  }
 }
 
 // Ticks of the 100 MHz clock after which a workgroup stops waiting for the others.  They are all resident unless the GPU is
@@ -569,7 +609,7 @@ __device__ __forceinline__ void load_pair(const double* W, int l, int Lp, int rI
 // convergence flag, l = 160 took 1980 us and 272 4280 us.  Eight times the workgroups with all but every eighth leaving at
 // once, to keep the rest on one XCD, gains 5 % below 128 and loses up to 13 % above.
 __global__ void __launch_bounds__(kJThreads)
-k_jacobi_rounds(double* W, int l, int Lp, int nblk2, double tol, double settled, double* sig, int* info) {
+k_jacobi_rounds(const double* R, int ldr, double* W, int l, int Lp, int nblk2, double tol, double settled, double* sig, int* info) {
   extern __shared__ __align__(16) double sh[];
   __shared__ int state;
   const int t = threadIdx.x, ld = Lp + 2;
@@ -632,17 +672,20 @@ k_jacobi_rounds(double* W, int l, int Lp, int nblk2, double tol, double settled,
   // norms of the rows of this workgroup's last pair, eight lanes a row; then their place in the descending order
   const int x = t >> 3, e0 = t & 7, i = x < kJB ? rI + x : rJ + x - kJB;
   double s2 = 0.0;
+  const double left = i < l ? sig[Lp + i] : 0.0;        // not zero: a row that was set aside
   if (i < l)
-    for (int e = e0; e < l; e += 8) { const double v = W[(int64_t)i * Lp + e]; s2 = fma(v, v, s2); }
-  const double si = sqrt(row8_sum(s2));
+    for (int e = e0; e < l; e += 8) {
+      if (left != 0.0) W[(int64_t)i * Lp + e] = R[(int64_t)i * ldr + e];
+      const double v = W[(int64_t)i * Lp + e];
+      s2 = fma(v, v, s2);
+    }
+  s2 = row8_sum(s2);
+  const double si = sqrt(left != 0.0 ? left : s2);
   if (i < l && e0 == 0) sig[Lp + i] = si;
   if (!meet()) return;
   if (i < l) {
     int rank = 0;
-    for (int j = e0; j < l; j += 8) {
-      const double sj = sig[Lp + j];
-      rank += (sj > si) || (sj == si && j < i);
-    }
+    for (int j = e0; j < l; j += 8) rank += ranks_before(sig[Lp + j], j, si, i);
     for (int off = 4; off > 0; off >>= 1) rank += __shfl_xor(rank, off, 8);
     if (e0 == 0) { sig[rank] = si; sig[2 * Lp + rank] = (double)i; }
   }
@@ -695,10 +738,10 @@ static int jacobi_global(const double* R, int ldr, int l, int Lp, SvdWork& w, co
                                       (int)jacobi_lds_bytes(kMaxL)));
     attr_set = true;
   }
-  hipLaunchKernelGGL(k_jacobi_init, dim3(Lp), dim3(128), 0, stream, R, ldr, l, Lp, w.W, w.info, breakdown_flag);
+  hipLaunchKernelGGL(k_jacobi_init, dim3(Lp), dim3(128), 0, stream, R, ldr, l, Lp, w.W, w.sig, w.info, breakdown_flag);
   const int nblk = (int)ceil_div(l, kJB), nblk2 = (nblk + 1) & ~1;
-  hipLaunchKernelGGL(k_jacobi_rounds, dim3(nblk2 / 2), dim3(kJThreads), jacobi_lds_bytes(Lp), stream, w.W, l, Lp, nblk2, tol,
-                     settled, w.sig, w.info);
+  hipLaunchKernelGGL(k_jacobi_rounds, dim3(nblk2 / 2), dim3(kJThreads), jacobi_lds_bytes(Lp), stream, R, ldr, w.W, l, Lp, nblk2,
+                     tol, settled, w.sig, w.info);
   BRSVD_HIP_TRY(hipGetLastError());
   return BRSVD_OK;
 }

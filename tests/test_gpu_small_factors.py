@@ -89,6 +89,28 @@ def test_small_svd_of_equal_and_zero_values():
         assert bool((B.brsvd_small_svd(torch.zeros(l, l, dtype=torch.float64, device=dev))[0] == 0).all())
 
 
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), float("-inf"), 1e160])
+@pytest.mark.parametrize("l", [30, 40, 60, 110, 160])
+def test_small_svd_with_a_row_that_is_not_finite(l, bad):
+    """The row keeps its own norm (infinite, or NaN before all others) and the other rows are orthogonalised as if it were not
+    there; nothing an earlier call left in the scratch comes out."""
+    dev = need_gpu()
+    g = torch.Generator().manual_seed(l)
+    R = torch.linalg.qr(torch.randn(2 * l, l, generator=g, dtype=torch.float64))[1].contiguous()
+    for static in (False, True):
+        before = B.brsvd_small_svd(R.to(dev), static=static)[0].cpu()
+        Rb = R.clone()
+        Rb[3, 7] = bad
+        S, U, V, _ = (x.cpu() if isinstance(x, torch.Tensor) else x for x in B.brsvd_small_svd(Rb.to(dev), static=static))
+        assert bool(S[0].isnan()) if bad != bad else float(S[0]) == float("inf")
+        ref = torch.linalg.svdvals(torch.cat((R[:3], R[4:])))
+        assert float((S[1:] - ref).abs().max()) <= 1e-12 * float(ref[0])
+        eye = torch.eye(l - 1, dtype=torch.float64)
+        assert float((V[:, 1:].T @ V[:, 1:] - eye).abs().max()) <= 4e-13
+        again = B.brsvd_small_svd(R.to(dev), static=static)[0].cpu()
+        assert torch.equal(before, again)
+
+
 def test_block_pairs_on_several_streams():
     """Calls whose workgroups wait for each other, on four streams beside a stream of large products: every call ends and
     gives what it gives alone."""
