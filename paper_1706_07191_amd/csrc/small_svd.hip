@@ -304,8 +304,9 @@ __device__ __forceinline__ doublex4 mfma_f64(double a, double b, doublex4 c) {
 }
 
 // Rotation (c, s) that makes two rows with squared norms al, be and inner product ga orthogonal: tan of the smaller
-// angle, t = 2 ga / (tau +- sqrt(tau^2 + 4 ga^2)), tau = be - al.  t itself is worked out in single precision: that only
-// leaves 1e-7 of the inner product, while c and s, which have to be orthogonal, follow from it in double.
+// angle, t = 2 ga / (tau +- sqrt(tau^2 + 4 ga^2)), tau = be - al.  The denominator is worked out in single precision: that only
+// leaves 1e-7 of the inner product, while c and s, which have to be orthogonal, follow from t in double.  The numerator stays
+// in double: rows whose norms are more than 2^126 apart need a t below the single-precision range.
 // Identity when |ga| <= tol * sqrt(al * be); big: above the settled bar.  Returns t.
 __device__ __forceinline__ double rotation(double al, double be, double ga, double tol2, double settled2, double& c,
                                            double& s, bool& big) {
@@ -314,12 +315,13 @@ __device__ __forceinline__ double rotation(double al, double be, double ga, doub
   const bool rot = gg > tol2 * ab;
   const double tau = be - al, g2 = 2.0 * ga;
   const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(tau), fabs(g2)));
-  const float tf = (float)__builtin_amdgcn_ldexp(tau, ex), gf = (float)__builtin_amdgcn_ldexp(g2, ex);
-  const float den = fabsf(tf) + __builtin_amdgcn_sqrtf(fmaf(tf, tf, gf * gf));
-  const float t32 = copysignf(gf, gf * tf >= 0.f ? 1.f : -1.f) * __builtin_amdgcn_rcpf(den);
+  const double gd = __builtin_amdgcn_ldexp(g2, ex);
+  const float tf = (float)__builtin_amdgcn_ldexp(tau, ex), gf = (float)gd;
+  const float inv = copysignf(__builtin_amdgcn_rcpf(fabsf(tf) + __builtin_amdgcn_sqrtf(fmaf(tf, tf, gf * gf))), tf);
   // c = 1 / sqrt(1 + t^2) from a single-precision seed by one step of third order (2^-22 -> below 2^-64)
-  const float ts = rot ? t32 : 0.f;
-  const double t = (double)ts, x = fma(t, t, 1.0), y = (double)__builtin_amdgcn_rsqf(fmaf(ts, ts, 1.f));
+  const double t = rot ? gd * (double)inv : 0.0;
+  const float ts = rot ? gf * inv : 0.f;
+  const double x = fma(t, t, 1.0), y = (double)__builtin_amdgcn_rsqf(fmaf(ts, ts, 1.f));
   const double e = fma(-x * y, y, 1.0);
   c = fma(y, e * fma(e, 0.375, 0.5), y);
   s = c * t;

@@ -74,6 +74,49 @@ def test_small_svd(l, cond):
     assert float(((U * S) @ V.T - R).abs().max()) <= 1e-12
 
 
+def _singular_values_long(R):
+    """One-sided Jacobi on the rows in 80-bit arithmetic."""
+    W, l = R.numpy().astype(np.longdouble), R.shape[0]
+    n = l + l % 2
+    W = np.vstack((W, np.zeros((n - l, l), np.longdouble)))
+    for _ in range(30):
+        worst = 0.0
+        for step in range(n - 1):
+            i = np.arange(1, n // 2)
+            a, b = np.r_[n - 1, (step + i) % (n - 1)], np.r_[step, (step - i) % (n - 1)]
+            x, y = W[a], W[b]
+            al, be, ga = (x * x).sum(1), (y * y).sum(1), (x * y).sum(1)
+            on = ga * ga > np.longdouble(1e-36) * al * be
+            ga, tau = np.where(on, ga, 1), np.where(on, be - al, 0)
+            worst = max(worst, float(np.max(np.where(on, ga * ga / np.where(on, al * be, 1), 0))))
+            t = np.where(on, 2 * ga / (np.abs(tau) + np.hypot(tau, 2 * ga)) * np.where(tau < 0, -1, 1), 0)
+            c = 1 / np.sqrt(1 + t * t)
+            W[a], W[b] = c[:, None] * x - (c * t)[:, None] * y, (c * t)[:, None] * x + c[:, None] * y
+        if worst < 1e-18:
+            break
+    return np.sort(np.sqrt((W * W).sum(1)))[::-1][:l]
+
+
+@pytest.mark.parametrize("l", [20, 40, 60, 110, 272])
+@pytest.mark.parametrize("decades", [12, 30, 60])
+def test_small_svd_of_graded_rows(l, decades):
+    """Rows that shrink by many decades, times a well-conditioned matrix: rotations leave every singular value, also the smallest,
+    its own relative accuracy."""
+    dev = need_gpu()
+    print(f"[case] graded l={l} decades={decades}", flush=True)
+    g = torch.Generator().manual_seed(l + decades)
+    Bm = torch.eye(l, dtype=torch.float64) + 0.3 * torch.randn(l, l, generator=g, dtype=torch.float64) / np.sqrt(l)
+    R = torch.logspace(0, -decades, l, dtype=torch.float64)[:, None] * Bm
+    S, U, V, sweeps = (x.cpu() if isinstance(x, torch.Tensor) else x for x in B.brsvd_small_svd(R.to(dev).contiguous()))
+    ref = _singular_values_long(R)
+    rel = float(np.max(np.abs(S.numpy().astype(np.longdouble) - ref) / ref))
+    print(f"[case] sweeps={sweeps} rel={rel:.2e}", flush=True)
+    # about l rotations a sweep touch a row, each with a rounding of eps of the row it changes; as a random walk, times the
+    # condition of the matrix with its rows scaled to one (4 here)
+    assert rel <= 4 * 2.0 ** -52 * np.sqrt(l * sweeps) * 4
+    assert float((V.T @ V - torch.eye(l, dtype=torch.float64)).abs().max()) <= 4e-13
+
+
 def test_small_svd_of_equal_and_zero_values():
     dev = need_gpu()
     for l in (16, 30, 40, 100, 160):
