@@ -511,15 +511,21 @@ k_jacobi_small(const double* __restrict__ R, int ldr, int l, int Lp, double* __r
     if (t == 0) { info[0] = 0; info[1] = 0; }
     return;
   }
+  constexpr int XN = kJN / (kJThreads / 32);
   unsigned aside = 0;                                  // bit q: row (t >> 5) + q (kJThreads / 32) is set aside
+  double first[XN];
 #pragma unroll
-  for (int q = 0; q < kJN / (kJThreads / 32); ++q) {
+  for (int q = 0; q < XN; ++q) {
     const int i = (t >> 5) + q * (kJThreads / 32), c = t & 31;      // Lp <= 32: a lane has one entry of a row
-    double v = i < l && c < l ? R[(int64_t)i * ldr + c] : 0.0;
-    double s2 = v * v;
+    first[q] = R[(int64_t)min(i, l - 1) * ldr + min(c, l - 1)];
+    if (i >= l || c >= l) first[q] = 0.0;
+  }
 #pragma unroll
-    for (int off = 16; off > 0; off >>= 1) s2 += __shfl_xor(s2, off, 32);
-    if (!isfinite(s2)) { aside |= 1u << q; v = 0.0; }
+  for (int q = 0; q < XN; ++q) {
+    const int i = (t >> 5) + q * (kJThreads / 32), c = t & 31;
+    double v = first[q];
+    // (an entry whose square is near the largest double: nothing rotates against such a row)
+    if ((unsigned)(__ballot(!(fabs(v) < 0x1p509)) >> (t & 32))) { aside |= 1u << q; v = 0.0; }
     if (c < Lp) W[i * ld + c] = v;
   }
   double* work = W + kJN * ld;
