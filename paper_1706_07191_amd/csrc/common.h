@@ -194,8 +194,25 @@ int diag_ratio(const double* R, int l, int Lp, double* out, hipStream_t stream);
 struct SvdWork {
   double* W;     // Lp x Lp rows being orthogonalised
   double* sig;   // 3 * Lp
-  int* info;     // device, six: [0] sweeps, [1] converged, the others for the iteration itself
+  int* info;     // device, eight: [0] sweeps, [1] converged, the others for the iteration itself
 };
+// The work of the block Jacobi iteration in the order in which its workgroups take it: a ticket is one of the P = nblk2 / 2 block
+// pairs of one of the nblk2 - 1 rounds of a sweep (from 0).  Its turn comes once all tickets of the rounds before are done.
+struct JacobiTicket {
+  int sweep, round, pair, before;    // before: tickets of the earlier rounds
+};
+__host__ __device__ inline JacobiTicket jacobi_ticket(int ticket, int nblk2) {
+  const int P = nblk2 / 2, r = ticket / P;
+  return JacobiTicket{r / (nblk2 - 1), r % (nblk2 - 1), ticket - r * P, r * P};
+}
+// What a ticket is, when its turn has come and `last` is the latest sweep (from 1) that turned a pair above the settled bar: that sweep
+// is not the one before, or there have been enough: no more rotations, and the tickets that would have been the next two rounds
+// work out the norms and the ranks.
+enum { JACOBI_ROTATE = 0, JACOBI_NORMS, JACOBI_RANKS, JACOBI_END };
+__host__ __device__ inline int jacobi_work(const JacobiTicket& k, int last, int max_sweeps) {
+  if (k.sweep == 0 || (last >= k.sweep && k.sweep < max_sweeps)) return JACOBI_ROTATE;
+  return k.round == 0 ? JACOBI_NORMS : (k.round == 1 ? JACOBI_RANKS : JACOBI_END);
+}
 // R (l x l fp64, stride ldr): R = Ur diag(S) Vr^T.  Writes S (descending) as fp64 and/or in the
 // panels' type TO, the zero-padded (Lp x Lp) operands XV = Vr and XU = Ur used by the lifts (type TO),
 // and optional dense fp64 l x l Ur / Vr.  Skips the work when *breakdown_flag != 0.

@@ -172,6 +172,50 @@ int main() {
     }
   }
 
+  // ---- tickets of the block Jacobi iteration: with any number of resident workgroups, in any order of their steps, every pair of
+  // blocks is rotated once per sweep, no round starts before the one before has ended, and all workgroups come to an end ----
+  for (int it = 0; it < 600; ++it) {
+    const int nblk2 = 2 * (int)uniform(2, 16), P = nblk2 / 2, rounds = nblk2 - 1, max_sweeps = 5;
+    const int sweeps = (int)uniform(1, max_sweeps), resident = (int)uniform(1, P);
+    const bool settles = sweeps < max_sweeps || uniform(0, 1) == 1;
+    struct Group { int ticket, stage; };                 // stage 0: no ticket, 1: waits, 2: at work, 3: left
+    std::vector<Group> wg(P, Group{0, 0});
+    std::vector<int> turned(max_sweeps * rounds * P, 0), ended(4, 0);
+    int taken = 0, done = 0, last = 0, left = 0;
+    bool stuck = false;
+    // the workgroups from `resident` on only start when one before them has left
+    while (left < P && !stuck) {
+      std::vector<int> ready;
+      for (int g = 0; g < P && g < resident + left; ++g) {
+        if (wg[g].stage == 1 && done < brsvd::jacobi_ticket(wg[g].ticket, nblk2).before) continue;
+        if (wg[g].stage != 3) ready.push_back(g);
+      }
+      if (ready.empty()) { stuck = true; break; }
+      Group& g = wg[ready[uniform(0, (int)ready.size() - 1)]];
+      const brsvd::JacobiTicket k = brsvd::jacobi_ticket(g.ticket, nblk2);
+      if (g.stage == 0) {
+        g = Group{taken++, 1};
+      } else if (g.stage == 1) {
+        const int what = brsvd::jacobi_work(k, last, max_sweeps);
+        ++ended[what];
+        g.stage = what == brsvd::JACOBI_END ? 3 : 2;
+        left += g.stage == 3;
+        if (what == brsvd::JACOBI_ROTATE) {
+          CHECK(k.sweep < sweeps && done >= (k.sweep * rounds + k.round) * P && done < (k.sweep * rounds + k.round + 1) * P);
+          ++turned[(k.sweep * rounds + k.round) * P + k.pair];
+          if ((k.sweep + 1 < sweeps || !settles) && k.pair == P - 1 && k.round == (k.sweep % rounds)) last = k.sweep + 1;
+        } else if (what == brsvd::JACOBI_RANKS) {
+          CHECK(ended[brsvd::JACOBI_NORMS] == P && k.sweep == sweeps && (last < k.sweep) == settles);
+        }
+      } else {
+        ++done;
+        g.stage = 0;
+      }
+    }
+    CHECK(!stuck && left == P && ended[brsvd::JACOBI_RANKS] == P);
+    for (int x = 0; x < sweeps * rounds * P; ++x) CHECK(turned[x] == 1);
+  }
+
   // ---- step calls: scratch that is missing, misaligned or too short is refused before any device call ----
   {
     void* one = (void*)0x100;

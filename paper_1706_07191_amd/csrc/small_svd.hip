@@ -554,15 +554,15 @@ k_jacobi_small(const double* __restrict__ R, int ldr, int l, int Lp, double* __r
 }
 
 // ---- more than 32 rows: one workgroup per pair of blocks ---------------------------------------------------------------
-// info: [0] sweeps done, [1] converged, [2] arrivals, [3] last sweep (from 1) with a rotation above the bar, [4] nothing to do,
-// [5] a workgroup has given up waiting.
+// info: [0] sweeps done, [1] converged, [2] tickets done, [3] last sweep (from 1) with a rotation above the bar, [4] nothing to do,
+// [5] a workgroup has given up waiting, [6] tickets taken.
 // One workgroup of 128 threads per row; sig[Lp + i]: the squared norm of a row that is set aside, otherwise 0.
 __global__ void __launch_bounds__(128)
 k_jacobi_init(const double* __restrict__ R, int ldr, int l, int Lp, double* __restrict__ W, double* __restrict__ sig,
               int* __restrict__ info, const int* __restrict__ breakdown_flag) {
   __shared__ double part[2];
   const int c = threadIdx.x, i = blockIdx.x;
-  if (i == 0 && c < 6) info[c] = c == 4 && breakdown_flag && breakdown_flag[0] != 0;
+  if (i == 0 && c < 8) info[c] = c == 4 && breakdown_flag && breakdown_flag[0] != 0;
   double v[kMaxL / 128], s2 = 0.0;
 #pragma unroll
   for (int q = 0; q < kMaxL / 128; ++q) {
@@ -583,9 +583,9 @@ k_jacobi_init(const double* __restrict__ R, int ldr, int l, int Lp, double* __re
   }
 }
 
-// Ticks of the 100 MHz clock after which a workgroup stops waiting for the others.  They are all resident unless the GPU is
-// filled by other work, and start as that work ends; the limit only makes sure that every wait ends (the call then reports
-// that the iteration did not converge).
+// Ticks of the 100 MHz clock after which a workgroup stops waiting for the others (20 s).  Those it waits for are running (see
+// k_jacobi_rounds) and need some 30 us; the limit only makes sure that every wait ends (the call then reports that the
+// iteration did not converge).
 constexpr unsigned long long kMeetTicks = 2000000000ull;
 
 // The 32 rows of the block pair at rows rI and rJ of W, to LDS; rows from l on are zero.  64 H columns at a time are under way.
@@ -612,7 +612,10 @@ __device__ __forceinline__ void load_pair(const double* W, int l, int Lp, int rI
   }
 }
 
-// All sweeps in one launch: nblk2 / 2 workgroups rotate one pair of blocks each, meet, and go on with the pairs of the next round.
+// All sweeps in one launch.  The workgroups (nblk2 / 2 of them; any number will do) take tickets in order, one after the other, and
+// start on one when all tickets of the rounds before are done.  A workgroup therefore only waits for lower tickets, which
+// others have taken that are running, and the lowest of these waits for nothing: the iteration goes on however few of the
+// workgroups find room on the device, on a stream with a few CUs or beside kernels that fill the rest.
 // The rows travel through global memory between rounds; they are stored at the scope of the device, past the L2 of an XCD, which
 // leaves the releases at a meeting little to write back (2 to 4 % of the whole).  With a launch per round, and the host looking at the
 // convergence flag, l = 160 took 1980 us and 272 4280 us.  Eight times the workgroups with all but every eighth leaving at
@@ -620,85 +623,82 @@ __device__ __forceinline__ void load_pair(const double* W, int l, int Lp, int rI
 __global__ void __launch_bounds__(kJThreads)
 k_jacobi_rounds(const double* R, int ldr, double* W, int l, int Lp, int nblk2, double tol, double settled, double* sig, int* info) {
   extern __shared__ __align__(16) double sh[];
-  __shared__ int state;
+  __shared__ int next, state;
   const int t = threadIdx.x, ld = Lp + 2;
   if (info[4]) return;
   double* work = sh + kJN * ld;
   auto row = [&](int x) { return sh + x * ld; };
-  int arrivals = 0, sweeps = 0, rI = 0, rJ = 0;
-  bool converged = false;
-  // Waits for every workgroup, and makes what each wrote before visible to all; false: given up.
-  // Each wave releases what it wrote itself before the barrier: the barrier does not wait for stores that are under way, and a
-  // release by one wave waits for that wave's stores only.
-  auto meet = [&]() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  for (bool first = true;; first = false) {
+    // Each wave releases what it wrote itself before the barrier: the barrier does not wait for stores that are under way, and a
+    // release by one wave waits for that wave's stores only.
+    if (!first) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __syncthreads();
     if (t == 0) {
-      arrivals += gridDim.x;
-      __hip_atomic_fetch_add(info + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      bool all = true;
+      if (!first) __hip_atomic_fetch_add(info + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int ticket = __hip_atomic_fetch_add(info + 6, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int before = jacobi_ticket(ticket, nblk2).before;
+      bool turn = true;
       const unsigned long long start = wall_clock64();
-      while (__hip_atomic_load(info + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < arrivals) {
+      while (__hip_atomic_load(info + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < before) {
         if (wall_clock64() - start > kMeetTicks || __hip_atomic_load(info + 5, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
           __hip_atomic_store(info + 5, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          all = false;
+          turn = false;
           break;
         }
         __builtin_amdgcn_s_sleep(1);
       }
-      state = all ? __hip_atomic_load(info + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -1;
+      next = ticket;
+      state = turn ? __hip_atomic_load(info + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -1;
     }
     __syncthreads();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    return state >= 0;
-  };
-  while (!converged && sweeps < kMaxSweeps) {
-    ++sweeps;
-    bool any = false;
-    for (int outer = 0; outer < nblk2 - 1; ++outer) {
+    if (state < 0) return;
+    const JacobiTicket k = jacobi_ticket(__builtin_amdgcn_readfirstlane(next), nblk2);
+    const int last = __builtin_amdgcn_readfirstlane(state), what = jacobi_work(k, last, kMaxSweeps);
+    if (what == JACOBI_ROTATE) {
       int I, J;
-      rr_pair(blockIdx.x, outer, nblk2, I, J);
-      rI = I * kJB;                                     // I < J; the last blocks may be all padding
-      rJ = J * kJB;
+      rr_pair(k.pair, k.round, nblk2, I, J);
+      const int rI = I * kJB, rJ = J * kJB;             // I < J; the last blocks may be all padding
       auto grow = [&](int x) { return x < kJB ? rI + x : rJ + x - kJB; };
-      if (rI < l && (outer == 0 || rJ < l)) {           // uniform over the workgroup
+      if (rI < l && (k.round == 0 || rJ < l)) {         // uniform over the workgroup
         if (Lp <= 128) load_pair<2>(W, l, Lp, rI, rJ, sh, ld, t);
         else load_pair<4>(W, l, Lp, rI, rJ, sh, ld, t);
         __syncthreads();
         gram_32(row, Lp, work, t);
-        any |= sweep_32(work, t, outer == 0, tol * tol, settled * settled);
+        if (sweep_32(work, t, k.round == 0, tol * tol, settled * settled) && last <= k.sweep)
+          __hip_atomic_fetch_max(info + 3, k.sweep + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         for (int c0 = kJB * (t >> 6); c0 < Lp; c0 += 4 * kJB)
           apply_32(row, work + 2 * kJN * kJN, c0, t & 63, [&](int x, int c, double v) {
             if (grow(x) < l) __hip_atomic_store(W + (int64_t)grow(x) * Lp + c, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           });
       }
-      if (outer == nblk2 - 2 && any)
-        __hip_atomic_fetch_max(info + 3, sweeps, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (!meet()) return;
+      continue;
     }
-    converged = state < sweeps;                         // one that is ahead can only have noted a later sweep
-  }
-  // norms of the rows of this workgroup's last pair, eight lanes a row; then their place in the descending order
-  const int x = t >> 3, e0 = t & 7, i = x < kJB ? rI + x : rJ + x - kJB;
-  double s2 = 0.0;
-  const double left = i < l ? sig[Lp + i] : 0.0;        // not zero: a row that was set aside
-  if (i < l)
-    for (int e = e0; e < l; e += 8) {
-      if (left != 0.0) W[(int64_t)i * Lp + e] = R[(int64_t)i * ldr + e];
-      const double v = W[(int64_t)i * Lp + e];
-      s2 = fma(v, v, s2);
+    if (what == JACOBI_END) return;
+    // the rows of the blocks 2 pair and 2 pair + 1, eight lanes a row: their norms, then their places in the descending order
+    const int i = 2 * kJB * k.pair + (t >> 3), e0 = t & 7;
+    if (what == JACOBI_NORMS) {
+      double s2 = 0.0;
+      const double left = i < l ? sig[Lp + i] : 0.0;      // not zero: a row that was set aside
+      if (i < l)
+        for (int e = e0; e < l; e += 8) {
+          if (left != 0.0) W[(int64_t)i * Lp + e] = R[(int64_t)i * ldr + e];
+          const double v = W[(int64_t)i * Lp + e];
+          s2 = fma(v, v, s2);
+        }
+      s2 = row8_sum(s2);
+      if (i < l && e0 == 0) sig[Lp + i] = sqrt(left != 0.0 ? left : s2);
+    } else {
+      if (i < l) {
+        const double si = sig[Lp + i];
+        int rank = 0;
+        for (int j = e0; j < l; j += 8) rank += ranks_before(sig[Lp + j], j, si, i);
+        for (int off = 4; off > 0; off >>= 1) rank += __shfl_xor(rank, off, 8);
+        if (e0 == 0) { sig[rank] = si; sig[2 * Lp + rank] = (double)i; }
+      }
+      if (k.pair == 0 && t == 0) { info[0] = k.sweep; info[1] = last < k.sweep; }
     }
-  s2 = row8_sum(s2);
-  const double si = sqrt(left != 0.0 ? left : s2);
-  if (i < l && e0 == 0) sig[Lp + i] = si;
-  if (!meet()) return;
-  if (i < l) {
-    int rank = 0;
-    for (int j = e0; j < l; j += 8) rank += ranks_before(sig[Lp + j], j, si, i);
-    for (int off = 4; off > 0; off >>= 1) rank += __shfl_xor(rank, off, 8);
-    if (e0 == 0) { sig[rank] = si; sig[2 * Lp + rank] = (double)i; }
   }
-  if (blockIdx.x == 0 && t == 0) { info[0] = sweeps; info[1] = converged; }
 }
 
 // Sorted factors.  Vr[t][i] = W[o_i][t] / s_i;  Ur[kk][i] = sum_t R[kk][t] Vr[t][i] / s_i.
