@@ -1,6 +1,9 @@
 """The l x l factors at the edges of their tiles and of the kernels' ranges: Cholesky factor and inverse behind the
 orthonormalisation (16 x 16 tiles, in LDS up to 128, in global memory above), and the Jacobi SVD (row blocks of 16; one
 workgroup up to 32 rows, row rotations for three or five blocks, a workgroup per block pair otherwise)."""
+import threading
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -155,26 +158,54 @@ def test_small_svd_with_a_row_that_is_not_finite(l, bad):
 
 
 def test_block_pairs_on_several_streams():
-    """Calls whose workgroups wait for each other, on four streams beside a stream of large products: every call ends and
-    gives what it gives alone."""
+    """Calls whose workgroups wait for each other, at the same time on four streams (one host thread each: a call returns when
+    its work is done) beside a stream of large products: every call ends and gives what it gives alone."""
     dev = need_gpu()
     g = torch.Generator().manual_seed(9)
-    Rs = [torch.linalg.qr(torch.randn(l, l, generator=g, dtype=torch.float64))[1].to(dev).contiguous() for l in (81, 130, 200, 330)]
+    Rs = [torch.linalg.qr(torch.randn(l, l, generator=g, dtype=torch.float64))[1].to(dev).contiguous() for l in (81, 130, 200, 512)]
     alone = [B.brsvd_small_svd(R)[0].clone() for R in Rs]
-    big = torch.randn(4096, 4096, device=dev)
+    big = torch.randn(8192, 8192, device=dev)
+    product = torch.empty_like(big)
     streams = [torch.cuda.Stream() for _ in Rs]
     busy = torch.cuda.Stream()
+    outs = [tuple(torch.empty(s, dtype=torch.float64, device=dev) for s in (R.shape[0], R.shape, R.shape)) for R in Rs]
+    nbytes = [B.lib().brsvd_small_svd_scratch_bytes(R.shape[0]) for R in Rs]
+    scratch = [torch.empty(n, dtype=torch.uint8, device=dev) for n in nbytes]
+    start = threading.Barrier(len(Rs) + 1)
+    wrong, spans = [], [[] for _ in Rs]
+
+    def calls(i):
+        l = Rs[i].shape[0]
+        for _ in range(5):
+            start.wait(60)
+            for _ in range(4 * 512 // l):
+                t0 = time.perf_counter()
+                st = B.lib().brsvd_small_svd(Rs[i].data_ptr(), l, *(o.data_ptr() for o in outs[i]), None, scratch[i].data_ptr(),
+                                             nbytes[i], streams[i].cuda_stream)
+                spans[i].append((t0, time.perf_counter()))
+                if st != B.BRSVD_OK:
+                    wrong.append((l, st))
+            with torch.cuda.stream(streams[i]):
+                if not bool(torch.equal(alone[i], outs[i][0])):
+                    wrong.append((l, "values"))
+
+    threads = [threading.Thread(target=calls, args=(i,)) for i in range(len(Rs))]
     torch.cuda.synchronize()
-    with torch.cuda.stream(busy):
-        for _ in range(40):
-            big @ big
-    got = []
-    for R, st in zip(Rs, streams):
-        with torch.cuda.stream(st):
-            got.append(B.brsvd_small_svd(R)[0])
+    for th in threads:
+        th.start()
+    for _ in range(5):
+        with torch.cuda.stream(busy):          # some 40 ms of work, in the queue before the calls
+            for _ in range(5):
+                torch.mm(big, big, out=product)
+        start.wait(60)
+    for th in threads:
+        th.join(60)
     torch.cuda.synchronize()
-    for a, b in zip(alone, got):
-        assert bool((a == b).all())
+    assert not wrong and not any(th.is_alive() for th in threads)
+    # the calls did run beside each other
+    met = sum(a0 < b1 and b0 < a1 for a0, a1 in spans[3] for b0, b1 in spans[0])
+    print(f"[case] {met} calls of l=81 beside a call of l=512", flush=True)
+    assert met > 0
 
 
 @pytest.mark.parametrize("l", [49, 81, 112, 134, 161, 257, 512])
