@@ -35,6 +35,9 @@ typedef float floatx2 __attribute__((ext_vector_type(2)));
 
 constexpr int kSplitB = 32;          // contraction indices per block
 constexpr int kFragU = 64;           // 16-byte units of one operand fragment (16 x 32 bf16)
+// Flags of the workgroups that met a result that is not finite.  A workgroup beyond the last one shares a flag with an earlier
+// one; where the other raised it, its own results are only looked at in vain.
+constexpr int kSplitFlags = 4096;
 
 struct Frag3 { uintx4 p[3]; };       // h, m, l of eight contraction indices
 
@@ -62,23 +65,28 @@ __device__ __forceinline__ void split_pair(float a, float b, Frag3& f, int q) {
 __device__ __forceinline__ int64_t block_start(int64_t blk, int64_t K) { return min(blk * kSplitB, K - kSplitB); }
 
 // Packed panel: [block][column tile][h, m, l][lane][8 bf16], i.e. 3 KiB per block and tile of 16 columns; an even number of
-// blocks.  src: K x cols, leading dimension ld; columns cols.. are zero.  Also clears the flag of the products.
+// blocks.  src: K x cols, leading dimension ld; columns cols.. are zero.  nan: [column tile][block], a bit for each column with a
+// NaN.  Also clears the flags of the product's workgroups.
 __global__ void __launch_bounds__(256)
 k_split_pack(const float* __restrict__ src, int64_t K, int64_t ld, int cols, int nt_total, int64_t blocks,
-             uintx4* __restrict__ out, int* __restrict__ flag) {
+             uintx4* __restrict__ out, unsigned* __restrict__ nan, int* __restrict__ flags) {
   const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (id == 0) *flag = 0;
+  for (int64_t i = id; i < kSplitFlags; i += (int64_t)gridDim.x * 256) flags[i] = 0;
   const int lane = (int)(id & 63), r = lane & 15, g = lane >> 4;
   const int64_t tile = id >> 6, blk = tile / nt_total;
   if (blk >= blocks) return;
   const int nt = (int)(tile - blk * nt_total), col = 16 * nt + r;
   const int64_t k0 = block_start(blk, K);
   float v[8];
+  bool any_nan = false;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int64_t k = k0 + (e >> 2) * 16 + 4 * g + (e & 3);
     v[e] = k >= blk * kSplitB && col < cols ? src[k * ld + col] : 0.f;
+    any_nan |= v[e] != v[e];
   }
+  const unsigned long long b = __ballot(any_nan);                      // bit 16 * g + r
+  if (lane == 0) nan[nt * blocks + blk] = (unsigned)(b | b >> 16 | b >> 32 | b >> 48) & 0xffffu;
   Frag3 f;
 #pragma unroll
   for (int q = 0; q < 4; ++q) split_pair(v[2 * q], v[2 * q + 1], f, q);
@@ -281,7 +289,7 @@ template <int NT, int MT, int WR, int WC>
 __global__ void __launch_bounds__(WR * WC * 64)
 k_split_an(const float* __restrict__ A, int64_t lda, int rows, int K, const uintx4* __restrict__ XP, int64_t xstride,
            float* __restrict__ Y, int64_t ldy, int ncols, float* __restrict__ Part, int64_t ldp, int64_t split_stride,
-           AnShape sh, int* __restrict__ flag) {
+           AnShape sh, int* __restrict__ flags) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   constexpr int TR = WR * MT * 16;
   const AnWork w = an_work(sh, blockIdx.x);
@@ -297,7 +305,7 @@ k_split_an(const float* __restrict__ A, int64_t lda, int rows, int K, const uint
     s.out = w.partial ? Part + (int64_t)w.slot * split_stride - (int64_t)sh.whole * TR * ldp : Y;
     s.ldo = w.partial ? ldp : ldy;
     s.ncols = w.partial ? NT * 16 : ncols;
-    split_tile_waves<false, NT, MT, WR, WC>(s, XP, xstride, (uintx4*)lds_raw, flag);
+    split_tile_waves<false, NT, MT, WR, WC>(s, XP, xstride, (uintx4*)lds_raw, flags + blockIdx.x % kSplitFlags);
     __syncthreads();                                   // before the next strip reuses the staging buffers
   }
 }
@@ -307,7 +315,7 @@ template <int NT, int MT, int WR, int WC>
 __global__ void __launch_bounds__(WR * WC * 64)
 k_split_at(const float* __restrict__ A, int64_t lda, int64_t rows, int n, const uintx4* __restrict__ QP, int64_t xstride,
            float* __restrict__ Zpart, int64_t ldz, int64_t split_stride, int blocks, int blocks_per_sub,
-           int* __restrict__ flag) {
+           int* __restrict__ flags) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   SplitTile s;
   s.A = A;
@@ -320,46 +328,196 @@ k_split_at(const float* __restrict__ A, int64_t lda, int64_t rows, int n, const 
   s.out = Zpart + (int64_t)blockIdx.y * split_stride;
   s.ldo = ldz;
   s.ncols = NT * 16;
-  split_tile_waves<true, NT, MT, WR, WC>(s, QP, xstride, (uintx4*)lds_raw, flag);
+  split_tile_waves<true, NT, MT, WR, WC>(s, QP, xstride, (uintx4*)lds_raw, flags + (blockIdx.y * gridDim.x + blockIdx.x) % kSplitFlags);
 }
 
 // Products with infinities, NaN or overflow: a split infinity is inf + NaN + NaN, and inf times the zero low parts
-// of a short number is NaN, so such a product is taken once more with plain fp32 multiplications when a result of the
-// kernels above is not finite.  One wave per 16 x 16 tile of the output, grid stride; every workgroup leaves at once when the
-// flag is clear (about 3 us).  The whole product goes to `out` (rows from `part_row0` on: to the first partial panel, and the
-// other partial panels are cleared).
-template <bool AT>
-__global__ void __launch_bounds__(256)
-k_split_repair(const float* __restrict__ A, int64_t lda, int64_t rows, int64_t K, const float* __restrict__ X, int64_t ldx,
-               int xcols, float* __restrict__ Y, int64_t ldy, int ncols, float* __restrict__ part, int64_t ldp,
-               int64_t split_stride, int nsplit, int64_t part_row0, const int* __restrict__ flag) {
-  if (*flag == 0) return;
+// of a short number is NaN, so where a result of the kernels above is not finite it is worked out once more with plain fp32
+// multiplications.  One workgroup per workgroup of the product, with the same part of the contraction and the same place for the
+// result; it leaves at once when that one met nothing (about 3 us for the launch).  Otherwise it goes through pieces of 32 rows
+// (AT: columns of A) and 64 columns of the panel and redoes those that have a result that is not finite in a column of the
+// panel without a NaN: with one, it is NaN as it should be.  So a bad entry of A costs its rows or columns and a bad panel
+// nothing.
+// What bounds a piece: the latency of its operands, which come straight from global memory; so the eight waves share the
+// contraction.  Measured (us of the whole product, A X / A^T Q; plain kernels in brackets; before, when every tile of the product was
+// taken once more as soon as one entry was not finite):
+//                            finite                     one infinity in A                         an infinity in every row and column
+//   4000 x 4000 l=48         34 / 31 (41 / 40)          47 / 45 (41 / 40; before 429 / 526)       111 / 104
+//   20000 x 8000 l=110       210 / 212 (377 / 358)      338 / 472 (388 / 365; 7749 / 12884)       831 / 1516
+//   30000 x 20000 l=272      1836 / 1725 (2752 / 2835)  3025 / 4044 (2600 / 2815; 68574 / 97456)  7143 / 8865
+struct SplitRepair {
+  const float *A, *X;      // X: K x xcols, leading dimension ldx
+  int64_t lda, ldx, K;
+  int xcols, count, tile, nt_total;
+  const unsigned* nan;     // [column tile][block]
+  int64_t blocks;
+  const int* flags;
+};
+constexpr int kRepairNT = 4, kRepairWaves = 8, kMaxTiles = kMaxL / kTile;
+constexpr int kRepairMaxPieces = 256 / 32 * (kMaxTiles / kRepairNT);   // a tile has at most 256 rows (columns of A)
+
+// Whether the piece at rows w0.. of the output and column tiles nt0.. has a result that its columns do not explain (one wave).
+__device__ __forceinline__ bool repair_needed(const SplitRepair& p, int w0, int nt0, const unsigned* xnan, const float* out,
+                                              int64_t ldo, int ncols) {
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-  const int64_t ctiles = (ldp + 15) / 16, rtiles = (rows + 15) / 16, waves = (int64_t)gridDim.x * 4;
-  for (int64_t tile = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); tile < rtiles * ctiles; tile += waves) {
-    const int64_t row0 = tile / ctiles * 16;
-    const int col = (int)(tile % ctiles) * 16 + r;
-    const int64_t row = min(row0 + r, rows - 1);
-    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int64_t k = 0; k < K; k += 4) {
-      const int64_t kk = min(k + g, K - 1);
-      const float a = AT ? A[kk * lda + row] : A[row * lda + kk];
-      const float x = k + g < K && col < xcols ? X[kk * ldx + col] : 0.f;
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(k + g < K ? a : 0.f, x, acc, 0, 0, 0);
-    }
+  float worst = 0.f;                                     // NaN as soon as one is not finite
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int64_t i = row0 + 4 * g + v;
-      if (i >= rows) continue;
-      if (i < part_row0) {
-        if (col < ncols) Y[i * ldy + col] = acc[v];
-      } else if (col < ldp) {
-        float* p = part + (i - part_row0) * ldp + col;
-        p[0] = acc[v];
-        for (int s = 1; s < nsplit; ++s) p[(int64_t)s * split_stride] = 0.f;
-      }
+  for (int nt = 0; nt < kRepairNT; ++nt) {
+    const int tile = min(nt0 + nt, p.nt_total - 1), col = 16 * tile + r;
+    const bool look = col < ncols && !(xnan[tile] >> r & 1);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float y = out[(int64_t)min(w0 + 4 * i + g, p.count - 1) * ldo + min(col, ncols - 1)];
+      worst += look ? y * 0.f : 0.f;
     }
   }
+  return __any(!(worst == 0.f));
+}
+
+// One piece by all waves: rows w0.. of the output (a multiple of 32), column tiles nt0.., contraction [kbeg, kend).
+template <bool AT>
+__device__ __forceinline__ void repair_piece(const SplitRepair& p, int w0, int nt0, int64_t kbeg, int64_t kend,
+                                             floatx4* sum, float* out, int64_t ldo, int ncols) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
+  // the waves take equal parts of the contraction, multiples of 32, and add their sums in a fixed order
+  const int64_t part = (kend - kbeg + 32 * kRepairWaves - 1) / (32 * kRepairWaves) * 32;
+  const int64_t k_first = min(kend, kbeg + wave * part), k_last = min(kend, k_first + part);
+  floatx4 acc[2][kRepairNT];
+#pragma unroll
+  for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+    for (int nt = 0; nt < kRepairNT; ++nt) acc[mt][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+  // lane (r, g) holds the contraction indices k0 + 4 g + {0..3} and k0 + 16 + 4 g + {0..3} of row r and of column r
+  float a[2][8], x[kRepairNT][8];
+  typedef floatx4 floatx4u __attribute__((aligned(4)));
+  auto load = [&](int64_t k0, auto whole) {              // whole: all 32 indices are below kend
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int64_t kk = k0 + (e >> 2) * 16 + 4 * g + (e & 3);
+      const bool in = whole || kk < k_last;
+      const int64_t k = in ? kk : k_last - 1;
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt) {
+        const int64_t row = min(w0 + 16 * mt + r, p.count - 1);
+        if (AT || !whole) {
+          const float v = AT ? p.A[k * p.lda + row] : p.A[row * p.lda + k];
+          a[mt][e] = in ? v : 0.f;
+        } else if (e % 4 == 0) {
+          const floatx4 v = *(const floatx4u*)(p.A + row * p.lda + k);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) a[mt][e + i] = v[i];
+        }
+      }
+#pragma unroll
+      for (int nt = 0; nt < kRepairNT; ++nt) {
+        const int col = 16 * (nt0 + nt) + r;
+        const float v = p.X[k * p.ldx + min(col, p.xcols - 1)];
+        x[nt][e] = in && col < p.xcols ? v : 0.f;
+      }
+    }
+  };
+  auto add = [&]() {
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < kRepairNT; ++nt)
+          acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mt][e], x[nt][e], acc[mt][nt], 0, 0, 0);
+  };
+  int64_t k0 = k_first;
+#pragma nounroll
+  for (; k0 + 32 <= k_last; k0 += 32) {
+    load(k0, std::true_type{});
+    __builtin_amdgcn_sched_barrier(0);
+    add();
+  }
+  if (k0 < k_last) {
+    load(k0, std::false_type{});
+    add();
+  }
+#pragma unroll
+  for (int h = kRepairWaves / 2; h > 0; h /= 2) {
+    __syncthreads();
+    if (wave >= h && wave < 2 * h) {
+#pragma unroll
+      for (int i = 0; i < 2 * kRepairNT; ++i) sum[((wave - h) * 2 * kRepairNT + i) * 64 + lane] = acc[i / kRepairNT][i % kRepairNT];
+    }
+    __syncthreads();
+    if (wave < h) {
+#pragma unroll
+      for (int i = 0; i < 2 * kRepairNT; ++i) acc[i / kRepairNT][i % kRepairNT] += sum[(wave * 2 * kRepairNT + i) * 64 + lane];
+    }
+  }
+  if (wave != 0) return;
+#pragma unroll
+  for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int row = w0 + 16 * mt + 4 * g + v;
+      if (row >= p.count) continue;
+#pragma unroll
+      for (int nt = 0; nt < kRepairNT; ++nt) {
+        const int col = 16 * (nt0 + nt) + r;
+        if (nt0 + nt < p.nt_total && col < ncols) out[(int64_t)row * ldo + col] = acc[mt][nt][v];
+      }
+    }
+}
+
+// The tile of rows (columns of A) from `first` on, over `blocks` blocks of the contraction from b0 on.
+template <bool AT>
+__device__ __forceinline__ void repair_tile(const SplitRepair& p, int first, int64_t b0, int blocks, const unsigned* xnan, float* out,
+                                            int64_t ldo, int ncols) {
+  __shared__ floatx4 sum[kRepairWaves / 2 * 2 * kRepairNT * 64];
+  __shared__ int redo[kRepairMaxPieces];
+  const int strips = (p.nt_total + kRepairNT - 1) / kRepairNT, pieces = (min(p.tile, p.count - first) + 31) / 32 * strips;
+  for (int i = threadIdx.x >> 6; i < pieces; i += kRepairWaves) {
+    const bool bad = repair_needed(p, first + i / strips * 32, i % strips * kRepairNT, xnan, out, ldo, ncols);
+    if ((threadIdx.x & 63) == 0) redo[i] = bad;
+  }
+  __syncthreads();
+  for (int i = 0; i < pieces; ++i)
+    if (redo[i])
+      repair_piece<AT>(p, first + i / strips * 32, i % strips * kRepairNT, b0 * kSplitB, min(p.K, (b0 + blocks) * kSplitB), sum, out,
+                       ldo, ncols);
+  __syncthreads();                                       // before the next tile's `redo`
+}
+
+// Which columns of the panel have a NaN in the blocks [b0, b0 + blocks).
+__device__ __forceinline__ void nan_columns(const SplitRepair& p, int64_t b0, int blocks, unsigned* xnan) {
+  const int lane = threadIdx.x & 63;
+  for (int nt = threadIdx.x >> 6; nt < p.nt_total; nt += kRepairWaves) {
+    unsigned m = 0;
+    for (int b = lane; b < blocks; b += 64) m |= p.nan[nt * p.blocks + b0 + b];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) m |= __shfl_xor(m, off, 64);
+    if (lane == 0) xnan[nt] = m;
+  }
+  __syncthreads();
+}
+
+__global__ void __launch_bounds__(kRepairWaves * 64)
+k_split_repair_an(SplitRepair p, float* __restrict__ Y, int64_t ldy, int ncols, float* __restrict__ Part, int64_t ldp,
+                  int64_t split_stride, AnShape sh) {
+  __shared__ unsigned xnan[kMaxTiles];
+  if (p.flags[blockIdx.x % kSplitFlags] == 0) return;
+  const AnWork w = an_work(sh, blockIdx.x);
+  const int64_t b0 = 2 * (int64_t)w.c0;
+  const int blocks = 2 * (w.c1 - w.c0);
+  nan_columns(p, b0, blocks, xnan);
+  float* out = w.partial ? Part + (int64_t)w.slot * split_stride - (int64_t)sh.whole * p.tile * ldp : Y;
+  for (int seg = 0; seg < w.nseg; ++seg)
+    repair_tile<false>(p, (w.first_tile + seg) * p.tile, b0, blocks, xnan, out, w.partial ? ldp : ldy, w.partial ? (int)ldp : ncols);
+}
+
+__global__ void __launch_bounds__(kRepairWaves * 64)
+k_split_repair_at(SplitRepair p, float* __restrict__ Zpart, int64_t ldz, int64_t split_stride, int blocks_per_sub) {
+  __shared__ unsigned xnan[kMaxTiles];
+  if (p.flags[(blockIdx.y * gridDim.x + blockIdx.x) % kSplitFlags] == 0) return;
+  const int64_t b0 = (int64_t)blockIdx.y * blocks_per_sub;
+  const int blocks = (int)min((int64_t)blocks_per_sub, p.blocks - b0);
+  nan_columns(p, b0, blocks, xnan);
+  repair_tile<true>(p, blockIdx.x * p.tile, b0, blocks, xnan, Zpart + (int64_t)blockIdx.y * split_stride, ldz, (int)ldz);
 }
 
 // ---- host side --------------------------------------------------------------------------------------------------
@@ -372,7 +530,18 @@ static SplitCfg split_cfg(int nt) {
 }
 constexpr int kSplitSlots = 256;                        // one workgroup of eight waves per CU
 static int64_t split_chunks(int64_t K) { return ceil_div(K, 2 * kSplitB); }
-static uint64_t pack_panel_bytes(int64_t K, int Lp) { return (uint64_t)split_chunks(K) * 2 * (Lp / 16) * 3 * kFragU * 16; }
+// The packed panel, behind it the words that say which columns have a NaN, and the flags of the product's workgroups.
+struct PackLayout {
+  uint64_t nan, flags, bytes;
+};
+static PackLayout pack_layout(int64_t K, int Lp) {
+  const uint64_t tiles = (uint64_t)split_chunks(K) * 2 * (Lp / 16);
+  PackLayout o;
+  o.nan = tiles * 3 * kFragU * 16;
+  o.flags = o.nan + tiles * 4;
+  o.bytes = o.flags + kSplitFlags * 4;
+  return o;
+}
 
 bool split_fits(bool at, const float* A, int64_t out, int64_t K, int Lp, int64_t lda, uint64_t pack_bytes) {
   // byte offsets of a lane's loads: at most 255 rows and a row length, in 32 bits
@@ -380,7 +549,7 @@ bool split_fits(bool at, const float* A, int64_t out, int64_t K, int Lp, int64_t
   if (out > INT32_MAX || K > INT32_MAX) return false;
   const bool aligned = lda % 4 == 0 && (uintptr_t)A % 16 == 0;
   if (Lp < 48 && (at ? out : K) < kSplitLongRow && (!at || aligned)) return false;
-  return pack_bytes >= pack_panel_bytes(K, Lp) + 64;
+  return pack_bytes >= pack_layout(K, Lp).bytes;
 }
 
 SplitPlan split_an_plan(int64_t rows, int64_t K, int Lp, uint64_t scratch_bytes) {
@@ -440,11 +609,23 @@ static int split_lds(K kern, int nt, bool* done) {
   return BRSVD_OK;
 }
 
-static int split_pack(const float* X, int64_t K, int64_t ldx, int xcols, int Lp, void* pack, int** flag, hipStream_t stream) {
+struct Packed {
+  const uintx4* panel;
+  int64_t stride;                                        // 16-byte units of one block
+  int* flags;
+  SplitRepair repair;
+};
+
+static int split_pack(const float* A, int64_t lda, int64_t count, int tile, const float* X, int64_t K, int64_t ldx, int xcols, int Lp,
+                      void* pack, Packed* out, hipStream_t stream) {
+  const PackLayout lay = pack_layout(K, Lp);
   const int64_t blocks = 2 * split_chunks(K), units = blocks * (Lp / 16) * kFragU;
-  *flag = (int*)((char*)pack + pack_panel_bytes(K, Lp));
+  unsigned* nan = (unsigned*)((char*)pack + lay.nan);
+  int* flags = (int*)((char*)pack + lay.flags);
+  *out = Packed{(const uintx4*)pack, (Lp / 16) * 3 * kFragU, flags,
+                SplitRepair{A, X, lda, ldx, K, xcols, (int)count, tile, Lp / 16, nan, blocks, flags}};
   hipLaunchKernelGGL(k_split_pack, dim3((unsigned)ceil_div(units, 256)), dim3(256), 0, stream, X, K, ldx, xcols, Lp / 16,
-                     blocks, (uintx4*)pack, *flag);
+                     blocks, (uintx4*)pack, nan, flags);
   BRSVD_HIP_TRY(hipGetLastError());
   return BRSVD_OK;
 }
@@ -455,13 +636,13 @@ int split_gemm_an(const float* A, int64_t lda, int64_t rows, int64_t K, const fl
   if (!split_fits(false, A, rows, K, Lp, lda, pack_bytes) || ncols > Lp) return BRSVD_ERR_ARG;
   const SplitPlan p = split_an_plan(rows, K, Lp, scratch_bytes);
   float* part = (float*)scratch;
-  const int64_t stride = p.partial_rows * Lp, xstride = (Lp / 16) * 3 * kFragU;
-  int* flag;
-  BRSVD_TRY(split_pack(X, K, ldx, xcols, Lp, pack, &flag, stream));
+  const int64_t stride = p.partial_rows * Lp;
+  Packed x;
+  BRSVD_TRY(split_pack(A, lda, rows, p.tile, X, K, ldx, xcols, Lp, pack, &x, stream));
   for (int gi = 0; gi < p.groups; ++gi) {
     const int c0 = gi * p.nt * 16, nt = std::min(p.nt, (Lp - c0) / 16);
     if (nt <= 0) break;
-    const uintx4* xp = (const uintx4*)pack + (c0 / 16) * 3 * kFragU;
+    const uintx4* xp = x.panel + (c0 / 16) * 3 * kFragU;
 #define CALL(N, WR, WC)                                                                                              \
   {                                                                                                                  \
     if (p.tile != WR * kSplitMT * 16) return BRSVD_ERR_ARG;                                                          \
@@ -469,14 +650,14 @@ int split_gemm_an(const float* A, int64_t lda, int64_t rows, int64_t K, const fl
     static bool done = false;                                                                                        \
     BRSVD_TRY(split_lds(kern, N, &done));                                                                            \
     hipLaunchKernelGGL(kern, dim3(p.wgs), dim3(WR * WC * 64), 2 * N * 3 * kFragU * 16, stream, A, lda, (int)rows, (int)K, \
-                       xp, xstride, Y + c0, ldy, std::min(ncols - c0, N * 16), part ? part + c0 : nullptr, (int64_t)Lp, stride, p.sh, flag); \
+                       xp, x.stride, Y + c0, ldy, std::min(ncols - c0, N * 16), part ? part + c0 : nullptr, (int64_t)Lp, stride, p.sh, x.flags); \
   }
     BRSVD_SPLIT_SWITCH(nt, p.tile, CALL)
 #undef CALL
     BRSVD_HIP_TRY(hipGetLastError());
   }
-  hipLaunchKernelGGL(k_split_repair<false>, dim3(kSplitSlots), dim3(256), 0, stream, A, lda, rows, K, X, ldx, xcols, Y, ldy,
-                     ncols, part, (int64_t)Lp, stride, p.nsplit, rows - p.partial_rows, flag);
+  hipLaunchKernelGGL(k_split_repair_an, dim3(p.wgs), dim3(kRepairWaves * 64), 0, stream, x.repair, Y, ldy, ncols, part, (int64_t)Lp,
+                     stride, p.sh);
   BRSVD_HIP_TRY(hipGetLastError());
   if (ev) BRSVD_HIP_TRY(hipEventRecord(ev->stop, stream));
   if (p.nsplit > 0) {
@@ -495,13 +676,13 @@ int split_gemm_at(const float* A, int64_t lda, int64_t rows, int64_t n, const fl
   if (p.nsplit < 1) return BRSVD_ERR_BUDGET;
   if (p.nsplit > 65535) return BRSVD_ERR_ARG;
   float* part = (float*)scratch;
-  const int64_t stride = n * Lp, xstride = (Lp / 16) * 3 * kFragU;
-  int* flag;
-  BRSVD_TRY(split_pack(Q, rows, ldq, qcols, Lp, pack, &flag, stream));
+  const int64_t stride = n * Lp;
+  Packed x;
+  BRSVD_TRY(split_pack(A, lda, n, p.tile, Q, rows, ldq, qcols, Lp, pack, &x, stream));
   for (int gi = 0; gi < p.groups; ++gi) {
     const int c0 = gi * p.nt * 16, nt = std::min(p.nt, (Lp - c0) / 16);
     if (nt <= 0) break;
-    const uintx4* qp = (const uintx4*)pack + (c0 / 16) * 3 * kFragU;
+    const uintx4* qp = x.panel + (c0 / 16) * 3 * kFragU;
 #define CALL(N, WR, WC)                                                                                              \
   {                                                                                                                  \
     if (p.tile != WR * kSplitMT * 16) return BRSVD_ERR_ARG;                                                          \
@@ -509,14 +690,14 @@ int split_gemm_at(const float* A, int64_t lda, int64_t rows, int64_t n, const fl
     static bool done = false;                                                                                        \
     BRSVD_TRY(split_lds(kern, N, &done));                                                                            \
     hipLaunchKernelGGL(kern, dim3(p.col_tiles, p.nsplit), dim3(WR * WC * 64), 2 * N * 3 * kFragU * 16, stream, A, lda, rows, \
-                       (int)n, qp, xstride, part + c0, (int64_t)Lp, stride, p.blocks, p.blocks_per_sub, flag);       \
+                       (int)n, qp, x.stride, part + c0, (int64_t)Lp, stride, p.blocks, p.blocks_per_sub, x.flags);    \
   }
     BRSVD_SPLIT_SWITCH(nt, p.tile, CALL)
 #undef CALL
     BRSVD_HIP_TRY(hipGetLastError());
   }
-  hipLaunchKernelGGL(k_split_repair<true>, dim3(kSplitSlots), dim3(256), 0, stream, A, lda, n, rows, Q, ldq, qcols, nullptr,
-                     (int64_t)0, 0, part, (int64_t)Lp, stride, p.nsplit, (int64_t)0, flag);
+  hipLaunchKernelGGL(k_split_repair_at, dim3(p.col_tiles, p.nsplit), dim3(kRepairWaves * 64), 0, stream, x.repair, part, (int64_t)Lp,
+                     stride, p.blocks_per_sub);
   BRSVD_HIP_TRY(hipGetLastError());
   if (ev) BRSVD_HIP_TRY(hipEventRecord(ev->stop, stream));
   BRSVD_TRY(reduce_splits_f32(part, p.nsplit, stride, n, ncols, Lp, Z, ldz, accumulate, stream));
