@@ -3,7 +3,9 @@
 //
 //   a = h + m + l,   h = the upper 16 bits of a (8 significant bits), m = bf16(a - h), l = a - h - m
 //
-// (24 significant bits = 8 + 8 + 8, so nothing of a is lost, at any exponent).  Of the nine products of two such
+// (24 significant bits = 8 + 8 + 8, so nothing of a is lost from 2^-110 on; l of a smaller number would have bits below 2^-133,
+// where bf16 ends.  Rows of A or columns of a panel with no larger element are multiplied in fp32 after all, see k_split_repair_an.)
+// Of the nine products of two such
 // sums the six above 2^-24 are taken, l*h + h*l + m*m + m*h + h*m + h*h: six v_mfma_f32_16x16x32_bf16 do the work of
 // eight v_mfma_f32_16x16x4_f32 in 96 cycles instead of 256.  The dropped products are below 2^-22 of |a||x| at most and
 // 2^-26 on average, and random in sign.
@@ -35,9 +37,14 @@ typedef float floatx2 __attribute__((ext_vector_type(2)));
 
 constexpr int kSplitB = 32;          // contraction indices per block
 constexpr int kFragU = 64;           // 16-byte units of one operand fragment (16 x 32 bf16)
-// Flags of the workgroups that met a result that is not finite.  A workgroup beyond the last one shares a flag with an earlier
-// one; where the other raised it, its own results are only looked at in vain.
+// Flags of the workgroups that met a result that is not finite, and behind them of those that met a row (Z = A^T Q: a column) of
+// A with small elements only.  A workgroup beyond the last one shares a flag with an earlier one; where the other raised it,
+// its own results are only looked at in vain.
 constexpr int kSplitFlags = 4096;
+constexpr int kNotFinite = 1, kSmall = 2;
+// Elements from 2^-95 on have one of these exponent bits set.  They are split without loss, and their parts times anything of
+// ordinary size stay clear of the subnormal numbers; the third part of an element below 2^-110 would not fit bf16 (2^-133).
+constexpr unsigned kWholeBits = 0x70000000u;
 
 struct Frag3 { uintx4 p[3]; };       // h, m, l of eight contraction indices
 
@@ -59,6 +66,11 @@ __device__ __forceinline__ void split_pair(float a, float b, Frag3& f, int q) {
   f.p[2][q] = pack_bf16(ra, rb);
 }
 
+// bits |= a | b in one instruction: as plain code the compiler puts it off and keeps a and b in registers (20 more, and spills).
+__device__ __forceinline__ void or3(unsigned& bits, float a, float b) {
+  asm("v_or3_b32 %0, %0, %1, %2" : "+v"(bits) : "v"(a), "v"(b));
+}
+
 // First contraction index of block `blk`: the last blocks are moved back so that they end with the range, and the
 // indices the block before has already covered are zero in the packed panel.  Neither operand is then ever read
 // outside its range, and A needs no masks.  K >= kSplitB.
@@ -66,12 +78,13 @@ __device__ __forceinline__ int64_t block_start(int64_t blk, int64_t K) { return 
 
 // Packed panel: [block][column tile][h, m, l][lane][8 bf16], i.e. 3 KiB per block and tile of 16 columns; an even number of
 // blocks.  src: K x cols, leading dimension ld; columns cols.. are zero.  nan: [column tile][block], a bit for each column with a
-// NaN.  Also clears the flags of the product's workgroups.
+// NaN.  Also clears the flags of the product's workgroups and of the rows of A.
+// Where a column has small elements only in a block, its part of the panel is made NaN, so that its results are taken from the repair.
 __global__ void __launch_bounds__(256)
 k_split_pack(const float* __restrict__ src, int64_t K, int64_t ld, int cols, int nt_total, int64_t blocks,
-             uintx4* __restrict__ out, unsigned* __restrict__ nan, int* __restrict__ flags) {
+             uintx4* __restrict__ out, unsigned* __restrict__ nan, int* __restrict__ flags, int64_t nflags) {
   const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  for (int64_t i = id; i < kSplitFlags; i += (int64_t)gridDim.x * 256) flags[i] = 0;
+  for (int64_t i = id; i < nflags; i += (int64_t)gridDim.x * 256) flags[i] = 0;
   const int lane = (int)(id & 63), r = lane & 15, g = lane >> 4;
   const int64_t tile = id >> 6, blk = tile / nt_total;
   if (blk >= blocks) return;
@@ -79,17 +92,22 @@ k_split_pack(const float* __restrict__ src, int64_t K, int64_t ld, int cols, int
   const int64_t k0 = block_start(blk, K);
   float v[8];
   bool any_nan = false;
+  unsigned bits = 0;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int64_t k = k0 + (e >> 2) * 16 + 4 * g + (e & 3);
     v[e] = k >= blk * kSplitB && col < cols ? src[k * ld + col] : 0.f;
     any_nan |= v[e] != v[e];
+    bits |= __float_as_uint(v[e]);
   }
   const unsigned long long b = __ballot(any_nan);                      // bit 16 * g + r
   if (lane == 0) nan[nt * blocks + blk] = (unsigned)(b | b >> 16 | b >> 32 | b >> 48) & 0xffffu;
   Frag3 f;
 #pragma unroll
   for (int q = 0; q < 4; ++q) split_pair(v[2 * q], v[2 * q + 1], f, q);
+  bits |= __shfl_xor(bits, 16, 64);
+  bits |= __shfl_xor(bits, 32, 64);
+  if (!(bits & kWholeBits) && (bits & 0x7fffffffu)) f.p[0][0] = 0x7fc07fc0u;
   uintx4* o = out + tile * (3 * kFragU) + lane;
 #pragma unroll
   for (int p = 0; p < 3; ++p) o[p * kFragU] = f.p[p];
@@ -114,6 +132,7 @@ struct SplitTile {
   float* out;            // row `first` of the output is out + first * ldo
   int64_t ldo;
   int ncols;
+  int* whole;            // set for the rows (columns) with an element that is split without loss
 };
 
 // Workgroup: WR x WC waves; wave (wr, wc) owns MT tiles of 16 rows (AT: columns of A) and NTW tiles of the panel's
@@ -126,7 +145,7 @@ struct SplitTile {
 // the loads of the block after that, and the hand-over of the next block's packed panel from registers to LDS.  One barrier
 // per block.  A first version that did these things between the blocks ran at 75-85 % of this one.
 template <bool AT, int NT, int NTW, int MT, int WR, int WC>
-__device__ __forceinline__ bool split_tile(const SplitTile& s, const uintx4* __restrict__ XP, int64_t xstride, uintx4* lds,
+__device__ __forceinline__ int split_tile(const SplitTile& s, const uintx4* __restrict__ XP, int64_t xstride, uintx4* lds,
                                            int wr, int nt0) {
   constexpr int NTH = WR * WC * 64;
   constexpr int BUF = NT * 3 * kFragU;                 // 16-byte units of one staged block
@@ -155,9 +174,11 @@ __device__ __forceinline__ bool split_tile(const SplitTile& s, const uintx4* __r
   vecM rq[8];                                          // Z = A^T Q: [index] MT columns of one row of A
   Frag3 fa[MT], fb[MT];
   uintx4 xr[XPT];
+  unsigned bits[MT];                                   // of all elements of A this lane has split, by row (AT: column)
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
     tl[mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    bits[mt] = 0;
 #pragma unroll
     for (int nt = 0; nt < NTW; ++nt) acc[mt][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
   }
@@ -186,9 +207,11 @@ __device__ __forceinline__ bool split_tile(const SplitTile& s, const uintx4* __r
     if constexpr (AT) {
       const int q = p / MT, mt = p % MT;
       split_pair(rq[2 * q][mt], rq[2 * q + 1][mt], f[mt], q);
+      or3(bits[mt], rq[2 * q][mt], rq[2 * q + 1][mt]);
     } else {
       const int mt = p >> 2, q = p & 3;
       split_pair(ra[mt][q >> 1][2 * (q & 1)], ra[mt][q >> 1][2 * (q & 1) + 1], f[mt], q);
+      or3(bits[mt], ra[mt][q >> 1][2 * (q & 1)], ra[mt][q >> 1][2 * (q & 1) + 1]);
     }
   };
 
@@ -266,7 +289,17 @@ __device__ __forceinline__ bool split_tile(const SplitTile& s, const uintx4* __r
         }
       }
     }
-  return !(worst == 0.f);
+  // rows with an element that is split whole, and whether one has only smaller ones
+  int found = !(worst == 0.f) ? kNotFinite : 0;
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    unsigned b = bits[mt] | __shfl_xor(bits[mt], 16, 64);
+    b |= __shfl_xor(b, 32, 64);
+    const int row = AT ? c0 + mt : min(w0 + 16 * mt + r, s.count - 1);
+    if (b & kWholeBits) s.whole[row] = 1;
+    else if (b & 0x7fffffffu) found |= kSmall;
+  }
+  return found;
 }
 
 template <bool AT, int NT, int MT, int WR, int WC>
@@ -274,14 +307,15 @@ __device__ __forceinline__ void split_tile_waves(const SplitTile& s, const uintx
   constexpr int NTW = (NT + WC - 1) / WC;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wr = wave % WR, wc = wave / WR;
-  bool bad;
+  int found;
   if constexpr (NT % WC == 0) {
-    bad = split_tile<AT, NT, NTW, MT, WR, WC>(s, XP, xstride, lds, wr, wc * NTW);
+    found = split_tile<AT, NT, NTW, MT, WR, WC>(s, XP, xstride, lds, wr, wc * NTW);
   } else {
-    if (wc == 0) bad = split_tile<AT, NT, NTW, MT, WR, WC>(s, XP, xstride, lds, wr, 0);
-    else bad = split_tile<AT, NT, NTW - 1, MT, WR, WC>(s, XP, xstride, lds, wr, NTW);
+    if (wc == 0) found = split_tile<AT, NT, NTW, MT, WR, WC>(s, XP, xstride, lds, wr, 0);
+    else found = split_tile<AT, NT, NTW - 1, MT, WR, WC>(s, XP, xstride, lds, wr, NTW);
   }
-  if (bad) *flag = 1;
+  if (found & kNotFinite) flag[0] = 1;
+  if (found & kSmall) flag[kSplitFlags] = 1;
 }
 
 // Y = A X.  Work partition and partial panels as in k_gemm_an (AnShape), in chunks of two blocks.
@@ -289,7 +323,7 @@ template <int NT, int MT, int WR, int WC>
 __global__ void __launch_bounds__(WR * WC * 64)
 k_split_an(const float* __restrict__ A, int64_t lda, int rows, int K, const uintx4* __restrict__ XP, int64_t xstride,
            float* __restrict__ Y, int64_t ldy, int ncols, float* __restrict__ Part, int64_t ldp, int64_t split_stride,
-           AnShape sh, int* __restrict__ flags) {
+           AnShape sh, int* __restrict__ flags, int* __restrict__ whole) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   constexpr int TR = WR * MT * 16;
   const AnWork w = an_work(sh, blockIdx.x);
@@ -305,6 +339,7 @@ k_split_an(const float* __restrict__ A, int64_t lda, int rows, int K, const uint
     s.out = w.partial ? Part + (int64_t)w.slot * split_stride - (int64_t)sh.whole * TR * ldp : Y;
     s.ldo = w.partial ? ldp : ldy;
     s.ncols = w.partial ? NT * 16 : ncols;
+    s.whole = whole;
     split_tile_waves<false, NT, MT, WR, WC>(s, XP, xstride, (uintx4*)lds_raw, flags + blockIdx.x % kSplitFlags);
     __syncthreads();                                   // before the next strip reuses the staging buffers
   }
@@ -315,7 +350,7 @@ template <int NT, int MT, int WR, int WC>
 __global__ void __launch_bounds__(WR * WC * 64)
 k_split_at(const float* __restrict__ A, int64_t lda, int64_t rows, int n, const uintx4* __restrict__ QP, int64_t xstride,
            float* __restrict__ Zpart, int64_t ldz, int64_t split_stride, int blocks, int blocks_per_sub,
-           int* __restrict__ flags) {
+           int* __restrict__ flags, int* __restrict__ whole) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   SplitTile s;
   s.A = A;
@@ -328,12 +363,15 @@ k_split_at(const float* __restrict__ A, int64_t lda, int64_t rows, int n, const 
   s.out = Zpart + (int64_t)blockIdx.y * split_stride;
   s.ldo = ldz;
   s.ncols = NT * 16;
+  s.whole = whole;
   split_tile_waves<true, NT, MT, WR, WC>(s, QP, xstride, (uintx4*)lds_raw, flags + (blockIdx.y * gridDim.x + blockIdx.x) % kSplitFlags);
 }
 
 // Products with infinities, NaN or overflow: a split infinity is inf + NaN + NaN, and inf times the zero low parts
 // of a short number is NaN, so where a result of the kernels above is not finite it is worked out once more with plain fp32
-// multiplications.  One workgroup per workgroup of the product, with the same part of the contraction and the same place for the
+// multiplications.  So are the rows (AT: columns) of A that have elements below 2^-95 only, whose third parts bf16 may not hold:
+// next to a larger element what they lose is below the rounding of that one's products.  (Columns of the panel with such
+// elements only in a block of 32 are packed as NaN, which brings them here too.)  One workgroup per workgroup of the product, with the same part of the contraction and the same place for the
 // result; it leaves at once when that one met nothing (about 3 us for the launch).  Otherwise it goes through pieces of 32 rows
 // (AT: columns of A) and 64 columns of the panel and redoes those that have a result that is not finite in a column of the
 // panel without a NaN: with one, it is NaN as it should be.  So a bad entry of A costs its rows or columns and a bad panel
@@ -351,15 +389,16 @@ struct SplitRepair {
   int xcols, count, tile, nt_total;
   const unsigned* nan;     // [column tile][block]
   int64_t blocks;
-  const int* flags;
+  const int *flags, *whole;
 };
 constexpr int kRepairNT = 4, kRepairWaves = 8, kMaxTiles = kMaxL / kTile;
 constexpr int kRepairMaxPieces = 256 / 32 * (kMaxTiles / kRepairNT);   // a tile has at most 256 rows (columns of A)
 
 // Whether the piece at rows w0.. of the output and column tiles nt0.. has a result that its columns do not explain (one wave).
-__device__ __forceinline__ bool repair_needed(const SplitRepair& p, int w0, int nt0, const unsigned* xnan, const float* out,
-                                              int64_t ldo, int ncols) {
+__device__ __forceinline__ bool repair_needed(const SplitRepair& p, int w0, int nt0, bool small, const unsigned* xnan,
+                                              const float* out, int64_t ldo, int ncols) {
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  if (small && __any(p.whole[min(w0 + (lane & 31), p.count - 1)] == 0)) return true;
   float worst = 0.f;                                     // NaN as soon as one is not finite
 #pragma unroll
   for (int nt = 0; nt < kRepairNT; ++nt) {
@@ -466,13 +505,13 @@ __device__ __forceinline__ void repair_piece(const SplitRepair& p, int w0, int n
 
 // The tile of rows (columns of A) from `first` on, over `blocks` blocks of the contraction from b0 on.
 template <bool AT>
-__device__ __forceinline__ void repair_tile(const SplitRepair& p, int first, int64_t b0, int blocks, const unsigned* xnan, float* out,
-                                            int64_t ldo, int ncols) {
+__device__ __forceinline__ void repair_tile(const SplitRepair& p, int first, int64_t b0, int blocks, bool small, const unsigned* xnan,
+                                            float* out, int64_t ldo, int ncols) {
   __shared__ floatx4 sum[kRepairWaves / 2 * 2 * kRepairNT * 64];
   __shared__ int redo[kRepairMaxPieces];
   const int strips = (p.nt_total + kRepairNT - 1) / kRepairNT, pieces = (min(p.tile, p.count - first) + 31) / 32 * strips;
   for (int i = threadIdx.x >> 6; i < pieces; i += kRepairWaves) {
-    const bool bad = repair_needed(p, first + i / strips * 32, i % strips * kRepairNT, xnan, out, ldo, ncols);
+    const bool bad = repair_needed(p, first + i / strips * 32, i % strips * kRepairNT, small, xnan, out, ldo, ncols);
     if ((threadIdx.x & 63) == 0) redo[i] = bad;
   }
   __syncthreads();
@@ -500,24 +539,28 @@ __global__ void __launch_bounds__(kRepairWaves * 64)
 k_split_repair_an(SplitRepair p, float* __restrict__ Y, int64_t ldy, int ncols, float* __restrict__ Part, int64_t ldp,
                   int64_t split_stride, AnShape sh) {
   __shared__ unsigned xnan[kMaxTiles];
-  if (p.flags[blockIdx.x % kSplitFlags] == 0) return;
+  const int* flag = p.flags + blockIdx.x % kSplitFlags;
+  const bool small = flag[kSplitFlags] != 0;
+  if (flag[0] == 0 && !small) return;
   const AnWork w = an_work(sh, blockIdx.x);
   const int64_t b0 = 2 * (int64_t)w.c0;
   const int blocks = 2 * (w.c1 - w.c0);
   nan_columns(p, b0, blocks, xnan);
   float* out = w.partial ? Part + (int64_t)w.slot * split_stride - (int64_t)sh.whole * p.tile * ldp : Y;
   for (int seg = 0; seg < w.nseg; ++seg)
-    repair_tile<false>(p, (w.first_tile + seg) * p.tile, b0, blocks, xnan, out, w.partial ? ldp : ldy, w.partial ? (int)ldp : ncols);
+    repair_tile<false>(p, (w.first_tile + seg) * p.tile, b0, blocks, small, xnan, out, w.partial ? ldp : ldy, w.partial ? (int)ldp : ncols);
 }
 
 __global__ void __launch_bounds__(kRepairWaves * 64)
 k_split_repair_at(SplitRepair p, float* __restrict__ Zpart, int64_t ldz, int64_t split_stride, int blocks_per_sub) {
   __shared__ unsigned xnan[kMaxTiles];
-  if (p.flags[(blockIdx.y * gridDim.x + blockIdx.x) % kSplitFlags] == 0) return;
+  const int* flag = p.flags + (blockIdx.y * gridDim.x + blockIdx.x) % kSplitFlags;
+  const bool small = flag[kSplitFlags] != 0;
+  if (flag[0] == 0 && !small) return;
   const int64_t b0 = (int64_t)blockIdx.y * blocks_per_sub;
   const int blocks = (int)min((int64_t)blocks_per_sub, p.blocks - b0);
   nan_columns(p, b0, blocks, xnan);
-  repair_tile<true>(p, blockIdx.x * p.tile, b0, blocks, xnan, Zpart + (int64_t)blockIdx.y * split_stride, ldz, (int)ldz);
+  repair_tile<true>(p, blockIdx.x * p.tile, b0, blocks, small, xnan, Zpart + (int64_t)blockIdx.y * split_stride, ldz, (int)ldz);
 }
 
 // ---- host side --------------------------------------------------------------------------------------------------
@@ -530,16 +573,18 @@ static SplitCfg split_cfg(int nt) {
 }
 constexpr int kSplitSlots = 256;                        // one workgroup of eight waves per CU
 static int64_t split_chunks(int64_t K) { return ceil_div(K, 2 * kSplitB); }
-// The packed panel, behind it the words that say which columns have a NaN, and the flags of the product's workgroups.
+// The packed panel, behind it the words that say which columns have a NaN, and the flags of the product's workgroups and of the
+// `out` rows (columns) of A.
 struct PackLayout {
-  uint64_t nan, flags, bytes;
+  uint64_t nan, flags, whole, bytes;
 };
-static PackLayout pack_layout(int64_t K, int Lp) {
+static PackLayout pack_layout(int64_t out, int64_t K, int Lp) {
   const uint64_t tiles = (uint64_t)split_chunks(K) * 2 * (Lp / 16);
   PackLayout o;
   o.nan = tiles * 3 * kFragU * 16;
   o.flags = o.nan + tiles * 4;
-  o.bytes = o.flags + kSplitFlags * 4;
+  o.whole = o.flags + 2 * kSplitFlags * 4;
+  o.bytes = o.whole + (uint64_t)out * 4;
   return o;
 }
 
@@ -549,7 +594,7 @@ bool split_fits(bool at, const float* A, int64_t out, int64_t K, int Lp, int64_t
   if (out > INT32_MAX || K > INT32_MAX) return false;
   const bool aligned = lda % 4 == 0 && (uintptr_t)A % 16 == 0;
   if (Lp < 48 && (at ? out : K) < kSplitLongRow && (!at || aligned)) return false;
-  return pack_bytes >= pack_layout(K, Lp).bytes;
+  return pack_bytes >= pack_layout(out, K, Lp).bytes;
 }
 
 SplitPlan split_an_plan(int64_t rows, int64_t K, int Lp, uint64_t scratch_bytes) {
@@ -612,20 +657,20 @@ static int split_lds(K kern, int nt, bool* done) {
 struct Packed {
   const uintx4* panel;
   int64_t stride;                                        // 16-byte units of one block
-  int* flags;
+  int *flags, *whole;
   SplitRepair repair;
 };
 
 static int split_pack(const float* A, int64_t lda, int64_t count, int tile, const float* X, int64_t K, int64_t ldx, int xcols, int Lp,
                       void* pack, Packed* out, hipStream_t stream) {
-  const PackLayout lay = pack_layout(K, Lp);
+  const PackLayout lay = pack_layout(count, K, Lp);
   const int64_t blocks = 2 * split_chunks(K), units = blocks * (Lp / 16) * kFragU;
   unsigned* nan = (unsigned*)((char*)pack + lay.nan);
-  int* flags = (int*)((char*)pack + lay.flags);
-  *out = Packed{(const uintx4*)pack, (Lp / 16) * 3 * kFragU, flags,
-                SplitRepair{A, X, lda, ldx, K, xcols, (int)count, tile, Lp / 16, nan, blocks, flags}};
+  int *flags = (int*)((char*)pack + lay.flags), *whole = (int*)((char*)pack + lay.whole);
+  *out = Packed{(const uintx4*)pack, (Lp / 16) * 3 * kFragU, flags, whole,
+                SplitRepair{A, X, lda, ldx, K, xcols, (int)count, tile, Lp / 16, nan, blocks, flags, whole}};
   hipLaunchKernelGGL(k_split_pack, dim3((unsigned)ceil_div(units, 256)), dim3(256), 0, stream, X, K, ldx, xcols, Lp / 16,
-                     blocks, (uintx4*)pack, nan, flags);
+                     blocks, (uintx4*)pack, nan, flags, 2 * kSplitFlags + count);
   BRSVD_HIP_TRY(hipGetLastError());
   return BRSVD_OK;
 }
@@ -650,7 +695,7 @@ int split_gemm_an(const float* A, int64_t lda, int64_t rows, int64_t K, const fl
     static bool done = false;                                                                                        \
     BRSVD_TRY(split_lds(kern, N, &done));                                                                            \
     hipLaunchKernelGGL(kern, dim3(p.wgs), dim3(WR * WC * 64), 2 * N * 3 * kFragU * 16, stream, A, lda, (int)rows, (int)K, \
-                       xp, x.stride, Y + c0, ldy, std::min(ncols - c0, N * 16), part ? part + c0 : nullptr, (int64_t)Lp, stride, p.sh, x.flags); \
+                       xp, x.stride, Y + c0, ldy, std::min(ncols - c0, N * 16), part ? part + c0 : nullptr, (int64_t)Lp, stride, p.sh, x.flags, x.whole); \
   }
     BRSVD_SPLIT_SWITCH(nt, p.tile, CALL)
 #undef CALL
@@ -690,7 +735,7 @@ int split_gemm_at(const float* A, int64_t lda, int64_t rows, int64_t n, const fl
     static bool done = false;                                                                                        \
     BRSVD_TRY(split_lds(kern, N, &done));                                                                            \
     hipLaunchKernelGGL(kern, dim3(p.col_tiles, p.nsplit), dim3(WR * WC * 64), 2 * N * 3 * kFragU * 16, stream, A, lda, rows, \
-                       (int)n, qp, x.stride, part + c0, (int64_t)Lp, stride, p.blocks, p.blocks_per_sub, x.flags);    \
+                       (int)n, qp, x.stride, part + c0, (int64_t)Lp, stride, p.blocks, p.blocks_per_sub, x.flags, x.whole);    \
   }
     BRSVD_SPLIT_SWITCH(nt, p.tile, CALL)
 #undef CALL

@@ -167,7 +167,7 @@ int main() {
     // the packed panel fits where the driver and the step calls put it: the TSQR work area, two padded fp32 panels
     if (rows * n >= brsvd::kSplitMinA && n >= brsvd::kSplitMinK) {
       const int64_t most = rows > n ? rows : n;
-      CHECK(brsvd::split_fits(false, (const float*)0x4, rows, n, Lp, n, brsvd::tsqr_work_bytes(n, Lp)));
+      CHECK(brsvd::split_fits(false, (const float*)0x4, rows, n, Lp, n, brsvd::tsqr_work_bytes(most, Lp)));
       CHECK(brsvd::split_fits(true, (const float*)0x4, rows, n, Lp, n, 2ull * most * Lp * 4));
     }
   }

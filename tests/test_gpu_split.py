@@ -144,3 +144,48 @@ def test_split_products_not_finite_cost():
     print(f"[case] finite {finite} one infinity {one} panel {panel} us", flush=True)
     for a, b, c in zip(finite, one, panel):
         assert b <= 6 * a and c <= 2.5 * a            # measured 1.6 to 2.3 and 1.0 to 1.1
+
+
+@pytest.mark.parametrize("scale_a,scale_x", [(1e-33, 1e28), (1e-35, 1e30), (1e-37, 1e30), (1e-41, 1e35), (1e30, 1e-37), (1e28, 1e-41),
+                                             (1e-20, 1e-17)])
+@pytest.mark.parametrize("rows,n,l,pad,off", [(2049, 2050, 64, 0, 0), SHAPES[6], SHAPES[11]])
+def test_split_products_of_small_numbers(rows, n, l, pad, off, scale_a, scale_x):
+    """Numbers whose low parts bf16 does not hold, down to subnormal ones: no less accurate than plain fp32 products (whose bound
+    this is: K / 4 rounded additions, as a random walk, with a factor of two)."""
+    dev = need_gpu()
+    print(f"[case] split small rows={rows} n={n} l={l} {scale_a} {scale_x}", flush=True)
+    A, X, Q = _inputs(rows, n, l, pad, off, dev)
+    A.mul_(scale_a)
+    X, Q = X * scale_x, Q * scale_x
+    At = A.T.contiguous()
+    for got, a, x in ((B.brsvd_gemm_an(A, X), A, X), (B.brsvd_gemm_at(A, Q), At, Q)):
+        ref = a.double() @ x.double()
+        # the smallest results are subnormal themselves (2^-149 apart): half of that for each of the partial sums
+        bound = np.sqrt(a.shape[1]) * EPS32 * (a.abs().double() @ x.abs().double()) + 2.0 ** -149 * a.shape[1] / 32
+        assert bool(((got.double() - ref).abs() <= bound).all())
+        assert float((got.double() - ref).norm() / ref.norm()) <= 5e-7
+
+
+@pytest.mark.parametrize("rows,n,l,pad,off", [(2049, 2050, 64, 0, 0), SHAPES[4], SHAPES[6], SHAPES[11]])
+def test_split_products_of_small_rows_and_columns(rows, n, l, pad, off):
+    """Rows, columns and stretches of small numbers, and zeros, in an ordinary matrix: each row of Y and column of Z to its own scale."""
+    dev = need_gpu()
+    A, X, Q = _inputs(rows, n, l, pad, off, dev)
+    A[3] *= 1e-36
+    A[rows - 1] *= 1e-34
+    A[rows // 2] = 0.0
+    A[17, n // 2:] *= 1e-37                              # half a row: nothing of the row is lost
+    A[:, 5] *= 1e-36
+    A[:, n - 1] *= 1e-35
+    A[:, n // 2] = 0.0
+    X[:, l - 1] *= 1e-36
+    Q[:, 0] *= 1e-36
+    X[64:128, 2] *= 1e-36
+    At = A.T.contiguous()
+    for got, a, x in ((B.brsvd_gemm_an(A, X), A, X), (B.brsvd_gemm_at(A, Q), At, Q)):
+        ref, size = a.double() @ x.double(), a.abs().double() @ x.abs().double()
+        # rows and columns that are small alone; where both are, the products themselves are below the smallest number
+        err = (got.double() - ref).abs()
+        bound = np.sqrt(a.shape[1]) * EPS32 * size + 2.0 ** -149 * a.shape[1]
+        assert bool((err <= bound).all())
+        assert bool((got[ref == 0] == 0).all())
