@@ -719,9 +719,11 @@ struct AnCfg {
 };
 // Tile shapes picked from sweeps on MI355X (see the launch templates below, which must agree).
 constexpr int64_t kAnWideK = 1024;
+// Row tiles per wave: wide panels take one (in fp64 that keeps two waves per SIMD).
+static constexpr int an_mt(int nt, int esz) { return nt > (esz == 8 ? 4 : 14) ? 1 : 2; }
 static AnCfg an_cfg(int nt, int esz, int64_t K) {
   auto cfg = [](int mt, int waves, int kc) { return AnCfg{mt, waves, kc, waves * mt * 16}; };
-  if (esz == 8) return cfg(nt >= 5 ? 1 : 2, 4, 32);   // wide fp64 panels: one m-tile per wave keeps two waves per SIMD
+  if (esz == 8) return cfg(an_mt(nt, esz), 4, 32);
   // one column tile: bound by the read of A (k_gemm_an_narrow: tiles of 32 rows, chunks of 256 columns)
   if (nt <= kAnNarrowMaxNT && K >= kAnNarrowMinK) return AnCfg{2, 4, kAnNarrowKC, kAnNarrowRows};
   // eight waves share one staged panel chunk (half the staging per MFMA); short contractions keep four-wave
@@ -729,7 +731,7 @@ static AnCfg an_cfg(int nt, int esz, int64_t K) {
   // bound: more, smaller workgroups per CU overlap their load waits better (76800 x 2000, l = 20: 152 -> 135 us;
   // 100000 x 50000, l = 32: 4.5 -> 5.3 TB/s)
   if (nt <= 8) return cfg(2, (K >= kAnWideK && nt > 2) ? 8 : 4, 64);
-  return cfg(nt > 14 ? 1 : 2, 8, 32);
+  return cfg(an_mt(nt, esz), 8, 32);
 }
 // Discount of partial-panel traffic: 1 for HBM-bound widths, smaller once 2*Lp/8 flop/B is past the ridge.
 double traffic_weight(int nt) { return nt <= 2 ? 1.0 : (nt <= 4 ? 0.6 : 0.3); }
@@ -880,7 +882,7 @@ static int launch_an_nt(const T* A, int64_t lda, int rows, int K, const T* X, in
       if (K >= kAnNarrowMinK)
         return launch_an_narrow<NT>(A, lda, rows, K, X, ldx, Y, ldy, ncols, part, ldp, split_stride, p, stream);
     }
-    constexpr int MT = ((sizeof(T) == 8 && NT >= 5) || NT > 14) ? 1 : 2;
+    constexpr int MT = an_mt(NT, (int)sizeof(T));
     constexpr int KC = (sizeof(T) == 8 || NT > 8) ? 32 : 64;
     if constexpr (sizeof(T) == 4 && NT <= 8) {
       if (K >= kAnWideK && NT > 2)
@@ -968,8 +970,7 @@ static int gemm_an_t(const T* A, int64_t lda, int64_t rows, int64_t K, const T* 
     if (nt <= 0) break;
     // The plan is one for all groups: where a narrower last group would take an instance with another tile of rows (9 or 25
     // tiles in fp64, 29 in fp32), it starts earlier instead and computes a few columns again, to the same values.
-    const bool one_row_tile = (esz == 8 && nt >= 5) || nt > 14, plan_one = (esz == 8 && ng.nt >= 5) || ng.nt > 14;
-    if (one_row_tile != plan_one) { nt = ng.nt; c0 = Lp - nt * 16; }
+    if (an_mt(nt, esz) != an_mt(ng.nt, esz)) { nt = ng.nt; c0 = Lp - nt * 16; }
     int nc = ncols - c0 < nt * 16 ? ncols - c0 : nt * 16;   // valid output columns in this group (may be <= 0)
     BRSVD_TRY(launch_an<T>(nt, A, lda, (int)rows, (int)K, X + c0, Lp, Y + c0, ldy, nc, part ? part + c0 : nullptr,
                            Lp, prows * Lp, p, stream));
