@@ -58,6 +58,14 @@ def log(msg: str) -> None:
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
 
+def mfma_peak(B, which, A, l):
+    """The matrix-core peak (Tflop/s) behind A X (which = 0) or A^T Q (which = 1), by the kernels the library takes for it."""
+    m, n = A.shape
+    if A.element_size() == 8:
+        return PEAK_MFMA_F64_TFLOPS
+    return PEAK_SPLIT_F32_TFLOPS if B.brsvd_gemm_is_split(which, m, n, l, A.stride(0), A.data_ptr()) else PEAK_MFMA_F32_TFLOPS
+
+
 def kernel_figures(m, n, l, esz, seconds, launches, peak_mfma):
     """Roofline figures of one pass kernel: algorithmic bytes 4mn + 4(m+n)l and flops 2mnl per launch over all of A."""
     avg = seconds / max(launches, 1)
@@ -111,12 +119,11 @@ def run_in_core(B, torch, cfg, steps, warmup, fused=False, f64=False, copy_calib
     sec = (t1 - t0) / steps
     passes = acc["passes_over_A"] // steps
     bytes_a = float(acc["bytes_A_streamed"]) / steps
-    split = not f64 and l > 32 and m * n >= 1 << 22
-    peak_mfma = PEAK_MFMA_F64_TFLOPS if f64 else PEAK_SPLIT_F32_TFLOPS if split else PEAK_MFMA_F32_TFLOPS
-    kern = {"gemm_an": kernel_figures(m, n, l, esz, acc["gemm_an_seconds"], acc["gemm_an_launches"], peak_mfma),
-            "gemm_at": kernel_figures(m, n, l, esz, acc["gemm_at_seconds"], acc["gemm_at_launches"], peak_mfma)}
+    peaks = {"gemm_an": mfma_peak(B, 0, A, l), "gemm_at": mfma_peak(B, 1, A, l)}
+    kern = {name: kernel_figures(m, n, l, esz, acc[f"{name}_seconds"], acc[f"{name}_launches"], peaks[name]) for name in peaks}
     kname = "gemm_an" if acc["gemm_an_seconds"] >= acc["gemm_at_seconds"] else "gemm_at"
     kf = kern[kname]
+    peak_mfma = peaks[kname]
     ai = kf["algorithmic_flops"] / kf["algorithmic_bytes"]
     ridge = peak_mfma * 1e12 / (PEAK_HBM_GBS * 1e9)
     key = f"{cfg.name}:{kname}"
@@ -210,8 +217,8 @@ def sub_c5(B, torch, np, synth, reps=3):
     finally:
         B.brsvd_destroy(h)
     st = best
-    an = kernel_figures(m, n, l, 4, st["gemm_an_seconds"], st["gemm_an_launches"], PEAK_MFMA_F32_TFLOPS)
-    at = kernel_figures(m, n, l, 4, st["gemm_at_seconds"], st["gemm_at_launches"], PEAK_MFMA_F32_TFLOPS)
+    an = kernel_figures(m, n, l, 4, st["gemm_an_seconds"], st["gemm_an_launches"], mfma_peak(B, 0, D, l))
+    at = kernel_figures(m, n, l, 4, st["gemm_at_seconds"], st["gemm_at_launches"], mfma_peak(B, 1, D, l))
     upd = st["rpca_update_seconds"] / max(st["rpca_update_launches"], 1)
     upd_bytes = 16.0 * m * n          # reads M, Y; writes Y, X (L and S are formed once, after the loop)
     rec = {"workload": f"C5 robust PCA: D fp32 {m}x{n}, {iters} ALM iterations, k={cfg.k}, p={cfg.p}, q={cfg.q}, "
@@ -335,8 +342,8 @@ def sweep_gemm(B, torch, args):
             finally:
                 B.brsvd_destroy(h)
             rec = {"m": m, "n": n, "l": l}
-            for name in ("gemm_an", "gemm_at"):
-                f = kernel_figures(m, n, l, 4, best[f"{name}_seconds"], best[f"{name}_launches"], PEAK_MFMA_F32_TFLOPS)
+            for which, name in enumerate(("gemm_an", "gemm_at")):
+                f = kernel_figures(m, n, l, 4, best[f"{name}_seconds"], best[f"{name}_launches"], mfma_peak(B, which, A, l))
                 rec[name] = {"us": round(f["avg_launch_ms"] * 1e3, 1), "GBps": round(f["hbm_GBps"]), "hbm_frac": round(f["hbm_frac"], 3),
                              "TFLOPs": round(f["mfma_TFLOPs"], 1), "mfma_frac": round(f["mfma_frac"], 3)}
             print(json.dumps(rec), flush=True)

@@ -1167,6 +1167,16 @@ int brsvd_gemm_plan(int32_t which, int64_t rows, int64_t n, int32_t l, int64_t b
   return BRSVD_OK;
 }
 
+int brsvd_gemm_is_split(int32_t which, const void* A, int64_t lda, int64_t rows, int64_t n, int32_t l, int32_t dtype) {
+  if (which < 0 || which > 1 || rows < 1 || n < 1 || l < 1 || l > kMaxL || lda < n) return BRSVD_ERR_ARG;
+  if (dtype == BRSVD_DTYPE_F64) return 0;
+  if (dtype != BRSVD_DTYPE_F32) return BRSVD_ERR_ARG;
+  const int Lp = padded_l(l);
+  const uint64_t room = 2 * align_up((uint64_t)std::max(rows, n) * Lp * 4);      // as in the step calls
+  return which == 0 ? split_fits(false, (const float*)A, rows, n, Lp, lda, room)
+                    : split_fits(true, (const float*)A, n, rows, Lp, lda, room);
+}
+
 int brsvd_probe(int32_t kind, void* buf, uint64_t amount, double* seconds, double* work, void* stream) {
   return probe(kind, buf, amount, seconds, work, (hipStream_t)stream);
 }

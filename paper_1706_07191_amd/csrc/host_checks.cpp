@@ -169,6 +169,7 @@ int main() {
       const int64_t most = rows > n ? rows : n;
       CHECK(brsvd::split_fits(false, (const float*)0x4, rows, n, Lp, n, brsvd::tsqr_work_bytes(most, Lp)));
       CHECK(brsvd::split_fits(true, (const float*)0x4, rows, n, Lp, n, 2ull * most * Lp * 4));
+      CHECK(brsvd_gemm_is_split(0, (const void*)0x4, n, rows, n, Lp, BRSVD_DTYPE_F32) == 1);
     }
   }
 

@@ -99,3 +99,25 @@ def test_gemm_at_plan_tiles_every_block():
             assert col_tiles * waves * mt * 16 >= n > (col_tiles - 1) * waves * mt * 16
             assert rps % kc == 0 and sub * rps >= block and (sub - 1) * rps < block      # sub-ranges tile the block
             assert groups * nt * 16 >= (l + 15) // 16 * 16
+
+
+@pytest.mark.parametrize("which,rows,n,l,lda,address,split", [
+    (0, 20000, 20000, 110, 20000, 0, True), (1, 20000, 20000, 110, 20000, 0, True),
+    (0, 8200, 512, 48, 512, 0, True), (0, 8300, 511, 48, 511, 0, False),            # contraction of A X: n
+    (1, 8300, 511, 48, 511, 0, True), (1, 511, 8300, 48, 8300, 0, False),            # of A^T Q: rows
+    (0, 64, 65536, 48, 65536, 0, True), (0, 63, 70000, 48, 70000, 0, False),         # rows of Y
+    (0, 2048, 2048, 48, 2048, 0, True), (0, 2048, 2047, 48, 2047, 0, False),         # 4 M elements of A
+    (0, 60000, 20000, 16, 20000, 0, False), (0, 60000, 20000, 17, 20000, 0, True),   # 17 to 32 columns: long rows
+    (0, 76800, 2000, 32, 2000, 0, False), (1, 76800, 2000, 32, 2000, 0, False),
+    (1, 76800, 2000, 32, 2001, 0, True), (1, 76800, 2000, 32, 2000, 4, True),        # or, for A^T Q, unaligned ones
+    (0, 76800, 2000, 33, 2000, 0, True), (0, 3000, 3000, 110, (1 << 21) + 1, 0, False),
+])
+def test_which_products_are_split(which, rows, n, l, lda, address, split):
+    assert B.brsvd_gemm_is_split(which, rows, n, l, lda, address) == split
+    assert not B.brsvd_gemm_is_split(which, rows, n, l, lda, address, dtype=B.BRSVD_DTYPE_F64)
+
+
+def test_which_products_are_split_refuses():
+    for bad in ((2, 10, 10, 4, 10), (0, 0, 10, 4, 10), (0, 10, 10, 0, 10), (0, 10, 10, 513, 10), (0, 10, 10, 4, 9)):
+        with pytest.raises(B.BrsvdError):
+            B.brsvd_gemm_is_split(*bad)
