@@ -51,8 +51,9 @@ __device__ __forceinline__ double rcp_nr(double x) {
 // With results delivered in single precision the bar is lower: a last sweep whose largest cosine was below
 // kSettledF32 leaves cosines of the order l * kSettledF32^2 = 1e-8, an order of magnitude below what the fp32
 // lifts U = Q V_R and V = W_B U_R can show, and that saves one sweep of the seven to eight an l of 100 to 300 takes.
-// Row rotations skip pairs whose cosine is below kTolRows (a skipped rotation saves its traffic); on the 32 x 32 Gram matrix a
-// rotation costs the same whether it turns or not, so everything above rounding is rotated.
+// Row rotations of more than 20 rows skip pairs whose cosine is below kTolRows (a skipped rotation saves its traffic).  On the 32 x 32
+// Gram matrix a rotation costs the same whether it turns or not, and on up to 20 rows hardly more (1 %), so everything above
+// rounding is rotated there.
 constexpr double kTolRows = 1e-13, kTolBlocks = 1e-16;
 constexpr double kSettled = 1e-8;
 constexpr double kSettledF32 = 1e-5;
@@ -136,7 +137,7 @@ __device__ __forceinline__ double row8_sum(double v) {
   return v;
 }
 
-// ---- 33 to 48 and 65 to 80 rows: row rotations in LDS -------------------------------------------------------------------------
+// ---- up to 20, 33 to 48 and 65 to 80 rows: row rotations in LDS -------------------------------------------------------------------------
 // Each group of 16 lanes owns one row pair per step, so a wave handles 4 pairs with one instruction stream and up to
 // 64 pairs take 1024 threads.  EPL = elements of a row per lane = ceil(l / 16).
 // Pair schedule of a sweep (every pair of rows met exactly once): the index range is halved
@@ -283,17 +284,19 @@ k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __re
 // A sweep is a round robin over the block pairs.  Its first round rotates all 496 pairs of the 32 rows (31 steps of
 // 16 disjoint pairs), the others the 256 pairs across the two blocks (16 steps).
 //   l <= 32: one block pair, rows in LDS for all sweeps (k_jacobi_small);
-//   otherwise: one workgroup per block pair, rows in global memory, one launch (k_jacobi_rounds);
-//   but with three or five blocks, where a padding block goes round with the others, row rotations stay ahead (us, this against row
-//   rotations: l = 33 367 / 236, 48 354 / 296, 72 654 / 567; on the other side 60 407 / 414 (27 of 2526 less in a
-//   whole decomposition with single-precision results), 64 368 / 431, 96 673 / 824, 110 918 / 1064, 128 938 / 1458).
+//   otherwise: one workgroup per block pair, rows in global memory, one launch (k_jacobi_rounds).
+// Row rotations stay ahead (us of a call of brsvd_small_svd, this against row rotations)
+//   up to 20 rows, where the 31 steps of a sweep are more than their l: l = 4 85 / 44, 8 113 / 65, 12 114 / 84, 16 128 / 105, 18
+//   132 / 116 to 129, 20 132 / 120 to 133; on the other side 21 133 / 127 to 141, 22 120 to 134 / 140, 24 133 / 146, 30 135 / 170;
+//   and with three or five blocks, where a padding block goes round with the others: l = 33 367 / 236, 48 354 / 296, 72 654 / 567;
+//   on the other side 49 336 / 348, 56 336 / 341, 64 338 / 415, 81 612 / 709, 96 552 / 797, 128 877 / 1420.
 // What bounds it: the latency of a step, 800 to 900 cycles from barrier to barrier, half of it the rotation; the matrix products
-// take 5 to 9 thousand cycles of a round beside the 14 thousand of the steps (l = 160, 272).  Measured (us per call of the small
-// SVD, row rotations before and this): l = 20 143 -> 134, 30 181 -> 151, 110 1064 -> 918, 160 2867 -> 1440, 272 6140 -> 3690,
-// 512 13900 -> 9110.  Two
-// accumulator chains per product: four gain 2 % at l <= 32 and lose 6 % above 128.
+// take 5 to 9 thousand cycles of a round beside the 14 thousand of the steps (l = 160, 272).  Measured (us per call, row rotations, one
+// workgroup or a launch per round, and this): l = 30 170 -> 135, 64 415 -> 338, 128 1420 -> 877, 160 2658 -> 1204, 240 4895 -> 2518,
+// 512 13716 -> 8631.  Two accumulator chains per product: four gain 2 % at l <= 32 and lose 6 % above 128.
 constexpr int kJB = 16;
 constexpr int kJN = 2 * kJB;                      // rows of a block pair
+constexpr int kRowsMaxL = 20;                     // up to here, row rotations
 // Place of entry (x, y) of the Gram matrix and of J: odd rows have their halves exchanged, so that the two rows of 16
 // consecutive columns that half a wave touches, and 16 consecutive diagonal entries, lie on distinct banks.
 __device__ __forceinline__ int jat(int x, int y) { return x * kJN + (y ^ ((x & 1) << 4)); }
@@ -761,16 +764,15 @@ int small_svd(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* br
   if (l < 1 || l > kMaxL) return BRSVD_ERR_ARG;
   // fp64 factors or singular values asked for: the strict bar; single-precision results only: the relaxed one
   const double settled = (sizeof(TO) == 4 && !S && !Ur && !Vr) ? kSettledF32 : kSettled;
-  if (l <= kJN) {
+  const int nblk = (l + kJB - 1) / kJB;
+  if (l <= kRowsMaxL || nblk == 3 || nblk == 5) {
+    auto kern = l <= kJB ? k_jacobi_rows<1> : nblk == 2 ? k_jacobi_rows<2> : nblk == 3 ? k_jacobi_rows<3> : k_jacobi_rows<5>;
+    hipLaunchKernelGGL(kern, dim3(1), dim3(64 * LPP), (size_t)l * l * sizeof(double), stream, R, ldr, l, Lp, w.W, w.sig, w.info,
+                       breakdown_flag, l <= kRowsMaxL ? kTolBlocks : kTolRows, settled);
+    BRSVD_HIP_TRY(hipGetLastError());
+  } else if (l <= kJN) {
     hipLaunchKernelGGL(k_jacobi_small, dim3(1), dim3(kJThreads), jacobi_lds_bytes(Lp), stream, R, ldr, l, Lp, w.W, w.sig, w.info,
                        breakdown_flag, kTolBlocks, settled);
-    BRSVD_HIP_TRY(hipGetLastError());
-  } else if (l <= 5 * kJB && ((l + kJB - 1) / kJB) % 2) {   // three or five blocks
-    const size_t lds = (size_t)l * l * sizeof(double);
-    if (l <= 3 * kJB) hipLaunchKernelGGL(k_jacobi_rows<3>, dim3(1), dim3(64 * LPP), lds, stream, R, ldr, l, Lp, w.W, w.sig, w.info,
-                                          breakdown_flag, kTolRows, settled);
-    else hipLaunchKernelGGL(k_jacobi_rows<5>, dim3(1), dim3(64 * LPP), lds, stream, R, ldr, l, Lp, w.W, w.sig, w.info,
-                            breakdown_flag, kTolRows, settled);
     BRSVD_HIP_TRY(hipGetLastError());
   } else {
     BRSVD_TRY(jacobi_global(R, ldr, l, Lp, w, breakdown_flag, kTolBlocks, settled, stream));

@@ -1,6 +1,6 @@
 """The l x l factors at the edges of their tiles and of the kernels' ranges: Cholesky factor and inverse behind the
-orthonormalisation (16 x 16 tiles, in LDS up to 128, in global memory above), and the Jacobi SVD (row blocks of 16; one
-workgroup up to 32 rows, row rotations for three or five blocks, a workgroup per block pair otherwise)."""
+orthonormalisation (16 x 16 tiles, in LDS up to 128, in global memory above), and the Jacobi SVD (row blocks of 16; row
+rotations up to 20 rows and for three or five blocks, one workgroup up to 32 rows, a workgroup per block pair otherwise)."""
 import threading
 import time
 
@@ -75,6 +75,13 @@ def test_small_svd(l, cond):
     assert float((V.T @ V - eye).abs().max()) <= 4e-13
     assert float((U.T @ U - eye).abs().max()) <= 4e-13 * cond * 10
     assert float(((U * S) @ V.T - R).abs().max()) <= 1e-12
+
+
+@pytest.mark.parametrize("l", [2, 3, 20, 21])
+def test_small_svd_at_the_ends_of_the_row_rotations(l):
+    """Row rotations up to 20 rows, one block pair from 21 on."""
+    for cond in (1e2, 1e8):
+        test_small_svd(l, cond)
 
 
 def _singular_values_long(R):
