@@ -104,15 +104,21 @@ int reduce_splits_f32(float* part, int nsplit, int64_t split_stride, int64_t row
 
 // ---- the same two products for wide fp32 panels on the bf16 matrix cores (gemm_split.hip) ----
 // out x K (an) or K x out (at) is the part of A multiplied; pack is device memory for the split right panel.
-// Taken for contractions of at least 512 and 2^22 elements of A, from 48 padded columns on, and at 32 for rows of at least 8000 or
-// (Z = A^T Q) rows that do not start on 16-byte boundaries.  Measured, plain fp32 kernel and this one (us, A X / A^T Q):
-// 100000x50000 l=272 20944 / 21274 and 12640 / 13114; 20000x20000 l=110 877 / 791 and 514 / 514; 89083x2783 l=97 583 / 748 and
-// 336 / 343; 76800x2000 l=40 189 / 197 and 165 / 148; 4000x4000 l=48 36.8 / 30.9 and 31.9 / 25.6; 60000x20000 l=24 1035 / 834 and
-// 879 / 789; 8000x8000 l=30 54.7 / 57.9 and 51.4 / 50.5; 32256x2383 l=20 77.3 / 111.5 and 85.5 / 73.1.  Below, the extra launches
-// cost what the product saves, or the read of A bounds both: 2000x1000 l=60 21.2 / 23.6 and 24.2 / 18.0, 1024x1024 l=300 79 /
-// 35.6 and 73 / 36.8, 100000x50000 l=16 3287 / 3266 and 3911 / 3373, 76800x2000 l=20 (inside the robust-PCA loop) 129 / 115
-// and 139 / 126.
-constexpr int64_t kSplitMinK = 512, kSplitMinOut = 64, kSplitMinLp = 32, kSplitMinA = 1 << 22, kSplitLongRow = 8000;
+// Taken for contractions of at least 512 and 2^22 elements of A, from 48 padded columns on.  Measured, plain fp32 kernel and this one
+// (us, A X / A^T Q): 100000x50000 l=272 20944 / 21274 and 12640 / 13114; 20000x20000 l=110 877 / 791 and 514 / 514; 89083x2783 l=97
+// 583 / 748 and 336 / 343; 76800x2000 l=40 189 / 197 and 165 / 148; 4000x4000 l=48 36.8 / 30.9 and 31.9 / 25.6.  Below, the extra
+// launches cost what the product saves, or the read of A bounds both: 2000x1000 l=60 21.2 / 23.6 and 24.2 / 18.0, 1024x1024 l=300
+// 79 / 35.6 and 73 / 36.8, 100000x50000 l=16 3287 / 3266 and 3911 / 3373.
+// At 32 padded columns both kernels are near the read of A, and what decides is how they cut and read it (l = 24):
+//   A X: this one reads 64 bytes of a row at a time and loses where rows do not start on lines of 128 bytes: 20000x20004 338 and
+//     374, 30000x20003 510 and 567, 60000x8007 431 and 468; or where they are short or few: 20000x8000 137 and 143, 8000x16000 113 and
+//     118, 1000x8000 25 and 32.  From 14000 columns and 20000 rows on, on lines, it is level or ahead: 20000x20000 306 and 309,
+//     30000x14848 343 and 338, 60000x20000 887 and 873, 20000x50016 739 and 716.
+//   A^T Q: rows that vectors of 16 bytes do not fit cost the plain kernel a third: 60000x8007 507 and 349, 5003x1001 l=32 29 and 24.
+//     Otherwise few rows of A leave the plain one with too few workgroups, 1000x8000 24 and 21, 4000x10000 46 and 39, 6000x20000 112
+//     and 94, 2000x50000 95 and 87, and for many its panels are larger, 20000x20000 307 and 274, 60000x20000 832 and 813; between, the
+//     plain one is ahead: 12000x14000 128 and 138, 30000x8000 170 and 182, 4000x50000 160 and 173, 8000x24000 144 and 152.
+constexpr int64_t kSplitMinK = 512, kSplitMinOut = 64, kSplitMinLp = 32, kSplitMinA = 1 << 22;
 struct SplitPlan {
   int tile, groups, nt, nsplit, wgs;           // rows (columns of A) per workgroup, column groups, tiles per group, partial panels
   AnShape sh;                                  // an

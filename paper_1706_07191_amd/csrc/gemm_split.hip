@@ -592,8 +592,11 @@ bool split_fits(bool at, const float* A, int64_t out, int64_t K, int Lp, int64_t
   // byte offsets of a lane's loads: at most 255 rows and a row length, in 32 bits
   if (K < kSplitMinK || out < kSplitMinOut || Lp < kSplitMinLp || out * K < kSplitMinA || lda > (1 << 21)) return false;
   if (out > INT32_MAX || K > INT32_MAX) return false;
-  const bool aligned = lda % 4 == 0 && (uintptr_t)A % 16 == 0;
-  if (Lp < 48 && (at ? out : K) < kSplitLongRow && (!at || aligned)) return false;
+  if (Lp < 48) {                                         // both kernels are near the read of A: see common.h
+    const bool vectors = lda % 4 == 0 && (uintptr_t)A % 16 == 0, lines = lda % 32 == 0 && (uintptr_t)A % 128 == 0;
+    const bool few = out >= 8000 && K <= (out <= 20480 ? 6000 : 2048), many = out >= 14500 && K >= 20000;
+    if (at ? vectors && !few && !many : !lines || K < 14000 || out < 20000) return false;
+  }
   return pack_bytes >= pack_layout(out, K, Lp).bytes;
 }
 

@@ -12,8 +12,8 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = [  # rows, n, l, elements between A's rows beyond n, offset of A's base in elements
     (8200, 512, 33, 0, 0),       # shortest contraction of A X, 32 columns + 1
-    (530, 8001, 17, 0, 0),       # narrowest panel: both products from rows of 8000 on
-    (5003, 1001, 32, 0, 0),      # narrowest panel, short rows: A^T Q only
+    (530, 8001, 17, 0, 0),       # narrowest panel: A^T Q only, unaligned rows
+    (5003, 1001, 32, 0, 0),      # the same, short rows
     (513, 8200, 48, 0, 0),       # shortest contraction of A^T Q, not a multiple of its blocks
     (4097, 1031, 97, 0, 0),      # odd row length, one row more than whole tiles
     (2049, 2050, 160, 6, 1),     # ten column tiles (one column of waves), padded rows, odd base
@@ -23,6 +23,7 @@ SHAPES = [  # rows, n, l, elements between A's rows beyond n, offset of A's base
     (1100, 4000, 336, 0, 0),     # 21 column tiles: groups of 11 and 10
     (1025, 4100, 512, 0, 0),     # the largest sketch width
     (70000, 600, 110, 0, 0),     # more row tiles than workgroups: whole tiles and a cut leftover round
+    (20003, 14016, 17, 0, 0),    # narrowest panel, both products: long rows on lines
 ]
 
 

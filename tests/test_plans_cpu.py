@@ -107,9 +107,13 @@ def test_gemm_at_plan_tiles_every_block():
     (1, 8300, 511, 48, 511, 0, True), (1, 511, 8300, 48, 8300, 0, False),            # of A^T Q: rows
     (0, 64, 65536, 48, 65536, 0, True), (0, 63, 70000, 48, 70000, 0, False),         # rows of Y
     (0, 2048, 2048, 48, 2048, 0, True), (0, 2048, 2047, 48, 2047, 0, False),         # 4 M elements of A
-    (0, 60000, 20000, 16, 20000, 0, False), (0, 60000, 20000, 17, 20000, 0, True),   # 17 to 32 columns: long rows
-    (0, 76800, 2000, 32, 2000, 0, False), (1, 76800, 2000, 32, 2000, 0, False),
-    (1, 76800, 2000, 32, 2001, 0, True), (1, 76800, 2000, 32, 2000, 4, True),        # or, for A^T Q, unaligned ones
+    (0, 60000, 20000, 16, 20000, 0, False), (0, 60000, 20000, 17, 20000, 0, True),   # 17 to 32 columns, A X: long rows on lines
+    (0, 60000, 20000, 32, 20004, 0, False), (0, 60000, 20000, 32, 20000, 64, False), (0, 60000, 13984, 32, 13984, 0, False),
+    (0, 19999, 20000, 32, 20000, 0, False), (0, 76800, 2000, 32, 2000, 0, False),
+    (1, 76800, 2000, 32, 2000, 0, False), (1, 76800, 2000, 32, 2001, 0, True), (1, 76800, 2000, 32, 2000, 4, True),   # A^T Q: unaligned
+    (1, 6000, 8000, 32, 8000, 0, True), (1, 6001, 8000, 32, 8000, 0, False),         # rows, few
+    (1, 6000, 20484, 32, 20484, 0, False), (1, 2048, 20484, 32, 20484, 0, True),
+    (1, 20000, 14500, 32, 14500, 0, True), (1, 19999, 14500, 32, 14500, 0, False), (1, 20000, 14496, 32, 14496, 0, False),   # or many
     (0, 76800, 2000, 33, 2000, 0, True), (0, 3000, 3000, 110, (1 << 21) + 1, 0, False),
 ])
 def test_which_products_are_split(which, rows, n, l, lda, address, split):
