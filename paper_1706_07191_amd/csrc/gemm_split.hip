@@ -1,14 +1,13 @@
-// The two thin products of gemm_thin.hip for wide fp32 panels (more than 16 columns) on the bf16 matrix cores, with
-// every fp32 operand split exactly into three bf16 numbers:
+// The two thin products of gemm_thin.hip for wide fp32 panels over large A (more than 32 columns, and 17 to 32 where it pays; the rule
+// and what it was measured on: common.h) on the bf16 matrix cores, with every fp32 operand split exactly into three bf16 numbers:
 //
 //   a = h + m + l,   h = the upper 16 bits of a (8 significant bits), m = bf16(a - h), l = a - h - m
 //
 // (24 significant bits = 8 + 8 + 8, so nothing of a is lost from 2^-110 on; l of a smaller number would have bits below 2^-133,
-// where bf16 ends.  Rows of A or columns of a panel with no larger element are multiplied in fp32 after all, see k_split_repair_an.)
-// Of the nine products of two such
-// sums the six above 2^-24 are taken, l*h + h*l + m*m + m*h + h*m + h*h: six v_mfma_f32_16x16x32_bf16 do the work of
-// eight v_mfma_f32_16x16x4_f32 in 96 cycles instead of 256.  The dropped products are below 2^-22 of |a||x| at most and
-// 2^-26 on average, and random in sign.
+// where bf16 ends.  Rows of A or columns of a panel with no larger element are multiplied in fp32 after all: k_split_repair_an.)
+// Of the nine products of two such sums the six above 2^-24 are taken, l*h + h*l + m*m + m*h + h*m + h*h: six
+// v_mfma_f32_16x16x32_bf16 do the work of eight v_mfma_f32_16x16x4_f32 in 96 cycles instead of 256.  The dropped products are
+// below 2^-22 of |a||x| at most and 2^-26 on average, and random in sign.
 //
 // Accuracy.  The bf16 instruction truncates its sum to fp32 instead of rounding it, which over a long contraction
 // would add up to a bias (K = 20000, entries N(0.5, 1): 5e-6, against 2.2e-6 for the fp32 instruction).  So the six
@@ -16,7 +15,9 @@
 // products first -- only the last one can truncate anything that matters -- and that tile is added to the
 // running sum by rounded fp32 additions.  That makes K/32 additions where the fp32 instruction makes K/4 or more:
 // measured error against fp64, this kernel and the fp32 instruction: K = 112 6.1e-8 and 1.9e-7, K = 1000 1.2e-7
-// and 5.5e-7, K = 20000 4.7e-7 and 2.5e-6 (N(0,1) entries); K = 20000, N(0.5,1): 3.8e-7 and 2.2e-6.
+// and 5.5e-7, K = 20000 4.7e-7 and 2.5e-6 (N(0,1) entries); K = 20000, N(0.5,1): 3.8e-7 and 2.2e-6.  Where a sum has few terms
+// there are no additions to save, and the truncation shows: one entry in a row of A 4.1e-8 and 2.5e-8 (the rounding of a
+// single product), one in a hundred (K = 1000 and 4000) 7.1e-8 and 5.4e-8, 9.9e-8 and 7.3e-8.
 //
 // Both products are one kernel.  The contraction runs over blocks of 32 (columns of A for Y = A X, rows of A for
 // Z = A^T Q); the right panel is split once per call into the operand layout of the instruction (k_split_pack), A is
@@ -566,7 +567,8 @@ k_split_repair_at(SplitRepair p, float* __restrict__ Zpart, int64_t ldz, int64_t
 // ---- host side --------------------------------------------------------------------------------------------------
 struct SplitCfg { int wr, wc, tile; };
 constexpr int kSplitMT = 2;
-// Up to ten column tiles one wave holds them all (accumulators of 2 x 10 tiles: 234 registers of 256); wider panels take
+// Up to ten column tiles one wave holds them all (accumulators of 2 x 10 tiles: 230 registers of 256 for
+// A^T Q; A X takes all of them and, with 9, 10, 14, 16 and 17 tiles, 12 to 24 places in scratch); wider panels take
 // two columns of waves, i.e. half as many rows per workgroup.
 static SplitCfg split_cfg(int nt) {
   return nt <= 10 ? SplitCfg{8, 1, 8 * kSplitMT * 16} : SplitCfg{4, 2, 4 * kSplitMT * 16};
