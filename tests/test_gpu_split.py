@@ -190,3 +190,24 @@ def test_split_products_of_small_rows_and_columns(rows, n, l, pad, off):
         bound = np.sqrt(a.shape[1]) * EPS32 * size + 2.0 ** -149 * a.shape[1]
         assert bool((err <= bound).all())
         assert bool((got[ref == 0] == 0).all())
+
+
+def test_split_products_with_more_workgroups_than_flags():
+    """Workgroups from 4096 on share the flag of an earlier one: neither is missed, neither redoes what is right."""
+    dev = need_gpu()
+    rows, n, l = 1050000, 512, 33                        # 4102 row tiles
+    A, X, _ = _inputs(rows, n, l, 0, 0, dev)
+    bad = {5: float("inf"), 256 * 4096 + 7: float("nan"), 256 * 4000: float("-inf")}
+    for row, v in bad.items():
+        A[row, 6] = v
+    A[256 * 4098 + 1] *= 1e-36
+    X[6] = 1.0
+    Y = B.brsvd_gemm_an(A, X)
+    for row, v in bad.items():
+        assert bool((Y[row] == v).all()) if v == v else bool(Y[row].isnan().all())
+    ok = torch.ones(rows, dtype=torch.bool, device=dev)
+    ok[list(bad)] = False
+    for r0 in range(0, rows, 150000):
+        a, y, keep = A[r0:r0 + 150000], Y[r0:r0 + 150000], ok[r0:r0 + 150000]
+        err = (y.double() - a.double() @ X.double()).abs()[keep]
+        assert bool((err <= _bound(n, a, X)[keep]).all())
