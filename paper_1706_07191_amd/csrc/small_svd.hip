@@ -288,7 +288,8 @@ k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __re
 // Row rotations stay ahead (us of a call of brsvd_small_svd, this against row rotations)
 //   up to 20 rows, where the 31 steps of a sweep are more than their l: l = 4 85 / 44, 8 113 / 65, 12 114 / 84, 16 128 / 105, 18
 //   132 / 116 to 129, 20 132 / 120 to 133; on the other side 21 133 / 127 to 141, 22 120 to 134 / 140, 24 133 / 146, 30 135 / 170;
-//   and with three or five blocks, where a padding block goes round with the others: l = 33 367 / 236, 48 354 / 296, 72 654 / 567;
+//   and with three or five blocks, where a padding block goes round with the others: l = 33 293 / 224, 48 331 / 286, 72
+//   538 / 507, 80 539 / 551;
 //   on the other side 49 336 / 348, 56 336 / 341, 64 338 / 415, 81 612 / 709, 96 552 / 797, 128 877 / 1420.
 // What bounds it: the latency of a step, 800 to 900 cycles from barrier to barrier, half of it the rotation; the matrix products
 // take 5 to 9 thousand cycles of a round beside the 14 thousand of the steps (l = 160, 272).  Measured (us per call, row rotations, one
