@@ -179,8 +179,8 @@ int main() {
     const int nblk2 = 2 * (int)uniform(2, 16), P = nblk2 / 2, rounds = nblk2 - 1, max_sweeps = 5;
     const int sweeps = (int)uniform(1, max_sweeps), resident = (int)uniform(1, P);
     const bool settles = sweeps < max_sweeps || uniform(0, 1) == 1;
-    struct Group { int ticket, stage; };                 // stage 0: no ticket, 1: waits, 2: at work, 3: left
-    std::vector<Group> wg(P, Group{0, 0});
+    struct Group { int ticket, next, stage; };           // stage 0: no ticket, 1: waits, 2: at work with the next ticket drawn, 3: left
+    std::vector<Group> wg(P, Group{0, 0, 0});
     std::vector<int> turned(max_sweeps * rounds * P, 0), ended(4, 0);
     int taken = 0, done = 0, last = 0, left = 0;
     bool stuck = false;
@@ -195,12 +195,13 @@ int main() {
       Group& g = wg[ready[uniform(0, (int)ready.size() - 1)]];
       const brsvd::JacobiTicket k = brsvd::jacobi_ticket(g.ticket, nblk2);
       if (g.stage == 0) {
-        g = Group{taken++, 1};
+        g = Group{taken++, 0, 1};
       } else if (g.stage == 1) {
         const int what = brsvd::jacobi_work(k, last, max_sweeps);
         ++ended[what];
         g.stage = what == brsvd::JACOBI_END ? 3 : 2;
         left += g.stage == 3;
+        if (g.stage == 2) g.next = taken++;
         if (what == brsvd::JACOBI_ROTATE) {
           CHECK(k.sweep < sweeps && done >= (k.sweep * rounds + k.round) * P && done < (k.sweep * rounds + k.round + 1) * P);
           ++turned[(k.sweep * rounds + k.round) * P + k.pair];
@@ -210,7 +211,7 @@ int main() {
         }
       } else {
         ++done;
-        g.stage = 0;
+        g = Group{g.next, 0, 1};
       }
     }
     CHECK(!stuck && left == P && ended[brsvd::JACOBI_RANKS] == P);

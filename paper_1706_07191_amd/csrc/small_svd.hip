@@ -51,10 +51,10 @@ __device__ __forceinline__ double rcp_nr(double x) {
 // With results delivered in single precision the bar is lower: a last sweep whose largest cosine was below
 // kSettledF32 leaves cosines of the order l * kSettledF32^2 = 1e-8, an order of magnitude below what the fp32
 // lifts U = Q V_R and V = W_B U_R can show, and that saves one sweep of the seven to eight an l of 100 to 300 takes.
-// Row rotations of more than 20 rows skip pairs whose cosine is below kTolRows (a skipped rotation saves its traffic).  On the 32 x 32
-// Gram matrix a rotation costs the same whether it turns or not, and on up to 20 rows hardly more (1 %), so everything above
-// rounding is rotated there.
-constexpr double kTolRows = 1e-13, kTolBlocks = 1e-16;
+// Row rotations of more than 16 rows skip pairs whose cosine is below kTolRows (a skipped rotation saves its traffic).  On up to 16 rows
+// a rotation costs hardly more than its inner products (1 %), and everything above rounding is rotated.  On the 32 x 32 Gram matrix it
+// costs the same whether it turns or not: there is no bar.
+constexpr double kTolRows = 1e-13, kTolOneBlock = 1e-16;
 constexpr double kSettled = 1e-8;
 constexpr double kSettledF32 = 1e-5;
 // Rotation (c, s) that makes two rows with squared norms al, be and inner product ga orthogonal:
@@ -137,7 +137,7 @@ __device__ __forceinline__ double row8_sum(double v) {
   return v;
 }
 
-// ---- up to 20, 33 to 48 and 65 to 80 rows: row rotations in LDS -------------------------------------------------------------------------
+// ---- up to 16 and 33 to 40 rows: row rotations in LDS ---------------------------------------------------------------------------------
 // Each group of 16 lanes owns one row pair per step, so a wave handles 4 pairs with one instruction stream and up to
 // 64 pairs take 1024 threads.  EPL = elements of a row per lane = ceil(l / 16).
 // Pair schedule of a sweep (every pair of rows met exactly once): the index range is halved
@@ -285,23 +285,29 @@ k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __re
 // 16 disjoint pairs), the others the 256 pairs across the two blocks (16 steps).
 //   l <= 32: one block pair, rows in LDS for all sweeps (k_jacobi_small);
 //   otherwise: one workgroup per block pair, rows in global memory, one launch (k_jacobi_rounds).
-// Row rotations stay ahead (us of a call of brsvd_small_svd, this against row rotations)
-//   up to 20 rows, where the 31 steps of a sweep are more than their l: l = 4 85 / 44, 8 113 / 65, 12 114 / 84, 16 128 / 105, 18
-//   132 / 116 to 129, 20 132 / 120 to 133; on the other side 21 133 / 127 to 141, 22 120 to 134 / 140, 24 133 / 146, 30 135 / 170;
-//   and with three or five blocks, where a padding block goes round with the others: l = 33 293 / 224, 48 331 / 286, 72
-//   538 / 507, 80 539 / 551;
-//   on the other side 49 336 / 348, 56 336 / 341, 64 338 / 415, 81 612 / 709, 96 552 / 797, 128 877 / 1420.
-// What bounds it: the latency of a step, 800 to 900 cycles from barrier to barrier, half of it the rotation; the matrix products
-// take 5 to 9 thousand cycles of a round beside the 14 thousand of the steps (l = 160, 272).  Measured (us per call, row rotations, one
-// workgroup or a launch per round, and this): l = 30 170 -> 135, 64 415 -> 338, 128 1420 -> 877, 160 2658 -> 1204, 240 4895 -> 2518,
-// 512 13716 -> 8631.  Two accumulator chains per product: four gain 2 % at l <= 32 and lose 6 % above 128.
+// Row rotations stay ahead (us of the kernels of a call on an R of the range finder / of a panel with a geometric spectrum, this
+// against row rotations)
+//   up to 16 rows, where the 31 steps of a sweep are more than their l: l = 4 41 / 19 and 52 / 22, 8 52 / 32 and 77 / 42, 12 53 / 46 and
+//   75 / 62, 14 54 / 52 and 76 / 61, 16 54 / 54 and 76 / 74; on the other side 17 66 / 80 and 77 / 93, 20 67 / 84 and 78 / 98;
+//   and with three blocks up to 40 rows, where a fourth block goes round that is padding: l = 33 169 / 154 and 259 / 204, 36 170 / 160
+//   and 230 / 215, 40 170 / 173 and 231 / 230; on the other side 44 171 / 189 and 261 / 250, 48 171 / 199 and 232 / 263.
+// (One sweep more or less, 28 us at l = 33 to 48, is by chance.)
+// What bounds it: the latency of a step, 640 cycles from barrier to barrier -- 130 until the rotations are read from LDS, 60 for the
+// new inner product, 190 for the 13 dependent operations of the rotation, the rest its way back to LDS -- and of the meeting of the
+// workgroups.  At l = 110 a round takes 25 thousand cycles: 11.2 the 16 steps, 3.2 the Gram matrix, 4.1 J^T times the rows, 2.5 the load
+// of the rows and 3.7 the meeting (it was 29.7: 15.6, 4.9, 4.0, 2.2 and 4.7).  What made the difference: the matrix instructions
+// accumulate in vector registers, for which the kernel must ask for two waves per SIMD (with one, the compiler keeps accumulators in the
+// other half of the register file and moves all 16 of them to and fro around every four products); J on waves of its own;
+// a step without branches; a shorter chain; a ticket drawn ahead, one acquire for all waves (each costs 250 cycles).
+// Measured (us of the kernels, before and now): l = 24 68 -> 57, 30 85 -> 70, 48 199 -> 171 (row rotations before), 64 245 -> 206, 72 367 ->
+// 329 (row rotations before), 97 555 -> 447, 110 558 -> 451, 128 580 -> 464, 160 1312 -> 1040, 272 2197 -> 1686, 400 6078 -> 4454.
 constexpr int kJB = 16;
 constexpr int kJN = 2 * kJB;                      // rows of a block pair
-constexpr int kRowsMaxL = 20;                     // up to here, row rotations
+constexpr int kRowsMaxL = 16, kRowsMaxL3 = 40;    // up to here, row rotations: with one block, with three
 // Place of entry (x, y) of the Gram matrix and of J: odd rows have their halves exchanged, so that the two rows of 16
 // consecutive columns that half a wave touches, and 16 consecutive diagonal entries, lie on distinct banks.
 __device__ __forceinline__ int jat(int x, int y) { return x * kJN + (y ^ ((x & 1) << 4)); }
-constexpr int kJThreads = 256;                    // threads per block pair: (i, j) = pairs of rows
+constexpr int kJThreads = 512;                    // threads per block pair: two per pair (i, j) of pairs of rows, for the Gram matrix and for J
 constexpr int kJWork = 3 * kJN * kJN + 128;       // doubles of LDS per block pair: two Gram buffers, J, rotations
 
 __device__ __forceinline__ doublex4 mfma_f64(double a, double b, doublex4 c) {
@@ -312,24 +318,35 @@ __device__ __forceinline__ doublex4 mfma_f64(double a, double b, doublex4 c) {
 // angle, t = 2 ga / (tau +- sqrt(tau^2 + 4 ga^2)), tau = be - al.  The denominator is worked out in single precision: that only
 // leaves 1e-7 of the inner product, while c and s, which have to be orthogonal, follow from t in double.  The numerator stays
 // in double: rows whose norms are more than 2^126 apart need a t below the single-precision range.
-// Identity when |ga| <= tol * sqrt(al * be); big: above the settled bar.  Returns t.
-__device__ __forceinline__ double rotation(double al, double be, double ga, double tol2, double settled2, double& c,
-                                           double& s, bool& big) {
-  const double gg = ga * ga, ab = al * be;
-  big = gg > settled2 * ab;
-  const bool rot = gg > tol2 * ab;
-  const double tau = be - al, g2 = 2.0 * ga;
-  const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(tau), fabs(g2)));
-  const double gd = __builtin_amdgcn_ldexp(g2, ex);
-  const float tf = (float)__builtin_amdgcn_ldexp(tau, ex), gf = (float)gd;
-  const float inv = copysignf(__builtin_amdgcn_rcpf(fabsf(tf) + __builtin_amdgcn_sqrtf(fmaf(tf, tf, gf * gf))), tf);
-  // c = 1 / sqrt(1 + t^2) from a single-precision seed by one step of third order (2^-22 -> below 2^-64)
-  const double t = rot ? gd * (double)inv : 0.0;
-  const float ts = rot ? gf * inv : 0.f;
-  const double x = fma(t, t, 1.0), y = (double)__builtin_amdgcn_rsqf(fmaf(ts, ts, 1.f));
-  const double e = fma(-x * y, y, 1.0);
-  c = fma(y, e * fma(e, 0.375, 0.5), y);
-  s = c * t;
+// Everything is scaled by the power of two of the larger norm.  It bounds the inner product, so the scaling and all else that does
+// not depend on ga is ready before ga is (RotationOf), and 13 dependent operations lead from ga to (c, s).
+// Two rows of norm zero, or of one norm and a product below 1e-18 of it, have a denominator of 1e-18 at least, and |t| <= 1.
+struct RotationOf {
+  double eight, ab;       // 8 / 2^e with the sign of tau, 2^e the power of two of the larger norm; 64 al be / 2^(2 e)
+  float tf, hh;           // 4 |tau| / 2^e and its square
+};
+// The power of two of a squared norm, kept where 8 / 2^e is a normal number: its biased exponent (a norm that rounding has made
+// negative counts as zero).
+__device__ __forceinline__ int norm_exponent(double al) { return min(max(__double2hiint(al) >> 20, 3), 2046); }
+__device__ __forceinline__ RotationOf rotation_of(double al, int eal, double be, int ebe) {
+  const int hi = (2049 - max(eal, ebe)) << 20;
+  const double four = __hiloint2double(hi - (1 << 20), 0), as = al * four, bs = be * four, tau = bs - as;
+  const float tf = fabsf((float)tau);
+  return RotationOf{__hiloint2double(hi | (__double2hiint(tau) & 0x80000000), 0), 4.0 * as * bs, tf, fmaf(tf, tf, 1e-36f)};
+}
+// big: |ga| above the settled bar.  Returns t.
+__device__ __forceinline__ double rotation(const RotationOf& p, double ga, double settled2, double& c, double& s, bool& big) {
+  const double gd = ga * p.eight;                          // 8 ga / 2^e
+  big = gd * gd > settled2 * p.ab;
+  const float gf = (float)gd;
+  const float inv = __builtin_amdgcn_rcpf(p.tf + __builtin_amdgcn_sqrtf(fmaf(gf, gf, p.hh)));
+  const double t = gd * (double)inv;
+  // c = 1 / sqrt(1 + t^2) from a single-precision seed y by one step of third order (2^-22 -> below 2^-64)
+  const float ts = gf * inv;
+  const double y = (double)__builtin_amdgcn_rsqf(fmaf(ts, ts, 1.f)), ty = t * y;
+  const double e = fma(-ty, ty, fma(-y, y, 1.0)), w = fma(0.375 * e, e, 0.5 * e);
+  c = fma(y, w, y);
+  s = fma(ty, w, ty);
   return t;
 }
 
@@ -346,111 +363,149 @@ __device__ __forceinline__ double next_lane(double v, int lane) {
   else return v;
 }
 
-// The four waves of a block pair form the Gram matrix of its rows in G; row(x) is the LDS address of row x, cols (a multiple of
-// 16) its length.
+// The eight waves of a block pair form the Gram matrix of its rows in buffer 0 of work; row(x) is the LDS address of row x, cols (a
+// multiple of 16) its length.  It is symmetric: three tiles.  A matrix instruction of this kind keeps its SIMD busy for 64 cycles or
+// more, so the work is dealt out evenly over the SIMDs: the first three quarters of the columns go to one SIMD for each tile, shared
+// by its two waves w and w + 4, and the last quarter of all three tiles to wave 3 on the fourth.
 template <typename Row>
-__device__ __forceinline__ void gram_32(Row row, int cols, double* G, int t) {
-  const int lane = t & 63, w = t >> 6, r = lane & 15, g = lane >> 4;
-  if (w == 3) return;                                    // three tiles: the matrix is symmetric
-  const double *lo = row((w == 2 ? kJB : 0) + r), *hi = row((w == 0 ? 0 : kJB) + r);
-  doublex4 acc[2];
-  acc[0] = acc[1] = doublex4{0.0, 0.0, 0.0, 0.0};
-  // the operands of the next 16 columns are read while the products of these 16 run
-  double x[4], y[4];
+__device__ __forceinline__ void gram_32(Row row, int cols, double* work, int t) {
+  const int lane = t & 63, w = t >> 6, r = lane & 15, g = lane >> 4, q = w & 3, m = cols / 16;
+  doublex4 acc[3];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) { x[q] = lo[4 * q + g]; y[q] = hi[4 * q + g]; }
-  for (int k = 0; k < cols; k += 16) {
-    const int kn = k + 16 < cols ? k + 16 : k;
-    double xn[4], yn[4];
+  for (int k = 0; k < 3; ++k) acc[k] = doublex4{0.0, 0.0, 0.0, 0.0};
+  double* part = work + kJN * kJN + lane;        // partial tiles: those of waves 4, 5, 6, then the three of wave 3
+  if (q < 3) {
+    const double *lo = row((q == 2 ? kJB : 0) + r) + g, *hi = row((q == 0 ? 0 : kJB) + r) + g;
+    const int mid = 3 * m / 2, end = w < 4 ? mid : 3 * m;
+    int k = w < 4 ? 0 : mid;
+    for (; k + 2 <= end; k += 2) {
+      const double x0 = lo[4 * k], x1 = lo[4 * k + 4], y0 = hi[4 * k], y1 = hi[4 * k + 4];
+      acc[0] = mfma_f64(x0, y0, acc[0]);
+      acc[1] = mfma_f64(x1, y1, acc[1]);
+    }
+    if (k < end) acc[0] = mfma_f64(lo[4 * k], hi[4 * k], acc[0]);
+    acc[0] += acc[1];
+    if (w >= 4) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) { xn[q] = lo[kn + 4 * q + g]; yn[q] = hi[kn + 4 * q + g]; }
-    __builtin_amdgcn_sched_barrier(0);
+      for (int v = 0; v < 4; ++v) part[256 * q + 64 * v] = acc[0][v];
+    }
+  } else if (w == 3) {
+    const double *lo = row(r) + g, *hi = row(kJB + r) + g;
+    for (int k = 3 * m; k < 4 * m; ++k) {
+      const double x = lo[4 * k], y = hi[4 * k];
+      acc[0] = mfma_f64(x, x, acc[0]);
+      acc[1] = mfma_f64(x, y, acc[1]);
+      acc[2] = mfma_f64(y, y, acc[2]);
+    }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) acc[q & 1] = mfma_f64(x[q], y[q], acc[q & 1]);
+    for (int k = 0; k < 3; ++k)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) { x[q] = xn[q]; y[q] = yn[q]; }
+      for (int v = 0; v < 4; ++v) part[768 + 256 * k + 64 * v] = acc[k][v];
   }
+  __syncthreads();
+  if (w < 3) {
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int x = (w == 2 ? kJB : 0) + g + 4 * v, y = (w == 0 ? 0 : kJB) + r;
-    const double s = acc[0][v] + acc[1][v];
-    G[jat(x, y)] = s;
-    if (w == 1) G[jat(y, x)] = s;
+    for (int v = 0; v < 4; ++v) {
+      const int x = (w == 2 ? kJB : 0) + g + 4 * v, y = (w == 0 ? 0 : kJB) + r;
+      const double s = (acc[0][v] + part[256 * w + 64 * v]) + part[768 + 256 * w + 64 * v];
+      work[jat(x, y)] = s;
+      if (w == 1) work[jat(y, x)] = s;
+    }
   }
 }
 
 // The 32 rows in groups of 2 H: rotates all pairs of a row of the first half of a group with a row of its second half, in H steps
 // (row x of the one with row (x + step) mod H of the other), on the Gram matrix in buffer 0 of work, and updates J (fresh: J is
-// the identity so far).  Everything but the rotations lives in registers: thread (i, j) holds the 2 x 2 block of the pairs
-// i and j and two rows of J.  From one step to the next the rows of the second halves move up by one pair, i.e. columns come
+// the identity so far).  Everything but the rotations lives in registers: the first 256 threads hold the 2 x 2 blocks of the pairs
+// i and j, the others two rows of J each.  From one step to the next the rows of the second halves move up by one pair, i.e. columns come
 // from the next lane and rows through LDS from the thread of the next pair.  The thread (i, i) works out the next rotation of
 // pair i as soon as it has the new inner product: the squared norms follow from those before, al - t ga and be + t ga, so
-// a step is one read, four multiply-adds, the rotation and one write between two barriers.  store: the Gram matrix is left in
+// a step is one read, two multiplications and two multiply-adds, the rotation and one write between two barriers.  store: the Gram matrix is left in
 // buffer 0.  Every thread of the workgroup calls it; the caller's barriers separate it from what is around it.
 // Returns whether a rotation was above the settled bar.
 template <int H>
-__device__ __forceinline__ bool cross_pairs(double* work, int t, bool fresh, bool store, double tol2, double settled2) {
-  const int i = t >> 4, j = t & 15, up = (i & ~(H - 1)) | ((i + 1) & (H - 1));
+__device__ __forceinline__ bool cross_pairs(double* work, int t, bool fresh, bool store, double settled2) {
+  const int i = (t >> 4) & 15, j = t & 15, up = (i & ~(H - 1)) | ((i + 1) & (H - 1));
   auto top = [](int k) { return (k & ~(H - 1)) + k; };       // 2 H (k / H) + k mod H; the partner at step 0 is H rows below
   double* G = work;
   double2* T = (double2*)(work + kJN * kJN);                 // two buffers of 256
   double* J = work + 2 * kJN * kJN;
-  double* S = J + kJN * kJN;                                 // two buffers of 16 x {c, s, be, unused}
+  double2* C = (double2*)(J + kJN * kJN);                    // two buffers of 16 x {c, s}
+  double2* B = C + 32;                                       // two buffers of 16 x {squared norm, its exponent} of the second rows
+  if (t >= 256) {
+    const int f0 = jat(i, top(j)), f1 = jat(i, top(j) + H), h0 = f0 + kJB * kJN, h1 = f1 + kJB * kJN;   // rows i, 16 + i
+    double p0, p1, q0, q1;
+    if (fresh) {
+      p0 = top(j) == i; p1 = top(j) + H == i; q0 = top(j) == kJB + i; q1 = top(j) + H == kJB + i;
+    } else {
+      p0 = J[f0]; p1 = J[f1]; q0 = J[h0]; q1 = J[h1];
+    }
+    __syncthreads();
+    auto move = [&](int buf) {
+      const double2 rj = C[buf + j];
+      const double u = rj.y * p0 + rj.x * p1, w = rj.y * q0 + rj.x * q1;
+      p0 = rj.x * p0 - rj.y * p1;
+      q0 = rj.x * q0 - rj.y * q1;
+      p1 = next_lane<H>(u, j);
+      q1 = next_lane<H>(w, j);
+      __syncthreads();
+    };
+#pragma unroll 1
+    for (int step = 0; step + 1 < H; step += 2) { move(0); move(16); }
+    if (H == 1) move(0);
+    // H moves have brought every column home
+    J[f0] = p0;
+    J[f1] = p1;
+    J[h0] = q0;
+    J[h1] = q1;
+    return false;
+  }
   const int e0 = jat(top(i), top(j)), e1 = jat(top(i), top(j) + H);
   const int e2 = jat(top(i) + H, top(j)), e3 = jat(top(i) + H, top(j) + H);
-  const int f0 = jat(i, top(j)), f1 = jat(i, top(j) + H), h0 = f0 + kJB * kJN, h1 = f1 + kJB * kJN;   // rows i, 16 + i
   double a = G[e0], b = G[e1], bt = G[e2], cc = G[e3];
-  double p0, p1, q0, q1;
-  if (fresh) {
-    p0 = top(j) == i; p1 = top(j) + H == i; q0 = top(j) == kJB + i; q1 = top(j) + H == kJB + i;
-  } else {
-    p0 = J[f0]; p1 = J[f1]; q0 = J[h0]; q1 = J[h1];
-  }
   const bool diag = i == j;
   bool any = false;
   double al = a;
-  auto next_rotation = [&](double be, double ga, double* Sn) {
+  int eal = norm_exponent(al);
+  T[16 * up + j] = double2{bt, cc};                          // where step 0 looks for them
+  auto next_rotation = [&](const RotationOf& of, double be, double ga, int buf) {
     double c, s;
     bool big;
-    const double tg = rotation(al, be, ga, tol2, settled2, c, s, big) * ga;
+    const double tg = rotation(of, ga, settled2, c, s, big) * ga;
     any |= big && diag;
     al -= tg;
+    eal = norm_exponent(al);
+    double be_new = be + tg;
+    int ebe = norm_exponent(be_new);
+    asm volatile("" : "+v"(c), "+v"(s), "+v"(be_new), "+v"(ebe));      // before the branch, not in it
     if (diag) {
-      *(double2*)(Sn + 4 * i) = double2{c, s};
-      Sn[4 * i + 2] = be + tg;
+      C[buf + i] = double2{c, s};
+      B[buf + i] = double2{be_new, __hiloint2double(ebe, 0)};
     }
   };
-  next_rotation(cc, b, S);
+  next_rotation(rotation_of(al, eal, cc, norm_exponent(cc)), cc, b, 0);
   __syncthreads();
-#pragma unroll 1
-  for (int step = 0; step < H; ++step) {
-    const double* Sc = S + (step & 1) * 64;
-    const double2 rj = *(const double2*)(Sc + 4 * j), ri = *(const double2*)(Sc + 4 * i);
-    const double be = Sc[4 * up + 2];
-    if (step > 0) {
-      const double2 v = T[(step & 1) * 256 + 16 * up + j];
-      bt = v.x;
-      cc = v.y;
-    }
+  // One step.  The chain that everything waits for -- the rotations read, the new inner product, the next rotation,
+  // its store -- comes without a branch, so that the compiler lays the rest of the step into its gaps.
+  auto move = [&](int buf, bool more) {
+    const double2 rj = C[buf + j], ri = C[buf + i], be = B[buf + up];
+    const double2 v = T[16 * (buf + up) + j];
+    bt = v.x;
+    cc = v.y;
+    const RotationOf of = rotation_of(al, eal, be.x, __double2hiint(be.y));
     const double x0 = rj.x * a - rj.y * b, x1 = rj.y * a + rj.x * b;
     const double y0 = rj.x * bt - rj.y * cc, y1 = rj.y * bt + rj.x * cc;
     b = next_lane<H>(ri.x * x1 - ri.y * y1, j);
-    if (step + 1 < H) next_rotation(be, b, S + ((step & 1) ^ 1) * 64);
     a = ri.x * x0 - ri.y * y0;
-    T[((step & 1) ^ 1) * 256 + t] = double2{ri.y * x0 + ri.x * y0, next_lane<H>(ri.y * x1 + ri.x * y1, j)};
-    const double u = rj.y * p0 + rj.x * p1, v = rj.y * q0 + rj.x * q1;
-    p0 = rj.x * p0 - rj.y * p1;
-    q0 = rj.x * q0 - rj.y * q1;
-    p1 = next_lane<H>(u, j);
-    q1 = next_lane<H>(v, j);
+    T[16 * (buf ^ 16) + t] = double2{ri.y * x0 + ri.x * y0, next_lane<H>(ri.y * x1 + ri.x * y1, j)};
+    if (more) next_rotation(of, be.x, b, buf ^ 16);
     __syncthreads();
-  }
-  // H moves have brought every row and column home
-  J[f0] = p0;
-  J[f1] = p1;
-  J[h0] = q0;
-  J[h1] = q1;
-  if (store) {
+  };
+#pragma unroll 1
+  for (int step = 0; step + 2 < H; step += 2) { move(0, true); move(16, true); }
+  if (H > 1) move(0, true);
+  move(H > 1 ? 16 : 0, false);
+  if (store) {                                               // H moves have brought every row and column home
     const double2 v = T[(H & 1) * 256 + 16 * up + j];
     G[e0] = a;
     G[e1] = b;
@@ -461,20 +516,20 @@ __device__ __forceinline__ bool cross_pairs(double* work, int t, bool fresh, boo
 }
 
 // One sweep of rotations on the Gram matrix in buffer 0 of work: all pairs of the 32 rows, or those across the two blocks.
-__device__ __forceinline__ bool sweep_32(double* work, int t, bool all, double tol2, double settled2) {
+__device__ __forceinline__ bool sweep_32(double* work, int t, bool all, double settled2) {
   bool any = false;
   __syncthreads();
   if (all) {
-    any |= cross_pairs<8>(work, t, true, true, tol2, settled2);
+    any |= cross_pairs<8>(work, t, true, true, settled2);
     __syncthreads();
-    any |= cross_pairs<4>(work, t, false, true, tol2, settled2);
+    any |= cross_pairs<4>(work, t, false, true, settled2);
     __syncthreads();
-    any |= cross_pairs<2>(work, t, false, true, tol2, settled2);
+    any |= cross_pairs<2>(work, t, false, true, settled2);
     __syncthreads();
-    any |= cross_pairs<1>(work, t, false, true, tol2, settled2);
+    any |= cross_pairs<1>(work, t, false, true, settled2);
     __syncthreads();
   }
-  any |= cross_pairs<16>(work, t, !all, false, tol2, settled2);
+  any |= cross_pairs<16>(work, t, !all, false, settled2);
   __syncthreads();
   return any;
 }
@@ -504,9 +559,9 @@ __device__ __forceinline__ void apply_32(Row row, const double* J, int c0, int l
 static constexpr size_t jacobi_lds_bytes(int Lp) { return sizeof(double) * ((size_t)kJN * (Lp + 2) + kJWork); }
 
 // Up to 32 rows: one workgroup, one block pair.
-__global__ void __launch_bounds__(kJThreads)
+__global__ void __launch_bounds__(kJThreads, 2)
 k_jacobi_small(const double* __restrict__ R, int ldr, int l, int Lp, double* __restrict__ Wg, double* __restrict__ sig,
-               int* __restrict__ info, const int* __restrict__ breakdown_flag, double tol, double settled) {
+               int* __restrict__ info, const int* __restrict__ breakdown_flag, double settled) {
   extern __shared__ __align__(16) double W[];
   __shared__ int rotated;
   __shared__ int order_sh[kJN];
@@ -539,8 +594,8 @@ k_jacobi_small(const double* __restrict__ R, int ldr, int l, int Lp, double* __r
     if (t == 0) rotated = 0;
     __syncthreads();
     gram_32(row, Lp, work, t);
-    if (sweep_32(work, t, true, tol * tol, settled * settled)) rotated = 1;
-    for (int c0 = kJB * (t >> 6); c0 < Lp; c0 += 4 * kJB)
+    if (sweep_32(work, t, true, settled * settled)) rotated = 1;
+    for (int c0 = kJB * (t >> 6); c0 < Lp; c0 += (kJThreads / 64) * kJB)
       apply_32(row, work + 2 * kJN * kJN, c0, t & 63, [&](int x, int c, double v) { row(x)[c] = v; });
     __syncthreads();
     ++sweeps;
@@ -591,6 +646,7 @@ k_jacobi_init(const double* __restrict__ R, int ldr, int l, int Lp, double* __re
 // k_jacobi_rounds) and need some 30 us; the limit only makes sure that every wait ends (the call then reports that the
 // iteration did not converge).
 constexpr unsigned long long kMeetTicks = 2000000000ull;
+constexpr int kWaitStores = 0x0f70;              // s_waitcnt: no vector memory operation outstanding, the other counters as they are
 
 // The 32 rows of the block pair at rows rI and rJ of W, to LDS; rows from l on are zero.  64 H columns at a time are under way.
 template <int H>
@@ -618,47 +674,52 @@ __device__ __forceinline__ void load_pair(const double* W, int l, int Lp, int rI
 
 // All sweeps in one launch.  The workgroups (nblk2 / 2 of them; any number will do) take tickets in order, one after the other, and
 // start on one when all tickets of the rounds before are done.  A workgroup therefore only waits for lower tickets, which
-// others have taken that are running, and the lowest of these waits for nothing: the iteration goes on however few of the
-// workgroups find room on the device, on a stream with a few CUs or beside kernels that fill the rest.
+// running ones hold, and the lowest of these waits for nothing: the iteration goes on however few of the workgroups find room on
+// the device, on a stream with a few CUs or beside kernels that fill the rest.
+// A ticket is drawn while the one before it is worked on.  A workgroup works through its tickets in their order, so the lowest
+// unfinished one is still always at work or about to be.
 // The rows travel through global memory between rounds; they are stored at the scope of the device, past the L2 of an XCD, which
 // leaves the releases at a meeting little to write back (2 to 4 % of the whole).  With a launch per round, and the host looking at the
 // convergence flag, l = 160 took 1980 us and 272 4280 us.  Eight times the workgroups with all but every eighth leaving at
 // once, to keep the rest on one XCD, gains 5 % below 128 and loses up to 13 % above.
-__global__ void __launch_bounds__(kJThreads)
-k_jacobi_rounds(const double* R, int ldr, double* W, int l, int Lp, int nblk2, double tol, double settled, double* sig, int* info) {
+__global__ void __launch_bounds__(kJThreads, 2)
+k_jacobi_rounds(const double* R, int ldr, double* W, int l, int Lp, int nblk2, double settled, double* sig, int* info) {
   extern __shared__ __align__(16) double sh[];
   __shared__ int next, state;
   const int t = threadIdx.x, ld = Lp + 2;
   if (info[4]) return;
   double* work = sh + kJN * ld;
   auto row = [&](int x) { return sh + x * ld; };
-  for (bool first = true;; first = false) {
-    // Each wave releases what it wrote itself before the barrier: the barrier does not wait for stores that are under way, and a
-    // release by one wave waits for that wave's stores only.
-    if (!first) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __syncthreads();
+  int ticket = 0;
+  int* drawn = info + 6;
+  asm("" : "+v"(drawn));      // one that is known to be uniform makes the compiler wait for the result where it is asked for
+  if (t == 0) ticket = __hip_atomic_fetch_add(drawn, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (;;) {
     if (t == 0) {
-      if (!first) __hip_atomic_fetch_add(info + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const int ticket = __hip_atomic_fetch_add(info + 6, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const int before = jacobi_ticket(ticket, nblk2).before;
-      bool turn = true;
       const unsigned long long start = wall_clock64();
-      while (__hip_atomic_load(info + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < before) {
+      int now;
+      // the tickets done and the latest sweep with a rotation above the bar, in one load
+      for (;;) {
+        const unsigned long long both = __hip_atomic_load((unsigned long long*)(info + 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        now = (int)(both >> 32);
+        if ((int)both >= before) break;
         if (wall_clock64() - start > kMeetTicks || __hip_atomic_load(info + 5, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
           __hip_atomic_store(info + 5, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          turn = false;
+          now = -1;
           break;
         }
-        __builtin_amdgcn_s_sleep(1);
       }
       next = ticket;
-      state = turn ? __hip_atomic_load(info + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -1;
+      state = now;
+      // one wave acquires for the workgroup: what it invalidates is shared by all of them, and the others start behind the barrier
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
     __syncthreads();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     if (state < 0) return;
     const JacobiTicket k = jacobi_ticket(__builtin_amdgcn_readfirstlane(next), nblk2);
     const int last = __builtin_amdgcn_readfirstlane(state), what = jacobi_work(k, last, kMaxSweeps);
+    if (t == 0 && what != JACOBI_END) ticket = __hip_atomic_fetch_add(drawn, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (what == JACOBI_ROTATE) {
       int I, J;
       rr_pair(k.pair, k.round, nblk2, I, J);
@@ -669,41 +730,49 @@ k_jacobi_rounds(const double* R, int ldr, double* W, int l, int Lp, int nblk2, d
         else load_pair<4>(W, l, Lp, rI, rJ, sh, ld, t);
         __syncthreads();
         gram_32(row, Lp, work, t);
-        if (sweep_32(work, t, k.round == 0, tol * tol, settled * settled) && last <= k.sweep)
+        if (sweep_32(work, t, k.round == 0, settled * settled) && last <= k.sweep)
           __hip_atomic_fetch_max(info + 3, k.sweep + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        for (int c0 = kJB * (t >> 6); c0 < Lp; c0 += 4 * kJB)
+        for (int c0 = kJB * (t >> 6); c0 < Lp; c0 += (kJThreads / 64) * kJB)
           apply_32(row, work + 2 * kJN * kJN, c0, t & 63, [&](int x, int c, double v) {
             if (grow(x) < l) __hip_atomic_store(W + (int64_t)grow(x) * Lp + c, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           });
       }
-      continue;
-    }
-    if (what == JACOBI_END) return;
-    // the rows of the blocks 2 pair and 2 pair + 1, eight lanes a row: their norms, then their places in the descending order
-    const int i = 2 * kJB * k.pair + (t >> 3), e0 = t & 7;
-    if (what == JACOBI_NORMS) {
-      double s2 = 0.0;
-      const double left = i < l ? sig[Lp + i] : 0.0;      // not zero: a row that was set aside
-      if (i < l)
-        for (int e = e0; e < l; e += 8) {
-          if (left != 0.0) W[(int64_t)i * Lp + e] = R[(int64_t)i * ldr + e];
-          const double v = W[(int64_t)i * Lp + e];
-          s2 = fma(v, v, s2);
-        }
-      s2 = row8_sum(s2);
-      if (i < l && e0 == 0) sig[Lp + i] = sqrt(left != 0.0 ? left : s2);
     } else {
-      if (i < l) {
-        const double si = sig[Lp + i];
-        int rank = 0;
-        for (int j = e0; j < l; j += 8) rank += ranks_before(sig[Lp + j], j, si, i);
-        for (int off = 4; off > 0; off >>= 1) rank += __shfl_xor(rank, off, 8);
-        if (e0 == 0) { sig[rank] = si; sig[2 * Lp + rank] = (double)i; }
+      if (what == JACOBI_END) return;
+      // the rows of the blocks 2 pair and 2 pair + 1, eight lanes a row: their norms, then their places in the descending order
+      const int i = t < 256 ? 2 * kJB * k.pair + (t >> 3) : l, e0 = t & 7;
+      if (what == JACOBI_NORMS) {
+        double s2 = 0.0;
+        const double left = i < l ? sig[Lp + i] : 0.0;      // not zero: a row that was set aside
+        if (i < l)
+          for (int e = e0; e < l; e += 8) {
+            if (left != 0.0) W[(int64_t)i * Lp + e] = R[(int64_t)i * ldr + e];
+            const double v = W[(int64_t)i * Lp + e];
+            s2 = fma(v, v, s2);
+          }
+        s2 = row8_sum(s2);
+        if (i < l && e0 == 0) sig[Lp + i] = sqrt(left != 0.0 ? left : s2);
+      } else {
+        if (i < l) {
+          const double si = sig[Lp + i];
+          int rank = 0;
+          for (int j = e0; j < l; j += 8) rank += ranks_before(sig[Lp + j], j, si, i);
+          for (int off = 4; off > 0; off >>= 1) rank += __shfl_xor(rank, off, 8);
+          if (e0 == 0) { sig[rank] = si; sig[2 * Lp + rank] = (double)i; }
+        }
+        if (k.pair == 0 && t == 0) { info[0] = k.sweep; info[1] = last < k.sweep; }
       }
-      if (k.pair == 0 && t == 0) { info[0] = k.sweep; info[1] = last < k.sweep; }
+    }
+    // Each wave waits for its own stores before the barrier, which does not wait for them; then one releases for all.
+    __builtin_amdgcn_s_waitcnt(kWaitStores);
+    __syncthreads();
+    if (t == 0) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      __hip_atomic_fetch_add(info + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 }
+
 
 // Sorted factors.  Vr[t][i] = W[o_i][t] / s_i;  Ur[kk][i] = sum_t R[kk][t] Vr[t][i] / s_i.
 // XV / XU: fp32 zero-padded Lp x Lp right operands of the lifts; Ur / Vr: optional dense fp64.
@@ -743,8 +812,8 @@ __global__ void k_svd_outputs(const double* __restrict__ R, int ldr, const doubl
   if (XU) XU[idx] = xu;
 }
 
-static int jacobi_global(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* breakdown_flag, double tol,
-                         double settled, hipStream_t stream) {
+static int jacobi_global(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* breakdown_flag, double settled,
+                         hipStream_t stream) {
   static bool attr_set = false;
   if (!attr_set) {
     BRSVD_HIP_TRY(hipFuncSetAttribute((const void*)k_jacobi_rounds, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -754,7 +823,7 @@ static int jacobi_global(const double* R, int ldr, int l, int Lp, SvdWork& w, co
   hipLaunchKernelGGL(k_jacobi_init, dim3(Lp), dim3(128), 0, stream, R, ldr, l, Lp, w.W, w.sig, w.info, breakdown_flag);
   const int nblk = (int)ceil_div(l, kJB), nblk2 = (nblk + 1) & ~1;
   hipLaunchKernelGGL(k_jacobi_rounds, dim3(nblk2 / 2), dim3(kJThreads), jacobi_lds_bytes(Lp), stream, R, ldr, w.W, l, Lp, nblk2,
-                     tol, settled, w.sig, w.info);
+                     settled, w.sig, w.info);
   BRSVD_HIP_TRY(hipGetLastError());
   return BRSVD_OK;
 }
@@ -766,17 +835,17 @@ int small_svd(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* br
   // fp64 factors or singular values asked for: the strict bar; single-precision results only: the relaxed one
   const double settled = (sizeof(TO) == 4 && !S && !Ur && !Vr) ? kSettledF32 : kSettled;
   const int nblk = (l + kJB - 1) / kJB;
-  if (l <= kRowsMaxL || nblk == 3 || nblk == 5) {
-    auto kern = l <= kJB ? k_jacobi_rows<1> : nblk == 2 ? k_jacobi_rows<2> : nblk == 3 ? k_jacobi_rows<3> : k_jacobi_rows<5>;
+  if (l <= kRowsMaxL || (nblk == 3 && l <= kRowsMaxL3)) {
+    auto kern = nblk == 1 ? k_jacobi_rows<1> : k_jacobi_rows<3>;
     hipLaunchKernelGGL(kern, dim3(1), dim3(64 * LPP), (size_t)l * l * sizeof(double), stream, R, ldr, l, Lp, w.W, w.sig, w.info,
-                       breakdown_flag, l <= kRowsMaxL ? kTolBlocks : kTolRows, settled);
+                       breakdown_flag, nblk == 1 ? kTolOneBlock : kTolRows, settled);
     BRSVD_HIP_TRY(hipGetLastError());
   } else if (l <= kJN) {
     hipLaunchKernelGGL(k_jacobi_small, dim3(1), dim3(kJThreads), jacobi_lds_bytes(Lp), stream, R, ldr, l, Lp, w.W, w.sig, w.info,
-                       breakdown_flag, kTolBlocks, settled);
+                       breakdown_flag, settled);
     BRSVD_HIP_TRY(hipGetLastError());
   } else {
-    BRSVD_TRY(jacobi_global(R, ldr, l, Lp, w, breakdown_flag, kTolBlocks, settled, stream));
+    BRSVD_TRY(jacobi_global(R, ldr, l, Lp, w, breakdown_flag, settled, stream));
   }
   hipLaunchKernelGGL(k_svd_outputs<TO>, dim3((unsigned)ceil_div((int64_t)Lp * Lp, 256)), dim3(256), 0, stream, R, ldr,
                      w.W, w.sig, l, Lp, S, S32, XV, XU, Ur, Vr, breakdown_flag);

@@ -84,6 +84,23 @@ def test_small_svd_at_the_ends_of_the_row_rotations(l):
         test_small_svd(l, cond)
 
 
+@pytest.mark.parametrize("l", [13, 16, 17, 24, 40, 41, 44, 66, 72, 79])
+def test_small_svd_where_rows_and_blocks_meet(l):
+    """Row rotations up to 16 and from 33 to 40 rows, block pairs otherwise; well-conditioned, nearly rank deficient, and with all
+    entries so small that the squares of squared norms are below the smallest double."""
+    for cond in (1e2, 1e8):
+        test_small_svd(l, cond)
+    if l <= 16 or 33 <= l <= 40:
+        return
+    dev = need_gpu()
+    g = torch.Generator().manual_seed(l)
+    R = torch.linalg.qr(torch.randn(3 * l, l, generator=g, dtype=torch.float64))[1].contiguous()
+    S, U, V, _ = (x.cpu() if isinstance(x, torch.Tensor) else x for x in B.brsvd_small_svd((R * 2.0 ** -440).to(dev)))
+    ref = torch.linalg.svdvals(R)
+    assert float((S * 2.0 ** 440 - ref).abs().max()) <= 40 * 2.0 ** -52 * np.sqrt(l) * float(ref[0])
+    assert float((V.T @ V - torch.eye(l, dtype=torch.float64)).abs().max()) <= 4e-13
+
+
 def _singular_values_long(R):
     """One-sided Jacobi on the rows in 80-bit arithmetic."""
     W, l = R.numpy().astype(np.longdouble), R.shape[0]
