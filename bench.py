@@ -33,9 +33,9 @@ sys.path.insert(0, ROOT)
 PEAK_HBM_GBS = 8000.0        # MI355X HBM3E
 PEAK_MFMA_F32_TFLOPS = 157.3  # dense fp32 MFMA
 PEAK_MFMA_F64_TFLOPS = 78.6   # dense fp64 MFMA
-# Wide fp32 panels over large A are multiplied on the bf16 matrix cores, six bf16 products of exactly split operands for each
-# fp32 one: a sixth of the dense bf16 peak of 2500 TFLOP/s.
-PEAK_SPLIT_F32_TFLOPS = 2500.0 / 6.0
+# Wide fp32 panels over large A are multiplied on the 16-bit matrix cores, with operands split into three bf16 numbers (six matrix
+# products for each fp32 one) or two fp16 ones (three): a sixth or a third of the dense peak of 2500 TFLOP/s.
+PEAK_SPLIT_F32_TFLOPS = {3: 2500.0 / 6.0, 2: 2500.0 / 3.0}
 C4_ROWS = 160000              # the GPU machine pins at most about 64 GB of host memory: 160000 of the 200000 rows
 
 # HBM bytes per launch of the pass kernels from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this script, each
@@ -63,7 +63,9 @@ def mfma_peak(B, which, A, l):
     m, n = A.shape
     if A.element_size() == 8:
         return PEAK_MFMA_F64_TFLOPS
-    return PEAK_SPLIT_F32_TFLOPS if B.brsvd_gemm_is_split(which, m, n, l, A.stride(0), A.data_ptr()) else PEAK_MFMA_F32_TFLOPS
+    if not B.brsvd_gemm_is_split(which, m, n, l, A.stride(0), A.data_ptr()):
+        return PEAK_MFMA_F32_TFLOPS
+    return PEAK_SPLIT_F32_TFLOPS[B.brsvd_gemm_split_parts(which, m, n, l)]
 
 
 def kernel_figures(m, n, l, esz, seconds, launches, peak_mfma):

@@ -82,11 +82,15 @@ int brsvd_gemm_plan(int32_t which, int64_t rows, int64_t n, int32_t l, int64_t b
                     int32_t* out12);
 
 /* Whether Y = A X (which = 0) or Z = A^T Q (which = 1) with A (rows x n, leading dimension lda; the pointer is only
- * looked at for its alignment) and l columns takes the kernels for wide fp32 panels, whose operands are split into bf16
+ * looked at for its alignment) and l columns takes the kernels for wide fp32 panels, whose operands are split into 16-bit
  * numbers (1), or the plain ones that brsvd_gemm_plan describes (0): for pricing a measurement against the right peak.
  * Host-only, no GPU call; BRSVD_ERR_ARG for sizes that the products refuse.  Holds for the step calls and for the
  * passes of the product calls (on a host-resident A: with the rows of a block, and lda = n). */
 int brsvd_gemm_is_split(int32_t which, const void* A, int64_t lda, int64_t rows, int64_t n, int32_t l, int32_t dtype);
+
+/* Of products that brsvd_gemm_is_split answers 1 for: how many 16-bit numbers the operands are split into, three bf16 ones (six
+ * matrix products for one in fp32) or, for long contractions, two scaled fp16 ones (three).  Host-only. */
+int brsvd_gemm_split_parts(int32_t which, int64_t rows, int64_t n, int32_t l);
 
 /* Measurement helper, not a step of the method: measured peaks of the device, to put next to the
  * published ones in roofline figures.  One timed launch after one warm-up launch; synchronous.

@@ -67,7 +67,7 @@ EXPORTS = ["brsvd_workspace_bytes", "brsvd_create", "brsvd_run", "brsvd_run_f64"
 STEP_EXPORTS = ["brsvd_gemm_an", "brsvd_gemm_at", "brsvd_gemm_scratch_bytes", "brsvd_gemm_an_f64",
                 "brsvd_gemm_at_f64", "brsvd_gemm_scratch_bytes_f64", "brsvd_orth", "brsvd_orth_scratch_bytes",
                 "brsvd_small_svd", "brsvd_small_svd_scratch_bytes", "brsvd_small_svd_static", "brsvd_gemm_plan",
-                "brsvd_gemm_is_split", "brsvd_probe"]
+                "brsvd_gemm_is_split", "brsvd_gemm_split_parts", "brsvd_probe"]
 
 _lib = None
 
@@ -107,6 +107,7 @@ def lib() -> C.CDLL:
     L.brsvd_probe.argtypes = [i32, vp, u64, C.POINTER(dbl), C.POINTER(dbl), vp]
     L.brsvd_gemm_plan.argtypes = [i32, i64, i64, i32, i64, i32, C.POINTER(i32)]
     L.brsvd_gemm_is_split.argtypes = [i32, vp, i64, i64, i64, i32, i32]
+    L.brsvd_gemm_split_parts.argtypes = [i32, i64, i64, i32]
     L.brsvd_destroy.argtypes = [vp]
     L.brsvd_status_string.argtypes = [C.c_int]
     L.brsvd_status_string.restype = C.c_char_p
@@ -251,6 +252,14 @@ def brsvd_gemm_is_split(which, rows, n, l, lda=None, address=0, dtype=BRSVD_DTYP
     if r < 0:
         _check(r, "brsvd_gemm_is_split")
     return bool(r)
+
+
+def brsvd_gemm_split_parts(which, rows, n, l) -> int:
+    """How many 16-bit numbers a split product's operands are made of: 3 (bf16, six matrix products) or 2 (fp16, three)."""
+    r = lib().brsvd_gemm_split_parts(which, rows, n, l)
+    if r < 0:
+        _check(r, "brsvd_gemm_split_parts")
+    return r
 
 
 def brsvd_probe(kind, buf, amount):

@@ -20,7 +20,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(CSRC, "_build")
 LIB = os.path.join(HERE, "libbrsvd.so")
-SOURCES = ["gemm_split.hip", "gemm_thin.hip", "orth.hip", "tsqr.hip", "small_svd.hip", "rpca.hip", "philox.hip", "probe.hip", "brsvd.hip"]
+SOURCES = ["gemm_half.hip", "gemm_split.hip", "gemm_thin.hip", "orth.hip", "tsqr.hip", "small_svd.hip", "rpca.hip", "philox.hip", "probe.hip", "brsvd.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
@@ -51,7 +51,7 @@ def _stale(target: str, deps) -> bool:
 def build(force: bool = False, verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
     hipcc = _hipcc()
-    headers = [os.path.join(CSRC, "common.h"), os.path.join(ROOT, "include", "brsvd.h"),
+    headers = [os.path.join(CSRC, "common.h"), os.path.join(CSRC, "split.h"), os.path.join(ROOT, "include", "brsvd.h"),
                os.path.join(ROOT, "include", "brsvd_steps.h")]
     jobs = []
     objs = []
@@ -83,7 +83,7 @@ def build_host_asan(force: bool = False, verbose: bool = False) -> str:
     """Builds csrc/_build_asan/host_checks (see the module docstring) and returns its path."""
     os.makedirs(ASAN_DIR, exist_ok=True)
     hipcc = _hipcc()
-    headers = [os.path.join(CSRC, "common.h"), os.path.join(ROOT, "include", "brsvd.h"),
+    headers = [os.path.join(CSRC, "common.h"), os.path.join(CSRC, "split.h"), os.path.join(ROOT, "include", "brsvd.h"),
                os.path.join(ROOT, "include", "brsvd_steps.h")]
     base = [f for f in FLAGS if f != "-O3"]
     jobs, objs = [], []

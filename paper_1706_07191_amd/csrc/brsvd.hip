@@ -1177,6 +1177,11 @@ int brsvd_gemm_is_split(int32_t which, const void* A, int64_t lda, int64_t rows,
                     : split_fits(true, (const float*)A, n, rows, Lp, lda, room);
 }
 
+int brsvd_gemm_split_parts(int32_t which, int64_t rows, int64_t n, int32_t l) {
+  if (which < 0 || which > 1 || rows < kSplitMinOut || n < kSplitMinOut || l < 1 || l > kMaxL) return BRSVD_ERR_ARG;
+  return which == 0 ? split_parts(false, rows, n, padded_l(l)) : split_parts(true, n, rows, padded_l(l));
+}
+
 int brsvd_probe(int32_t kind, void* buf, uint64_t amount, double* seconds, double* work, void* stream) {
   return probe(kind, buf, amount, seconds, work, (hipStream_t)stream);
 }

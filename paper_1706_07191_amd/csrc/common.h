@@ -102,7 +102,7 @@ int pick_splits(int64_t tiles, int slots, int64_t units, double out_over_in, dou
 int reduce_splits_f32(float* part, int nsplit, int64_t split_stride, int64_t rows, int ncols, int64_t ldi, float* out,
                       int64_t ldo, bool accumulate, hipStream_t stream);
 
-// ---- the same two products for wide fp32 panels on the bf16 matrix cores (gemm_split.hip) ----
+// ---- the same two products for wide fp32 panels on the 16-bit matrix cores (gemm_split.hip, gemm_half.hip) ----
 // out x K (an) or K x out (at) is the part of A multiplied; pack is device memory for the split right panel.
 // Taken for contractions of at least 512 and 2^22 elements of A, from 48 padded columns on.  Measured, plain fp32 kernel and this one
 // (us, A X / A^T Q): 100000x50000 l=272 20944 / 21274 and 12640 / 13114; 20000x20000 l=110 877 / 791 and 514 / 514; 89083x2783 l=97
@@ -128,6 +128,7 @@ struct SplitPlan {
 SplitPlan split_an_plan(int64_t rows, int64_t K, int Lp, uint64_t scratch_bytes);
 SplitPlan split_at_plan(int64_t rows, int64_t n, int Lp, uint64_t scratch_bytes);
 bool split_fits(bool at, const float* A, int64_t out, int64_t K, int Lp, int64_t lda, uint64_t pack_bytes);
+int split_parts(bool at, int64_t out, int64_t K, int Lp);   // 16-bit numbers an operand is split into, with all the scratch it can use
 // X (K x xcols, leading dimension ldx) and Q (rows x qcols, ldq) need no padding; Lp = padded width of the partial panels.
 int split_gemm_an(const float* A, int64_t lda, int64_t rows, int64_t K, const float* X, int64_t ldx, int xcols, int Lp,
                   float* Y, int64_t ldy, int ncols, void* scratch, uint64_t scratch_bytes, void* pack,

@@ -1,5 +1,6 @@
 // The two thin products of gemm_thin.hip for wide fp32 panels over large A (more than 32 columns, and 17 to 32 where it pays; the rule
-// and what it was measured on: common.h) on the bf16 matrix cores, with every fp32 operand split exactly into three bf16 numbers:
+// and what it was measured on: common.h) on the bf16 matrix cores -- the shorter contractions, and what gemm_half.hip leaves of the
+// longer ones -- with every fp32 operand split exactly into three bf16 numbers:
 //
 //   a = h + m + l,   h = the upper 16 bits of a (8 significant bits), m = bf16(a - h), l = a - h - m
 //
@@ -25,115 +26,71 @@
 //   operands: lane = 16*g + r holds eight contraction indices 4*g + {0..3}, 16 + 4*g + {0..3} of the block (any
 //   assignment is allowed as long as both operands share it), for row / column r; D: component v of lane (r, g) is
 //   entry [4*g + v][r].
-#include <algorithm>
-
-#include "common.h"
+#include "split.h"
 
 namespace brsvd {
-
-typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-
-constexpr int kSplitB = 32;          // contraction indices per block
-constexpr int kFragU = 64;           // 16-byte units of one operand fragment (16 x 32 bf16)
-// Flags of the workgroups that met a result that is not finite, and behind them of those that met a row (Z = A^T Q: a column) of
-// A with small elements only.  A workgroup beyond the last one shares a flag with an earlier one; where the other raised it,
-// its own results are only looked at in vain.
-constexpr int kSplitFlags = 4096;
-constexpr int kNotFinite = 1, kSmall = 2;
-// Elements from 2^-95 on have one of these exponent bits set.  They are split without loss, and their parts times anything of
-// ordinary size stay clear of the subnormal numbers; the third part of an element below 2^-110 would not fit bf16 (2^-133).
-constexpr unsigned kWholeBits = 0x70000000u;
-
-struct Frag3 { uintx4 p[3]; };       // h, m, l of eight contraction indices
 
 __device__ __forceinline__ floatx4 mfma_bf16(uintx4 a, uintx4 b, floatx4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
-__device__ __forceinline__ unsigned pack_bf16(float a, float b) {
-  return __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{a, b}, bf16x2));
-}
-// Pair q (elements 2q, 2q + 1) of a fragment.
-__device__ __forceinline__ void split_pair(float a, float b, Frag3& f, int q) {
-  const unsigned ua = __float_as_uint(a), ub = __float_as_uint(b);
-  f.p[0][q] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);              // the two upper halves
-  float ra = a - __uint_as_float(ua & 0xffff0000u), rb = b - __uint_as_float(ub & 0xffff0000u);
-  const unsigned m = pack_bf16(ra, rb);
-  f.p[1][q] = m;
-  ra -= __uint_as_float(m << 16);
-  rb -= __uint_as_float(m & 0xffff0000u);
-  f.p[2][q] = pack_bf16(ra, rb);
-}
-
 // bits |= a | b in one instruction: as plain code the compiler puts it off and keeps a and b in registers (20 more, and spills).
 __device__ __forceinline__ void or3(unsigned& bits, float a, float b) {
   asm("v_or3_b32 %0, %0, %1, %2" : "+v"(bits) : "v"(a), "v"(b));
 }
 
-// First contraction index of block `blk`: the last blocks are moved back so that they end with the range, and the
-// indices the block before has already covered are zero in the packed panel.  Neither operand is then ever read
-// outside its range, and A needs no masks.  K >= kSplitB.
-__device__ __forceinline__ int64_t block_start(int64_t blk, int64_t K) { return min(blk * kSplitB, K - kSplitB); }
-
-// Packed panel: [block][column tile][h, m, l][lane][8 bf16], i.e. 3 KiB per block and tile of 16 columns; an even number of
-// blocks.  src: K x cols, leading dimension ld; columns cols.. are zero.  nan: [column tile][block], a bit for each column with a
-// NaN.  Also clears the flags of the product's workgroups and of the rows of A.
+struct PackedPanel {                  // written by k_split_pack; panel points to the first column tile
+  static constexpr int kUnits = 1;    // 16-byte units a thread hands over at a time
+  typedef uintx4 Unit;
+  const uintx4* panel;
+  int64_t stride;                     // 16-byte units of one block
+  template <int NT>
+  __device__ __forceinline__ void load(Unit& u, int id, int64_t blk, int64_t) const {
+    u = panel[blk * stride + min(id, NT * 3 * kFragU - 1)];
+  }
+  template <int NT>
+  __device__ __forceinline__ void store(const Unit& u, int id, int64_t, int64_t, uintx4* buf) const {
+    buf[min(id, NT * 3 * kFragU - 1)] = u;
+  }
+};
+// nan: [column tile][block], a bit for each column with a NaN.  Also clears the flags of the product's workgroups and of the rows of A.
 // Where a column has small elements only in a block, its part of the panel is made NaN, so that its results are taken from the repair.
 __global__ void __launch_bounds__(256)
 k_split_pack(const float* __restrict__ src, int64_t K, int64_t ld, int cols, int nt_total, int64_t blocks,
              uintx4* __restrict__ out, unsigned* __restrict__ nan, int* __restrict__ flags, int64_t nflags) {
   const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
   for (int64_t i = id; i < nflags; i += (int64_t)gridDim.x * 256) flags[i] = 0;
-  const int lane = (int)(id & 63), r = lane & 15, g = lane >> 4;
   const int64_t tile = id >> 6, blk = tile / nt_total;
   if (blk >= blocks) return;
-  const int nt = (int)(tile - blk * nt_total), col = 16 * nt + r;
-  const int64_t k0 = block_start(blk, K);
-  float v[8];
-  bool any_nan = false;
-  unsigned bits = 0;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int64_t k = k0 + (e >> 2) * 16 + 4 * g + (e & 3);
-    v[e] = k >= blk * kSplitB && col < cols ? src[k * ld + col] : 0.f;
-    any_nan |= v[e] != v[e];
-    bits |= __float_as_uint(v[e]);
-  }
-  const unsigned long long b = __ballot(any_nan);                      // bit 16 * g + r
-  if (lane == 0) nan[nt * blocks + blk] = (unsigned)(b | b >> 16 | b >> 32 | b >> 48) & 0xffffu;
-  Frag3 f;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) split_pair(v[2 * q], v[2 * q + 1], f, q);
-  bits |= __shfl_xor(bits, 16, 64);
-  bits |= __shfl_xor(bits, 32, 64);
-  if (!(bits & kWholeBits) && (bits & 0x7fffffffu)) f.p[0][0] = 0x7fc07fc0u;
-  uintx4* o = out + tile * (3 * kFragU) + lane;
-#pragma unroll
-  for (int p = 0; p < 3; ++p) o[p * kFragU] = f.p[p];
+  const int nt = (int)(tile - blk * nt_total);
+  const unsigned b = split_pack_fragment(src, K, ld, cols, blk, nt, out + tile * (3 * kFragU));
+  if ((threadIdx.x & 63) == 0) nan[nt * blocks + blk] = b;
 }
-
-template <int I, int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<I + 1, N>(f);
+struct RawPanel {
+  static constexpr int kUnits = 3;
+  struct Unit { float v[8]; };
+  const float* X;
+  int64_t ld;
+  int cols;
+  template <int NT>
+  __device__ __forceinline__ void load(Unit& u, int id, int64_t blk, int64_t K) const {
+    const int lane = id & 63, nt = min(id >> 6, NT - 1);
+    const float* p = X + block_start(blk, K) * ld + min(16 * nt + (lane & 15), cols - 1);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) u.v[e] = p[((e >> 2) * 16 + 4 * (lane >> 4) + (e & 3)) * ld];
   }
-}
-
-// What one workgroup multiplies: `blocks` blocks (even) of the contraction from block `b0` on, and where its result goes.
-struct SplitTile {
-  const float* A;        // Y = A X: first row of the tile;  Z = A^T Q: first row of A
-  int64_t lda;
-  int64_t K;             // length of the contraction
-  int64_t b0;
-  int blocks;
-  int first, count;      // first row (column) of the tile and how many rows (columns) the output has in all
-  float* out;            // row `first` of the output is out + first * ldo
-  int64_t ldo;
-  int ncols;
-  int* whole;            // set for the rows (columns) with an element that is split without loss
+  template <int NT>
+  __device__ __forceinline__ void store(const Unit& u, int id, int64_t blk, int64_t K, uintx4* buf) const {
+    const int lane = id & 63, nt = min(id >> 6, NT - 1);
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int64_t k = block_start(blk, K) + (e >> 2) * 16 + 4 * (lane >> 4) + (e & 3);
+      v[e] = k >= blk * kSplitB && 16 * nt + (lane & 15) < cols ? u.v[e] : 0.f;
+    }
+    const Frag3 f = split_panel_fragment(v);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) buf[(nt * 3 + p) * kFragU + lane] = f.p[p];
+  }
 };
 
 // Workgroup: WR x WC waves; wave (wr, wc) owns MT tiles of 16 rows (AT: columns of A) and NTW tiles of the panel's
@@ -145,12 +102,13 @@ struct SplitTile {
 // fragments from LDS, the addition of the previous tile's block sum, the split of the next block's part of A with
 // the loads of the block after that, and the hand-over of the next block's packed panel from registers to LDS.  One barrier
 // per block.  A first version that did these things between the blocks ran at 75-85 % of this one.
-template <bool AT, int NT, int NTW, int MT, int WR, int WC>
-__device__ __forceinline__ int split_tile(const SplitTile& s, const uintx4* __restrict__ XP, int64_t xstride, uintx4* lds,
-                                           int wr, int nt0) {
+//
+// Panel: a packed one (PackedPanel), or the panel as it is (RawPanel: its part of a block is split on its way to LDS).
+template <bool AT, int NT, int NTW, int MT, int WR, int WC, typename Panel>
+__device__ __forceinline__ int split_tile(const SplitTile& s, const Panel& panel, uintx4* lds, int wr, int nt0) {
   constexpr int NTH = WR * WC * 64;
   constexpr int BUF = NT * 3 * kFragU;                 // 16-byte units of one staged block
-  constexpr int XPT = (BUF + NTH - 1) / NTH;
+  constexpr int XPT = (BUF / Panel::kUnits + NTH - 1) / NTH;
   constexpr int SL = NTW * 6;                          // slots of matrix instructions per block
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int w0 = s.first + wr * (MT * 16);             // first row (column) of this wave
@@ -174,7 +132,7 @@ __device__ __forceinline__ int split_tile(const SplitTile& s, const uintx4* __re
   floatx4 ra[MT][2];                                   // Y = A X: [tile][half block] four indices of one row
   vecM rq[8];                                          // Z = A^T Q: [index] MT columns of one row of A
   Frag3 fa[MT], fb[MT];
-  uintx4 xr[XPT];
+  typename Panel::Unit xr[XPT];
   unsigned bits[MT];                                   // of all elements of A this lane has split, by row (AT: column)
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
@@ -184,8 +142,8 @@ __device__ __forceinline__ int split_tile(const SplitTile& s, const uintx4* __re
     for (int nt = 0; nt < NTW; ++nt) acc[mt][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
   }
   const int last = s.blocks - 1;
-  auto xid = [&](int x) { return min(tid + x * NTH, BUF - 1); };
-  auto load_x = [&](int x, const uintx4* src) { xr[x] = src[xid(x)]; };
+  auto load_x = [&](int x, int c) { panel.template load<NT>(xr[x], tid + x * NTH, s.b0 + c, s.K); };
+  auto store_x = [&](int x, int c, uintx4* buf) { panel.template store<NT>(xr[x], tid + x * NTH, s.b0 + c, s.K, buf); };
   // base of block c: A + k0 (row part of the address is in off) or A + k0 * lda
   auto block_base = [&](int c) {
     const int64_t k0 = block_start(s.b0 + c, s.K);
@@ -216,13 +174,11 @@ __device__ __forceinline__ int split_tile(const SplitTile& s, const uintx4* __re
     }
   };
 
-  const uintx4* xb = XP + s.b0 * xstride;
   {
     const char* base = block_base(0);
-    static_for<0, XPT>([&](auto x) { load_x(x, xb); });
+    static_for<0, XPT>([&](auto x) { load_x(x, 0); });
     static_for<0, 4 * MT>([&](auto p) { load_a(p, base); });
-    const uintx4* xb1 = xb + xstride;
-    static_for<0, XPT>([&](auto x) { lds[xid(x)] = xr[x]; load_x(x, xb1); });
+    static_for<0, XPT>([&](auto x) { store_x(x, 0, lds); load_x(x, 1); });
     base = block_base(1);
     static_for<0, 4 * MT>([&](auto p) { split_a(p, fa); load_a(p, base); });
   }
@@ -232,7 +188,6 @@ __device__ __forceinline__ int split_tile(const SplitTile& s, const uintx4* __re
     const uintx4* bb = lds + (c & 1) * BUF + nt0 * (3 * kFragU) + lane;
     uintx4* nxt = lds + ((c & 1) ^ 1) * BUF;
     const int c2 = min(c + 2, last);
-    const uintx4* x2 = xb + c2 * xstride;
     const char* base2 = block_base(c2);
     uintx4 b[2][3];
 #pragma unroll
@@ -250,7 +205,7 @@ __device__ __forceinline__ int split_tile(const SplitTile& s, const uintx4* __re
       for (int p = sl * (4 * MT) / SL; p < (sl + 1) * (4 * MT) / SL; ++p) { split_a(p, nf); load_a(p, base2); }
       // the next block's packed panel goes to LDS, the one after it is requested
 #pragma unroll
-      for (int x = sl * XPT / SL; x < (sl + 1) * XPT / SL; ++x) { nxt[xid(x)] = xr[x]; load_x(x, x2); }
+      for (int x = sl * XPT / SL; x < (sl + 1) * XPT / SL; ++x) { store_x(x, min(c + 1, last), nxt); load_x(x, c2); }
       // the previous tile's block sum
       constexpr int pv = (nt + NTW - 1) % NTW;
 #pragma unroll
@@ -303,20 +258,17 @@ __device__ __forceinline__ int split_tile(const SplitTile& s, const uintx4* __re
   return found;
 }
 
-template <bool AT, int NT, int MT, int WR, int WC>
-__device__ __forceinline__ void split_tile_waves(const SplitTile& s, const uintx4* XP, int64_t xstride, uintx4* lds, int* flag) {
+template <bool AT, int NT, int MT, int WR, int WC, typename Panel>
+__device__ __forceinline__ int split_tile_waves(const SplitTile& s, const Panel& panel, uintx4* lds) {
   constexpr int NTW = (NT + WC - 1) / WC;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wr = wave % WR, wc = wave / WR;
-  int found;
   if constexpr (NT % WC == 0) {
-    found = split_tile<AT, NT, NTW, MT, WR, WC>(s, XP, xstride, lds, wr, wc * NTW);
+    return split_tile<AT, NT, NTW, MT, WR, WC>(s, panel, lds, wr, wc * NTW);
   } else {
-    if (wc == 0) found = split_tile<AT, NT, NTW, MT, WR, WC>(s, XP, xstride, lds, wr, 0);
-    else found = split_tile<AT, NT, NTW - 1, MT, WR, WC>(s, XP, xstride, lds, wr, NTW);
+    if (wc == 0) return split_tile<AT, NT, NTW, MT, WR, WC>(s, panel, lds, wr, 0);
+    return split_tile<AT, NT, NTW - 1, MT, WR, WC>(s, panel, lds, wr, NTW);
   }
-  if (found & kNotFinite) flag[0] = 1;
-  if (found & kSmall) flag[kSplitFlags] = 1;
 }
 
 // Y = A X.  Work partition and partial panels as in k_gemm_an (AnShape), in chunks of two blocks.
@@ -341,7 +293,9 @@ k_split_an(const float* __restrict__ A, int64_t lda, int rows, int K, const uint
     s.ldo = w.partial ? ldp : ldy;
     s.ncols = w.partial ? NT * 16 : ncols;
     s.whole = whole;
-    split_tile_waves<false, NT, MT, WR, WC>(s, XP, xstride, (uintx4*)lds_raw, flags + blockIdx.x % kSplitFlags);
+    const int found = split_tile_waves<false, NT, MT, WR, WC>(s, PackedPanel{XP, xstride}, (uintx4*)lds_raw);
+    if (found & kNotFinite) flags[blockIdx.x % kSplitFlags] = 1;
+    if (found & kSmall) flags[kSplitFlags + blockIdx.x % kSplitFlags] = 1;
     __syncthreads();                                   // before the next strip reuses the staging buffers
   }
 }
@@ -365,7 +319,10 @@ k_split_at(const float* __restrict__ A, int64_t lda, int64_t rows, int n, const 
   s.ldo = ldz;
   s.ncols = NT * 16;
   s.whole = whole;
-  split_tile_waves<true, NT, MT, WR, WC>(s, QP, xstride, (uintx4*)lds_raw, flags + (blockIdx.y * gridDim.x + blockIdx.x) % kSplitFlags);
+  const int found = split_tile_waves<true, NT, MT, WR, WC>(s, PackedPanel{QP, xstride}, (uintx4*)lds_raw);
+  int* flag = flags + (blockIdx.y * gridDim.x + blockIdx.x) % kSplitFlags;
+  if (found & kNotFinite) flag[0] = 1;
+  if (found & kSmall) flag[kSplitFlags] = 1;
 }
 
 // Products with infinities, NaN or overflow: a split infinity is inf + NaN + NaN, and inf times the zero low parts
@@ -564,30 +521,81 @@ k_split_repair_at(SplitRepair p, float* __restrict__ Zpart, int64_t ldz, int64_t
   repair_tile<true>(p, blockIdx.x * p.tile, b0, blocks, small, xnan, Zpart + (int64_t)blockIdx.y * split_stride, ldz, (int)ldz);
 }
 
-// ---- host side --------------------------------------------------------------------------------------------------
-struct SplitCfg { int wr, wc, tile; };
-constexpr int kSplitMT = 2;
-// Up to ten column tiles one wave holds them all (accumulators of 2 x 10 tiles: 230 registers of 256 for
-// A^T Q; A X takes all of them and, with 9, 10, 14, 16 and 17 tiles, 12 to 24 places in scratch); wider panels take
-// two columns of waves, i.e. half as many rows per workgroup.
-static SplitCfg split_cfg(int nt) {
-  return nt <= 10 ? SplitCfg{8, 1, 8 * kSplitMT * 16} : SplitCfg{4, 2, 4 * kSplitMT * 16};
-}
-constexpr int kSplitSlots = 256;                        // one workgroup of eight waves per CU
-static int64_t split_chunks(int64_t K) { return ceil_div(K, 2 * kSplitB); }
-// The packed panel, behind it the words that say which columns have a NaN, and the flags of the product's workgroups and of the
-// `out` rows (columns) of A.
-struct PackLayout {
-  uint64_t nan, flags, whole, bytes;
+// What is left of a product of gemm_half.hip: the workgroups that gave up do their part with bf16 numbers, then (and where a result
+// was not finite) the repair above, for the column tiles of one launch.  Which rows have small elements only is decided within the
+// workgroup's part, so the result does not depend on what the others have come to.  No work for ordinary numbers (about 3 us for the
+// launch).
+struct SplitFix {
+  SplitRepair p;           // of the launch's columns
+  PackedPanel panel;       // the same columns, in bf16 numbers if a word of redo is kRedoPacked
+  const int* redo;
 };
-static PackLayout pack_layout(int64_t out, int64_t K, int Lp) {
-  const uint64_t tiles = (uint64_t)split_chunks(K) * 2 * (Lp / 16);
-  PackLayout o;
-  o.nan = tiles * 3 * kFragU * 16;
-  o.flags = o.nan + tiles * 4;
-  o.whole = o.flags + 2 * kSplitFlags * 4;
-  o.bytes = o.whole + (uint64_t)out * 4;
-  return o;
+template <bool AT, int NT, int MT, int WR, int WC>
+__device__ __forceinline__ void split_fix(const SplitFix& f, SplitTile s, int redo, uintx4* lds) {
+  __shared__ unsigned xnan[kMaxTiles];
+  __shared__ int whole[MT + WR * MT * 16], found;        // (the last MT columns of A may begin before the tile)
+  SplitRepair p = f.p;
+  if (threadIdx.x < MT + WR * MT * 16) whole[threadIdx.x] = 0;
+  if (threadIdx.x == 0) found = 0;
+  __syncthreads();
+  s.whole = whole + MT - s.first;                        // addressed like the words of all rows
+  int mine = 0;
+  if (redo == kRedoPacked) mine = split_tile_waves<AT, NT, MT, WR, WC>(s, f.panel, lds);
+  else if (redo == kRedoRaw) mine = split_tile_waves<AT, NT, MT, WR, WC>(s, RawPanel{p.X, p.ldx, p.xcols}, lds);
+  if (mine & kSmall) found = 1;
+  __threadfence_block();
+  __syncthreads();
+  const bool small = found != 0;
+  p.whole = s.whole;
+  nan_columns(p, s.b0, s.blocks, xnan);
+  repair_tile<AT>(p, s.first, s.b0, s.blocks, small, xnan, s.out, s.ldo, s.ncols);
+}
+
+template <int NT, int MT, int WR, int WC>
+__global__ void __launch_bounds__(WR * WC * 64)
+k_split_fix_an(SplitFix f, float* __restrict__ Y, int64_t ldy, int ncols, float* __restrict__ Part, int64_t ldp, int64_t split_stride,
+               AnShape sh) {
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  constexpr int TR = WR * MT * 16;
+  const int redo = f.redo[blockIdx.x % kSplitFlags];
+  if (!redo && f.p.flags[blockIdx.x % kSplitFlags] == 0) return;
+  const AnWork w = an_work(sh, blockIdx.x);
+  for (int seg = 0; seg < w.nseg; ++seg) {
+    SplitTile s;
+    s.first = (w.first_tile + seg) * TR;
+    s.A = f.p.A + (int64_t)s.first * f.p.lda;
+    s.lda = f.p.lda;
+    s.K = f.p.K;
+    s.b0 = 2 * (int64_t)w.c0;
+    s.blocks = 2 * (w.c1 - w.c0);
+    s.count = f.p.count;
+    s.out = w.partial ? Part + (int64_t)w.slot * split_stride - (int64_t)sh.whole * TR * ldp : Y;
+    s.ldo = w.partial ? ldp : ldy;
+    s.ncols = w.partial ? NT * 16 : ncols;
+    split_fix<false, NT, MT, WR, WC>(f, s, redo, (uintx4*)lds_raw);
+    __syncthreads();
+  }
+}
+
+template <int NT, int MT, int WR, int WC>
+__global__ void __launch_bounds__(WR * WC * 64)
+k_split_fix_at(SplitFix f, float* __restrict__ Zpart, int64_t ldz, int64_t split_stride, int blocks_per_sub) {
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  const int wg = (blockIdx.y * gridDim.x + blockIdx.x) % kSplitFlags;
+  const int redo = f.redo[wg];
+  if (!redo && f.p.flags[wg] == 0) return;
+  SplitTile s;
+  s.A = f.p.A;
+  s.lda = f.p.lda;
+  s.K = f.p.K;
+  s.b0 = (int64_t)blockIdx.y * blocks_per_sub;
+  s.blocks = (int)min((int64_t)blocks_per_sub, f.p.blocks - s.b0);
+  s.first = blockIdx.x * (WR * MT * 16);
+  s.count = f.p.count;
+  s.out = Zpart + (int64_t)blockIdx.y * split_stride;
+  s.ldo = ldz;
+  s.ncols = NT * 16;
+  split_fix<true, NT, MT, WR, WC>(f, s, redo, (uintx4*)lds_raw);
 }
 
 bool split_fits(bool at, const float* A, int64_t out, int64_t K, int Lp, int64_t lda, uint64_t pack_bytes) {
@@ -680,6 +688,45 @@ static int split_pack(const float* A, int64_t lda, int64_t count, int tile, cons
   return BRSVD_OK;
 }
 
+// Whether the products of two fp16 numbers each (gemm_half.hip) are taken: `piece` = contraction indices one workgroup adds up, on
+// average.  They are where their results are at least as accurate: what the split loses (7e-8 of a product) has to be less than what
+// the additions lose, half as many as here.  Relative error, 3 x bf16 and 2 x fp16 (N(0, 1) entries, K x outputs, pieces):
+//   1000 x 300000 1000 1.20e-7 / 1.33e-7    4000 x 8000 500 1.24e-7 / 1.42e-7     2100 x 30000 1050 1.29e-7 / 1.40e-7
+//   6000 x 16000 1500 1.63e-7 / 1.58e-7     12000 x 8192 1500 1.87e-7 / 1.71e-7   2500 x 60000 2500 1.78e-7 / 1.64e-7
+//   8192 x 1000 256 1.51e-7 / 1.59e-7       12000 x 2000 375 1.72e-7 / 1.72e-7    16384 x 1000 512 1.81e-7 / 1.75e-7
+constexpr int64_t kHalfMinPiece = 1408, kHalfMinK = 16384;
+static bool half_fits(int64_t K, int64_t piece) { return piece >= kHalfMinPiece || K >= kHalfMinK; }
+static bool half_fits_an(int64_t K, const SplitPlan& p) {
+  const AnShape& sh = p.sh;
+  const int64_t tiles = sh.whole + sh.lt, chunks = (int64_t)sh.whole * sh.C + (sh.lt > 0 ? (int64_t)sh.lt * ((sh.C - sh.x) / sh.f) : 0);
+  return half_fits(K, 2 * kSplitB * chunks / tiles);
+}
+static bool half_fits_at(int64_t K, const SplitPlan& p) { return half_fits(K, kSplitB * std::min(p.blocks, p.blocks_per_sub)); }
+int split_parts(bool at, int64_t out, int64_t K, int Lp) {
+  if (at) return half_fits_at(K, split_at_plan(K, out, Lp, UINT64_MAX)) ? 2 : 3;
+  return half_fits_an(K, split_an_plan(out, K, Lp, UINT64_MAX)) ? 2 : 3;
+}
+// The place of the packed panel, of the words and of the flags is that of three bf16 numbers; the flags of rows with small elements
+// only say which workgroups have to be redone.
+static int half_prepare(const float* A, int64_t lda, int64_t count, int tile, const float* X, int64_t K, int64_t ldx, int xcols,
+                        int Lp, bool at, void* pack, Packed* out, HalfPacked* hp, hipStream_t stream) {
+  const PackLayout lay = pack_layout(count, K, Lp);
+  unsigned* nan = (unsigned*)((char*)pack + lay.nan);
+  int* flags = (int*)((char*)pack + lay.flags);
+  *out = Packed{(const uintx4*)pack, 0, flags, nullptr,
+                SplitRepair{A, X, lda, ldx, K, xcols, (int)count, tile, Lp / 16, nan, 2 * split_chunks(K), flags, nullptr}};
+  *hp = HalfPacked{pack, nan, flags, flags + kSplitFlags, X, ldx, xcols};
+  return half_pack(A, lda, count, K, Lp, at, *hp, stream);
+}
+// The column tiles [c0 / 16, c0 / 16 + nt) alone.
+static SplitRepair group_repair(SplitRepair p, int c0, int nt) {
+  p.X += c0;
+  p.xcols = std::min(p.xcols - c0, nt * 16);
+  p.nan += c0 / 16 * p.blocks;
+  p.nt_total = nt;
+  return p;
+}
+
 int split_gemm_an(const float* A, int64_t lda, int64_t rows, int64_t K, const float* X, int64_t ldx, int xcols, int Lp,
                   float* Y, int64_t ldy, int ncols, void* scratch, uint64_t scratch_bytes, void* pack,
                   uint64_t pack_bytes, hipStream_t stream, const KernelEvents* ev) {
@@ -688,10 +735,30 @@ int split_gemm_an(const float* A, int64_t lda, int64_t rows, int64_t K, const fl
   float* part = (float*)scratch;
   const int64_t stride = p.partial_rows * Lp;
   Packed x;
-  BRSVD_TRY(split_pack(A, lda, rows, p.tile, X, K, ldx, xcols, Lp, pack, &x, stream));
+  const bool half = half_fits_an(K, p);
+  HalfPacked hp;
+  if (half) BRSVD_TRY(half_prepare(A, lda, rows, p.tile, X, K, ldx, xcols, Lp, false, pack, &x, &hp, stream));
+  else BRSVD_TRY(split_pack(A, lda, rows, p.tile, X, K, ldx, xcols, Lp, pack, &x, stream));
   for (int gi = 0; gi < p.groups; ++gi) {
     const int c0 = gi * p.nt * 16, nt = std::min(p.nt, (Lp - c0) / 16);
     if (nt <= 0) break;
+    if (half) {
+      BRSVD_TRY(half_an(A, lda, rows, K, hp, Lp, c0, nt, p.tile, Y + c0, ldy, std::min(ncols - c0, nt * 16), part ? part + c0 : nullptr,
+                        stride, p.sh, p.wgs, stream));
+      const SplitFix fix{group_repair(x.repair, c0, nt), PackedPanel{(const uintx4*)hp.panel + (c0 / 16) * 3 * kFragU, (Lp / 16) * 3 * kFragU}, hp.redo};
+#define CALL(N, WR, WC)                                                                                              \
+  {                                                                                                                  \
+    auto kern = k_split_fix_an<N, kSplitMT, WR, WC>;                                                                 \
+    static bool done = false;                                                                                        \
+    BRSVD_TRY(split_lds(kern, N, &done));                                                                            \
+    hipLaunchKernelGGL(kern, dim3(p.wgs), dim3(WR * WC * 64), 2 * N * 3 * kFragU * 16, stream, fix, Y + c0, ldy,      \
+                       std::min(ncols - c0, N * 16), part ? part + c0 : nullptr, (int64_t)Lp, stride, p.sh);         \
+  }
+      BRSVD_SPLIT_SWITCH(nt, p.tile, CALL)
+#undef CALL
+      BRSVD_HIP_TRY(hipGetLastError());
+      continue;
+    }
     const uintx4* xp = x.panel + (c0 / 16) * 3 * kFragU;
 #define CALL(N, WR, WC)                                                                                              \
   {                                                                                                                  \
@@ -706,9 +773,11 @@ int split_gemm_an(const float* A, int64_t lda, int64_t rows, int64_t K, const fl
 #undef CALL
     BRSVD_HIP_TRY(hipGetLastError());
   }
-  hipLaunchKernelGGL(k_split_repair_an, dim3(p.wgs), dim3(kRepairWaves * 64), 0, stream, x.repair, Y, ldy, ncols, part, (int64_t)Lp,
-                     stride, p.sh);
-  BRSVD_HIP_TRY(hipGetLastError());
+  if (!half) {
+    hipLaunchKernelGGL(k_split_repair_an, dim3(p.wgs), dim3(kRepairWaves * 64), 0, stream, x.repair, Y, ldy, ncols, part, (int64_t)Lp,
+                       stride, p.sh);
+    BRSVD_HIP_TRY(hipGetLastError());
+  }
   if (ev) BRSVD_HIP_TRY(hipEventRecord(ev->stop, stream));
   if (p.nsplit > 0) {
     const int64_t r0 = rows - p.partial_rows;
@@ -728,10 +797,30 @@ int split_gemm_at(const float* A, int64_t lda, int64_t rows, int64_t n, const fl
   float* part = (float*)scratch;
   const int64_t stride = n * Lp;
   Packed x;
-  BRSVD_TRY(split_pack(A, lda, n, p.tile, Q, rows, ldq, qcols, Lp, pack, &x, stream));
+  const bool half = half_fits_at(rows, p);
+  HalfPacked hp;
+  if (half) BRSVD_TRY(half_prepare(A, lda, n, p.tile, Q, rows, ldq, qcols, Lp, true, pack, &x, &hp, stream));
+  else BRSVD_TRY(split_pack(A, lda, n, p.tile, Q, rows, ldq, qcols, Lp, pack, &x, stream));
   for (int gi = 0; gi < p.groups; ++gi) {
     const int c0 = gi * p.nt * 16, nt = std::min(p.nt, (Lp - c0) / 16);
     if (nt <= 0) break;
+    if (half) {
+      BRSVD_TRY(half_at(A, lda, rows, n, hp, Lp, c0, nt, p.tile, part + c0, stride, p.col_tiles, p.nsplit, p.blocks, p.blocks_per_sub,
+                        stream));
+      const SplitFix fix{group_repair(x.repair, c0, nt), PackedPanel{(const uintx4*)hp.panel + (c0 / 16) * 3 * kFragU, (Lp / 16) * 3 * kFragU}, hp.redo};
+#define CALL(N, WR, WC)                                                                                              \
+  {                                                                                                                  \
+    auto kern = k_split_fix_at<N, kSplitMT, WR, WC>;                                                                 \
+    static bool done = false;                                                                                        \
+    BRSVD_TRY(split_lds(kern, N, &done));                                                                            \
+    hipLaunchKernelGGL(kern, dim3(p.col_tiles, p.nsplit), dim3(WR * WC * 64), 2 * N * 3 * kFragU * 16, stream, fix,   \
+                       part + c0, (int64_t)Lp, stride, p.blocks_per_sub);                                            \
+  }
+      BRSVD_SPLIT_SWITCH(nt, p.tile, CALL)
+#undef CALL
+      BRSVD_HIP_TRY(hipGetLastError());
+      continue;
+    }
     const uintx4* qp = x.panel + (c0 / 16) * 3 * kFragU;
 #define CALL(N, WR, WC)                                                                                              \
   {                                                                                                                  \
@@ -746,9 +835,11 @@ int split_gemm_at(const float* A, int64_t lda, int64_t rows, int64_t n, const fl
 #undef CALL
     BRSVD_HIP_TRY(hipGetLastError());
   }
-  hipLaunchKernelGGL(k_split_repair_at, dim3(p.col_tiles, p.nsplit), dim3(kRepairWaves * 64), 0, stream, x.repair, part, (int64_t)Lp,
-                     stride, p.blocks_per_sub);
-  BRSVD_HIP_TRY(hipGetLastError());
+  if (!half) {
+    hipLaunchKernelGGL(k_split_repair_at, dim3(p.col_tiles, p.nsplit), dim3(kRepairWaves * 64), 0, stream, x.repair, part, (int64_t)Lp,
+                       stride, p.blocks_per_sub);
+    BRSVD_HIP_TRY(hipGetLastError());
+  }
   if (ev) BRSVD_HIP_TRY(hipEventRecord(ev->stop, stream));
   BRSVD_TRY(reduce_splits_f32(part, p.nsplit, stride, n, ncols, Lp, Z, ldz, accumulate, stream));
   if (ev) BRSVD_HIP_TRY(hipEventRecord(ev->sum_stop, stream));

@@ -1,0 +1,149 @@
+"""The products of wide fp32 panels over long contractions, whose operands are split into two scaled fp16 numbers: elementwise error
+against fp64 at the edges of their tiles, and numbers of every range, which one scale for 64 of them does not hold."""
+import pytest
+import torch
+
+import paper_1706_07191_amd as B
+from tests.gpu_util import need_gpu
+from tests.test_gpu_split import _bound, _inputs
+from tests.test_gpu_split import test_split_products_not_finite_in_every_part_of_a_plan as _not_finite
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [  # rows, n, l, elements between A's rows beyond n, offset of A's base; one product or both are of this kind
+    (257, 16411, 33, 0, 0),      # one row more than a tile, last step 27 indices, unaligned rows
+    (16449, 258, 48, 0, 0),      # A^T Q: last step one index
+    (20003, 14016, 17, 0, 0),    # narrowest panel
+    (16385, 16390, 80, 0, 0),    # both products, whole steps and one index over
+    (16384, 300, 144, 2, 1),     # nine tiles in one column of waves, padded rows, odd base
+    (300, 16500, 145, 0, 3),     # ten
+    (300, 16500, 161, 0, 0),     # eleven: two columns of waves
+    (16500, 301, 208, 0, 0),     # thirteen: seven units of the panel a thread, in two rounds of four
+    (400, 16390, 272, 0, 0),     # seventeen
+    (16390, 400, 273, 0, 0),     # two column groups
+    (300, 20000, 336, 0, 0),     # groups of eleven and ten tiles
+    (17000, 300, 512, 0, 0),     # the largest sketch width, two tiles a wave in the packing
+    (70000, 1500, 110, 0, 0),    # more row tiles than workgroups: whole contractions and a cut leftover round
+]
+
+
+def _check(A, X, Q, bound=_bound):
+    """Both products where they are of this kind."""
+    rows, n, l = A.shape[0], A.shape[1], X.shape[1]
+    kinds = [w for w in (0, 1) if B.brsvd_gemm_is_split(w, rows, n, l, A.stride(0), A.data_ptr()) and B.brsvd_gemm_split_parts(w, rows, n, l) == 2]
+    assert kinds
+    At = A.T.contiguous()
+    for w in kinds:
+        a, x = (A, X) if w == 0 else (At, Q)
+        got = B.brsvd_gemm_an(A, X) if w == 0 else B.brsvd_gemm_at(A, Q)
+        err = (got.double() - a.double() @ x.double()).abs()
+        assert bool((err <= bound(a.shape[1], a, x)).all()), w
+
+
+@pytest.mark.parametrize("rows,n,l,pad,off", SHAPES)
+@pytest.mark.parametrize("mean", [0.0, 0.5])
+def test_half_products(rows, n, l, pad, off, mean):
+    dev = need_gpu()
+    print(f"[case] half rows={rows} n={n} l={l} pad={pad} off={off} mean={mean}", flush=True)
+    _check(*_inputs(rows, n, l, pad, off, dev, mean))
+
+
+def _log_uniform(shape, lo, hi, dev):
+    g = torch.Generator(device=dev)
+    g.manual_seed(77)
+    return 10.0 ** (lo + (hi - lo) * torch.rand(shape, generator=g, device=dev))
+
+
+def _graded(A, X, Q):            # columns over 24 decades, undone by the panel; rows likewise
+    d, e = torch.logspace(-12, 12, A.shape[1], device=A.device), torch.logspace(-9, 9, A.shape[0], device=A.device)
+    p = torch.randperm(len(d), generator=torch.Generator().manual_seed(5)).to(A.device)
+    A *= d[p]
+    X /= d[p][:, None]
+    A *= e[:, None]
+    Q /= e[:, None]
+
+
+def _outliers(A, X, Q):          # large columns and rows of A where a column of the panel is zero, or small
+    A[:, ::37] *= 1e7
+    A[::41] *= 1e7
+    X[::37, 0], X[::37, 3] = 0.0, X[::37, 3] * 1e-9
+    Q[::41, 0], Q[::41, 3] = 0.0, Q[::41, 3] * 1e-9
+
+
+def _few_outliers(A, X, Q):      # one element in a workgroup's part
+    A[100, 200] = 1e9
+    A[A.shape[0] - 1, A.shape[1] - 1] = -1e12
+    X[200], Q[100] = 0.0, 0.0
+
+
+def _any_range(A, X, Q):         # 30 decades without order
+    A *= _log_uniform(A.shape, -30, 0, A.device)
+
+
+def _panel_any_range(A, X, Q):
+    X *= _log_uniform(X.shape, -20, 0, X.device)
+    Q *= _log_uniform(Q.shape, -20, 0, Q.device)
+
+
+def _indicators(A, X, Q):        # sums over groups of columns, one group of large numbers
+    A[:, ::5] *= 1e8
+    A[::5] *= 1e8
+    for P in (X, Q):
+        k = torch.arange(P.shape[0], device=P.device)
+        P.zero_()
+        P[k, k % 5 % P.shape[1]] = 1.0
+
+
+def _blocks(A, X, Q):            # rows of A that only meet the small part of the panel, cut within a step
+    h, k = A.shape[0] // 2 + 5, A.shape[1] // 2 + 5
+    A[:h, k:], A[h:, :k] = 0.0, 0.0
+    X[k:] *= 1e-9
+    Q[h:] *= 1e-9
+
+
+def _sparse(A, X, Q):            # a few numbers in a row, and none
+    g = torch.Generator(device=A.device)
+    g.manual_seed(9)
+    A *= torch.rand(A.shape, generator=g, device=A.device) < 0.002
+    A[7], A[:, 9] = 0.0, 0.0
+
+
+def _zeros(A, X, Q):
+    A[64:128, :], A[:, 64:200] = 0.0, 0.0
+    X[64:200], Q[64:128] = 0.0, 0.0
+    X[:, 1], Q[:, 1] = 0.0, 0.0
+
+
+@pytest.mark.parametrize("change", [_graded, _outliers, _few_outliers, _any_range, _panel_any_range, _indicators, _blocks, _sparse, _zeros])
+@pytest.mark.parametrize("rows,n,l,pad,off", [SHAPES[3], SHAPES[6], SHAPES[9], SHAPES[12]])
+def test_half_products_of_every_range(rows, n, l, pad, off, change):
+    """Each entry to the scale of the products it is made of, as with plain fp32 arithmetic."""
+    dev = need_gpu()
+    print(f"[case] half range {change.__name__} rows={rows} n={n} l={l}", flush=True)
+    A, X, Q = _inputs(rows, n, l, pad, off, dev)
+    change(A, X, Q)
+    # small products may be subnormal (2^-149 apart, half of that for each of the partial sums)
+    _check(A, X, Q, lambda K, a, x: _bound(K, a, x) + 2.0 ** -149 * K / 32)
+
+
+@pytest.mark.parametrize("scale_a,scale_x", [(1e-33, 1e28), (1e-41, 1e35), (1e30, 1e-37), (1e28, 1e-41), (1e-20, 1e-17), (1e30, 1e5)])
+def test_half_products_at_any_exponent(scale_a, scale_x):
+    dev = need_gpu()
+    A, X, Q = _inputs(*SHAPES[3][:3], 0, 0, dev)
+    A.mul_(scale_a)
+    _check(A, X * scale_x, Q * scale_x, lambda K, a, x: _bound(K, a, x) + 2.0 ** -149 * K / 32)
+
+
+@pytest.mark.parametrize("rows,n,l,pad,off", [SHAPES[3], (600, 16500, 161, 0, 0), (16500, 600, 273, 0, 0), SHAPES[12]])
+def test_half_products_not_finite(rows, n, l, pad, off):
+    _not_finite(rows, n, l, pad, off)
+
+
+def test_half_products_repeat_bit_for_bit():
+    """Also where some workgroups give up and redo their part."""
+    dev = need_gpu()
+    A, X, Q = _inputs(*SHAPES[3][:3], 0, 0, dev)
+    _few_outliers(A, X, Q)
+    first = B.brsvd_gemm_an(A, X), B.brsvd_gemm_at(A, Q)
+    for _ in range(3):
+        assert torch.equal(B.brsvd_gemm_an(A, X), first[0]) and torch.equal(B.brsvd_gemm_at(A, Q), first[1])

@@ -121,7 +121,19 @@ def test_which_products_are_split(which, rows, n, l, lda, address, split):
     assert not B.brsvd_gemm_is_split(which, rows, n, l, lda, address, dtype=B.BRSVD_DTYPE_F64)
 
 
+@pytest.mark.parametrize("which,rows,n,l,parts", [
+    (0, 20000, 20000, 110, 2), (1, 20000, 20000, 110, 2), (0, 89083, 2783, 97, 2), (1, 89083, 2783, 97, 2),
+    (0, 1000, 16384, 64, 2), (0, 1000, 16383, 64, 3), (1, 16384, 1000, 64, 2), (1, 16383, 1000, 64, 3),      # the contraction
+    (0, 65536, 1409, 64, 2), (0, 65536, 1344, 64, 3), (0, 16000, 5632, 64, 2), (0, 16000, 5000, 64, 3),      # or a workgroup's part of it
+])
+def test_parts_of_split_products(which, rows, n, l, parts):
+    assert B.brsvd_gemm_split_parts(which, rows, n, l) == parts
+
+
 def test_which_products_are_split_refuses():
+    for bad in ((2, 100, 100, 4), (0, 63, 100, 4), (1, 100, 100, 513), (0, 100, 100, 0)):
+        with pytest.raises(B.BrsvdError):
+            B.brsvd_gemm_split_parts(*bad)
     for bad in ((2, 10, 10, 4, 10), (0, 0, 10, 4, 10), (0, 10, 10, 0, 10), (0, 10, 10, 513, 10), (0, 10, 10, 4, 9)):
         with pytest.raises(B.BrsvdError):
             B.brsvd_gemm_is_split(*bad)
