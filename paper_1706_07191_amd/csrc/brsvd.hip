@@ -490,8 +490,8 @@ int enqueue_brsvd(brsvd_handle h, const T* A, int64_t lda, const T* Omega, T* U,
   }
   {
     Region r(h, CAT_LIFT, cs, true);
-    BRSVD_TRY(gemm_an(Ym, Lp, m, Lp, XV, Lp, U, l, l, scr, scr_bytes, cs));          // U = Q * Vr
-    BRSVD_TRY(gemm_an(Xn, Lp, n, Lp, XU, Lp, Tn, Lp, Lp, scr, scr_bytes, cs));       // V = W_B * Ur
+    BRSVD_TRY(apply_panel(Ym, m, Lp, XV, U, l, l, scr, scr_bytes, cs));          // U = Q * Vr
+    BRSVD_TRY(apply_panel(Xn, n, Lp, XU, Tn, Lp, Lp, scr, scr_bytes, cs));       // V = W_B * Ur
     BRSVD_TRY(transpose_panel(Tn, n, Lp, l, Vt, cs));
   }
   return BRSVD_OK;
@@ -573,8 +573,8 @@ int enqueue_alg2(brsvd_handle h, const T* A, int64_t lda, uint64_t seed, const T
   }
   {
     Region r(h, CAT_LIFT, cs);
-    BRSVD_TRY(gemm_an(Cm, Lp, m, Lp, XU, Lp, U, l, l, scr, scr_bytes, cs));            // U = W_C * Ur
-    BRSVD_TRY(gemm_an(Yn, Lp, n, Lp, XV, Lp, Pn1, Lp, Lp, scr, scr_bytes, cs));        // V = Q * Vr
+    BRSVD_TRY(apply_panel(Cm, m, Lp, XU, U, l, l, scr, scr_bytes, cs));            // U = W_C * Ur
+    BRSVD_TRY(apply_panel(Yn, n, Lp, XV, Pn1, Lp, Lp, scr, scr_bytes, cs));        // V = Q * Vr
     BRSVD_TRY(transpose_panel(Pn1, n, Lp, l, Vt, cs));
   }
   return BRSVD_OK;

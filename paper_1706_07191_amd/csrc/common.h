@@ -172,6 +172,10 @@ struct OrthWorkT {
   int64_t comp_rows = 0;
 };
 typedef OrthWorkT<float> OrthWork;
+// out (rows x ncols, leading dimension ldo) = P X; P: rows x Lp padded panel, X: zero-padded Lp x Lp factor.  scratch as for gemm_an.
+template <typename T>
+int apply_panel(const T* P, int64_t rows, int Lp, const T* X, T* out, int64_t ldo, int ncols, void* scratch, uint64_t scratch_bytes,
+                hipStream_t stream);
 // Applies the current w.Rinv to the companion panel, if any.
 template <typename T> int apply_to_companion(OrthWorkT<T>& w, int Lp, hipStream_t stream);
 uint64_t orth_gram_slots(int64_t rows, int Lp);   // Lp x Lp fp64 slots of partial Gram sums for such a panel

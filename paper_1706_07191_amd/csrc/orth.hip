@@ -8,6 +8,7 @@
 // The paper orthonormalises with a TSQR-based CAQR; range(P) -- all the method needs -- is the
 // same for any orthonormalisation.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 
@@ -450,11 +451,91 @@ int chol_inv_factored(double* G, int l, int Lp, double* Rout, T* Rinv, int* flag
   return chol_inv<T>(G, l, Lp, Rout, Rinv, flags, 0.0, stream, 1);
 }
 
+// ---- panel times an Lp x Lp factor ----------------------------------------------------------
+// out = P X for a narrow fp32 panel (rows x Lp, Lp = 16 NT): no staging and no barrier.  A wave holds all of X in registers and walks
+// over tiles of 16 rows, the next tile's loads in flight under the matrix instructions (v_mfma_f32_16x16x4_f32).  X is the first
+// operand: lane (r, g) holds X[16j + 4g + i][16t + r] for the instructions (j, i) of tile t, and the 16 bytes P[r][16j + 4g ..] of its
+// row; its results are out[r][16t + 4g ..], 16 bytes again.
+// What bounds it: the panel's read and write.  k_gemm_an, made for long contractions, takes chunks of 64 indices with a barrier
+// each, half of them padding at 32 columns.  Measured, k_gemm_an and this (us, padded columns): 2073600x32 132 and 105 (5.1 TB/s),
+// 400000x48 37.6 and 32.2, 76800x32 9.1 and 6.4, 2000x32 4.5 and 1.8 to 3.9; with four tiles 1000000x64 125 and 131.
+template <int NT>
+__global__ void __launch_bounds__(256)
+k_apply(const float* __restrict__ P, int64_t rows, const float* __restrict__ X, float* __restrict__ out, int64_t ldo, int ncols) {
+  constexpr int Lp = 16 * NT;
+  typedef floatx4 floatx4u __attribute__((aligned(4)));
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int64_t tiles = (rows + 15) / 16, stride = (int64_t)gridDim.x * 4;
+  int64_t tile = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (tile >= tiles) return;
+  auto load = [&](int64_t t, floatx4 (&a)[NT]) {
+    const float* p = P + min(t * 16 + r, rows - 1) * Lp + 4 * g;
+#pragma unroll
+    for (int j = 0; j < NT; ++j) a[j] = *(const floatx4*)(p + 16 * j);
+  };
+  floatx4 next[NT];
+  load(tile, next);
+  float x[NT][NT][4];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[t][j][i] = X[(16 * j + 4 * g + i) * Lp + 16 * t + r];
+  for (; tile < tiles; tile += stride) {
+    floatx4 a[NT], acc[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) { a[j] = next[j]; acc[j] = floatx4{0.f, 0.f, 0.f, 0.f}; }
+    if (tile + stride < tiles) load(tile + stride, next);
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t][j][i], a[j][i], acc[t], 0, 0, 0);
+    const int64_t row = tile * 16 + r;
+    if (row < rows) {
+      float* o = out + row * ldo;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const int col = 16 * t + 4 * g;
+        if (col + 4 <= ncols) {
+          *(floatx4u*)(o + col) = acc[t];
+        } else {
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            if (col + v < ncols) o[col + v] = acc[t][v];
+        }
+      }
+    }
+  }
+}
+
+template <typename T>
+int apply_panel(const T* P, int64_t rows, int Lp, const T* X, T* out, int64_t ldo, int ncols, void* scratch, uint64_t scratch_bytes,
+                hipStream_t stream) {
+  if constexpr (std::is_same<T, float>::value) {
+    // from 64 columns on the matrix cores bound both kernels, and more of X than this takes too many registers
+    if (Lp <= 48) {
+      const dim3 grid((unsigned)std::min<int64_t>(ceil_div(rows, 64), 2048)), block(256);   // eight workgroups of four waves per CU
+      switch (Lp / 16) {
+        case 1: hipLaunchKernelGGL(k_apply<1>, grid, block, 0, stream, P, rows, X, out, ldo, ncols); break;
+        case 2: hipLaunchKernelGGL(k_apply<2>, grid, block, 0, stream, P, rows, X, out, ldo, ncols); break;
+        default: hipLaunchKernelGGL(k_apply<3>, grid, block, 0, stream, P, rows, X, out, ldo, ncols); break;
+      }
+      BRSVD_HIP_TRY(hipGetLastError());
+      return BRSVD_OK;
+    }
+  }
+  return gemm_an(P, Lp, rows, Lp, X, Lp, out, ldo, ncols, scratch, scratch_bytes, stream);
+}
+template int apply_panel<float>(const float*, int64_t, int, const float*, float*, int64_t, int, void*, uint64_t, hipStream_t);
+template int apply_panel<double>(const double*, int64_t, int, const double*, double*, int64_t, int, void*, uint64_t, hipStream_t);
+
 template <typename T>
 int apply_to_companion(OrthWorkT<T>& w, int Lp, hipStream_t stream) {
   if (!w.comp) return BRSVD_OK;
-  BRSVD_TRY(gemm_an(w.comp, Lp, w.comp_rows, Lp, w.Rinv, Lp, w.comp_tmp, Lp, Lp, w.gemm_scratch, w.gemm_scratch_bytes,
-                    stream));
+  BRSVD_TRY(apply_panel(w.comp, w.comp_rows, Lp, w.Rinv, w.comp_tmp, Lp, Lp, w.gemm_scratch, w.gemm_scratch_bytes, stream));
   T* t = w.comp; w.comp = w.comp_tmp; w.comp_tmp = t;
   return BRSVD_OK;
 }
@@ -507,7 +588,7 @@ int cholqr_sweeps(T* P, T* tmp, int64_t rows, int l, int Lp, int nsweeps, OrthWo
     const int lenient = (sweep + 1 < nsweeps || !strict_last) ? 1 : 0;
     double* Rs = (Rtot || publish_R) ? w.R[sweep] : nullptr;      // the factor is only written out when someone reads it
     BRSVD_TRY(chol_inv<T>(w.G, l, Lp, Rs, w.Rinv, w.flags, tol, stream, 0, lenient));
-    BRSVD_TRY(gemm_an(src, Lp, rows, Lp, w.Rinv, Lp, dst, Lp, Lp, w.gemm_scratch, w.gemm_scratch_bytes, stream));
+    BRSVD_TRY(apply_panel(src, rows, Lp, w.Rinv, dst, Lp, Lp, w.gemm_scratch, w.gemm_scratch_bytes, stream));
     BRSVD_TRY(apply_to_companion<T>(w, Lp, stream));
     T* t = src; src = dst; dst = t;
   }

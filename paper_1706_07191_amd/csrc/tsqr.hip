@@ -141,7 +141,7 @@ int tsqr_panel(T* P, T* tmp, int64_t rows, int l, int Lp, OrthWorkT<T>& w, doubl
   BRSVD_HIP_TRY(hipGetLastError());
   double* Rt = stack[cur ^ 1];    // free now: keeps the TSQR factor for the product R2 * R
   BRSVD_TRY(chol_inv_factored<T>(w.G, l, Lp, Rt, w.Rinv, w.flags, stream));
-  BRSVD_TRY(gemm_an(P, Lp, rows, Lp, w.Rinv, Lp, tmp, Lp, Lp, w.gemm_scratch, w.gemm_scratch_bytes, stream));
+  BRSVD_TRY(apply_panel(P, rows, Lp, w.Rinv, tmp, Lp, Lp, w.gemm_scratch, w.gemm_scratch_bytes, stream));
   BRSVD_TRY(apply_to_companion<T>(w, Lp, stream));
   T* res = nullptr;
   BRSVD_TRY(cholqr_sweeps<T>(tmp, P, rows, l, Lp, 1, w, nullptr, &res, stream, true, Rtot != nullptr));

@@ -247,3 +247,27 @@ def test_workgroups_see_each_others_rows(l):
         for _ in range(60):
             again = B.brsvd_small_svd(R)
             assert all(bool(torch.equal(a.nan_to_num(), b.nan_to_num())) for a, b in zip(first, again))
+
+
+@pytest.mark.parametrize("l", [1, 16, 17, 33, 48])
+@pytest.mark.parametrize("rows", [51, 1000, 131089])
+def test_narrow_panels_times_their_factors(l, rows):
+    """Tiles of 16 rows that end in a remainder, and more of them than waves (131072 rows): the factors applied by the
+    orthonormalisation (whole padded panels) and by the lift (l columns)."""
+    dev = need_gpu()
+    print(f"[case] apply l={l} rows={rows}", flush=True)
+    P = _panel(rows, l, 30.0, 11).to(dev)
+    Q, R, _ = B.brsvd_orth(P.clone(), want_R=True)
+    Pd, Qd = P.double(), Q.double()
+    # two sweeps, each a product over l terms with a rounding per term
+    assert float((Qd @ R.double() - Pd).abs().max() / Pd.abs().max()) <= 4 * (l + 2) * EPS32
+    assert float((Qd.T @ Qd - torch.eye(l, device=dev, dtype=torch.float64)).abs().max()) <= 4 * (l + 2) * EPS32
+    A = (P @ _panel(l + 40, l, 3.0, 12).to(dev).T).contiguous()
+    h = B.brsvd_create(B.make_params(rows, l + 40, l, 0, 1))
+    try:
+        U, S, Vt, _ = B.brsvd_run(h, A, torch.randn(l + 40, l, generator=torch.Generator().manual_seed(3)).to(dev))
+    finally:
+        B.brsvd_destroy(h)
+    err = (U.double() * S.double()) @ Vt.double() - A.double()
+    assert float(err.norm() / A.double().norm()) <= 1e-5            # rank l exactly, fp32 products
+    assert float((U.double().T @ U.double() - torch.eye(l, device=dev, dtype=torch.float64)).abs().max()) <= 1e-5
