@@ -766,16 +766,20 @@ int norm2_power_impl(brsvd_handle h, const T* A, int64_t lda, const T* x0, int32
   const uint64_t scr_bytes = h->lay.gemm_scratch_bytes;
   double* part = h->at<double>(h->lay.rpca_part);
   double* scal = h->at<double>(h->lay.scal);
-  BRSVD_TRY(pad_panel(x0, n, 1, xn, L1, cs));
-  BRSVD_TRY(rpca_norms<T>(xn, n * L1, part, scal, cs));
-  BRSVD_TRY(scale_rsqrt<T>(xn, n * L1, scal + 1, cs));
-  for (int it = 0; it < iters; ++it) {
-    BRSVD_TRY(gemm_an(A, lda, m, n, xn, L1, ym, L1, L1, scr, scr_bytes, cs));              // y = A x
-    BRSVD_TRY(rpca_norms<T>(ym, m * L1, part, scal + 2, cs));                                  // est^2 = |y|^2
-    BRSVD_TRY(gemm_at(A, lda, m, n, ym, L1, zn, false, m, scr, scr_bytes, cs));            // z = A^T y
-    BRSVD_TRY(rpca_norms<T>(zn, n * L1, part, scal + 4, cs));
-    BRSVD_TRY(scale_rsqrt<T>(zn, n * L1, scal + 5, cs));                                       // x = z / |z|
-    std::swap(xn, zn);
+  if (power_fits<T>(m, n, scr_bytes)) {
+    BRSVD_TRY(power_method<T>(A, lda, m, n, x0, iters, xn, scr, scr_bytes, scal + 3, cs));
+  } else {                              // longer rows: two products on panels
+    BRSVD_TRY(pad_panel(x0, n, 1, xn, L1, cs));
+    BRSVD_TRY(rpca_norms<T>(xn, n * L1, part, scal, cs));
+    BRSVD_TRY(scale_rsqrt<T>(xn, n * L1, scal + 1, cs));
+    for (int it = 0; it < iters; ++it) {
+      BRSVD_TRY(gemm_an(A, lda, m, n, xn, L1, ym, L1, L1, scr, scr_bytes, cs));              // y = A x
+      BRSVD_TRY(rpca_norms<T>(ym, m * L1, part, scal + 2, cs));                                  // est^2 = |y|^2
+      BRSVD_TRY(gemm_at(A, lda, m, n, ym, L1, zn, false, m, scr, scr_bytes, cs));            // z = A^T y
+      BRSVD_TRY(rpca_norms<T>(zn, n * L1, part, scal + 4, cs));
+      BRSVD_TRY(scale_rsqrt<T>(zn, n * L1, scal + 5, cs));                                       // x = z / |z|
+      std::swap(xn, zn);
+    }
   }
   BRSVD_HIP_TRY(hipMemcpyAsync(h->host_scal, scal + 3, sizeof(double), hipMemcpyDeviceToHost, cs));
   BRSVD_HIP_TRY(hipStreamSynchronize(cs));

@@ -253,6 +253,12 @@ int rpca_residual_sum(double* part, int nparts, double* resid2_out, hipStream_t 
 template <typename T>
 int rpca_finalize(const T* M, const T* U, const T* sig, const T* Vt, int64_t m, int64_t n, int l, T mu, T lambda,
                   const T* Yin, T* Lout, T* S, hipStream_t stream);
+// `iters` steps x = z / |z|, y = A x, z = A^T y of the power method, z = x0 at first; *y2 (device) = |y|^2 of the last.  z: n elements of
+// workspace.  For rows that a workgroup can hold, and scratch for at least 64 parts of z (power_fits).
+template <typename T> bool power_fits(int64_t m, int64_t n, uint64_t scratch_bytes);
+template <typename T>
+int power_method(const T* A, int64_t lda, int64_t m, int64_t n, const T* x0, int iters, T* z, void* scratch, uint64_t scratch_bytes,
+                 double* y2, hipStream_t stream);
 // P[0..count) *= 1 / sqrt(*s2) (device scalar; a zero scalar zeroes P).
 template <typename T> int scale_rsqrt(T* P, int64_t count, const double* s2, hipStream_t stream);
 

@@ -261,6 +261,195 @@ k_rpca_update_vec(const T* __restrict__ M, const T* __restrict__ U, const T* __r
   }
 }
 
+// ---- one step of the power method for ||A||_2: y = A x, z = A^T y with a single read of A ------
+// A row is held in registers between its product with x and its part of z.  TPR threads share a row, each with K vectors
+// of 16 bytes of it, at distance TPR vectors (consecutive threads read consecutive addresses), in RB rows at a time; the
+// threads keep the same columns for all their rows, so x and the sums z stay in registers as well.  TPR <= 64: the row's product is added up
+// within a wave; TPR = 256: across the workgroup's four waves, through LDS.  Rows start at any element address.  The workgroups' parts of z are
+// added by k_power_sum, in their order.
+// What bounds it: the read of A.  Measured (us per step, with two products on 16-column panels and three norms before, and now):
+// 2073600x100 fp32 420 and 156 (5.6 TB/s), 76800x2000 245 and 127 (5.1 TB/s), 32256x2383 fp64 265 and 141 (4.7 TB/s).
+template <typename T, int TPR, int K, int RB>
+__global__ void __launch_bounds__(256)
+k_power_step(const T* __restrict__ A, int64_t lda, int64_t rows, int n, const T* __restrict__ x, const double* __restrict__ xx, int nxx,
+             T* __restrict__ zpart, double* __restrict__ yy) {
+  constexpr int V = 16 / sizeof(T), GROUPS = 256 / TPR, WAVES = TPR > 64 ? TPR / 64 : 1;
+  typedef T vec __attribute__((ext_vector_type(V)));
+  typedef vec vecu __attribute__((aligned(sizeof(T))));
+  __shared__ vec comb[256];
+  __shared__ T dots[2][RB][4];
+  __shared__ double sh[4];
+  const int tid = threadIdx.x, lane = tid & 63, tr = tid % TPR, grp = tid / TPR;
+  // x / |x|, or zero if x is
+  double s2 = 0.0;
+  for (int i = lane; i < nxx; i += 64) s2 += xx[i];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s2 += __shfl_xor(s2, o, 64);
+  const T scale = s2 > 0.0 ? (T)(1.0 / sqrt(s2)) : (s2 == 0.0 ? T(0) : (T)s2);
+  int col[K];                                          // of the load; elements before `own` belong to the vector before
+  int own[K];
+  vec xv[K], z[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int c = (k * TPR + tr) * V;
+    col[k] = min(c, n - V);
+    own[k] = min(c - col[k], V);
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      xv[k][v] = v >= own[k] ? x[col[k] + v] * scale : T(0);
+      z[k][v] = T(0);
+    }
+  }
+  double ysum = 0.0;
+  int parity = 0;
+  for (int64_t r0 = (int64_t)blockIdx.x * (GROUPS * RB); r0 < rows; r0 += (int64_t)gridDim.x * (GROUPS * RB)) {
+    vec a[RB][K];
+    T y[RB];
+    bool valid[RB];
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+      const int64_t row = r0 + grp * RB + b;
+      valid[b] = row < rows;
+      const T* p = A + (valid[b] ? row : rows - 1) * lda;
+#pragma unroll
+      for (int k = 0; k < K; ++k) a[b][k] = *(const vecu*)(p + col[k]);
+    }
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+      T d = T(0);
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          a[b][k][v] = valid[b] && v >= own[k] ? a[b][k][v] : T(0);
+          d = fma(a[b][k][v], xv[k][v], d);
+        }
+#pragma unroll
+      for (int o = (TPR < 64 ? TPR : 64) / 2; o > 0; o >>= 1) d += __shfl_xor(d, o, 64);
+      y[b] = d;
+    }
+    if constexpr (WAVES > 1) {
+      if (lane == 0) {
+#pragma unroll
+        for (int b = 0; b < RB; ++b) dots[parity][b][tid >> 6] = y[b];
+      }
+      __syncthreads();                                 // the other half is written before the next one
+#pragma unroll
+      for (int b = 0; b < RB; ++b) y[b] = (dots[parity][b][0] + dots[parity][b][1]) + (dots[parity][b][2] + dots[parity][b][3]);
+      parity ^= 1;
+    }
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+      if (tr == 0) ysum = fma((double)y[b], (double)y[b], ysum);
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int v = 0; v < V; ++v) z[k][v] = fma(a[b][k][v], y[b], z[k][v]);
+    }
+  }
+  // the groups' sums, in their order
+  T* out = zpart + (int64_t)blockIdx.x * n;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    vec s = z[k];
+    if constexpr (GROUPS > 1) {
+      __syncthreads();
+      comb[tid] = s;
+      __syncthreads();
+      for (int g = 1; g < GROUPS; ++g) s += comb[g * TPR + tr];
+    }
+    if (grp == 0) {
+#pragma unroll
+      for (int v = 0; v < V; ++v)
+        if (v >= own[k]) out[col[k] + v] = s[v];
+    }
+  }
+  const double t = block_sum(ysum, sh);
+  if (tid == 0) yy[blockIdx.x] = t;
+}
+
+// z = sum of `parts` rows of zpart (64 columns per workgroup, 16 threads each), zz[workgroup] = its part of |z|^2; the first
+// workgroup also adds up yy.
+template <typename T>
+__global__ void __launch_bounds__(1024)
+k_power_sum(const T* __restrict__ zpart, int parts, int n, T* __restrict__ z, double* __restrict__ zz, const double* __restrict__ yy,
+            double* __restrict__ y2) {
+  __shared__ double sums[16][64];
+  __shared__ double sh[16];
+  const int tid = threadIdx.x, c = tid & 63, h = tid >> 6, col = blockIdx.x * 64 + c;
+  double s = 0.0;
+  if (col < n) {
+#pragma unroll 8
+    for (int p = h; p < parts; p += 16) s += (double)zpart[(int64_t)p * n + col];
+  }
+  sums[h][c] = s;
+  __syncthreads();
+  double v = 0.0;
+  if (h == 0 && col < n) {
+    for (int w = 0; w < 16; ++w) v += sums[w][c];
+    const T zc = (T)v;
+    z[col] = zc;
+    v = (double)zc * (double)zc;
+  }
+  const double t = block_sum(v, sh);
+  if (tid == 0) zz[blockIdx.x] = t;
+  if (blockIdx.x == 0 && yy) {
+    __syncthreads();
+    double e = 0.0;
+    for (int p = tid; p < parts; p += 1024) e += yy[p];
+    const double est = block_sum(e, sh);
+    if (tid == 0) *y2 = est;
+  }
+}
+
+// Columns a workgroup can hold (8 vectors for each of 256 threads); z's parts in scratch, and behind them the sums of squares.
+constexpr int kPowerParts = 1024;
+template <typename T>
+static int power_parts(int64_t m, int64_t n, uint64_t scratch_bytes) {
+  constexpr int V = 16 / sizeof(T);
+  if (n < V || n > 8 * 256 * V) return 0;
+  const uint64_t fixed = 8 * (uint64_t)(kPowerParts + 2 * ceil_div(n, 64) + 2);
+  if (scratch_bytes < fixed) return 0;
+  return (int)std::min<uint64_t>(std::min<uint64_t>(kPowerParts, (uint64_t)ceil_div(m, 16)), (scratch_bytes - fixed) / ((uint64_t)n * sizeof(T)));
+}
+template <typename T>
+bool power_fits(int64_t m, int64_t n, uint64_t scratch_bytes) {
+  return power_parts<T>(m, n, scratch_bytes) >= std::min<int64_t>(64, ceil_div(m, 16));
+}
+
+template <typename T>
+int power_method(const T* A, int64_t lda, int64_t m, int64_t n, const T* x0, int iters, T* z, void* scratch, uint64_t scratch_bytes,
+                 double* y2, hipStream_t stream) {
+  if (!power_fits<T>(m, n, scratch_bytes)) return BRSVD_ERR_ARG;
+  const int parts = power_parts<T>(m, n, scratch_bytes), wgs = (int)ceil_div(n, 64);
+  double* yy = (double*)scratch;
+  double* zz = yy + kPowerParts;
+  T* zpart = (T*)(zz + 2 * wgs + 2);
+  const dim3 grid(parts), block(256);
+  hipLaunchKernelGGL(k_power_sum<T>, dim3(wgs), dim3(1024), 0, stream, x0, 1, (int)n, z, zz, nullptr, nullptr);
+  BRSVD_HIP_TRY(hipGetLastError());
+  const int64_t vecs = ceil_div(n, 16 / (int64_t)sizeof(T));
+  for (int it = 0; it < iters; ++it) {
+#define CALL(TPR, K, RB) \
+  hipLaunchKernelGGL((k_power_step<T, TPR, K, RB>), grid, block, 0, stream, A, lda, m, (int)n, z, zz, wgs, zpart, yy)
+    if (vecs <= 16) CALL(16, 1, 8);
+    else if (vecs <= 32) CALL(32, 1, 8);
+    else if (vecs <= 64) CALL(64, 1, 8);
+    else if (vecs <= 128) CALL(64, 2, 4);
+    else if (vecs <= 256) CALL(64, 4, 4);
+    else if (vecs <= 512) CALL(64, 8, 2);
+    else if (vecs <= 768) CALL(256, 3, 4);
+    else if (vecs <= 1024) CALL(256, 4, 4);
+    else if (vecs <= 1536) CALL(256, 6, 2);
+    else CALL(256, 8, 2);
+#undef CALL
+    BRSVD_HIP_TRY(hipGetLastError());
+    hipLaunchKernelGGL(k_power_sum<T>, dim3(wgs), dim3(1024), 0, stream, zpart, parts, (int)n, z, zz, yy, y2);
+    BRSVD_HIP_TRY(hipGetLastError());
+  }
+  return BRSVD_OK;
+}
+
 // P *= 1 / sqrt(*s2)  (normalisation of a power-method vector held in a padded panel)
 template <typename T>
 __global__ void k_scale_rsqrt(T* __restrict__ P, int64_t count, const double* __restrict__ s2) {
@@ -389,6 +578,8 @@ int scale_rsqrt(T* P, int64_t count, const double* s2, hipStream_t stream) {
                               T*, double*, int*, hipStream_t);                                                      \
   template int rpca_finalize<T>(const T*, const T*, const T*, const T*, int64_t, int64_t, int, T, T, const T*, T*,  \
                                 T*, hipStream_t);                                                                   \
+  template bool power_fits<T>(int64_t, int64_t, uint64_t);                                                                      \
+  template int power_method<T>(const T*, int64_t, int64_t, int64_t, const T*, int, T*, void*, uint64_t, double*, hipStream_t);  \
   template int scale_rsqrt<T>(T*, int64_t, const double*, hipStream_t);
 BRSVD_RPCA_INSTANTIATE(float)
 BRSVD_RPCA_INSTANTIATE(double)

@@ -278,3 +278,31 @@ def test_rpca_paper_shapes_full_size(m, n, tol):
     assert float(torch.linalg.norm(L - L0) / torch.linalg.norm(L0)) < 2e-3
     assert float(torch.linalg.norm(S - S0) / torch.linalg.norm(S0)) < 2e-3
     assert st["passes_over_A"] == done * (2 * cfg.q + 2)
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("n", [3, 4, 5, 61, 64, 65, 130, 257, 515, 1027, 2047, 2050, 3073, 4099, 6146, 8191, 8193])
+def test_norm2_power_row_lengths(n, f64):
+    """Rows that end within a vector, one longer than a group of threads holds and than a workgroup does; rows and a base off the
+    16-byte grid; fewer rows than a workgroup takes at a time, and a remainder."""
+    dev = need_gpu()
+    dt = torch.float64 if f64 else torch.float32
+    for m, pad, off in ((13, 0, 0), (1031, 3, 1)):
+        print(f"[case] power m={m} n={n} pad={pad} f64={f64}", flush=True)
+        flat = torch.full((m * (n + pad) + 8,), float("nan"), device=dev, dtype=dt)      # nothing but A is read
+        A = flat[off:off + m * (n + pad)].view(m, n + pad)[:, :n]
+        A.copy_(synth.gaussian(m, n, 31, device=dev).to(dt) + 0.25)
+        x0 = synth.gaussian(n, 1, 32, device=dev).reshape(-1).to(dt)
+        h = B.brsvd_create(B.make_params(m, n, 1, 0, 1, dtype=B.BRSVD_DTYPE_F64 if f64 else B.BRSVD_DTYPE_F32))
+        try:
+            for iters in (1, 3):
+                got = B.brsvd_norm2_power(h, A, x0, iters)
+                want = O.norm2_power(A.double().cpu().numpy(), x0.double().cpu().numpy(), iters)
+                # two sums per step, of n and of m terms, each with a rounding per term, as random walks
+                eps = 2.0 ** -52 if f64 else 2.0 ** -23
+                assert abs(got - want) <= 4 * iters * np.sqrt(m + n) * eps * want
+            assert B.brsvd_norm2_power(h, A, torch.zeros_like(x0), 2) == 0.0
+            A[m // 2, n // 2] = float("nan")
+            assert not np.isfinite(B.brsvd_norm2_power(h, A, x0, 2))
+        finally:
+            B.brsvd_destroy(h)
