@@ -79,7 +79,7 @@ def test_small_svd(l, cond):
 
 @pytest.mark.parametrize("l", [2, 3, 20, 21])
 def test_small_svd_at_the_ends_of_the_row_rotations(l):
-    """Row rotations up to 20 rows, one block pair from 21 on."""
+    """Row rotations up to 16 rows, one block pair from 17 on."""
     for cond in (1e2, 1e8):
         test_small_svd(l, cond)
 
