@@ -307,39 +307,40 @@ bool uses_split(brsvd_handle h, bool at, const T* A, int64_t out, int64_t K, int
   return split_fits(at, A, out, K, h->Lp, lda, h->lay.tsqr_bytes);
 }
 
+// whole: wide fp32 operands are split without loss (three bf16 numbers), see enqueue_alg2.
 template <typename T>
-int product_an(brsvd_handle h, const T* A, int64_t lda, int64_t rows, const T* X, T* Y, const KernelEvents* ke) {
+int product_an(brsvd_handle h, const T* A, int64_t lda, int64_t rows, const T* X, T* Y, const KernelEvents* ke, bool whole = false) {
   const int Lp = h->Lp;
   void* scr = h->arena + h->lay.gemm_scratch;
   if constexpr (sizeof(T) == 4) {
     if (uses_split<T>(h, false, A, rows, h->prm.n, lda))
       return split_gemm_an(A, lda, rows, h->prm.n, X, Lp, Lp, Lp, Y, Lp, Lp, scr, h->lay.gemm_scratch_bytes,
-                           h->arena + h->lay.tsqr, h->lay.tsqr_bytes, h->compute, ke);
+                           h->arena + h->lay.tsqr, h->lay.tsqr_bytes, h->compute, ke, whole);
   }
   return gemm_an(A, lda, rows, h->prm.n, X, Lp, Y, Lp, Lp, scr, h->lay.gemm_scratch_bytes, h->compute, ke);
 }
 
 template <typename T>
 int product_at(brsvd_handle h, const T* A, int64_t lda, int64_t rows, const T* Q, T* Z, bool accumulate,
-               const KernelEvents* ke) {
+               const KernelEvents* ke, bool whole = false) {
   const int Lp = h->Lp;
   void* scr = h->arena + h->lay.gemm_scratch;
   if constexpr (sizeof(T) == 4) {
     if (uses_split<T>(h, true, A, h->prm.n, rows, lda))
       return split_gemm_at(A, lda, rows, h->prm.n, Q, Lp, Lp, Lp, Z, Lp, Lp, accumulate, scr, h->lay.gemm_scratch_bytes,
-                           h->arena + h->lay.tsqr, h->lay.tsqr_bytes, h->compute, ke);
+                           h->arena + h->lay.tsqr, h->lay.tsqr_bytes, h->compute, ke, whole);
   }
   return gemm_at(A, lda, rows, h->prm.n, Q, Lp, Z, accumulate, rows, scr, h->lay.gemm_scratch_bytes, h->compute, ke);
 }
 
 template <typename T>
-int pass_an(brsvd_handle h, const T* A, int64_t lda, const T* X, T* Y, bool follows = false) {
+int pass_an(brsvd_handle h, const T* A, int64_t lda, const T* X, T* Y, bool follows = false, bool whole = false) {
   const int Lp = h->Lp;
   const int64_t m = h->prm.m, n = h->prm.n;
   if (!h->host_a) {
     KernelEvents ke;
     bool t = kernel_events(h, CAT_AN, m, &ke, follows);
-    return product_an<T>(h, A, lda, m, X, Y, t ? &ke : nullptr);
+    return product_an<T>(h, A, lda, m, X, Y, t ? &ke : nullptr, whole);
   }
   Streamer st(h, A, lda);
   for (int i = 0; i < h->nblocks; ++i) {
@@ -347,7 +348,7 @@ int pass_an(brsvd_handle h, const T* A, int64_t lda, const T* X, T* Y, bool foll
     BRSVD_TRY(st.acquire(i, &blk));
     KernelEvents ke;
     bool t = kernel_events(h, CAT_AN, st.rows_of(i), &ke);
-    BRSVD_TRY(product_an<T>(h, blk, n, st.rows_of(i), X, Y + (int64_t)i * h->b * Lp, t ? &ke : nullptr));
+    BRSVD_TRY(product_an<T>(h, blk, n, st.rows_of(i), X, Y + (int64_t)i * h->b * Lp, t ? &ke : nullptr, whole));
     BRSVD_TRY(st.release(i));
   }
   return BRSVD_OK;
@@ -505,6 +506,8 @@ int enqueue_brsvd(brsvd_handle h, const T* A, int64_t lda, const T* Omega, T* U,
 //   second sweep   C_I = A_I Q  (C = B^T, m x l)
 //   C = W_C R, R = Ur diag(s) Vr^T   =>   A ~ (W_C Ur) diag(s) (Q Vr)^T
 // Two reads of A whatever q is.  Omega (m x l, device) overrides the generator when not null.
+// The powers of a block are not orthonormalised in between, so the columns of Y are nearly parallel and what its products lose comes
+// out multiplied by its condition: rounding of 1e-7 as 2e-4 in U and V (40000 x 12000, l = 60).  Their operands keep all 24 bits.
 template <typename T>
 int enqueue_alg2(brsvd_handle h, const T* A, int64_t lda, uint64_t seed, const T* Omega, T* U, T* S, T* Vt,
                  int method) {
@@ -531,7 +534,7 @@ int enqueue_alg2(brsvd_handle h, const T* A, int64_t lda, uint64_t seed, const T
     auto at = [&](const T* Qp, T* Z, bool accumulate) {
       KernelEvents ke;
       bool t = kernel_events(h, CAT_AT, rows, &ke);
-      return product_at<T>(h, blk, ldb, rows, Qp, Z, accumulate, t ? &ke : nullptr);
+      return product_at<T>(h, blk, ldb, rows, Qp, Z, accumulate, t ? &ke : nullptr, true);
     };
     if (q == 0) {
       BRSVD_TRY(at(OmI, Yn, i > 0));
@@ -540,7 +543,7 @@ int enqueue_alg2(brsvd_handle h, const T* A, int64_t lda, uint64_t seed, const T
       for (int t = 0; t < q; ++t) {
         KernelEvents ke;
         bool tm = kernel_events(h, CAT_AN, rows, &ke);
-        BRSVD_TRY(product_an<T>(h, blk, ldb, rows, Pn1, TI, tm ? &ke : nullptr));
+        BRSVD_TRY(product_an<T>(h, blk, ldb, rows, Pn1, TI, tm ? &ke : nullptr, true));
         const bool last = t == q - 1;
         BRSVD_TRY(at(TI, last ? Yn : Pn1, last && i > 0));
       }
@@ -554,7 +557,7 @@ int enqueue_alg2(brsvd_handle h, const T* A, int64_t lda, uint64_t seed, const T
   }
   T* Cm = h->Pm<T>(0);
   T* Tm = h->Pm<T>(1);
-  BRSVD_TRY(pass_an<T>(h, A, lda, Yn, Cm));                 // second sweep: C = A Q
+  BRSVD_TRY(pass_an<T>(h, A, lda, Yn, Cm, false, true));                 // second sweep: C = A Q
   double* Rtot = h->at<double>(h->lay.Rtot);
   {
     Region r(h, CAT_ORTH, cs);

@@ -129,13 +129,14 @@ SplitPlan split_an_plan(int64_t rows, int64_t K, int Lp, uint64_t scratch_bytes)
 SplitPlan split_at_plan(int64_t rows, int64_t n, int Lp, uint64_t scratch_bytes);
 bool split_fits(bool at, const float* A, int64_t out, int64_t K, int Lp, int64_t lda, uint64_t pack_bytes);
 int split_parts(bool at, int64_t out, int64_t K, int Lp);   // 16-bit numbers an operand is split into, with all the scratch it can use
-// X (K x xcols, leading dimension ldx) and Q (rows x qcols, ldq) need no padding; Lp = padded width of the partial panels.
+// X (K x xcols, leading dimension ldx) and Q (rows x qcols, ldq) need no padding; Lp = padded width of the partial panels.  whole: three
+// bf16 numbers, which hold all 24 bits of an operand, whatever its length.
 int split_gemm_an(const float* A, int64_t lda, int64_t rows, int64_t K, const float* X, int64_t ldx, int xcols, int Lp,
                   float* Y, int64_t ldy, int ncols, void* scratch, uint64_t scratch_bytes, void* pack,
-                  uint64_t pack_bytes, hipStream_t stream, const KernelEvents* ev = nullptr);
+                  uint64_t pack_bytes, hipStream_t stream, const KernelEvents* ev = nullptr, bool whole = false);
 int split_gemm_at(const float* A, int64_t lda, int64_t rows, int64_t n, const float* Q, int64_t ldq, int qcols, int Lp,
                   float* Z, int64_t ldz, int ncols, bool accumulate, void* scratch, uint64_t scratch_bytes, void* pack,
-                  uint64_t pack_bytes, hipStream_t stream, const KernelEvents* ev = nullptr);
+                  uint64_t pack_bytes, hipStream_t stream, const KernelEvents* ev = nullptr, bool whole = false);
 
 // Launch plans as numbers (see brsvd_gemm_plan in the C ABI).
 void gemm_an_plan_describe(int64_t rows, int64_t K, int Lp, int esz, int32_t out[12]);

@@ -729,13 +729,13 @@ static SplitRepair group_repair(SplitRepair p, int c0, int nt) {
 
 int split_gemm_an(const float* A, int64_t lda, int64_t rows, int64_t K, const float* X, int64_t ldx, int xcols, int Lp,
                   float* Y, int64_t ldy, int ncols, void* scratch, uint64_t scratch_bytes, void* pack,
-                  uint64_t pack_bytes, hipStream_t stream, const KernelEvents* ev) {
+                  uint64_t pack_bytes, hipStream_t stream, const KernelEvents* ev, bool whole) {
   if (!split_fits(false, A, rows, K, Lp, lda, pack_bytes) || ncols > Lp) return BRSVD_ERR_ARG;
   const SplitPlan p = split_an_plan(rows, K, Lp, scratch_bytes);
   float* part = (float*)scratch;
   const int64_t stride = p.partial_rows * Lp;
   Packed x;
-  const bool half = half_fits_an(K, p);
+  const bool half = !whole && half_fits_an(K, p);
   HalfPacked hp;
   if (half) BRSVD_TRY(half_prepare(A, lda, rows, p.tile, X, K, ldx, xcols, Lp, false, pack, &x, &hp, stream));
   else BRSVD_TRY(split_pack(A, lda, rows, p.tile, X, K, ldx, xcols, Lp, pack, &x, stream));
@@ -789,7 +789,7 @@ int split_gemm_an(const float* A, int64_t lda, int64_t rows, int64_t K, const fl
 
 int split_gemm_at(const float* A, int64_t lda, int64_t rows, int64_t n, const float* Q, int64_t ldq, int qcols, int Lp,
                   float* Z, int64_t ldz, int ncols, bool accumulate, void* scratch, uint64_t scratch_bytes, void* pack,
-                  uint64_t pack_bytes, hipStream_t stream, const KernelEvents* ev) {
+                  uint64_t pack_bytes, hipStream_t stream, const KernelEvents* ev, bool whole) {
   if (!split_fits(true, A, n, rows, Lp, lda, pack_bytes) || ncols > Lp) return BRSVD_ERR_ARG;
   const SplitPlan p = split_at_plan(rows, n, Lp, scratch_bytes);
   if (p.nsplit < 1) return BRSVD_ERR_BUDGET;
@@ -797,7 +797,7 @@ int split_gemm_at(const float* A, int64_t lda, int64_t rows, int64_t n, const fl
   float* part = (float*)scratch;
   const int64_t stride = n * Lp;
   Packed x;
-  const bool half = half_fits_at(rows, p);
+  const bool half = !whole && half_fits_at(rows, p);
   HalfPacked hp;
   if (half) BRSVD_TRY(half_prepare(A, lda, n, p.tile, Q, rows, ldq, qcols, Lp, true, pack, &x, &hp, stream));
   else BRSVD_TRY(split_pack(A, lda, n, p.tile, Q, rows, ldq, qcols, Lp, pack, &x, stream));

@@ -8,7 +8,7 @@ import paper_1706_07191_amd as B
 from oracle import brsvd_oracle as O
 from oracle import philox as PX
 from paper_1706_07191_amd import synth
-from tests.gpu_util import ORTH_TOL, RECON_RTOL, SIGMA_RTOL, need_gpu, note
+from tests.gpu_util import EPS32, ORTH_TOL, RECON_RTOL, SIGMA_RTOL, need_gpu, note
 
 pytestmark = pytest.mark.gpu
 
@@ -181,3 +181,28 @@ def test_alg2_seeded_random_shapes():
         assert st["passes_over_A"] == (2 * q + 2) * (1 + st["orth_fallbacks"])
         assert f["sigma_rel"] <= SIGMA_RTOL and f["orthU"] <= ORTH_TOL and f["orthV"] <= ORTH_TOL
         assert abs(f["err_gpu"] - f["err_oracle"]) <= RECON_RTOL * f["err_oracle"]
+
+
+def test_alg2_products_keep_all_bits():
+    """The sketch of the block-local scheme is taken with operands of 24 bits, over long contractions too.  With q = 0 and one block it
+    is A^T Omega; a panel with one more column, sparse enough that its product takes that route in any case, gives the same columns bit
+    for bit.  Their condition is about 1e4, so that V would leave their span by 1e-3 if the sketch were rounded otherwise."""
+    dev = need_gpu()
+    m, n, l = 20000, 1500, 60
+    g = torch.Generator(device=dev)
+    g.manual_seed(3)
+    rnd = lambda *shape: torch.randn(*shape, generator=g, device=dev)
+    A = (rnd(m, l) * torch.logspace(0, -4, l, device=dev)) @ rnd(l, n) + 1e-6 * rnd(m, n)
+    Om = rnd(m, l)
+    assert B.brsvd_gemm_is_split(1, m, n, l) and B.brsvd_gemm_split_parts(1, m, n, l) == 2
+    h = B.brsvd_create(B.make_params(m, n, l - 10, 10, 0, row_block=m))
+    try:
+        _, _, Vt, _ = B.brsvd_run_alg2(h, A, l, Omega=Om)
+    finally:
+        B.brsvd_destroy(h)
+    wide = torch.zeros(m, l + 1, device=dev)
+    wide[:, :l] = Om
+    wide[::64, l] = 1.0
+    Q = B.brsvd_orth(B.brsvd_gemm_at(A, wide)[:, :l].contiguous())[0].double()
+    V = Vt.double().T
+    assert float((V - Q @ (Q.T @ V)).norm()) <= 2.0 * l * EPS32 * l ** 0.5
