@@ -9,20 +9,22 @@
 //
 // Range.  fp16 ends at 2^-24, so a number is only held to its 23 bits down to 2^-17 of the largest one under the same scale, below to
 // an error of 2^-39 of that one.  The scale of A belongs to a row (A^T Q: a column) and a step of 64 contraction indices, that of the
-// panel to a step.  An error of that kind only matters where the larger numbers don't enter the result, so the product is left to
-// bf16 numbers (which hold every range) when
-//   - the panel's step has a row below 2^-12 of its largest number (but not zero), or a column that is not zero with more than an
-//     eighth of its entries below that: there, the large numbers of A could meet small or no entries of the panel; or an infinity.
-//     Then, and where the packing's sample of A (16 rows per step) looks like the next, all workgroups leave their parts to k_split_fix_*;
-//   - in a row's step, four successive indices (4g.. of a lane) have no number above 2^-17 of the largest, but one that is not zero
-//     (for N(0, 1) entries the chance is below 2^-60): outliers, or numbers of many magnitudes; or the scales' product leaves the range
-//     of fp32.  Then the workgroup that meets it leaves its part, and what it has done by then is lost.
-// Measured, plain numbers, six bf16 products, and both in turn (us, A X / A^T Q, 20000x20000 l=64): 354 / 316; 380 / 369; all of A in
-// 40 decades 408 / 385, 20 rows of the panel zero 412 / 403, a single outlier in A 639 / 629.
+// panel to a step.  With M and N the largest of the two, such errors come to at most 2^-39 M N for each index of either operand that is
+// that small, and that is little beside the step's sum of |a||x| as long as enough large numbers meet:
+//   - of the 16 runs of four successive indices in a row's step, 14 or more hold a number of at least 2^-7 M;
+//   - a column of the panel has no more than 11 of its 64 entries below 2^-9 N, or is zero.
+// Each of those 11 takes the large number of one run, so at least 3 are left: the sum of |a||x| is at least 3 * 2^-16 M N, and the
+// (50 + 11) 2^-39 M N are less than 2^-18.6 of it.  With the 2^-21 that the split itself and l*l may lose, a step's sum is off by less
+// than 2^-18 of |a||x|, what 64 rounded fp32 additions may lose, whatever the numbers are.  (The last two steps of a contraction
+// may have as few as 32 indices.  Of those the first 32 count: 7 of 8 runs, 5 entries, and less than 2^-17 is lost.)  Of N(0, 1) entries a
+// step of a row fails with a chance below 10^-16, one of a panel of 272 columns below 10^-11 (of 32 indices 2 * 10^-5).
+// Where a test fails, or the scales' product leaves the range of fp32, or the panel has an infinity, bf16 numbers (which hold every
+// range) take over:
+//   - for a panel, and where the packing's sample of A (16 rows per step) fails: all workgroups leave their parts to k_split_fix_*;
+//   - for a row of A: the workgroup that meets it leaves its part, and what it has done by then is lost.
 //
 // Accuracy.  A step's six products are added into one register tile, which is then added to the running sum by rounded fp32
 // fused multiply-adds: half as many additions as in gemm_split.hip, whose error is the larger part of both.  Measured: half_fits.
-// Where a sum has a single term, it has the error of the split alone (4e-8), where three bf16 numbers lose nothing.
 #include "split.h"
 
 namespace brsvd {
@@ -67,13 +69,28 @@ __device__ __forceinline__ float max_ror(float x) {
 }
 __device__ __forceinline__ float max_row(float x) { return max_ror<0x121>(max_ror<0x122>(max_ror<0x124>(max_ror<0x128>(x)))); }
 
-// The largest of each four successive indices of a row's step and of the whole; whether four are lost beside it.
-__device__ __forceinline__ bool half_range(const float (&qm)[4], unsigned& m) {
-  m = max_groups(__float_as_uint(fmaxf(fmaxf(qm[0], qm[1]), fmaxf(qm[2], qm[3]))));
-  unsigned low = __float_as_uint(qm[0]) - 1;           // zero counts as the largest
-#pragma unroll
-  for (int q = 1; q < 4; ++q) low = min(low, __float_as_uint(qm[q]) - 1);
-  return low < __float_as_uint(__uint_as_float(m) * 0x1p-17f);
+__device__ __forceinline__ int sum_groups(int v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  v = (int)a[0] + (int)a[1];
+  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return (int)b[0] + (int)b[1];
+}
+// The test of a row's step, see above: run = the largest of each four successive indices that this lane holds (the other groups of lanes
+// hold the rest), m = the largest of the step; false if too few of them are large.  whole: 64 indices, otherwise the first 32 count.
+// (Where 2^-7 m rounds to zero, m is so small that fp16 holds every number of the row whole.)
+constexpr float kLargeRun = 0x1p-7f, kLargeEntry = 0x1p-9f;
+constexpr int kMinRuns = 14, kMaxSmall = 11, kMinRunsHalf = 7, kMaxSmallHalf = 5;
+__device__ __forceinline__ bool half_range(const float (&run)[4], bool whole, unsigned& m) {
+  m = max_groups(__float_as_uint(fmaxf(fmaxf(run[0], run[1]), fmaxf(run[2], run[3]))));
+  const float thr = __uint_as_float(m) * kLargeRun;
+  const int n0 = (run[0] >= thr ? 1 : 0) + (run[1] >= thr ? 1 : 0), n1 = (run[2] >= thr ? 1 : 0) + (run[3] >= thr ? 1 : 0);
+  return sum_groups(n0 + (whole ? n1 : 0)) >= (whole ? kMinRuns : kMinRunsHalf);
+}
+
+// The steps before those that may have less than 64 indices.
+__device__ __forceinline__ int whole_steps(int64_t K) {
+  const int n = (int)((K + kSplitB - 1) / kSplitB);
+  return n & 1 ? (n - 3) / 2 : (int)(K / kHalfStep);
 }
 
 // Packed panel: [step][column tile][block of the step][h, l][lane][8 fp16], 4 KiB per step and tile of 16 columns.  One workgroup per step
@@ -87,10 +104,10 @@ k_half_pack(const float* __restrict__ src, int64_t K, int64_t ld, int cols, int 
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, threads = (int64_t)gridDim.x * blockDim.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6, r = lane & 15, g = lane >> 4;
   const int64_t chunk = blockIdx.x, blocks = 2 * (int64_t)gridDim.x;
-  __shared__ unsigned top[kHalfStep];
+  __shared__ unsigned top;
   __shared__ int untame;
-  if (threadIdx.x < kHalfStep) top[threadIdx.x] = 0;
-  if (threadIdx.x == 0) untame = 0;
+  if (threadIdx.x == 0) { top = 0; untame = 0; }
+  const bool whole = chunk < whole_steps(K);
   float v[PER][16];
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
@@ -98,43 +115,38 @@ k_half_pack(const float* __restrict__ src, int64_t K, int64_t ld, int cols, int 
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       const int64_t blk = 2 * chunk + (e >> 3), k = block_start(blk, K) + ((e >> 2) & 1) * 16 + 4 * g + (e & 3);
-      v[i][e] = k >= blk * kSplitB && col < cols ? src[k * ld + col] : 0.f;
+      v[i][e] = k >= block_first(blk, K) && col < cols ? src[k * ld + col] : 0.f;
     }
   }
   bool bad = false;
   if (wave == 0) {
     const int64_t row = (chunk * 2654435761u + r) % count_a;             // of A (column, if at)
-    float qm[4];
+    float run[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const float* p = A + (at ? row : row * lda);
       const int64_t k = block_start(2 * chunk + (q >> 1), K) + (q & 1) * 16 + 4 * g, step = at ? lda : 1;
-      qm[q] = fmaxf(fmaxf(fabsf(p[k * step]), fabsf(p[(k + 1) * step])), fmaxf(fabsf(p[(k + 2) * step]), fabsf(p[(k + 3) * step])));
+      run[q] = fmaxf(fmaxf(fabsf(p[k * step]), fabsf(p[(k + 1) * step])), fmaxf(fabsf(p[(k + 2) * step]), fabsf(p[(k + 3) * step])));
     }
     unsigned m;
-    bad = half_range(qm, m);
+    bad = !half_range(run, whole, m);
   }
   for (int64_t i = id; i < 2 * kSplitFlags; i += threads) flags[i] = 0;
   __syncthreads();
+  float most = 0.f;                                                       // (fmaxf leaves NaN out)
 #pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    float m = fabsf(v[0][e]);
+  for (int i = 0; i < PER; ++i)
 #pragma unroll
-    for (int i = 1; i < PER; ++i) m = fmaxf(m, fabsf(v[i][e]));
-    m = max_row(m);
-    if (r == e) atomicMax(&top[(e >> 2) * 16 + 4 * g + (e & 3)], __float_as_uint(m));
-  }
+    for (int e = 0; e < 16; ++e) most = fmaxf(most, fabsf(v[i][e]));
+  const unsigned wave_max = max_groups(__float_as_uint(max_row(most)));
+  if (lane == 0) atomicMax(&top, wave_max);
   __syncthreads();
-  const float row = __uint_as_float(top[lane]);
-  float most = max_row(row);
-  most = fmaxf(most, __shfl_xor(most, 16, 64));
-  most = fmaxf(most, __shfl_xor(most, 32, 64));
-  const unsigned gmax = __float_as_uint(most);
+  const unsigned gmax = top;
   const unsigned ex = gmax == 0 ? 127u << 23 : max(gmax & kExpMask, 15u << 23);
-  const float scale = __uint_as_float((268u << 23) - ex), thr = most * 0x1p-12f;
-  const int valid = (int)max((int64_t)0, min((int64_t)kHalfStep, K - chunk * kHalfStep));
+  const float scale = __uint_as_float((268u << 23) - ex), thr = __uint_as_float(gmax) * kLargeEntry;
+  const int need = whole ? kHalfStep - kMaxSmall : kHalfStep / 2 - kMaxSmallHalf;
   unsigned first = 0;
-  bad |= (row != 0.f && row < thr) || gmax >= kExpMask;
+  bad |= gmax >= kExpMask;
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
     const int nt = wave + i * waves;
@@ -147,7 +159,7 @@ k_half_pack(const float* __restrict__ src, int64_t K, int64_t ld, int cols, int 
     for (int e = 0; e < 16; ++e) {
       any_nan[e >> 3] |= v[i][e] != v[i][e];
       cm = fmaxf(cm, fabsf(v[i][e]));
-      count += fabsf(v[i][e]) >= thr ? 1 : 0;
+      count += fabsf(v[i][e]) >= thr && (whole || e < 8) ? 1 : 0;
     }
 #pragma unroll
     for (int q = 0; q < 8; ++q) half_pair(v[i][2 * q], v[i][2 * q + 1], scale, f[q >> 2], q & 3);
@@ -163,7 +175,7 @@ k_half_pack(const float* __restrict__ src, int64_t K, int64_t ld, int cols, int 
     count += __shfl_xor(count, 16, 64);
     count += __shfl_xor(count, 32, 64);
     cm = __uint_as_float(max_groups(__float_as_uint(cm)));
-    bad |= cm != 0.f && count < valid - valid / 8;
+    bad |= cm != 0.f && count < need;
   }
   if (bad) untame = 1;
   __syncthreads();
@@ -220,13 +232,14 @@ __device__ __forceinline__ int half_tile(const SplitTile& s, const uintx4* __res
 #pragma unroll
     for (int nt = 0; nt < NTW; ++nt) acc[mt][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
   }
-  const int last = s.blocks / 2 - 1;
+  const int b0 = (int)s.b0, K = (int)s.K, empty = (int)empty_block(s.K);
+  const int last = s.blocks / 2 - 1, whole_end = whole_steps(s.K) - (int)(s.b0 / 2);
   // (written by an earlier kernel: a scalar load, which does not wait for the loads of A as a vector load would)
   const auto* sw = (const __attribute__((address_space(4))) unsigned*)(words + s.b0);
   auto step_scale = [&](int c) { return ((sw[2 * c] >> 16) - 155u) << 23; };
   auto xid = [&](int x) { return min(tid + x * NTH, BUF - 1); };
   auto block_base = [&](int c, int sub) {
-    const int64_t k0 = block_start(s.b0 + 2 * c + sub, s.K);
+    const int64_t k0 = block_start(b0 + 2 * c + sub, empty, K);
     return (const char*)(s.A + (AT ? k0 * s.lda : k0));
   };
   auto elem = [&](int mt, int q, int i) -> float {     // element i of quarter q of the step
@@ -252,16 +265,17 @@ __device__ __forceinline__ int half_tile(const SplitTile& s, const uintx4* __res
     half_pair(elem(mt, q, i), elem(mt, q, i + 1), scale[mt], f[mt][q >> 1], pr & 3);
   };
   // The scale of each row (column) for this step; false if it does not do for all of them.
-  auto scan = [&](unsigned sx) {
+  auto scan = [&](unsigned sx, int c) {
+    const bool whole = c < whole_end;
     bool bad = false;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-      float qm[4];
+      float run[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        qm[q] = fmaxf(fmaxf(fabsf(elem(mt, q, 0)), fabsf(elem(mt, q, 1))), fmaxf(fabsf(elem(mt, q, 2)), fabsf(elem(mt, q, 3))));
+        run[q] = fmaxf(fmaxf(fabsf(elem(mt, q, 0)), fabsf(elem(mt, q, 1))), fmaxf(fabsf(elem(mt, q, 2)), fabsf(elem(mt, q, 3))));
       unsigned m;
-      bad |= half_range(qm, m);
+      bad |= !half_range(run, whole, m);
       const unsigned eb = m == 0 ? 127u << 23 : max(m & kExpMask, 15u << 23);
       const int comb = (int)(eb + sx);
       bad |= m != 0 && (unsigned)comb - kExpOne > 253u * kExpOne;
@@ -278,7 +292,7 @@ __device__ __forceinline__ int half_tile(const SplitTile& s, const uintx4* __res
     static_for<0, XPT>([&](auto x) { lds[xid(x)] = xb[xid(x)]; });
     const int c1 = min(1, last);
     static_for<0, XH>([&](auto x) { xr[x] = xb[c1 * xstride + xid(x)]; });
-    vote[8 + wave] = __any(scan(step_scale(0)));
+    vote[8 + wave] = __any(scan(step_scale(0), 0));
     p0 = block_base(c1, 0);
     p1 = block_base(c1, 1);
     static_for<0, 8 * MT>([&](auto p) { split_a(p, fa); if (EARLY) load_a(p, p0, p1); });
@@ -315,7 +329,7 @@ __device__ __forceinline__ int half_tile(const SplitTile& s, const uintx4* __res
         }
       }
       if constexpr (sl == SCAN) {
-        vote[(c & 1) * 8 + wave] = __any(scan(sx));         // without a branch: one would let the compiler put off what stands before it
+        vote[(c & 1) * 8 + wave] = __any(scan(sx, c1));         // without a branch: one would let the compiler put off what stands before it
       }
       if constexpr (sl > SCAN) {
         constexpr int u = sl - SCAN - 1, n = SL - SCAN - 1;

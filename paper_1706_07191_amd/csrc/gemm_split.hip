@@ -85,7 +85,7 @@ struct RawPanel {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const int64_t k = block_start(blk, K) + (e >> 2) * 16 + 4 * (lane >> 4) + (e & 3);
-      v[e] = k >= blk * kSplitB && 16 * nt + (lane & 15) < cols ? u.v[e] : 0.f;
+      v[e] = k >= block_first(blk, K) && 16 * nt + (lane & 15) < cols ? u.v[e] : 0.f;
     }
     const Frag3 f = split_panel_fragment(v);
 #pragma unroll
@@ -141,12 +141,12 @@ __device__ __forceinline__ int split_tile(const SplitTile& s, const Panel& panel
 #pragma unroll
     for (int nt = 0; nt < NTW; ++nt) acc[mt][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
   }
-  const int last = s.blocks - 1;
+  const int last = s.blocks - 1, b0 = (int)s.b0, K = (int)s.K, empty = (int)empty_block(s.K);
   auto load_x = [&](int x, int c) { panel.template load<NT>(xr[x], tid + x * NTH, s.b0 + c, s.K); };
   auto store_x = [&](int x, int c, uintx4* buf) { panel.template store<NT>(xr[x], tid + x * NTH, s.b0 + c, s.K, buf); };
   // base of block c: A + k0 (row part of the address is in off) or A + k0 * lda
   auto block_base = [&](int c) {
-    const int64_t k0 = block_start(s.b0 + c, s.K);
+    const int64_t k0 = block_start(b0 + c, empty, K);
     return (const char*)(s.A + (AT ? k0 * s.lda : k0));
   };
   // the loads that become possible once pairs 0..p of the block have been split
@@ -467,6 +467,8 @@ __device__ __forceinline__ void repair_tile(const SplitRepair& p, int first, int
                                             float* out, int64_t ldo, int ncols) {
   __shared__ floatx4 sum[kRepairWaves / 2 * 2 * kRepairNT * 64];
   __shared__ int redo[kRepairMaxPieces];
+  // (the blocks are an even number: the first is not the empty one)
+  const int64_t kbeg = block_index(b0, p.K) * kSplitB, kend = min(p.K, block_index(b0 + blocks, p.K) * kSplitB);
   const int strips = (p.nt_total + kRepairNT - 1) / kRepairNT, pieces = (min(p.tile, p.count - first) + 31) / 32 * strips;
   for (int i = threadIdx.x >> 6; i < pieces; i += kRepairWaves) {
     const bool bad = repair_needed(p, first + i / strips * 32, i % strips * kRepairNT, small, xnan, out, ldo, ncols);
@@ -475,8 +477,7 @@ __device__ __forceinline__ void repair_tile(const SplitRepair& p, int first, int
   __syncthreads();
   for (int i = 0; i < pieces; ++i)
     if (redo[i])
-      repair_piece<AT>(p, first + i / strips * 32, i % strips * kRepairNT, b0 * kSplitB, min(p.K, (b0 + blocks) * kSplitB), sum, out,
-                       ldo, ncols);
+      repair_piece<AT>(p, first + i / strips * 32, i % strips * kRepairNT, kbeg, kend, sum, out, ldo, ncols);
   __syncthreads();                                       // before the next tile's `redo`
 }
 
@@ -601,7 +602,7 @@ k_split_fix_at(SplitFix f, float* __restrict__ Zpart, int64_t ldz, int64_t split
 bool split_fits(bool at, const float* A, int64_t out, int64_t K, int Lp, int64_t lda, uint64_t pack_bytes) {
   // byte offsets of a lane's loads: at most 255 rows and a row length, in 32 bits
   if (K < kSplitMinK || out < kSplitMinOut || Lp < kSplitMinLp || out * K < kSplitMinA || lda > (1 << 21)) return false;
-  if (out > INT32_MAX || K > INT32_MAX) return false;
+  if (out > INT32_MAX || K > INT32_MAX - 2 * kSplitB) return false;     // block_start
   if (Lp < 48) {                                         // both kernels are near the read of A: see common.h
     const bool vectors = lda % 4 == 0 && (uintptr_t)A % 16 == 0, lines = lda % 32 == 0 && (uintptr_t)A % 128 == 0;
     const bool few = out >= 8000 && K <= (out <= 20480 ? 6000 : 2048), many = out >= 14500 && K >= 20000;

@@ -18,10 +18,19 @@ constexpr int kFragU = 64;           // 16-byte units of one operand fragment (1
 constexpr int kSplitFlags = 4096;
 constexpr int kNotFinite = 1, kSmall = 2, kRedo = 4;
 
-// First contraction index of block `blk`: the last blocks are moved back so that they end with the range, and the
-// indices the block before has already covered are zero in the packed panel.  Neither operand is then ever read
-// outside its range, and A needs no masks.  K >= kSplitB.
-__device__ __forceinline__ int64_t block_start(int64_t blk, int64_t K) { return min(blk * kSplitB, K - kSplitB); }
+// Blocks are taken in twos.  Where their number is odd an empty one stands before the last two, so that the first of any two is whole.
+// Block `blk` covers the contraction indices from block_first on (K for the empty one).  It is read from block_start on: the last one is
+// moved back so that it ends with the range, and the indices the block before has already covered are zero in the packed panel.
+// Neither operand is then ever read outside its range, and A needs no masks.  K >= 3 * kSplitB.
+__device__ __forceinline__ int64_t empty_block(int64_t K) {
+  const int64_t n = (K + kSplitB - 1) / kSplitB;
+  return n & 1 ? n - 2 : n;
+}
+__device__ __forceinline__ int64_t block_index(int64_t blk, int64_t K) { return blk > empty_block(K) ? blk - 1 : blk; }
+__device__ __forceinline__ int64_t block_first(int64_t blk, int64_t K) { return blk == empty_block(K) ? K : block_index(blk, K) * kSplitB; }
+__device__ __forceinline__ int64_t block_start(int64_t blk, int64_t K) { return min(block_index(blk, K) * kSplitB, K - kSplitB); }
+// The same in 32 bits (split_fits), which is all that scalar instructions compare: in 64 the addresses take vector registers.
+__device__ __forceinline__ int block_start(int blk, int empty, int K) { return min((blk - (blk > empty ? 1 : 0)) * kSplitB, K - kSplitB); }
 
 template <int I, int N, typename F>
 __device__ __forceinline__ void static_for(F&& f) {
@@ -79,7 +88,7 @@ __device__ __forceinline__ unsigned split_pack_fragment(const float* __restrict_
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int64_t k = k0 + (e >> 2) * 16 + 4 * g + (e & 3);
-    v[e] = k >= blk * kSplitB && col < cols ? src[k * ld + col] : 0.f;
+    v[e] = k >= block_first(blk, K) && col < cols ? src[k * ld + col] : 0.f;
     any_nan |= v[e] != v[e];
   }
   const unsigned long long b = __ballot(any_nan);                      // bit 16 * g + r

@@ -27,17 +27,24 @@ SHAPES = [  # rows, n, l, elements between A's rows beyond n, offset of A's base
 ]
 
 
-def _check(A, X, Q, bound=_bound):
-    """Both products where they are of this kind."""
-    rows, n, l = A.shape[0], A.shape[1], X.shape[1]
+def _kinds(A, l):
+    """Which of the two products are of this kind."""
+    rows, n = A.shape
     kinds = [w for w in (0, 1) if B.brsvd_gemm_is_split(w, rows, n, l, A.stride(0), A.data_ptr()) and B.brsvd_gemm_split_parts(w, rows, n, l) == 2]
     assert kinds
-    At = A.T.contiguous()
-    for w in kinds:
-        a, x = (A, X) if w == 0 else (At, Q)
-        got = B.brsvd_gemm_an(A, X) if w == 0 else B.brsvd_gemm_at(A, Q)
-        err = (got.double() - a.double() @ x.double()).abs()
-        assert bool((err <= bound(a.shape[1], a, x)).all()), w
+    return kinds
+
+
+def _check_one(w, A, X, Q, bound):
+    a, x = (A, X) if w == 0 else (A.T.contiguous(), Q)
+    got = B.brsvd_gemm_an(A, X) if w == 0 else B.brsvd_gemm_at(A, Q)
+    err = (got.double() - a.double() @ x.double()).abs()
+    assert bool((err <= bound(a.shape[1], a, x)).all()), w
+
+
+def _check(A, X, Q, bound=_bound):
+    for w in _kinds(A, X.shape[1]):
+        _check_one(w, A, X, Q, bound)
 
 
 @pytest.mark.parametrize("rows,n,l,pad,off", SHAPES)
@@ -124,6 +131,60 @@ def test_half_products_of_every_range(rows, n, l, pad, off, change):
     change(A, X, Q)
     # small products may be subnormal (2^-149 apart, half of that for each of the partial sums)
     _check(A, X, Q, lambda K, a, x: _bound(K, a, x) + 2.0 ** -149 * K / 32)
+
+
+# Sums of numbers that one scale per 64 loses, where the large ones beside them meet nothing.  a: some rows, x: one column of the panel.
+def _covered(a, x, t):           # a large number and three small ones in every other four, the rest zero
+    a.zero_()
+    for i in range(4):
+        a[:, i::8] = 1.0 if i == 0 else t
+    x.copy_(x.sign())
+    x[::8] = 0.0
+
+
+def _selected(a, x, t):          # one number in 64, which meets a small one
+    a.zero_()
+    a[:, 5::64] = 1.0
+    x[5::64] *= t
+
+
+def _weak_fours(a, x, t):        # a number in every four that is large enough by itself, against a small entry
+    a.copy_(a.sign() * t)
+    a[:, 1::4] = 2.0 ** -16
+    a[:, ::64] = 1.0
+    x.copy_(x.sign())
+    x[1::4] = 2.0 ** -9
+    x[::64] = 0.0
+
+
+def _at_the_limit(a, x, t):      # what the two tests of a step just let pass, for a panel with largest entries of 8
+    k = torch.arange(a.shape[1], device=a.device) % 64
+    a.copy_(a.sign() * t)
+    a[:, (k % 2 == 0) & (k < 40)] = 2.0 ** -6
+    a[:, k == 40] = 1.0
+    x.copy_(x.sign() * 8.0)
+    x[(k % 2 == 0) & (k < 20) | (k == 40)] = 0.0
+    x[(k % 2 == 0) & (k >= 20) & (k < 40)] = 2.0 ** -6
+
+
+@pytest.mark.parametrize("pattern", [_covered, _selected, _weak_fours, _at_the_limit])
+@pytest.mark.parametrize("t", [2.0 ** -20, 2.0 ** -26, 2.0 ** -30, 2.0 ** -36, 2.0 ** -42])
+@pytest.mark.parametrize("rows,n,l,pad,off", [SHAPES[3], SHAPES[8], SHAPES[12]])
+def test_half_products_of_numbers_beside_larger_ones(rows, n, l, pad, off, pattern, t):
+    dev = need_gpu()
+    print(f"[case] half beside {pattern.__name__} {t} rows={rows} n={n} l={l}", flush=True)
+    A, X, Q = _inputs(rows, n, l, pad, off, dev)
+    X.clamp_(-8.0, 8.0)
+    Q.clamp_(-8.0, 8.0)
+    before = A.clone()
+    for w in _kinds(A, l):
+        A.copy_(before)
+        a, x = (A, X) if w == 0 else (A.T, Q)
+        rr = torch.tensor([1, 40, a.shape[0] // 2, a.shape[0] - 1], device=dev)
+        picked, column = a[rr], x[:, 0].clone()
+        pattern(picked, column, t)
+        a[rr], x[:, 0] = picked, column
+        _check_one(w, A, X, Q, lambda K, a_, x_: _bound(K, a_, x_) + 2.0 ** -149 * K / 32)
 
 
 @pytest.mark.parametrize("scale_a,scale_x", [(1e-33, 1e28), (1e-41, 1e35), (1e30, 1e-37), (1e28, 1e-41), (1e-20, 1e-17), (1e30, 1e5)])
