@@ -18,10 +18,15 @@
 // than 2^-18 of |a||x|, what 64 rounded fp32 additions may lose, whatever the numbers are.  (The last two steps of a contraction
 // may have as few as 32 indices.  Of those the first 32 count: 7 of 8 runs, 5 entries, and less than 2^-17 is lost.)  Of N(0, 1) entries a
 // step of a row fails with a chance below 10^-16, one of a panel of 272 columns below 10^-11 (of 32 indices 2 * 10^-5).
-// Where a test fails, or the scales' product leaves the range of fp32, or the panel has an infinity, bf16 numbers (which hold every
-// range) take over:
-//   - for a panel, and where the packing's sample of A (16 rows per step) fails: all workgroups leave their parts to k_split_fix_*;
-//   - for a row of A: the workgroup that meets it leaves its part, and what it has done by then is lost.
+// A row's step that fails, or whose scales' product leaves the range of fp32, is multiplied as zeros and noted; the wave that did so adds
+// its 64 products in fp32 at the end.  bf16 numbers (which hold every range) take over
+//   - where a column of the panel fails, or it has an infinity, or one of the up to 64 rows per step that the packing looks at fails: all
+//     workgroups leave their parts to k_split_fix_*;
+//   - where a wave meets more steps with such rows than it can note (kMaxNoted), or more rows in all than it is worth (kMaxRows): what its
+//     workgroup has done is done again.
+// Measured, six bf16 products and this (us, A X / A^T Q, 60000x6000 l=110): N(0, 1) entries 491 / 480 and 401 / 376, one of them 10^6 477 / 470
+// and 390 / 378 (744 / 551 when its workgroup did its part again), 24 of them 479 / 484 and 407 / 493 (sampled in A^T Q), half of A zero
+// 470 / 480 and 511 / 485.
 //
 // Accuracy.  A step's six products are added into one register tile, which is then added to the running sum by rounded fp32
 // fused multiply-adds: half as many additions as in gemm_split.hip, whose error is the larger part of both.  Measured: half_fits.
@@ -51,6 +56,7 @@ constexpr int kHalfEarly = 8;                     // see EARLY
 constexpr int kHalfStep = 2 * kSplitB;            // contraction indices per step: one scale, one block sum
 constexpr unsigned kExpMask = 0x7f800000u, kExpOne = 1u << 23;
 constexpr unsigned kUntame = 0x100;               // bit of the upper half of a step's word: not fit for this
+constexpr int kMaxNoted = 31, kMaxRows = 64, kSampled = 64;
 // Scales: the largest number becomes one in [2^14, 2^15), i.e. it is multiplied by 2^(14 - (E - 127)) with its exponent field E, at
 // least 15 (then 2^126, and even subnormal numbers are held whole).  A block sum is multiplied by 2^(E_A - 141 + E_X - 141), whose
 // exponent field is E_A + E_X - 155.  The upper half of a step's word holds E_X.
@@ -119,8 +125,8 @@ k_half_pack(const float* __restrict__ src, int64_t K, int64_t ld, int cols, int 
     }
   }
   bool bad = false;
-  if (wave == 0) {
-    const int64_t row = (chunk * 2654435761u + r) % count_a;             // of A (column, if at)
+  if (wave < kSampled / 16) {
+    const int64_t row = (chunk * 2654435761u + threadIdx.x / 64 * 16 + r) % count_a;             // of A (column, if at)
     float run[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -182,6 +188,22 @@ k_half_pack(const float* __restrict__ src, int64_t K, int64_t ld, int cols, int 
   if (threadIdx.x == 0) words[2 * chunk] = first | (ex >> 23 | (untame ? kUntame : 0)) << 16;
 }
 
+struct HalfPanel {
+  const uintx4* panel;     // of the launch's columns
+  int64_t stride;          // 16-byte units of one step
+  const unsigned* words;
+  int *flags, *redo;
+  int c0;                  // the first of the launch's columns
+  // all columns, and the panel as it was
+  uintx4* all;
+  const float* X;
+  int64_t ld, steps;
+  int cols, nt_total;
+};
+// In LDS: the steps with rows that were left out, and these rows as bits, for each wave; one more entry than it may hold, which is
+// written for the steps without.
+typedef uint2 Noted[8][kMaxNoted + 1];
+
 // Workgroup: as in gemm_split.hip, WR x WC waves of MT tiles of 16 rows (AT: columns of A) and NTW tiles of the panel's columns; but the
 // panel is the first operand of the instruction and A the second, so that a lane's results belong to one row and that row's scale
 // is in the lane that split it.
@@ -195,8 +217,8 @@ k_half_pack(const float* __restrict__ src, int64_t K, int64_t ld, int cols, int 
 // Measured, six bf16 products and this (us of the whole product, A X / A^T Q): 100000x50000 l=272 12982 / 13720 and 9058 / 9350;
 // 20000x20000 l=110 579 / 534 and 472 / 398, l=64 407 / 386 and 354 / 316; 89083x2783 l=97 346 / 342 and 298 / 274.
 template <bool AT, int NT, int NTW, int MT, int WR, int WC>
-__device__ __forceinline__ int half_tile(const SplitTile& s, const uintx4* __restrict__ XP, int64_t xstride,
-                                         const unsigned* __restrict__ words, uintx4* lds, int* vote, int wave, int wr, int nt0) {
+__device__ __forceinline__ int half_tile(const SplitTile& s, const HalfPanel& panel, uintx4* lds, Noted& notes, int wave, int wr,
+                                         int nt0) {
   constexpr int NTH = WR * WC * 64;
   constexpr int BUF = NT * 4 * kFragU;                 // 16-byte units of one staged step
   // units a thread hands over per step, XH of them on their way at a time (the last ones may repeat the end of the buffer)
@@ -235,8 +257,8 @@ __device__ __forceinline__ int half_tile(const SplitTile& s, const uintx4* __res
   const int b0 = (int)s.b0, K = (int)s.K, empty = (int)empty_block(s.K);
   const int last = s.blocks / 2 - 1, whole_end = whole_steps(s.K) - (int)(s.b0 / 2);
   // (written by an earlier kernel: a scalar load, which does not wait for the loads of A as a vector load would)
-  const auto* sw = (const __attribute__((address_space(4))) unsigned*)(words + s.b0);
-  auto step_scale = [&](int c) { return ((sw[2 * c] >> 16) - 155u) << 23; };
+  const auto* sw = (const __attribute__((address_space(4))) unsigned*)(panel.words + s.b0);
+  auto step_scale = [&](int c) { return ((sw[2 * c] >> 16 & 0xff) - 155u) << 23; };
   auto xid = [&](int x) { return min(tid + x * NTH, BUF - 1); };
   auto block_base = [&](int c, int sub) {
     const int64_t k0 = block_start(b0 + 2 * c + sub, empty, K);
@@ -264,10 +286,10 @@ __device__ __forceinline__ int half_tile(const SplitTile& s, const uintx4* __res
     const int mt = AT ? p % MT : p >> 3, pr = AT ? p / MT : p & 7, q = pr >> 1, i = 2 * (pr & 1);   // pair pr of the 16 elements
     half_pair(elem(mt, q, i), elem(mt, q, i + 1), scale[mt], f[mt][q >> 1], pr & 3);
   };
-  // The scale of each row (column) for this step; false if it does not do for all of them.
+  // The scale of each row (column) for step c; those that fail are left out and noted.
   auto scan = [&](unsigned sx, int c) {
     const bool whole = c < whole_end;
-    bool bad = false;
+    unsigned rows = 0;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       float run[4];
@@ -275,24 +297,36 @@ __device__ __forceinline__ int half_tile(const SplitTile& s, const uintx4* __res
       for (int q = 0; q < 4; ++q)
         run[q] = fmaxf(fmaxf(fabsf(elem(mt, q, 0)), fabsf(elem(mt, q, 1))), fmaxf(fabsf(elem(mt, q, 2)), fabsf(elem(mt, q, 3))));
       unsigned m;
-      bad |= !half_range(run, whole, m);
+      bool bad = !half_range(run, whole, m);
       const unsigned eb = m == 0 ? 127u << 23 : max(m & kExpMask, 15u << 23);
       const int comb = (int)(eb + sx);
       bad |= m != 0 && (unsigned)comb - kExpOne > 253u * kExpOne;
-      scale[mt] = __uint_as_float((268u << 23) - eb);
+      scale[mt] = bad ? 0.f : __uint_as_float((268u << 23) - eb);
       inv_next[mt] = __int_as_float(max((int)kExpOne, min(comb, (int)(254u << 23))));
+      rows |= ((unsigned)__ballot(bad) & 0xffffu) << (16 * mt);            // the same in all groups of lanes
     }
-    return bad;
+    return rows;
   };
-
-  const uintx4* xb = XP + s.b0 / 2 * xstride;
+  unsigned own = 0;                                    // rows (columns) that are stored, as bits like those of a note
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    const int row = AT ? c0 + mt : w0 + mt * 16 + r;
+    own |= ((unsigned)__ballot(row < s.count && (!AT || row >= w0 + MT * r)) & 0xffffu) << (16 * mt);
+  }
+  int noted = 0;                                       // without a branch, see step
+  auto note = [&](int c, unsigned rows) {
+    rows &= own;
+    notes[wave][min(noted, kMaxNoted)] = uint2{(unsigned)c, rows};
+    noted += rows != 0;
+  };
+  const uintx4* xb = panel.panel + s.b0 / 2 * panel.stride;
   {
     const char *p0 = block_base(0, 0), *p1 = block_base(0, 1);
     static_for<0, 8 * MT>([&](auto p) { load_a(p, p0, p1); });
     static_for<0, XPT>([&](auto x) { lds[xid(x)] = xb[xid(x)]; });
     const int c1 = min(1, last);
-    static_for<0, XH>([&](auto x) { xr[x] = xb[c1 * xstride + xid(x)]; });
-    vote[8 + wave] = __any(scan(step_scale(0), 0));
+    static_for<0, XH>([&](auto x) { xr[x] = xb[c1 * panel.stride + xid(x)]; });
+    note(0, scan(step_scale(0), 0));
     p0 = block_base(c1, 0);
     p1 = block_base(c1, 1);
     static_for<0, 8 * MT>([&](auto p) { split_a(p, fa); if (EARLY) load_a(p, p0, p1); });
@@ -301,15 +335,13 @@ __device__ __forceinline__ int half_tile(const SplitTile& s, const uintx4* __res
   for (int mt = 0; mt < MT; ++mt) inv[mt] = inv_next[mt];
   __syncthreads();
 
-  int stopped = 0;                                     // the same in all waves; no branch inside a step, see the vote
   auto step = [&](int c, const Frag2 (&cf)[MT][2], Frag2 (&nf)[MT][2]) __attribute__((always_inline)) {
     const uintx4* bb = lds + (c & 1) * BUF + nt0 * (4 * kFragU) + lane;
     uintx4* nxt = lds + ((c & 1) ^ 1) * BUF;
     const int c1 = min(c + 1, last), c2 = min(c + 2, last);
-    const uintx4 *x1 = xb + c1 * xstride, *x2 = xb + c2 * xstride;
+    const uintx4 *x1 = xb + c1 * panel.stride, *x2 = xb + c2 * panel.stride;
     const char *p0 = block_base(EARLY ? c2 : c1, 0), *p1 = block_base(EARLY ? c2 : c1, 1);
     const unsigned sx = step_scale(c1);
-    const int stop = vote[((c + 1) & 1) * 8 + (lane & 7)];
     uintx4 b[2][2];
 #pragma unroll
     for (int p = 0; p < 2; ++p) b[0][p] = bb[p * kFragU];
@@ -329,7 +361,9 @@ __device__ __forceinline__ int half_tile(const SplitTile& s, const uintx4* __res
         }
       }
       if constexpr (sl == SCAN) {
-        vote[(c & 1) * 8 + wave] = __any(scan(sx, c1));         // without a branch: one would let the compiler put off what stands before it
+        // without a branch: one would let the compiler put off what stands before it
+        const unsigned rows = scan(sx, c1);
+        note(c1, c < last ? rows : 0);
       }
       if constexpr (sl > SCAN) {
         constexpr int u = sl - SCAN - 1, n = SL - SCAN - 1;
@@ -351,7 +385,6 @@ __device__ __forceinline__ int half_tile(const SplitTile& s, const uintx4* __res
       if constexpr (u2 + 1 < 2 * NTW && j < 2) b[(u2 + 1) & 1][j] = bb[((u2 + 1) * 2 + j) * kFragU];
     });
     __builtin_amdgcn_sched_barrier(0);
-    stopped |= __any(stop);
     __syncthreads();
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
@@ -362,19 +395,22 @@ __device__ __forceinline__ int half_tile(const SplitTile& s, const uintx4* __res
   };
   int c = 0;
 #pragma nounroll
-  for (; c < last && !stopped; c += 2) {
+  for (; c < last; c += 2) {
     step(c, fa, fb);
     step(c + 1, fb, fa);
   }
-  if (c == last && !stopped) step(c, fa, fb);
-  if (stopped) return kRedo;
+  if (c == last) step(c, fa, fb);
+  if (noted > kMaxNoted) return kRedo;
+  int left_out = 0;
+  for (int i = 0; i < noted; ++i) left_out += __popc(notes[wave][i].y);
+  if (left_out > kMaxRows) return kRedo;
 
   // lane (r, g) holds columns 4g..4g+3 of every tile of the panel, for row (column of A) r
   float worst = 0.f;                                   // NaN as soon as one result is not finite
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
     const int row = AT ? c0 + mt : w0 + mt * 16 + r;
-    const bool valid = AT ? w0 + MT * r < s.count : row < s.count;
+    const bool valid = own >> (16 * mt + r) & 1;         // (a column belongs to the lane that has it first)
     if (valid) {
       float* o = s.out + (int64_t)row * s.ldo;
 #pragma unroll
@@ -392,35 +428,52 @@ __device__ __forceinline__ int half_tile(const SplitTile& s, const uintx4* __res
       }
     }
   }
+  // What was left out: a row's 64 numbers in the lanes, the panel's columns across them.
+  if (left_out > 0) {
+    __threadfence_block();                             // other lanes have stored what is added to
+    for (int i = 0; i < noted; ++i) {
+      const int c = __builtin_amdgcn_readfirstlane(notes[wave][i].x);
+      const int64_t k0 = block_index(s.b0 + 2 * c, s.K) * kSplitB;
+      const int n = (int)(min(s.K, block_index(s.b0 + 2 * c + 2, s.K) * kSplitB) - k0);
+      for (unsigned rows = __builtin_amdgcn_readfirstlane(notes[wave][i].y); rows; rows &= rows - 1) {
+        const int mt = (__ffs(rows) - 1) / 16, rr = (__ffs(rows) - 1) % 16;
+        const int row = AT ? max(0, min(w0 + MT * rr, s.count - MT)) + mt : w0 + mt * 16 + rr;
+        const int64_t k = k0 + min(lane, n - 1);
+        const float own = AT ? s.A[k * s.lda + row] : s.A[(row - s.first) * s.lda + k];
+        const int a = __float_as_int(lane < n ? own : 0.f);
+        for (int j = 0; j < NTW * 16; j += 64) {         // (all lanes: v_readlane reads those beyond the last column too)
+          const int col = nt0 * 16 + j + lane, xcol = min(panel.c0 + col, panel.cols - 1);
+          const float* p = panel.X + k0 * panel.ld + xcol;
+          float sum[4] = {0.f, 0.f, 0.f, 0.f};
+          for (int k = 0; k < n; k += 16) {
+            float v[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) v[e] = p[min(k + e, n - 1) * panel.ld];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) sum[e & 3] = fmaf(__int_as_float(__builtin_amdgcn_readlane(a, k + e)), v[e], sum[e & 3]);
+          }
+          if (j + lane < NTW * 16 && col < s.ncols && panel.c0 + col < panel.cols) s.out[(int64_t)row * s.ldo + col] += (sum[0] + sum[1]) + (sum[2] + sum[3]);
+        }
+      }
+    }
+  }
   return !(worst == 0.f) ? kNotFinite : 0;
 }
 
 template <bool AT, int NT, int MT, int WR, int WC>
-__device__ __forceinline__ int half_tile_waves(const SplitTile& s, const uintx4* XP, int64_t xstride, const unsigned* words,
-                                               uintx4* lds, int* vote) {
+__device__ __forceinline__ int half_tile_waves(const SplitTile& s, const HalfPanel& panel, uintx4* lds, Noted& notes) {
   constexpr int NTW = (NT + WC - 1) / WC;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wr = wave % WR, wc = wave / WR;
   if constexpr (NT % WC == 0) {
-    return half_tile<AT, NT, NTW, MT, WR, WC>(s, XP, xstride, words, lds, vote, wave, wr, wc * NTW);
+    return half_tile<AT, NT, NTW, MT, WR, WC>(s, panel, lds, notes, wave, wr, wc * NTW);
   } else {
-    if (wc == 0) return half_tile<AT, NT, NTW, MT, WR, WC>(s, XP, xstride, words, lds, vote, wave, wr, 0);
-    return half_tile<AT, NT, NTW - 1, MT, WR, WC>(s, XP, xstride, words, lds, vote, wave, wr, NTW);
+    if (wc == 0) return half_tile<AT, NT, NTW, MT, WR, WC>(s, panel, lds, notes, wave, wr, 0);
+    return half_tile<AT, NT, NTW - 1, MT, WR, WC>(s, panel, lds, notes, wave, wr, NTW);
   }
 }
 
-struct HalfPanel {
-  const uintx4* panel;     // of the launch's columns
-  int64_t stride;          // 16-byte units of one step
-  const unsigned* words;
-  int *flags, *redo;
-  // the whole of it, and as it was
-  uintx4* all;
-  const float* X;
-  int64_t ld, steps;
-  int cols, nt_total;
-};
-// Whether a step of the panel is not fit for this product: then all workgroups leave their parts, and pack the panel in bf16 numbers in
+// Whether a step of the panel or of the sampled rows is not fit for this product: then all workgroups leave their parts, and pack the panel in bf16 numbers in
 // the place of these before they go.  (All threads.)
 __device__ __forceinline__ bool half_leave(const HalfPanel& x, int64_t K, int wg, int wgs) {
   int bad = 0;
@@ -441,7 +494,7 @@ __global__ void __launch_bounds__(WR * WC * 64)
 k_half_an(const float* __restrict__ A, int64_t lda, int rows, int K, HalfPanel x, float* __restrict__ Y, int64_t ldy, int ncols,
           float* __restrict__ Part, int64_t ldp, int64_t split_stride, AnShape sh) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  __shared__ int vote[16];
+  __shared__ Noted notes;
   constexpr int TR = WR * MT * 16;
   const AnWork w = an_work(sh, blockIdx.x);
   if (half_leave(x, K, blockIdx.x, gridDim.x)) return;
@@ -457,9 +510,9 @@ k_half_an(const float* __restrict__ A, int64_t lda, int rows, int K, HalfPanel x
     s.out = w.partial ? Part + (int64_t)w.slot * split_stride - (int64_t)sh.whole * TR * ldp : Y;
     s.ldo = w.partial ? ldp : ldy;
     s.ncols = w.partial ? NT * 16 : ncols;
-    const int found = half_tile_waves<false, NT, MT, WR, WC>(s, x.panel, x.stride, x.words, (uintx4*)lds_raw, vote);
+    const int found = half_tile_waves<false, NT, MT, WR, WC>(s, x, (uintx4*)lds_raw, notes);
     if (found & kNotFinite) x.flags[blockIdx.x % kSplitFlags] = 1;
-    if (found & kRedo) { x.redo[blockIdx.x % kSplitFlags] = kRedoRaw; return; }
+    if (found & kRedo) x.redo[blockIdx.x % kSplitFlags] = kRedoRaw;
     __syncthreads();                                   // before the next strip reuses the staging buffers
   }
 }
@@ -469,7 +522,7 @@ __global__ void __launch_bounds__(WR * WC * 64)
 k_half_at(const float* __restrict__ A, int64_t lda, int64_t rows, int n, HalfPanel x, float* __restrict__ Zpart, int64_t ldz,
           int64_t split_stride, int blocks, int blocks_per_sub) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  __shared__ int vote[16];
+  __shared__ Noted notes;
   SplitTile s;
   s.A = A;
   s.lda = lda;
@@ -483,7 +536,7 @@ k_half_at(const float* __restrict__ A, int64_t lda, int64_t rows, int n, HalfPan
   s.ncols = NT * 16;
   const int wg = blockIdx.y * gridDim.x + blockIdx.x;
   if (half_leave(x, rows, wg, gridDim.x * gridDim.y)) return;
-  const int found = half_tile_waves<true, NT, MT, WR, WC>(s, x.panel, x.stride, x.words, (uintx4*)lds_raw, vote);
+  const int found = half_tile_waves<true, NT, MT, WR, WC>(s, x, (uintx4*)lds_raw, notes);
   if (found & kNotFinite) x.flags[wg % kSplitFlags] = 1;
   if (found & kRedo) x.redo[wg % kSplitFlags] = kRedoRaw;
 }
@@ -524,7 +577,7 @@ int half_pack(const float* A, int64_t lda, int64_t count, int64_t K, int Lp, boo
 
 // The column tiles from c0 / 16 on.
 static HalfPanel half_panel(const HalfPacked& x, int64_t K, int Lp, int c0) {
-  return HalfPanel{(const uintx4*)x.panel + (c0 / 16) * 4 * kFragU, (int64_t)(Lp / 16) * 4 * kFragU, x.words, x.flags, x.redo,
+  return HalfPanel{(const uintx4*)x.panel + (c0 / 16) * 4 * kFragU, (int64_t)(Lp / 16) * 4 * kFragU, x.words, x.flags, x.redo, c0,
                    (uintx4*)x.panel, x.X, x.ldx, split_chunks(K), x.xcols, Lp / 16};
 }
 

@@ -114,7 +114,7 @@ __device__ __forceinline__ int split_tile(const SplitTile& s, const Panel& panel
   const int w0 = s.first + wr * (MT * 16);             // first row (column) of this wave
 
   // Byte offsets of this lane's loads from a uniform base (below 2^32: see split_fits).  Rows past the end repeat the last one, columns past the end the
-  // last MT; their results are not stored, or stored twice with the same value.
+  // last MT; their results are not stored.
   unsigned off[AT ? 1 : MT];
   int c0 = 0;
   if constexpr (AT) {
@@ -232,9 +232,9 @@ __device__ __forceinline__ int split_tile(const SplitTile& s, const Panel& panel
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int i = 4 * g + v;
-      // row i of tile mt is the mt-th of the MT columns lane i loaded (AT), or row 16 * mt + i
+      // row i of tile mt is the mt-th of the MT columns lane i loaded (AT; a column belongs to the lane that has it first), or row 16 * mt + i
       const int row = AT ? max(0, min(w0 + MT * i, s.count - MT)) + mt : w0 + mt * 16 + i;
-      const bool valid = AT ? w0 + MT * i < s.count : row < s.count;
+      const bool valid = row < s.count && (!AT || row >= w0 + MT * i);
       if (valid) {
         float* o = s.out + (int64_t)row * s.ldo;
 #pragma unroll
@@ -543,10 +543,11 @@ __device__ __forceinline__ void split_fix(const SplitFix& f, SplitTile s, int re
   int mine = 0;
   if (redo == kRedoPacked) mine = split_tile_waves<AT, NT, MT, WR, WC>(s, f.panel, lds);
   else if (redo == kRedoRaw) mine = split_tile_waves<AT, NT, MT, WR, WC>(s, RawPanel{p.X, p.ldx, p.xcols}, lds);
-  if (mine & kSmall) found = 1;
+  if (mine) atomicOr(&found, mine);
   __threadfence_block();
   __syncthreads();
-  const bool small = found != 0;
+  if (redo && found == 0) return;
+  const bool small = found & kSmall;
   p.whole = s.whole;
   nan_columns(p, s.b0, s.blocks, xnan);
   repair_tile<AT>(p, s.first, s.b0, s.blocks, small, xnan, s.out, s.ldo, s.ncols);

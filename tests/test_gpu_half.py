@@ -187,6 +187,51 @@ def test_half_products_of_numbers_beside_larger_ones(rows, n, l, pad, off, patte
         _check_one(w, A, X, Q, lambda K, a_, x_: _bound(K, a_, x_) + 2.0 ** -149 * K / 32)
 
 
+def _unsampled(count, row, steps):
+    """The steps in which the packing's sample of A has not got this row."""
+    return [c for c in range(steps) if (row - c * 2654435761) % count >= 64]
+
+
+@pytest.mark.parametrize("rows,n,l,pad,off", [SHAPES[3], (16449, 257, 48, 0, 0), SHAPES[7], SHAPES[9], SHAPES[10], SHAPES[12]])
+@pytest.mark.parametrize("places", ["one", "ends", "ten steps", "all steps", "all rows"])
+def test_half_products_with_rare_outliers(rows, n, l, pad, off, places):
+    """Rows that are left out of a step and added in fp32 leave all others bit for bit as they are.  (All steps of a row, or two of all
+    rows of the last tile, are more than a wave keeps: then only the results of that tile may change.)"""
+    dev = need_gpu()
+    print(f"[case] half outliers {places} rows={rows} n={n} l={l}", flush=True)
+    A, X, Q = _inputs(rows, n, l, pad, off, dev)
+    for P in (X, Q):
+        P[5::64] = P[5::64].sign()
+        P[5::64, 0] = 0.0
+    before = A.clone()
+    for w in _kinds(A, l):
+        A.copy_(before)
+        plain = B.brsvd_gemm_an(A, X) if w == 0 else B.brsvd_gemm_at(A, Q)
+        a = A if w == 0 else A.T
+        count, K = a.shape
+        steps = K // 64 + (K % 64 > 5)
+        if places == "one":
+            at = [(count // 2, _unsampled(count, count // 2, steps)[steps // 2])]
+        elif places == "ends":
+            at = [(r, c) for r in (0, count - 2, count - 1) for c in _unsampled(count, r, steps)[::max(1, steps - 2)]]
+            at += [(r, steps - 1) for r in (count - 2, count - 1) if steps - 1 in _unsampled(count, r, steps)]
+        elif places == "ten steps":
+            at = [(count - 1, c) for c in _unsampled(count, count - 1, steps)[:10]]
+        elif places == "all steps":
+            at = [(count - 1, c) for c in _unsampled(count, count - 1, steps)]
+        else:
+            at = [(r, c) for r in range((count - 1) // 256 * 256, count) for c in _unsampled(count, r, steps)[2:4]]
+        for r, c in at:
+            a[r, 64 * c + 5] = 1e9
+        _check_one(w, A, X, Q, _bound)
+        got = B.brsvd_gemm_an(A, X) if w == 0 else B.brsvd_gemm_at(A, Q)
+        same = torch.ones(count, dtype=torch.bool, device=dev)
+        same[[r for r, _ in at]] = False
+        if places.startswith("all"):
+            same[(count - 1) // 256 * 256:] = False
+        assert torch.equal(got[same], plain[same])
+
+
 @pytest.mark.parametrize("scale_a,scale_x", [(1e-33, 1e28), (1e-41, 1e35), (1e30, 1e-37), (1e28, 1e-41), (1e-20, 1e-17), (1e30, 1e5)])
 def test_half_products_at_any_exponent(scale_a, scale_x):
     dev = need_gpu()
