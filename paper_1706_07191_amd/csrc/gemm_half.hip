@@ -106,7 +106,8 @@ __device__ __forceinline__ int whole_steps(int64_t K) {
 template <int PER>
 __global__ void __launch_bounds__(1024)
 k_half_pack(const float* __restrict__ src, int64_t K, int64_t ld, int cols, int nt_total, uintx4* __restrict__ out,
-            unsigned* __restrict__ words, int* __restrict__ flags, const float* __restrict__ A, int64_t lda, int64_t count_a, int at) {
+            unsigned* __restrict__ words, int* __restrict__ flags, int64_t nflags, const float* __restrict__ A, int64_t lda, int64_t count_a,
+            int at) {
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, threads = (int64_t)gridDim.x * blockDim.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6, r = lane & 15, g = lane >> 4;
   const int64_t chunk = blockIdx.x, blocks = 2 * (int64_t)gridDim.x;
@@ -137,7 +138,7 @@ k_half_pack(const float* __restrict__ src, int64_t K, int64_t ld, int cols, int 
     unsigned m;
     bad = !half_range(run, whole, m);
   }
-  for (int64_t i = id; i < 2 * kSplitFlags; i += threads) flags[i] = 0;
+  for (int64_t i = id; i < nflags; i += threads) flags[i] = 0;
   __syncthreads();
   float most = 0.f;                                                       // (fmaxf leaves NaN out)
 #pragma unroll
@@ -484,7 +485,7 @@ __device__ __forceinline__ bool half_leave(const HalfPanel& x, int64_t K, int wg
     const int64_t blk = i / x.nt_total;
     split_pack_fragment(x.X, K, x.ld, x.cols, blk, (int)(i - blk * x.nt_total), x.all + i * (3 * kFragU));
   }
-  if (threadIdx.x == 0) x.redo[wg % kSplitFlags] = kRedoPacked;
+  if (threadIdx.x == 0) x.redo[wg] = kRedoPacked;
   return true;
 }
 
@@ -512,7 +513,7 @@ k_half_an(const float* __restrict__ A, int64_t lda, int rows, int K, HalfPanel x
     s.ncols = w.partial ? NT * 16 : ncols;
     const int found = half_tile_waves<false, NT, MT, WR, WC>(s, x, (uintx4*)lds_raw, notes);
     if (found & kNotFinite) x.flags[blockIdx.x % kSplitFlags] = 1;
-    if (found & kRedo) x.redo[blockIdx.x % kSplitFlags] = kRedoRaw;
+    if (found & kRedo) x.redo[blockIdx.x] = kRedoRaw;
     __syncthreads();                                   // before the next strip reuses the staging buffers
   }
 }
@@ -538,7 +539,7 @@ k_half_at(const float* __restrict__ A, int64_t lda, int64_t rows, int n, HalfPan
   if (half_leave(x, rows, wg, gridDim.x * gridDim.y)) return;
   const int found = half_tile_waves<true, NT, MT, WR, WC>(s, x, (uintx4*)lds_raw, notes);
   if (found & kNotFinite) x.flags[wg % kSplitFlags] = 1;
-  if (found & kRedo) x.redo[wg % kSplitFlags] = kRedoRaw;
+  if (found & kRedo) x.redo[wg] = kRedoRaw;
 }
 
 // ---- host side --------------------------------------------------------------------------------------------------
@@ -567,10 +568,10 @@ int half_pack(const float* A, int64_t lda, int64_t count, int64_t K, int Lp, boo
   const dim3 grid((unsigned)split_chunks(K));
   if (nt <= 16)
     hipLaunchKernelGGL(k_half_pack<1>, grid, dim3(64 * nt), 0, stream, x.X, K, x.ldx, x.xcols, nt, (uintx4*)x.panel, x.words, x.flags,
-                       A, lda, count, (int)at);
+                       x.nflags, A, lda, count, (int)at);
   else
     hipLaunchKernelGGL(k_half_pack<2>, grid, dim3(64 * ((nt + 1) / 2)), 0, stream, x.X, K, x.ldx, x.xcols, nt, (uintx4*)x.panel, x.words,
-                       x.flags, A, lda, count, (int)at);
+                       x.flags, x.nflags, A, lda, count, (int)at);
   BRSVD_HIP_TRY(hipGetLastError());
   return BRSVD_OK;
 }

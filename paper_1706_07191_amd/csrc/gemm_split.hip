@@ -559,7 +559,7 @@ k_split_fix_an(SplitFix f, float* __restrict__ Y, int64_t ldy, int ncols, float*
                AnShape sh) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   constexpr int TR = WR * MT * 16;
-  const int redo = f.redo[blockIdx.x % kSplitFlags];
+  const int redo = f.redo[blockIdx.x];
   if (!redo && f.p.flags[blockIdx.x % kSplitFlags] == 0) return;
   const AnWork w = an_work(sh, blockIdx.x);
   for (int seg = 0; seg < w.nseg; ++seg) {
@@ -583,9 +583,9 @@ template <int NT, int MT, int WR, int WC>
 __global__ void __launch_bounds__(WR * WC * 64)
 k_split_fix_at(SplitFix f, float* __restrict__ Zpart, int64_t ldz, int64_t split_stride, int blocks_per_sub) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  const int wg = (blockIdx.y * gridDim.x + blockIdx.x) % kSplitFlags;
+  const int wg = blockIdx.y * gridDim.x + blockIdx.x;
   const int redo = f.redo[wg];
-  if (!redo && f.p.flags[wg] == 0) return;
+  if (!redo && f.p.flags[wg % kSplitFlags] == 0) return;
   SplitTile s;
   s.A = f.p.A;
   s.lda = f.p.lda;
@@ -698,26 +698,29 @@ static int split_pack(const float* A, int64_t lda, int64_t count, int tile, cons
 //   8192 x 1000 256 1.51e-7 / 1.59e-7       12000 x 2000 375 1.72e-7 / 1.72e-7    16384 x 1000 512 1.81e-7 / 1.75e-7
 constexpr int64_t kHalfMinPiece = 1408, kHalfMinK = 16384;
 static bool half_fits(int64_t K, int64_t piece) { return piece >= kHalfMinPiece || K >= kHalfMinK; }
-static bool half_fits_an(int64_t K, const SplitPlan& p) {
+// The place of the packed panel, of the words and of the flags is that of three bf16 numbers; from the flags of rows with small elements
+// only on, and through the words of all rows behind them, stands what each workgroup left undone.
+static bool half_room(int64_t wgs, int64_t out) { return wgs <= kSplitFlags + out; }
+static bool half_fits_an(int64_t out, int64_t K, const SplitPlan& p) {
   const AnShape& sh = p.sh;
   const int64_t tiles = sh.whole + sh.lt, chunks = (int64_t)sh.whole * sh.C + (sh.lt > 0 ? (int64_t)sh.lt * ((sh.C - sh.x) / sh.f) : 0);
-  return half_fits(K, 2 * kSplitB * chunks / tiles);
+  return half_fits(K, 2 * kSplitB * chunks / tiles) && half_room(p.wgs, out);
 }
-static bool half_fits_at(int64_t K, const SplitPlan& p) { return half_fits(K, kSplitB * std::min(p.blocks, p.blocks_per_sub)); }
+static bool half_fits_at(int64_t out, int64_t K, const SplitPlan& p) {
+  return half_fits(K, kSplitB * std::min(p.blocks, p.blocks_per_sub)) && half_room((int64_t)p.col_tiles * p.nsplit, out);
+}
 int split_parts(bool at, int64_t out, int64_t K, int Lp) {
-  if (at) return half_fits_at(K, split_at_plan(K, out, Lp, UINT64_MAX)) ? 2 : 3;
-  return half_fits_an(K, split_an_plan(out, K, Lp, UINT64_MAX)) ? 2 : 3;
+  if (at) return half_fits_at(out, K, split_at_plan(K, out, Lp, UINT64_MAX)) ? 2 : 3;
+  return half_fits_an(out, K, split_an_plan(out, K, Lp, UINT64_MAX)) ? 2 : 3;
 }
-// The place of the packed panel, of the words and of the flags is that of three bf16 numbers; the flags of rows with small elements
-// only say which workgroups have to be redone.
 static int half_prepare(const float* A, int64_t lda, int64_t count, int tile, const float* X, int64_t K, int64_t ldx, int xcols,
-                        int Lp, bool at, void* pack, Packed* out, HalfPacked* hp, hipStream_t stream) {
+                        int Lp, bool at, int64_t wgs, void* pack, Packed* out, HalfPacked* hp, hipStream_t stream) {
   const PackLayout lay = pack_layout(count, K, Lp);
   unsigned* nan = (unsigned*)((char*)pack + lay.nan);
   int* flags = (int*)((char*)pack + lay.flags);
   *out = Packed{(const uintx4*)pack, 0, flags, nullptr,
                 SplitRepair{A, X, lda, ldx, K, xcols, (int)count, tile, Lp / 16, nan, 2 * split_chunks(K), flags, nullptr}};
-  *hp = HalfPacked{pack, nan, flags, flags + kSplitFlags, X, ldx, xcols};
+  *hp = HalfPacked{pack, nan, flags, flags + kSplitFlags, kSplitFlags + wgs, X, ldx, xcols};
   return half_pack(A, lda, count, K, Lp, at, *hp, stream);
 }
 // The column tiles [c0 / 16, c0 / 16 + nt) alone.
@@ -737,9 +740,9 @@ int split_gemm_an(const float* A, int64_t lda, int64_t rows, int64_t K, const fl
   float* part = (float*)scratch;
   const int64_t stride = p.partial_rows * Lp;
   Packed x;
-  const bool half = !whole && half_fits_an(K, p);
+  const bool half = !whole && half_fits_an(rows, K, p);
   HalfPacked hp;
-  if (half) BRSVD_TRY(half_prepare(A, lda, rows, p.tile, X, K, ldx, xcols, Lp, false, pack, &x, &hp, stream));
+  if (half) BRSVD_TRY(half_prepare(A, lda, rows, p.tile, X, K, ldx, xcols, Lp, false, p.wgs, pack, &x, &hp, stream));
   else BRSVD_TRY(split_pack(A, lda, rows, p.tile, X, K, ldx, xcols, Lp, pack, &x, stream));
   for (int gi = 0; gi < p.groups; ++gi) {
     const int c0 = gi * p.nt * 16, nt = std::min(p.nt, (Lp - c0) / 16);
@@ -799,9 +802,9 @@ int split_gemm_at(const float* A, int64_t lda, int64_t rows, int64_t n, const fl
   float* part = (float*)scratch;
   const int64_t stride = n * Lp;
   Packed x;
-  const bool half = !whole && half_fits_at(rows, p);
+  const bool half = !whole && half_fits_at(n, rows, p);
   HalfPacked hp;
-  if (half) BRSVD_TRY(half_prepare(A, lda, n, p.tile, Q, rows, ldq, qcols, Lp, true, pack, &x, &hp, stream));
+  if (half) BRSVD_TRY(half_prepare(A, lda, n, p.tile, Q, rows, ldq, qcols, Lp, true, (int64_t)p.col_tiles * p.nsplit, pack, &x, &hp, stream));
   else BRSVD_TRY(split_pack(A, lda, n, p.tile, Q, rows, ldq, qcols, Lp, pack, &x, stream));
   for (int gi = 0; gi < p.groups; ++gi) {
     const int c0 = gi * p.nt * 16, nt = std::min(p.nt, (Lp - c0) / 16);

@@ -14,7 +14,7 @@ constexpr int kSplitB = 32;          // contraction indices per block
 constexpr int kFragU = 64;           // 16-byte units of one operand fragment (16 x 32 numbers of 16 bits)
 // Flags of the workgroups that met a result that is not finite, and behind them of those that met a row (Z = A^T Q: a column) of
 // A with small elements only.  A workgroup beyond the last one shares a flag with an earlier one; where the other raised it,
-// its own results are only looked at in vain.
+// its own results are only looked at in vain.  (What a workgroup left undone in gemm_half.hip is a word of its own.)
 constexpr int kSplitFlags = 4096;
 constexpr int kNotFinite = 1, kSmall = 2, kRedo = 4;
 
@@ -146,6 +146,7 @@ struct HalfPacked {
   void* panel;
   unsigned* words;
   int *flags, *redo;
+  int64_t nflags;          // words of both
   const float* X;
   int64_t ldx;
   int xcols;

@@ -253,3 +253,20 @@ def test_half_products_repeat_bit_for_bit():
     first = B.brsvd_gemm_an(A, X), B.brsvd_gemm_at(A, Q)
     for _ in range(3):
         assert torch.equal(B.brsvd_gemm_an(A, X), first[0]) and torch.equal(B.brsvd_gemm_at(A, Q), first[1])
+
+
+def test_half_products_with_more_workgroups_than_flags():
+    """A workgroup beyond the 4096th does its part again by itself: the results of all others stay as they are, bit for bit."""
+    dev = need_gpu()
+    rows, n, l = 1060000, 1472, 48
+    A, X = torch.randn(rows, n, generator=torch.Generator(device=dev).manual_seed(4), device=dev), _inputs(1, n, l, 0, 0, dev)[1]
+    assert 0 in _kinds(A, l)
+    plain = B.brsvd_gemm_an(A, X)
+    steps = [c for c in range(n // 64) if all((rows - i - c * 2654435761) % rows >= 64 for i in range(1, 9))]
+    for i in range(1, 9):                # more than a wave keeps
+        A[rows - i, [64 * c for c in steps]] = 1e9
+    got = B.brsvd_gemm_an(A, X)
+    assert torch.equal(got[:4096 * 256], plain[:4096 * 256])
+    tail = slice(rows - 300, rows)
+    err = (got[tail].double() - A[tail].double() @ X.double()).abs()
+    assert bool((err <= _bound(n, A[tail], X)).all())
