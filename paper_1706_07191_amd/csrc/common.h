@@ -260,7 +260,7 @@ template <typename T> bool power_fits(int64_t m, int64_t n, uint64_t scratch_byt
 template <typename T>
 int power_method(const T* A, int64_t lda, int64_t m, int64_t n, const T* x0, int iters, T* z, void* scratch, uint64_t scratch_bytes,
                  double* y2, hipStream_t stream);
-// P[0..count) *= 1 / sqrt(*s2) (device scalar; a zero scalar zeroes P).
+// P[0..count) *= 1 / sqrt(*s2) (device scalar; a zero scalar zeroes P, NaN makes it NaN).
 template <typename T> int scale_rsqrt(T* P, int64_t count, const double* s2, hipStream_t stream);
 
 // ---- device-side Gaussian generator (philox.hip) -------------------------------------------

@@ -285,7 +285,7 @@ k_power_step(const T* __restrict__ A, int64_t lda, int64_t rows, int n, const T*
   for (int i = lane; i < nxx; i += 64) s2 += xx[i];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) s2 += __shfl_xor(s2, o, 64);
-  const T scale = s2 > 0.0 ? (T)(1.0 / sqrt(s2)) : (s2 == 0.0 ? T(0) : (T)s2);
+  const double scale = s2 > 0.0 ? 1.0 / sqrt(s2) : s2;   // (in single precision it is infinite or subnormal for some x that are not)
   int col[K];                                          // of the load; elements before `own` belong to the vector before
   int own[K];
   vec xv[K], z[K];
@@ -296,7 +296,7 @@ k_power_step(const T* __restrict__ A, int64_t lda, int64_t rows, int n, const T*
     own[k] = min(c - col[k], V);
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-      xv[k][v] = v >= own[k] ? x[col[k] + v] * scale : T(0);
+      xv[k][v] = v >= own[k] ? (T)((double)x[col[k] + v] * scale) : T(0);
       z[k][v] = T(0);
     }
   }
@@ -456,7 +456,7 @@ __global__ void k_scale_rsqrt(T* __restrict__ P, int64_t count, const double* __
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= count) return;
   const double v = *s2;
-  P[i] = v > 0.0 ? (T)((double)P[i] / sqrt(v)) : T(0);
+  P[i] = v > 0.0 ? (T)((double)P[i] / sqrt(v)) : (T)v;
 }
 
 // Shape of the update kernel's workgroups for rows of n elements of esz bytes: vector columns per tile

@@ -306,3 +306,25 @@ def test_norm2_power_row_lengths(n, f64):
             assert not np.isfinite(B.brsvd_norm2_power(h, A, x0, 2))
         finally:
             B.brsvd_destroy(h)
+
+
+@pytest.mark.parametrize("n", [61, 2050, 8193])
+@pytest.mark.parametrize("square", [1e-39, 2e38])
+def test_norm2_power_at_the_ends_of_the_range(n, square):
+    """A^T A x is a vector of single precision whose norm (`square`) has no reciprocal there, or one that is subnormal."""
+    dev = need_gpu()
+    m = 517
+    A = synth.gaussian(m, n, 33, device=dev) + 0.25
+    x0 = synth.gaussian(n, 1, 34, device=dev).reshape(-1)
+    Ah, xh = A.double().cpu().numpy(), x0.double().cpu().numpy()
+    scale = float(np.float32(np.sqrt(square) / O.norm2_power(Ah, xh, 6)))
+    h = B.brsvd_create(B.make_params(m, n, 1, 0, 1))
+    try:
+        got = B.brsvd_norm2_power(h, A * scale, x0, 4)
+        x0[n // 3] = float("nan")
+        assert not np.isfinite(B.brsvd_norm2_power(h, A, x0, 2))
+    finally:
+        B.brsvd_destroy(h)
+    want = O.norm2_power((A * scale).double().cpu().numpy(), xh, 4)
+    # as above; entries of A^T A x may be subnormal, i.e. half of 2^-149 off each, and so may the partial sums of up to m / 16 workgroups
+    assert abs(got - want) <= (16 * np.sqrt(m + n) * 2.0 ** -23 + 4 * 2.0 ** -150 * np.sqrt(n) * (1 + m / 16) / square) * want
