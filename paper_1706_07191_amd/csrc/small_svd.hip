@@ -138,29 +138,30 @@ __device__ __forceinline__ double row8_sum(double v) {
 }
 
 // ---- up to 16 and 33 to 40 rows: row rotations in LDS ---------------------------------------------------------------------------------
-// Each group of 16 lanes owns one row pair per step, so a wave handles 4 pairs with one instruction stream and up to
-// 64 pairs take 1024 threads.  EPL = elements of a row per lane = ceil(l / 16).
+// Each group of 16 lanes owns one row pair per step, so a wave handles 4 pairs with one instruction stream: 8 pairs take 128 threads,
+// 24 take 384.  EPL = elements of a row per lane = ceil(l / 16).
 // Pair schedule of a sweep (every pair of rows met exactly once): the index range is halved
 // recursively.  At a level, every segment [base, base + n) is cut into a top half of h = ceil(n/2) rows
 // and a bottom half; in step s top row i meets bottom row (i + s) mod h, so h steps pair every top with
 // every bottom of the segment; the next level does the same inside both halves, all segments side by
 // side (l-1 .. l+1 steps in all).  Within a level a group keeps its top row in registers and only the
 // bottom rows travel through LDS, which halves the LDS traffic of the round-robin schedule.
-constexpr int kJLev = 7;      // levels for l <= 128
 constexpr int LPP = 16;
+constexpr int kRowsMaxL = 16, kRowsMaxL3 = 40;    // row rotations up to here: with one block of 16 rows, with three
+constexpr int rows_threads(int epl) { return (epl == 1 ? 8 : 24) * LPP; }      // most pairs of a step: of 40 rows in eight segments of 5
 
 template <int EPL>
-__global__ void __launch_bounds__(64 * LPP)
+__global__ void __launch_bounds__(rows_threads(EPL))
 k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __restrict__ Wg,
              double* __restrict__ sig, int* __restrict__ info, const int* __restrict__ breakdown_flag,
              double tol, double settled) {
   extern __shared__ double W[];
   __shared__ int rotated;
   __shared__ int order_sh[kMaxL];
-  __shared__ short tb_top[kJLev][64], tb_bb[kJLev][64], tb_bs[kJLev][64], tb_hi[kJLev][64];
-  __shared__ short seg_base[2][128], seg_size[2][128];
-  __shared__ int lev_steps[kJLev];
-  constexpr int NT = 64 * LPP;
+  constexpr int NT = rows_threads(EPL), PAIRS = NT / LPP, LEV = EPL == 1 ? 4 : 6;      // levels: 16 8 4 2, 40 20 10 5 3 2
+  __shared__ short tb_top[LEV][PAIRS], tb_bb[LEV][PAIRS], tb_bs[LEV][PAIRS], tb_hi[LEV][PAIRS];
+  __shared__ short seg_base[2][1 << LEV], seg_size[2][1 << LEV];
+  __shared__ int lev_steps[LEV];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (breakdown_flag && breakdown_flag[0] != 0) {
     if (tid == 0) { info[0] = 0; info[1] = 0; }
@@ -173,9 +174,9 @@ k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __re
   }
   // schedule tables: per level and group, the top row, the bottom half [bb, bb + bs) and (h << 8) | i
   if (tid == 0) { seg_base[0][0] = 0; seg_size[0][0] = (short)l; }
-  for (int lev = 0; lev < kJLev; ++lev) {
+  for (int lev = 0; lev < LEV; ++lev) {
     const int nseg = 1 << lev, cur = lev & 1;
-    if (tid < 64) tb_top[lev][tid] = -1;
+    if (tid < PAIRS) tb_top[lev][tid] = -1;
     __syncthreads();
     if (tid < nseg) {
       const int base = seg_base[cur][tid], size = seg_size[cur][tid];
@@ -185,7 +186,7 @@ k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __re
         for (int k = 0; k < tid; ++k) { const int sz = seg_size[cur][k]; if (sz >= 2) off += (sz + 1) >> 1; }
         for (int i = 0; i < h; ++i) {
           const int gid = off + i;
-          if (gid < 64) {
+          if (gid < PAIRS) {
             tb_top[lev][gid] = (short)(base + i); tb_bb[lev][gid] = (short)(base + h);
             tb_bs[lev][gid] = (short)nb; tb_hi[lev][gid] = (short)((h << 8) | i);
           }
@@ -210,7 +211,7 @@ k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __re
     if (tid == 0) rotated = 0;
     __syncthreads();
     bool any = false;
-    for (int lev = 0; lev < kJLev; ++lev) {
+    for (int lev = 0; lev < LEV; ++lev) {
       const int steps = lev_steps[lev];
       if (steps == 0) continue;                        // uniform over the workgroup
       const int top = tb_top[lev][pi], bb = tb_bb[lev][pi], bs = tb_bs[lev][pi];
@@ -291,7 +292,8 @@ k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __re
 //   75 / 62, 14 54 / 52 and 76 / 61, 16 54 / 54 and 76 / 74; on the other side 17 66 / 80 and 77 / 93, 20 67 / 84 and 78 / 98;
 //   and with three blocks up to 40 rows, where a fourth block goes round that is padding: l = 33 169 / 154 and 259 / 204, 36 170 / 160
 //   and 230 / 215, 40 170 / 173 and 231 / 230; on the other side 44 171 / 189 and 261 / 250, 48 171 / 199 and 232 / 263.
-// (One sweep more or less, 28 us at l = 33 to 48, is by chance.)
+// (One sweep more or less, 28 us at l = 33 to 48, is by chance.  Row rotations were timed with 1024 threads, of which most only met the
+// others at the barriers; with those they need a call of brsvd_small_svd takes 61 us in the place of 77 at l = 16 and 163 of 189 at 40.)
 // What bounds it: the latency of a step, 640 cycles from barrier to barrier -- 130 until the rotations are read from LDS, 60 for the
 // new inner product, 190 for the 13 dependent operations of the rotation, the rest its way back to LDS -- and of the meeting of the
 // workgroups.  At l = 110 a round takes 25 thousand cycles: 11.2 the 16 steps, 3.2 the Gram matrix, 4.1 J^T times the rows, 2.5 the load
@@ -303,7 +305,6 @@ k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __re
 // 329 (row rotations before), 97 555 -> 447, 110 558 -> 451, 128 580 -> 464, 160 1312 -> 1040, 272 2197 -> 1686, 400 6078 -> 4454.
 constexpr int kJB = 16;
 constexpr int kJN = 2 * kJB;                      // rows of a block pair
-constexpr int kRowsMaxL = 16, kRowsMaxL3 = 40;    // up to here, row rotations: with one block, with three
 // Place of entry (x, y) of the Gram matrix and of J: odd rows have their halves exchanged, so that the two rows of 16
 // consecutive columns that half a wave touches, and 16 consecutive diagonal entries, lie on distinct banks.
 __device__ __forceinline__ int jat(int x, int y) { return x * kJN + (y ^ ((x & 1) << 4)); }
@@ -837,7 +838,7 @@ int small_svd(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* br
   const int nblk = (l + kJB - 1) / kJB;
   if (l <= kRowsMaxL || (nblk == 3 && l <= kRowsMaxL3)) {
     auto kern = nblk == 1 ? k_jacobi_rows<1> : k_jacobi_rows<3>;
-    hipLaunchKernelGGL(kern, dim3(1), dim3(64 * LPP), (size_t)l * l * sizeof(double), stream, R, ldr, l, Lp, w.W, w.sig, w.info,
+    hipLaunchKernelGGL(kern, dim3(1), dim3(rows_threads(nblk)), (size_t)l * l * sizeof(double), stream, R, ldr, l, Lp, w.W, w.sig, w.info,
                        breakdown_flag, nblk == 1 ? kTolOneBlock : kTolRows, settled);
     BRSVD_HIP_TRY(hipGetLastError());
   } else if (l <= kJN) {
