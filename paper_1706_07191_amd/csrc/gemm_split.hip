@@ -691,11 +691,16 @@ static int split_pack(const float* A, int64_t lda, int64_t count, int tile, cons
 }
 
 // Whether the products of two fp16 numbers each (gemm_half.hip) are taken: `piece` = contraction indices one workgroup adds up, on
-// average.  They are where their results are at least as accurate: what the split loses (7e-8 of a product) has to be less than what
-// the additions lose, half as many as here.  Relative error, 3 x bf16 and 2 x fp16 (N(0, 1) entries, K x outputs, pieces):
-//   1000 x 300000 1000 1.20e-7 / 1.33e-7    4000 x 8000 500 1.24e-7 / 1.42e-7     2100 x 30000 1050 1.29e-7 / 1.40e-7
-//   6000 x 16000 1500 1.63e-7 / 1.58e-7     12000 x 8192 1500 1.87e-7 / 1.71e-7   2500 x 60000 2500 1.78e-7 / 1.64e-7
-//   8192 x 1000 256 1.51e-7 / 1.59e-7       12000 x 2000 375 1.72e-7 / 1.72e-7    16384 x 1000 512 1.81e-7 / 1.75e-7
+// average.  They are where their results are about as accurate or more: what the split loses (7e-8 of a product) has to be less than what
+// the additions lose, half as many as here.  Relative error, 3 x bf16 and 2 x fp16 (N(0, 1) entries, K x outputs, pieces; a test holds the
+// second to the first):
+//   1000 x 300000 1000 1.20e-7 / 1.33e-7    1472 x 60000 1472 1.40e-7 / 1.44e-7   2100 x 30000 1050 1.29e-7 / 1.40e-7
+//   1900 x 60000 1900 1.58e-7 / 1.53e-7     6000 x 16000 1500 1.63e-7 / 1.58e-7   12000 x 8192 1500 1.87e-7 / 1.71e-7
+//   4000 x 8000 500 1.24e-7 / 1.42e-7       8192 x 1000 256 1.51e-7 / 1.59e-7     12000 x 2000 375 1.72e-7 / 1.72e-7
+//   16384 x 1000 512 1.81e-7 / 1.75e-7      33000 x 1000 520 2.27e-7 / 2.01e-7    89083 x 2783 3.86e-7 / 2.98e-7
+// Entries uniform in (0, 1): 1472 x 60000 1.41e-7 / 1.40e-7, 16384 x 1000 1.88e-7 / 1.90e-7 (l = 48; 1.75e-7 / 1.73e-7 with l = 110), 89083 x 2783
+// 3.42e-7 / 2.68e-7.  A of rank 2 l times orthonormal columns along it, where both are near the rounding of the result: 2783 x 89083
+// 1.25e-7 / 9.4e-8, 33000 x 1000 5.06e-8 / 5.07e-8, 200000 x 300 5.3e-8 / 5.6e-8.
 constexpr int64_t kHalfMinPiece = 1408, kHalfMinK = 16384;
 static bool half_fits(int64_t K, int64_t piece) { return piece >= kHalfMinPiece || K >= kHalfMinK; }
 // The place of the packed panel, of the words and of the flags is that of three bf16 numbers; from the flags of rows with small elements

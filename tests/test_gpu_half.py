@@ -270,3 +270,26 @@ def test_half_products_with_more_workgroups_than_flags():
     tail = slice(rows - 300, rows)
     err = (got[tail].double() - A[tail].double() @ X.double()).abs()
     assert bool((err <= _bound(n, A[tail], X)).all())
+
+
+@pytest.mark.parametrize("w,rows,n,l,most", [
+    (0, 70000, 1409, 110, 1.05), (1, 1472, 60000, 110, 1.05), (0, 60000, 1800, 110, 1.0), (1, 1800, 60000, 110, 1.0), (0, 16000, 6000, 97, 1.0),
+    (0, 1000, 16390, 110, 1.0), (1, 16390, 1000, 110, 1.0), (0, 8192, 12000, 60, 1.0), (1, 89083, 2783, 97, 0.9), (0, 20000, 20000, 110, 0.9)])
+def test_half_products_are_as_accurate_as_six_bf16_ones(w, rows, n, l, most):
+    """From the lines on where they are taken (at the shortest one both are alike: 2^-24 of each product is lost in place of half of 44 rounded
+    additions).  The last column decides: one number in 64 leaves all of them to bf16."""
+    dev = need_gpu()
+    g = torch.Generator(device=dev).manual_seed(12)
+    A = torch.randn(rows, n, generator=g, device=dev)
+    P = torch.randn(n if w == 0 else rows, l, generator=g, device=dev)
+    assert B.brsvd_gemm_is_split(w, rows, n, l) and B.brsvd_gemm_split_parts(w, rows, n, l) == 2
+    product = B.brsvd_gemm_an if w == 0 else B.brsvd_gemm_at
+    exact = (A.double() @ P.double() if w == 0 else A.double().T.contiguous() @ P.double())[:, :l - 1]
+    error = []
+    for sparse in (False, True):
+        if sparse:
+            P[:, l - 1] = 0.0
+            P[::64, l - 1] = 1.0
+        error.append(float((product(A, P)[:, :l - 1].double() - exact).norm() / exact.norm()))
+    print(f"[case] half {w} {rows}x{n} l={l} errors {error[0]:.3e} {error[1]:.3e}", flush=True)
+    assert error[0] != error[1] and error[0] <= most * error[1]
