@@ -82,15 +82,16 @@ __device__ __forceinline__ int sum_groups(int v) {
   return (int)b[0] + (int)b[1];
 }
 // The test of a row's step, see above: run = the largest of each four successive indices that this lane holds (the other groups of lanes
-// hold the rest), m = the largest of the step; false if too few of them are large.  whole: 64 indices, otherwise the first 32 count.
-// (Where 2^-7 m rounds to zero, m is so small that fp16 holds every number of the row whole.)
+// hold the rest), m = the largest of the step; returns how many of the lane's are large, min_runs of them in all groups pass.  whole: 64
+// indices, otherwise the first 32 count.  (Where 2^-7 m rounds to zero, m is so small that fp16 holds every number of the row whole.)
 constexpr float kLargeRun = 0x1p-7f, kLargeEntry = 0x1p-9f;
-constexpr int kMinRuns = 14, kMaxSmall = 11, kMinRunsHalf = 7, kMaxSmallHalf = 5;
-__device__ __forceinline__ bool half_range(const float (&run)[4], bool whole, unsigned& m) {
+constexpr int kMaxSmall = 11, kMaxSmallHalf = 5;
+__device__ __forceinline__ int min_runs(bool whole) { return whole ? 14 : 7; }
+__device__ __forceinline__ int large_runs(const float (&run)[4], bool whole, unsigned& m) {
   m = max_groups(__float_as_uint(fmaxf(fmaxf(run[0], run[1]), fmaxf(run[2], run[3]))));
   const float thr = __uint_as_float(m) * kLargeRun;
   const int n0 = (run[0] >= thr ? 1 : 0) + (run[1] >= thr ? 1 : 0), n1 = (run[2] >= thr ? 1 : 0) + (run[3] >= thr ? 1 : 0);
-  return sum_groups(n0 + (whole ? n1 : 0)) >= (whole ? kMinRuns : kMinRunsHalf);
+  return n0 + (whole ? n1 : 0);
 }
 
 // The steps before those that may have less than 64 indices.
@@ -136,7 +137,7 @@ k_half_pack(const float* __restrict__ src, int64_t K, int64_t ld, int cols, int 
       run[q] = fmaxf(fmaxf(fabsf(p[k * step]), fabsf(p[(k + 1) * step])), fmaxf(fabsf(p[(k + 2) * step]), fabsf(p[(k + 3) * step])));
     }
     unsigned m;
-    bad = !half_range(run, whole, m);
+    bad = sum_groups(large_runs(run, whole, m)) < min_runs(whole);
   }
   for (int64_t i = id; i < nflags; i += threads) flags[i] = 0;
   __syncthreads();
@@ -290,15 +291,21 @@ __device__ __forceinline__ int half_tile(const SplitTile& s, const HalfPanel& pa
   // The scale of each row (column) for step c; those that fail are left out and noted.
   auto scan = [&](unsigned sx, int c) {
     const bool whole = c < whole_end;
-    unsigned rows = 0;
+    unsigned rows = 0, most[MT];
+    int large = 0;                                     // of all rows' counts, in bytes
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       float run[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         run[q] = fmaxf(fmaxf(fabsf(elem(mt, q, 0)), fabsf(elem(mt, q, 1))), fmaxf(fabsf(elem(mt, q, 2)), fabsf(elem(mt, q, 3))));
-      unsigned m;
-      bool bad = !half_range(run, whole, m);
+      large += large_runs(run, whole, most[mt]) << (8 * mt);
+    }
+    large = sum_groups(large);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      const unsigned m = most[mt];
+      bool bad = (large >> (8 * mt) & 0xff) < min_runs(whole);
       const unsigned eb = m == 0 ? 127u << 23 : max(m & kExpMask, 15u << 23);
       const int comb = (int)(eb + sx);
       bad |= m != 0 && (unsigned)comb - kExpOne > 253u * kExpOne;
