@@ -42,8 +42,8 @@ C4_ROWS = 160000              # the GPU machine pins at most about 64 GB of host mem
 # scaled by a plain 1 GiB copy in the same run.  Hardware counters cannot be read from inside the timed run, so
 # these are offline figures; `traffic_source` in the JSON names the summary they come from.
 OFFLINE_HBM_TRAFFIC = {
-    "C3:gemm_an": 2.2012e10, "C3:gemm_at": 2.5137e10,
-    "C2:gemm_an": 1.7369e9, "C2:gemm_at": 1.7012e9,
+    "C3:gemm_an": 2.1973e10, "C3:gemm_at": 2.5171e10,
+    "C2:gemm_an": 1.7355e9, "C2:gemm_at": 1.7014e9,
     "C5:gemm_an": 6.8064e8, "C5:gemm_at": 7.0227e8, "C5:rpca_update": 2.5175e9,
 }
 OFFLINE_HBM_TRAFFIC_SOURCE = {

@@ -101,9 +101,9 @@ __device__ __forceinline__ int whole_steps(int64_t K) {
 }
 
 // Packed panel: [step][column tile][block of the step][h, l][lane][8 fp16], 4 KiB per step and tile of 16 columns.  One workgroup per step
-// of 64 rows, PER tiles of columns per wave.  Also clears the flags, and looks at the step in 16 rows (AT: columns) of A, so that
-// a matrix of many magnitudes is not found out by every workgroup of the product on its own.
-// What bounds it: the latency of its loads and of two reductions (5 us; with four waves that read the panel twice 10 to 22).
+// of 64 rows, PER tiles of columns per wave.  Also clears the flags, and looks at the step in up to 64 rows (AT: columns) of A, 16 per
+// wave, so that a matrix of many magnitudes is not found out by every workgroup of the product on its own.
+// What bounds it: the latency of its loads and of two reductions (20000 x 110 9.5 us, 100000 x 272 56 us).
 template <int PER>
 __global__ void __launch_bounds__(1024)
 k_half_pack(const float* __restrict__ src, int64_t K, int64_t ld, int cols, int nt_total, uintx4* __restrict__ out,
@@ -210,14 +210,17 @@ typedef uint2 Noted[8][kMaxNoted + 1];
 // panel is the first operand of the instruction and A the second, so that a lane's results belong to one row and that row's scale
 // is in the lane that split it.
 //
-// What bounds it: from 15 column tiles on the power of the matrix cores (clock 1.5 GHz, 51 % busy; the six bf16 products: 1.65 GHz,
-// 77 %), below that, and with 4 tiles alone, the latency of the loads of A.  As there, everything else is spread over the stream of matrix
+// What bounds it: below 15 column tiles, and with 4 alone, the latency of the loads of A.  With 17 the chip is at its power limit (1.65 GHz),
+// but the matrix cores are only 47 % busy (the six bf16 products: 63 to 67 % at the same clock); where the rest of the power goes is not
+// established -- from 11 tiles on both columns of waves load, scan and split the same rows, and A X keeps 8 to 88 bytes a lane in scratch
+// (13 to 17 tiles).  As there, everything else is spread over the stream of matrix
 // instructions: the panel's fragments from LDS, the block sums, the scale of the next step (all of its part of A has to be there:
 // in the middle of the step), its split, the loads, and the hand-over of the panel, in parts to need fewer registers.  The code of a
-// step has no branch, and none is taken before the sums of both steps of an iteration are complete on either path: the compiler
-// would put off sums past it and run out of registers (25 more per column tile).
-// Measured, six bf16 products and this (us of the whole product, A X / A^T Q): 100000x50000 l=272 12982 / 13720 and 9058 / 9350;
-// 20000x20000 l=110 579 / 534 and 472 / 398, l=64 407 / 386 and 354 / 316; 89083x2783 l=97 346 / 342 and 298 / 274.
+// step has no branch, also not for the rows that are left out: the compiler would put off sums past it and run out of registers (25 more
+// per column tile).
+// Measured, six bf16 products and this (us of the whole product, A X / A^T Q): 100000x50000 l=272 12982 / 13720 and 9315 / 9678;
+// 20000x20000 l=110 579 / 534 and 473 / 397, l=64 407 / 386 and 354 / 320; 89083x2783 l=97 346 / 342 and 302 / 273.  (Without the test of every
+// row's step, which numbers beside larger ones need, 2 % less.)
 template <bool AT, int NT, int NTW, int MT, int WR, int WC>
 __device__ __forceinline__ int half_tile(const SplitTile& s, const HalfPanel& panel, uintx4* lds, Noted& notes, int wave, int wr,
                                          int nt0) {

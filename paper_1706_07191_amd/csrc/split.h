@@ -115,9 +115,10 @@ struct SplitTile {
 // ---- host side --------------------------------------------------------------------------------------------------
 struct SplitCfg { int wr, wc, tile; };
 constexpr int kSplitMT = 2;
-// Up to ten column tiles one wave holds them all (accumulators of 2 x 10 tiles: 230 registers of 256 for
-// A^T Q; A X takes all of them and, with 9, 10, 14, 16 and 17 tiles, 12 to 24 places in scratch); wider panels take
-// two columns of waves, i.e. half as many rows per workgroup.
+// Up to ten column tiles one wave holds them all (accumulators of 2 x 10 tiles); wider panels take two columns of waves, i.e. half as many
+// rows per workgroup.  Registers: three bf16 numbers take all 256 for A X from 9 tiles on and 36 to 212 bytes a lane of scratch (none with
+// 12 tiles), for A^T Q up to 228 and 88 bytes with 15 and 17 tiles; two fp16 ones all for A X from 9 tiles on and 8 to 88 bytes with 13 to
+// 17, for A^T Q up to 245 and none.
 static SplitCfg split_cfg(int nt) {
   return nt <= 10 ? SplitCfg{8, 1, 8 * kSplitMT * 16} : SplitCfg{4, 2, 4 * kSplitMT * 16};
 }
