@@ -94,12 +94,6 @@ __device__ __forceinline__ int large_runs(const float (&run)[4], bool whole, uns
   return n0 + (whole ? n1 : 0);
 }
 
-// The steps before those that may have less than 64 indices.
-__device__ __forceinline__ int whole_steps(int64_t K) {
-  const int n = (int)((K + kSplitB - 1) / kSplitB);
-  return n & 1 ? (n - 3) / 2 : (int)(K / kHalfStep);
-}
-
 // Packed panel: [step][column tile][block of the step][h, l][lane][8 fp16], 4 KiB per step and tile of 16 columns.  One workgroup per step
 // of 64 rows, PER tiles of columns per wave.  Also clears the flags, and looks at the step in up to 64 rows (AT: columns) of A, 16 per
 // wave, so that a matrix of many magnitudes is not found out by every workgroup of the product on its own.

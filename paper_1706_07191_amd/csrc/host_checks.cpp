@@ -15,6 +15,7 @@
 #include "brsvd.h"
 #include "brsvd_steps.h"
 #include "common.h"
+#include "split.h"
 
 static int g_checks = 0, g_failed = 0;
 #define CHECK(cond)                                                             \
@@ -41,6 +42,25 @@ static int64_t uniform(int64_t lo, int64_t hi) { return lo + (int64_t)(next_u64(
 int main() {
   uint64_t bytes = 0;
   brsvd_handle h = nullptr;
+
+  // ---- blocks of a split contraction: read inside the range, every index covered once, the first of any two whole ----
+  for (int i = 0; i < 4000; ++i) {
+    using namespace brsvd;
+    const int64_t K = i < 1500 ? 3 * kSplitB + i : uniform(512, 200000), chunks = split_chunks(K);
+    std::vector<unsigned char> covered((size_t)K, 0);
+    int64_t next = 0;                                    // the first index that the chunks before do not cover
+    bool good = true;
+    for (int64_t c = 0; c < chunks; ++c) {
+      good &= next == std::min(K, block_index(2 * c, K) * kSplitB) && block_first(2 * c, K) == block_start(2 * c, K);
+      if (c < whole_steps(K)) good &= block_first(2 * c + 1, K) == block_start(2 * c, K) + kSplitB;
+      for (int64_t b = 2 * c; b < 2 * c + 2; ++b) {
+        const int64_t k0 = block_start(b, K), first = block_first(b, K);
+        good &= k0 >= 0 && k0 + kSplitB <= K && k0 == block_start((int)b, (int)empty_block(K), (int)K);
+        for (int64_t k = std::max(k0, first); k < k0 + kSplitB; ++k) { good &= covered[k]++ == 0; ++next; }
+      }
+    }
+    CHECK(good && next == K);
+  }
 
   // ---- argument validation ----
   CHECK(brsvd_workspace_bytes(nullptr, &bytes) == BRSVD_ERR_ARG);

@@ -22,15 +22,26 @@ constexpr int kNotFinite = 1, kSmall = 2, kRedo = 4;
 // Block `blk` covers the contraction indices from block_first on (K for the empty one).  It is read from block_start on: the last one is
 // moved back so that it ends with the range, and the indices the block before has already covered are zero in the packed panel.
 // Neither operand is then ever read outside its range, and A needs no masks.  K >= 3 * kSplitB.
-__device__ __forceinline__ int64_t empty_block(int64_t K) {
+__host__ __device__ inline int64_t empty_block(int64_t K) {
   const int64_t n = (K + kSplitB - 1) / kSplitB;
   return n & 1 ? n - 2 : n;
 }
-__device__ __forceinline__ int64_t block_index(int64_t blk, int64_t K) { return blk > empty_block(K) ? blk - 1 : blk; }
-__device__ __forceinline__ int64_t block_first(int64_t blk, int64_t K) { return blk == empty_block(K) ? K : block_index(blk, K) * kSplitB; }
-__device__ __forceinline__ int64_t block_start(int64_t blk, int64_t K) { return min(block_index(blk, K) * kSplitB, K - kSplitB); }
+__host__ __device__ inline int64_t block_index(int64_t blk, int64_t K) { return blk > empty_block(K) ? blk - 1 : blk; }
+__host__ __device__ inline int64_t block_first(int64_t blk, int64_t K) { return blk == empty_block(K) ? K : block_index(blk, K) * kSplitB; }
+__host__ __device__ inline int64_t block_start(int64_t blk, int64_t K) {
+  const int64_t k = block_index(blk, K) * kSplitB;
+  return k < K - kSplitB ? k : K - kSplitB;
+}
 // The same in 32 bits (split_fits), which is all that scalar instructions compare: in 64 the addresses take vector registers.
-__device__ __forceinline__ int block_start(int blk, int empty, int K) { return min((blk - (blk > empty ? 1 : 0)) * kSplitB, K - kSplitB); }
+__host__ __device__ inline int block_start(int blk, int empty, int K) {
+  const int k = (blk - (blk > empty ? 1 : 0)) * kSplitB;
+  return k < K - kSplitB ? k : K - kSplitB;
+}
+// The twos of blocks before those that may have less than 64 indices.
+__host__ __device__ inline int whole_steps(int64_t K) {
+  const int n = (int)((K + kSplitB - 1) / kSplitB);
+  return n & 1 ? (n - 3) / 2 : (int)(K / (2 * kSplitB));
+}
 
 template <int I, int N, typename F>
 __device__ __forceinline__ void static_for(F&& f) {
