@@ -137,9 +137,9 @@ __device__ __forceinline__ double row8_sum(double v) {
   return v;
 }
 
-// ---- up to 16 and 33 to 40 rows: row rotations in LDS ---------------------------------------------------------------------------------
+// ---- up to 16 and 33 to 48 rows: row rotations in LDS ---------------------------------------------------------------------------------
 // Each group of 16 lanes owns one row pair per step, so a wave handles 4 pairs with one instruction stream: 8 pairs take 128 threads,
-// 24 take 384.  EPL = elements of a row per lane = ceil(l / 16).
+// 32 take 512.  EPL = elements of a row per lane = ceil(l / 16).
 // Pair schedule of a sweep (every pair of rows met exactly once): the index range is halved
 // recursively.  At a level, every segment [base, base + n) is cut into a top half of h = ceil(n/2) rows
 // and a bottom half; in step s top row i meets bottom row (i + s) mod h, so h steps pair every top with
@@ -147,18 +147,17 @@ __device__ __forceinline__ double row8_sum(double v) {
 // side (l-1 .. l+1 steps in all).  Within a level a group keeps its top row in registers and only the
 // bottom rows travel through LDS, which halves the LDS traffic of the round-robin schedule.
 constexpr int LPP = 16;
-constexpr int kRowsMaxL = 16, kRowsMaxL3 = 40;    // row rotations up to here: with one block of 16 rows, with three
-constexpr int rows_threads(int epl) { return (epl == 1 ? 8 : 24) * LPP; }      // most pairs of a step: of 40 rows in eight segments of 5
+constexpr int kRowsMaxL = 16;                      // row rotations up to here, with one block of 16 rows, and with three
 
-template <int EPL>
-__global__ void __launch_bounds__(rows_threads(EPL))
+template <int EPL, int PAIRS>       // PAIRS = the most of a step: 8 up to 16 rows, 24 up to 40 (eight segments of 5), 32 up to 48
+__global__ void __launch_bounds__(PAIRS * LPP)
 k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __restrict__ Wg,
              double* __restrict__ sig, int* __restrict__ info, const int* __restrict__ breakdown_flag,
              double tol, double settled) {
   extern __shared__ double W[];
-  __shared__ int rotated;
+  __shared__ int rotated, top;
   __shared__ int order_sh[kMaxL];
-  constexpr int NT = rows_threads(EPL), PAIRS = NT / LPP, LEV = EPL == 1 ? 4 : 6;      // levels: 16 8 4 2, 40 20 10 5 3 2
+  constexpr int NT = PAIRS * LPP, LEV = EPL == 1 ? 4 : 6;      // levels: 16 8 4 2, 40 20 10 5 3 2
   __shared__ short tb_top[LEV][PAIRS], tb_bb[LEV][PAIRS], tb_bs[LEV][PAIRS], tb_hi[LEV][PAIRS];
   __shared__ short seg_base[2][1 << LEV], seg_size[2][1 << LEV];
   __shared__ int lev_steps[LEV];
@@ -168,10 +167,22 @@ k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __re
     return;
   }
   const int ld = l;
+  // The bars compare squares of squared norms.  Where even those of the largest entry would be close to the smallest double, all entries are
+  // multiplied by a power of two (and by its inverse in the end).
+  if (tid == 0) top = 0;
+  __syncthreads();
+  int most = 0;
   for (int idx = tid; idx < l * l; idx += NT) {
     int i = idx / l, c = idx - i * l;
-    W[i * ld + c] = R[(int64_t)i * ldr + c];
+    const double v = R[(int64_t)i * ldr + c];
+    W[i * ld + c] = v;
+    most = max(most, __double2hiint(v) >> 20 & 0x7ff);
   }
+  atomicMax(&top, most);
+  __syncthreads();
+  const int shift = top > 823 ? 0 : 1023 - top;
+  if (shift != 0)
+    for (int idx = tid; idx < l * l; idx += NT) W[idx] = ldexp(W[idx], shift);
   // schedule tables: per level and group, the top row, the bottom half [bb, bb + bs) and (h << 8) | i
   if (tid == 0) { seg_base[0][0] = 0; seg_size[0][0] = (short)l; }
   for (int lev = 0; lev < LEV; ++lev) {
@@ -268,6 +279,10 @@ k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __re
     converged = (rotated == 0);
     __syncthreads();
   }
+  if (shift != 0) {
+    for (int idx = tid; idx < l * l; idx += NT) W[idx] = ldexp(W[idx], -shift);
+    __syncthreads();
+  }
   publish<NT>(W, ld, l, Lp, Wg, sig, order_sh, tid, lane, wave);
   if (tid == 0) { info[0] = sweeps; info[1] = converged; }
 }
@@ -290,10 +305,11 @@ k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __re
 // against row rotations)
 //   up to 16 rows, where the 31 steps of a sweep are more than their l: l = 4 41 / 19 and 52 / 22, 8 52 / 32 and 77 / 42, 12 53 / 46 and
 //   75 / 62, 14 54 / 52 and 76 / 61, 16 54 / 54 and 76 / 74; on the other side 17 66 / 80 and 77 / 93, 20 67 / 84 and 78 / 98;
-//   and with three blocks up to 40 rows, where a fourth block goes round that is padding: l = 33 169 / 154 and 259 / 204, 36 170 / 160
-//   and 230 / 215, 40 170 / 173 and 231 / 230; on the other side 44 171 / 189 and 261 / 250, 48 171 / 199 and 232 / 263.
-// (One sweep more or less, 28 us at l = 33 to 48, is by chance.  Row rotations were timed with 1024 threads, of which most only met the
-// others at the barriers; with those they need a call of brsvd_small_svd takes 61 us in the place of 77 at l = 16 and 163 of 189 at 40.)
+//   and with three blocks, where a fourth block goes round that is padding (us of a call of brsvd_small_svd, on a panel's R / on one of equal
+//   columns): l = 33 - / 132 and 193, 40 - / 165 and 219, 41 196 and 286 / 172 and 227, 44 195 and 288 / 177 and 233, 48 196 and 281 / 186
+//   and 271.
+// (One sweep more or less, 28 us at l = 33 to 48, is by chance.  The figures up to 20 rows are with 1024 threads for the row rotations, of which
+// most only met the others at the barriers; with those they need a call takes 63 us in the place of 77 at l = 16.)
 // What bounds it: the latency of a step, 640 cycles from barrier to barrier -- 130 until the rotations are read from LDS, 60 for the
 // new inner product, 190 for the 13 dependent operations of the rotation, the rest its way back to LDS -- and of the meeting of the
 // workgroups.  At l = 110 a round takes 25 thousand cycles: 11.2 the 16 steps, 3.2 the Gram matrix, 4.1 J^T times the rows, 2.5 the load
@@ -836,9 +852,10 @@ int small_svd(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* br
   // fp64 factors or singular values asked for: the strict bar; single-precision results only: the relaxed one
   const double settled = (sizeof(TO) == 4 && !S && !Ur && !Vr) ? kSettledF32 : kSettled;
   const int nblk = (l + kJB - 1) / kJB;
-  if (l <= kRowsMaxL || (nblk == 3 && l <= kRowsMaxL3)) {
-    auto kern = nblk == 1 ? k_jacobi_rows<1> : k_jacobi_rows<3>;
-    hipLaunchKernelGGL(kern, dim3(1), dim3(rows_threads(nblk)), (size_t)l * l * sizeof(double), stream, R, ldr, l, Lp, w.W, w.sig, w.info,
+  if (l <= kRowsMaxL || nblk == 3) {
+    auto kern = nblk == 1 ? k_jacobi_rows<1, 8> : l <= 40 ? k_jacobi_rows<3, 24> : k_jacobi_rows<3, 32>;
+    const int threads = LPP * (nblk == 1 ? 8 : l <= 40 ? 24 : 32);
+    hipLaunchKernelGGL(kern, dim3(1), dim3(threads), (size_t)l * l * sizeof(double), stream, R, ldr, l, Lp, w.W, w.sig, w.info,
                        breakdown_flag, nblk == 1 ? kTolOneBlock : kTolRows, settled);
     BRSVD_HIP_TRY(hipGetLastError());
   } else if (l <= kJN) {

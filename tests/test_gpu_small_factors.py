@@ -84,20 +84,18 @@ def test_small_svd_at_the_ends_of_the_row_rotations(l):
         test_small_svd(l, cond)
 
 
-@pytest.mark.parametrize("l", [13, 16, 17, 24, 40, 41, 44, 66, 72, 79])
+@pytest.mark.parametrize("l", [13, 16, 17, 24, 33, 40, 41, 44, 48, 49, 66, 72, 79])
 def test_small_svd_where_rows_and_blocks_meet(l):
-    """Row rotations up to 16 and from 33 to 40 rows, block pairs otherwise; well-conditioned, nearly rank deficient, and with all
-    entries so small that the squares of squared norms are below the smallest double.  (Row rotations compare these squares with each other:
-    there, entries whose squares of squared norms are normal numbers, times 1e-32 as well.)"""
+    """Row rotations up to 16 and from 33 to 48 rows, block pairs otherwise; well-conditioned, nearly rank deficient, and with all
+    entries so small that the squares of squared norms are below the smallest double."""
     for cond in (1e2, 1e8):
         test_small_svd(l, cond)
-    e = 200 if l <= 16 or 33 <= l <= 40 else 440
     dev = need_gpu()
     g = torch.Generator().manual_seed(l)
     R = torch.linalg.qr(torch.randn(3 * l, l, generator=g, dtype=torch.float64))[1].contiguous()
-    S, U, V, _ = (x.cpu() if isinstance(x, torch.Tensor) else x for x in B.brsvd_small_svd((R * 2.0 ** -e).to(dev)))
     ref = torch.linalg.svdvals(R)
-    assert float((S * 2.0 ** e - ref).abs().max()) <= 40 * 2.0 ** -52 * np.sqrt(l) * float(ref[0])
+    S, U, V, _ = (x.cpu() if isinstance(x, torch.Tensor) else x for x in B.brsvd_small_svd((R * 2.0 ** -440).to(dev)))
+    assert float((S * 2.0 ** 440 - ref).abs().max()) <= 40 * 2.0 ** -52 * np.sqrt(l) * float(ref[0])
     assert float((V.T @ V - torch.eye(l, dtype=torch.float64)).abs().max()) <= 4e-13
 
 
