@@ -1,6 +1,6 @@
 """The l x l factors at the edges of their tiles and of the kernels' ranges: Cholesky factor and inverse behind the
 orthonormalisation (16 x 16 tiles, in LDS up to 128, in global memory above), and the Jacobi SVD (row blocks of 16; row
-rotations up to 16 and for 33 to 40 rows, one workgroup up to 32 rows, a workgroup per block pair otherwise)."""
+rotations up to 16 and for 33 to 48 rows, one workgroup up to 32 rows, a workgroup per block pair otherwise)."""
 import threading
 import time
 
