@@ -32,7 +32,7 @@ enum Cat { CAT_AN = 0, CAT_AT, CAT_ORTH, CAT_SVD, CAT_LIFT, CAT_COPY, CAT_ELEM, 
 
 struct Layout {
   // offsets into the arena
-  uint64_t Pm[2], Pn[2], gemm_scratch, gram_part, G, R0, R1, Rinv, Rtot, XV, XU, svdW, sig,
+  uint64_t Pm[2], Pn[2], gemm_scratch, gram_part, G, R0, R1, Rinv, Rtot, leftQ, Rx, XV, XU, svdW, sig,
       S32, flags, tsqr, stage[2], scal, rpcaU, rpcaVt, rpca_part, total;
   uint64_t gemm_scratch_bytes, tsqr_bytes, stage_bytes;
   int gram_chunks;
@@ -127,7 +127,8 @@ Layout make_layout(const brsvd_params& p, int64_t b) {
   L.gram_part = take((uint64_t)L.gram_chunks * Lp * Lp * 8);
   const uint64_t sq8 = (uint64_t)Lp * Lp * 8;
   L.G = take(sq8); L.R0 = take(sq8); L.R1 = take(sq8); L.Rtot = take(sq8);
-  take(2 * sq8);             // not used: the workspace keeps the size that callers' budgets were chosen for
+  L.leftQ = take(sq8);
+  L.Rx = take(sq8);
   const uint64_t sqe = (uint64_t)Lp * Lp * esz;
   L.Rinv = take(sqe); L.XV = take(sqe); L.XU = take(sqe);
   L.svdW = take(sq8);
@@ -255,6 +256,31 @@ OrthWorkT<T> orth_work(brsvd_handle h) {
   w.tsqr_work = h->arena + h->lay.tsqr;
   w.tsqr_bytes = h->lay.tsqr_bytes;
   return w;
+}
+
+// The end of both schemes.  C = W R1 is the thin QR of the last panel, taken of A (or A^T) times a basis Q left; so far Q and W are orthonormal only
+// together with their last factors (see Basis).  The factor of the whole is Rtot = R2 Rx with Rx = R1 left, Rtot = Ur diag(s) Vr^T, and the lifts
+// Q left Vr and W R2^-1 Ur = W Rx Vr diag(1/s) take the open factors in: XV = left Vr, XU = Rx Vr diag(1/s).
+template <typename T>
+int small_factors(brsvd_handle h, const Basis<T>& W, const T* left, const int* flags, T* S, hipStream_t cs) {
+  const int l = h->l, Lp = h->Lp;
+  SvdWork sw;
+  sw.W = h->at<double>(h->lay.svdW);
+  sw.sig = h->at<double>(h->lay.sig);
+  sw.info = h->at<int>(h->lay.flags) + 4;
+  double* Rx = h->at<double>(h->lay.Rx);
+  double* Rtot = h->at<double>(h->lay.Rtot);
+  OpenFactors<T> open{left, W.R1};
+  if (left) {
+    BRSVD_TRY(triu_mul(W.R1, left, l, Lp, Rx, cs));
+    open.Rx = Rx;
+  }
+  const double* R = open.Rx;
+  if (W.R2) {
+    BRSVD_TRY(triu_mul(W.R2, open.Rx, l, Lp, Rtot, cs));
+    R = Rtot;
+  }
+  return small_svd<T>(R, Lp, l, Lp, sw, flags, nullptr, S, h->at<T>(h->lay.XV), h->at<T>(h->lay.XU), nullptr, nullptr, cs, &open);
 }
 
 // ---- one pass over A ---------------------------------------------------------------------------
@@ -421,6 +447,9 @@ int enqueue_brsvd(brsvd_handle h, const T* A, int64_t lda, const T* Omega, T* U,
   T* Tn = h->Pn<T>(1);
   T* Ym = h->Pm<T>(0);    // current m x Lp panel
   T* Tm = h->Pm<T>(1);
+  T* leftQ = h->at<T>(h->lay.leftQ);
+  double* Rtot = h->at<double>(h->lay.Rtot);
+  Basis<T> Q{}, W{};      // of the last m x Lp panel and of B^T
   T* res;
 
   BRSVD_TRY(pad_panel(Omega, n, l, Xn, Lp, cs));
@@ -440,20 +469,26 @@ int enqueue_brsvd(brsvd_handle h, const T* A, int64_t lda, const T* Omega, T* U,
       // the factor R of Y = Q R is kept (in the buffer the thin QR of B^T overwrites below) for its diagonal:
       // the host reads min |R_ii| / max |R_ii| at the end of the run and decides whether B^T = C^T R^-1 can be
       // trusted in this precision
-      double* Ry = h->at<double>(h->lay.Rtot);
-      BRSVD_TRY(orth_panel<T>(Ym, Tm, m, l, Lp, method, true, ow, Ry, &res, cs));
-      BRSVD_TRY(diag_ratio(Ry, l, Lp, h->at<double>(h->lay.scal) + kScalFusedRatio, cs));
+      BRSVD_TRY(orth_panel<T>(Ym, Tm, m, l, Lp, method, true, ow, Rtot, &res, cs));
+      BRSVD_TRY(diag_ratio(Rtot, l, Lp, h->at<double>(h->lay.scal) + kScalFusedRatio, cs));
       if (res != Ym) std::swap(Ym, Tm);
       Xn = ow.comp; Tn = ow.comp_tmp;     // B^T and a free n x Lp buffer
       ow.comp = ow.comp_tmp = nullptr; ow.comp_rows = 0;
     }
   } else {
-    BRSVD_TRY(pass_an<T>(h, A, lda, Xn, Ym));
-    {
+    auto orth_m = [&](bool last) -> int {
       Region r(h, CAT_ORTH, cs, !h->host_a);
-      BRSVD_TRY(orth_panel<T>(Ym, Tm, m, l, Lp, method, q == 0, ow, nullptr, &res, cs));
+      if (last) {
+        BRSVD_TRY(orth_basis<T>(Ym, Tm, m, l, Lp, method, ow, leftQ, Rtot, false, &Q, cs));
+        res = Q.panel;
+      } else {
+        BRSVD_TRY(orth_panel<T>(Ym, Tm, m, l, Lp, method, false, ow, nullptr, &res, cs));
+      }
       if (res != Ym) std::swap(Ym, Tm);
-    }
+      return BRSVD_OK;
+    };
+    BRSVD_TRY(pass_an<T>(h, A, lda, Xn, Ym));
+    BRSVD_TRY(orth_m(q == 0));
     for (int it = 0; it < q; ++it) {
       BRSVD_TRY(pass_at<T>(h, A, lda, Ym, Xn, true));
       {
@@ -463,31 +498,22 @@ int enqueue_brsvd(brsvd_handle h, const T* A, int64_t lda, const T* Omega, T* U,
       }
       BRSVD_TRY(pass_an<T>(h, A, lda, Xn, Tm, true));
       std::swap(Ym, Tm);
-      {
-        Region r(h, CAT_ORTH, cs, !h->host_a);
-        BRSVD_TRY(orth_panel<T>(Ym, Tm, m, l, Lp, method, it == q - 1, ow, nullptr, &res, cs));
-        if (res != Ym) std::swap(Ym, Tm);
-      }
+      BRSVD_TRY(orth_m(it == q - 1));
     }
-    // projection B^T = A^T Q
+    // projection B^T = A^T Q, but for Q's last factor
     BRSVD_TRY(pass_at<T>(h, A, lda, Ym, Xn, true));
   }
   // thin QR of B^T, the small SVD, the lifts
-  double* Rtot = h->at<double>(h->lay.Rtot);
   {
     Region r(h, CAT_ORTH, cs, !h->host_a);
-    BRSVD_TRY(orth_panel<T>(Xn, Tn, n, l, Lp, method, true, ow, Rtot, &res, cs));
-    if (res != Xn) std::swap(Xn, Tn);
+    BRSVD_TRY(orth_basis<T>(Xn, Tn, n, l, Lp, method, ow, h->at<T>(h->lay.Rinv), Rtot, true, &W, cs));
+    if (W.panel != Xn) std::swap(Xn, Tn);
   }
-  SvdWork sw;
-  sw.W = h->at<double>(h->lay.svdW);
-  sw.sig = h->at<double>(h->lay.sig);
-  sw.info = h->at<int>(h->lay.flags) + 4;
   T* XV = h->at<T>(h->lay.XV);
   T* XU = h->at<T>(h->lay.XU);
   {
     Region r(h, CAT_SVD, cs, true);
-    BRSVD_TRY(small_svd<T>(Rtot, Lp, l, Lp, sw, ow.flags, nullptr, S, XV, XU, nullptr, nullptr, cs));
+    BRSVD_TRY(small_factors<T>(h, W, Q.left, ow.flags, S, cs));
   }
   {
     Region r(h, CAT_LIFT, cs, true);
@@ -521,7 +547,8 @@ int enqueue_alg2(brsvd_handle h, const T* A, int64_t lda, uint64_t seed, const T
   T* Pn1 = h->Pn<T>(1);
   T* OmI = h->Pm<T>(0);     // b x Lp windows of the two m x Lp panels
   T* TI = h->Pm<T>(1);
-  T* res;
+  double* Rtot = h->at<double>(h->lay.Rtot);
+  Basis<T> Q{}, W{};
 
   Streamer st(h, A, lda);
   for (int i = 0; i < h->nblocks; ++i) {
@@ -552,27 +579,22 @@ int enqueue_alg2(brsvd_handle h, const T* A, int64_t lda, uint64_t seed, const T
   }
   {
     Region r(h, CAT_ORTH, cs);
-    BRSVD_TRY(orth_panel<T>(Yn, Pn1, n, l, Lp, method, true, ow, nullptr, &res, cs));
-    if (res != Yn) std::swap(Yn, Pn1);
+    BRSVD_TRY(orth_basis<T>(Yn, Pn1, n, l, Lp, method, ow, h->at<T>(h->lay.leftQ), Rtot, false, &Q, cs));
+    if (Q.panel != Yn) std::swap(Yn, Pn1);
   }
   T* Cm = h->Pm<T>(0);
   T* Tm = h->Pm<T>(1);
   BRSVD_TRY(pass_an<T>(h, A, lda, Yn, Cm, false, true));                 // second sweep: C = A Q
-  double* Rtot = h->at<double>(h->lay.Rtot);
   {
     Region r(h, CAT_ORTH, cs);
-    BRSVD_TRY(orth_panel<T>(Cm, Tm, m, l, Lp, method, true, ow, Rtot, &res, cs));
-    if (res != Cm) std::swap(Cm, Tm);
+    BRSVD_TRY(orth_basis<T>(Cm, Tm, m, l, Lp, method, ow, h->at<T>(h->lay.Rinv), Rtot, true, &W, cs));
+    if (W.panel != Cm) std::swap(Cm, Tm);
   }
-  SvdWork sw;
-  sw.W = h->at<double>(h->lay.svdW);
-  sw.sig = h->at<double>(h->lay.sig);
-  sw.info = h->at<int>(h->lay.flags) + 4;
   T* XV = h->at<T>(h->lay.XV);
   T* XU = h->at<T>(h->lay.XU);
   {
     Region r(h, CAT_SVD, cs);
-    BRSVD_TRY(small_svd<T>(Rtot, Lp, l, Lp, sw, ow.flags, nullptr, S, XV, XU, nullptr, nullptr, cs));
+    BRSVD_TRY(small_factors<T>(h, W, Q.left, ow.flags, S, cs));
   }
   {
     Region r(h, CAT_LIFT, cs);

@@ -30,6 +30,21 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
     if (s__ != BRSVD_OK) return s__;    \
   } while (0)
 
+// Products of l x l factors: the waves of a workgroup that share the contraction of one 16 x 16 tile.  Adds their accumulators in wave order, the sum
+// is in wave 0, for which it returns true.
+constexpr int kTileWaves = 8;
+__device__ __forceinline__ bool sum_over_waves(doublex4& acc, double (*part)[256], int lane, int wave) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) part[wave][64 * v + lane] = acc[v];
+  __syncthreads();
+  if (wave != 0) return false;
+#pragma unroll
+  for (int w = 1; w < kTileWaves; ++w)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[v] += part[w][64 * v + lane];
+  return true;
+}
+
 // ---- thin-panel GEMMs (gemm_thin.hip) ------------------------------------------------------
 // Optional events for per-kernel timing of one call: stop directly behind the MFMA kernel launch(es), sum_stop behind the
 // split-sum kernels that follow (recorded even when there is nothing to sum).  The caller records the start.
@@ -189,6 +204,18 @@ uint64_t tsqr_work_bytes(int64_t rows, int Lp);
 template <typename T>
 int orth_panel(T* P, T* tmp, int64_t rows, int l, int Lp, int method, bool final_basis, OrthWorkT<T>& w,
                double* Rtot, T** result, hipStream_t stream);
+// The same for a basis that reaches the output, with the last l x l factor left to the caller: the orthonormal basis of P is panel * left (left
+// null: the panel itself), and with want_R P = panel * R1, left^-1 = R2 (null if left is).  left: room for an Lp x Lp factor; Rtot: for
+// an fp64 one, used with want_R only.
+template <typename T>
+struct Basis {
+  T* panel;
+  const T* left;
+  const double *R1, *R2;
+};
+template <typename T>
+int orth_basis(T* P, T* tmp, int64_t rows, int l, int Lp, int method, OrthWorkT<T>& w, T* left, double* Rtot, bool want_R, Basis<T>* out,
+               hipStream_t stream);
 // Pieces shared between the CholeskyQR and the Householder-tree routes (orth.hip, tsqr.hip).
 template <typename T>
 int cholqr_sweeps(T* P, T* tmp, int64_t rows, int l, int Lp, int nsweeps, OrthWorkT<T>& w, double* Rtot,
@@ -198,7 +225,9 @@ int chol_inv_factored(double* G, int l, int Lp, double* Rout, T* Rinv, int* flag
 template <typename T>
 int tsqr_panel(T* P, T* tmp, int64_t rows, int l, int Lp, OrthWorkT<T>& w, double* Rtot, T** result,
                hipStream_t stream);
-int triu_mul(const double* R2, const double* R1, int l, int Lp, double* Rtot, hipStream_t stream);
+// C = A B, upper triangular l x l factors (strides Lp)
+template <typename TB>
+int triu_mul(const double* A, const TB* B, int l, int Lp, double* C, hipStream_t stream);
 // *out (device) = min |R_ii| / max |R_ii| of the l x l triangular factor R (stride Lp)
 int diag_ratio(const double* R, int l, int Lp, double* out, hipStream_t stream);
 
@@ -228,9 +257,16 @@ __host__ __device__ inline int jacobi_work(const JacobiTicket& k, int last, int 
 // R (l x l fp64, stride ldr): R = Ur diag(S) Vr^T.  Writes S (descending) as fp64 and/or in the
 // panels' type TO, the zero-padded (Lp x Lp) operands XV = Vr and XU = Ur used by the lifts (type TO),
 // and optional dense fp64 l x l Ur / Vr.  Skips the work when *breakdown_flag != 0.
+// open: the lifts' panels are not orthonormal yet (see Basis): XV = left Vr (left null: Vr) and XU = Rx Vr / diag(S), Rx upper triangular with
+// stride ldr; there are no dense results then.
+template <typename TO>
+struct OpenFactors {
+  const TO* left;
+  const double* Rx;
+};
 template <typename TO>
 int small_svd(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* breakdown_flag,
-              double* S, TO* S32, TO* XV, TO* XU, double* Ur, double* Vr, hipStream_t stream);
+              double* S, TO* S32, TO* XV, TO* XU, double* Ur, double* Vr, hipStream_t stream, const OpenFactors<TO>* open = nullptr);
 
 // ---- robust-PCA elementwise kernels (rpca.hip) ---------------------------------------------
 // Number of doubles of partial-sum scratch the reductions below need.

@@ -343,16 +343,43 @@ k_chol_inv(double* __restrict__ G, int l, int Lp, double* __restrict__ Rout, TO*
   }
 }
 
-// Rtot = R2 * R1 (both upper triangular, l x l, stride Lp).
-__global__ void k_triu_mul(const double* __restrict__ R2, const double* __restrict__ R1, int l, int Lp,
-                           double* __restrict__ Rtot) {
-  int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= l * l) return;
-  int i = idx / l, c = idx - i * l;
-  double s = 0.0;
-#pragma unroll 8
-  for (int k = i; k <= c; ++k) s = fma(R2[(int64_t)i * Lp + k], R1[(int64_t)k * Lp + c], s);
-  Rtot[(int64_t)i * Lp + c] = s;
+// C = A B of upper triangular l x l factors (strides Lp), a workgroup per tile of 16 x 16; what lies below their diagonals is not looked at.
+// What bounds it: the latency of the loads, so eight waves share the contraction (v_mfma_f64_16x16x4_f64).  Measured (us with the launch,
+// one thread per entry before): l = 30 4.3 -> 2.8, 110 11.9 -> 5.1, 160 12.7 -> 6.0, 272 18.2 -> 5.6.
+template <typename TB>
+__global__ void __launch_bounds__(kTileWaves * 64)
+k_triu_mul(const double* __restrict__ A, const TB* __restrict__ B, int l, int Lp, double* __restrict__ C) {
+  __shared__ double part[kTileWaves][256];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
+  const int i0 = kNB * blockIdx.y, j0 = kNB * blockIdx.x, row = i0 + r, col = j0 + r;
+  doublex4 acc = {0.0, 0.0, 0.0, 0.0};
+  double an[4], bn[4];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = k0 + 4 * q + g;
+      const bool ina = row <= k && k < l && row < l, inb = k <= col && col < l;
+      an[q] = A[(int64_t)(ina ? row : 0) * Lp + (ina ? k : 0)];
+      bn[q] = (double)B[(int64_t)(inb ? k : 0) * Lp + (inb ? col : 0)];
+      if (!ina) an[q] = 0.0;
+      if (!inb) bn[q] = 0.0;
+    }
+  };
+  load(i0 + kNB * wave);
+  for (int k0 = i0 + kNB * wave; k0 <= j0; k0 += kTileWaves * kNB) {
+    double a[4], b[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) { a[q] = an[q]; b[q] = bn[q]; }
+    load(k0 + kTileWaves * kNB);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc = mfma_f64(a[q], b[q], acc);
+  }
+  if (!sum_over_waves(acc, part, lane, wave)) return;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int i = i0 + g + 4 * v;
+    if (i < l && col < l) C[(int64_t)i * Lp + col] = acc[v];
+  }
 }
 
 // Row chunks of the Gram kernel.  Up to 64 chunks of at least 64 rows fill the chip for panels of
@@ -564,13 +591,17 @@ int diag_ratio(const double* R, int l, int Lp, double* out, hipStream_t stream) 
   return BRSVD_OK;
 }
 
-int triu_mul(const double* R2, const double* R1, int l, int Lp, double* Rtot, hipStream_t stream) {
-  hipLaunchKernelGGL(k_triu_mul, dim3((unsigned)ceil_div((int64_t)l * l, 256)), dim3(256), 0, stream, R2, R1, l, Lp,
-                     Rtot);
+template <typename TB>
+int triu_mul(const double* A, const TB* B, int l, int Lp, double* C, hipStream_t stream) {
+  const unsigned nt = (unsigned)ceil_div(l, kNB);
+  hipLaunchKernelGGL(k_triu_mul<TB>, dim3(nt, nt), dim3(kTileWaves * 64), 0, stream, A, B, l, Lp, C);
   BRSVD_HIP_TRY(hipGetLastError());
   return BRSVD_OK;
 }
+template int triu_mul<float>(const double*, const float*, int, int, double*, hipStream_t);
+template int triu_mul<double>(const double*, const double*, int, int, double*, hipStream_t);
 
+constexpr double kPivotTol = 1e-12;
 // Only the last sweep of a basis that reaches the output must succeed without clamped pivots (its
 // input is then already nearly orthonormal, so a small pivot there means the panel really lost
 // rank to working precision).  Earlier sweeps, and the single sweep of an intermediate panel, clamp:
@@ -580,14 +611,13 @@ int triu_mul(const double* R2, const double* R1, int l, int Lp, double* Rtot, hi
 template <typename T>
 int cholqr_sweeps(T* P, T* tmp, int64_t rows, int l, int Lp, int nsweeps, OrthWorkT<T>& w, double* Rtot,
                   T** result, hipStream_t stream, bool strict_last, bool publish_R) {
-  const double tol = 1e-12;
   T* src = P;
   T* dst = tmp;
   for (int sweep = 0; sweep < nsweeps; ++sweep) {
     BRSVD_TRY(gram<T>(src, rows, Lp, w, stream));
     const int lenient = (sweep + 1 < nsweeps || !strict_last) ? 1 : 0;
     double* Rs = (Rtot || publish_R) ? w.R[sweep] : nullptr;      // the factor is only written out when someone reads it
-    BRSVD_TRY(chol_inv<T>(w.G, l, Lp, Rs, w.Rinv, w.flags, tol, stream, 0, lenient));
+    BRSVD_TRY(chol_inv<T>(w.G, l, Lp, Rs, w.Rinv, w.flags, kPivotTol, stream, 0, lenient));
     BRSVD_TRY(apply_panel(src, rows, Lp, w.Rinv, dst, Lp, Lp, w.gemm_scratch, w.gemm_scratch_bytes, stream));
     BRSVD_TRY(apply_to_companion<T>(w, Lp, stream));
     T* t = src; src = dst; dst = t;
@@ -614,12 +644,33 @@ int orth_panel(T* P, T* tmp, int64_t rows, int l, int Lp, int method, bool final
   return cholqr_sweeps<T>(P, tmp, rows, l, Lp, final_basis ? 2 : 1, w, Rtot, result, stream, final_basis);
 }
 
+// The second sweep of CholeskyQR, G2 = Q1^T Q1 = R2^T R2, without its pass over the panel Q2 = Q1 R2^-1: everything that follows is a product of Q1 with
+// an l x l factor or a product from the left that R2^-1 can be multiplied to afterwards.  R2 is close to the identity (where a pivot was clamped, to
+// a diagonal matrix times a well-conditioned one), so nothing is lost by taking R2^-1 to the other side.
+template <typename T>
+int orth_basis(T* P, T* tmp, int64_t rows, int l, int Lp, int method, OrthWorkT<T>& w, T* left, double* Rtot, bool want_R, Basis<T>* out,
+               hipStream_t stream) {
+  if (rows < l) return BRSVD_ERR_ARG;
+  if (method == BRSVD_ORTH_TSQR) {
+    *out = Basis<T>{nullptr, nullptr, want_R ? Rtot : nullptr, nullptr};
+    return tsqr_panel<T>(P, tmp, rows, l, Lp, w, want_R ? Rtot : nullptr, &out->panel, stream);
+  }
+  BRSVD_TRY(cholqr_sweeps<T>(P, tmp, rows, l, Lp, 1, w, nullptr, &out->panel, stream, false, want_R));
+  BRSVD_TRY(gram<T>(out->panel, rows, Lp, w, stream));
+  BRSVD_TRY(chol_inv<T>(w.G, l, Lp, want_R ? w.R[1] : nullptr, left, w.flags, kPivotTol, stream));
+  out->left = left;
+  out->R1 = want_R ? w.R[0] : nullptr;
+  out->R2 = want_R ? w.R[1] : nullptr;
+  return BRSVD_OK;
+}
+
 #define BRSVD_ORTH_INSTANTIATE(T)                                                                               \
   template int chol_inv_factored<T>(double*, int, int, double*, T*, int*, hipStream_t);                         \
   template int apply_to_companion<T>(OrthWorkT<T>&, int, hipStream_t);                                          \
   template int cholqr_sweeps<T>(T*, T*, int64_t, int, int, int, OrthWorkT<T>&, double*, T**, hipStream_t, bool, \
                                 bool);                                                                          \
-  template int orth_panel<T>(T*, T*, int64_t, int, int, int, bool, OrthWorkT<T>&, double*, T**, hipStream_t);
+  template int orth_panel<T>(T*, T*, int64_t, int, int, int, bool, OrthWorkT<T>&, double*, T**, hipStream_t);   \
+  template int orth_basis<T>(T*, T*, int64_t, int, int, int, OrthWorkT<T>&, T*, double*, bool, Basis<T>*, hipStream_t);
 BRSVD_ORTH_INSTANTIATE(float)
 BRSVD_ORTH_INSTANTIATE(double)
 #undef BRSVD_ORTH_INSTANTIATE

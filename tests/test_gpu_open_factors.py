@@ -1,0 +1,49 @@
+"""Output bases whose last l x l factor goes into the lifts instead of over the panel: brsvd_run against the fp64 oracle at the edges of the 16 x 16
+tiles of the small factors, on matrices of full numerical rank (second factor near the identity) and of rank k < l (second factor far from it)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1706_07191_amd as B
+from oracle import brsvd_oracle as O
+from tests.gpu_util import check_against_oracle, need_gpu, note
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("k,p,q", [(1, 0, 0), (6, 10, 1), (7, 10, 0), (22, 10, 2), (23, 10, 1), (119, 9, 1), (119, 10, 1), (247, 10, 0)])
+@pytest.mark.parametrize("full", [True, False])
+def test_open_bases(k, p, q, f64, full):
+    dev = need_gpu()
+    m, n, l = 900, 777, k + p
+    print(f"[case] open bases k={k} p={p} q={q} f64={f64} full={full}", flush=True)
+    g = torch.Generator().manual_seed(1000 * k + 10 * q + full)
+    w = torch.exp(-torch.arange(k, dtype=torch.float64) * (np.log(30.0) / k))
+    A = (torch.randn(m, k, generator=g, dtype=torch.float64) * w) @ torch.randn(k, n, generator=g, dtype=torch.float64)
+    if full:
+        A = A + 1e-2 * torch.randn(m, n, generator=g, dtype=torch.float64)
+    Om = torch.randn(n, l, generator=g, dtype=torch.float64)
+    if not f64:
+        A, Om = A.float(), Om.float()
+    h = B.brsvd_create(B.make_params(m, n, k, p, q, dtype=B.BRSVD_DTYPE_F64 if f64 else B.BRSVD_DTYPE_F32))
+    try:
+        U, S, Vt, _ = B.brsvd_run(h, A.to(dev), Om.to(dev))
+        torch.cuda.synchronize()
+    finally:
+        B.brsvd_destroy(h)
+    if full and not f64:
+        check_against_oracle(A.numpy(), Om.numpy(), k, p, q, m, U, S, Vt, f"open l={l}")
+        return
+    # (rank k: the vectors of the zero singular values are noise, of U only orthogonal as far as the Gram matrix of noise is accurate)
+    Uo, so, Vto = O.brsvd(A.numpy(), Om.numpy(), k, p, q, row_block=m)
+    U, S, Vt = U.double().cpu().numpy(), S.double().cpu().numpy(), Vt.double().cpu().numpy()
+    eps = 2.0 ** -53 if f64 else 2.0 ** -24
+    f = {"sigma": float(np.max(np.abs(S[:k] - so[:k]) / so[:k])), "orthU": O.orth_defect(U[:, :k]), "orthV": O.orth_defect(Vt[:k].T),
+         "err": O.recon_error(A.numpy(), U, S, Vt, k=k), "err_oracle": O.recon_error(A.numpy(), Uo, so, Vto, k=k)}
+    note(f"[open l={l} f64={f64} full={full}] " + " ".join(f"{a}={b:.2e}" for a, b in f.items()))
+    # The condition of the sketch is below 30 * 8 sqrt(k) on k directions; the products, the factors and the lifts lose 10 sqrt(l) eps each times
+    # that, and the small SVD stops at cosines of 1e-8 squared, against sigma_1 / sigma_k < 100.
+    tol = max(240 * np.sqrt(k) * 10 * np.sqrt(l) * eps, 1e-14)
+    assert f["sigma"] <= tol and f["orthU"] <= tol and f["orthV"] <= max(tol, 1e-13), (f, tol)
+    assert abs(f["err"] - f["err_oracle"]) <= tol, (f, tol)
