@@ -116,6 +116,10 @@ k_gram(const T* __restrict__ P, int64_t rows, int Lp, int64_t rows_per_chunk, do
 // 128 87.4 -> 38.9, 160 151 -> 65, 272 383 -> 208, 400 895 -> 562.
 // A pivot <= tol * its original diagonal entry is clamped to that value (lenient) or sets
 // flag[0] = 1 + column of its tile and ends the kernel.
+// A matrix close to the identity, as in the second sweep of CholeskyQR and after a Householder tree, needs no elimination: for G = I + E the factor is
+// R = I + N, N the strict upper triangle and half the diagonal of E, and R^-1 = I - N, both to the order of |E|_F^2.  Taken where |E|_F is at most
+// `near_eye`; the panels' precision sets it (near_eye_of).  Measured, elimination and this (us with the
+// launch): l = 20 9.4 and 4.1, 72 22 and 6.4, 97 29 and 8, 110 31 and 10, 160 63 and 15, 272 225 and 43.
 constexpr int kNB = 16;
 constexpr int kCholLdsMaxLp = 128;    // largest padded size whose fp64 matrix fits the LDS
 
@@ -204,9 +208,10 @@ __device__ __forceinline__ bool chol_diag_wave(doublex4& D, doublex4& E, const d
 template <bool IN_LDS, bool FACTORED, typename TO>
 __global__ void __launch_bounds__(1024)
 k_chol_inv(double* __restrict__ G, int l, int Lp, double* __restrict__ Rout, TO* __restrict__ Rinv_out,
-           int* __restrict__ flag, double tol, int lenient) {
+           int* __restrict__ flag, double tol, int lenient, double near_eye) {
   extern __shared__ double smem[];
   __shared__ int bad;
+  __shared__ double off_eye[16];
   const int ldp = chol_ldp(Lp), ld = IN_LDS ? chol_ldm(Lp) : Lp;
   double* e = smem;                                // 16 x 17: E_kk
   double* d0 = e + kNB * (kNB + 1);                // Lp: original diagonal
@@ -219,6 +224,7 @@ k_chol_inv(double* __restrict__ G, int l, int Lp, double* __restrict__ Rout, TO*
 
   // The matrix is padded to Lp x Lp with an identity block; R^-1 is zero below its diagonal tiles and in the padding.
   for (int idx = tid; idx < Lp * Lp; idx += blockDim.x) Rinv_out[idx] = TO(0);
+  double e2 = 0.0;                    // |G - I|_F^2
   for (int t = wave; t < nb * (nb + 1) / 2; t += nw) {
     int ti = 0, rem = t;
     while (rem >= nb - ti) { rem -= nb - ti; ++ti; }
@@ -230,12 +236,32 @@ k_chol_inv(double* __restrict__ G, int l, int Lp, double* __restrict__ Rout, TO*
       const bool in = row < l && col < l;
       v[q] = G[(int64_t)(in ? row : 0) * Lp + (in ? col : 0)];
       if (!in) v[q] = row == col ? 1.0 : 0.0;
+      const double e = v[q] - (row == col ? 1.0 : 0.0);
+      e2 = fma(ti == tj ? e : 2.0 * e, e, e2);
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int row = kNB * ti + g + 4 * q;
       if (IN_LDS || row >= l || col >= l) M[(int64_t)row * ld + col] = v[q];
       if (row == col) d0[row] = v[q];
+    }
+  }
+  if (!FACTORED && near_eye > 0.0) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) e2 += __shfl_xor(e2, off, 64);
+    if (lane == 0) off_eye[wave] = e2;
+    __syncthreads();
+    e2 = 0.0;
+    for (int w = 0; w < nw; ++w) e2 += off_eye[w];
+    if (e2 <= near_eye * near_eye) {  // (not when it is NaN)
+#pragma unroll 8
+      for (int idx = tid; idx < l * l; idx += blockDim.x) {
+        const int i = idx / l, j = idx - i * l;
+        const double d = i == j ? 1.0 : 0.0, n = i > j ? 0.0 : M[(int64_t)i * ld + j] - d, half = i == j ? 0.5 * n : n;
+        if (Rout) Rout[(int64_t)i * Lp + j] = d + half;
+        if (i <= j) Rinv_out[(int64_t)i * Lp + j] = (TO)(d - half);
+      }
+      return;
     }
   }
   // the diagonal tile of step k (wave 0), its factor stored, E_kk left for the panel
@@ -451,7 +477,7 @@ static int gram(const T* P, int64_t rows, int Lp, OrthWorkT<T>& w, hipStream_t s
 // otherwise such a pivot raises the breakdown flag and ends the kernel.
 template <typename TO>
 static int chol_inv(double* G, int l, int Lp, double* Rout, TO* Rinv, int* flags, double tol, hipStream_t stream,
-                    int factored = 0, int lenient = 0) {
+                    int factored = 0, int lenient = 0, double near_eye = 0.0) {
   const bool in_lds = Lp <= kCholLdsMaxLp;
   const size_t lds = chol_lds_bytes(Lp, in_lds);
   // a step has at most one panel tile per wave up to 16 column tiles; two tiles leave work for four waves only
@@ -461,7 +487,7 @@ static int chol_inv(double* G, int l, int Lp, double* Rout, TO* Rinv, int* flags
       BRSVD_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds));
       *attr_set = true;
     }
-    hipLaunchKernelGGL(kern, dim3(1), dim3(threads), lds, stream, G, l, Lp, Rout, Rinv, flags, tol, lenient);
+    hipLaunchKernelGGL(kern, dim3(1), dim3(threads), lds, stream, G, l, Lp, Rout, Rinv, flags, tol, lenient, near_eye);
     BRSVD_HIP_TRY(hipGetLastError());
     return BRSVD_OK;
   };
@@ -602,6 +628,9 @@ template int triu_mul<float>(const double*, const float*, int, int, double*, hip
 template int triu_mul<double>(const double*, const double*, int, int, double*, hipStream_t);
 
 constexpr double kPivotTol = 1e-12;
+// |G - I|_F up to which the factor of G is taken to first order: its square, by which factor and inverse are off at most, is a sixth of the rounding of the panels
+// (1e-8 of 6e-8, and 1.6e-17 of 1.1e-16).
+template <typename T> constexpr double near_eye_of() { return sizeof(T) == 4 ? 1e-4 : 4e-9; }
 // Only the last sweep of a basis that reaches the output must succeed without clamped pivots (its
 // input is then already nearly orthonormal, so a small pivot there means the panel really lost
 // rank to working precision).  Earlier sweeps, and the single sweep of an intermediate panel, clamp:
@@ -617,7 +646,7 @@ int cholqr_sweeps(T* P, T* tmp, int64_t rows, int l, int Lp, int nsweeps, OrthWo
     BRSVD_TRY(gram<T>(src, rows, Lp, w, stream));
     const int lenient = (sweep + 1 < nsweeps || !strict_last) ? 1 : 0;
     double* Rs = (Rtot || publish_R) ? w.R[sweep] : nullptr;      // the factor is only written out when someone reads it
-    BRSVD_TRY(chol_inv<T>(w.G, l, Lp, Rs, w.Rinv, w.flags, kPivotTol, stream, 0, lenient));
+    BRSVD_TRY(chol_inv<T>(w.G, l, Lp, Rs, w.Rinv, w.flags, kPivotTol, stream, 0, lenient, lenient ? 0.0 : near_eye_of<T>()));
     BRSVD_TRY(apply_panel(src, rows, Lp, w.Rinv, dst, Lp, Lp, w.gemm_scratch, w.gemm_scratch_bytes, stream));
     BRSVD_TRY(apply_to_companion<T>(w, Lp, stream));
     T* t = src; src = dst; dst = t;
@@ -657,7 +686,7 @@ int orth_basis(T* P, T* tmp, int64_t rows, int l, int Lp, int method, OrthWorkT<
   }
   BRSVD_TRY(cholqr_sweeps<T>(P, tmp, rows, l, Lp, 1, w, nullptr, &out->panel, stream, false, want_R));
   BRSVD_TRY(gram<T>(out->panel, rows, Lp, w, stream));
-  BRSVD_TRY(chol_inv<T>(w.G, l, Lp, want_R ? w.R[1] : nullptr, left, w.flags, kPivotTol, stream));
+  BRSVD_TRY(chol_inv<T>(w.G, l, Lp, want_R ? w.R[1] : nullptr, left, w.flags, kPivotTol, stream, 0, 0, near_eye_of<T>()));
   out->left = left;
   out->R1 = want_R ? w.R[0] : nullptr;
   out->R2 = want_R ? w.R[1] : nullptr;

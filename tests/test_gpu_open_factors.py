@@ -47,3 +47,28 @@ def test_open_bases(k, p, q, f64, full):
     tol = max(240 * np.sqrt(k) * 10 * np.sqrt(l) * eps, 1e-14)
     assert f["sigma"] <= tol and f["orthU"] <= tol and f["orthV"] <= max(tol, 1e-13), (f, tol)
     assert abs(f["err"] - f["err_oracle"]) <= tol, (f, tol)
+
+
+@pytest.mark.parametrize("l", [15, 16, 17, 128, 129])
+@pytest.mark.parametrize("spread", [1.0, 1e3])
+def test_second_factor_on_both_sides_of_the_line(l, spread):
+    """brsvd_orth: with columns of equal weight the second factor is next to the identity and taken to first order; a spread of 1e3 and parallel
+    columns take it past the line for some of the sizes.  Q must be orthonormal and P = Q R either way."""
+    dev = need_gpu()
+    m = 3000
+    print(f"[case] second factor l={l} spread={spread}", flush=True)
+    g = torch.Generator().manual_seed(7 * l)
+    w = torch.exp(-torch.arange(l, dtype=torch.float64) * (np.log(spread) / l))
+    P = (torch.randn(m, l, generator=g, dtype=torch.float64) * w) @ torch.linalg.qr(torch.randn(l, l, generator=g, dtype=torch.float64))[0]
+    if spread > 1:
+        P = P + 30 * torch.randn(m, 1, generator=g, dtype=torch.float64)
+    P = P.float()
+    Q, R, fallback = B.brsvd_orth(P.to(dev).clone(), want_R=True)
+    Q, R = Q.double().cpu(), R.cpu()
+    eps = 2.0 ** -24
+    defect = float(torch.linalg.norm(Q.T @ Q - torch.eye(l, dtype=torch.float64), 2))
+    back = float(torch.linalg.norm(Q @ R - P.double()) / torch.linalg.norm(P.double()))
+    note(f"[second factor l={l} spread={spread}] defect={defect:.2e} back={back:.2e}")
+    # Q's entries are rounded to eps each and its last product sums l terms; the first-order factor leaves 1e-8 at most.
+    assert not fallback and defect <= 4 * np.sqrt(l) * eps + 1e-8 and back <= 8 * np.sqrt(l) * eps, (defect, back)
+    assert bool((torch.tril(R, -1) == 0).all()) and bool((torch.diagonal(R) > 0).all())
