@@ -113,7 +113,7 @@ k_gram(const T* __restrict__ P, int64_t rows, int Lp, int64_t rows_per_chunk, do
 // Newton steps, the scale of the row) up to l of 128, where M is in LDS; above that M stays in global memory (L2) and the
 // tile updates, 2 l^3 / 3 flops on one CU, take over.  Measured (us with the launch; before: the factorisation with
 // row-wise panel solves, then a recursive inversion): l = 20 19.8 -> 11.3, 60 38.0 -> 20.2, 110 73.7 -> 33.1,
-// 128 87.4 -> 38.9, 160 151 -> 65, 272 383 -> 208, 400 895 -> 562.
+// 128 87.4 -> 38.9, 160 151 -> 65, 272 383 -> 208, 400 895 -> 562.  Since then padding needs no pivots: l = 20 9.4 -> 8.3.
 // A pivot <= tol * its original diagonal entry is clamped to that value (lenient) or sets
 // flag[0] = 1 + column of its tile and ends the kernel.
 // A matrix close to the identity, as in the second sweep of CholeskyQR and after a Householder tree, needs no elimination: for G = I + E the factor is
@@ -159,10 +159,10 @@ __device__ __forceinline__ double rcp_fast(double x) {
 //   D -= (row_j / d_j)^T row_j,  E -= (row_j / d_j)^T E_j   (first operand masked to the rows below j),
 // with no value moved between lanes.  The next pivot is taken from the old tile, d_(j+1) = D_(j+1,j+1) -
 // D_(j,j+1)^2 / d_j, so its reciprocal is worked out while the instruction runs.  Rows are scaled by 1/sqrt(d)
-// at the end: D = R_kk, E = R_kk^-T.  FACTORED: D is already R_kk.  d0: original diagonal of the tile.  Returns false if
+// at the end: D = R_kk, E = R_kk^-T.  cnt: rows of the tile that are not padding (those are rows of the identity and need no pivots).  FACTORED: D is already R_kk.  d0: original diagonal of the tile.  Returns false if
 // a pivot had to be clamped.
 template <bool FACTORED>
-__device__ __forceinline__ bool chol_diag_wave(doublex4& D, doublex4& E, const double* d0, double tol, int lane) {
+__device__ __forceinline__ bool chol_diag_wave(doublex4& D, doublex4& E, const double* d0, double tol, int lane, int cnt) {
   const int r = lane & 15, g = lane >> 4;
   const double floors = tol * d0[r];
   doublex4 ds;
@@ -181,6 +181,7 @@ __device__ __forceinline__ bool chol_diag_wave(doublex4& D, doublex4& E, const d
   for (int j = 0; j < kNB; ++j) {
     const bool mine = g == (j & 3);
     ds[j >> 2] = mine ? d : ds[j >> 2];
+    if (j + 1 >= cnt) break;
     if (j + 1 < kNB) {
       const double x = shfl_d(D[j >> 2], 16 * (j & 3) + j + 1), dn = shfl_d(D[(j + 1) >> 2], 16 * ((j + 1) & 3) + j + 1);
       const double a = mine && r > j ? D[j >> 2] * -inv : 0.0;
@@ -267,7 +268,7 @@ k_chol_inv(double* __restrict__ G, int l, int Lp, double* __restrict__ Rout, TO*
   // the diagonal tile of step k (wave 0), its factor stored, E_kk left for the panel
   auto diagonal = [&](int k, doublex4 D) {
     doublex4 E;
-    const bool ok = chol_diag_wave<FACTORED>(D, E, d0 + kNB * k, tol, lane);
+    const bool ok = chol_diag_wave<FACTORED>(D, E, d0 + kNB * k, tol, lane, min(kNB, l - kNB * k));
     if (!ok && !lenient && lane == 0) bad = kNB * k + 1;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
