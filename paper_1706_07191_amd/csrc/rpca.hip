@@ -23,18 +23,39 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
   return s;   // valid in thread 0
 }
 
-// part[2*b] = max |M| over the block's slice, part[2*b+1] = sum M^2.
+// part[2*b] = max |M| over the block's slice, part[2*b+1] = sum M^2.  Bound by the read of M: vectors of 16 bytes, four of them under way per thread, and
+// single elements up to M's first whole vector and behind its last.  Measured (us, one element at a time before):
+// 76800x2000 fp32 270 -> 94 (6.6 TB/s), 2073600x100 365 -> 127, 32256x2383 fp64 152 -> 93.
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_rpca_norms(const T* __restrict__ M, int64_t count, double* __restrict__ part) {
+  constexpr int V = 16 / sizeof(T), AH = 4;
+  typedef T vec __attribute__((ext_vector_type(V)));
   __shared__ double sh[4];
   __shared__ double shm[4];
   double mx = 0.0, ss = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (int64_t)gridDim.x * 256) {
-    const double v = (double)M[i];
+  auto take = [&](T x) {
+    const double v = (double)x;
     mx = fmax(mx, fabs(v));
     ss = fma(v, v, ss);
+  };
+  const int64_t head = min((int64_t)((16 - (uintptr_t)M % 16) % 16 / sizeof(T)), count), vecs = (count - head) / V;
+  const vec* Mv = (const vec*)(M + head);
+  const int64_t t0 = (int64_t)blockIdx.x * 256 + threadIdx.x, stride = (int64_t)gridDim.x * 256;
+  for (int64_t i = t0; i < vecs; i += AH * stride) {
+    vec v[AH];
+#pragma unroll
+    for (int a = 0; a < AH; ++a) v[a] = __builtin_nontemporal_load(Mv + min(i + a * stride, vecs - 1));
+#pragma unroll
+    for (int a = 0; a < AH; ++a)
+      if (i + a * stride < vecs) {
+#pragma unroll
+        for (int c = 0; c < V; ++c) take(v[a][c]);
+      }
   }
+  if (t0 < head) take(M[t0]);
+  const int64_t tail = head + vecs * V + t0;
+  if (tail < count) take(M[tail]);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));

@@ -328,3 +328,33 @@ def test_norm2_power_at_the_ends_of_the_range(n, square):
     want = O.norm2_power((A * scale).double().cpu().numpy(), xh, 4)
     # as above; entries of A^T A x may be subnormal, i.e. half of 2^-149 off each, and so may the partial sums of up to m / 16 workgroups
     assert abs(got - want) <= (16 * np.sqrt(m + n) * 2.0 ** -23 + 4 * 2.0 ** -150 * np.sqrt(n) * (1 + m / 16) / square) * want
+
+
+@pytest.mark.parametrize("dtype,off", [(torch.float32, 0), (torch.float32, 1), (torch.float32, 2), (torch.float32, 3), (torch.float64, 1)])
+@pytest.mark.parametrize("m,n", [(37, 29), (5, 3), (700, 641)])
+def test_norms_at_every_alignment(dtype, off, m, n):
+    """The norms before the first iteration are read in vectors: M at every offset from 16 bytes, with ends that are no whole vector.  The largest entry
+    decides the first multiplier, the Frobenius norm the residuals."""
+    dev = need_gpu()
+    print(f"[case] norms {dtype} +{off} {m}x{n}", flush=True)
+    g = torch.Generator().manual_seed(off + m)
+    M = torch.randn(m, n, generator=g, dtype=dtype)
+    for big in (0, m * n // 2, m * n - 1):
+        Mb = M.clone()
+        Mb.view(-1)[big] = 40.0
+        buf = torch.empty(m * n + off, dtype=dtype, device=dev)[off:].reshape(m, n)
+        buf.copy_(Mb)
+        Om = torch.randn(1, n, 2, generator=torch.Generator().manual_seed(3), dtype=dtype)
+        h = B.brsvd_create(B.make_params(m, n, 1, 1, 1, dtype=B.BRSVD_DTYPE_F64 if dtype == torch.float64 else B.BRSVD_DTYPE_F32))
+        try:
+            lam, n2 = 1.0 / np.sqrt(max(m, n)), 1.0            # the largest entry over lambda is above n2
+            L, S, res, _, _ = B.brsvd_rpca_ialm_tol(h, buf, Om.to(dev), 1, 0.0, lam, 0.7, 1.5, norm2_M=n2)
+        finally:
+            B.brsvd_destroy(h)
+        Md, L, S = Mb.double(), L.double().cpu(), S.double().cpu()
+        want = float(torch.linalg.norm(Md - L - S) / torch.linalg.norm(Md))
+        eps = 2.0 ** -53 if dtype == torch.float64 else 2.0 ** -24
+        assert abs(res[0] - want) <= 16 * eps * (1.0 + want), (res, want)
+        x = Md - L + Md / (float(Mb.abs().max()) / lam) / 0.7   # S = shrink(M - L + Y0 / mu0, lambda / mu0), Y0 = M / J
+        t = lam / 0.7
+        assert float((S - (x - x.clamp(-t, t))).abs().max()) <= 16 * eps * 60.0
