@@ -1341,24 +1341,29 @@ int brsvd_orth(float* P, int64_t rows, int32_t l, int32_t method, double* R, int
     w.gram_part = (double*)take((uint64_t)o.chunks * o.sq8);
     w.gram_chunks_max = o.chunks;
     w.G = (double*)take(o.sq8); w.R[0] = (double*)take(o.sq8); w.R[1] = (double*)take(o.sq8);
-    take(o.sq8);             // not used: the scratch keeps the size that callers have planned
+    float* left = (float*)take(o.sq8);
     double* Rtot = (double*)take(o.sq8);
     w.Rinv = (float*)take(o.sq4);
     w.flags = (int*)take(256);
     w.gemm_scratch = take(o.gs); w.gemm_scratch_bytes = o.gs;
     w.tsqr_work = take(o.tb); w.tsqr_bytes = o.tb;
-    if (hipMemsetAsync(buf, 0, o.total, s) != hipSuccess) { status = BRSVD_ERR_HIP; break; }
     int m_now = method;
     for (int attempt = 0; attempt < 2; ++attempt) {
-      float* res = nullptr;
-      if ((status = pad_panel(P, rows, l, P0, Lp, s)) != BRSVD_OK) break;
+      // P is left alone until it is known that there is a result: the sweeps go from P to P1 and stop short of the last product.  A panel whose rows are
+      // whole tiles, on 16 bytes, is taken as it is.
+      const bool as_is = m_now != BRSVD_ORTH_TSQR && l == Lp && (uintptr_t)P % 16 == 0;
+      Basis<float> Q{};
+      if (!as_is && (status = pad_panel(P, rows, l, P0, Lp, s)) != BRSVD_OK) break;
       if (hipMemsetAsync(w.flags, 0, 256, s) != hipSuccess) { status = BRSVD_ERR_HIP; break; }
-      if ((status = orth_panel(P0, P1, rows, l, Lp, m_now, true, w, Rtot, &res, s)) != BRSVD_OK) break;
+      if ((status = orth_basis(as_is ? P : P0, P1, rows, l, Lp, m_now, w, left, Rtot, true, &Q, s)) != BRSVD_OK) break;
+      if (Q.R2 && R && (status = triu_mul(Q.R2, Q.R1, l, Lp, Rtot, s)) != BRSVD_OK) break;
       int flag = 0;
       if (hipMemcpyAsync(&flag, w.flags, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess ||
           hipStreamSynchronize(s) != hipSuccess) { status = BRSVD_ERR_HIP; break; }
       if (flag == 0) {
-        if ((status = unpad_panel(res, rows, Lp, l, P, false, s)) != BRSVD_OK) break;
+        if (Q.left) status = apply_panel(Q.panel, rows, Lp, Q.left, P, l, l, w.gemm_scratch, w.gemm_scratch_bytes, s);
+        else status = unpad_panel(Q.panel, rows, Lp, l, P, false, s);
+        if (status != BRSVD_OK) break;
         if (R) {
           if (hipMemcpy2DAsync(R, (size_t)l * 8, Rtot, (size_t)Lp * 8, (size_t)l * 8, (size_t)l,
                                hipMemcpyDeviceToDevice, s) != hipSuccess) { status = BRSVD_ERR_HIP; break; }

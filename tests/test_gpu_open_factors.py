@@ -72,3 +72,20 @@ def test_second_factor_on_both_sides_of_the_line(l, spread):
     # Q's entries are rounded to eps each and its last product sums l terms; the first-order factor leaves 1e-8 at most.
     assert not fallback and defect <= 4 * np.sqrt(l) * eps + 1e-8 and back <= 8 * np.sqrt(l) * eps, (defect, back)
     assert bool((torch.tril(R, -1) == 0).all()) and bool((torch.diagonal(R) > 0).all())
+
+
+@pytest.mark.parametrize("rows,l", [(64, 16), (1001, 32), (3001, 64), (2000, 144)])
+def test_orth_of_a_panel_taken_as_it_is(rows, l):
+    """A panel of whole tiles on 16 bytes is not copied first: the same bits as one that is, because it starts elsewhere."""
+    dev = need_gpu()
+    print(f"[case] orth as it is {rows} x {l}", flush=True)
+    P = torch.randn(rows, l, generator=torch.Generator().manual_seed(rows), dtype=torch.float32).to(dev)
+    off = torch.empty(rows * l + 1, dtype=torch.float32, device=dev)[1:].reshape(rows, l)
+    off.copy_(P)
+    assert off.data_ptr() % 16 != 0
+    Q, R, _ = B.brsvd_orth(P.clone(), want_R=True)
+    Qo, Ro, _ = B.brsvd_orth(off, want_R=True)
+    assert torch.equal(Q, Qo) and torch.equal(R, Ro)
+    Qn, _, _ = B.brsvd_orth(P.clone())
+    assert torch.equal(Q, Qn)
+    assert O.orth_defect(Q.double().cpu().numpy()) <= 4 * np.sqrt(l) * 2.0 ** -24 + 1e-8
