@@ -21,7 +21,7 @@ namespace brsvd {
 // each tile of the two blocks: that value is at once the A operand (entry [i = r][k = g] of the
 // transposed tile) and the B operand ([k = g][j = r]), so the panel goes from global memory straight
 // into the MFMA operands.  The eight waves of a workgroup take the steps of the chunk round-robin and
-// add their accumulators through LDS in wave order; chunks are added by the caller in chunk order.
+// add their accumulators through LDS in wave order; the chunks are added by k_gram_sum.
 // Accumulator layout of the instruction: component v of lane (r, g) is entry [g + 4*v][r].
 constexpr int kGramWaves = 8;
 constexpr int kGramRowStep = 4 * kGramWaves;
@@ -411,8 +411,7 @@ k_triu_mul(const double* __restrict__ A, const TB* __restrict__ B, int l, int Lp
 
 // Row chunks of the Gram kernel.  Up to 64 chunks of at least 64 rows fill the chip for panels of
 // ordinary height; very tall panels get one chunk per 1024 rows, bounded by about 2048 workgroups
-// per launch and 64 MB of partial sums.  The partial sums are added in chunk order (in two levels
-// of at most kGramFan terms when there are more than kGramFan chunks), so the result is deterministic.
+// per launch and 64 MB of partial sums.
 constexpr int kGramFan = 64;
 uint64_t orth_gram_chunks(int64_t rows, int Lp) {
   const int nbk = (Lp + 63) / 64, pairs = nbk * (nbk + 1) / 2;
@@ -422,22 +421,36 @@ uint64_t orth_gram_chunks(int64_t rows, int Lp) {
   const int64_t tall = std::min<int64_t>(rows / 1024, cap);
   return (uint64_t)std::max<int64_t>(std::max(c, tall), 1);
 }
-// Slots of Lp x Lp doubles the partial sums need (chunks, plus the first-level sums).
+// Slots of Lp x Lp doubles of the workspace (of the partial sums, and some that are not used: the workspace keeps the size that callers' budgets
+// were chosen for).
 uint64_t orth_gram_slots(int64_t rows, int Lp) {
   const uint64_t c = orth_gram_chunks(rows, Lp);
   return c > (uint64_t)kGramFan ? c + ceil_div(c, kGramFan) : c;
 }
 
-// out[g] = sum of the slots [g*fan, min((g+1)*fan, nsplit)) of part, in slot order.
-__global__ void k_reduce_groups(const double* __restrict__ part, int nsplit, int fan, int64_t count,
-                                double* __restrict__ out) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= count) return;
-  const int s0 = blockIdx.y * fan, s1 = min(nsplit, s0 + fan);
+// G = the sum of the chunks' parts.  A workgroup takes 32 entries of the upper tiles; each is added up by 32 threads, thread s the chunks s, s + 32, ...
+// in order, and then their sums in order: the result does not depend on timing.
+// What bounds it: the latency of the loads, which come from all dies.  One thread per entry, over all entries, in two launches from 65 (small factors:
+// 257) chunks on, and this (us): l = 30 3.1 and 2.6, 72 7.3 and 4.8, 110 9.1 and 4.8, 160 10.5 and 5.1, 272 14.4 and 11.0; 76800x32 (75 chunks) 6.1 and 4.6,
+// 2073600x32 (2025) 11.2 and 11.6.
+__global__ void __launch_bounds__(1024)
+k_gram_sum(const double* __restrict__ part, int chunks, int Lp, double* __restrict__ G) {
+  __shared__ double sums[32][33];
+  const int e = threadIdx.x & 31, slice = threadIdx.x >> 5, NT = Lp / 16;
+  int i = 0, j = (int)(blockIdx.x >> 3);           // eight workgroups per tile
+  while (j >= NT - i) { j -= NT - i; ++i; }
+  j += i;
+  const int in_tile = (int)(blockIdx.x & 7) * 32 + e, row = 16 * i + (in_tile >> 4), col = 16 * j + (in_tile & 15);
+  const double* p = part + (int64_t)row * Lp + col;
   double s = 0.0;
-#pragma unroll 8
-  for (int i = s0; i < s1; ++i) s += part[(int64_t)i * count + idx];
-  out[(int64_t)blockIdx.y * count + idx] = s;
+#pragma unroll 16
+  for (int c = slice; c < chunks; c += 32) s += p[(int64_t)c * Lp * Lp];
+  sums[slice][e] = s;
+  __syncthreads();
+  if (slice != 0) return;
+#pragma unroll
+  for (int k = 1; k < 32; ++k) s += sums[k][e];
+  G[(int64_t)row * Lp + col] = s;
 }
 
 template <typename T>
@@ -456,20 +469,7 @@ static int gram(const T* P, int64_t rows, int Lp, OrthWorkT<T>& w, hipStream_t s
     default: hipLaunchKernelGGL((k_gram<T, 4>), grid, block, 0, stream, P, rows, Lp, rpc, w.gram_part); break;
   }
   BRSVD_HIP_TRY(hipGetLastError());
-  const int64_t count = (int64_t)Lp * Lp;
-  const unsigned bx = (unsigned)ceil_div(count, 256);
-  // small factors (up to 64 x 64) are summed in one level up to 256 chunks: a thread's serial sum is short against a
-  // second launch on the latency-bound chain Gram -> Cholesky -> apply
-  const int fan = count <= 4096 ? 4 * kGramFan : kGramFan;
-  if (chunks > fan) {
-    const int groups = (int)ceil_div(chunks, kGramFan);
-    double* lvl1 = w.gram_part + (int64_t)chunks * count;
-    hipLaunchKernelGGL(k_reduce_groups, dim3(bx, groups), dim3(256), 0, stream, w.gram_part, chunks, kGramFan, count,
-                       lvl1);
-    hipLaunchKernelGGL(k_reduce_groups, dim3(bx, 1), dim3(256), 0, stream, lvl1, groups, groups, count, w.G);
-  } else {
-    hipLaunchKernelGGL(k_reduce_groups, dim3(bx, 1), dim3(256), 0, stream, w.gram_part, chunks, chunks, count, w.G);
-  }
+  hipLaunchKernelGGL(k_gram_sum, dim3(nt * (nt + 1) / 2 * 8), dim3(1024), 0, stream, w.gram_part, chunks, Lp, w.G);
   BRSVD_HIP_TRY(hipGetLastError());
   return BRSVD_OK;
 }
