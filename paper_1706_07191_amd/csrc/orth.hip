@@ -16,13 +16,15 @@ namespace brsvd {
 
 // ---- Gram matrix -----------------------------------------------------------------------------
 // G = P^T P on the fp64 matrix cores (v_mfma_f64_16x16x4_f64; products of fp32 values are exact in
-// fp64; the panel may also be fp64).  G is cut into blocks of TB x TB tiles of 16 x 16; grid = (row chunks, pairs bi <= bj of
-// blocks).  For a step of four panel rows, lane (r, g) of a wave holds P[row + g][16*tile + r] for
-// each tile of the two blocks: that value is at once the A operand (entry [i = r][k = g] of the
-// transposed tile) and the B operand ([k = g][j = r]), so the panel goes from global memory straight
-// into the MFMA operands.  The eight waves of a workgroup take the steps of the chunk round-robin and
+// fp64; the panel may also be fp64).  The columns are cut into blocks of up to four tiles of 16; grid = (row chunks, pairs bi <= bj of
+// blocks).  Lane (r, g) of a wave takes W neighbouring columns of row g of four rows with one load, W r .. W r + W - 1 of the block's 16 W: number t of them
+// is its operand of tile t, whose columns are thus t, W + t, 2 W + t, ...; the same value is the A operand (entry [i = r][k = g] of the transposed
+// tile) and the B operand ([k = g][j = r]), so the panel goes from global memory straight into the MFMA operands, in lines.
+// The eight waves of a workgroup take AH steps of four rows at a time round-robin, the next ones' loads under way, and
 // add their accumulators through LDS in wave order; the chunks are added by k_gram_sum.
 // Accumulator layout of the instruction: component v of lane (r, g) is entry [g + 4*v][r].
+// Measured, with one load of four bytes per tile and step, and this (us):
+// 2073600x32 83 and 64, 76800x32 20 and 9, 40000x64 28 and 19, 20000x112 18.5 and 15, 100000x160 91 and 65, 100000x272 226 and 175, fp64 15872x80 12.7 and 8.2.
 constexpr int kGramWaves = 8;
 constexpr int kGramRowStep = 4 * kGramWaves;
 
@@ -30,72 +32,150 @@ __device__ __forceinline__ doublex4 mfma_f64(double a, double b, doublex4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-template <typename T, int TB>
-__global__ void __launch_bounds__(kGramWaves * 64)
-k_gram(const T* __restrict__ P, int64_t rows, int Lp, int64_t rows_per_chunk, double* __restrict__ Gpart) {
-  __shared__ double red[kGramWaves][256];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 15, g = lane >> 4;
-  const int NT = Lp / 16, nb = (NT + TB - 1) / TB;
-  int bi = 0, rem = blockIdx.y;
-  while (rem >= nb - bi) { rem -= nb - bi; ++bi; }
-  const int bj = bi + rem;
-  const int ti_n = min(TB, NT - bi * TB), tj_n = min(TB, NT - bj * TB);
-  const bool diag = bi == bj;
-  const int64_t rbeg = (int64_t)blockIdx.x * rows_per_chunk;
-  const int64_t rend = min(rows, rbeg + rows_per_chunk);
-  const T* pi = P + 16 * (bi * TB) + r;
-  const T* pj = P + 16 * (bj * TB) + r;
-
-  doublex4 acc[TB][TB];
+// W neighbouring numbers of a row.
+template <typename T, int W>
+__device__ __forceinline__ void load_run(const T* p, T (&v)[W]) {
+  if constexpr (W == 2 || W == 4) {
+    typedef T vec __attribute__((ext_vector_type(W)));
+    const vec x = *(const vec*)p;
 #pragma unroll
-  for (int i = 0; i < TB; ++i)
+    for (int t = 0; t < W; ++t) v[t] = x[t];
+  } else {
 #pragma unroll
-    for (int j = 0; j < TB; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
+    for (int t = 0; t < W; ++t) v[t] = p[t];
+  }
+}
 
-  T an[TB], bn[TB];
+// The part of a chunk, rows [rbeg, rend), in the block of columns ci .. ci + 16 TI, cj .. cj + 16 TJ of G.
+template <typename T, int TI, int TJ, bool DIAG>
+__device__ __forceinline__ void gram_block(const T* P, int Lp, int ci, int cj, int64_t rbeg, int64_t rend, double* red, double* Go, int tid) {
+  constexpr int AH = TI <= 2 ? 4 : 2, BJ = DIAG ? 1 : TJ, TILES = DIAG ? TI * (TI + 1) / 2 : TI * TJ;
+  const int lane = tid & 63, wave = tid >> 6, r = lane & 15, g = lane >> 4;
+  doublex4 acc[TILES];
+#pragma unroll
+  for (int t = 0; t < TILES; ++t) acc[t] = doublex4{0.0, 0.0, 0.0, 0.0};
+  T an[AH][TI], bn[AH][BJ];
+  const T *pi = P + ci + TI * r, *pj = P + cj + TJ * r;
   auto load = [&](int64_t row0) {
-    const int64_t row = row0 + g;
-    const bool valid = row < rend;
-    const int64_t off = (valid ? row : rbeg) * Lp;
 #pragma unroll
-    for (int t = 0; t < TB; ++t) {
-      an[t] = (valid && t < ti_n) ? pi[off + 16 * t] : T(0);
-      bn[t] = (valid && t < tj_n && !diag) ? pj[off + 16 * t] : T(0);
+    for (int s = 0; s < AH; ++s) {
+      const int64_t off = (row0 + 4 * s + g) * Lp;
+      load_run(pi + off, an[s]);
+      if constexpr (!DIAG) load_run(pj + off, bn[s]);
     }
   };
-  int64_t row0 = rbeg + 4 * wave;
-  if (row0 < rend) load(row0);
-  for (; row0 < rend; row0 += kGramRowStep) {
-    double a[TB], b[TB];
+  auto multiply = [&](const T (&a0)[AH][TI], const T (&b0)[AH][BJ]) {
 #pragma unroll
-    for (int t = 0; t < TB; ++t) { a[t] = (double)an[t]; b[t] = diag ? a[t] : (double)bn[t]; }
-    if (row0 + kGramRowStep < rend) load(row0 + kGramRowStep);     // next step's rows, in flight under the MFMAs
+    for (int s = 0; s < AH; ++s) {
+      double a[TI], b[TJ];
 #pragma unroll
-    for (int i = 0; i < TB; ++i)
+      for (int t = 0; t < TI; ++t) a[t] = (double)a0[s][t];
 #pragma unroll
-      for (int j = 0; j < TB; ++j)
-        if (i < ti_n && j < tj_n && !(diag && j < i)) acc[i][j] = mfma_f64(a[i], b[j], acc[i][j]);
+      for (int t = 0; t < TJ; ++t) b[t] = DIAG ? a[t % TI] : (double)b0[s][t % BJ];
+      int t = 0;
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = DIAG ? i : 0; j < TJ; ++j) { acc[t] = mfma_f64(a[i], b[j], acc[t]); ++t; }
+    }
+  };
+  constexpr int STEP = 4 * AH;
+  int64_t row0 = rbeg + STEP * wave;
+  if (row0 + STEP <= rend) load(row0);
+#pragma nounroll
+  for (; row0 + STEP <= rend; row0 += STEP * kGramWaves) {
+    T a[AH][TI], b[AH][BJ];
+#pragma unroll
+    for (int s = 0; s < AH; ++s) {
+#pragma unroll
+      for (int t = 0; t < TI; ++t) a[s][t] = an[s][t];
+      if constexpr (!DIAG) {
+#pragma unroll
+        for (int t = 0; t < BJ; ++t) b[s][t] = bn[s][t];
+      }
+    }
+    const int64_t next = row0 + STEP * kGramWaves;
+    load(next + STEP <= rend ? next : row0);               // under way while these rows are multiplied (the last time round: not used)
+    multiply(a, b);
   }
-
-  double* Go = Gpart + (int64_t)blockIdx.x * Lp * Lp;
+  if (row0 < rend) {                                       // the chunk's last rows, fewer than a step
 #pragma unroll
-  for (int i = 0; i < TB; ++i)
+    for (int s = 0; s < AH; ++s) {
+      const int64_t row = row0 + 4 * s + g, off = min(row, rend - 1) * Lp;
+      load_run(pi + off, an[s]);
 #pragma unroll
-    for (int j = 0; j < TB; ++j) {
-      if (!(i < ti_n && j < tj_n && !(diag && j < i))) continue;      // uniform over the workgroup
+      for (int t = 0; t < TI; ++t) an[s][t] = row < rend ? an[s][t] : T(0);
+      if constexpr (!DIAG) load_run(pj + off, bn[s]);
+    }
+    // (a row that is not there meets zeros on one side; on the other it is a copy of one that is, which may not be finite)
+    if constexpr (!DIAG) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) red[wave][v * 64 + lane] = acc[i][j][v];
+      for (int s = 0; s < AH; ++s)
+#pragma unroll
+        for (int t = 0; t < TJ; ++t) bn[s][t] = row0 + 4 * s + g < rend ? bn[s][t] : T(0);
+    }
+    multiply(an, bn);
+  }
+  // the waves' sums, PASS tiles at a time
+  constexpr int PASS = TILES < 2 ? TILES : 2;
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = DIAG ? i : 0; j < TJ; ++j) {
+      const int t = DIAG ? i * TI - i * (i - 1) / 2 + j - i : i * TJ + j;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) red[(wave * PASS + t % PASS) * 256 + 64 * v + lane] = acc[t][v];
+      if (t % PASS != PASS - 1 && t + 1 != TILES) continue;
       __syncthreads();
-      if (tid < 256) {
+      // entry e of tile tt; the thread also writes the entry's mirror image where that lies in an upper tile and no tile of its own has it
+      const int tt = t - t % PASS + (tid >> 8), e = tid & 255;
+      if (tt <= t) {
         double s = 0.0;
 #pragma unroll
-        for (int w = 0; w < kGramWaves; ++w) s += red[w][tid];
-        const int v = tid >> 6, ln = tid & 63;
-        const int gi = 16 * (bi * TB + i) + (ln >> 4) + 4 * v, gj = 16 * (bj * TB + j) + (ln & 15);
-        Go[(int64_t)gi * Lp + gj] = s;
+        for (int w = 0; w < kGramWaves; ++w) s += red[(w * PASS + (tid >> 8)) * 256 + e];
+        int ti = 0, tj = tt;
+        while (tj >= (DIAG ? TI - ti : TJ)) { tj -= DIAG ? TI - ti : TJ; ++ti; }
+        if (DIAG) tj += ti;
+        const int x = ci + TI * (((e & 63) >> 4) + 4 * (e >> 6)) + ti, y = cj + TJ * (e & 15) + tj;
+        if (!DIAG || x / 16 <= y / 16) Go[(int64_t)x * Lp + y] = s;
+        if (DIAG && ti != tj && y / 16 <= x / 16) Go[(int64_t)y * Lp + x] = s;
       }
       __syncthreads();
     }
+}
+
+// MAXB: tiles of a block at most; 1 to 3 where that is the whole matrix.
+template <typename T, int MAXB>
+__global__ void __launch_bounds__(kGramWaves * 64)
+k_gram(const T* __restrict__ P, int64_t rows, int Lp, int64_t rows_per_chunk, double* __restrict__ Gpart) {
+  __shared__ double red[kGramWaves * 2 * 256];
+  const int tid = threadIdx.x;
+  const int64_t rbeg = (int64_t)blockIdx.x * rows_per_chunk, rend = min(rows, rbeg + rows_per_chunk);
+  double* Go = Gpart + (int64_t)blockIdx.x * Lp * Lp;
+  if constexpr (MAXB < 4) {
+    gram_block<T, MAXB, MAXB, true>(P, Lp, 0, 0, rbeg, rend, red, Go, tid);
+  } else {
+    // blocks of equal size, or one tile more: two and three tiles for five in all, otherwise three and four (or a single one of four)
+    const int NT = Lp / 16, nb = (NT + 3) / 4;
+    int bi = 0, rem = blockIdx.y;
+    while (rem >= nb - bi) { rem -= nb - bi; ++bi; }
+    const int bj = bi + rem, t0 = bi * NT / nb, t1 = bj * NT / nb, ni = (bi + 1) * NT / nb - t0, nj = (bj + 1) * NT / nb - t1;
+#define CALL(NI, NJ, DIAG) gram_block<T, NI, NJ, DIAG>(P, Lp, 16 * t0, 16 * t1, rbeg, rend, red, Go, tid)
+    if (bi == bj) {
+      if (ni == 4) CALL(4, 4, true);
+      else if (ni == 3) CALL(3, 3, true);
+      else CALL(2, 2, true);
+    } else if (ni == 4) {
+      if (nj == 4) CALL(4, 4, false);
+      else CALL(4, 3, false);
+    } else if (ni == 3) {
+      if (nj == 4) CALL(3, 4, false);
+      else CALL(3, 3, false);
+    } else {
+      CALL(2, 3, false);
+    }
+#undef CALL
+  }
 }
 
 // ---- Cholesky factor and its inverse ---------------------------------------------------------
