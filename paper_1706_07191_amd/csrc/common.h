@@ -179,7 +179,7 @@ struct OrthWorkT {
   int* flags;          // device: [0] = breakdown flag (0 = none, else 1 + column)
   void* gemm_scratch;
   uint64_t gemm_scratch_bytes;
-  void* tsqr_work;     // TSQR scratch
+  void* tsqr_work;     // TSQR scratch; otherwise partial Gram sums
   uint64_t tsqr_bytes;
   // Optional companion panel (comp_rows x Lp): every R^-1 applied to the panel being orthonormalised
   // is applied to it as well (comp <- comp * R^-1, ping-ponging with comp_tmp; the result is in comp).

@@ -26,7 +26,6 @@ namespace brsvd {
 // Measured, with one load of four bytes per tile and step, and this (us):
 // 2073600x32 83 and 64, 76800x32 20 and 9, 40000x64 28 and 19, 20000x112 18.5 and 15, 100000x160 91 and 65, 100000x272 226 and 175, fp64 15872x80 12.7 and 8.2.
 constexpr int kGramWaves = 8;
-constexpr int kGramRowStep = 4 * kGramWaves;
 
 __device__ __forceinline__ doublex4 mfma_f64(double a, double b, doublex4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
@@ -489,23 +488,26 @@ k_triu_mul(const double* __restrict__ A, const TB* __restrict__ B, int l, int Lp
   }
 }
 
-// Row chunks of the Gram kernel.  Up to 64 chunks of at least 64 rows fill the chip for panels of
-// ordinary height; very tall panels get one chunk per 1024 rows, bounded by about 2048 workgroups
-// per launch and 64 MB of partial sums.
+// Slots of Lp x Lp doubles for partial sums in the workspace (its size is what callers' budgets were chosen for): enough for a Gram matrix that has
+// nothing else, after a Householder tree.
 constexpr int kGramFan = 64;
-uint64_t orth_gram_chunks(int64_t rows, int Lp) {
+uint64_t orth_gram_slots(int64_t rows, int Lp) {
   const int nbk = (Lp + 63) / 64, pairs = nbk * (nbk + 1) / 2;
   int64_t c = std::min<int64_t>(ceil_div(rows, 64), 64);
   c = std::min<int64_t>(c, std::max<int64_t>(1, ceil_div(1024, pairs)));
   const int64_t cap = std::min<int64_t>(std::max(2048 / pairs, 1), (64ll << 20) / ((int64_t)Lp * Lp * 8));
   const int64_t tall = std::min<int64_t>(rows / 1024, cap);
-  return (uint64_t)std::max<int64_t>(std::max(c, tall), 1);
+  c = std::max<int64_t>(std::max(c, tall), 1);
+  return (uint64_t)(c > kGramFan ? c + ceil_div(c, kGramFan) : c);
 }
-// Slots of Lp x Lp doubles of the workspace (of the partial sums, and some that are not used: the workspace keeps the size that callers' budgets
-// were chosen for).
-uint64_t orth_gram_slots(int64_t rows, int Lp) {
-  const uint64_t c = orth_gram_chunks(rows, Lp);
-  return c > (uint64_t)kGramFan ? c + ceil_div(c, kGramFan) : c;
+// Row chunks of the Gram kernel: of 64 rows at least (eight per wave), and as many as give every CU a workgroup: one where all blocks of tiles are of a size, more
+// where a chunk's pairs of blocks are not, so that the short ones fill the gaps.  Two per CU for the tallest narrow panels, whose workgroups have rows enough.
+// Measured (us with the sum, workgroups in all: 256 / 512 / 1024): 76800x32 10.2 / 11.6 / 12.6, 2073600x32 76 / 71 / 79, 40000x64 15 / 20 / 20 (23 with 64),
+// 20000x112 16.7 / 17.3 / 16.5 (20 with 192), 89083x112 38 / 39 / 45, 100000x160 73 / 69 / 78, 100000x272 192 / 181 / 170, 50000x272 104 / 99 / 97; chunks of
+// 64 / 128 / 256 rows: 2000x32 5.8 / 8.0 / 7.4, 12000x64 11.8 / 11.4 / 14.0, 2783x112 10.4 / 11.7 / 15.0.
+static int64_t gram_chunks(int64_t rows, int pairs) {
+  const int64_t wgs = pairs > 6 ? 1024 : pairs > 3 || (pairs == 1 && rows >= (1 << 20)) ? 512 : 256;
+  return std::min<int64_t>(ceil_div(rows, 64), std::max<int64_t>(1, wgs / pairs));
 }
 
 // G = the sum of the chunks' parts.  A workgroup takes 32 entries of the upper tiles; each is added up by 32 threads, thread s the chunks s, s + 32, ...
@@ -535,21 +537,25 @@ k_gram_sum(const double* __restrict__ part, int chunks, int Lp, double* __restri
 
 template <typename T>
 static int gram(const T* P, int64_t rows, int Lp, OrthWorkT<T>& w, hipStream_t stream) {
-  int chunks = (int)orth_gram_chunks(rows, Lp);
-  if ((int64_t)orth_gram_slots(rows, Lp) > w.gram_chunks_max) return BRSVD_ERR_BUDGET;
+  const int nt = Lp / 16, nb = (nt + 3) / 4, pairs = nb * (nb + 1) / 2;
+  // the partial sums lie in the work area of the Householder tree, unless that is in use
+  const int64_t slot = (int64_t)Lp * Lp * 8;
+  const bool tree = (int64_t)w.tsqr_bytes / slot > w.gram_chunks_max;
+  double* part = tree ? (double*)w.tsqr_work : w.gram_part;
+  int chunks = (int)std::min<int64_t>(gram_chunks(rows, pairs), tree ? w.tsqr_bytes / slot : w.gram_chunks_max);
+  if (chunks < 1) return BRSVD_ERR_BUDGET;
   int64_t rpc = ceil_div(rows, chunks);
-  rpc = ceil_div(rpc, kGramRowStep) * kGramRowStep;
+  rpc = ceil_div(rpc, 8) * 8;
   chunks = (int)ceil_div(rows, rpc);
-  const int nt = Lp / 16, nb = (nt + 3) / 4;       // blocks of (up to) four tiles; a single smaller block when nt < 4
-  dim3 grid(chunks, nb * (nb + 1) / 2), block(kGramWaves * 64);
+  dim3 grid(chunks, pairs), block(kGramWaves * 64);
   switch (nt) {
-    case 1: hipLaunchKernelGGL((k_gram<T, 1>), grid, block, 0, stream, P, rows, Lp, rpc, w.gram_part); break;
-    case 2: hipLaunchKernelGGL((k_gram<T, 2>), grid, block, 0, stream, P, rows, Lp, rpc, w.gram_part); break;
-    case 3: hipLaunchKernelGGL((k_gram<T, 3>), grid, block, 0, stream, P, rows, Lp, rpc, w.gram_part); break;
-    default: hipLaunchKernelGGL((k_gram<T, 4>), grid, block, 0, stream, P, rows, Lp, rpc, w.gram_part); break;
+    case 1: hipLaunchKernelGGL((k_gram<T, 1>), grid, block, 0, stream, P, rows, Lp, rpc, part); break;
+    case 2: hipLaunchKernelGGL((k_gram<T, 2>), grid, block, 0, stream, P, rows, Lp, rpc, part); break;
+    case 3: hipLaunchKernelGGL((k_gram<T, 3>), grid, block, 0, stream, P, rows, Lp, rpc, part); break;
+    default: hipLaunchKernelGGL((k_gram<T, 4>), grid, block, 0, stream, P, rows, Lp, rpc, part); break;
   }
   BRSVD_HIP_TRY(hipGetLastError());
-  hipLaunchKernelGGL(k_gram_sum, dim3(nt * (nt + 1) / 2 * 8), dim3(1024), 0, stream, w.gram_part, chunks, Lp, w.G);
+  hipLaunchKernelGGL(k_gram_sum, dim3(nt * (nt + 1) / 2 * 8), dim3(1024), 0, stream, part, chunks, Lp, w.G);
   BRSVD_HIP_TRY(hipGetLastError());
   return BRSVD_OK;
 }

@@ -89,3 +89,23 @@ def test_orth_of_a_panel_taken_as_it_is(rows, l):
     Qn, _, _ = B.brsvd_orth(P.clone())
     assert torch.equal(Q, Qn)
     assert O.orth_defect(Q.double().cpu().numpy()) <= 4 * np.sqrt(l) * 2.0 ** -24 + 1e-8
+
+
+@pytest.mark.parametrize("l", [1, 16, 17, 33, 49, 65, 81, 97, 113, 129, 145, 177, 193, 257, 400])
+def test_gram_over_all_block_sizes(l):
+    """The Gram matrix by blocks of one to four tiles, of every combination, with chunks whose last rows are no whole step: Q^T Q = I and P = Q R."""
+    dev = need_gpu()
+    for rows in (2 * l + 1, 2 * l + 9, 64 * 5 + l, 5003):
+        print(f"[case] gram blocks {rows} x {l}", flush=True)
+        P = torch.randn(rows, l, generator=torch.Generator().manual_seed(rows + l), dtype=torch.float64)
+        P[:, 0] *= 30.0
+        P[-1] *= 10.0                                 # the last row counts
+        P = P.float()
+        for method in (B.BRSVD_ORTH_AUTO, B.BRSVD_ORTH_TSQR) if l in (17, 65) else (B.BRSVD_ORTH_AUTO,):
+            Q, R, fallback = B.brsvd_orth(P.to(dev).clone(), method=method, want_R=True)
+            Q, R = Q.double().cpu(), R.cpu()
+            eps = 2.0 ** -24
+            defect = float(torch.linalg.norm(Q.T @ Q - torch.eye(l, dtype=torch.float64), 2))
+            back = float(torch.linalg.norm(Q @ R - P.double()) / torch.linalg.norm(P.double()))
+            # as in the test of the second factor, entries of Q up to 1 in place of 1 / sqrt(rows)
+            assert not fallback and defect <= 4 * np.sqrt(l) * eps + 1e-8 and back <= 8 * np.sqrt(l) * eps, (rows, method, defect, back)
