@@ -590,35 +590,46 @@ __global__ void k_reduce_splits(const T* __restrict__ part, int nsplit, int64_t 
   out[row * ldo + col] = s;
 }
 
-// The same sum for partial panels that are contiguous (all ldi columns summed, ldo == ldi): 16 bytes per
-// thread, splits unrolled so that several loads are in flight.
-template <typename T>
+// The same in units of 16 bytes (ldi and split_stride are whole units; part starts on one).  SL threads share a unit: thread s adds the slots s, s + SL, ... in
+// order, and their sums are added in order.
+// What bounds it: the latency of the loads for small panels, of which a thread has eight at a time under way, and the read of the slots for large ones.
+// Measured, one thread per unit, in two launches from 64 slots on, and this (us): 1000x32, 64 slots 9.1
+// and 4.9; 2000x32 9.7 and 4.0; 100x32, 1024 slots 14.5 and 7.5; into panels of 24 columns 9.5 and 6.4 to 8.8.
+template <typename T, int SL>
 __global__ void __launch_bounds__(256)
-k_reduce_splits_flat(const T* __restrict__ part, int nsplit, int64_t split_stride, int64_t count16,
-                     T* __restrict__ out, int accumulate) {
+k_split_sum(const T* __restrict__ part, int nsplit, int64_t split_stride, int64_t units, int units_per_row, int ncols, T* __restrict__ out, int64_t ldo,
+            int accumulate) {
   typedef typename El<T>::u16 unit16;
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= count16) return;
-  constexpr int EPU = El<T>::kPerU16;
-  const T* p = part + idx * EPU;
-  unit16 s = accumulate ? *(const unit16*)(out + idx * EPU) : unit16{};
+  constexpr int EPU = El<T>::kPerU16, PER = 256 / SL;
+  __shared__ unit16 sums[256];
+  const int tid = threadIdx.x, slice = tid / PER;
+  const int64_t u = (int64_t)blockIdx.x * PER + tid % PER;
+  unit16 s = unit16{};
+  if (u < units) {
+    const T* p = part + u * EPU;
 #pragma unroll 8
-  for (int i = 0; i < nsplit; ++i) s += *(const unit16*)(p + (int64_t)i * split_stride);
-  *(unit16*)(out + idx * EPU) = s;
-}
-
-// In-place first level of a long split sum: slot g*fan <- sum of the slots [g*fan, min((g+1)*fan, nsplit))
-// in slot order (blockIdx.y = g).  Each thread only touches its own element of every slot.
-template <typename T>
-__global__ void k_reduce_groups_inplace(T* __restrict__ part, int nsplit, int fan, int64_t split_stride,
-                                        int64_t count) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= count) return;                 // count <= split_stride elements of every slot take part
-  const int s0 = blockIdx.y * fan, s1 = min(nsplit, s0 + fan);
-  T* p = part + idx;
-  T s = p[(int64_t)s0 * split_stride];
-  for (int i = s0 + 1; i < s1; ++i) s += p[(int64_t)i * split_stride];
-  p[(int64_t)s0 * split_stride] = s;
+    for (int i = slice; i < nsplit; i += SL) s += *(const unit16*)(p + (int64_t)i * split_stride);
+  }
+  if constexpr (SL > 1) {
+    sums[tid] = s;
+    __syncthreads();
+    if (slice != 0) return;
+#pragma unroll
+    for (int k = 1; k < SL; ++k) s += sums[k * PER + tid];
+  }
+  if (u >= units) return;
+  const int64_t row = u / units_per_row;
+  const int col = (int)(u - row * units_per_row) * EPU;
+  T* o = out + row * ldo + col;
+  if (col + EPU <= ncols) {
+    typedef unit16 unit16u __attribute__((aligned(sizeof(T))));
+    if (accumulate) s += *(const unit16u*)o;
+    *(unit16u*)o = s;
+  } else {
+#pragma unroll
+    for (int v = 0; v < EPU; ++v)
+      if (col + v < ncols) o[v] = accumulate ? o[v] + s[v] : s[v];
+  }
 }
 
 template <typename T>
@@ -914,32 +925,36 @@ static int launch_an(int nt, const T* A, int64_t lda, int rows, int K, const T* 
 #undef CALL
 }
 
-// Sum of the split partial panels in split order; long sums (more than kReduceFan splits) are taken in
-// two levels, groups of kReduceFan consecutive splits first, so that no thread walks thousands of
-// slots serially.  Either way the association is fixed by the plan, not by timing.
-constexpr int kReduceFan = 16;
+// Sum of the split partial panels.  The association is fixed by the plan, not by timing.
 template <typename T>
 static int reduce_splits(T* part, int nsplit, int64_t split_stride, int64_t rows, int ncols, int64_t ldi, T* out,
                          int64_t ldo, bool accumulate, hipStream_t stream) {
-  int64_t total = rows * ncols;
-  if (total == 0) return BRSVD_OK;
-  if (nsplit > 2 * kReduceFan) {
-    const int groups = (int)ceil_div(nsplit, kReduceFan);
-    const int64_t count = rows * ldi;       // the rows being reduced, all ldi columns of each
-    hipLaunchKernelGGL(k_reduce_groups_inplace<T>, dim3((unsigned)ceil_div(count, 256), groups), dim3(256), 0, stream,
-                       part, nsplit, kReduceFan, split_stride, count);
-    nsplit = groups;
-    split_stride *= kReduceFan;
-  }
-  constexpr int EPU = 16 / (int)sizeof(T);
-  const bool flat = ncols == ldi && ldo == ldi && total % EPU == 0 && split_stride % EPU == 0 &&
-                    ((uintptr_t)part) % 16 == 0 && ((uintptr_t)out) % 16 == 0;
-  if (flat)
-    hipLaunchKernelGGL(k_reduce_splits_flat<T>, dim3((unsigned)ceil_div(total / EPU, 256)), dim3(256), 0, stream, part,
-                       nsplit, split_stride, total / EPU, out, accumulate ? 1 : 0);
-  else
+  if (ncols <= 0 || rows <= 0) return BRSVD_OK;
+  constexpr int EPU = El<T>::kPerU16;
+  if (ldi % EPU != 0 || split_stride % EPU != 0 || (uintptr_t)part % 16 != 0) {      // (a caller's scratch may start anywhere)
+    const int64_t total = rows * ncols;
     hipLaunchKernelGGL(k_reduce_splits<T>, dim3((unsigned)ceil_div(total, 256)), dim3(256), 0, stream,
                        part, nsplit, split_stride, rows, ncols, ldi, out, ldo, accumulate ? 1 : 0);
+    BRSVD_HIP_TRY(hipGetLastError());
+    return BRSVD_OK;
+  }
+  // as many threads per unit as leave each eight loads, while there are fewer than four waves per SIMD
+  const int upr = (int)(ldi / EPU);
+  const int64_t units = rows * upr;
+  int sl = 1;
+  while (sl < 32 && nsplit > 8 * sl && units * sl < 4 * 4 * 256 * 64) sl *= 2;
+#define CALL(SL)                                                                                                                      \
+  hipLaunchKernelGGL((k_split_sum<T, SL>), dim3((unsigned)ceil_div(units, 256 / SL)), dim3(256), 0, stream, part, nsplit, split_stride, units, \
+                     upr, ncols, out, ldo, accumulate ? 1 : 0)
+  switch (sl) {
+    case 1: CALL(1); break;
+    case 2: CALL(2); break;
+    case 4: CALL(4); break;
+    case 8: CALL(8); break;
+    case 16: CALL(16); break;
+    default: CALL(32); break;
+  }
+#undef CALL
   BRSVD_HIP_TRY(hipGetLastError());
   return BRSVD_OK;
 }
