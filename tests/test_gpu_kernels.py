@@ -229,3 +229,21 @@ def test_gemm_f64_matches_oracle(rows, n, l):
         Yv = B.brsvd_gemm_an(Av, X.to(dev)[1:n - 2].contiguous())
         refv = An[:, 1:n - 2] @ Xn[1:n - 2]
         assert np.max(np.abs(Yv.cpu().numpy() - refv)) <= 1e-11 * max(1.0, np.max(np.abs(refv)))
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("rows,n,l", [(2000, 1000, 30), (129, 259, 17), (3000, 600, 40), (257, 323, 33), (1000, 1000, 300), (1500, 1001, 100), (64, 2048, 20),
+                                      (8000, 480, 30)])
+def test_small_products_cut_along_the_contraction(rows, n, l, f64):
+    """Y = A X where the contraction is cut into pieces because the row tiles alone leave the chip idle: last pieces and last rows of any length."""
+    dev = need_gpu()
+    print(f"[case] small A X {rows}x{n} l={l} f64={f64}", flush=True)
+    g = torch.Generator().manual_seed(rows + n + l)
+    dt = torch.float64 if f64 else torch.float32
+    A, X = torch.randn(rows, n, generator=g, dtype=dt), torch.randn(n, l, generator=g, dtype=dt)
+    Y = B.brsvd_gemm_an(A.to(dev), X.to(dev)).cpu()
+    # the sum of n rounded products is off by sqrt(n) eps of their size at random, and never by more than n eps
+    want, size = A.double() @ X.double(), A.double().abs() @ X.double().abs()
+    eps = 2.0 ** -53 if f64 else 2.0 ** -24
+    assert float(((Y.double() - want).abs() / size).max()) <= 4 * np.sqrt(n) * eps
+    assert torch.equal(Y, B.brsvd_gemm_an(A.to(dev), X.to(dev)).cpu())
