@@ -57,6 +57,11 @@ __device__ __forceinline__ double rcp_nr(double x) {
 constexpr double kTolRows = 1e-13, kTolOneBlock = 1e-16;
 constexpr double kSettled = 1e-8;
 constexpr double kSettledF32 = 1e-5;
+// In the last sweeps most block pairs have nothing left to rotate: one whose cosines are all below kIdle (results in single precision: kIdleF32) is left
+// as it is, for the price of its Gram matrix.  kIdle is the rounding of the Gram matrix; kIdleF32 leaves V within 1e-8 of orthogonal,
+// less than the bar before it may.  On R of the range finder (l = 97, 110, 272) 80 to 95 % of the block pairs of the last sweep.
+constexpr double kIdle = 1e-15, kIdleF32 = 4e-9;
+constexpr int kIdleFrom = 3;                       // earlier sweeps (from 0) have none
 // Rotation (c, s) that makes two rows with squared norms al, be and inner product ga orthogonal:
 // with zeta = (be - al) / (2 ga), t = sign(zeta) / (|zeta| + sqrt(1 + zeta^2)), c = 1/sqrt(1+t^2),
 // s = c t, written so that it needs one reciprocal and two reciprocal square roots.
@@ -319,6 +324,8 @@ k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __re
 // a step without branches; a shorter chain; a ticket drawn ahead, one acquire for all waves (each costs 250 cycles).
 // Measured (us of the kernels, before and now): l = 24 68 -> 57, 30 85 -> 70, 48 199 -> 171 (row rotations before), 64 245 -> 206, 72 367 ->
 // 329 (row rotations before), 97 555 -> 447, 110 558 -> 451, 128 580 -> 464, 160 1312 -> 1040, 272 2197 -> 1686, 400 6078 -> 4454.
+// Since then pairs with nothing left to rotate are passed over (kIdle), before and now: SVD runs with l = 30 63 -> 55, 72 333 -> 317, 97 470 -> 426, 110 601 ->
+// 559, 272 1649 -> 1578.
 constexpr int kJB = 16;
 constexpr int kJN = 2 * kJB;                      // rows of a block pair
 // Place of entry (x, y) of the Gram matrix and of J: odd rows have their halves exchanged, so that the two rows of 16
@@ -532,6 +539,20 @@ __device__ __forceinline__ bool cross_pairs(double* work, int t, bool fresh, boo
   return any;
 }
 
+// Whether a cosine in the Gram matrix in buffer 0 of work, of all pairs of the 32 rows or of those across the two blocks, is above the idle bar (or not a number).
+// Products of square roots, so that norms of 1e-265 do not underflow.  Every thread of the workgroup calls it.
+__device__ __forceinline__ bool busy_32(const double* work, int t, bool all, double idle) {
+  __syncthreads();
+  bool busy = false;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int e = t + q * kJThreads, x = e >> 5, y = e & 31;
+    if (x < y && (all || (x < kJB && y >= kJB)))
+      busy |= !(fabs(work[jat(x, y)]) <= idle * (sqrt(work[jat(x, x)]) * sqrt(work[jat(y, y)])));
+  }
+  return __syncthreads_or(busy);
+}
+
 // One sweep of rotations on the Gram matrix in buffer 0 of work: all pairs of the 32 rows, or those across the two blocks.
 __device__ __forceinline__ bool sweep_32(double* work, int t, bool all, double settled2) {
   bool any = false;
@@ -578,7 +599,7 @@ static constexpr size_t jacobi_lds_bytes(int Lp) { return sizeof(double) * ((siz
 // Up to 32 rows: one workgroup, one block pair.
 __global__ void __launch_bounds__(kJThreads, 2)
 k_jacobi_small(const double* __restrict__ R, int ldr, int l, int Lp, double* __restrict__ Wg, double* __restrict__ sig,
-               int* __restrict__ info, const int* __restrict__ breakdown_flag, double settled) {
+               int* __restrict__ info, const int* __restrict__ breakdown_flag, double settled, double idle) {
   extern __shared__ __align__(16) double W[];
   __shared__ int rotated;
   __shared__ int order_sh[kJN];
@@ -611,6 +632,11 @@ k_jacobi_small(const double* __restrict__ R, int ldr, int l, int Lp, double* __r
     if (t == 0) rotated = 0;
     __syncthreads();
     gram_32(row, Lp, work, t);
+    if (sweeps >= kIdleFrom && !busy_32(work, t, true, idle)) {      // uniform over the workgroup
+      ++sweeps;
+      converged = 1;
+      break;
+    }
     if (sweep_32(work, t, true, settled * settled)) rotated = 1;
     for (int c0 = kJB * (t >> 6); c0 < Lp; c0 += (kJThreads / 64) * kJB)
       apply_32(row, work + 2 * kJN * kJN, c0, t & 63, [&](int x, int c, double v) { row(x)[c] = v; });
@@ -700,7 +726,7 @@ __device__ __forceinline__ void load_pair(const double* W, int l, int Lp, int rI
 // convergence flag, l = 160 took 1980 us and 272 4280 us.  Eight times the workgroups with all but every eighth leaving at
 // once, to keep the rest on one XCD, gains 5 % below 128 and loses up to 13 % above.
 __global__ void __launch_bounds__(kJThreads, 2)
-k_jacobi_rounds(const double* R, int ldr, double* W, int l, int Lp, int nblk2, double settled, double* sig, int* info) {
+k_jacobi_rounds(const double* R, int ldr, double* W, int l, int Lp, int nblk2, double settled, double idle, double* sig, int* info) {
   extern __shared__ __align__(16) double sh[];
   __shared__ int next, state;
   const int t = threadIdx.x, ld = Lp + 2;
@@ -747,9 +773,10 @@ k_jacobi_rounds(const double* R, int ldr, double* W, int l, int Lp, int nblk2, d
         else load_pair<4>(W, l, Lp, rI, rJ, sh, ld, t);
         __syncthreads();
         gram_32(row, Lp, work, t);
-        if (sweep_32(work, t, k.round == 0, settled * settled) && last <= k.sweep)
+        const bool busy = k.sweep < kIdleFrom || busy_32(work, t, k.round == 0, idle);
+        if (busy && sweep_32(work, t, k.round == 0, settled * settled) && last <= k.sweep)
           __hip_atomic_fetch_max(info + 3, k.sweep + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        for (int c0 = kJB * (t >> 6); c0 < Lp; c0 += (kJThreads / 64) * kJB)
+        for (int c0 = kJB * (t >> 6); busy && c0 < Lp; c0 += (kJThreads / 64) * kJB)
           apply_32(row, work + 2 * kJN * kJN, c0, t & 63, [&](int x, int c, double v) {
             if (grow(x) < l) __hip_atomic_store(W + (int64_t)grow(x) * Lp + c, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           });
@@ -873,7 +900,7 @@ static int jacobi_global(const double* R, int ldr, int l, int Lp, SvdWork& w, co
   hipLaunchKernelGGL(k_jacobi_init, dim3(Lp), dim3(128), 0, stream, R, ldr, l, Lp, w.W, w.sig, w.info, breakdown_flag);
   const int nblk = (int)ceil_div(l, kJB), nblk2 = (nblk + 1) & ~1;
   hipLaunchKernelGGL(k_jacobi_rounds, dim3(nblk2 / 2), dim3(kJThreads), jacobi_lds_bytes(Lp), stream, R, ldr, w.W, l, Lp, nblk2,
-                     settled, w.sig, w.info);
+                     settled, settled == kSettledF32 ? kIdleF32 : kIdle, w.sig, w.info);
   BRSVD_HIP_TRY(hipGetLastError());
   return BRSVD_OK;
 }
@@ -893,7 +920,7 @@ int small_svd(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* br
     BRSVD_HIP_TRY(hipGetLastError());
   } else if (l <= kJN) {
     hipLaunchKernelGGL(k_jacobi_small, dim3(1), dim3(kJThreads), jacobi_lds_bytes(Lp), stream, R, ldr, l, Lp, w.W, w.sig, w.info,
-                       breakdown_flag, settled);
+                       breakdown_flag, settled, settled == kSettledF32 ? kIdleF32 : kIdle);
     BRSVD_HIP_TRY(hipGetLastError());
   } else {
     BRSVD_TRY(jacobi_global(R, ldr, l, Lp, w, breakdown_flag, settled, stream));
