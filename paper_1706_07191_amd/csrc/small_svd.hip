@@ -553,12 +553,12 @@ __device__ __forceinline__ bool busy_32(const double* work, int t, bool all, dou
   return __syncthreads_or(busy);
 }
 
-// One sweep of rotations on the Gram matrix in buffer 0 of work: all pairs of the 32 rows, or those across the two blocks.
-__device__ __forceinline__ bool sweep_32(double* work, int t, bool all, double settled2) {
+// One sweep of rotations on the Gram matrix in buffer 0 of work: all pairs of the 32 rows, or those across the two blocks.  fresh, store: as for cross_pairs.
+__device__ __forceinline__ bool sweep_32(double* work, int t, bool all, double settled2, bool fresh = true, bool store = false) {
   bool any = false;
   __syncthreads();
   if (all) {
-    any |= cross_pairs<8>(work, t, true, true, settled2);
+    any |= cross_pairs<8>(work, t, fresh, true, settled2);
     __syncthreads();
     any |= cross_pairs<4>(work, t, false, true, settled2);
     __syncthreads();
@@ -567,7 +567,7 @@ __device__ __forceinline__ bool sweep_32(double* work, int t, bool all, double s
     any |= cross_pairs<1>(work, t, false, true, settled2);
     __syncthreads();
   }
-  any |= cross_pairs<16>(work, t, !all, false, settled2);
+  any |= cross_pairs<16>(work, t, !all && fresh, store, settled2);
   __syncthreads();
   return any;
 }
@@ -596,7 +596,9 @@ __device__ __forceinline__ void apply_32(Row row, const double* J, int c0, int l
 // rows a wave reads over the banks.
 static constexpr size_t jacobi_lds_bytes(int Lp) { return sizeof(double) * ((size_t)kJN * (Lp + 2) + kJWork); }
 
-// Up to 32 rows: one workgroup, one block pair.
+// Up to 32 rows: one workgroup, one block pair.  A sweep is 31 steps, and a third as much for the Gram matrix and J^T times the rows, which
+// two sweeps on one Gram matrix need once (us, before and with it: l = 30 55 and 50, 20 67 and 64).
+constexpr int kTwoSweeps = 4;                      // from sweep 0 to 4, two at a time
 __global__ void __launch_bounds__(kJThreads, 2)
 k_jacobi_small(const double* __restrict__ R, int ldr, int l, int Lp, double* __restrict__ Wg, double* __restrict__ sig,
                int* __restrict__ info, const int* __restrict__ breakdown_flag, double settled, double idle) {
@@ -637,7 +639,13 @@ k_jacobi_small(const double* __restrict__ R, int ldr, int l, int Lp, double* __r
       converged = 1;
       break;
     }
-    if (sweep_32(work, t, true, settled * settled)) rotated = 1;
+    // The first sweeps come in pairs on one Gram matrix: what the rotated matrix has lost by the second is little beside the cosines that are left.
+    const bool two = sweeps < kTwoSweeps;
+    if (two) {
+      sweep_32(work, t, true, settled * settled, true, true);
+      ++sweeps;
+    }
+    if (sweep_32(work, t, true, settled * settled, !two)) rotated = 1;
     for (int c0 = kJB * (t >> 6); c0 < Lp; c0 += (kJThreads / 64) * kJB)
       apply_32(row, work + 2 * kJN * kJN, c0, t & 63, [&](int x, int c, double v) { row(x)[c] = v; });
     __syncthreads();
