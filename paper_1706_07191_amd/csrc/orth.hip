@@ -45,6 +45,38 @@ __device__ __forceinline__ void load_run(const T* p, T (&v)[W]) {
   }
 }
 
+// The sums of WAVES waves' accumulators, in wave order, to the workgroup's part Go of G: block of columns ci .. ci + 16 TI, cj .. cj + 16 TJ.  red: room for two
+// tiles per wave.
+template <int TI, int TJ, bool DIAG, int WAVES, int TILES>
+__device__ __forceinline__ void gram_store(const doublex4 (&acc)[TILES], int Lp, int ci, int cj, double* red, double* Go, int tid) {
+  const int lane = tid & 63, wave = tid >> 6;
+  constexpr int PASS = TILES < 2 ? TILES : 2;
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = DIAG ? i : 0; j < TJ; ++j) {
+      const int t = DIAG ? i * TI - i * (i - 1) / 2 + j - i : i * TJ + j;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) red[(wave * PASS + t % PASS) * 256 + 64 * v + lane] = acc[t][v];
+      if (t % PASS != PASS - 1 && t + 1 != TILES) continue;
+      __syncthreads();
+      // entry e of tile tt; the thread also writes the entry's mirror image where that lies in an upper tile and no tile of its own has it
+      const int tt = t - t % PASS + (tid >> 8), e = tid & 255;
+      if (tt <= t) {
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) s += red[(w * PASS + (tid >> 8)) * 256 + e];
+        int ti = 0, tj = tt;
+        while (tj >= (DIAG ? TI - ti : TJ)) { tj -= DIAG ? TI - ti : TJ; ++ti; }
+        if (DIAG) tj += ti;
+        const int x = ci + TI * (((e & 63) >> 4) + 4 * (e >> 6)) + ti, y = cj + TJ * (e & 15) + tj;
+        if (!DIAG || x / 16 <= y / 16) Go[(int64_t)x * Lp + y] = s;
+        if (DIAG && ti != tj && y / 16 <= x / 16) Go[(int64_t)y * Lp + x] = s;
+      }
+      __syncthreads();
+    }
+}
+
 // The part of a chunk, rows [rbeg, rend), in the block of columns ci .. ci + 16 TI, cj .. cj + 16 TJ of G.
 template <typename T, int TI, int TJ, bool DIAG>
 __device__ __forceinline__ void gram_block(const T* P, int Lp, int ci, int cj, int64_t rbeg, int64_t rend, double* red, double* Go, int tid) {
@@ -115,32 +147,7 @@ __device__ __forceinline__ void gram_block(const T* P, int Lp, int ci, int cj, i
     }
     multiply(an, bn);
   }
-  // the waves' sums, PASS tiles at a time
-  constexpr int PASS = TILES < 2 ? TILES : 2;
-#pragma unroll
-  for (int i = 0; i < TI; ++i)
-#pragma unroll
-    for (int j = DIAG ? i : 0; j < TJ; ++j) {
-      const int t = DIAG ? i * TI - i * (i - 1) / 2 + j - i : i * TJ + j;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) red[(wave * PASS + t % PASS) * 256 + 64 * v + lane] = acc[t][v];
-      if (t % PASS != PASS - 1 && t + 1 != TILES) continue;
-      __syncthreads();
-      // entry e of tile tt; the thread also writes the entry's mirror image where that lies in an upper tile and no tile of its own has it
-      const int tt = t - t % PASS + (tid >> 8), e = tid & 255;
-      if (tt <= t) {
-        double s = 0.0;
-#pragma unroll
-        for (int w = 0; w < kGramWaves; ++w) s += red[(w * PASS + (tid >> 8)) * 256 + e];
-        int ti = 0, tj = tt;
-        while (tj >= (DIAG ? TI - ti : TJ)) { tj -= DIAG ? TI - ti : TJ; ++ti; }
-        if (DIAG) tj += ti;
-        const int x = ci + TI * (((e & 63) >> 4) + 4 * (e >> 6)) + ti, y = cj + TJ * (e & 15) + tj;
-        if (!DIAG || x / 16 <= y / 16) Go[(int64_t)x * Lp + y] = s;
-        if (DIAG && ti != tj && y / 16 <= x / 16) Go[(int64_t)y * Lp + x] = s;
-      }
-      __syncthreads();
-    }
+  gram_store<TI, TJ, DIAG, kGramWaves>(acc, Lp, ci, cj, red, Go, tid);
 }
 
 // MAXB: tiles of a block at most; 1 to 3 where that is the whole matrix.
@@ -535,14 +542,29 @@ k_gram_sum(const double* __restrict__ part, int chunks, int Lp, double* __restri
   G[(int64_t)row * Lp + col] = s;
 }
 
+// Where the partial sums lie, and for how many chunks there is room: in the work area of the Householder tree, unless that is in use.
+struct GramPlace {
+  double* part;
+  int64_t room;
+};
+template <typename T>
+static GramPlace gram_place(const OrthWorkT<T>& w, int Lp) {
+  const int64_t slot = (int64_t)Lp * Lp * 8, tree = (int64_t)w.tsqr_bytes / slot;
+  return tree > w.gram_chunks_max ? GramPlace{(double*)w.tsqr_work, tree} : GramPlace{w.gram_part, w.gram_chunks_max};
+}
+static int gram_sum(const double* part, int chunks, int Lp, double* G, hipStream_t stream) {
+  const int nt = Lp / 16;
+  hipLaunchKernelGGL(k_gram_sum, dim3(nt * (nt + 1) / 2 * 8), dim3(1024), 0, stream, part, chunks, Lp, G);
+  BRSVD_HIP_TRY(hipGetLastError());
+  return BRSVD_OK;
+}
+
 template <typename T>
 static int gram(const T* P, int64_t rows, int Lp, OrthWorkT<T>& w, hipStream_t stream) {
   const int nt = Lp / 16, nb = (nt + 3) / 4, pairs = nb * (nb + 1) / 2;
-  // the partial sums lie in the work area of the Householder tree, unless that is in use
-  const int64_t slot = (int64_t)Lp * Lp * 8;
-  const bool tree = (int64_t)w.tsqr_bytes / slot > w.gram_chunks_max;
-  double* part = tree ? (double*)w.tsqr_work : w.gram_part;
-  int chunks = (int)std::min<int64_t>(gram_chunks(rows, pairs), tree ? w.tsqr_bytes / slot : w.gram_chunks_max);
+  const GramPlace at = gram_place(w, Lp);
+  double* part = at.part;
+  int chunks = (int)std::min(gram_chunks(rows, pairs), at.room);
   if (chunks < 1) return BRSVD_ERR_BUDGET;
   int64_t rpc = ceil_div(rows, chunks);
   rpc = ceil_div(rpc, 8) * 8;
@@ -555,9 +577,7 @@ static int gram(const T* P, int64_t rows, int Lp, OrthWorkT<T>& w, hipStream_t s
     default: hipLaunchKernelGGL((k_gram<T, 4>), grid, block, 0, stream, P, rows, Lp, rpc, part); break;
   }
   BRSVD_HIP_TRY(hipGetLastError());
-  hipLaunchKernelGGL(k_gram_sum, dim3(nt * (nt + 1) / 2 * 8), dim3(1024), 0, stream, part, chunks, Lp, w.G);
-  BRSVD_HIP_TRY(hipGetLastError());
-  return BRSVD_OK;
+  return gram_sum(part, chunks, Lp, w.G, stream);
 }
 
 // lenient != 0: pivots below tol * (original diagonal) are clamped and the factorisation goes on;
@@ -649,6 +669,88 @@ k_apply(const float* __restrict__ P, int64_t rows, const float* __restrict__ X, 
       }
     }
   }
+}
+
+// The same with the Gram matrix of what is written, for the second sweep of CholeskyQR: that saves a read of the panel.  A wave puts each tile in LDS (its own
+// place, no barrier) and takes it up again in the order of the Gram kernel's operands; Gpart as there, one part per workgroup.
+// What bounds it: the panel's read and write, as before; the fp64 matrix instructions run under them.  Measured, product, Gram matrix and its sum, and with
+// this (us): 2073600x32 101 + 61 + 5 and 101 + 5, 76800x32 5.5 + 5 + 4.6 and 9 + 4.6, 2000x32 3.3 + 3.4 + 2.7 and 4.5 + 2.7.
+constexpr int kApplyGramWaves = 8;
+template <int NT>
+__global__ void __launch_bounds__(kApplyGramWaves * 64)
+k_apply_gram(const float* __restrict__ P, int64_t rows, const float* __restrict__ X, float* __restrict__ out, double* __restrict__ Gpart) {
+  constexpr int Lp = 16 * NT, TILES = NT * (NT + 1) / 2, LD = Lp + 4;
+  __shared__ __align__(16) float place[kApplyGramWaves][16 * LD];
+  __shared__ double red[kApplyGramWaves * 2 * 256];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 15, g = lane >> 4;
+  const int64_t tiles = (rows + 15) / 16, stride = (int64_t)gridDim.x * kApplyGramWaves;
+  int64_t tile = (int64_t)blockIdx.x * kApplyGramWaves + wave;
+  auto load = [&](int64_t t, floatx4 (&a)[NT]) {
+    const float* p = P + min(t * 16 + r, rows - 1) * Lp + 4 * g;
+#pragma unroll
+    for (int j = 0; j < NT; ++j) a[j] = *(const floatx4*)(p + 16 * j);
+  };
+  floatx4 next[NT];
+  load(min(tile, tiles - 1), next);
+  float x[NT][NT][4];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[t][j][i] = X[(16 * j + 4 * g + i) * Lp + 16 * t + r];
+  doublex4 gram[TILES];
+#pragma unroll
+  for (int t = 0; t < TILES; ++t) gram[t] = doublex4{0.0, 0.0, 0.0, 0.0};
+  float* mine = place[wave];
+#pragma nounroll
+  for (; tile < tiles; tile += stride) {
+    floatx4 a[NT], acc[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) { a[j] = next[j]; acc[j] = floatx4{0.f, 0.f, 0.f, 0.f}; }
+    load(min(tile + stride, tiles - 1), next);
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t][j][i], a[j][i], acc[t], 0, 0, 0);
+    const int64_t row = tile * 16 + r;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      if (row < rows) *(floatx4*)(out + row * Lp + 16 * t + 4 * g) = acc[t];
+      *(floatx4*)(mine + r * LD + 16 * t + 4 * g) = row < rows ? acc[t] : floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      double b[NT];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) b[t] = (double)mine[(4 * s + g) * LD + NT * r + t];
+      int t = 0;
+#pragma unroll
+      for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = i; j < NT; ++j) { gram[t] = mfma_f64(b[i], b[j], gram[t]); ++t; }
+    }
+  }
+  gram_store<NT, NT, true, kApplyGramWaves>(gram, Lp, 0, 0, red, Gpart + (int64_t)blockIdx.x * Lp * Lp, tid);
+}
+
+// out = P X and w.G = out^T out, where both are one kernel: fp32 panels of up to three tiles.
+static bool apply_gram_fits(int Lp, int esz) { return esz == 4 && Lp <= 48; }
+static int apply_gram(const float* P, int64_t rows, int Lp, const float* X, float* out, OrthWork& w, hipStream_t stream) {
+  const GramPlace at = gram_place(w, Lp);
+  const int64_t wgs = std::min<int64_t>(ceil_div(rows, 16 * kApplyGramWaves), rows >= (1 << 20) ? 512 : 256);
+  const int chunks = (int)std::min(wgs, at.room);
+  if (chunks < 1) return BRSVD_ERR_BUDGET;
+  const dim3 grid(chunks), block(kApplyGramWaves * 64);
+  switch (Lp / 16) {
+    case 1: hipLaunchKernelGGL(k_apply_gram<1>, grid, block, 0, stream, P, rows, X, out, at.part); break;
+    case 2: hipLaunchKernelGGL(k_apply_gram<2>, grid, block, 0, stream, P, rows, X, out, at.part); break;
+    default: hipLaunchKernelGGL(k_apply_gram<3>, grid, block, 0, stream, P, rows, X, out, at.part); break;
+  }
+  BRSVD_HIP_TRY(hipGetLastError());
+  return gram_sum(at.part, chunks, Lp, w.G, stream);
 }
 
 template <typename T>
@@ -767,12 +869,23 @@ template <typename T>
 int orth_basis(T* P, T* tmp, int64_t rows, int l, int Lp, int method, OrthWorkT<T>& w, T* left, double* Rtot, bool want_R, Basis<T>* out,
                hipStream_t stream) {
   if (rows < l) return BRSVD_ERR_ARG;
+  out->panel = nullptr;
   if (method == BRSVD_ORTH_TSQR) {
     *out = Basis<T>{nullptr, nullptr, want_R ? Rtot : nullptr, nullptr};
     return tsqr_panel<T>(P, tmp, rows, l, Lp, w, want_R ? Rtot : nullptr, &out->panel, stream);
   }
-  BRSVD_TRY(cholqr_sweeps<T>(P, tmp, rows, l, Lp, 1, w, nullptr, &out->panel, stream, false, want_R));
-  BRSVD_TRY(gram<T>(out->panel, rows, Lp, w, stream));
+  if constexpr (std::is_same<T, float>::value) {
+    if (apply_gram_fits(Lp, 4) && !w.comp) {
+      BRSVD_TRY(gram<T>(P, rows, Lp, w, stream));
+      BRSVD_TRY(chol_inv<T>(w.G, l, Lp, want_R ? w.R[0] : nullptr, w.Rinv, w.flags, kPivotTol, stream, 0, 1));
+      BRSVD_TRY(apply_gram(P, rows, Lp, w.Rinv, tmp, w, stream));
+      out->panel = tmp;
+    }
+  }
+  if (!out->panel) {
+    BRSVD_TRY(cholqr_sweeps<T>(P, tmp, rows, l, Lp, 1, w, nullptr, &out->panel, stream, false, want_R));
+    BRSVD_TRY(gram<T>(out->panel, rows, Lp, w, stream));
+  }
   BRSVD_TRY(chol_inv<T>(w.G, l, Lp, want_R ? w.R[1] : nullptr, left, w.flags, kPivotTol, stream, 0, 0, near_eye_of<T>()));
   out->left = left;
   out->R1 = want_R ? w.R[0] : nullptr;
