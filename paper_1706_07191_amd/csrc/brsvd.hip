@@ -16,6 +16,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "brsvd_steps.h"
@@ -487,7 +488,18 @@ int enqueue_brsvd(brsvd_handle h, const T* A, int64_t lda, const T* Omega, T* U,
       if (res != Ym) std::swap(Ym, Tm);
       return BRSVD_OK;
     };
-    BRSVD_TRY(pass_an<T>(h, A, lda, Xn, Ym));
+    // Y = A X; for tall matrices of short rows with the Gram matrix that orth_m starts from
+    auto product = [&](const T* X, T* Y, bool follows) -> int {
+      if constexpr (std::is_same<T, float>::value) {
+        if (!h->host_a && method != BRSVD_ORTH_TSQR && an_gram_fits(m, n, Lp, 4)) {
+          KernelEvents ke;
+          const bool t = kernel_events(h, CAT_AN, m, &ke, follows);
+          return an_gram(A, lda, m, n, X, Lp, Y, ow, cs, t ? &ke : nullptr);
+        }
+      }
+      return pass_an<T>(h, A, lda, X, Y, follows);
+    };
+    BRSVD_TRY(product(Xn, Ym, false));
     BRSVD_TRY(orth_m(q == 0));
     for (int it = 0; it < q; ++it) {
       BRSVD_TRY(pass_at<T>(h, A, lda, Ym, Xn, true));
@@ -496,7 +508,7 @@ int enqueue_brsvd(brsvd_handle h, const T* A, int64_t lda, const T* Omega, T* U,
         BRSVD_TRY(orth_panel<T>(Xn, Tn, n, l, Lp, method, false, ow, nullptr, &res, cs));
         if (res != Xn) std::swap(Xn, Tn);
       }
-      BRSVD_TRY(pass_an<T>(h, A, lda, Xn, Tm, true));
+      BRSVD_TRY(product(Xn, Tm, true));
       std::swap(Ym, Tm);
       BRSVD_TRY(orth_m(it == q - 1));
     }

@@ -176,6 +176,7 @@ struct OrthWorkT {
   double* G;           // Lp x Lp
   double* R[2];        // upper-triangular factors of the two CholeskyQR sweeps (stride Lp)
   T* Rinv;             // Lp x Lp zero-padded inverse factor in the panels' type (right operand of the apply GEMM)
+  bool G_of_panel = false;   // G is already the Gram matrix of the panel that is orthonormalised next (an_gram)
   int* flags;          // device: [0] = breakdown flag (0 = none, else 1 + column)
   void* gemm_scratch;
   uint64_t gemm_scratch_bytes;
@@ -192,6 +193,9 @@ typedef OrthWorkT<float> OrthWork;
 template <typename T>
 int apply_panel(const T* P, int64_t rows, int Lp, const T* X, T* out, int64_t ldo, int ncols, void* scratch, uint64_t scratch_bytes,
                 hipStream_t stream);
+// Y (rows x Lp) = A X with the Gram matrix of Y in w.G, for tall matrices of short rows: the next orthonormalisation by CholeskyQR on w starts from there.
+bool an_gram_fits(int64_t rows, int64_t K, int Lp, int esz);
+int an_gram(const float* A, int64_t lda, int64_t rows, int64_t K, const float* X, int Lp, float* Y, OrthWork& w, hipStream_t stream, const KernelEvents* ev);
 // Applies the current w.Rinv to the companion panel, if any.
 template <typename T> int apply_to_companion(OrthWorkT<T>& w, int Lp, hipStream_t stream);
 uint64_t orth_gram_slots(int64_t rows, int Lp);   // Lp x Lp fp64 slots of partial Gram sums for such a panel

@@ -61,11 +61,14 @@ __device__ __forceinline__ void gram_store(const doublex4 (&acc)[TILES], int Lp,
       if (t % PASS != PASS - 1 && t + 1 != TILES) continue;
       __syncthreads();
       // entry e of tile tt; the thread also writes the entry's mirror image where that lies in an upper tile and no tile of its own has it
-      const int tt = t - t % PASS + (tid >> 8), e = tid & 255;
-      if (tt <= t) {
+      const int e = tid & 255;
+#pragma unroll
+      for (int h = tid >> 8; h < PASS; h += WAVES / 4) {
+        const int tt = t - t % PASS + h;
+        if (tt > t) continue;
         double s = 0.0;
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) s += red[(w * PASS + (tid >> 8)) * 256 + e];
+        for (int w = 0; w < WAVES; ++w) s += red[(w * PASS + h) * 256 + e];
         int ti = 0, tj = tt;
         while (tj >= (DIAG ? TI - ti : TJ)) { tj -= DIAG ? TI - ti : TJ; ++ti; }
         if (DIAG) tj += ti;
@@ -561,6 +564,10 @@ static int gram_sum(const double* part, int chunks, int Lp, double* G, hipStream
 
 template <typename T>
 static int gram(const T* P, int64_t rows, int Lp, OrthWorkT<T>& w, hipStream_t stream) {
+  if (w.G_of_panel) {                  // came with the product that wrote the panel
+    w.G_of_panel = false;
+    return BRSVD_OK;
+  }
   const int nt = Lp / 16, nb = (nt + 3) / 4, pairs = nb * (nb + 1) / 2;
   const GramPlace at = gram_place(w, Lp);
   double* part = at.part;
@@ -675,42 +682,61 @@ k_apply(const float* __restrict__ P, int64_t rows, const float* __restrict__ X, 
 // place, no barrier) and takes it up again in the order of the Gram kernel's operands; Gpart as there, one part per workgroup.
 // What bounds it: the panel's read and write, as before; the fp64 matrix instructions run under them.  Measured, product, Gram matrix and its sum, and with
 // this (us): 2073600x32 101 + 61 + 5 and 101 + 5, 76800x32 5.5 + 5 + 4.6 and 9 + 4.6, 2000x32 3.3 + 3.4 + 2.7 and 4.5 + 2.7.
-constexpr int kApplyGramWaves = 8;
-template <int NT>
-__global__ void __launch_bounds__(kApplyGramWaves * 64)
-k_apply_gram(const float* __restrict__ P, int64_t rows, const float* __restrict__ X, float* __restrict__ out, double* __restrict__ Gpart) {
-  constexpr int Lp = 16 * NT, TILES = NT * (NT + 1) / 2, LD = Lp + 4;
-  __shared__ __align__(16) float place[kApplyGramWaves][16 * LD];
-  __shared__ double red[kApplyGramWaves * 2 * 256];
+// It also does Y = A X with the Gram matrix of Y for tall matrices of short rows (K up to 128, KT tiles of 16; rows at any element address): all of X is in registers
+// there as well.  A lane whose four indices lie behind K repeats the row's last ones and meets zeros of X.  k_gemm_an, Gram
+// matrix and sum, and this (us): 2073600x100 l=20 214 + 61 + 5 and 208 + 4.
+template <int KT> constexpr int rows_gram_waves() { return KT <= 3 ? 8 : 4; }
+template <int KT, int NT>
+__global__ void __launch_bounds__(rows_gram_waves<KT>() * 64)
+k_rows_gram(const float* __restrict__ A, int64_t lda, int64_t rows, int K, const float* __restrict__ X, float* __restrict__ out, double* __restrict__ Gpart) {
+  constexpr int Lp = 16 * NT, TILES = NT * (NT + 1) / 2, LD = Lp + 4, WAVES = rows_gram_waves<KT>();
+  typedef floatx4 floatx4u __attribute__((aligned(4)));
+  __shared__ __align__(16) float place[WAVES][16 * LD];
+  __shared__ double red[WAVES * 2 * 256];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 15, g = lane >> 4;
-  const int64_t tiles = (rows + 15) / 16, stride = (int64_t)gridDim.x * kApplyGramWaves;
-  int64_t tile = (int64_t)blockIdx.x * kApplyGramWaves + wave;
-  auto load = [&](int64_t t, floatx4 (&a)[NT]) {
-    const float* p = P + min(t * 16 + r, rows - 1) * Lp + 4 * g;
+  const int64_t tiles = (rows + 15) / 16, stride = (int64_t)gridDim.x * WAVES;
+  int64_t tile = (int64_t)blockIdx.x * WAVES + wave;
+  const bool whole = (K & 3) == 0;                 // no lane's four indices straddle K
+  auto load = [&](int64_t t, floatx4 (&a)[KT]) {
+    const float* p = A + min(t * 16 + r, rows - 1) * lda;
 #pragma unroll
-    for (int j = 0; j < NT; ++j) a[j] = *(const floatx4*)(p + 16 * j);
+    for (int j = 0; j < KT; ++j) {
+      const int k = 16 * j + 4 * g;
+      if (j < KT - 1 || whole) {
+        a[j] = *(const floatx4u*)(p + min(k, K - 4));
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a[j][i] = p[min(k + i, K - 1)];
+      }
+    }
   };
-  floatx4 next[NT];
+  floatx4 next[KT];
   load(min(tile, tiles - 1), next);
-  float x[NT][NT][4];
+  float x[NT][KT][4];
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
-    for (int j = 0; j < NT; ++j)
+    for (int j = 0; j < KT; ++j)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) x[t][j][i] = X[(16 * j + 4 * g + i) * Lp + 16 * t + r];
+      for (int i = 0; i < 4; ++i) {
+        const int k = 16 * j + 4 * g + i;
+        const float v = X[min(k, K - 1) * Lp + 16 * t + r];
+        x[t][j][i] = k < K ? v : 0.f;
+      }
   doublex4 gram[TILES];
 #pragma unroll
   for (int t = 0; t < TILES; ++t) gram[t] = doublex4{0.0, 0.0, 0.0, 0.0};
   float* mine = place[wave];
 #pragma nounroll
   for (; tile < tiles; tile += stride) {
-    floatx4 a[NT], acc[NT];
+    floatx4 a[KT], acc[NT];
 #pragma unroll
-    for (int j = 0; j < NT; ++j) { a[j] = next[j]; acc[j] = floatx4{0.f, 0.f, 0.f, 0.f}; }
+    for (int t = 0; t < NT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < KT; ++j) a[j] = next[j];
     load(min(tile + stride, tiles - 1), next);
 #pragma unroll
-    for (int j = 0; j < NT; ++j)
+    for (int j = 0; j < KT; ++j)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -733,24 +759,46 @@ k_apply_gram(const float* __restrict__ P, int64_t rows, const float* __restrict_
         for (int j = i; j < NT; ++j) { gram[t] = mfma_f64(b[i], b[j], gram[t]); ++t; }
     }
   }
-  gram_store<NT, NT, true, kApplyGramWaves>(gram, Lp, 0, 0, red, Gpart + (int64_t)blockIdx.x * Lp * Lp, tid);
+  gram_store<NT, NT, true, WAVES>(gram, Lp, 0, 0, red, Gpart + (int64_t)blockIdx.x * Lp * Lp, tid);
 }
 
-// out = P X and w.G = out^T out, where both are one kernel: fp32 panels of up to three tiles.
-static bool apply_gram_fits(int Lp, int esz) { return esz == 4 && Lp <= 48; }
-static int apply_gram(const float* P, int64_t rows, int Lp, const float* X, float* out, OrthWork& w, hipStream_t stream) {
+// out = A X and w.G = out^T out, where both are one kernel.
+template <int KT, int NT>
+static int rows_gram(const float* A, int64_t lda, int64_t rows, int K, const float* X, float* out, OrthWork& w, hipStream_t stream) {
+  constexpr int WAVES = rows_gram_waves<KT>(), Lp = 16 * NT;
   const GramPlace at = gram_place(w, Lp);
-  const int64_t wgs = std::min<int64_t>(ceil_div(rows, 16 * kApplyGramWaves), rows >= (1 << 20) ? 512 : 256);
-  const int chunks = (int)std::min(wgs, at.room);
+  const int64_t most = rows >= (1 << 20) ? 512 : 256;      // two and one per CU
+  const int chunks = (int)std::min(std::min<int64_t>(ceil_div(rows, 16 * WAVES), most), at.room);
   if (chunks < 1) return BRSVD_ERR_BUDGET;
-  const dim3 grid(chunks), block(kApplyGramWaves * 64);
-  switch (Lp / 16) {
-    case 1: hipLaunchKernelGGL(k_apply_gram<1>, grid, block, 0, stream, P, rows, X, out, at.part); break;
-    case 2: hipLaunchKernelGGL(k_apply_gram<2>, grid, block, 0, stream, P, rows, X, out, at.part); break;
-    default: hipLaunchKernelGGL(k_apply_gram<3>, grid, block, 0, stream, P, rows, X, out, at.part); break;
-  }
+  hipLaunchKernelGGL((k_rows_gram<KT, NT>), dim3(chunks), dim3(WAVES * 64), 0, stream, A, lda, rows, K, X, out, at.part);
   BRSVD_HIP_TRY(hipGetLastError());
   return gram_sum(at.part, chunks, Lp, w.G, stream);
+}
+// The panel times a factor: fp32 panels of up to three tiles.
+static bool apply_gram_fits(int Lp, int esz) { return esz == 4 && Lp <= 48; }
+static int apply_gram(const float* P, int64_t rows, int Lp, const float* X, float* out, OrthWork& w, hipStream_t stream) {
+  switch (Lp / 16) {
+    case 1: return rows_gram<1, 1>(P, Lp, rows, Lp, X, out, w, stream);
+    case 2: return rows_gram<2, 2>(P, Lp, rows, Lp, X, out, w, stream);
+    default: return rows_gram<3, 3>(P, Lp, rows, Lp, X, out, w, stream);
+  }
+}
+// A X: rows of up to 128 numbers, and enough of them for the matrix to be read from memory, not from the caches.
+bool an_gram_fits(int64_t rows, int64_t K, int Lp, int esz) { return esz == 4 && Lp <= 32 && K >= 4 && K <= 128 && rows >= 131072; }
+int an_gram(const float* A, int64_t lda, int64_t rows, int64_t K, const float* X, int Lp, float* Y, OrthWork& w, hipStream_t stream, const KernelEvents* ev) {
+  if (!an_gram_fits(rows, K, Lp, 4)) return BRSVD_ERR_ARG;
+  int status = BRSVD_ERR_ARG;
+#define CALL(KT) case KT: status = Lp == 16 ? rows_gram<KT, 1>(A, lda, rows, (int)K, X, Y, w, stream) : rows_gram<KT, 2>(A, lda, rows, (int)K, X, Y, w, stream); break;
+  switch (ceil_div(K, 16)) {
+    CALL(1) CALL(2) CALL(3) CALL(4) CALL(5) CALL(6) CALL(7) CALL(8)
+  }
+#undef CALL
+  if (ev) {
+    BRSVD_HIP_TRY(hipEventRecord(ev->stop, stream));
+    BRSVD_HIP_TRY(hipEventRecord(ev->sum_stop, stream));
+  }
+  w.G_of_panel = status == BRSVD_OK;
+  return status;
 }
 
 template <typename T>

@@ -109,3 +109,25 @@ def test_gram_over_all_block_sizes(l):
             back = float(torch.linalg.norm(Q @ R - P.double()) / torch.linalg.norm(P.double()))
             # as in the test of the second factor, entries of Q up to 1 in place of 1 / sqrt(rows)
             assert not fallback and defect <= 4 * np.sqrt(l) * eps + 1e-8 and back <= 8 * np.sqrt(l) * eps, (rows, method, defect, back)
+
+
+@pytest.mark.parametrize("n,l", [(100, 20), (64, 32), (61, 16), (128, 17), (127, 32), (33, 9), (17, 17)])
+def test_tall_matrices_of_short_rows(n, l):
+    """More rows than the product and its Gram matrix are one kernel from, rows of every length up to its largest, at every alignment."""
+    dev = need_gpu()
+    m, k = 131072 + 5, max(l - 4, 1)
+    print(f"[case] short rows n={n} l={l}", flush=True)
+    g = torch.Generator().manual_seed(n * l)
+    w = torch.exp(-torch.arange(n, dtype=torch.float64) * (np.log(50.0) / l))
+    A = ((torch.randn(m, n, generator=g, dtype=torch.float64) * w) @ torch.linalg.qr(torch.randn(n, n, generator=g, dtype=torch.float64))[0]).float()
+    A[-1] *= 20.0                                     # the last row counts
+    Om = torch.randn(n, l, generator=g)
+    big = torch.empty(m, n + 1, device=dev)           # rows that start anywhere
+    big[:, 1:].copy_(A)
+    h = B.brsvd_create(B.make_params(m, n, k, l - k, 1))
+    try:
+        for Ad, lda in ((A.to(dev), n), (big[:, 1:], n + 1)):
+            U, S, Vt, _ = B.brsvd_run(h, Ad, Om.to(dev), lda=lda)
+            check_against_oracle(A.numpy(), Om.numpy(), k, l - k, 1, m, U, S, Vt, f"short rows {n} {l} {lda}")
+    finally:
+        B.brsvd_destroy(h)
