@@ -1,10 +1,10 @@
 // Orthonormalisation of tall thin panels (Alg. 1 step 3, Alg. 2 line 6) on gfx950.
 //
-// Main route: CholeskyQR applied twice.  G = P^T P is accumulated in fp64 (products of fp32
-// values are exact in fp64), factored G = R^T R in fp64, and P <- P * R^-1 is one more thin
-// GEMM on the MFMA path.  Pivots that fall below a relative threshold are clamped in every sweep
-// but the last one of an output basis; there such a pivot raises the breakdown flag and the caller
-// switches to the Householder-based TSQR route (tsqr.hip).
+// Main route: CholeskyQR.  G = P^T P is accumulated in fp64 (products of fp32 values are exact in fp64), factored
+// G = R^T R in fp64, and P <- P * R^-1 is one more thin GEMM on the MFMA path.  A basis that reaches the output gets a second
+// factor, which goes into the l x l factors that the panel meets later (orth_basis) or is applied too (orth_panel).  Pivots
+// that fall below a relative threshold are clamped in every sweep but the last one of an output basis; there such a pivot
+// raises the breakdown flag and the caller switches to the Householder-based TSQR route (tsqr.hip).
 // The paper orthonormalises with a TSQR-based CAQR; range(P) -- all the method needs -- is the
 // same for any orthonormalisation.
 #include <algorithm>
