@@ -685,7 +685,9 @@ k_apply(const float* __restrict__ P, int64_t rows, const float* __restrict__ X, 
 // It also does Y = A X with the Gram matrix of Y for tall matrices of short rows (K up to 128, KT tiles of 16; rows at any element address): all of X is in registers
 // there as well.  A lane whose four indices lie behind K repeats the row's last ones and meets zeros of X.  k_gemm_an, Gram
 // matrix and sum, and this (us): 2073600x100 l=20 214 + 61 + 5 and 208 + 4.
-template <int KT> constexpr int rows_gram_waves() { return KT <= 3 ? 8 : 4; }
+// Waves of a workgroup: eight, two of whose workgroups fit a CU, up to 64 indices; four where registers run out (SVD runs, q = 1, with four and eight,
+// us: 1000000x64 l = 32 750 and 731, 1000000x100 828 and 859, 2073600x96 1415 and 1492).
+template <int KT> constexpr int rows_gram_waves() { return KT <= 4 ? 8 : 4; }
 template <int KT, int NT>
 __global__ void __launch_bounds__(rows_gram_waves<KT>() * 64)
 k_rows_gram(const float* __restrict__ A, int64_t lda, int64_t rows, int K, const float* __restrict__ X, float* __restrict__ out, double* __restrict__ Gpart) {
@@ -783,8 +785,10 @@ static int apply_gram(const float* P, int64_t rows, int Lp, const float* X, floa
     default: return rows_gram<3, 3>(P, Lp, rows, Lp, X, out, w, stream);
   }
 }
-// A X: rows of up to 128 numbers, and enough of them for the matrix to be read from memory, not from the caches.
-bool an_gram_fits(int64_t rows, int64_t K, int Lp, int esz) { return esz == 4 && Lp <= 32 && K >= 4 && K <= 128 && rows >= 131072; }
+// A X: rows of up to 128 numbers, and some wavefronts for every CU.  SVD runs, q = 1, with the product and the Gram matrix apart and in one (us): 4100x50 l = 32 242 and
+// 235, 16384x50 256 and 238, 16384x128 259 and 254, 131072x65 l = 16 246 and 236, 131072x128 l = 32 322 and 326, 1000000x50 879 and 793, 1000000x64 733 and
+// 733, 1000000x100 885 and 828, 2073600x33 l = 16 898 and 747.  Fewer rows are matters of launches, and the small products' plan cuts them.
+bool an_gram_fits(int64_t rows, int64_t K, int Lp, int esz) { return esz == 4 && Lp <= 32 && K >= 4 && K <= 128 && rows >= 4096; }
 int an_gram(const float* A, int64_t lda, int64_t rows, int64_t K, const float* X, int Lp, float* Y, OrthWork& w, hipStream_t stream, const KernelEvents* ev) {
   if (!an_gram_fits(rows, K, Lp, 4)) return BRSVD_ERR_ARG;
   int status = BRSVD_ERR_ARG;

@@ -111,12 +111,13 @@ def test_gram_over_all_block_sizes(l):
             assert not fallback and defect <= 4 * np.sqrt(l) * eps + 1e-8 and back <= 8 * np.sqrt(l) * eps, (rows, method, defect, back)
 
 
-@pytest.mark.parametrize("n,l", [(100, 20), (64, 32), (61, 16), (128, 17), (127, 32), (33, 9), (17, 17)])
-def test_tall_matrices_of_short_rows(n, l):
-    """More rows than the product and its Gram matrix are one kernel from, rows of every length up to its largest, at every alignment."""
+@pytest.mark.parametrize("n,l,m", [(100, 20, 131077), (64, 32, 131077), (61, 16, 4096), (128, 17, 4101), (127, 32, 40001), (33, 9, 4101), (17, 17, 131077),
+                                   (65, 32, 4096)])
+def test_tall_matrices_of_short_rows(n, l, m):
+    """Rows from as many as the product and its Gram matrix are one kernel for, of every length up to its largest, at every alignment."""
     dev = need_gpu()
-    m, k = 131072 + 5, max(l - 4, 1)
-    print(f"[case] short rows n={n} l={l}", flush=True)
+    k = max(l - 4, 1)
+    print(f"[case] short rows n={n} l={l} m={m}", flush=True)
     g = torch.Generator().manual_seed(n * l)
     w = torch.exp(-torch.arange(n, dtype=torch.float64) * (np.log(50.0) / l))
     A = ((torch.randn(m, n, generator=g, dtype=torch.float64) * w) @ torch.linalg.qr(torch.randn(n, n, generator=g, dtype=torch.float64))[0]).float()
