@@ -57,10 +57,15 @@ __device__ __forceinline__ double rcp_nr(double x) {
 constexpr double kTolRows = 1e-13, kTolOneBlock = 1e-16;
 constexpr double kSettled = 1e-8;
 constexpr double kSettledF32 = 1e-5;
-// In the last sweeps most block pairs have nothing left to rotate: one whose cosines are all below kIdle (results in single precision: kIdleF32) is left
-// as it is, for the price of its Gram matrix.  kIdle is the rounding of the Gram matrix; kIdleF32 leaves V within 1e-8 of orthogonal,
-// less than the bar before it may.  On R of the range finder (l = 97, 110, 272) 80 to 95 % of the block pairs of the last sweep.
-constexpr double kIdle = 1e-15, kIdleF32 = 4e-9;
+// In the last sweeps of more than 32 rows most block pairs have nothing left to rotate.  For results in single precision one is left as
+// it is, for the price of its Gram matrix, when the inner product of every two of its rows is at most kIdleF32 of the smaller of their
+// squared norms.  Rows i and j that keep a product g leave g / (s_i s_j) in V^T V, but U = R V / s carries that times s_i / s_j: the bar
+// is on g / s_j^2, which holds for both whatever the condition of R.  U and V then are within 1e-8 of orthogonal, where the rounding
+// of the panels leaves 2e-7; the results' defects are the same to two digits with and without it (l = 30 to 400, s_1 / s_l from 64 to 1e6).
+// (The same bar on the cosines left U off by 3e-6 at l = 200 and a condition of 1e4, by 1e-3 at 1e6.)  Everything rotated and with
+// this (us of the small SVD): l = 72 305 and 287, 97 449 and 432, 160 694 and 636, 110 and 272 no difference; a bar of 3e-11
+// gains nothing.  fp64 results have no bar: one that both factors allow, 1e-15, gains nothing.
+constexpr double kIdleF32 = 4e-9;
 constexpr int kIdleFrom = 3;                       // earlier sweeps (from 0) have none
 // Rotation (c, s) that makes two rows with squared norms al, be and inner product ga orthogonal:
 // with zeta = (be - al) / (2 ga), t = sign(zeta) / (|zeta| + sqrt(1 + zeta^2)), c = 1/sqrt(1+t^2),
@@ -324,8 +329,7 @@ k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __re
 // a step without branches; a shorter chain; a ticket drawn ahead, one acquire for all waves (each costs 250 cycles).
 // Measured (us of the kernels, before and now): l = 24 68 -> 57, 30 85 -> 70, 48 199 -> 171 (row rotations before), 64 245 -> 206, 72 367 ->
 // 329 (row rotations before), 97 555 -> 447, 110 558 -> 451, 128 580 -> 464, 160 1312 -> 1040, 272 2197 -> 1686, 400 6078 -> 4454.
-// Since then pairs with nothing left to rotate are passed over (kIdle), before and now: SVD runs with l = 30 63 -> 55, 72 333 -> 317, 97 470 -> 426, 110 601 ->
-// 559, 272 1649 -> 1578.
+// Since then fp32 results pass over pairs with nothing left to rotate (kIdleF32).
 constexpr int kJB = 16;
 constexpr int kJN = 2 * kJB;                      // rows of a block pair
 // Place of entry (x, y) of the Gram matrix and of J: odd rows have their halves exchanged, so that the two rows of 16
@@ -539,8 +543,8 @@ __device__ __forceinline__ bool cross_pairs(double* work, int t, bool fresh, boo
   return any;
 }
 
-// Whether a cosine in the Gram matrix in buffer 0 of work, of all pairs of the 32 rows or of those across the two blocks, is above the idle bar (or not a number).
-// Products of square roots, so that norms of 1e-265 do not underflow.  Every thread of the workgroup calls it.
+// Whether an inner product in the Gram matrix in buffer 0 of work, of all pairs of the 32 rows or of those across the two blocks, is
+// above the idle bar (or not a number).  Every thread of the workgroup calls it.
 __device__ __forceinline__ bool busy_32(const double* work, int t, bool all, double idle) {
   __syncthreads();
   bool busy = false;
@@ -548,7 +552,7 @@ __device__ __forceinline__ bool busy_32(const double* work, int t, bool all, dou
   for (int q = 0; q < 2; ++q) {
     const int e = t + q * kJThreads, x = e >> 5, y = e & 31;
     if (x < y && (all || (x < kJB && y >= kJB)))
-      busy |= !(fabs(work[jat(x, y)]) <= idle * (sqrt(work[jat(x, x)]) * sqrt(work[jat(y, y)])));
+      busy |= !(fabs(work[jat(x, y)]) <= idle * fmin(work[jat(x, x)], work[jat(y, y)]));
   }
   return __syncthreads_or(busy);
 }
@@ -601,7 +605,7 @@ static constexpr size_t jacobi_lds_bytes(int Lp) { return sizeof(double) * ((siz
 constexpr int kTwoSweeps = 4;                      // from sweep 0 to 4, two at a time
 __global__ void __launch_bounds__(kJThreads, 2)
 k_jacobi_small(const double* __restrict__ R, int ldr, int l, int Lp, double* __restrict__ Wg, double* __restrict__ sig,
-               int* __restrict__ info, const int* __restrict__ breakdown_flag, double settled, double idle) {
+               int* __restrict__ info, const int* __restrict__ breakdown_flag, double settled) {
   extern __shared__ __align__(16) double W[];
   __shared__ int rotated;
   __shared__ int order_sh[kJN];
@@ -634,11 +638,6 @@ k_jacobi_small(const double* __restrict__ R, int ldr, int l, int Lp, double* __r
     if (t == 0) rotated = 0;
     __syncthreads();
     gram_32(row, Lp, work, t);
-    if (sweeps >= kIdleFrom && !busy_32(work, t, true, idle)) {      // uniform over the workgroup
-      ++sweeps;
-      converged = 1;
-      break;
-    }
     // The first sweeps come in pairs on one Gram matrix: what the rotated matrix has lost by the second is little beside the cosines that are left.
     const bool two = sweeps < kTwoSweeps;
     if (two) {
@@ -781,7 +780,7 @@ k_jacobi_rounds(const double* R, int ldr, double* W, int l, int Lp, int nblk2, d
         else load_pair<4>(W, l, Lp, rI, rJ, sh, ld, t);
         __syncthreads();
         gram_32(row, Lp, work, t);
-        const bool busy = k.sweep < kIdleFrom || busy_32(work, t, k.round == 0, idle);
+        const bool busy = idle == 0.0 || k.sweep < kIdleFrom || busy_32(work, t, k.round == 0, idle);   // uniform over the workgroup
         if (busy && sweep_32(work, t, k.round == 0, settled * settled) && last <= k.sweep)
           __hip_atomic_fetch_max(info + 3, k.sweep + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         for (int c0 = kJB * (t >> 6); busy && c0 < Lp; c0 += (kJThreads / 64) * kJB)
@@ -908,7 +907,7 @@ static int jacobi_global(const double* R, int ldr, int l, int Lp, SvdWork& w, co
   hipLaunchKernelGGL(k_jacobi_init, dim3(Lp), dim3(128), 0, stream, R, ldr, l, Lp, w.W, w.sig, w.info, breakdown_flag);
   const int nblk = (int)ceil_div(l, kJB), nblk2 = (nblk + 1) & ~1;
   hipLaunchKernelGGL(k_jacobi_rounds, dim3(nblk2 / 2), dim3(kJThreads), jacobi_lds_bytes(Lp), stream, R, ldr, w.W, l, Lp, nblk2,
-                     settled, settled == kSettledF32 ? kIdleF32 : kIdle, w.sig, w.info);
+                     settled, settled == kSettledF32 ? kIdleF32 : 0.0, w.sig, w.info);
   BRSVD_HIP_TRY(hipGetLastError());
   return BRSVD_OK;
 }
@@ -928,7 +927,7 @@ int small_svd(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* br
     BRSVD_HIP_TRY(hipGetLastError());
   } else if (l <= kJN) {
     hipLaunchKernelGGL(k_jacobi_small, dim3(1), dim3(kJThreads), jacobi_lds_bytes(Lp), stream, R, ldr, l, Lp, w.W, w.sig, w.info,
-                       breakdown_flag, settled, settled == kSettledF32 ? kIdleF32 : kIdle);
+                       breakdown_flag, settled);
     BRSVD_HIP_TRY(hipGetLastError());
   } else {
     BRSVD_TRY(jacobi_global(R, ldr, l, Lp, w, breakdown_flag, settled, stream));

@@ -9,6 +9,7 @@ import pytest
 import torch
 
 import paper_1706_07191_amd as B
+from paper_1706_07191_amd import synth
 from tests.gpu_util import EPS32, need_gpu
 
 pytestmark = pytest.mark.gpu
@@ -140,6 +141,29 @@ def test_small_svd_of_graded_rows(l, decades):
     # condition of the matrix with its rows scaled to one (4 here)
     assert rel <= 4 * 2.0 ** -52 * np.sqrt(l * sweeps) * 4
     assert float((V.T @ V - torch.eye(l, dtype=torch.float64)).abs().max()) <= 4e-13
+
+
+@pytest.mark.parametrize("l", [30, 97, 200, 400])
+@pytest.mark.parametrize("q", [0, 1])
+@pytest.mark.parametrize("ratio", [1e-4, 1e-6])
+def test_vectors_of_steep_spectra(l, q, ratio):
+    """fp32 SVDs whose small factor has a condition of 1e4 and 1e6: V = W_B (R V_R / s) carries a cosine that the iteration leaves
+    between rows i and j times s_i / s_j, so block pairs may only be passed over by a bar that knows the norms."""
+    dev = need_gpu()
+    print(f"[case] steep spectrum l={l} q={q} ratio={ratio}", flush=True)
+    m, n = 3 * l + 300, 3 * l + 200
+    s = torch.exp(-torch.arange(2 * l, dtype=torch.float64) * (np.log(1 / ratio) / l))
+    A = synth.exact_spectrum_matrix(m, n, s, l + q, torch.float32).contiguous()
+    h = B.brsvd_create(B.make_params(m, n, l - 10, 10, q))
+    try:
+        U, S, Vt, st = B.brsvd_run(h, A.to(dev), synth.gaussian(n, l, 5).to(dev))
+    finally:
+        B.brsvd_destroy(h)
+    eye = torch.eye(l, dtype=torch.float64, device=dev)
+    for X in (U.double(), Vt.double().T):
+        # entries rounded to 2^-24 of themselves leave a random matrix of variance 2^-48 in X^T X, of norm 2 sqrt(l) 2^-24
+        assert float(torch.linalg.norm(X.T @ X - eye, 2)) <= 2 * np.sqrt(l) * 2.0 ** -24
+    assert 0.3 * ratio < float(S[-1] / S[0]) < 3 * ratio and st["orth_fallbacks"] == 0
 
 
 def test_small_svd_of_equal_and_zero_values():
