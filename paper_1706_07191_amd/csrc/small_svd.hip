@@ -57,15 +57,14 @@ __device__ __forceinline__ double rcp_nr(double x) {
 constexpr double kTolRows = 1e-13, kTolOneBlock = 1e-16;
 constexpr double kSettled = 1e-8;
 constexpr double kSettledF32 = 1e-5;
-// In the last sweeps of more than 32 rows most block pairs have nothing left to rotate.  For results in single precision one is left as
-// it is, for the price of its Gram matrix, when the inner product of every two of its rows is at most kIdleF32 of the smaller of their
-// squared norms.  Rows i and j that keep a product g leave g / (s_i s_j) in V^T V, but U = R V / s carries that times s_i / s_j: the bar
-// is on g / s_j^2, which holds for both whatever the condition of R.  U and V then are within 1e-8 of orthogonal, where the rounding
-// of the panels leaves 2e-7; the results' defects are the same to two digits with and without it (l = 30 to 400, s_1 / s_l from 64 to 1e6).
-// (The same bar on the cosines left U off by 3e-6 at l = 200 and a condition of 1e4, by 1e-3 at 1e6.)  Everything rotated and with
-// this (us of the small SVD): l = 72 305 and 287, 97 449 and 432, 160 694 and 636, 110 and 272 no difference; a bar of 3e-11
-// gains nothing.  fp64 results have no bar: one that both factors allow, 1e-15, gains nothing.
-constexpr double kIdleF32 = 4e-9;
+// In the last sweeps most block pairs have nothing left to rotate.  One is left as it is, for the price of its Gram matrix, when the inner
+// product of every two of its rows is at most kIdle (results in single precision: kIdleF32) of the smaller of their squared norms.  Rows i
+// and j that keep a product g leave g / (s_i s_j) in V^T V, but U = R V / s carries that times s_i / s_j: the bar is on g / s_j^2, which
+// holds for both whatever the condition of R.  kIdle is near the rounding of a cosine; kIdleF32 leaves U and V within 1e-8 of
+// orthogonal, where the rounding of the panels leaves 2e-7.  The results' defects are the same to two digits with and without the bars
+// (l = 30 to 400, s_1 / s_l from 64 to 1e6; fp64 2e-15 to 1e-13).  (4e-9 and 1e-15 on the cosines left V of the SVD off by 3e-6 and 4e-14 at l =
+// 200 and a condition of 1e4, by 6e-4 and 1e-10 at 1e6.)
+constexpr double kIdle = 1e-15, kIdleF32 = 4e-9;
 constexpr int kIdleFrom = 3;                       // earlier sweeps (from 0) have none
 // Rotation (c, s) that makes two rows with squared norms al, be and inner product ga orthogonal:
 // with zeta = (be - al) / (2 ga), t = sign(zeta) / (|zeta| + sqrt(1 + zeta^2)), c = 1/sqrt(1+t^2),
@@ -601,11 +600,13 @@ __device__ __forceinline__ void apply_32(Row row, const double* J, int c0, int l
 static constexpr size_t jacobi_lds_bytes(int Lp) { return sizeof(double) * ((size_t)kJN * (Lp + 2) + kJWork); }
 
 // Up to 32 rows: one workgroup, one block pair.  A sweep is 31 steps, and a third as much for the Gram matrix and J^T times the rows, which
-// two sweeps on one Gram matrix need once (us, before and with it: l = 30 55 and 50, 20 67 and 64).
+// two sweeps on one Gram matrix need once (us, before and with it: l = 30 55 and 50, 20 67 and 64).  That matrix does not tell when to
+// stop: what is left of two rows that were nearly parallel is lost in it, and may be far from orthogonal.  After a pair of sweeps whose second
+// one met nothing above the bar, a fresh Gram matrix without anything above the idle bar ends the iteration, or a single sweep on it decides.
 constexpr int kTwoSweeps = 4;                      // from sweep 0 to 4, two at a time
 __global__ void __launch_bounds__(kJThreads, 2)
 k_jacobi_small(const double* __restrict__ R, int ldr, int l, int Lp, double* __restrict__ Wg, double* __restrict__ sig,
-               int* __restrict__ info, const int* __restrict__ breakdown_flag, double settled) {
+               int* __restrict__ info, const int* __restrict__ breakdown_flag, double settled, double idle) {
   extern __shared__ __align__(16) double W[];
   __shared__ int rotated;
   __shared__ int order_sh[kJN];
@@ -632,14 +633,17 @@ k_jacobi_small(const double* __restrict__ R, int ldr, int l, int Lp, double* __r
     if (c < Lp) W[i * ld + c] = v;
   }
   double* work = W + kJN * ld;
-  int sweeps = 0, converged = (l < 2);
+  int sweeps = 0, converged = (l < 2), quiet = 0;      // quiet: the second of a pair of sweeps met nothing above the bar
   auto row = [&](int x) { return W + x * ld; };
   while (!converged && sweeps < kMaxSweeps) {
     if (t == 0) rotated = 0;
     __syncthreads();
     gram_32(row, Lp, work, t);
-    // The first sweeps come in pairs on one Gram matrix: what the rotated matrix has lost by the second is little beside the cosines that are left.
-    const bool two = sweeps < kTwoSweeps;
+    if (quiet && !busy_32(work, t, true, idle)) {        // uniform over the workgroup
+      converged = 1;
+      break;
+    }
+    const bool two = sweeps < kTwoSweeps && !quiet;
     if (two) {
       sweep_32(work, t, true, settled * settled, true, true);
       ++sweeps;
@@ -649,7 +653,8 @@ k_jacobi_small(const double* __restrict__ R, int ldr, int l, int Lp, double* __r
       apply_32(row, work + 2 * kJN * kJN, c0, t & 63, [&](int x, int c, double v) { row(x)[c] = v; });
     __syncthreads();
     ++sweeps;
-    converged = rotated == 0;
+    quiet = rotated == 0;
+    converged = quiet && !two;
     __syncthreads();
   }
 #pragma unroll
@@ -927,7 +932,7 @@ int small_svd(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* br
     BRSVD_HIP_TRY(hipGetLastError());
   } else if (l <= kJN) {
     hipLaunchKernelGGL(k_jacobi_small, dim3(1), dim3(kJThreads), jacobi_lds_bytes(Lp), stream, R, ldr, l, Lp, w.W, w.sig, w.info,
-                       breakdown_flag, settled);
+                       breakdown_flag, settled, settled == kSettledF32 ? kIdleF32 : kIdle);
     BRSVD_HIP_TRY(hipGetLastError());
   } else {
     BRSVD_TRY(jacobi_global(R, ldr, l, Lp, w, breakdown_flag, settled, stream));

@@ -146,24 +146,48 @@ def test_small_svd_of_graded_rows(l, decades):
 @pytest.mark.parametrize("l", [30, 97, 200, 400])
 @pytest.mark.parametrize("q", [0, 1])
 @pytest.mark.parametrize("ratio", [1e-4, 1e-6])
-def test_vectors_of_steep_spectra(l, q, ratio):
-    """fp32 SVDs whose small factor has a condition of 1e4 and 1e6: V = W_B (R V_R / s) carries a cosine that the iteration leaves
+@pytest.mark.parametrize("f64", [False, True])
+def test_vectors_of_steep_spectra(l, q, ratio, f64):
+    """SVDs whose small factor has a condition of 1e4 and 1e6: V = W_B (R V_R / s) carries a cosine that the iteration leaves
     between rows i and j times s_i / s_j, so block pairs may only be passed over by a bar that knows the norms."""
     dev = need_gpu()
-    print(f"[case] steep spectrum l={l} q={q} ratio={ratio}", flush=True)
+    print(f"[case] steep spectrum l={l} q={q} ratio={ratio} f64={f64}", flush=True)
+    dt = torch.float64 if f64 else torch.float32
     m, n = 3 * l + 300, 3 * l + 200
     s = torch.exp(-torch.arange(2 * l, dtype=torch.float64) * (np.log(1 / ratio) / l))
-    A = synth.exact_spectrum_matrix(m, n, s, l + q, torch.float32).contiguous()
-    h = B.brsvd_create(B.make_params(m, n, l - 10, 10, q))
+    A = synth.exact_spectrum_matrix(m, n, s, l + q, dt).contiguous()
+    h = B.brsvd_create(B.make_params(m, n, l - 10, 10, q, dtype=B.BRSVD_DTYPE_F64 if f64 else B.BRSVD_DTYPE_F32))
     try:
-        U, S, Vt, st = B.brsvd_run(h, A.to(dev), synth.gaussian(n, l, 5).to(dev))
+        U, S, Vt, st = B.brsvd_run(h, A.to(dev), synth.gaussian(n, l, 5, dtype=dt).to(dev))
     finally:
         B.brsvd_destroy(h)
     eye = torch.eye(l, dtype=torch.float64, device=dev)
+    # fp32: entries rounded to 2^-24 of themselves leave a random matrix of variance 2^-48 in X^T X, of norm 2 sqrt(l) 2^-24.
+    # fp64: a row meets l rotations in each of up to ten sweeps, as a random walk sqrt(10 l) roundings; twice over for what R V / s adds
+    tol = 4 * 2 * np.sqrt(l) * np.sqrt(10 * l) * 2.0 ** -53 if f64 else 2 * np.sqrt(l) * 2.0 ** -24
     for X in (U.double(), Vt.double().T):
-        # entries rounded to 2^-24 of themselves leave a random matrix of variance 2^-48 in X^T X, of norm 2 sqrt(l) 2^-24
-        assert float(torch.linalg.norm(X.T @ X - eye, 2)) <= 2 * np.sqrt(l) * 2.0 ** -24
+        assert float(torch.linalg.norm(X.T @ X - eye, 2)) <= tol
     assert 0.3 * ratio < float(S[-1] / S[0]) < 3 * ratio and st["orth_fallbacks"] == 0
+
+
+@pytest.mark.parametrize("l", [17, 24, 32])
+@pytest.mark.parametrize("d", [1e-8, 1e-9])
+def test_small_svd_of_two_parallel_rows(l, d):
+    """Two rows e_i and e_i + d e_j in a random basis, the others orthogonal: the first rotation leaves nothing on the Gram matrix it was
+    taken from, but the rows it gives have a cosine of d / 2, which U = R V / s shows times s_1 / s_l.  The end of the iteration has
+    to be seen on a Gram matrix of the rows themselves."""
+    dev = need_gpu()
+    print(f"[case] parallel rows l={l} d={d}", flush=True)
+    eye = torch.eye(l, dtype=torch.float64)
+    for i, j in ((0, 8), (0, 16), (2, 3)):
+        for seed in range(60):
+            R = torch.diag(torch.linspace(3, 5, l, dtype=torch.float64))
+            R[j, j], R[i, i], R[j, i] = d, 1, 1
+            R = R @ torch.linalg.qr(torch.randn(l, l, generator=torch.Generator().manual_seed(seed), dtype=torch.float64))[0]
+            S, U, V, _ = (x.cpu() if isinstance(x, torch.Tensor) else x for x in B.brsvd_small_svd(R.to(dev).contiguous()))
+            assert float((V.T @ V - eye).abs().max()) <= 4e-13, (i, j, seed)
+            # U = R V / s: the rounding of R V, of rows of norm s_1, over s_l
+            assert float((U.T @ U - eye).abs().max()) <= 8 * 2.0 ** -53 * float(S[0] / S[-1]), (i, j, seed)
 
 
 def test_small_svd_of_equal_and_zero_values():
