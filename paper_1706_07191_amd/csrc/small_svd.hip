@@ -64,6 +64,10 @@ constexpr double kSettledF32 = 1e-5;
 // orthogonal, where the rounding of the panels leaves 2e-7.  The results' defects are the same to two digits with and without the bars
 // (l = 30 to 400, s_1 / s_l from 64 to 1e6; fp64 2e-15 to 1e-13).  (4e-9 and 1e-15 on the cosines left V of the SVD off by 3e-6 and 4e-14 at l =
 // 200 and a condition of 1e4, by 6e-4 and 1e-10 at 1e6.)
+// Over 32 rows, everything rotated and with the bars (us of the small SVD of an SVD run): fp32 l = 72 326 and 289, 97 450 and 431, 110 450 and
+// 431, 160 742 and 637, 272 1664 and 1555 (with 1e-12 72 304, 97 447, 110 430, 160 694, 272 1570); fp64 l = 110 532 and 504, 160 737 and 703, 272
+// 1897 and 1798.  Calls for dense factors (brsvd_small_svd) take any matrix, not the graded R of a range finder, and hardly ever meet an
+// idle pair (a panel's R, condition 100, without and with: l = 72 524 and 537, 110 693 and 711, 160 1081 and 1091): no bar for those.
 constexpr double kIdle = 1e-15, kIdleF32 = 4e-9;
 constexpr int kIdleFrom = 3;                       // earlier sweeps (from 0) have none
 // Rotation (c, s) that makes two rows with squared norms al, be and inner product ga orthogonal:
@@ -328,7 +332,7 @@ k_jacobi_rows(const double* __restrict__ R, int ldr, int l, int Lp, double* __re
 // a step without branches; a shorter chain; a ticket drawn ahead, one acquire for all waves (each costs 250 cycles).
 // Measured (us of the kernels, before and now): l = 24 68 -> 57, 30 85 -> 70, 48 199 -> 171 (row rotations before), 64 245 -> 206, 72 367 ->
 // 329 (row rotations before), 97 555 -> 447, 110 558 -> 451, 128 580 -> 464, 160 1312 -> 1040, 272 2197 -> 1686, 400 6078 -> 4454.
-// Since then fp32 results pass over pairs with nothing left to rotate (kIdleF32).
+// Since then SVD runs pass over pairs with nothing left to rotate (kIdle).
 constexpr int kJB = 16;
 constexpr int kJN = 2 * kJB;                      // rows of a block pair
 // Place of entry (x, y) of the Gram matrix and of J: odd rows have their halves exchanged, so that the two rows of 16
@@ -901,7 +905,7 @@ k_svd_outputs(const double* __restrict__ R, int ldr, int upper, const TO* __rest
   }
 }
 
-static int jacobi_global(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* breakdown_flag, double settled,
+static int jacobi_global(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* breakdown_flag, double settled, double idle,
                          hipStream_t stream) {
   static bool attr_set = false;
   if (!attr_set) {
@@ -912,7 +916,7 @@ static int jacobi_global(const double* R, int ldr, int l, int Lp, SvdWork& w, co
   hipLaunchKernelGGL(k_jacobi_init, dim3(Lp), dim3(128), 0, stream, R, ldr, l, Lp, w.W, w.sig, w.info, breakdown_flag);
   const int nblk = (int)ceil_div(l, kJB), nblk2 = (nblk + 1) & ~1;
   hipLaunchKernelGGL(k_jacobi_rounds, dim3(nblk2 / 2), dim3(kJThreads), jacobi_lds_bytes(Lp), stream, R, ldr, w.W, l, Lp, nblk2,
-                     settled, settled == kSettledF32 ? kIdleF32 : 0.0, w.sig, w.info);
+                     settled, idle, w.sig, w.info);
   BRSVD_HIP_TRY(hipGetLastError());
   return BRSVD_OK;
 }
@@ -923,6 +927,7 @@ int small_svd(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* br
   if (l < 1 || l > kMaxL || (open && (!open->Rx || Ur || Vr))) return BRSVD_ERR_ARG;
   // fp64 factors or singular values asked for: the strict bar; single-precision results only: the relaxed one
   const double settled = (sizeof(TO) == 4 && !S && !Ur && !Vr) ? kSettledF32 : kSettled;
+  const double idle = settled == kSettledF32 ? kIdleF32 : kIdle;
   const int nblk = (l + kJB - 1) / kJB;
   if (l <= kRowsMaxL || nblk == 3) {
     auto kern = nblk == 1 ? k_jacobi_rows<1, 8> : l <= 40 ? k_jacobi_rows<3, 24> : k_jacobi_rows<3, 32>;
@@ -932,10 +937,10 @@ int small_svd(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* br
     BRSVD_HIP_TRY(hipGetLastError());
   } else if (l <= kJN) {
     hipLaunchKernelGGL(k_jacobi_small, dim3(1), dim3(kJThreads), jacobi_lds_bytes(Lp), stream, R, ldr, l, Lp, w.W, w.sig, w.info,
-                       breakdown_flag, settled, settled == kSettledF32 ? kIdleF32 : kIdle);
+                       breakdown_flag, settled, idle);
     BRSVD_HIP_TRY(hipGetLastError());
   } else {
-    BRSVD_TRY(jacobi_global(R, ldr, l, Lp, w, breakdown_flag, settled, stream));
+    BRSVD_TRY(jacobi_global(R, ldr, l, Lp, w, breakdown_flag, settled, Ur || Vr ? 0.0 : idle, stream));
   }
   const dim3 tiles(Lp / kTile, Lp / kTile, 2);
   hipLaunchKernelGGL(k_svd_outputs<TO>, tiles, dim3(kTileWaves * 64), 0, stream, open ? open->Rx : R, ldr, open ? 1 : 0, open ? open->left : nullptr, w.W,
