@@ -1367,8 +1367,8 @@ int brsvd_orth(float* P, int64_t rows, int32_t l, int32_t method, double* R, int
       Basis<float> Q{};
       if (!as_is && (status = pad_panel(P, rows, l, P0, Lp, s)) != BRSVD_OK) break;
       if (hipMemsetAsync(w.flags, 0, 256, s) != hipSuccess) { status = BRSVD_ERR_HIP; break; }
-      if ((status = orth_basis(as_is ? P : P0, P1, rows, l, Lp, m_now, w, left, Rtot, true, &Q, s)) != BRSVD_OK) break;
-      if (Q.R2 && R && (status = triu_mul(Q.R2, Q.R1, l, Lp, Rtot, s)) != BRSVD_OK) break;
+      if ((status = orth_basis(as_is ? P : P0, P1, rows, l, Lp, m_now, w, left, Rtot, R != nullptr, &Q, s)) != BRSVD_OK) break;
+      if (Q.R2 && (status = triu_mul(Q.R2, Q.R1, l, Lp, Rtot, s)) != BRSVD_OK) break;
       int flag = 0;
       if (hipMemcpyAsync(&flag, w.flags, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess ||
           hipStreamSynchronize(s) != hipSuccess) { status = BRSVD_ERR_HIP; break; }

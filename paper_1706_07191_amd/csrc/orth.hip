@@ -8,6 +8,7 @@
 // The paper orthonormalises with a TSQR-based CAQR; range(P) -- all the method needs -- is the
 // same for any orthonormalisation.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "common.h"
@@ -205,10 +206,11 @@ k_gram(const T* __restrict__ P, int64_t rows, int Lp, int64_t rows_per_chunk, do
 // 128 87.4 -> 38.9, 160 151 -> 65, 272 383 -> 208, 400 895 -> 562.  Since then padding needs no pivots: l = 20 9.4 -> 8.3.
 // A pivot <= tol * its original diagonal entry is clamped to that value (lenient) or sets
 // flag[0] = 1 + column of its tile and ends the kernel.
-// A matrix close to the identity, as in the second sweep of CholeskyQR and after a Householder tree, needs no elimination: for G = I + E the factor is
-// R = I + N, N the strict upper triangle and half the diagonal of E, and R^-1 = I - N, both to the order of |E|_F^2.  Taken where |E|_F is at most
-// `near_eye`; the panels' precision sets it (near_eye_of).  Measured, elimination and this (us with the
-// launch): l = 20 9.4 and 4.1, 72 22 and 6.4, 97 29 and 8, 110 31 and 10, 160 63 and 15, 272 225 and 43.
+// A matrix close to the identity, as in the second sweep of CholeskyQR and after a Householder tree, needs no elimination: for G = I + E, and N the
+// strict upper triangle and half the diagonal of E, the factor is R = I + N - H, H the strict upper triangle and half the diagonal of N^T N,
+// and R^-1 = I - N, to the orders |E|_F^3 and |E|_F^2.  R^-1 is rounded to the panels' precision, R stays in fp64.  Taken where |E|_F is at most
+// `near_eye` (near_eye_of).  Measured, elimination and this with R (us): l = 20 8.0 and 4.0, 72 21 and 7.0, 97 30 and 11, 110 31 and 11, 160 62 and 29,
+// 272 192 and 97, 400 526 and 255; without R 7.6 and 3.4, 21 and 4.7, 28 and 7.3, 30 and 6.2, 58 and 12, 177 and 28, 494 and 61.
 constexpr int kNB = 16;
 constexpr int kCholLdsMaxLp = 128;    // largest padded size whose fp64 matrix fits the LDS
 
@@ -344,12 +346,46 @@ k_chol_inv(double* __restrict__ G, int l, int Lp, double* __restrict__ Rout, TO*
     e2 = 0.0;
     for (int w = 0; w < nw; ++w) e2 += off_eye[w];
     if (e2 <= near_eye * near_eye) {  // (not when it is NaN)
-#pragma unroll 8
-      for (int idx = tid; idx < l * l; idx += blockDim.x) {
-        const int i = idx / l, j = idx - i * l;
-        const double d = i == j ? 1.0 : 0.0, n = i > j ? 0.0 : M[(int64_t)i * ld + j] - d, half = i == j ? 0.5 * n : n;
-        if (Rout) Rout[(int64_t)i * Lp + j] = d + half;
-        if (i <= j) Rinv_out[(int64_t)i * Lp + j] = (TO)(d - half);
+      const bool second = Rout && e2 > 1.6e-17;            // otherwise H is less than a rounding
+      auto n_at = [&](int i, int j) {
+        const double v = M[(int64_t)i * ld + j];
+        return i < j ? v : (i == j ? 0.5 * (v - 1.0) : 0.0);
+      };
+      for (int t = wave; t < nb * (nb + 1) / 2; t += nw) {
+        int ti = 0, rem = t;
+        while (rem >= nb - ti) { rem -= nb - ti; ++ti; }
+        const int tj = ti + rem, col = kNB * tj + r;
+        doublex4 h = {0.0, 0.0, 0.0, 0.0};
+        if (second) {
+          double a[4], b[4];
+          const double *pa = M + (int64_t)g * ld + kNB * ti + r, *pb = M + (int64_t)g * ld + col;
+          for (int k = 0; k < ti; ++k) {                     // tiles above the diagonal ones: N is E there
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) { a[kk] = pa[4 * kk * ld]; b[kk] = pb[4 * kk * ld]; }
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) h = mfma_f64(a[kk], b[kk], h);
+            pa += kNB * ld;
+            pb += kNB * ld;
+          }
+#pragma unroll
+          for (int kk = 0; kk < 4; ++kk) {
+            a[kk] = n_at(kNB * ti + 4 * kk + g, kNB * ti + r);
+            b[kk] = n_at(kNB * ti + 4 * kk + g, col);
+          }
+#pragma unroll
+          for (int kk = 0; kk < 4; ++kk) h = mfma_f64(a[kk], b[kk], h);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int row = kNB * ti + g + 4 * v;
+          if (row >= l || col >= l) continue;
+          const double d = row == col ? 1.0 : 0.0, n = n_at(row, col);
+          if (row <= col) Rinv_out[(int64_t)row * Lp + col] = (TO)(d - n);
+          if (Rout) {
+            Rout[(int64_t)row * Lp + col] = row <= col ? d + (n - (row == col ? 0.5 : 1.0) * h[v]) : 0.0;
+            if (ti < tj) Rout[(int64_t)col * Lp + row] = 0.0;
+          }
+        }
       }
       return;
     }
@@ -869,9 +905,10 @@ template int triu_mul<float>(const double*, const float*, int, int, double*, hip
 template int triu_mul<double>(const double*, const double*, int, int, double*, hipStream_t);
 
 constexpr double kPivotTol = 1e-12;
-// |G - I|_F up to which the factor of G is taken to first order: its square, by which factor and inverse are off at most, is a sixth of the rounding of the panels
-// (1e-8 of 6e-8, and 1.6e-17 of 1.1e-16).
-template <typename T> constexpr double near_eye_of() { return sizeof(T) == 4 ? 1e-4 : 4e-9; }
+// |G - I|_F up to which the factor of G (l x l) is not eliminated.  R, in fp64, is then off by at most |E|_F^3 / 2, a quarter of a rounding for each of
+// the l steps of an elimination, its inverse by |E|_F^2 / 2, which in the panels' precision is a hundredth of a rounding (8e-10 of 6e-8 at l = 272)
+// and a seventh (8e-18 of 1.1e-16).  First sweeps of panels with conditions up to a few hundred leave 5e-7 to 2e-5 in fp32.
+template <typename T> double near_eye_of(int l) { return sizeof(T) == 4 ? cbrt(l * 0x1p-52) : 4e-9; }
 // Only the last sweep of a basis that reaches the output must succeed without clamped pivots (its
 // input is then already nearly orthonormal, so a small pivot there means the panel really lost
 // rank to working precision).  Earlier sweeps, and the single sweep of an intermediate panel, clamp:
@@ -887,7 +924,7 @@ int cholqr_sweeps(T* P, T* tmp, int64_t rows, int l, int Lp, int nsweeps, OrthWo
     BRSVD_TRY(gram<T>(src, rows, Lp, w, stream));
     const int lenient = (sweep + 1 < nsweeps || !strict_last) ? 1 : 0;
     double* Rs = (Rtot || publish_R) ? w.R[sweep] : nullptr;      // the factor is only written out when someone reads it
-    BRSVD_TRY(chol_inv<T>(w.G, l, Lp, Rs, w.Rinv, w.flags, kPivotTol, stream, 0, lenient, lenient ? 0.0 : near_eye_of<T>()));
+    BRSVD_TRY(chol_inv<T>(w.G, l, Lp, Rs, w.Rinv, w.flags, kPivotTol, stream, 0, lenient, lenient ? 0.0 : near_eye_of<T>(l)));
     BRSVD_TRY(apply_panel(src, rows, Lp, w.Rinv, dst, Lp, Lp, w.gemm_scratch, w.gemm_scratch_bytes, stream));
     BRSVD_TRY(apply_to_companion<T>(w, Lp, stream));
     T* t = src; src = dst; dst = t;
@@ -938,7 +975,7 @@ int orth_basis(T* P, T* tmp, int64_t rows, int l, int Lp, int method, OrthWorkT<
     BRSVD_TRY(cholqr_sweeps<T>(P, tmp, rows, l, Lp, 1, w, nullptr, &out->panel, stream, false, want_R));
     BRSVD_TRY(gram<T>(out->panel, rows, Lp, w, stream));
   }
-  BRSVD_TRY(chol_inv<T>(w.G, l, Lp, want_R ? w.R[1] : nullptr, left, w.flags, kPivotTol, stream, 0, 0, near_eye_of<T>()));
+  BRSVD_TRY(chol_inv<T>(w.G, l, Lp, want_R ? w.R[1] : nullptr, left, w.flags, kPivotTol, stream, 0, 0, near_eye_of<T>(l)));
   out->left = left;
   out->R1 = want_R ? w.R[0] : nullptr;
   out->R2 = want_R ? w.R[1] : nullptr;

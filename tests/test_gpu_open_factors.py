@@ -52,7 +52,7 @@ def test_open_bases(k, p, q, f64, full):
 @pytest.mark.parametrize("l", [15, 16, 17, 128, 129])
 @pytest.mark.parametrize("spread", [1.0, 1e3])
 def test_second_factor_on_both_sides_of_the_line(l, spread):
-    """brsvd_orth: with columns of equal weight the second factor is next to the identity and taken to first order; a spread of 1e3 and parallel
+    """brsvd_orth: with columns of equal weight the second factor is next to the identity and not eliminated; a spread of 1e3 and parallel
     columns take it past the line for some of the sizes.  Q must be orthonormal and P = Q R either way."""
     dev = need_gpu()
     m = 3000
@@ -69,9 +69,48 @@ def test_second_factor_on_both_sides_of_the_line(l, spread):
     defect = float(torch.linalg.norm(Q.T @ Q - torch.eye(l, dtype=torch.float64), 2))
     back = float(torch.linalg.norm(Q @ R - P.double()) / torch.linalg.norm(P.double()))
     note(f"[second factor l={l} spread={spread}] defect={defect:.2e} back={back:.2e}")
-    # Q's entries are rounded to eps each and its last product sums l terms; the first-order factor leaves 1e-8 at most.
+    # Q's entries are rounded to eps each and its last product sums l terms; the factor leaves 1e-9 at most.
     assert not fallback and defect <= 4 * np.sqrt(l) * eps + 1e-8 and back <= 8 * np.sqrt(l) * eps, (defect, back)
     assert bool((torch.tril(R, -1) == 0).all()) and bool((torch.diagonal(R) > 0).all())
+
+
+def _panel_with_known_factors(l, s, pairs):
+    """Rows of at most two numbers, all powers of two, so that P R1^-1 comes out the same in whatever order it is summed.  For columns (c, d) of a pair
+    the Gram matrix is [[4^s, 4^s - 1], [4^s - 1, 4^s - 1 + b]], whose elimination is exact: R1 = [[2^s, 2^s - 2^-s], [0, sqrt(b + 1 - 4^-s)]]."""
+    rows, R1 = [], torch.eye(l, dtype=torch.float64)
+    for t, (c, d) in enumerate(pairs):
+        b = 1 + t % 7
+        rows += [((c, 2.0 ** i), (d, 2.0 ** i)) for i in range(s) for _ in range(3)]
+        rows += [((c, 1.0),)] + [((d, 1.0),)] * b
+        R1[c, c], R1[c, d], R1[d, d] = 2.0 ** s, 2.0 ** s - 2.0 ** -s, np.sqrt(b + 1 - 4.0 ** -s)
+    alone = set(range(l)) - {x for p in pairs for x in p}
+    rows += [((c, 1.0),) for c in sorted(alone)]
+    P = torch.zeros(max(len(rows), l), l)
+    for i, row in enumerate(rows):
+        for c, v in row:
+            P[i, c] = v
+    return P, R1
+
+
+@pytest.mark.parametrize("l", [2, 16, 30, 47, 128, 160, 272])
+@pytest.mark.parametrize("s", [3, 5, 6, 7, 8, 10])
+def test_factor_of_a_basis_is_exact(l, s):
+    """The factor R = R2 R1 that brsvd_orth returns in fp64, where R2 is next to the identity and not eliminated (|R2^T R2 - I| = 1e-7 to 3e-5) and past
+    that line (to 2e-4): the Cholesky factor of the Gram matrix of the rounded first basis times R1."""
+    dev = need_gpu()
+    print(f"[case] exact factor l={l} s={s}", flush=True)
+    # within a tile of 16 and across tiles, no column twice
+    pairs = [(c, c + 20 if c % 16 and c + 20 < l else c + 1 + c // 16 % 3) for c in range(0, l - 3, 8)] or [(0, 1)]
+    P, R1 = _panel_with_known_factors(l, s, pairs)
+    inv = torch.linalg.inv(R1).float().double()
+    Q1 = (P.double() @ inv).float().double()              # two exact products, one rounding
+    R2 = torch.linalg.cholesky(Q1.T @ Q1).T
+    Q, R, fallback = B.brsvd_orth(P.to(dev).clone(), want_R=True)
+    e2 = float(torch.linalg.norm(Q1.T @ Q1 - torch.eye(l, dtype=torch.float64)))
+    rel = float((R.cpu() - R2 @ R1).abs().max() / R1.abs().max())
+    note(f"[exact factor l={l} s={s}] |E|={e2:.1e} rel={rel:.1e}")
+    # R1, R2 and their product to a few roundings in 64 bits; what is left out of R2 is below a quarter of a rounding for each of its rows
+    assert not fallback and rel <= (4 + l / 4) * 2.0 ** -53, (e2, rel)
 
 
 @pytest.mark.parametrize("rows,l", [(64, 16), (1001, 32), (3001, 64), (2000, 144)])
