@@ -714,6 +714,14 @@ k_apply(const float* __restrict__ P, int64_t rows, const float* __restrict__ X, 
   }
 }
 
+// Between LDS accesses of the lanes of one wave to each other's numbers: those before it are done and seen by all lanes.  (The hardware keeps a
+// wave's LDS accesses in order; this keeps the compiler to it.)
+__device__ __forceinline__ void wave_exchange() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // The same with the Gram matrix of what is written, for the second sweep of CholeskyQR: that saves a read of the panel.  A wave puts each tile in LDS (its own
 // place, no barrier) and takes it up again in the order of the Gram kernel's operands; Gpart as there, one part per workgroup.
 // What bounds it: the panel's read and write, as before; the fp64 matrix instructions run under them.  Measured, product, Gram matrix and its sum, and with
@@ -785,6 +793,7 @@ k_rows_gram(const float* __restrict__ A, int64_t lda, int64_t rows, int K, const
       if (row < rows) *(floatx4*)(out + row * Lp + 16 * t + 4 * g) = acc[t];
       *(floatx4*)(mine + r * LD + 16 * t + 4 * g) = row < rows ? acc[t] : floatx4{0.f, 0.f, 0.f, 0.f};
     }
+    wave_exchange();
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       double b[NT];
@@ -796,6 +805,7 @@ k_rows_gram(const float* __restrict__ A, int64_t lda, int64_t rows, int K, const
 #pragma unroll
         for (int j = i; j < NT; ++j) { gram[t] = mfma_f64(b[i], b[j], gram[t]); ++t; }
     }
+    wave_exchange();                               // the next tile goes where this one was read
   }
   gram_store<NT, NT, true, WAVES>(gram, Lp, 0, 0, red, Gpart + (int64_t)blockIdx.x * Lp * Lp, tid);
 }

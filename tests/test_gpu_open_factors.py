@@ -150,6 +150,26 @@ def test_gram_over_all_block_sizes(l):
             assert not fallback and defect <= 4 * np.sqrt(l) * eps + 1e-8 and back <= 8 * np.sqrt(l) * eps, (rows, method, defect, back)
 
 
+@pytest.mark.parametrize("l", [1, 16, 17, 32, 33, 48])
+@pytest.mark.parametrize("rows", [49, 127, 128, 129, 32767, 32769, 65553, (1 << 20) + 5])
+def test_narrow_panels_with_the_gram_matrix_of_the_product(rows, l):
+    """Panels of up to three tiles, whose second Gram matrix is formed by the waves that apply the first factor, tile by tile through LDS: as many rows
+    as a wave, a workgroup and all of them have at a time, and a few more or less.  Q^T Q = I and P = Q R."""
+    dev = need_gpu()
+    print(f"[case] product and Gram matrix {rows} x {l}", flush=True)
+    P = torch.randn(rows, l, generator=torch.Generator().manual_seed(rows + l))
+    P[:, 0] *= 30.0
+    P[-1] *= 10.0                                     # the last row counts
+    P = P.to(dev)
+    Q, R, fallback = B.brsvd_orth(P.clone(), want_R=True)
+    Q, P = Q.double(), P.double()
+    eps = 2.0 ** -24
+    defect = float(torch.linalg.norm(Q.T @ Q - torch.eye(l, dtype=torch.float64, device=dev), 2))
+    back = float(torch.linalg.norm(Q @ R - P) / torch.linalg.norm(P))
+    # as in the test of all block sizes
+    assert not fallback and defect <= 4 * np.sqrt(l) * eps + 1e-8 and back <= 8 * np.sqrt(l) * eps, (defect, back)
+
+
 @pytest.mark.parametrize("n,l,m", [(100, 20, 131077), (64, 32, 131077), (61, 16, 4096), (128, 17, 4101), (127, 32, 40001), (33, 9, 4101), (17, 17, 131077),
                                    (65, 32, 4096)])
 def test_tall_matrices_of_short_rows(n, l, m):
