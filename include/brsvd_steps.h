@@ -71,7 +71,8 @@ int brsvd_small_svd_static(const double* R, int32_t l, double* S, double* Ur, do
 
 /* How the plain kernels of the two thin products would cut them into workgroups (host-only, no GPU call): for checking the
  * plans' invariants and for reading profiles.  Wide fp32 panels over large A take other kernels with plans of their own
- * (csrc/gemm_split.hip) when the scratch allows it.  which = 0: Y = A X with A rows x n, out12 = {rows per
+ * (csrc/gemm_split.hip) when the scratch allows it.  The plans of the plain kernels are functions of the sizes: scratch
+ * beyond brsvd_gemm_scratch_bytes changes neither them nor the order of a sum.  which = 0: Y = A X with A rows x n, out12 = {rows per
  * tile, row tiles, chunks per tile C, whole tiles, leftover tiles, main splits f, tail chunks x, tail
  * strips per workgroup j, partial panels per leftover tile, workgroups, column groups, column tiles per
  * group}.  which = 1: Z += A^T Q, out12 = {m-tiles per wave, waves, column tiles, row blocks,

@@ -1199,7 +1199,7 @@ int brsvd_gemm_plan(int32_t which, int64_t rows, int64_t n, int32_t l, int64_t b
   if (which == 0) gemm_an_plan_describe(rows, n, padded_l(l), esz, out12);
   else if (which == 1) gemm_at_plan_describe(rows, n, padded_l(l), block_rows, esz, out12);
   else if (which == 2) {
-    const uint64_t an = gemm_an_scratch_bytes(rows, n, padded_l(l), esz);
+    const uint64_t an = gemm_an_split_bytes(rows, n, padded_l(l), esz);
     const uint64_t at = gemm_at_scratch_bytes(rows, n, padded_l(l), block_rows, esz);
     for (int i = 0; i < 12; ++i) out12[i] = 0;
     out12[0] = (int32_t)(an & 0x7fffffff); out12[1] = (int32_t)(an >> 31);

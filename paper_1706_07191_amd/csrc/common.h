@@ -55,6 +55,8 @@ struct KernelEvents {
 // Y (rows x ncols, ldy) = A (rows x K, lda) * X (K x Lp padded panel, ldx = Lp).
 // scratch holds partial sums when the launch is split along K.  fp32 and fp64 (esz = element size).
 uint64_t gemm_an_scratch_bytes(int64_t rows, int64_t K, int Lp, int esz = 4);
+// Bytes of the partial panels that are used where the scratch is also enough for gemm_at of the same A (small products are cut further then).
+uint64_t gemm_an_split_bytes(int64_t rows, int64_t K, int Lp, int esz = 4);
 int gemm_an(const float* A, int64_t lda, int64_t rows, int64_t K, const float* X, int Lp,
             float* Y, int64_t ldy, int ncols, void* scratch, uint64_t scratch_bytes,
             hipStream_t stream, const KernelEvents* ev = nullptr);

@@ -798,23 +798,34 @@ static AnPlan an_plan(int64_t rows, int64_t K, int nt, int esz) {
   return p;
 }
 
-// The plan of a small product with all the scratch there is.  Where no tile has a workgroup to itself in a full round and the pieces of an_plan leave most slots
-// empty, the contraction is cut into as many pieces f as a model of the time likes best: a workgroup's chunks one after the other, each the latency of a
-// barrier and its matrix instructions, and the partial panels' way to memory and back with a launch for their sum.
-// Measured (us, product and sum, before and now): 2000x1000 l=30 17.4 and 10.2, 2000x2000 l=24 19.2 and 12.3, 1000x3000 l=24 20.6 and 12.1, 3000x600 l=40 23.7 and 13.1,
-// 8000x480 l=30 16.2 and 11.5, 1500x1000 l=100 34.0 and 19.8, 1000x1000 l=300 82 and 41.
-static AnPlan an_plan_with(int64_t rows, int64_t K, int nt, int esz, int Lp, uint64_t scratch_bytes) {
+// Rows that take part in a split sum: those of the leftover tiles.
+static int64_t an_partial_rows(const AnPlan& p, int64_t rows) {
+  return p.nsplit > 0 ? rows - (int64_t)p.sh.whole * p.tile_rows : 0;
+}
+// Bytes of its partial panels.
+static uint64_t an_need(const AnPlan& p, int64_t rows, int Lp, int esz) { return (uint64_t)p.nsplit * an_partial_rows(p, rows) * Lp * esz; }
+
+// The plan that is launched.  Where no tile has a workgroup to itself in a full round and the pieces of an_plan leave most slots
+// empty (small products), the contraction is cut into as many pieces f as a model of the time likes best: a workgroup's chunks one after the
+// other, each the latency of a barrier and its matrix instructions, and the partial panels' way to memory and back with a launch for
+// their sum.  A function of the shape, as the sums' order follows it: the pieces' panels fit what the two products of this shape ask
+// for (gemm_an_scratch_bytes, gemm_at_scratch_bytes).  Products with an l x l factor may have less, and then keep an_plan.
+// Measured (us, product and sum, before and now): 2000x1000 l=30 17.4 and 10.2, 2000x2000 l=24 19.2 and 12.3, 1000x3000 l=24 20.6 and 12.1, 3000x600
+// l=40 23.7 and 13.1, 8000x480 l=30 16.2 and 11.5, 1500x1000 l=100 34.0 and 19.8, 1000x1000 l=300 82 and 41.
+static AnPlan an_plan_launched(int64_t rows, int64_t K, int nt, int esz, int Lp) {
   AnPlan p = an_plan(rows, K, nt, esz);
   const AnCfg c = an_cfg(nt, esz, K);
   const bool narrow = esz == 4 && nt <= kAnNarrowMaxNT && K >= kAnNarrowMinK;
   const int T = p.row_tiles, C = p.sh.C, S = wg_slots(2 * c.kc * (nt * 16 + 4) * esz, an_wg_per_cu_regs(esz, c.waves));
-  if (narrow || 2 * T > S || (p.sh.whole > 0 && p.sh.whole < T)) return p;
+  const int most = std::min(S / T, C / 2);
+  if (narrow || most < 2 || (p.sh.whole > 0 && p.sh.whole < T)) return p;
+  const uint64_t room = std::max(an_need(p, rows, Lp, esz), gemm_at_scratch_bytes(rows, K, Lp, rows, esz));
   const double chunk = (1500 + c.waves / 4 * c.mt * nt * c.kc * (esz == 8 ? 16 : 8)) / 2400.0;      // us
   const double panel = (double)rows * Lp * esz;
   auto cost = [&](int f) { return (double)ceil_div(C, f) * chunk + (f > 1 ? 2.5 + f * panel / 1.5e6 : 0.0); };
   int best = std::max(p.nsplit, 1);
   double least = 0.85 * cost(best);
-  for (int f = 2; f <= std::min(S / T, C / 2) && (uint64_t)f * (uint64_t)panel <= scratch_bytes; ++f)
+  for (int f = 2; f <= most && (uint64_t)f * (uint64_t)panel <= room; ++f)
     if (cost(f) < least) { best = f; least = cost(f); }
   if (best == std::max(p.nsplit, 1)) return p;
   p.sh.whole = 0;
@@ -825,21 +836,18 @@ static AnPlan an_plan_with(int64_t rows, int64_t K, int nt, int esz, int Lp, uin
   return p;
 }
 
-// Rows that take part in a split sum: those of the leftover tiles.
-static int64_t an_partial_rows(const AnPlan& p, int64_t rows) {
-  return p.nsplit > 0 ? rows - (int64_t)p.sh.whole * p.tile_rows : 0;
-}
-
 uint64_t gemm_an_scratch_bytes(int64_t rows, int64_t K, int Lp, int esz) {
   NGroups ng = column_groups(Lp, esz);
-  AnPlan p = an_plan(rows, K, ng.nt, esz);
-  return (uint64_t)p.nsplit * an_partial_rows(p, rows) * Lp * esz;
+  return an_need(an_plan(rows, K, ng.nt, esz), rows, Lp, esz);
+}
+uint64_t gemm_an_split_bytes(int64_t rows, int64_t K, int Lp, int esz) {
+  return an_need(an_plan_launched(rows, K, column_groups(Lp, esz).nt, esz, Lp), rows, Lp, esz);
 }
 
 // The launch plans as plain numbers, for host-side checks of their invariants.
 void gemm_an_plan_describe(int64_t rows, int64_t K, int Lp, int esz, int32_t out[12]) {
   NGroups ng = column_groups(Lp, esz);
-  AnPlan p = an_plan(rows, K, ng.nt, esz);
+  AnPlan p = an_plan_launched(rows, K, ng.nt, esz, Lp);
   const int32_t v[12] = {p.tile_rows, p.row_tiles, p.sh.C, p.sh.whole, p.sh.lt, p.sh.f, p.sh.x, p.sh.j, p.nsplit, p.wgs,
                          ng.groups, ng.nt};
   for (int i = 0; i < 12; ++i) out[i] = v[i];
@@ -998,9 +1006,10 @@ static int gemm_an_t(const T* A, int64_t lda, int64_t rows, int64_t K, const T* 
   if (rows > INT32_MAX || K > INT32_MAX) return BRSVD_ERR_ARG;
   constexpr int esz = (int)sizeof(T);
   NGroups ng = column_groups(Lp, esz);
-  const AnPlan p = an_plan_with(rows, K, ng.nt, esz, Lp, scratch_bytes);
+  AnPlan p = an_plan_launched(rows, K, ng.nt, esz, Lp);
+  if (scratch_bytes < an_need(p, rows, Lp, esz)) p = an_plan(rows, K, ng.nt, esz);
   const int64_t prows = an_partial_rows(p, rows);
-  if (scratch_bytes < (uint64_t)p.nsplit * prows * Lp * esz) return BRSVD_ERR_BUDGET;
+  if (scratch_bytes < an_need(p, rows, Lp, esz)) return BRSVD_ERR_BUDGET;
   if (verbose())
     fprintf(stderr, "[brsvd] gemm_an f%d rows=%ld K=%ld Lp=%d: %d whole tiles + %d leftover tiles x %d splits + tail of %d "
             "chunks (%d per workgroup), %d chunks per tile, %d workgroups\n", esz * 8, (long)rows, (long)K, Lp,

@@ -247,3 +247,24 @@ def test_small_products_cut_along_the_contraction(rows, n, l, f64):
     eps = 2.0 ** -53 if f64 else 2.0 ** -24
     assert float(((Y.double() - want).abs() / size).max()) <= 4 * np.sqrt(n) * eps
     assert torch.equal(Y, B.brsvd_gemm_an(A.to(dev), X.to(dev)).cpu())
+
+
+@pytest.mark.parametrize("rows,n,l", [(2000, 1000, 30), (78, 98, 49), (98, 3443, 57), (562, 554, 235), (120, 2611, 53), (17841, 469, 197)])
+@pytest.mark.parametrize("f64", [False, True])
+def test_scratch_beyond_the_need_changes_no_bit(rows, n, l, f64):
+    """A product and the order of its sums are functions of the sizes: with the scratch that is asked for and with 64 times as much the same bits."""
+    dev = need_gpu()
+    print(f"[case] scratch {rows} x {n} l={l} f64={f64}", flush=True)
+    dt = torch.float64 if f64 else torch.float32
+    A = synth.gaussian(rows, n, 121, dtype=dt).to(dev)
+    X = synth.gaussian(n, l, 122, dtype=dt).to(dev)
+    fn = B.lib().brsvd_gemm_an_f64 if f64 else B.lib().brsvd_gemm_an
+    need = B.brsvd_gemm_scratch_bytes(rows, n, l, f64=f64)
+    out = []
+    for size in (need, 64 * need):
+        scratch = torch.empty(size, dtype=torch.uint8, device=dev)
+        Y = torch.empty(rows, l, dtype=dt, device=dev)
+        assert fn(A.data_ptr(), n, rows, n, X.data_ptr(), l, Y.data_ptr(), scratch.data_ptr(), size, None) == B.BRSVD_OK
+        torch.cuda.synchronize()
+        out.append(Y)
+    assert torch.equal(out[0], out[1])

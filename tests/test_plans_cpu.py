@@ -75,6 +75,37 @@ def test_gemm_an_plan_covers_every_unit_once(rows, K, l, dtype):
     _check_an(rows, K, l, dtype)
 
 
+@pytest.mark.parametrize("rows,K,l,f64,cut", [
+    (2000, 1000, 30, False, True), (2000, 2000, 24, False, True), (1000, 3000, 24, False, True), (8000, 480, 30, False, True),
+    (1500, 1000, 100, False, True), (1000, 1000, 300, False, True), (1500, 1200, 40, True, True), (3000, 600, 64, True, True),
+    (2000, 1000, 16, False, False),                  # one column tile over long rows has a kernel and a plan of its own
+    (40000, 480, 30, False, False),                  # more than half as many tiles as slots
+    (2000, 192, 30, False, False)])                  # three chunks: not two pieces of two
+def test_gemm_an_plan_of_small_products(rows, K, l, f64, cut):
+    """The plan that is reported is the launched one: small products are cut along the contraction until the chip is busy."""
+    dtype = B.BRSVD_DTYPE_F64 if f64 else B.BRSVD_DTYPE_F32
+    _check_an(rows, K, l, dtype)
+    _, T, C, whole, lt, f, x, j, nsplit, wgs, _, _ = B.brsvd_gemm_plan(0, rows, K, l, 0, dtype)
+    assert (whole == 0 and lt == T and x == 0 and f == nsplit >= 2 and wgs == T * f and C >= 2 * f) == cut
+
+
+def test_gemm_an_plan_random_small_shapes():
+    rng = random.Random(17067191)
+    cuts = 0
+    for _ in range(600):
+        rows, K, l = rng.randint(1, 20000), rng.randint(64, 6000), rng.randint(1, 512)
+        dtype = rng.choice([B.BRSVD_DTYPE_F32, B.BRSVD_DTYPE_F64])
+        _check_an(rows, K, l, dtype)
+        plan = B.brsvd_gemm_plan(0, rows, K, l, 0, dtype)
+        cuts += plan[3] == 0 and plan[8] >= 2
+        an, at = B.brsvd_gemm_plan(2, rows, K, l, 0, dtype)[:2], B.brsvd_gemm_plan(2, rows, K, l, 0, dtype)[2:4]
+        # inside what the two products of this shape ask for
+        panel = -(-max(rows, K) * ((l + 15) // 16 * 16) * (8 if dtype == B.BRSVD_DTYPE_F64 else 4) // 256) * 256
+        assert an[0] + (an[1] << 31) <= B.brsvd_gemm_scratch_bytes(rows, K, l, f64=dtype == B.BRSVD_DTYPE_F64) - 2 * panel
+        assert at[0] + (at[1] << 31) <= B.brsvd_gemm_scratch_bytes(rows, K, l, f64=dtype == B.BRSVD_DTYPE_F64) - 2 * panel
+    assert cuts > 100
+
+
 def test_gemm_an_plan_random_shapes():
     rng = random.Random(1706)
     for _ in range(400):
