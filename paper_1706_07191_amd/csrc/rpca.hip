@@ -204,10 +204,21 @@ k_rpca_update_vec(const T* __restrict__ M, const T* __restrict__ U, const T* __r
       }
     }
   }
-  // The singular values come in descending order: those from `terms` on are shrunk to zero and add nothing (five of 20 left: 2073600x100 640 -> 610 us,
-  // 76800x2000 437 -> 432).
+  // The singular values come in descending order (NaN first): those from `terms` on are shrunk to zero and add nothing (five of 20 left: 2073600x100
+  // 640 -> 610 us, 76800x2000 437 -> 432).  Looked for with scalar loads (vector loads would wait for those of M before them), one after the
+  // other up to 32, by bisection above.  Where all are left (us, without a look, one after the other, by bisection): l = 20 2073600x100 660, 672 and 684,
+  // 76800x2000 441, 443 and 448; l = 50 2073600x100 1035, 1083 and 1041; l = 120 76800x2000 940, 1104 and 948; l = 300 20000x2000 557, 715 and 568.
   int terms = 0;
-  while (terms < l && !(sig[terms] <= inv_mu)) ++terms;
+  if (l <= 32) {
+    while (terms < l && !(sig[terms] <= inv_mu)) ++terms;
+  } else {
+    for (int end = l; terms < end;) {
+      const int mid = (terms + end) >> 1;
+      const bool left = __builtin_amdgcn_readfirstlane(!(sig[mid] <= inv_mu)) != 0;      // scalar, like all that depends on it
+      terms = left ? mid + 1 : terms;
+      end = left ? end : mid;
+    }
+  }
   for (int idx = tid; idx < tile_rows * l; idx += NTHREADS) {
     const int i = idx / l, t = idx - i * l;
     const int64_t row = row0 + i;

@@ -358,3 +358,33 @@ def test_norms_at_every_alignment(dtype, off, m, n):
         x = Md - L + Md / (float(Mb.abs().max()) / lam) / 0.7   # S = shrink(M - L + Y0 / mu0, lambda / mu0), Y0 = M / J
         t = lam / 0.7
         assert float((S - (x - x.clamp(-t, t))).abs().max()) <= 16 * eps * 60.0
+
+
+@pytest.mark.parametrize("l", [5, 32, 33, 64, 100, 300])
+@pytest.mark.parametrize("f64", [False, True])
+def test_singular_values_left_after_the_shrinkage(l, f64):
+    """One iteration on a matrix of rank l - 1 with known singular values: from none to all of them are above the threshold, and L is the matrix with
+    its singular values shrunk."""
+    dev = need_gpu()
+    dt = torch.float64 if f64 else torch.float32
+    m, n, r = 700, 360, l - 1
+    s = torch.linspace(3.0, 1.0, r, dtype=torch.float64)
+    M = synth.exact_spectrum_matrix(m, n, s, l, torch.float64)
+    u, _, vt = torch.linalg.svd(M, full_matrices=False)
+    M = M.to(dt)
+    lam = 1e-4
+    J = float(M.double().abs().max()) / lam                     # the multiplier starts as M / J
+    assert J > 10
+    h = B.brsvd_create(B.make_params(m, n, r, 1, 1, dtype=B.BRSVD_DTYPE_F64 if f64 else B.BRSVD_DTYPE_F32))
+    try:
+        for left in sorted({0, 1, r // 2, r - 1, r}):
+            print(f"[case] shrinkage l={l} f64={f64} left={left}", flush=True)
+            edge = [4.0] + s.tolist() + [0.0]
+            t = (edge[left] + edge[left + 1]) / 2               # between the last value that is left and the next
+            x = t / (1 - t / J)                                 # 1 / mu, as the matrix decomposed is M (1 + 1 / (J mu))
+            L = B.brsvd_rpca_ialm_tol(h, M.to(dev), synth.gaussian(n, l, 9, dtype=dt).reshape(1, n, l).to(dev), 1, 0.0, lam, 1 / x, 1.5, norm2_M=3.0)[0]
+            want = (u[:, :r] * (s * (1 + x / J) - x).clamp(min=0)) @ vt[:r]
+            # fp32: the SVD's values and vectors to 1e-6 of the largest value, over gaps that L, a function of the matrix, does not see
+            assert float((L.double().cpu() - want).norm()) <= (1e-11 if f64 else 1e-5) * float(s.norm())
+    finally:
+        B.brsvd_destroy(h)
