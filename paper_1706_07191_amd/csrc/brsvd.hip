@@ -1102,9 +1102,8 @@ static int create_impl(const brsvd_params* params, brsvd_handle* handle_out) {
     } else {
       h->arena = (char*)params->workspace;      // resolve_block has checked that it is large enough
     }
-    if (hipMemset(h->arena + h->lay.gram_part, 0, (size_t)h->lay.gram_chunks * h->Lp * h->Lp * 8) != hipSuccess) {
-      status = BRSVD_ERR_HIP; break;
-    }
+    // nothing in the arena has to be cleared, but a workspace that is no device memory is refused here
+    if (hipMemset(h->arena + h->lay.flags, 0, 256) != hipSuccess) { status = BRSVD_ERR_HIP; break; }
     if (hipHostMalloc((void**)&h->host_flags, kAlign + 64, hipHostMallocDefault) != hipSuccess) { status = BRSVD_ERR_ALLOC; break; }
     h->host_scal = (double*)((char*)h->host_flags + kAlign);
     std::memset(h->host_flags, 0, kAlign + 64);

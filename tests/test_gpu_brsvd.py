@@ -199,6 +199,37 @@ def test_caller_owned_workspace():
         assert ei.value.status == B.BRSVD_ERR_BUDGET
 
 
+@pytest.mark.parametrize("m,n,k,p", [(900, 700, 20, 10), (1200, 900, 100, 10), (1300, 1100, 256, 16), (5000, 60, 16, 4)])
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("method", [B.BRSVD_ORTH_AUTO, B.BRSVD_ORTH_TSQR])
+def test_nothing_in_the_workspace_has_to_be_cleared(m, n, k, p, f64, method):
+    """A workspace that is full of NaN gives the bits of one that is full of zeros: both schemes and a robust-PCA iteration."""
+    dev = need_gpu()
+    print(f"[case] workspace {m} x {n} l={k + p} f64={f64} method={method}", flush=True)
+    dt = torch.float64 if f64 else torch.float32
+    A = synth.gaussian(m, n, 61, dtype=dt).to(dev)
+    Om = synth.gaussian(n, k + p, 62, dtype=dt).to(dev)
+    out = []
+    for fill in (0x00, 0xff):
+        par = dict(row_block=400, orth_method=method, dtype=B.BRSVD_DTYPE_F64 if f64 else B.BRSVD_DTYPE_F32)
+        need = B.brsvd_workspace_bytes(B.make_params(m, n, k, p, 1, **par))
+        res = []
+        for call in ("run", "alg2", "rpca"):
+            ws = torch.full((need,), fill, dtype=torch.uint8, device=dev)
+            h = B.brsvd_create(B.make_params(m, n, k, p, 1, workspace=ws, **par))
+            try:
+                if call == "run":
+                    res += B.brsvd_run(h, A, Om)[:3]
+                elif call == "alg2":
+                    res += B.brsvd_run_alg2(h, A, k + p, seed=5)[:3]
+                else:
+                    res += B.brsvd_rpca_ialm_tol(h, A, Om.reshape(1, n, k + p), 1, 0.0, 0.05, 0.02, 1.5, norm2_M=80.0)[:2]
+            finally:
+                B.brsvd_destroy(h)
+        out.append(res)
+    assert all(torch.equal(a, b) and bool(torch.isfinite(a).all()) for a, b in zip(*out))
+
+
 def test_timing_levels():
     """timing_level 1 times the pass kernels and the whole call only; the results do not depend on it."""
     dev = need_gpu()
