@@ -49,9 +49,9 @@ uint64_t brsvd_orth_scratch_bytes(int64_t rows, int32_t l);
 /* One-sided Jacobi SVD of an l x l fp64 matrix R (row-major): R = Ur diag(S) Vr^T.
  * Outputs: S (l doubles, descending), Ur and Vr (l x l fp64, row-major, columns are the singular
  * vectors).  Rows of R whose squared norm is not finite are left out of the rotations and keep their norm
- * (infinite, or NaN before all others); the other values are those of R without them.  Alg. 1 step 5 applied to the triangular factor of B^T.  scratch: at least
- * brsvd_small_svd_scratch_bytes(l), 256-byte aligned (BRSVD_ERR_BUDGET otherwise); its contents need
- * no initialisation.  Synchronises `stream`; *sweeps (HOST, may be NULL) receives the sweep count. */
+ * (infinite, or NaN before all others); the other values are those of R without them.  Alg. 1 step 5 applied to
+ * the triangular factor of B^T.  scratch: at least brsvd_small_svd_scratch_bytes(l), 256-byte aligned
+ * (BRSVD_ERR_BUDGET otherwise); its contents need no initialisation.  Synchronises `stream`; *sweeps (HOST, may be NULL) receives the sweep count. */
 int brsvd_small_svd(const double* R, int32_t l, double* S, double* Ur, double* Vr,
                     int32_t* sweeps, void* scratch, uint64_t scratch_bytes, void* stream);
 uint64_t brsvd_small_svd_scratch_bytes(int32_t l);

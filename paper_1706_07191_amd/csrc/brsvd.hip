@@ -1360,8 +1360,8 @@ int brsvd_orth(float* P, int64_t rows, int32_t l, int32_t method, double* R, int
     w.tsqr_work = take(o.tb); w.tsqr_bytes = o.tb;
     int m_now = method;
     for (int attempt = 0; attempt < 2; ++attempt) {
-      // P is left alone until it is known that there is a result: the sweeps go from P to P1 and stop short of the last product.  A panel whose rows are
-      // whole tiles, on 16 bytes, is taken as it is.
+      // P is left alone until it is known that there is a result: the sweeps go from P to P1 and stop short of the last product.  A panel whose rows
+      // are whole tiles, on 16 bytes, is taken as it is.
       const bool as_is = m_now != BRSVD_ORTH_TSQR && l == Lp && (uintptr_t)P % 16 == 0;
       Basis<float> Q{};
       if (!as_is && (status = pad_panel(P, rows, l, P0, Lp, s)) != BRSVD_OK) break;

@@ -195,9 +195,11 @@ typedef OrthWorkT<float> OrthWork;
 template <typename T>
 int apply_panel(const T* P, int64_t rows, int Lp, const T* X, T* out, int64_t ldo, int ncols, void* scratch, uint64_t scratch_bytes,
                 hipStream_t stream);
-// Y (rows x Lp) = A X with the Gram matrix of Y in w.G, for tall matrices of short rows: the next orthonormalisation by CholeskyQR on w starts from there.
+// Y (rows x Lp) = A X with the Gram matrix of Y in w.G, for tall matrices of short rows: the next orthonormalisation by CholeskyQR on w starts from
+// there.
 bool an_gram_fits(int64_t rows, int64_t K, int Lp, int esz);
-int an_gram(const float* A, int64_t lda, int64_t rows, int64_t K, const float* X, int Lp, float* Y, OrthWork& w, hipStream_t stream, const KernelEvents* ev);
+int an_gram(const float* A, int64_t lda, int64_t rows, int64_t K, const float* X, int Lp, float* Y, OrthWork& w, hipStream_t stream,
+            const KernelEvents* ev);
 // Applies the current w.Rinv to the companion panel, if any.
 template <typename T> int apply_to_companion(OrthWorkT<T>& w, int Lp, hipStream_t stream);
 uint64_t orth_gram_slots(int64_t rows, int Lp);   // Lp x Lp fp64 slots of partial Gram sums for such a panel

@@ -590,15 +590,15 @@ __global__ void k_reduce_splits(const T* __restrict__ part, int nsplit, int64_t 
   out[row * ldo + col] = s;
 }
 
-// The same in units of 16 bytes (ldi and split_stride are whole units; part starts on one).  SL threads share a unit: thread s adds the slots s, s + SL, ... in
-// order, and their sums are added in order.
-// What bounds it: the latency of the loads for small panels, of which a thread has eight at a time under way, and the read of the slots for large ones.
-// Measured, one thread per unit, in two launches from 64 slots on, and this (us): 1000x32, 64 slots 9.1
+// The same in units of 16 bytes (ldi and split_stride are whole units; part starts on one).  SL threads share a unit: thread s adds the slots s, s +
+// SL, ... in order, and their sums are added in order.
+// What bounds it: the latency of the loads for small panels, of which a thread has eight at a time under way, and the read of the slots for large
+// ones. Measured, one thread per unit, in two launches from 64 slots on, and this (us): 1000x32, 64 slots 9.1
 // and 4.9; 2000x32 9.7 and 4.0; 100x32, 1024 slots 14.5 and 7.5; into panels of 24 columns 9.5 and 6.4 to 8.8.
 template <typename T, int SL>
 __global__ void __launch_bounds__(256)
-k_split_sum(const T* __restrict__ part, int nsplit, int64_t split_stride, int64_t units, int units_per_row, int ncols, T* __restrict__ out, int64_t ldo,
-            int accumulate) {
+k_split_sum(const T* __restrict__ part, int nsplit, int64_t split_stride, int64_t units, int units_per_row, int ncols, T* __restrict__ out,
+            int64_t ldo, int accumulate) {
   typedef typename El<T>::u16 unit16;
   constexpr int EPU = El<T>::kPerU16, PER = 256 / SL;
   __shared__ unit16 sums[256];
@@ -1076,7 +1076,7 @@ static AtPlan at_plan(int64_t rows, int64_t n, int nt, int64_t block_rows, int e
   const int lds_bytes = 2 * kAtKC * at_ld(nt, esz) * esz;
   // one partial panel (n x Lp) per split, against block_rows x n of A read per block
   const int want = pick_splits((int64_t)p.col_tiles * p.nblocks, wg_slots(lds_bytes, at_wg_per_cu_regs(nt, p.waves)), max_sub,
-                               (double)(nt * 16) / (double)block_rows, traffic_weight(nt), 4096);   // long split sums take two levels
+                               (double)(nt * 16) / (double)block_rows, traffic_weight(nt), 4096);
   int64_t rps = ceil_div(block_rows, want);
   rps = ceil_div(rps, kAtKC) * kAtKC;
   p.rows_per_sub = (int)rps;

@@ -18,14 +18,15 @@ namespace brsvd {
 // ---- Gram matrix -----------------------------------------------------------------------------
 // G = P^T P on the fp64 matrix cores (v_mfma_f64_16x16x4_f64; products of fp32 values are exact in
 // fp64; the panel may also be fp64).  The columns are cut into blocks of up to four tiles of 16; grid = (row chunks, pairs bi <= bj of
-// blocks).  Lane (r, g) of a wave takes W neighbouring columns of row g of four rows with one load, W r .. W r + W - 1 of the block's 16 W: number t of them
-// is its operand of tile t, whose columns are thus t, W + t, 2 W + t, ...; the same value is the A operand (entry [i = r][k = g] of the transposed
-// tile) and the B operand ([k = g][j = r]), so the panel goes from global memory straight into the MFMA operands, in lines.
+// blocks).  Lane (r, g) of a wave takes W neighbouring columns of row g of four rows with one load, W r .. W r + W - 1 of the block's 16 W: number t
+// of them is its operand of tile t, whose columns are thus t, W + t, 2 W + t, ...; the same value is the A operand (entry [i = r][k = g] of the
+// transposed tile) and the B operand ([k = g][j = r]), so the panel goes from global memory straight into the MFMA operands, in lines.
 // The eight waves of a workgroup take AH steps of four rows at a time round-robin, the next ones' loads under way, and
 // add their accumulators through LDS in wave order; the chunks are added by k_gram_sum.
 // Accumulator layout of the instruction: component v of lane (r, g) is entry [g + 4*v][r].
 // Measured, with one load of four bytes per tile and step, and this (us):
-// 2073600x32 83 and 64, 76800x32 20 and 9, 40000x64 28 and 19, 20000x112 18.5 and 15, 100000x160 91 and 65, 100000x272 226 and 175, fp64 15872x80 12.7 and 8.2.
+// 2073600x32 83 and 64, 76800x32 20 and 9, 40000x64 28 and 19, 20000x112 18.5 and 15, 100000x160 91 and 65, 100000x272 226 and 175, fp64 15872x80
+// 12.7 and 8.2.
 constexpr int kGramWaves = 8;
 
 __device__ __forceinline__ doublex4 mfma_f64(double a, double b, doublex4 c) {
@@ -46,8 +47,8 @@ __device__ __forceinline__ void load_run(const T* p, T (&v)[W]) {
   }
 }
 
-// The sums of WAVES waves' accumulators, in wave order, to the workgroup's part Go of G: block of columns ci .. ci + 16 TI, cj .. cj + 16 TJ.  red: room for two
-// tiles per wave.
+// The sums of WAVES waves' accumulators, in wave order, to the workgroup's part Go of G: block of columns ci .. ci + 16 TI, cj .. cj + 16 TJ.  red:
+// room for two tiles per wave.
 template <int TI, int TJ, bool DIAG, int WAVES, int TILES>
 __device__ __forceinline__ void gram_store(const doublex4 (&acc)[TILES], int Lp, int ci, int cj, double* red, double* Go, int tid) {
   const int lane = tid & 63, wave = tid >> 6;
@@ -209,8 +210,8 @@ k_gram(const T* __restrict__ P, int64_t rows, int Lp, int64_t rows_per_chunk, do
 // A matrix close to the identity, as in the second sweep of CholeskyQR and after a Householder tree, needs no elimination: for G = I + E, and N the
 // strict upper triangle and half the diagonal of E, the factor is R = I + N - H, H the strict upper triangle and half the diagonal of N^T N,
 // and R^-1 = I - N, to the orders |E|_F^3 and |E|_F^2.  R^-1 is rounded to the panels' precision, R stays in fp64.  Taken where |E|_F is at most
-// `near_eye` (near_eye_of).  Measured, elimination and this with R (us): l = 20 8.0 and 4.0, 72 21 and 7.0, 97 30 and 11, 110 31 and 11, 160 62 and 29,
-// 272 192 and 97, 400 526 and 255; without R 7.6 and 3.4, 21 and 4.7, 28 and 7.3, 30 and 6.2, 58 and 12, 177 and 28, 494 and 61.
+// `near_eye` (near_eye_of).  Measured, elimination and this with R (us): l = 20 8.0 and 4.0, 72 21 and 7.0, 97 30 and 11, 110 31 and 11, 160 62 and
+// 29, 272 192 and 97, 400 526 and 255; without R 7.6 and 3.4, 21 and 4.7, 28 and 7.3, 30 and 6.2, 58 and 12, 177 and 28, 494 and 61.
 constexpr int kNB = 16;
 constexpr int kCholLdsMaxLp = 128;    // largest padded size whose fp64 matrix fits the LDS
 
@@ -250,8 +251,8 @@ __device__ __forceinline__ double rcp_fast(double x) {
 //   D -= (row_j / d_j)^T row_j,  E -= (row_j / d_j)^T E_j   (first operand masked to the rows below j),
 // with no value moved between lanes.  The next pivot is taken from the old tile, d_(j+1) = D_(j+1,j+1) -
 // D_(j,j+1)^2 / d_j, so its reciprocal is worked out while the instruction runs.  Rows are scaled by 1/sqrt(d)
-// at the end: D = R_kk, E = R_kk^-T.  cnt: rows of the tile that are not padding (those are rows of the identity and need no pivots).  FACTORED: D is already R_kk.  d0: original diagonal of the tile.  Returns false if
-// a pivot had to be clamped.
+// at the end: D = R_kk, E = R_kk^-T.  cnt: rows of the tile that are not padding (those are rows of the identity and need no pivots).  FACTORED: D
+// is already R_kk.  d0: original diagonal of the tile.  Returns false if a pivot had to be clamped.
 template <bool FACTORED>
 __device__ __forceinline__ bool chol_diag_wave(doublex4& D, doublex4& E, const double* d0, double tol, int lane, int cnt) {
   const int r = lane & 15, g = lane >> 4;
@@ -546,21 +547,22 @@ uint64_t orth_gram_slots(int64_t rows, int Lp) {
   c = std::max<int64_t>(std::max(c, tall), 1);
   return (uint64_t)(c > kGramFan ? c + ceil_div(c, kGramFan) : c);
 }
-// Row chunks of the Gram kernel: of 64 rows at least (eight per wave), and as many as give every CU a workgroup: one where all blocks of tiles are of a size, more
-// where a chunk's pairs of blocks are not, so that the short ones fill the gaps.  Two per CU for the tallest narrow panels, whose workgroups have rows enough.
-// Measured (us with the sum, workgroups in all: 256 / 512 / 1024): 76800x32 10.2 / 11.6 / 12.6, 2073600x32 76 / 71 / 79, 40000x64 15 / 20 / 20 (23 with 64),
-// 20000x112 16.7 / 17.3 / 16.5 (20 with 192), 89083x112 38 / 39 / 45, 100000x160 73 / 69 / 78, 100000x272 192 / 181 / 170, 50000x272 104 / 99 / 97; chunks of
-// 64 / 128 / 256 rows: 2000x32 5.8 / 8.0 / 7.4, 12000x64 11.8 / 11.4 / 14.0, 2783x112 10.4 / 11.7 / 15.0.
+// Row chunks of the Gram kernel: of 64 rows at least (eight per wave), and as many as give every CU a workgroup: one where all blocks of tiles are
+// of a size, more where a chunk's pairs of blocks are not, so that the short ones fill the gaps.  Two per CU for the tallest narrow panels, whose
+// workgroups have rows enough. Measured (us with the sum, workgroups in all: 256 / 512 / 1024): 76800x32 10.2 / 11.6 / 12.6, 2073600x32 76 / 71 /
+// 79, 40000x64 15 / 20 / 20 (23 with 64), 20000x112 16.7 / 17.3 / 16.5 (20 with 192), 89083x112 38 / 39 / 45, 100000x160 73 / 69 / 78, 100000x272
+// 192 / 181 / 170, 50000x272 104 / 99 / 97; chunks of 64 / 128 / 256 rows: 2000x32 5.8 / 8.0 / 7.4, 12000x64 11.8 / 11.4 / 14.0, 2783x112 10.4 /
+// 11.7 / 15.0.
 static int64_t gram_chunks(int64_t rows, int pairs) {
   const int64_t wgs = pairs > 6 ? 1024 : pairs > 3 || (pairs == 1 && rows >= (1 << 20)) ? 512 : 256;
   return std::min<int64_t>(ceil_div(rows, 64), std::max<int64_t>(1, wgs / pairs));
 }
 
-// G = the sum of the chunks' parts.  A workgroup takes 32 entries of the upper tiles; each is added up by 32 threads, thread s the chunks s, s + 32, ...
-// in order, and then their sums in order: the result does not depend on timing.
-// What bounds it: the latency of the loads, which come from all dies.  One thread per entry, over all entries, in two launches from 65 (small factors:
-// 257) chunks on, and this (us): l = 30 3.1 and 2.6, 72 7.3 and 4.8, 110 9.1 and 4.8, 160 10.5 and 5.1, 272 14.4 and 11.0; 76800x32 (75 chunks) 6.1 and 4.6,
-// 2073600x32 (2025) 11.2 and 11.6.
+// G = the sum of the chunks' parts.  A workgroup takes 32 entries of the upper tiles; each is added up by 32 threads, thread s the chunks s, s + 32,
+// ... in order, and then their sums in order: the result does not depend on timing.
+// What bounds it: the latency of the loads, which come from all dies.  One thread per entry, over all entries, in two launches from 65 (small
+// factors: 257) chunks on, and this (us): l = 30 3.1 and 2.6, 72 7.3 and 4.8, 110 9.1 and 4.8, 160 10.5 and 5.1, 272 14.4 and 11.0; 76800x32 (75
+// chunks) 6.1 and 4.6, 2073600x32 (2025) 11.2 and 11.6.
 __global__ void __launch_bounds__(1024)
 k_gram_sum(const double* __restrict__ part, int chunks, int Lp, double* __restrict__ G) {
   __shared__ double sums[32][33];
@@ -722,19 +724,20 @@ __device__ __forceinline__ void wave_exchange() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The same with the Gram matrix of what is written, for the second sweep of CholeskyQR: that saves a read of the panel.  A wave puts each tile in LDS (its own
-// place, no barrier) and takes it up again in the order of the Gram kernel's operands; Gpart as there, one part per workgroup.
-// What bounds it: the panel's read and write, as before; the fp64 matrix instructions run under them.  Measured, product, Gram matrix and its sum, and with
-// this (us): 2073600x32 101 + 61 + 5 and 101 + 5, 76800x32 5.5 + 5 + 4.6 and 9 + 4.6, 2000x32 3.3 + 3.4 + 2.7 and 4.5 + 2.7.
-// It also does Y = A X with the Gram matrix of Y for tall matrices of short rows (K up to 128, KT tiles of 16; rows at any element address): all of X is in registers
-// there as well.  A lane whose four indices lie behind K repeats the row's last ones and meets zeros of X.  k_gemm_an, Gram
+// The same with the Gram matrix of what is written, for the second sweep of CholeskyQR: that saves a read of the panel.  A wave puts each tile in
+// LDS (its own place, no barrier) and takes it up again in the order of the Gram kernel's operands; Gpart as there, one part per workgroup.
+// What bounds it: the panel's read and write, as before; the fp64 matrix instructions run under them.  Measured, product, Gram matrix and its sum,
+// and with this (us): 2073600x32 101 + 61 + 5 and 101 + 5, 76800x32 5.5 + 5 + 4.6 and 9 + 4.6, 2000x32 3.3 + 3.4 + 2.7 and 4.5 + 2.7.
+// It also does Y = A X with the Gram matrix of Y for tall matrices of short rows (K up to 128, KT tiles of 16; rows at any element address): all of
+// X is in registers there as well.  A lane whose four indices lie behind K repeats the row's last ones and meets zeros of X.  k_gemm_an, Gram
 // matrix and sum, and this (us): 2073600x100 l=20 214 + 61 + 5 and 208 + 4.
-// Waves of a workgroup: eight, two of whose workgroups fit a CU, up to 64 indices; four where registers run out (SVD runs, q = 1, with four and eight,
-// us: 1000000x64 l = 32 750 and 731, 1000000x100 828 and 859, 2073600x96 1415 and 1492).
+// Waves of a workgroup: eight, two of whose workgroups fit a CU, up to 64 indices; four where registers run out (SVD runs, q = 1, with four and
+// eight, us: 1000000x64 l = 32 750 and 731, 1000000x100 828 and 859, 2073600x96 1415 and 1492).
 template <int KT> constexpr int rows_gram_waves() { return KT <= 4 ? 8 : 4; }
 template <int KT, int NT>
 __global__ void __launch_bounds__(rows_gram_waves<KT>() * 64)
-k_rows_gram(const float* __restrict__ A, int64_t lda, int64_t rows, int K, const float* __restrict__ X, float* __restrict__ out, double* __restrict__ Gpart) {
+k_rows_gram(const float* __restrict__ A, int64_t lda, int64_t rows, int K, const float* __restrict__ X, float* __restrict__ out,
+            double* __restrict__ Gpart) {
   constexpr int Lp = 16 * NT, TILES = NT * (NT + 1) / 2, LD = Lp + 4, WAVES = rows_gram_waves<KT>();
   typedef floatx4 floatx4u __attribute__((aligned(4)));
   __shared__ __align__(16) float place[WAVES][16 * LD];
@@ -831,14 +834,20 @@ static int apply_gram(const float* P, int64_t rows, int Lp, const float* X, floa
     default: return rows_gram<3, 3>(P, Lp, rows, Lp, X, out, w, stream);
   }
 }
-// A X: rows of up to 128 numbers, and some wavefronts for every CU.  SVD runs, q = 1, with the product and the Gram matrix apart and in one (us): 4100x50 l = 32 242 and
-// 235, 16384x50 256 and 238, 16384x128 259 and 254, 131072x65 l = 16 246 and 236, 131072x128 l = 32 322 and 326, 1000000x50 879 and 793, 1000000x64 733 and
-// 733, 1000000x100 885 and 828, 2073600x33 l = 16 898 and 747.  Fewer rows are matters of launches, and the small products' plan cuts them.
+// A X: rows of up to 128 numbers, and some wavefronts for every CU.  SVD runs, q = 1, with the product and the Gram matrix apart and in one (us):
+// 4200x48 l = 32 252 and 245, 16384x128 270 and 263, 131072x96 l = 16 252 and 255, 131072x128 l = 32 343 and 339, 1000000x48 l = 32 745 and 707,
+// 1000000x64 744 and 736, 1000000x128 903 and 875, 2073600x48 l = 16 801 and 757, 2073600x80 l = 32 1476 and 1317; of 74 shapes from 4200x48
+// to 2073600x100 all but 131072x96 l = 16 gain 1 to 11 percent.  Fewer rows are matters of launches, and the small products' plan cuts them.
 bool an_gram_fits(int64_t rows, int64_t K, int Lp, int esz) { return esz == 4 && Lp <= 32 && K >= 4 && K <= 128 && rows >= 4096; }
-int an_gram(const float* A, int64_t lda, int64_t rows, int64_t K, const float* X, int Lp, float* Y, OrthWork& w, hipStream_t stream, const KernelEvents* ev) {
+int an_gram(const float* A, int64_t lda, int64_t rows, int64_t K, const float* X, int Lp, float* Y, OrthWork& w, hipStream_t stream,
+            const KernelEvents* ev) {
   if (!an_gram_fits(rows, K, Lp, 4)) return BRSVD_ERR_ARG;
   int status = BRSVD_ERR_ARG;
-#define CALL(KT) case KT: status = Lp == 16 ? rows_gram<KT, 1>(A, lda, rows, (int)K, X, Y, w, stream) : rows_gram<KT, 2>(A, lda, rows, (int)K, X, Y, w, stream); break;
+#define CALL(KT)                                                            \
+  case KT:                                                                  \
+    status = Lp == 16 ? rows_gram<KT, 1>(A, lda, rows, (int)K, X, Y, w, stream)  \
+                      : rows_gram<KT, 2>(A, lda, rows, (int)K, X, Y, w, stream); \
+    break;
   switch (ceil_div(K, 16)) {
     CALL(1) CALL(2) CALL(3) CALL(4) CALL(5) CALL(6) CALL(7) CALL(8)
   }
@@ -915,9 +924,9 @@ template int triu_mul<float>(const double*, const float*, int, int, double*, hip
 template int triu_mul<double>(const double*, const double*, int, int, double*, hipStream_t);
 
 constexpr double kPivotTol = 1e-12;
-// |G - I|_F up to which the factor of G (l x l) is not eliminated.  R, in fp64, is then off by at most |E|_F^3 / 2, a quarter of a rounding for each of
-// the l steps of an elimination, its inverse by |E|_F^2 / 2, which in the panels' precision is a hundredth of a rounding (8e-10 of 6e-8 at l = 272)
-// and a seventh (8e-18 of 1.1e-16).  First sweeps of panels with conditions up to a few hundred leave 5e-7 to 2e-5 in fp32.
+// |G - I|_F up to which the factor of G (l x l) is not eliminated.  R, in fp64, is then off by at most |E|_F^3 / 2, a quarter of a rounding for each
+// of the l steps of an elimination, its inverse by |E|_F^2 / 2, which in the panels' precision is a hundredth of a rounding (8e-10 of 6e-8 at l =
+// 272) and a seventh (8e-18 of 1.1e-16).  First sweeps of panels with conditions up to a few hundred leave 5e-7 to 2e-5 in fp32.
 template <typename T> double near_eye_of(int l) { return sizeof(T) == 4 ? cbrt(l * 0x1p-52) : 4e-9; }
 // Only the last sweep of a basis that reaches the output must succeed without clamped pivots (its
 // input is then already nearly orthonormal, so a small pivot there means the panel really lost
@@ -961,9 +970,9 @@ int orth_panel(T* P, T* tmp, int64_t rows, int l, int Lp, int method, bool final
   return cholqr_sweeps<T>(P, tmp, rows, l, Lp, final_basis ? 2 : 1, w, Rtot, result, stream, final_basis);
 }
 
-// The second sweep of CholeskyQR, G2 = Q1^T Q1 = R2^T R2, without its pass over the panel Q2 = Q1 R2^-1: everything that follows is a product of Q1 with
-// an l x l factor or a product from the left that R2^-1 can be multiplied to afterwards.  R2 is close to the identity (where a pivot was clamped, to
-// a diagonal matrix times a well-conditioned one), so nothing is lost by taking R2^-1 to the other side.
+// The second sweep of CholeskyQR, G2 = Q1^T Q1 = R2^T R2, without its pass over the panel Q2 = Q1 R2^-1: everything that follows is a product of Q1
+// with an l x l factor or a product from the left that R2^-1 can be multiplied to afterwards.  R2 is close to the identity (where a pivot was
+// clamped, to a diagonal matrix times a well-conditioned one), so nothing is lost by taking R2^-1 to the other side.
 template <typename T>
 int orth_basis(T* P, T* tmp, int64_t rows, int l, int Lp, int method, OrthWorkT<T>& w, T* left, double* Rtot, bool want_R, Basis<T>* out,
                hipStream_t stream) {

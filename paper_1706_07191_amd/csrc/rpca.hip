@@ -23,8 +23,8 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
   return s;   // valid in thread 0
 }
 
-// part[2*b] = max |M| over the block's slice, part[2*b+1] = sum M^2.  Bound by the read of M: vectors of 16 bytes, four of them under way per thread, and
-// single elements up to M's first whole vector and behind its last.  Measured (us, one element at a time before):
+// part[2*b] = max |M| over the block's slice, part[2*b+1] = sum M^2.  Bound by the read of M: vectors of 16 bytes, four of them under way per
+// thread, and single elements up to M's first whole vector and behind its last.  Measured (us, one element at a time before):
 // 76800x2000 fp32 270 -> 94 (6.6 TB/s), 2073600x100 365 -> 127, 32256x2383 fp64 152 -> 93.
 template <typename T>
 __global__ void __launch_bounds__(256)
@@ -206,8 +206,9 @@ k_rpca_update_vec(const T* __restrict__ M, const T* __restrict__ U, const T* __r
   }
   // The singular values come in descending order (NaN first): those from `terms` on are shrunk to zero and add nothing (five of 20 left: 2073600x100
   // 640 -> 610 us, 76800x2000 437 -> 432).  Looked for with scalar loads (vector loads would wait for those of M before them), one after the
-  // other up to 32, by bisection above.  Where all are left (us, without a look, one after the other, by bisection): l = 20 2073600x100 660, 672 and 684,
-  // 76800x2000 441, 443 and 448; l = 50 2073600x100 1035, 1083 and 1041; l = 120 76800x2000 940, 1104 and 948; l = 300 20000x2000 557, 715 and 568.
+  // other up to 32, by bisection above.  Where all are left (us, without a look, one after the other, by bisection): l = 20 2073600x100 660, 672 and
+  // 684, 76800x2000 441, 443 and 448; l = 50 2073600x100 1035, 1083 and 1041; l = 120 76800x2000 940, 1104 and 948; l = 300 20000x2000 557, 715 and
+  // 568.
   int terms = 0;
   if (l <= 32) {
     while (terms < l && !(sig[terms] <= inv_mu)) ++terms;

@@ -560,7 +560,8 @@ __device__ __forceinline__ bool busy_32(const double* work, int t, bool all, dou
   return __syncthreads_or(busy);
 }
 
-// One sweep of rotations on the Gram matrix in buffer 0 of work: all pairs of the 32 rows, or those across the two blocks.  fresh, store: as for cross_pairs.
+// One sweep of rotations on the Gram matrix in buffer 0 of work: all pairs of the 32 rows, or those across the two blocks.  fresh, store: as for
+// cross_pairs.
 __device__ __forceinline__ bool sweep_32(double* work, int t, bool all, double settled2, bool fresh = true, bool store = false) {
   bool any = false;
   __syncthreads();
@@ -837,8 +838,8 @@ k_jacobi_rounds(const double* R, int ldr, double* W, int l, int Lp, int nblk2, d
 // Sorted factors.  Vr[t][i] = W[o_i][t] / s_i;  Ur[kk][i] = sum_t R[kk][t] Vr[t][i] / s_i.
 // XV / XU: zero-padded Lp x Lp right operands of the lifts; Ur / Vr: optional dense fp64.  left: XV = left Vr; upper: R (then not the matrix
 // whose SVD this is) and left are upper triangular.
-// A workgroup per tile of 16 x 16 of XU (blockIdx.z = 0) or XV, on v_mfma_f64_16x16x4_f64: lane (r, g) holds R[kk + r][t + g] and W[o_(i+r)][t + g], which
-// come from other dies' work, at a latency of a microsecond and more; eight waves share the contraction for that.
+// A workgroup per tile of 16 x 16 of XU (blockIdx.z = 0) or XV, on v_mfma_f64_16x16x4_f64: lane (r, g) holds R[kk + r][t + g] and W[o_(i+r)][t + g],
+// which come from other dies' work, at a latency of a microsecond and more; eight waves share the contraction for that.
 // Measured (us with the launch; one thread per entry before, without the product for XV): l = 30 6.0 -> 4.7, 110 13.4 -> 7.7, 272 42.8 -> 13.9.
 template <typename TO>
 __global__ void __launch_bounds__(kTileWaves * 64)
@@ -943,8 +944,8 @@ int small_svd(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* br
     BRSVD_TRY(jacobi_global(R, ldr, l, Lp, w, breakdown_flag, settled, Ur || Vr ? 0.0 : idle, stream));
   }
   const dim3 tiles(Lp / kTile, Lp / kTile, 2);
-  hipLaunchKernelGGL(k_svd_outputs<TO>, tiles, dim3(kTileWaves * 64), 0, stream, open ? open->Rx : R, ldr, open ? 1 : 0, open ? open->left : nullptr, w.W,
-                     w.sig, l, Lp, S, S32, XV, XU, Ur, Vr, breakdown_flag);
+  hipLaunchKernelGGL(k_svd_outputs<TO>, tiles, dim3(kTileWaves * 64), 0, stream, open ? open->Rx : R, ldr, open ? 1 : 0,
+                     open ? open->left : nullptr, w.W, w.sig, l, Lp, S, S32, XV, XU, Ur, Vr, breakdown_flag);
   BRSVD_HIP_TRY(hipGetLastError());
   return BRSVD_OK;
 }

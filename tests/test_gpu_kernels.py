@@ -232,7 +232,8 @@ def test_gemm_f64_matches_oracle(rows, n, l):
 
 
 @pytest.mark.parametrize("f64", [False, True])
-@pytest.mark.parametrize("rows,n,l", [(2000, 1000, 30), (129, 259, 17), (3000, 600, 40), (257, 323, 33), (1000, 1000, 300), (1500, 1001, 100), (64, 2048, 20),
+@pytest.mark.parametrize("rows,n,l", [(2000, 1000, 30), (129, 259, 17), (3000, 600, 40), (257, 323, 33), (1000, 1000, 300),
+                                      (1500, 1001, 100), (64, 2048, 20),
                                       (8000, 480, 30)])
 def test_small_products_cut_along_the_contraction(rows, n, l, f64):
     """Y = A X where the contraction is cut into pieces because the row tiles alone leave the chip idle: last pieces and last rows of any length."""

@@ -75,8 +75,9 @@ def test_second_factor_on_both_sides_of_the_line(l, spread):
 
 
 def _panel_with_known_factors(l, s, pairs):
-    """Rows of at most two numbers, all powers of two, so that P R1^-1 comes out the same in whatever order it is summed.  For columns (c, d) of a pair
-    the Gram matrix is [[4^s, 4^s - 1], [4^s - 1, 4^s - 1 + b]], whose elimination is exact: R1 = [[2^s, 2^s - 2^-s], [0, sqrt(b + 1 - 4^-s)]]."""
+    """Rows of at most two numbers, all powers of two, so that P R1^-1 comes out the same in whatever order it is summed.  For columns (c, d)
+    of a pair the Gram matrix is [[4^s, 4^s - 1], [4^s - 1, 4^s - 1 + b]], whose elimination is exact:
+    R1 = [[2^s, 2^s - 2^-s], [0, sqrt(b + 1 - 4^-s)]]."""
     rows, R1 = [], torch.eye(l, dtype=torch.float64)
     for t, (c, d) in enumerate(pairs):
         b = 1 + t % 7
@@ -95,8 +96,8 @@ def _panel_with_known_factors(l, s, pairs):
 @pytest.mark.parametrize("l", [2, 16, 30, 47, 128, 160, 272])
 @pytest.mark.parametrize("s", [3, 5, 6, 7, 8, 10])
 def test_factor_of_a_basis_is_exact(l, s):
-    """The factor R = R2 R1 that brsvd_orth returns in fp64, where R2 is next to the identity and not eliminated (|R2^T R2 - I| = 1e-7 to 3e-5) and past
-    that line (to 2e-4): the Cholesky factor of the Gram matrix of the rounded first basis times R1."""
+    """The factor R = R2 R1 that brsvd_orth returns in fp64, where R2 is next to the identity and not eliminated (|R2^T R2 - I| = 1e-7 to 3e-5)
+    and past that line (to 2e-4): the Cholesky factor of the Gram matrix of the rounded first basis times R1."""
     dev = need_gpu()
     print(f"[case] exact factor l={l} s={s}", flush=True)
     # within a tile of 16 and across tiles, no column twice
@@ -153,8 +154,8 @@ def test_gram_over_all_block_sizes(l):
 @pytest.mark.parametrize("l", [1, 16, 17, 32, 33, 48])
 @pytest.mark.parametrize("rows", [49, 127, 128, 129, 32767, 32769, 65553, (1 << 20) + 5])
 def test_narrow_panels_with_the_gram_matrix_of_the_product(rows, l):
-    """Panels of up to three tiles, whose second Gram matrix is formed by the waves that apply the first factor, tile by tile through LDS: as many rows
-    as a wave, a workgroup and all of them have at a time, and a few more or less.  Q^T Q = I and P = Q R."""
+    """Panels of up to three tiles, whose second Gram matrix is formed by the waves that apply the first factor, tile by tile through LDS: as
+    many rows as a wave, a workgroup and all of them have at a time, and a few more or less.  Q^T Q = I and P = Q R."""
     dev = need_gpu()
     print(f"[case] product and Gram matrix {rows} x {l}", flush=True)
     P = torch.randn(rows, l, generator=torch.Generator().manual_seed(rows + l))
@@ -170,7 +171,8 @@ def test_narrow_panels_with_the_gram_matrix_of_the_product(rows, l):
     assert not fallback and defect <= 4 * np.sqrt(l) * eps + 1e-8 and back <= 8 * np.sqrt(l) * eps, (defect, back)
 
 
-@pytest.mark.parametrize("n,l,m", [(100, 20, 131077), (64, 32, 131077), (61, 16, 4096), (128, 17, 4101), (127, 32, 40001), (33, 9, 4101), (17, 17, 131077),
+@pytest.mark.parametrize("n,l,m", [(100, 20, 131077), (64, 32, 131077), (61, 16, 4096), (128, 17, 4101), (127, 32, 40001),
+                                   (33, 9, 4101), (17, 17, 131077),
                                    (65, 32, 4096)])
 def test_tall_matrices_of_short_rows(n, l, m):
     """Rows from as many as the product and its Gram matrix are one kernel for, of every length up to its largest, at every alignment."""

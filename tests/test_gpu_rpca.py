@@ -333,8 +333,8 @@ def test_norm2_power_at_the_ends_of_the_range(n, square):
 @pytest.mark.parametrize("dtype,off", [(torch.float32, 0), (torch.float32, 1), (torch.float32, 2), (torch.float32, 3), (torch.float64, 1)])
 @pytest.mark.parametrize("m,n", [(37, 29), (5, 3), (700, 641)])
 def test_norms_at_every_alignment(dtype, off, m, n):
-    """The norms before the first iteration are read in vectors: M at every offset from 16 bytes, with ends that are no whole vector.  The largest entry
-    decides the first multiplier, the Frobenius norm the residuals."""
+    """The norms before the first iteration are read in vectors: M at every offset from 16 bytes, with ends that are no whole vector.  The
+    largest entry decides the first multiplier, the Frobenius norm the residuals."""
     dev = need_gpu()
     print(f"[case] norms {dtype} +{off} {m}x{n}", flush=True)
     g = torch.Generator().manual_seed(off + m)
@@ -382,7 +382,8 @@ def test_singular_values_left_after_the_shrinkage(l, f64):
             edge = [4.0] + s.tolist() + [0.0]
             t = (edge[left] + edge[left + 1]) / 2               # between the last value that is left and the next
             x = t / (1 - t / J)                                 # 1 / mu, as the matrix decomposed is M (1 + 1 / (J mu))
-            L = B.brsvd_rpca_ialm_tol(h, M.to(dev), synth.gaussian(n, l, 9, dtype=dt).reshape(1, n, l).to(dev), 1, 0.0, lam, 1 / x, 1.5, norm2_M=3.0)[0]
+            Om = synth.gaussian(n, l, 9, dtype=dt).reshape(1, n, l).to(dev)
+            L = B.brsvd_rpca_ialm_tol(h, M.to(dev), Om, 1, 0.0, lam, 1 / x, 1.5, norm2_M=3.0)[0]
             want = (u[:, :r] * (s * (1 + x / J) - x).clamp(min=0)) @ vt[:r]
             # fp32: the SVD's values and vectors to 1e-6 of the largest value, over gaps that L, a function of the matrix, does not see
             assert float((L.double().cpu() - want).norm()) <= (1e-11 if f64 else 1e-5) * float(s.norm())
