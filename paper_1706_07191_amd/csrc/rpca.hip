@@ -147,7 +147,8 @@ constexpr int kRpcaTR = 32;
 // reaches 5.4 TB/s = 570 us; without the store of S the kernel takes 476 us, with the loads hoisted 458 us, with
 // line-aligned accesses 443 us; plain kernels with two reads and two writes per element: 401 us as one flat array,
 // 456 us in this kernel's tiles, 434 us in the tiles with line-aligned accesses).
-template <typename T, int WAVES, int RPT, bool STREAM, bool FINAL>
+// WIDE: more than 32 singular values (an instance of its own: with both ways to look for their number in one, l = 20 takes 1 to 3 percent longer).
+template <typename T, int WAVES, int RPT, bool STREAM, bool FINAL, bool WIDE>
 __global__ void __launch_bounds__(WAVES * 64)
 k_rpca_update_vec(const T* __restrict__ M, const T* __restrict__ U, const T* __restrict__ sig,
                   const T* __restrict__ Vt, int64_t m, int64_t n, int l, T inv_mu, T mu,
@@ -210,7 +211,7 @@ k_rpca_update_vec(const T* __restrict__ M, const T* __restrict__ U, const T* __r
   // 684, 76800x2000 441, 443 and 448; l = 50 2073600x100 1035, 1083 and 1041; l = 120 76800x2000 940, 1104 and 948; l = 300 20000x2000 557, 715 and
   // 568.
   int terms = 0;
-  if (l <= 32) {
+  if constexpr (!WIDE) {
     while (terms < l && !(sig[terms] <= inv_mu)) ++terms;
   } else {
     for (int end = l; terms < end;) {
@@ -560,12 +561,14 @@ static int rpca_update_launch(const T* M, const T* U, const T* sig, const T* Vt,
   const uintptr_t bits = FINAL ? ((uintptr_t)M | (uintptr_t)Yin | (uintptr_t)S | (uintptr_t)Lout)
                                : ((uintptr_t)M | (uintptr_t)Yin | (uintptr_t)Yout | (uintptr_t)X);
   const bool stream_ok = n % VW == 0 && bits % 16 == 0;
-  auto kern = stream_ok ? k_rpca_update_vec<T, kRpcaUpdWaves, kRpcaUpdRPT, true, FINAL>
-                        : k_rpca_update_vec<T, kRpcaUpdWaves, kRpcaUpdRPT, false, FINAL>;
-  static bool attr_set[2] = {false, false};
-  if (!attr_set[stream_ok]) {
+  constexpr int W = kRpcaUpdWaves, RPT = kRpcaUpdRPT;
+  const bool wide = l > 32;
+  auto kern = wide ? (stream_ok ? k_rpca_update_vec<T, W, RPT, true, FINAL, true> : k_rpca_update_vec<T, W, RPT, false, FINAL, true>)
+                   : (stream_ok ? k_rpca_update_vec<T, W, RPT, true, FINAL, false> : k_rpca_update_vec<T, W, RPT, false, FINAL, false>);
+  static bool attr_set[2][2] = {{false, false}, {false, false}};
+  if (!attr_set[wide][stream_ok]) {
     BRSVD_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds));
-    attr_set[stream_ok] = true;
+    attr_set[wide][stream_ok] = true;
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(kRpcaUpdWaves * 64), lds, stream, M, U, sig, Vt, m, n, l, T(1) / mu,
                      mu, lambda / mu, T(1) / mu_next, Yin, Yout, X, Lout, S, part, sh.cvt, sh.col_tiles, line_shift ? 1 : 0);
