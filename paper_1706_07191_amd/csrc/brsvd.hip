@@ -1355,17 +1355,18 @@ int brsvd_orth(float* P, int64_t rows, int32_t l, int32_t method, double* R, int
     float* left = (float*)take(o.sq8);
     double* Rtot = (double*)take(o.sq8);
     w.Rinv = (float*)take(o.sq4);
-    w.flags = (int*)take(256);
     w.gemm_scratch = take(o.gs); w.gemm_scratch_bytes = o.gs;
     w.tsqr_work = take(o.tb); w.tsqr_bytes = o.tb;
+    w.flags = (int*)take(256);
     int m_now = method;
     for (int attempt = 0; attempt < 2; ++attempt) {
       // P is left alone until it is known that there is a result: the sweeps go from P to P1 and stop short of the last product.  A panel whose rows
       // are whole tiles, on 16 bytes, is taken as it is.
       const bool as_is = m_now != BRSVD_ORTH_TSQR && l == Lp && (uintptr_t)P % 16 == 0;
       Basis<float> Q{};
-      if (!as_is && (status = pad_panel(P, rows, l, P0, Lp, s)) != BRSVD_OK) break;
+      // before any kernel: a scratch that is no device memory, or ends too early, is refused here
       if (hipMemsetAsync(w.flags, 0, 256, s) != hipSuccess) { status = BRSVD_ERR_HIP; break; }
+      if (!as_is && (status = pad_panel(P, rows, l, P0, Lp, s)) != BRSVD_OK) break;
       if ((status = orth_basis(as_is ? P : P0, P1, rows, l, Lp, m_now, w, left, Rtot, R != nullptr, &Q, s)) != BRSVD_OK) break;
       if (Q.R2 && (status = triu_mul(Q.R2, Q.R1, l, Lp, Rtot, s)) != BRSVD_OK) break;
       int flag = 0;

@@ -131,6 +131,24 @@ def test_orth_of_a_panel_taken_as_it_is(rows, l):
     assert O.orth_defect(Q.double().cpu().numpy()) <= 4 * np.sqrt(l) * 2.0 ** -24 + 1e-8
 
 
+@pytest.mark.parametrize("rows,l", [(500, 30), (500, 32), (900, 70)])
+@pytest.mark.parametrize("method", [B.BRSVD_ORTH_AUTO, B.BRSVD_ORTH_TSQR])
+def test_orth_refuses_a_scratch_in_host_memory(rows, l, method):
+    """The scratch is first touched by a call that the runtime refuses for pageable host memory, not by a kernel; P stays as it is."""
+    dev = need_gpu()
+    print(f"[case] orth with host scratch {rows} x {l} method={method}", flush=True)
+    size = B.lib().brsvd_orth_scratch_bytes(rows, l)
+    host = np.zeros(size + 256, dtype=np.uint8)
+    at = -(-host.ctypes.data // 256) * 256
+    P = torch.randn(rows, l, generator=torch.Generator().manual_seed(l)).to(dev)
+    before = P.clone()
+    torch.cuda.synchronize()
+    assert B.lib().brsvd_orth(P.data_ptr(), rows, l, method, None, None, at, size, None) == B.BRSVD_ERR_HIP
+    B.lib().hipGetLastError()                    # the runtime's own record of the refused call
+    assert torch.equal(P, before) and not host.any()
+    assert not B.brsvd_orth(P, method)[2]
+
+
 @pytest.mark.parametrize("l", [1, 16, 17, 33, 49, 65, 81, 97, 113, 129, 145, 177, 193, 257, 400])
 def test_gram_over_all_block_sizes(l):
     """The Gram matrix by blocks of one to four tiles, of every combination, with chunks whose last rows are no whole step: Q^T Q = I and P = Q R."""
