@@ -35,7 +35,7 @@ struct Layout {
   // offsets into the arena
   uint64_t Pm[2], Pn[2], gemm_scratch, gram_part, G, R0, R1, Rinv, Rtot, leftQ, Rx, XV, XU, svdW, sig,
       S32, flags, tsqr, stage[2], scal, rpcaU, rpcaVt, rpca_part, total;
-  uint64_t gemm_scratch_bytes, tsqr_bytes, stage_bytes;
+  uint64_t gemm_scratch_bytes, apply_scratch_bytes, tsqr_bytes, stage_bytes;
   int gram_chunks;
 };
 
@@ -107,11 +107,6 @@ Layout make_layout(const brsvd_params& p, int64_t b) {
   for (int i = 0; i < 2; ++i) L.Pn[i] = take((uint64_t)n * Lp * esz);
   // split-sum scratch: the largest of every GEMM shape issued by the driver
   uint64_t gs = 0;
-  // products on one row block (streamed A, and the block-local scheme on any A), also on a ragged last block
-  for (int64_t rows : {b, m - (m - 1) / b * b}) {
-    gs = std::max(gs, gemm_an_scratch_bytes(rows, n, Lp, esz));
-    gs = std::max(gs, gemm_at_scratch_bytes(rows, n, Lp, rows, esz));
-  }
   if (!host) {   // device-resident A: one launch over all rows
     gs = std::max(gs, gemm_an_scratch_bytes(m, n, Lp, esz));
     gs = std::max(gs, gemm_at_scratch_bytes(m, n, Lp, m, esz));
@@ -122,6 +117,14 @@ Layout make_layout(const brsvd_params& p, int64_t b) {
   }
   gs = std::max(gs, gemm_an_scratch_bytes(m, Lp, Lp, esz));
   gs = std::max(gs, gemm_an_scratch_bytes(n, Lp, Lp, esz));
+  // What the panels' products with l x l factors may use, as it decides how those are cut: for device-resident A no function of b.
+  L.apply_scratch_bytes = gs;
+  // products on one row block (streamed A, and the block-local scheme on any A), also on a ragged last block
+  for (int64_t rows : {b, m - (m - 1) / b * b}) {
+    gs = std::max(gs, gemm_an_scratch_bytes(rows, n, Lp, esz));
+    gs = std::max(gs, gemm_at_scratch_bytes(rows, n, Lp, rows, esz));
+  }
+  if (host) L.apply_scratch_bytes = gs;
   L.gemm_scratch_bytes = gs;
   L.gemm_scratch = take(gs);
   L.gram_chunks = (int)std::max(orth_gram_slots(m, Lp), orth_gram_slots(n, Lp));
@@ -253,7 +256,7 @@ OrthWorkT<T> orth_work(brsvd_handle h) {
   w.Rinv = h->at<T>(h->lay.Rinv);
   w.flags = h->at<int>(h->lay.flags);
   w.gemm_scratch = h->arena + h->lay.gemm_scratch;
-  w.gemm_scratch_bytes = h->lay.gemm_scratch_bytes;
+  w.gemm_scratch_bytes = h->lay.apply_scratch_bytes;
   w.tsqr_work = h->arena + h->lay.tsqr;
   w.tsqr_bytes = h->lay.tsqr_bytes;
   return w;
@@ -442,7 +445,7 @@ int enqueue_brsvd(brsvd_handle h, const T* A, int64_t lda, const T* Omega, T* U,
   hipStream_t cs = h->compute;
   OrthWorkT<T> ow = orth_work<T>(h);
   void* scr = h->arena + h->lay.gemm_scratch;
-  const uint64_t scr_bytes = h->lay.gemm_scratch_bytes;
+  const uint64_t scr_bytes = h->lay.apply_scratch_bytes;
 
   T* Xn = h->Pn<T>(0);    // current n x Lp panel (Omega, then W)
   T* Tn = h->Pn<T>(1);
@@ -554,7 +557,7 @@ int enqueue_alg2(brsvd_handle h, const T* A, int64_t lda, uint64_t seed, const T
   hipStream_t cs = h->compute;
   OrthWorkT<T> ow = orth_work<T>(h);
   void* scr = h->arena + h->lay.gemm_scratch;
-  const uint64_t scr_bytes = h->lay.gemm_scratch_bytes;
+  const uint64_t scr_bytes = h->lay.apply_scratch_bytes;
   T* Yn = h->Pn<T>(0);
   T* Pn1 = h->Pn<T>(1);
   T* OmI = h->Pm<T>(0);     // b x Lp windows of the two m x Lp panels

@@ -230,6 +230,25 @@ def test_nothing_in_the_workspace_has_to_be_cleared(m, n, k, p, f64, method):
     assert all(torch.equal(a, b) and bool(torch.isfinite(a).all()) for a, b in zip(*out))
 
 
+@pytest.mark.parametrize("m,n,l,block", [(8199, 187, 184, 8025), (9056, 274, 185, 4022)])
+def test_row_block_changes_no_bit_of_a_resident_svd(m, n, l, block):
+    """A in device memory is not walked in blocks by brsvd_run, so the row block may not show in the result.  These are sizes where the scratch of
+    that block's products has room for one more piece of a panel's product with an l x l factor than the scratch of A's own."""
+    dev = need_gpu()
+    print(f"[case] row blocks {m} x {n} l={l}", flush=True)
+    A = synth.gaussian(m, n, 71).to(dev)
+    Om = synth.gaussian(n, l, 72).to(dev)
+    out = []
+    for b in (512, block, m):
+        h = B.brsvd_create(B.make_params(m, n, l - 3, 3, 1, row_block=b))
+        try:
+            out.append(B.brsvd_run(h, A, Om)[:3])
+        finally:
+            B.brsvd_destroy(h)
+    for other in out[1:]:
+        assert all(torch.equal(x, y) for x, y in zip(out[0], other))
+
+
 def test_timing_levels():
     """timing_level 1 times the pass kernels and the whole call only; the results do not depend on it."""
     dev = need_gpu()
