@@ -483,7 +483,7 @@ int enqueue_brsvd(brsvd_handle h, const T* A, int64_t lda, const T* Omega, T* U,
     auto orth_m = [&](bool last) -> int {
       Region r(h, CAT_ORTH, cs, !h->host_a);
       if (last) {
-        BRSVD_TRY(orth_basis<T>(Ym, Tm, m, l, Lp, method, ow, leftQ, Rtot, false, &Q, cs));
+        BRSVD_TRY(orth_basis<T>(Ym, Tm, m, l, Lp, method, ow, leftQ, Rtot, false, true, &Q, cs));
         res = Q.panel;
       } else {
         BRSVD_TRY(orth_panel<T>(Ym, Tm, m, l, Lp, method, false, ow, nullptr, &res, cs));
@@ -521,7 +521,7 @@ int enqueue_brsvd(brsvd_handle h, const T* A, int64_t lda, const T* Omega, T* U,
   // thin QR of B^T, the small SVD, the lifts
   {
     Region r(h, CAT_ORTH, cs, !h->host_a);
-    BRSVD_TRY(orth_basis<T>(Xn, Tn, n, l, Lp, method, ow, h->at<T>(h->lay.Rinv), Rtot, true, &W, cs));
+    BRSVD_TRY(orth_basis<T>(Xn, Tn, n, l, Lp, method, ow, h->at<T>(h->lay.Rinv), Rtot, true, false, &W, cs));
     if (W.panel != Xn) std::swap(Xn, Tn);
   }
   T* XV = h->at<T>(h->lay.XV);
@@ -594,7 +594,7 @@ int enqueue_alg2(brsvd_handle h, const T* A, int64_t lda, uint64_t seed, const T
   }
   {
     Region r(h, CAT_ORTH, cs);
-    BRSVD_TRY(orth_basis<T>(Yn, Pn1, n, l, Lp, method, ow, h->at<T>(h->lay.leftQ), Rtot, false, &Q, cs));
+    BRSVD_TRY(orth_basis<T>(Yn, Pn1, n, l, Lp, method, ow, h->at<T>(h->lay.leftQ), Rtot, false, true, &Q, cs));
     if (Q.panel != Yn) std::swap(Yn, Pn1);
   }
   T* Cm = h->Pm<T>(0);
@@ -602,7 +602,7 @@ int enqueue_alg2(brsvd_handle h, const T* A, int64_t lda, uint64_t seed, const T
   BRSVD_TRY(pass_an<T>(h, A, lda, Yn, Cm, false, true));                 // second sweep: C = A Q
   {
     Region r(h, CAT_ORTH, cs);
-    BRSVD_TRY(orth_basis<T>(Cm, Tm, m, l, Lp, method, ow, h->at<T>(h->lay.Rinv), Rtot, true, &W, cs));
+    BRSVD_TRY(orth_basis<T>(Cm, Tm, m, l, Lp, method, ow, h->at<T>(h->lay.Rinv), Rtot, true, false, &W, cs));
     if (W.panel != Cm) std::swap(Cm, Tm);
   }
   T* XV = h->at<T>(h->lay.XV);
@@ -1370,7 +1370,7 @@ int brsvd_orth(float* P, int64_t rows, int32_t l, int32_t method, double* R, int
       // before any kernel: a scratch that is no device memory, or ends too early, is refused here
       if (hipMemsetAsync(w.flags, 0, 256, s) != hipSuccess) { status = BRSVD_ERR_HIP; break; }
       if (!as_is && (status = pad_panel(P, rows, l, P0, Lp, s)) != BRSVD_OK) break;
-      if ((status = orth_basis(as_is ? P : P0, P1, rows, l, Lp, m_now, w, left, Rtot, R != nullptr, &Q, s)) != BRSVD_OK) break;
+      if ((status = orth_basis(as_is ? P : P0, P1, rows, l, Lp, m_now, w, left, Rtot, R != nullptr, false, &Q, s)) != BRSVD_OK) break;
       if (Q.R2 && (status = triu_mul(Q.R2, Q.R1, l, Lp, Rtot, s)) != BRSVD_OK) break;
       int flag = 0;
       if (hipMemcpyAsync(&flag, w.flags, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess ||

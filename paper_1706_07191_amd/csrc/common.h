@@ -179,7 +179,7 @@ struct OrthWorkT {
   double* R[2];        // upper-triangular factors of the two CholeskyQR sweeps (stride Lp)
   T* Rinv;             // Lp x Lp zero-padded inverse factor in the panels' type (right operand of the apply GEMM)
   bool G_of_panel = false;   // G is already the Gram matrix of the panel that is orthonormalised next (an_gram)
-  int* flags;          // device: [0] = breakdown flag (0 = none, else 1 + column)
+  int* flags;          // device: [0] = breakdown flag (0 = none, else 1 + column), [1] = the last basis was far from orthonormal (orth_basis)
   void* gemm_scratch;
   uint64_t gemm_scratch_bytes;
   void* tsqr_work;     // TSQR scratch; otherwise partial Gram sums
@@ -214,7 +214,7 @@ int orth_panel(T* P, T* tmp, int64_t rows, int l, int Lp, int method, bool final
                double* Rtot, T** result, hipStream_t stream);
 // The same for a basis that reaches the output, with the last l x l factor left to the caller: the orthonormal basis of P is panel * left (left
 // null: the panel itself), and with want_R P = panel * R1, left^-1 = R2 (null if left is).  left: room for an Lp x Lp factor; Rtot: for
-// an fp64 one, used with want_R only.
+// an fp64 one, used with want_R only.  settle: panel is next to orthonormal by itself; w.Rinv and w.flags[1] are used for it.
 template <typename T>
 struct Basis {
   T* panel;
@@ -222,8 +222,8 @@ struct Basis {
   const double *R1, *R2;
 };
 template <typename T>
-int orth_basis(T* P, T* tmp, int64_t rows, int l, int Lp, int method, OrthWorkT<T>& w, T* left, double* Rtot, bool want_R, Basis<T>* out,
-               hipStream_t stream);
+int orth_basis(T* P, T* tmp, int64_t rows, int l, int Lp, int method, OrthWorkT<T>& w, T* left, double* Rtot, bool want_R, bool settle,
+               Basis<T>* out, hipStream_t stream);
 // Pieces shared between the CholeskyQR and the Householder-tree routes (orth.hip, tsqr.hip).
 template <typename T>
 int cholqr_sweeps(T* P, T* tmp, int64_t rows, int l, int Lp, int nsweeps, OrthWorkT<T>& w, double* Rtot,

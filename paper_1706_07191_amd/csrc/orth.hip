@@ -212,7 +212,9 @@ k_gram(const T* __restrict__ P, int64_t rows, int Lp, int64_t rows_per_chunk, do
 // and R^-1 = I - N, to the orders |E|_F^3 and |E|_F^2.  R^-1 is rounded to the panels' precision, R stays in fp64.  Taken where |E|_F is at most
 // `near_eye` (near_eye_of).  Measured, elimination and this with R (us): l = 20 8.0 and 4.0, 72 21 and 7.0, 97 30 and 11, 110 31 and 11, 160 62 and
 // 29, 272 192 and 97, 400 526 and 255; without R 7.6 and 3.4, 21 and 4.7, 28 and 7.3, 30 and 6.2, 58 and 12, 177 and 28, 494 and 61.
+// far_inv: if |E|_F is above kFarFromEye, R^-1 goes there, the identity into its own place and 1 into flag[1], otherwise 0 (see k_apply_far).
 constexpr int kNB = 16;
+constexpr double kFarFromEye = 0.1;
 constexpr int kCholLdsMaxLp = 128;    // largest padded size whose fp64 matrix fits the LDS
 
 // Row strides (in doubles): 16 modulo 32 puts the four rows a wave reads at once on distinct banks; the matrix of
@@ -301,7 +303,7 @@ __device__ __forceinline__ bool chol_diag_wave(doublex4& D, doublex4& E, const d
 template <bool IN_LDS, bool FACTORED, typename TO>
 __global__ void __launch_bounds__(1024)
 k_chol_inv(double* __restrict__ G, int l, int Lp, double* __restrict__ Rout, TO* __restrict__ Rinv_out,
-           int* __restrict__ flag, double tol, int lenient, double near_eye) {
+           int* __restrict__ flag, double tol, int lenient, double near_eye, TO* __restrict__ far_inv) {
   extern __shared__ double smem[];
   __shared__ int bad;
   __shared__ double off_eye[16];
@@ -346,6 +348,15 @@ k_chol_inv(double* __restrict__ G, int l, int Lp, double* __restrict__ Rout, TO*
     __syncthreads();
     e2 = 0.0;
     for (int w = 0; w < nw; ++w) e2 += off_eye[w];
+    if (far_inv) {
+      const bool far = !(e2 <= kFarFromEye * kFarFromEye);
+      if (tid == 0) flag[1] = far;
+      if (far) {
+        for (int idx = tid; idx < Lp * Lp; idx += blockDim.x) far_inv[idx] = TO(0);
+        for (int i = tid; i < l; i += blockDim.x) Rinv_out[(int64_t)i * Lp + i] = TO(1);
+        Rinv_out = far_inv;
+      }
+    }
     if (e2 <= near_eye * near_eye) {  // (not when it is NaN)
       const bool second = Rout && e2 > 1.6e-17;            // otherwise H is less than a rounding
       auto n_at = [&](int i, int j) {
@@ -629,7 +640,7 @@ static int gram(const T* P, int64_t rows, int Lp, OrthWorkT<T>& w, hipStream_t s
 // otherwise such a pivot raises the breakdown flag and ends the kernel.
 template <typename TO>
 static int chol_inv(double* G, int l, int Lp, double* Rout, TO* Rinv, int* flags, double tol, hipStream_t stream,
-                    int factored = 0, int lenient = 0, double near_eye = 0.0) {
+                    int factored = 0, int lenient = 0, double near_eye = 0.0, TO* far_inv = nullptr) {
   const bool in_lds = Lp <= kCholLdsMaxLp;
   const size_t lds = chol_lds_bytes(Lp, in_lds);
   // a step has at most one panel tile per wave up to 16 column tiles; two tiles leave work for four waves only
@@ -639,7 +650,7 @@ static int chol_inv(double* G, int l, int Lp, double* Rout, TO* Rinv, int* flags
       BRSVD_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds));
       *attr_set = true;
     }
-    hipLaunchKernelGGL(kern, dim3(1), dim3(threads), lds, stream, G, l, Lp, Rout, Rinv, flags, tol, lenient, near_eye);
+    hipLaunchKernelGGL(kern, dim3(1), dim3(threads), lds, stream, G, l, Lp, Rout, Rinv, flags, tol, lenient, near_eye, far_inv);
     BRSVD_HIP_TRY(hipGetLastError());
     return BRSVD_OK;
   };
@@ -881,6 +892,64 @@ int apply_panel(const T* P, int64_t rows, int Lp, const T* X, T* out, int64_t ld
 template int apply_panel<float>(const float*, int64_t, int, const float*, float*, int64_t, int, void*, uint64_t, hipStream_t);
 template int apply_panel<double>(const double*, int64_t, int, const double*, double*, int64_t, int, void*, uint64_t, hipStream_t);
 
+// P <- P X for X upper triangular, in place, if *far is set.  A wave takes 16 rows into LDS and all columns from there, one tile of 16 after the
+// other.  What bounds it: mostly the launch, as *far is not set (us: 2000x32 2.2, 20000x112 and 2073600x32 3.9); where it is, a wave's loads of X
+// (2073600x32 254, 20000x112 24, 100000x272 347, fp64 15872x80 18; in the SVD of a matrix of rank 2, q = 1, against the two applications of a basis
+// that is always orthonormalised twice: 2073600x100 l = 20 1676 and 1843, 20000x5000 l = 110 1535 and 1627, 100000x4000 l = 272 9495 and 9826).
+template <typename T>
+__global__ void __launch_bounds__(64)
+k_apply_far(T* P, int64_t rows, int Lp, const T* __restrict__ X, const int* __restrict__ far) {
+  if (*far == 0) return;
+  extern __shared__ __align__(16) char far_smem[];
+  T* place = (T*)far_smem;
+  const int LD = Lp + 16 / (int)sizeof(T), lane = threadIdx.x, r = lane & 15, g = lane >> 4;
+  constexpr int V = 16 / sizeof(T);
+  typedef T vec __attribute__((ext_vector_type(V)));
+  for (int64_t row0 = (int64_t)blockIdx.x * 16; row0 < rows; row0 += (int64_t)gridDim.x * 16) {
+    const int n = (int)min((int64_t)16, rows - row0), units = Lp / V;
+    T* p = P + row0 * Lp;
+    __syncthreads();
+    for (int u = lane; u < 16 * units; u += 64) {
+      const int i = u / units;
+      *(vec*)(place + i * LD + (u - i * units) * V) = *(const vec*)(p + (int64_t)min(i, n - 1) * Lp + (u - i * units) * V);
+    }
+    __syncthreads();
+    for (int c0 = 0; c0 < Lp; c0 += 16) {
+      typename std::conditional<sizeof(T) == 8, doublex4, floatx4>::type acc = {0, 0, 0, 0};
+      for (int k0 = 0; k0 <= c0; k0 += 16) {
+        T a[4], b[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          a[q] = place[r * LD + k0 + 4 * q + g];
+          b[q] = X[(int64_t)(k0 + 4 * q + g) * Lp + c0 + r];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if constexpr (sizeof(T) == 8) acc = mfma_f64(a[q], b[q], acc);
+          else acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q], b[q], acc, 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int i = sizeof(T) == 8 ? g + 4 * v : 4 * g + v;
+        if (i < n) p[(int64_t)i * Lp + c0 + r] = acc[v];
+      }
+    }
+  }
+}
+template <typename T>
+static int apply_far(T* P, int64_t rows, int Lp, const T* X, const int* far, hipStream_t stream) {
+  static bool attr_set = false;
+  if (!attr_set) {
+    BRSVD_HIP_TRY(hipFuncSetAttribute((const void*)k_apply_far<T>, hipFuncAttributeMaxDynamicSharedMemorySize, 16 * (kMaxL * (int)sizeof(T) + 16)));
+    attr_set = true;
+  }
+  const int64_t wgs = std::min<int64_t>(ceil_div(rows, 16), 2048);
+  hipLaunchKernelGGL(k_apply_far<T>, dim3((unsigned)wgs), dim3(64), 16 * (Lp * sizeof(T) + 16), stream, P, rows, Lp, X, far);
+  BRSVD_HIP_TRY(hipGetLastError());
+  return BRSVD_OK;
+}
+
 template <typename T>
 int apply_to_companion(OrthWorkT<T>& w, int Lp, hipStream_t stream) {
   if (!w.comp) return BRSVD_OK;
@@ -972,10 +1041,14 @@ int orth_panel(T* P, T* tmp, int64_t rows, int l, int Lp, int method, bool final
 
 // The second sweep of CholeskyQR, G2 = Q1^T Q1 = R2^T R2, without its pass over the panel Q2 = Q1 R2^-1: everything that follows is a product of Q1
 // with an l x l factor or a product from the left that R2^-1 can be multiplied to afterwards.  R2 is close to the identity (where a pivot was
-// clamped, to a diagonal matrix times a well-conditioned one), so nothing is lost by taking R2^-1 to the other side.
+// clamped, to a diagonal matrix times a well-conditioned one), so little is lost by taking R2^-1 to the other side.
+// settle: of a basis Q that A is multiplied by.  A column of Q1 whose pivot was clamped is rounding, and as much along the columns before it as
+// across them; A^T Q1 then holds A's largest values there, and their rounding stays when R2^-1 takes them out: zero singular values came out as
+// 1e-7 to 9e-7 of the largest (fp64 8e-16 to 2e-14) in the place of 4e-8 (7e-17) at most.  So Q1 <- Q1 R2^-1 and left = I after all where Q1 is far
+// from orthonormal.
 template <typename T>
-int orth_basis(T* P, T* tmp, int64_t rows, int l, int Lp, int method, OrthWorkT<T>& w, T* left, double* Rtot, bool want_R, Basis<T>* out,
-               hipStream_t stream) {
+int orth_basis(T* P, T* tmp, int64_t rows, int l, int Lp, int method, OrthWorkT<T>& w, T* left, double* Rtot, bool want_R, bool settle,
+               Basis<T>* out, hipStream_t stream) {
   if (rows < l) return BRSVD_ERR_ARG;
   out->panel = nullptr;
   if (method == BRSVD_ORTH_TSQR) {
@@ -994,7 +1067,9 @@ int orth_basis(T* P, T* tmp, int64_t rows, int l, int Lp, int method, OrthWorkT<
     BRSVD_TRY(cholqr_sweeps<T>(P, tmp, rows, l, Lp, 1, w, nullptr, &out->panel, stream, false, want_R));
     BRSVD_TRY(gram<T>(out->panel, rows, Lp, w, stream));
   }
-  BRSVD_TRY(chol_inv<T>(w.G, l, Lp, want_R ? w.R[1] : nullptr, left, w.flags, kPivotTol, stream, 0, 0, near_eye_of<T>(l)));
+  BRSVD_TRY(chol_inv<T>(w.G, l, Lp, want_R ? w.R[1] : nullptr, left, w.flags, kPivotTol, stream, 0, 0, near_eye_of<T>(l),
+                        settle ? w.Rinv : nullptr));
+  if (settle) BRSVD_TRY(apply_far<T>(out->panel, rows, Lp, w.Rinv, w.flags + 1, stream));
   out->left = left;
   out->R1 = want_R ? w.R[0] : nullptr;
   out->R2 = want_R ? w.R[1] : nullptr;
@@ -1007,7 +1082,8 @@ int orth_basis(T* P, T* tmp, int64_t rows, int l, int Lp, int method, OrthWorkT<
   template int cholqr_sweeps<T>(T*, T*, int64_t, int, int, int, OrthWorkT<T>&, double*, T**, hipStream_t, bool, \
                                 bool);                                                                          \
   template int orth_panel<T>(T*, T*, int64_t, int, int, int, bool, OrthWorkT<T>&, double*, T**, hipStream_t);   \
-  template int orth_basis<T>(T*, T*, int64_t, int, int, int, OrthWorkT<T>&, T*, double*, bool, Basis<T>*, hipStream_t);
+  template int orth_basis<T>(T*, T*, int64_t, int, int, int, OrthWorkT<T>&, T*, double*, bool, bool, Basis<T>*, \
+                                hipStream_t);
 BRSVD_ORTH_INSTANTIATE(float)
 BRSVD_ORTH_INSTANTIATE(double)
 #undef BRSVD_ORTH_INSTANTIATE

@@ -49,6 +49,33 @@ def test_open_bases(k, p, q, f64, full):
     assert abs(f["err"] - f["err_oracle"]) <= tol, (f, tol)
 
 
+@pytest.mark.parametrize("m,n,l", [(5000, 52, 32), (3000, 700, 30), (901, 1100, 100), (5000, 700, 144), (2100, 1900, 400)])
+@pytest.mark.parametrize("rank", [1, 3])
+@pytest.mark.parametrize("f64", [False, True])
+def test_matrices_of_lower_rank_than_the_sketch(m, n, l, rank, f64):
+    """The first factor of a sketch of lower rank than its width leaves columns of rounding that are far from orthogonal to the others.  What
+    they give as singular values has to be the rounding of an orthonormal basis, so the second factor goes over the panel there."""
+    dev = need_gpu()
+    print(f"[case] rank {rank} of {l}, {m} x {n} f64={f64}", flush=True)
+    dt, eps = (torch.float64, 2.0 ** -53) if f64 else (torch.float32, 2.0 ** -24)
+    worst = 0.0
+    for seed in range(3):
+        g = torch.Generator().manual_seed(seed)
+        A = (torch.randn(m, rank, generator=g, dtype=torch.float64) @ torch.randn(rank, n, generator=g, dtype=torch.float64)).to(dt).to(dev)
+        Om = torch.randn(n, l, generator=g, dtype=dt).to(dev)
+        Om2 = torch.randn(m, l, generator=g, dtype=dt).to(dev)
+        h = B.brsvd_create(B.make_params(m, n, l - 2, 2, 1, row_block=1000, dtype=B.BRSVD_DTYPE_F64 if f64 else B.BRSVD_DTYPE_F32))
+        try:
+            for S in (B.brsvd_run(h, A, Om)[1], B.brsvd_run_alg2(h, A, l, Omega=Om2)[1]):
+                worst = max(worst, float(S[rank] / S[0]) / eps)
+        finally:
+            B.brsvd_destroy(h)
+    note(f"[lower rank {m}x{n} l={l} rank={rank} f64={f64}] {worst:.2f}")
+    # a column that is orthogonal to the range of A meets the rounding of its own numbers, which a sum over the rows averages: less than one
+    # rounding of the largest value (with the second factor always over the panel 0.1 to 0.6 of it)
+    assert worst <= 1
+
+
 @pytest.mark.parametrize("l", [15, 16, 17, 128, 129])
 @pytest.mark.parametrize("spread", [1.0, 1e3])
 def test_second_factor_on_both_sides_of_the_line(l, spread):
