@@ -199,6 +199,20 @@ def test_caller_owned_workspace():
         assert ei.value.status == B.BRSVD_ERR_BUDGET
 
 
+@pytest.mark.parametrize("host", [False, True])
+def test_a_workspace_in_host_memory_is_refused(host):
+    """brsvd_create clears a few bytes of the workspace, which the runtime refuses for pageable host memory: no kernel ever sees it."""
+    need_gpu()
+    par = dict(row_block=400, a_location=B.BRSVD_A_HOST_PINNED if host else B.BRSVD_A_DEVICE)
+    need = B.brsvd_workspace_bytes(B.make_params(900, 700, 20, 10, 1, **par))
+    ws = torch.zeros(need + 256, dtype=torch.uint8)
+    at = -ws.data_ptr() % 256
+    with pytest.raises(B.BrsvdError) as ei:
+        B.brsvd_create(B.make_params(900, 700, 20, 10, 1, workspace=ws[at:at + need], **par))
+    B.lib().hipGetLastError()                        # the runtime's own record of the refused call
+    assert ei.value.status == B.BRSVD_ERR_HIP and not bool(ws.any())
+
+
 @pytest.mark.parametrize("m,n,k,p", [(900, 700, 20, 10), (1200, 900, 100, 10), (1300, 1100, 256, 16), (5000, 60, 16, 4)])
 @pytest.mark.parametrize("f64", [False, True])
 @pytest.mark.parametrize("method", [B.BRSVD_ORTH_AUTO, B.BRSVD_ORTH_TSQR])
