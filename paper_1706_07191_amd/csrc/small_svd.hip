@@ -46,15 +46,17 @@ __device__ __forceinline__ double rcp_nr(double x) {
 }
 
 // Sweeps end when a whole sweep met no pair with |cos| above kSettled: all cosines are then of the order
-// l * kSettled^2 after that sweep's rotations (quadratic convergence), below the rotation threshold, so
+// l * kSettled^2 after that sweep's rotations (quadratic convergence), of the order of rounding, so
 // a further sweep that would only confirm it is not run.
 // With results delivered in single precision the bar is lower: a last sweep whose largest cosine was below
 // kSettledF32 leaves cosines of the order l * kSettledF32^2 = 1e-8, an order of magnitude below what the fp32
 // lifts U = Q V_R and V = W_B U_R can show, and that saves one sweep of the seven to eight an l of 100 to 300 takes.
-// Row rotations of more than 16 rows skip pairs whose cosine is below kTolRows (a skipped rotation saves its traffic).  On up to 16 rows
-// a rotation costs hardly more than its inner products (1 %), and everything above rounding is rotated.  On the 32 x 32 Gram matrix it
-// costs the same whether it turns or not: there is no bar.
-constexpr double kTolRows = 1e-13, kTolOneBlock = 1e-16;
+// Row rotations turn everything above rounding: what is left counts times s_i / s_j in U = R V / s.  (A bar of 1e-13 from 33 rows on, whose skipped
+// rotations save their traffic, left V of fp64 runs with l = 40 off by 7e-12 at a condition of 64 and 3e-8 at 1e6, now 2e-14 and 5e-11, and of fp32
+// runs on sketches of lower rank than their width by 7e-5, now 5e-7; small SVD of SVD runs, with it and now, us: fp32 l = 33 136 and 139, 40 158 and
+// 158, 48 179 and 179, fp64 151 and 154, 173 and 176, 197 and 203.)  On the 32 x 32 Gram matrix a rotation costs the same whether it turns or not:
+// there is no bar.
+constexpr double kTolRows = 1e-16;
 constexpr double kSettled = 1e-8;
 constexpr double kSettledF32 = 1e-5;
 // In the last sweeps most block pairs have nothing left to rotate.  One is left as it is, for the price of its Gram matrix, when the inner
@@ -934,7 +936,7 @@ int small_svd(const double* R, int ldr, int l, int Lp, SvdWork& w, const int* br
     auto kern = nblk == 1 ? k_jacobi_rows<1, 8> : l <= 40 ? k_jacobi_rows<3, 24> : k_jacobi_rows<3, 32>;
     const int threads = LPP * (nblk == 1 ? 8 : l <= 40 ? 24 : 32);
     hipLaunchKernelGGL(kern, dim3(1), dim3(threads), (size_t)l * l * sizeof(double), stream, R, ldr, l, Lp, w.W, w.sig, w.info,
-                       breakdown_flag, nblk == 1 ? kTolOneBlock : kTolRows, settled);
+                       breakdown_flag, kTolRows, settled);
     BRSVD_HIP_TRY(hipGetLastError());
   } else if (l <= kJN) {
     hipLaunchKernelGGL(k_jacobi_small, dim3(1), dim3(kJThreads), jacobi_lds_bytes(Lp), stream, R, ldr, l, Lp, w.W, w.sig, w.info,

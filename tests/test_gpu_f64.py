@@ -11,7 +11,7 @@ from tests.gpu_util import need_gpu, note
 pytestmark = pytest.mark.gpu
 
 # Both sides compute in fp64; they differ in summation order, in the orthonormaliser (CholeskyQR2 against
-# Householder) and in the small SVD (one-sided Jacobi with rotation threshold 1e-13 against LAPACK), so
+# Householder) and in the small SVD (one-sided Jacobi with rotation threshold 1e-16 against LAPACK), so
 # agreement is limited by eps64 times the condition of the sketch panels, and the orthogonality of V =
 # W_B (R V_R / sigma) by the Jacobi threshold times sigma_1 / sigma_l (a few hundred here): observed
 # sigma 4e-15 .. 4e-14, U 2e-13 .. 7e-13, V 1e-12 .. 2e-11, reconstruction errors equal to 15 digits.

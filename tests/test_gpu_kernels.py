@@ -191,7 +191,7 @@ def test_small_svd_jacobi(l):
     assert np.max(np.abs(S - s_true) / s_true) < 1e-9
     assert np.all(np.diff(S) <= 0)
     assert np.linalg.norm((Ur * S) @ Vr.T - R) < 1e-11 * np.linalg.norm(R)
-    # Ur = R Vr diag(1/s): its error is the Jacobi tolerance (1e-13) times cond(R) = 1e6
+    # Ur = R Vr diag(1/s): its error is below 1e-13 times cond(R) = 1e6
     assert np.linalg.norm(Ur.T @ Ur - np.eye(l), 2) < 5e-7
     assert np.linalg.norm(Vr.T @ Vr - np.eye(l), 2) < 1e-10
     assert 1 <= sweeps <= 20 or l == 1

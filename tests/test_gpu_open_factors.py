@@ -6,7 +6,7 @@ import torch
 
 import paper_1706_07191_amd as B
 from oracle import brsvd_oracle as O
-from tests.gpu_util import check_against_oracle, need_gpu, note
+from tests.gpu_util import ORTH_TOL, check_against_oracle, need_gpu, note
 
 pytestmark = pytest.mark.gpu
 
@@ -49,7 +49,7 @@ def test_open_bases(k, p, q, f64, full):
     assert abs(f["err"] - f["err_oracle"]) <= tol, (f, tol)
 
 
-@pytest.mark.parametrize("m,n,l", [(5000, 52, 32), (3000, 700, 30), (901, 1100, 100), (5000, 700, 144), (2100, 1900, 400)])
+@pytest.mark.parametrize("m,n,l", [(5000, 52, 32), (3000, 700, 30), (3000, 700, 40), (901, 1100, 100), (5000, 700, 144), (2100, 1900, 400)])
 @pytest.mark.parametrize("rank", [1, 3])
 @pytest.mark.parametrize("f64", [False, True])
 def test_matrices_of_lower_rank_than_the_sketch(m, n, l, rank, f64):
@@ -66,8 +66,10 @@ def test_matrices_of_lower_rank_than_the_sketch(m, n, l, rank, f64):
         Om2 = torch.randn(m, l, generator=g, dtype=dt).to(dev)
         h = B.brsvd_create(B.make_params(m, n, l - 2, 2, 1, row_block=1000, dtype=B.BRSVD_DTYPE_F64 if f64 else B.BRSVD_DTYPE_F32))
         try:
-            for S in (B.brsvd_run(h, A, Om)[1], B.brsvd_run_alg2(h, A, l, Omega=Om2)[1]):
+            for U, S, Vt, _ in (B.brsvd_run(h, A, Om), B.brsvd_run_alg2(h, A, l, Omega=Om2)):
                 worst = max(worst, float(S[rank] / S[0]) / eps)
+                if not f64:
+                    assert O.orth_defect(U.double().cpu().numpy()) <= ORTH_TOL and O.orth_defect(Vt.double().cpu().numpy().T) <= ORTH_TOL
         finally:
             B.brsvd_destroy(h)
     note(f"[lower rank {m}x{n} l={l} rank={rank} f64={f64}] {worst:.2f}")
